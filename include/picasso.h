@@ -442,6 +442,12 @@ int picasso_f2f_backward(picasso_ctx* ctx, void* stream, const float* d_gy, cons
                          const int32_t* d_poff, int32_t F, int32_t P, int32_t C, const float* d_w, float* d_gtex,
                          float* d_gw);
 
+/* Zeroes the rows of d_gtex [P,C] that picasso_f2f_backward leaves untouched: those in front of the first facet's
+ * points and behind the last facet's (all rows if the last offset is below the first).  For callers whose
+ * d_gtex is uninitialised (clearing all of it would write the whole array twice); queued in front of that call. */
+int picasso_f2f_clear_unowned(picasso_ctx* ctx, void* stream, const int32_t* d_poff, int32_t F, int32_t P, int32_t C,
+                              float* d_gtex);
+
 /* Facet2vertex (Sec. 4.2, last equation): per channel I_v = (1 / |N(v)|) sum over the
  * corners at v of (sum_t pi_ft w_t) J_f; a vertex without facets gets 0.
  * d_y [F,C], d_pi [F,T], d_w [T,C] -> d_x [N,C]. */

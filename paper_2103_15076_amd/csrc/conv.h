@@ -3,14 +3,22 @@
 // facet2vertex with Gaussian-mixture fuzzy coefficients; supplementary section
 // "Backward propagations of different convolutions").
 //
-// Features are fp32 [rows, C] row-major; one lane owns VEC consecutive channels
-// of one output row, so neighbouring lanes read neighbouring addresses.  Sums
-// over a vertex's facets run over its corners in ascending order (the corner
+// Features are fp32 [rows, C] row-major; one lane owns four consecutive channels of one row (RowMap in
+// pooling.h: any channel count, any 4-byte aligned address), so neighbouring lanes read neighbouring
+// addresses.  Sums over a vertex's facets run over its corners in ascending order (the corner
 // CSR), filter gradients are reduced in two fixed stages; there are no fp
 // atomics, so results do not depend on scheduling.
+//
+// What bounds these kernels, apart from the feature rows' bytes, is the memory pipeline of a compute unit (16 bytes
+// for each of 64 lanes take it 16 cycles, whether they come from memory or all from one cached word): indices,
+// levels and coefficients are therefore fetched once per item, one item per lane, and handed to the lanes of a row
+// through LDS, the filter stays in registers or LDS, several rows are gathered per lane before the first is
+// used, and one pass makes every gradient of a direction.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "pooling.h"
 
@@ -20,25 +28,43 @@ namespace conv {
 
 using pool::BLOCK;
 using pool::Pack;
-using pool::load_pack;
-using pool::store_pack;
+using pool::RowLane;
+using pool::RowMap;
+using pool::arrived;
+using pool::at;
+using pool::row_at;
+using pool::load_row;
+using pool::row_lane;
+using pool::store_row;
 
 // Index arrays come from the caller.  They are checked once, where the corner lists are built
 // (corner_keys_kernel reports a bad index); the kernels below only make sure that a bad one
 // cannot reach outside the arrays: it is read as index 0.
 __device__ __forceinline__ int in_range_or_zero(int i, int n) { return ((unsigned)i < (unsigned)n) ? i : 0; }
 
-// Workgroups are handed to the 8 accelerator dies in turn, and each die has its own L2.  The facet
-// rows that neighbouring vertices gather overlap (mesh numbering has locality), so the facet2vertex
-// forward kernel deals its work out in 8 contiguous parts, one per die: workgroup b works as
-// number (b % 8) * (G / 8) + b / 8 of a grid of G workgroups, G a multiple of 8 (xcd_grid).
-__device__ __forceinline__ long long xcd_block() {
+// Workgroups are handed to the 8 accelerator dies in turn, and each die has its own L2.  The rows that
+// neighbouring vertices and facets gather overlap (mesh numbering has locality), so the kernels deal their work
+// out in 8 contiguous parts, one per die: workgroup b works as number (b % 8) * (G / 8) + b / 8 of a
+// grid of G workgroups, G a multiple of 8 (otherwise as number b).
+__device__ __forceinline__ int xcd_block() {
+    if (gridDim.x & 7u) return (int)blockIdx.x;
     const unsigned g8 = gridDim.x >> 3;
-    return (long long)(blockIdx.x & 7u) * g8 + (blockIdx.x >> 3);
+    return (int)((blockIdx.x & 7u) * g8 + (blockIdx.x >> 3));
 }
-inline int xcd_grid(long long threads) {
-    const long long g = (threads + BLOCK - 1) / BLOCK;
-    return (int)((g + 7) / 8 * 8 > 0 ? (g + 7) / 8 * 8 : 8);
+inline dim3 xcd_grid(dim3 g) { return dim3((g.x + 7) / 8 * 8, g.y); }
+
+// The two indexes off[v], off[v + 1] and the three of a facet in one load each.
+struct __attribute__((packed, aligned(4))) Int2 { int a, b; };
+struct __attribute__((packed, aligned(4))) Int3 { int a, b, c; };
+__device__ __forceinline__ Int2 load_pair(const int* p) { return *reinterpret_cast<const Int2*>(p); }
+__device__ __forceinline__ Int3 load_triple(const int* p) { return *reinterpret_cast<const Int3*>(p); }
+
+// x / n for r = 1 / n: the quotient corrected by its own remainder and fixed up for the special cases, which
+// rounds like a division (short of subnormal quotients) at a third of its instructions; used where one
+// n divides several values.
+__device__ __forceinline__ float quotient(float x, float n, float r) {
+    const float q = x * r;
+    return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-q, n, x), r, q), n, x);
 }
 
 // ---------------------------------------------------------------------------
@@ -199,163 +225,333 @@ __device__ __forceinline__ void lattice_moments(int k, float& a_minus_b, float& 
     b = (n - 1.0f) / (12.0f * n);
 }
 
-template <int VEC>
+// LDS written by the lanes of a wave is read by others of the same wave from here on.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+// A wave takes `per_wave` consecutive facets: their vertices and moments go to LDS, one facet per lane, then the wave's lanes
+// make the facets' rows, rw of them side by side.  (64 channels, 1.9 M facets: 214 us with the indices and the
+// filter loaded per row.)
+constexpr int V2F_UNROLL = 2;
+// At most 64; few enough that all waves of the chip get some.
+inline int facets_per_wave(const RowMap& m, long long F) {
+    const long long turn = (long long)m.rw * V2F_UNROLL;
+    return (int)std::min<long long>(64, std::max<long long>(m.rw, F / (8192 * turn) * turn));
+}
+template <int KIND>
 __global__ __launch_bounds__(BLOCK) void v2f_forward_kernel(const float* __restrict__ x, int N, int C,
                                                             const int* __restrict__ facets, int F,
                                                             const int* __restrict__ level,
-                                                            const float* __restrict__ w, float* __restrict__ y) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int f = (int)(idx / Q), q = (int)(idx % Q);
-    if (f >= F) return;
-    float amb, b;
-    lattice_moments(level ? level[f] : 1, amb, b);
-    const size_t co = (size_t)q * VEC;
-    Pack<VEC> xs[3], ws[3];
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        xs[s] = load_pack<VEC>(x + (size_t)in_range_or_zero(facets[3 * (size_t)f + s], N) * C + co);
-        ws[s] = load_pack<VEC>(w + (size_t)s * C + co);
-    }
-    Pack<VEC> out;
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) {
-        const float dot = (ws[0].v[k] * xs[0].v[k] + ws[1].v[k] * xs[1].v[k]) + ws[2].v[k] * xs[2].v[k];
-        const float wsum = (ws[0].v[k] + ws[1].v[k]) + ws[2].v[k];
-        const float xsum = (xs[0].v[k] + xs[1].v[k]) + xs[2].v[k];
-        out.v[k] = amb * dot + b * (wsum * xsum);
-    }
-    store_pack<VEC>(y + (size_t)f * C + co, out);
-}
-
-// dJ/dI_s = (M w)_s = (a - b) w_s + b sum_r w_r (supplementary, vertex2facet kernel), summed over
-// the corners of the vertex in ascending order.
-template <int VEC>
-__global__ __launch_bounds__(BLOCK) void v2f_backward_x_kernel(const float* __restrict__ gy, int C,
-                                                               const int* __restrict__ level,
-                                                               const float* __restrict__ w,
-                                                               const int* __restrict__ off,
-                                                               const int* __restrict__ corners, int N, int H,
-                                                               float* __restrict__ gx) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int v = (int)(idx / Q), q = (int)(idx % Q);
-    if (v >= N) return;
-    const size_t co = (size_t)q * VEC;
-    Pack<VEC> ws[3], wsum, acc;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) ws[s] = load_pack<VEC>(w + (size_t)s * C + co);
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) {
-        wsum.v[k] = (ws[0].v[k] + ws[1].v[k]) + ws[2].v[k];
-        acc.v[k] = 0.0f;
-    }
-    const int jb = max(off[v], 0), je = min(off[v + 1], H);
-    for (int j = jb; j < je; ++j) {
-        const int i = in_range_or_zero(corners[j], H);
-        const int f = i / 3, s = i - 3 * f;
+                                                            const float* __restrict__ w, float* __restrict__ y,
+                                                            int per_wave, RowMap map) {
+    __shared__ int4 sv[BLOCK];
+    __shared__ float2 sm[BLOCK];
+    const RowLane l = row_lane(map, blockIdx.y);
+    const int w0 = wave_id() * 64, lane = (int)threadIdx.x & 63;
+    const int base = (xcd_block() * (BLOCK / 64) + wave_id()) * per_wave, n = min(per_wave, F - base);
+    if (n <= 0) return;
+    if (lane < n) {
+        const Int3 v = load_triple(row_at<KIND>(facets, base + lane, 3, 0));
+        sv[w0 + lane] = make_int4(in_range_or_zero(v.a, N), in_range_or_zero(v.b, N), in_range_or_zero(v.c, N), 0);
         float amb, b;
-        lattice_moments(level ? level[f] : 1, amb, b);
-        const Pack<VEC> g = load_pack<VEC>(gy + (size_t)f * C + co);
+        lattice_moments(level ? *at<KIND>(level, base + lane) : 1, amb, b);
+        sm[w0 + lane] = make_float2(amb, b);
+    }
+    wave_sync();
+    if (!l.on) return;
+    const int c0 = 4 * l.q, left = C - c0;
+    Pack ws[3], wsum;
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            const float wk = s == 0 ? ws[0].v[k] : (s == 1 ? ws[1].v[k] : ws[2].v[k]);
-            acc.v[k] = acc.v[k] + g.v[k] * (amb * wk + b * wsum.v[k]);
+    for (int s = 0; s < 3; ++s) ws[s] = load_row<KIND>(row_at<KIND>(w, s, C, c0), left);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) wsum.v[i] = (ws[0].v[i] + ws[1].v[i]) + ws[2].v[i];
+    for (int i0 = l.r; i0 < n; i0 += map.rw * V2F_UNROLL) {
+        Pack xs[V2F_UNROLL][3];
+#pragma unroll
+        for (int u = 0; u < V2F_UNROLL; ++u) {  // (rows behind the last load that one again)
+            const int4 v = sv[w0 + min(i0 + u * map.rw, n - 1)];
+            xs[u][0] = load_row<KIND>(row_at<KIND>(x, v.x, C, c0), left);
+            xs[u][1] = load_row<KIND>(row_at<KIND>(x, v.y, C, c0), left);
+            xs[u][2] = load_row<KIND>(row_at<KIND>(x, v.z, C, c0), left);
+        }
+#pragma unroll
+        for (int u = 0; u < V2F_UNROLL; ++u)
+#pragma unroll
+            for (int s = 0; s < 3; ++s) arrived(xs[u][s]);
+#pragma unroll
+        for (int u = 0; u < V2F_UNROLL; ++u) {
+            const int i1 = i0 + u * map.rw;
+            if (i1 < n) {
+                const float2 m = sm[w0 + i1];
+                Pack out;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float dot = fmaf(ws[2].v[i], xs[u][2].v[i], fmaf(ws[1].v[i], xs[u][1].v[i], ws[0].v[i] * xs[u][0].v[i]));
+                    const float xsum = (xs[u][0].v[i] + xs[u][1].v[i]) + xs[u][2].v[i];
+                    out.v[i] = fmaf(m.x, dot, m.y * (wsum.v[i] * xsum));
+                }
+                store_row<KIND>(row_at<KIND>(y, base + i1, C, c0), out, left);
+            }
         }
     }
-    store_pack<VEC>(gx + (size_t)v * C + co, acc);
 }
 
 // ---------------------------------------------------------------------------
-// Filter gradients: a sum over all rows (facets) of ROWS values per channel, in
-// two fixed stages.  Stage 1: workgroup g sums the rows [g * chunk, (g + 1) *
-// chunk); lane (r, q) of it takes every R-th row of the chunk for channel pack
-// q (a launch covers up to BLOCK packs), then the R lanes of a pack are summed in LDS in a fixed tree.  Stage 2
-// adds the workgroups' partial sums in ascending order.
+// A wave's walk over `n` (at most 64) rows from row0 on, each a range of items [off[row], off[row + 1]): the corners of
+// a vertex, the texture points of a facet.  The items' small data (Op::stage) are fetched 64 at a time, one item per
+// lane, into the wave's LDS window.  2^split lane groups share a row's items (WalkMap), each taking every 2^split-th of
+// them from the window, UNROLL at a time: Op::load starts the gather of an item's feature row, Op::use adds it up.
+// Op::end makes the row from a group's sums; sums over a row's groups go through GroupSum.  Every sum has a fixed order.
+// Offsets are clipped to [0, n_items]; soff holds 65 ints of the wave's own.
 // ---------------------------------------------------------------------------
-template <int ROWS, int VEC, class Term>
-__global__ __launch_bounds__(BLOCK) void reduce_rows_stage1_kernel(Term term, int n_rows, int C, int chunk,
-                                                                   float* __restrict__ partial, int q0, int Q) {
-    extern __shared__ float lds[];  // [BLOCK][ROWS * VEC]
-    // this launch takes the channel packs q0 .. q0 + Q - 1, Q <= BLOCK (the host makes as many launches as
-    // the channels need)
-    const int R = BLOCK / Q;
-    const int r = threadIdx.x / Q, q = q0 + threadIdx.x % Q;
-    float acc[ROWS * VEC];
+constexpr int WALK_WINDOW = 64;
+constexpr int WALK_WAVE_ROWS = 64;
+struct WalkMap {
+    RowMap row;
+    int split, rows, per_wave;  // rows side by side in a wave, rows of a wave's walk
+};
+// So that a step's items about fill the window (`average` items per row) and, where rows differ in length, no
+// group walks alone for long; and walks as long as keep all waves busy.
+inline WalkMap walk_map(int C, long long n_rows, double average) {
+    WalkMap m;
+    m.row = pool::row_map(C);
+    m.split = 0;
+    while (m.split < 3 && (m.row.rw >> (m.split + 1)) >= 1 && (m.row.rw >> m.split) * average > 48.0) ++m.split;
+    m.rows = m.row.rw >> m.split;
+    const long long most = std::max(1, 32 / m.rows), busy = n_rows / (8192ll * m.rows);
+    m.per_wave = m.rows * (int)std::max<long long>(1, std::min(most, busy));
+    return m;
+}
+
+struct GroupSum {
+    int split, qc;
+    __device__ __forceinline__ float operator()(float v) const {  // valid in a row's first group
+        for (int d = 1 << split >> 1; d > 0; d >>= 1) v += __shfl_down(v, (unsigned)(d * qc), 64);
+        return v;
+    }
+    __device__ __forceinline__ void operator()(Pack& p) const {
 #pragma unroll
-    for (int k = 0; k < ROWS * VEC; ++k) acc[k] = 0.0f;
-    const int begin = blockIdx.x * chunk;
-    const int end = begin + chunk < n_rows ? begin + chunk : n_rows;
-    if (r < R)
-        for (int f = begin + r; f < end; f += R) term.template add<VEC>(f, q, acc);
+        for (int i = 0; i < 4; ++i) p.v[i] = (*this)(p.v[i]);
+    }
+};
+
+template <int KIND, int UNROLL, class Op>
+__device__ __forceinline__ void walk_rows(Op& op, const int* __restrict__ off, int row0, int n, int n_items, const WalkMap& map,
+                                          const RowLane& l, int* soff) {
+    const int lane = (int)threadIdx.x & 63;
+    const int r = l.r >> map.split, sub = l.r & ((1 << map.split) - 1);
+    const bool on_row = l.on && r < map.rows;
+    const GroupSum sum{map.split, map.row.qc};
+    wave_sync();
+    for (int i = lane; i <= n; i += 64) soff[i] = min(max(*at<KIND>(off, row0 + i), 0), n_items);
+    wave_sync();
+    const int last = __builtin_amdgcn_readfirstlane(soff[n]);
+    int w0 = 0, w1 = 0;  // the items in the window
+    for (int g = 0; g < n; g += map.rows) {
+        const bool on = on_row && g + r < n;
+        const int s = soff[min(g + r, n)], e = on ? soff[min(g + r + 1, n)] : s;
+        const int ge = __builtin_amdgcn_readfirstlane(soff[min(g + map.rows, n)]);
+        int from = __builtin_amdgcn_readfirstlane(soff[g]);
+        op.begin(row0 + g + r, on, e - s);
+        for (;;) {
+            if (!(w0 <= from && ge <= w1)) {
+                wave_sync();
+                if (from + lane < last) op.stage(lane, from + lane);
+                w0 = from;
+                w1 = from + WALK_WINDOW;
+                wave_sync();
+            }
+            const int end = min(e, w1), step = 1 << map.split;
+            for (int j = max(s, from) + sub; j < end; j += step * UNROLL) {
 #pragma unroll
-    for (int k = 0; k < ROWS * VEC; ++k) lds[(size_t)threadIdx.x * (ROWS * VEC) + k] = (r < R) ? acc[k] : 0.0f;
+                for (int u = 0; u < UNROLL; ++u) op.load(u, min(j + u * step, end - 1) - w0, min(j + u * step, end - 1));
+#pragma unroll
+                for (int u = 0; u < UNROLL; ++u) op.wait(u);
+#pragma unroll
+                for (int u = 0; u < UNROLL; ++u)
+                    if (j + u * step < end) op.use(u, j + u * step - w0, j + u * step);
+            }
+            if (ge <= w1) break;
+            from = w1;
+        }
+        op.end(row0 + g + r, on, on && sub == 0, sum);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Filter gradients: a sum over all rows (facets, or vertices) per channel, in two fixed stages.  Stage 1, at
+// the end of the kernels below: workgroup g has taken the rows [g * chunk, (g + 1) * chunk), each lane some
+// of them for its channel pack, summing in registers; the lanes of a pack are now summed within the waves and over
+// them in a fixed tree, row by row of the gradient, and left in partial[g][rows][C].  Stage 2 adds the workgroups' partial sums.
+// ---------------------------------------------------------------------------
+// A facet's fuzzy coefficients of `rows` components (facet2vertex below), 4 (NP - 1) < rows <= 4 NP, in NP slots of four: with NP > 1
+// the last four slots hold the last four components (one 16-byte load each, without a branch), so that some of
+// them hold a component a second time; such slots are left out (slot_used; uniform, so a scalar branch).
+template <int NP>
+__device__ __forceinline__ int slot_component(int slot, int rows) {
+    return NP == 1 || slot < 4 * (NP - 1) ? slot : rows - 4 * NP + slot;
+}
+template <int NP>
+__device__ __forceinline__ bool slot_used(int slot, int rows) {
+    if (NP == 1) return slot < rows;
+    return slot < 4 * (NP - 1) || slot >= 4 * NP - (rows - 4 * (NP - 1));
+}
+template <int KIND, int NP, int ROWS>
+__device__ __forceinline__ void rows_to_partial(const float (&acc)[ROWS][4], int rows, const RowMap& map, const RowLane& l,
+                                                int C, float4* lds /* [2][BLOCK] */, float* __restrict__ partial) {
+    const int wave = wave_id(), lq = l.q - (int)blockIdx.y * map.qc;
+    int top = 1;  // smallest power of two >= rw
+    while (top < map.rw) top <<= 1;
     __syncthreads();
-    // lanes r = 0 .. R-1 of pack q sit at threads r * Q + q: halve the number of live r each step
-    for (int live = R; live > 1;) {
-        const int half = (live + 1) >> 1;
-        if (r < live - half) {
+    int turn = 0;
 #pragma unroll
-            for (int k = 0; k < ROWS * VEC; ++k)
-                lds[(size_t)threadIdx.x * (ROWS * VEC) + k] =
-                    lds[(size_t)threadIdx.x * (ROWS * VEC) + k] + lds[(size_t)(threadIdx.x + half * Q) * (ROWS * VEC) + k];
+    for (int row = 0; row < ROWS; ++row) {
+        if (slot_used<NP>(row, rows)) {  // (the same in all lanes)
+            float t[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) t[k] = l.on ? acc[row][k] : 0.0f;
+            for (int d = top >> 1; d > 0; d >>= 1) {  // the wave's rows
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float o = __shfl_down(t[k], (unsigned)(d * map.qc), 64);
+                    if (l.r + d < map.rw) t[k] += o;
+                }
+            }
+            float4* buf = lds + (turn & 1) * BLOCK;  // (two in turn: a barrier per row of the gradient)
+            if (l.on && l.r == 0) buf[wave * 64 + lq] = make_float4(t[0], t[1], t[2], t[3]);
+            __syncthreads();
+            if (wave == (turn & (BLOCK / 64 - 1)) && l.on && l.r == 0) {
+                const float4 a = buf[lq], b = buf[64 + lq], c = buf[128 + lq], d = buf[192 + lq];
+                const Pack out{{(a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y), (a.z + b.z) + (c.z + d.z), (a.w + b.w) + (c.w + d.w)}};
+                store_row<KIND>(partial + ((size_t)blockIdx.x * rows + slot_component<NP>(row, rows)) * C + 4 * l.q, out,
+                                C - 4 * l.q);
+            }
+            ++turn;
         }
-        __syncthreads();
-        live = half;
-    }
-    if (r == 0) {
-#pragma unroll
-        for (int row = 0; row < ROWS; ++row)
-#pragma unroll
-            for (int k = 0; k < VEC; ++k)
-                partial[((size_t)blockIdx.x * ROWS + row) * C + (size_t)q * VEC + k] =
-                    lds[(size_t)threadIdx.x * (ROWS * VEC) + row * VEC + k];
     }
 }
 
-// out[row][c] = sum over the workgroups' partials, rows < rows_used: one wave per output value,
-// lane l adds the groups l, l + 64, ... in ascending order, then the 64 lanes are added in a fixed
-// butterfly.
-__global__ __launch_bounds__(BLOCK) void reduce_rows_stage2_kernel(const float* __restrict__ partial, int groups,
-                                                                   int rows, int rows_used, int C,
+// out[i] = sum over the workgroups' partials of value i of `width`: one wave per value, lane l adds the groups l,
+// l + 64, ... (eight loads in flight), then the 64 lanes are added in a fixed butterfly.
+__global__ __launch_bounds__(BLOCK) void reduce_rows_stage2_kernel(const float* __restrict__ partial, int groups, int width,
                                                                    float* __restrict__ out) {
     const int lane = threadIdx.x & 63;
-    const int idx = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
-    if (idx >= rows_used * C) return;  // (whole waves leave together)
-    const int row = idx / C, c = idx % C;
+    const int i = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
+    if (i >= width) return;  // (whole waves leave together)
     float acc = 0.0f;
-    for (int g = lane; g < groups; g += 64) acc = acc + partial[((size_t)g * rows + row) * C + c];
+    for (int g0 = lane; g0 < groups; g0 += 64 * 8) {
+        float t[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t[j] = g0 + 64 * j < groups ? partial[(size_t)(g0 + 64 * j) * width + i] : 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc = acc + t[j];
+    }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) acc = acc + __shfl_xor(acc, d, 64);
-    if (lane == 0) out[(size_t)row * C + c] = acc;
+    if (lane == 0) out[i] = acc;
 }
 
-// dJ/dw_s = (M I)_s = (a - b) I_s + b sum_r I_r, times the incoming gradient (supplementary,
-// vertex2facet kernel): the three rows of gw.
-struct V2fWeightTerm {
+// Backward pass of vertex2facet (supplementary, vertex2facet kernel): dJ/dI_s = (M w)_s = (a - b) w_s + b sum_r
+// w_r and dJ/dw_s = (M I)_s = (a - b) I_s + b sum_r I_r.  Both follow from the same two sums over the corners of
+// a vertex, A_s = sum of (a - b) g over its corners in place s of their facets and B = sum of b g:
+//   gx_v = sum_s w_s A_s + (sum_s w_s) B,   gw_s = sum_v x_v (A_s + B),
+// so one walk over the corner lists, which gathers the facets' gradients once, makes both gradients.
+// (Two passes before, gw summed over the facets from three gathered vertex rows each.)
+template <int KIND>
+struct V2fBackwardOp {
+    static constexpr int UNROLL = 3;
     const float* gy;
-    const float* x;
-    const int* facets;
     const int* level;
-    int C, N;
-    template <int VEC>
-    __device__ __forceinline__ void add(int f, int q, float* acc) const {
-        const size_t co = (size_t)q * VEC;
+    const int* corners;
+    float* gx;
+    const float* x;  // null: no filter gradient
+    int C, c0, left, H;
+    int2* win_f;     // [WALK_WINDOW] facet, place of the corner in it
+    float2* win_m;   // [WALK_WINDOW] moments of the facet's level
+    Pack ws[3], wsum, g[UNROLL];
+    float A[3][4], B[4], gw[3][4];
+    __device__ void stage(int slot, int j) {
+        const int i = in_range_or_zero(*at<KIND>(corners, j), H), f = i / 3;
         float amb, b;
-        lattice_moments(level ? level[f] : 1, amb, b);
-        const Pack<VEC> g = load_pack<VEC>(gy + (size_t)f * C + co);
-        Pack<VEC> xs[3];
+        lattice_moments(level ? *at<KIND>(level, f) : 1, amb, b);
+        win_f[slot] = make_int2(f, i - 3 * f);
+        win_m[slot] = make_float2(amb, b);
+    }
+    __device__ void begin(int, bool, int) {
 #pragma unroll
-        for (int s = 0; s < 3; ++s)
-            xs[s] = load_pack<VEC>(x + (size_t)in_range_or_zero(facets[3 * (size_t)f + s], N) * C + co);
+        for (int i = 0; i < 4; ++i) A[0][i] = A[1][i] = A[2][i] = B[i] = 0.0f;
+    }
+    __device__ void load(int u, int slot, int) { g[u] = load_row<KIND>(row_at<KIND>(gy, win_f[slot].x, C, c0), left); }
+    __device__ void wait(int u) { arrived(g[u]); }
+    __device__ void use(int u, int slot, int) {
+        const float2 m = win_m[slot];
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            const float xsum = (xs[0].v[k] + xs[1].v[k]) + xs[2].v[k];
+        for (int i = 0; i < 4; ++i) B[i] = fmaf(m.y, g[u].v[i], B[i]);
+        if (m.x != 0.0f) {  // (a facet of level 1, nearly every one, has a = b)
+            const int s = win_f[slot].y;
 #pragma unroll
-            for (int s = 0; s < 3; ++s) acc[s * VEC + k] = acc[s * VEC + k] + g.v[k] * (amb * xs[s].v[k] + b * xsum);
+            for (int p = 0; p < 3; ++p) {
+                const float a = s == p ? m.x : 0.0f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) A[p][i] = fmaf(a, g[u].v[i], A[p][i]);
+            }
+        }
+    }
+    __device__ void end(int v, bool on, bool first, const GroupSum& sum) {
+        if (gx) {
+            Pack out;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                out.v[i] = fmaf(wsum.v[i], B[i], fmaf(ws[2].v[i], A[2][i], fmaf(ws[1].v[i], A[1][i], ws[0].v[i] * A[0][i])));
+            sum(out);
+            if (first) store_row<KIND>(row_at<KIND>(gx, v, C, c0), out, left);
+        }
+        if (x && on) {
+            const Pack xv = load_row<KIND>(row_at<KIND>(x, v, C, c0), left);
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) gw[s][i] = fmaf(xv.v[i], A[s][i] + B[i], gw[s][i]);
         }
     }
 };
+
+// Workgroup b walks over the vertices of its chunk, map.per_wave of them per wave and turn.
+template <int KIND>
+__global__ __launch_bounds__(BLOCK) void v2f_backward_kernel(const float* __restrict__ gy, const float* __restrict__ x, int C,
+                                                             const int* __restrict__ level,
+                                                             const float* __restrict__ w,
+                                                             const int* __restrict__ off,
+                                                             const int* __restrict__ corners, int N, int H, int chunk,
+                                                             float* __restrict__ gx,
+                                                             float* __restrict__ partial, WalkMap map) {
+    __shared__ int2 win_f[BLOCK / 64 * WALK_WINDOW];
+    __shared__ float2 win_m[BLOCK / 64 * WALK_WINDOW];
+    __shared__ int soff[BLOCK / 64][WALK_WAVE_ROWS + 1];
+    __shared__ float4 lds[2 * BLOCK];
+    const RowLane l = row_lane(map.row, blockIdx.y);
+    const int wave = wave_id();
+    V2fBackwardOp<KIND> op;
+    op.gy = gy; op.level = level; op.corners = corners; op.gx = gx; op.x = partial ? x : nullptr;
+    op.C = C; op.c0 = 4 * l.q; op.left = C - op.c0; op.H = H;
+    op.win_f = win_f + wave * WALK_WINDOW; op.win_m = win_m + wave * WALK_WINDOW;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        op.ws[s] = l.on ? load_row<KIND>(row_at<KIND>(w, s, C, op.c0), op.left) : Pack{};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) op.gw[s][i] = 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) op.wsum.v[i] = (op.ws[0].v[i] + op.ws[1].v[i]) + op.ws[2].v[i];
+    const int begin = min(xcd_block() * chunk, N), end = min(begin + chunk, N);
+    for (int v = begin + wave * map.per_wave; v < end; v += map.per_wave * (BLOCK / 64))
+        walk_rows<KIND, V2fBackwardOp<KIND>::UNROLL>(op, off, v, min(map.per_wave, end - v), H, map, l, soff[wave]);
+    if (partial) rows_to_partial<KIND, 1>(op.gw, 3, map.row, l, C, lds, partial);
+}
 
 // ---------------------------------------------------------------------------
 // Facet2facet (Sec. 4.1, for meshes rendered with textures): every facet has
@@ -364,239 +560,456 @@ struct V2fWeightTerm {
 // sum_k W_k T_k.  Points of facet f = poff[f] .. poff[f+1]; tex [P,C], bary [P,3].
 // One lane owns VEC channels of one facet and walks the facet's points in order.
 // ---------------------------------------------------------------------------
-template <int VEC>
-__device__ __forceinline__ Pack<VEC> point_filter(const float* __restrict__ bary, const Pack<VEC>* ws, int k) {
-    const float x0 = bary[3 * (size_t)k], x1 = bary[3 * (size_t)k + 1], x2 = bary[3 * (size_t)k + 2];
-    Pack<VEC> wk;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) wk.v[i] = (x0 * ws[0].v[i] + x1 * ws[1].v[i]) + x2 * ws[2].v[i];
-    return wk;
+struct __attribute__((packed, aligned(4))) Float3 { float a, b, c; };
+template <int KIND>
+__device__ __forceinline__ Float3 load_bary(const float* __restrict__ bary, int k) {
+    return *reinterpret_cast<const Float3*>(row_at<KIND>(bary, k, 3, 0));
 }
 
-template <int VEC>
+template <int KIND>
+struct F2fForwardOp {
+    static constexpr int UNROLL = 4;
+    const float* tex;
+    const float* bary;
+    float* y;
+    int C, c0, left;
+    Float3* win;  // [WALK_WINDOW]
+    Pack ws[3], acc, t[UNROLL];
+    float n;
+    __device__ void stage(int slot, int k) { win[slot] = load_bary<KIND>(bary, k); }
+    __device__ void begin(int, bool, int count) {
+        acc = Pack{};
+        n = (float)count;
+    }
+    __device__ void load(int u, int, int k) { t[u] = load_row<KIND>(row_at<KIND>(tex, k, C, c0), left); }
+    __device__ void wait(int u) { arrived(t[u]); }
+    __device__ void use(int u, int slot, int) {
+        const Float3 xi = win[slot];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float wk = fmaf(xi.c, ws[2].v[i], fmaf(xi.b, ws[1].v[i], xi.a * ws[0].v[i]));
+            acc.v[i] = fmaf(wk, t[u].v[i], acc.v[i]);
+        }
+    }
+    __device__ void end(int f, bool, bool first, const GroupSum& sum) {
+        sum(acc);
+        if (!first) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc.v[i] = n > 0.0f ? acc.v[i] / n : 0.0f;
+        store_row<KIND>(row_at<KIND>(y, f, C, c0), acc, left);
+    }
+};
+
+template <int KIND>
 __global__ __launch_bounds__(BLOCK) void f2f_forward_kernel(const float* __restrict__ tex,
                                                             const float* __restrict__ bary,
                                                             const int* __restrict__ poff, int F, int P, int C,
-                                                            const float* __restrict__ w, float* __restrict__ y) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int f = (int)(idx / Q), q = (int)(idx % Q);
-    if (f >= F) return;
-    const size_t co = (size_t)q * VEC;
-    Pack<VEC> ws[3], acc;
+                                                            const float* __restrict__ w, 
+                                                            float* __restrict__ y, WalkMap map) {
+    __shared__ Float3 win[BLOCK / 64 * WALK_WINDOW];
+    __shared__ int soff[BLOCK / 64][WALK_WAVE_ROWS + 1];
+    const RowLane l = row_lane(map.row, blockIdx.y);
+    const int wave = wave_id();
+    const int f0 = (xcd_block() * (BLOCK / 64) + wave) * map.per_wave;
+    if (f0 >= F) return;
+    F2fForwardOp<KIND> op;
+    op.tex = tex; op.bary = bary; op.y = y; op.C = C; op.c0 = 4 * l.q; op.left = C - op.c0;
+    op.win = win + wave * WALK_WINDOW;
 #pragma unroll
-    for (int s = 0; s < 3; ++s) ws[s] = load_pack<VEC>(w + (size_t)s * C + co);
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) acc.v[i] = 0.0f;
-    const int kb = max(poff[f], 0), ke = min(poff[f + 1], P);
-    for (int k = kb; k < ke; ++k) {
-        const Pack<VEC> wk = point_filter<VEC>(bary, ws, k);
-        const Pack<VEC> t = load_pack<VEC>(tex + (size_t)k * C + co);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) acc.v[i] = acc.v[i] + wk.v[i] * t.v[i];
-    }
-    const float g = (float)(ke - kb);
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) acc.v[i] = (ke > kb) ? acc.v[i] / g : 0.0f;
-    store_pack<VEC>(y + (size_t)f * C + co, acc);
+    for (int s = 0; s < 3; ++s) op.ws[s] = l.on ? load_row<KIND>(row_at<KIND>(w, s, C, op.c0), op.left) : Pack{};
+    walk_rows<KIND, F2fForwardOp<KIND>::UNROLL>(op, poff, f0, min(map.per_wave, F - f0), P, map, l, soff[wave]);
 }
 
-// dJ/dT_k = W_k / Gamma_f, times the facet's incoming gradient: the same walk, one row written per point.
-template <int VEC>
-__global__ __launch_bounds__(BLOCK) void f2f_backward_tex_kernel(const float* __restrict__ gy,
-                                                                 const float* __restrict__ bary,
-                                                                 const int* __restrict__ poff, int F, int P, int C,
-                                                                 const float* __restrict__ w,
-                                                                 float* __restrict__ gtex) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int f = (int)(idx / Q), q = (int)(idx % Q);
-    if (f >= F) return;
-    const size_t co = (size_t)q * VEC;
-    Pack<VEC> ws[3];
+// Backward pass: dJ/dT_k = W_k / Gamma_f and dJ/dw_s = (1 / Gamma_f) sum_k xi_ks T_k, each times the facet's
+// incoming gradient.  Nothing is summed per facet, so the wave's rows are points, whatever their facets' sizes: a
+// wave takes per_wave facets at a time and their points 64 at a time, one lane finding a point's facet among
+// the offsets.  (Walking facet by facet left half of the lanes idle: 183 us at 1.8 M points, 32 channels.)
+template <int KIND>
+__global__ __launch_bounds__(BLOCK) void f2f_backward_kernel(const float* __restrict__ gy, const float* __restrict__ tex,
+                                                             const float* __restrict__ bary,
+                                                             const int* __restrict__ poff, int F, int P, int C,
+                                                             const float* __restrict__ w, int chunk, int per_wave,
+                                                             float* __restrict__ gtex, float* __restrict__ partial,
+                                                             RowMap map) {
+    __shared__ float4 sb[BLOCK];   // per point: barycentric coordinates, 1 / Gamma of its facet
+    __shared__ int2 sf[BLOCK];     // ... facet, Gamma
+    __shared__ int soff[BLOCK / 64][WALK_WAVE_ROWS + 1];
+    __shared__ float4 lds[2 * BLOCK];
+    const RowLane l = row_lane(map, blockIdx.y);
+    const int wave = wave_id(), w0 = wave * 64, lane = (int)threadIdx.x & 63;
+    const int c0 = 4 * l.q, left = C - c0;
+    Pack ws[3];
+    float gw[3][4] = {};
 #pragma unroll
-    for (int s = 0; s < 3; ++s) ws[s] = load_pack<VEC>(w + (size_t)s * C + co);
-    const Pack<VEC> g = load_pack<VEC>(gy + (size_t)f * C + co);
-    const int kb = max(poff[f], 0), ke = min(poff[f + 1], P);
-    const float n = (float)(ke - kb);
-    for (int k = kb; k < ke; ++k) {
-        Pack<VEC> wk = point_filter<VEC>(bary, ws, k);
+    for (int s = 0; s < 3; ++s) ws[s] = l.on ? load_row<KIND>(row_at<KIND>(w, s, C, c0), left) : Pack{};
+    const int begin = min(xcd_block() * chunk, F), end = min(begin + chunk, F);
+    for (int f0 = begin + wave * per_wave; f0 < end; f0 += per_wave * (BLOCK / 64)) {
+        const int n = min(per_wave, end - f0);
+        wave_sync();
+        for (int i = lane; i <= n; i += 64) soff[wave][i] = min(max(*at<KIND>(poff, f0 + i), 0), P);
+        wave_sync();
+        const int p_end = __builtin_amdgcn_readfirstlane(soff[wave][n]);
+        for (int p0 = __builtin_amdgcn_readfirstlane(soff[wave][0]); p0 < p_end; p0 += 64) {
+            const int np = min(64, p_end - p0);
+            wave_sync();
+            if (lane < np) {
+                int lo = 0, hi = n;  // soff[lo] <= p0 + lane < soff[hi]
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (soff[wave][mid] <= p0 + lane) lo = mid; else hi = mid;
+                }
+                const int count = soff[wave][lo + 1] - soff[wave][lo];
+                const Float3 xi = load_bary<KIND>(bary, p0 + lane);
+                sb[w0 + lane] = make_float4(xi.a, xi.b, xi.c, 1.0f / (float)count);
+                sf[w0 + lane] = make_int2(f0 + lo, count);
+            }
+            wave_sync();
+            for (int i = l.r; l.on && i < np; i += map.rw) {
+                const float4 xi = sb[w0 + i];
+                const int2 fc = sf[w0 + i];
+                const Pack g = load_row<KIND>(row_at<KIND>(gy, fc.x, C, c0), left);
+                const Pack t = partial ? load_row<KIND>(row_at<KIND>(tex, p0 + i, C, c0), left) : Pack{};
+                const float count = (float)fc.y;
+                Pack out;
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) wk.v[i] = (g.v[i] * wk.v[i]) / n;
-        store_pack<VEC>(gtex + (size_t)k * C + co, wk);
-    }
-}
-
-// dJ/dw_s = (1 / Gamma_f) sum_k xi_ks T_k, times the incoming gradient: the three rows of gw.
-struct F2fWeightTerm {
-    const float* gy;
-    const float* tex;
-    const float* bary;
-    const int* poff;
-    int C, P;
-    template <int VEC>
-    __device__ __forceinline__ void add(int f, int q, float* acc) const {
-        const size_t co = (size_t)q * VEC;
-        const int kb = max(poff[f], 0), ke = min(poff[f + 1], P);
-        if (ke <= kb) return;
-        const Pack<VEC> g = load_pack<VEC>(gy + (size_t)f * C + co);
-        float m[3 * VEC];
-#pragma unroll
-        for (int i = 0; i < 3 * VEC; ++i) m[i] = 0.0f;
-        for (int k = kb; k < ke; ++k) {
-            const Pack<VEC> t = load_pack<VEC>(tex + (size_t)k * C + co);
-#pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                const float x = bary[3 * (size_t)k + s];
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) m[s * VEC + i] = m[s * VEC + i] + x * t.v[i];
+                for (int k = 0; k < 4; ++k) {
+                    const float gn = quotient(g.v[k], count, xi.w), gt = gn * t.v[k];
+                    out.v[k] = gn * fmaf(xi.z, ws[2].v[k], fmaf(xi.y, ws[1].v[k], xi.x * ws[0].v[k]));
+                    gw[0][k] = fmaf(xi.x, gt, gw[0][k]);
+                    gw[1][k] = fmaf(xi.y, gt, gw[1][k]);
+                    gw[2][k] = fmaf(xi.z, gt, gw[2][k]);
+                }
+                if (gtex) store_row<KIND>(row_at<KIND>(gtex, p0 + i, C, c0), out, left);
             }
         }
-        const float n = (float)(ke - kb);
-#pragma unroll
-        for (int s = 0; s < 3; ++s)
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[s * VEC + i] = acc[s * VEC + i] + (g.v[i] * m[s * VEC + i]) / n;
     }
-};
+    if (partial) rows_to_partial<KIND, 1>(gw, 3, map, l, C, lds, partial);
+}
+
+// Zeroes the rows of gtex that belong to no facet (in front of the kernel above): every row from poff[0] to below
+// poff[F] is between two consecutive offsets, so these are the rows in front of the first and behind the last.
+__global__ __launch_bounds__(BLOCK) void f2f_clear_kernel(const int* __restrict__ poff, int F, int P, int C,
+                                                          float* __restrict__ gtex) {
+    long long head = (long long)min(max(poff[0], 0), P) * C;
+    const long long tail = (long long)min(max(poff[F], 0), P) * C;
+    const long long n = (long long)P * C, stride = (long long)gridDim.x * BLOCK, g = (long long)blockIdx.x * BLOCK + threadIdx.x;
+    if (tail < head) head = n;  // (offsets that descend: any row may belong to no facet)
+    for (long long i = g; i < head; i += stride) gtex[i] = 0.0f;
+    for (long long i = tail + g; i < n; i += stride) gtex[i] = 0.0f;
+}
 
 // ---------------------------------------------------------------------------
 // Facet2vertex (Sec. 4.2): I_v = (1 / |N(v)|) sum_{f in N(v)} (sum_t pi_ft w_t) J_f,
 // N(v) = the corners at v in ascending order.
 // ---------------------------------------------------------------------------
-template <int VEC>
-__device__ __forceinline__ Pack<VEC> fuzzy_filter(const float* __restrict__ pi, const float* __restrict__ w, int T,
-                                                  int C, int f, size_t co) {
-    Pack<VEC> coef;
+template <int NP>
+__device__ __forceinline__ void load_coefficients(float (&p)[4 * NP], const float* __restrict__ pi, int rows) {
+    if constexpr (NP == 1) {
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) coef.v[k] = 0.0f;
-    for (int t = 0; t < T; ++t) {
-        const float p = pi[(size_t)f * T + t];
-        const Pack<VEC> wt = load_pack<VEC>(w + (size_t)t * C + co);
+        for (int t = 0; t < 4; ++t) p[t] = pi[min(t, rows - 1)];
+    } else {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) coef.v[k] = coef.v[k] + p * wt.v[k];
+        for (int g = 0; g < NP; ++g) {
+            const Pack q = load_row<pool::ROW_EVEN>(g + 1 < NP ? pi + 4 * g : pi + (rows - 4), 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[4 * g + i] = q.v[i];
+        }
     }
-    return coef;
 }
 
-// W_IN_LDS: the filter (T x C floats, at most F2V_LDS_FLOATS) is copied to LDS first, so the T
-// reads per corner and lane do not go to memory.
-constexpr int F2V_LDS_FLOATS = 12288;
+// Up to 16 components: one running sum sum_f pi_ft J_f per component and channel in registers, the filter applied
+// once per vertex at the end (a sixth of the filter reads of applying it per corner).
+template <int NP, int KIND>
+struct F2vForwardOp {
+    static constexpr int UNROLL = NP <= 2 ? 3 : 2, TT = 4 * NP;  // (registers)
+    const float* y;
+    const float* pi;
+    const int* corners;
+    float* x;
+    int C, c0, left, H, T, lq;
+    int* win_f;      // [WALK_WINDOW] facet
+    float4* win_p;   // [NP][WALK_WINDOW] its coefficients
+    const float4* wl;  // [TT][64] filter
+    Pack yf[UNROLL];
+    float acc[TT][4], n;
+    __device__ void stage(int slot, int j) {
+        const int f = in_range_or_zero(*at<KIND>(corners, j), H) / 3;
+        win_f[slot] = f;
+        float p[TT];
+        load_coefficients<NP>(p, row_at<KIND>(pi, f, T, 0), T);
+#pragma unroll
+        for (int g = 0; g < NP; ++g) win_p[g * WALK_WINDOW + slot] = make_float4(p[4 * g], p[4 * g + 1], p[4 * g + 2], p[4 * g + 3]);
+    }
+    __device__ void begin(int, bool, int count) {
+        n = (float)count;
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[t][i] = 0.0f;
+    }
+    __device__ void load(int u, int slot, int) { yf[u] = load_row<KIND>(row_at<KIND>(y, win_f[slot], C, c0), left); }
+    __device__ void wait(int u) { arrived(yf[u]); }
+    __device__ void use(int u, int slot, int) {
+#pragma unroll
+        for (int g = 0; g < NP; ++g) {
+            const float4 p4 = win_p[g * WALK_WINDOW + slot];
+            const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (slot_used<NP>(4 * g + t, T))
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[4 * g + t][i] = fmaf(p[t], yf[u].v[i], acc[4 * g + t][i]);
+        }
+    }
+    __device__ void end(int v, bool, bool first, const GroupSum& sum) {
+        Pack out{};
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+            if (slot_used<NP>(t, T)) {
+                const float4 wt = wl[t * 64 + lq];
+                out.v[0] = fmaf(wt.x, acc[t][0], out.v[0]); out.v[1] = fmaf(wt.y, acc[t][1], out.v[1]);
+                out.v[2] = fmaf(wt.z, acc[t][2], out.v[2]); out.v[3] = fmaf(wt.w, acc[t][3], out.v[3]);
+            }
+        sum(out);
+        if (!first) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out.v[i] = n > 0.0f ? out.v[i] / n : 0.0f;
+        store_row<KIND>(row_at<KIND>(x, v, C, c0), out, left);
+    }
+};
 
-template <int VEC, bool W_IN_LDS>
+// The filter rows t0 .. t0 + rows - 1 of the channels this workgroup works on, in slots as above, to LDS.  By all
+// its threads; ends with a barrier.
+template <int NP, int KIND>
+__device__ __forceinline__ void filter_to_lds(float4* wl /* [4 NP][64] */, const float* __restrict__ w, int t0, int rows, int C,
+                                              const RowMap& map) {
+    const int q0 = blockIdx.y * map.qc, qn = min(map.qc, map.Q - q0);
+    for (int i = threadIdx.x; i < 4 * NP * 64; i += BLOCK) {
+        const int t = i >> 6, q = i & 63;
+        if (q >= qn || !slot_used<NP>(t, rows)) continue;
+        const Pack p = load_row<KIND>(w + (size_t)(t0 + slot_component<NP>(t, rows)) * C + 4 * (q0 + q), C - 4 * (q0 + q));
+        wl[i] = make_float4(p.v[0], p.v[1], p.v[2], p.v[3]);
+    }
+    __syncthreads();
+}
+
+template <int NP, int KIND>
 __global__ __launch_bounds__(BLOCK) void f2v_forward_kernel(const float* __restrict__ y, int C,
                                                             const float* __restrict__ pi, int T,
                                                             const float* __restrict__ w,
                                                             const int* __restrict__ off,
-                                                            const int* __restrict__ corners, int N, int H,
-                                                            float* __restrict__ x) {
-    extern __shared__ float wl[];
-    if (W_IN_LDS) {
-        for (int i = threadIdx.x; i < T * C; i += BLOCK) wl[i] = w[i];
-        __syncthreads();
-    }
-    const float* wsrc = W_IN_LDS ? wl : w;
-    const int Q = C / VEC;
-    const long long idx = xcd_block() * BLOCK + threadIdx.x;
-    const int v = (int)(idx / Q), q = (int)(idx % Q);
-    if (v >= N) return;
-    const size_t co = (size_t)q * VEC;
-    const int s = max(off[v], 0), e = min(off[v + 1], H);
-    Pack<VEC> acc;
+                                                            const int* __restrict__ corners, int N, int H, 
+                                                            float* __restrict__ x, WalkMap map) {
+    __shared__ float4 wl[4 * NP * 64];
+    __shared__ float4 win_p[BLOCK / 64 * NP * WALK_WINDOW];
+    __shared__ int win_f[BLOCK / 64 * WALK_WINDOW];
+    __shared__ int soff[BLOCK / 64][WALK_WAVE_ROWS + 1];
+    const RowLane l = row_lane(map.row, blockIdx.y);
+    const int wave = wave_id();
+    filter_to_lds<NP, KIND>(wl, w, 0, T, C, map.row);
+    const int v0 = (xcd_block() * (BLOCK / 64) + wave) * map.per_wave;
+    if (v0 >= N) return;
+    F2vForwardOp<NP, KIND> op;
+    op.y = y; op.pi = pi; op.corners = corners; op.x = x;
+    op.C = C; op.c0 = 4 * l.q; op.left = C - op.c0; op.H = H; op.T = T; op.lq = l.q - (int)blockIdx.y * map.row.qc;
+    op.win_f = win_f + wave * WALK_WINDOW; op.win_p = win_p + wave * NP * WALK_WINDOW; op.wl = wl;
+    walk_rows<KIND, F2vForwardOp<NP, KIND>::UNROLL>(op, off, v0, min(map.per_wave, N - v0), H, map, l, soff[wave]);
+}
+
+// sum_t pi_ft w_t of four channels, any number of components
+template <int KIND>
+__device__ __forceinline__ Pack fuzzy_filter(const float* __restrict__ pi, const float* __restrict__ w, int t0, int T, int C,
+                                             int c0, Pack coef) {
+    for (int t = t0; t < T; ++t) {
+        const float p = pi[t];
+        const Pack wt = load_row<KIND>(row_at<KIND>(w, t, C, c0), C - c0);
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) acc.v[k] = 0.0f;
+        for (int i = 0; i < 4; ++i) coef.v[i] = fmaf(p, wt.v[i], coef.v[i]);
+    }
+    return coef;
+}
+
+// More components than the registers of the kernel above hold: the filter is applied per corner.
+template <int KIND>
+__global__ __launch_bounds__(BLOCK) void f2v_forward_many_kernel(const float* __restrict__ y, int C,
+                                                                 const float* __restrict__ pi, int T,
+                                                                 const float* __restrict__ w,
+                                                                 const int* __restrict__ off,
+                                                                 const int* __restrict__ corners, int N, int H,
+                                                                 float* __restrict__ x, RowMap map) {
+    const RowLane l = row_lane(map, blockIdx.y);
+    const int v = pool::wave_row(map, xcd_block()) + l.r;
+    if (!l.on || v >= N) return;
+    const int c0 = 4 * l.q, left = C - c0;
+    const int s = max(off[v], 0), e = min(off[v + 1], H);
+    Pack acc{};
     for (int j = s; j < e; ++j) {
         const int f = in_range_or_zero(corners[j], H) / 3;
-        const Pack<VEC> coef = fuzzy_filter<VEC>(pi, wsrc, T, C, f, co);
-        const Pack<VEC> yf = load_pack<VEC>(y + (size_t)f * C + co);
+        const Pack yf = load_row<KIND>(row_at<KIND>(y, f, C, c0), left);
+        const Pack coef = fuzzy_filter<KIND>(row_at<KIND>(pi, f, T, 0), w, 0, T, C, c0, Pack{});
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) acc.v[k] = acc.v[k] + coef.v[k] * yf.v[k];
+        for (int i = 0; i < 4; ++i) acc.v[i] = fmaf(coef.v[i], yf.v[i], acc.v[i]);
     }
     const float n = (float)(e - s);
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) acc.v[k] = (e > s) ? acc.v[k] / n : 0.0f;
-    store_pack<VEC>(x + (size_t)v * C + co, acc);
+    for (int i = 0; i < 4; ++i) acc.v[i] = (e > s) ? acc.v[i] / n : 0.0f;
+    store_row<KIND>(row_at<KIND>(x, v, C, c0), acc, left);
 }
 
-// Incoming gradient of a facet's three vertices, each divided by its vertex's |N(v)|, summed.
-template <int VEC>
-__device__ __forceinline__ Pack<VEC> gathered_vertex_gradient(const float* __restrict__ gx,
-                                                              const int* __restrict__ facets,
-                                                              const int* __restrict__ off, int N, int C, int f,
-                                                              size_t co) {
-    Pack<VEC> g;
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) g.v[k] = 0.0f;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        const int v = in_range_or_zero(facets[3 * (size_t)f + s], N);
-        const float n = (float)(off[v + 1] - off[v]);
-        const Pack<VEC> gv = load_pack<VEC>(gx + (size_t)v * C + co);
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) g.v[k] = g.v[k] + gv.v[k] / n;
+// Sum over the lanes of one row (neighbours within a wave, at places 0 .. n - 1; this lane at place q of them),
+// valid in the row's first lane.
+__device__ __forceinline__ float row_sum(float v, int q, int n) {
+    for (int d = 1; d < n; d <<= 1) {
+        const float o = __shfl_down(v, d, 64);
+        if (q + d < n) v += o;
     }
-    return g;
+    return v;
 }
 
-// dI_v/dJ_f = (sum_t pi_ft w_t) / |N(v)| (supplementary, facet2vertex kernel), summed over the
-// facet's three corners.
-template <int VEC>
-__global__ __launch_bounds__(BLOCK) void f2v_backward_y_kernel(const float* __restrict__ gx, int C,
-                                                               const float* __restrict__ pi, int T,
-                                                               const float* __restrict__ w,
-                                                               const int* __restrict__ facets, int F,
-                                                               const int* __restrict__ off, int N,
-                                                               float* __restrict__ gy) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int f = (int)(idx / Q), q = (int)(idx % Q);
-    if (f >= F) return;
-    const size_t co = (size_t)q * VEC;
-    const Pack<VEC> coef = fuzzy_filter<VEC>(pi, w, T, C, f, co);
-    Pack<VEC> g = gathered_vertex_gradient<VEC>(gx, facets, off, N, C, f, co);
+// Backward pass of facet2vertex (supplementary, facet2vertex kernel).  With G = the incoming gradients of a
+// facet's three vertices, each divided by its |N(v)|, summed:
+//   gy_f = (sum_t pi_ft w_t) G,   gw_t = sum_f pi_ft (J_f G),   gpi_ft = sum over channels of w_t (J_f G),
+// so one pass over the facets, which gathers the vertices' gradients once, makes all three (one pass for each
+// before).  It takes the filter rows t0 .. t0 + rows - 1, rows <= 4 NP (slots as above); gy is made by the pass with t0 = 0, whose caller leaves
+// it null in the others.  GPI: a row's lanes lie in one wave (row_map's one_wave) and are summed there.  A wave
+// takes per_wave facets at a time, whose indices, counts and coefficients it brings to LDS, one facet per lane.
+template <int NP, int KIND, bool GPI>
+__global__ __launch_bounds__(BLOCK) void f2v_backward_kernel(const float* __restrict__ gx, const float* __restrict__ y, int C,
+                                                             const float* __restrict__ pi, int T, int t0, int rows,
+                                                             const float* __restrict__ w,
+                                                             const int* __restrict__ facets, int F,
+                                                             const int* __restrict__ off, int N, int chunk, int per_wave,
+                                                             float* __restrict__ gy, float* __restrict__ partial,
+                                                             float* __restrict__ gpi, RowMap map) {
+    constexpr int TT = 4 * NP;
+    __shared__ float4 wl[TT * 64 > 2 * BLOCK ? TT * 64 : 2 * BLOCK];
+    __shared__ int4 sv[BLOCK];         // per facet of the waves' batches: its vertices,
+    __shared__ float4 sn[BLOCK], sr[BLOCK];  // ... their |N(v)| and the reciprocals,
+    __shared__ float4 sp[NP * BLOCK];  // ... its coefficients
+    const RowLane l = row_lane(map, blockIdx.y);
+    const int c0 = 4 * l.q, left = C - c0, lq = l.q - (int)blockIdx.y * map.qc;
+    const int w0 = wave_id() * 64, lane = (int)threadIdx.x & 63;
+    filter_to_lds<NP, KIND>(wl, w, t0, rows, C, map);
+    float gw[TT][4] = {};
+    const int begin = min(xcd_block() * chunk, F), end = min(begin + chunk, F);
+    for (int base = begin + wave_id() * per_wave; base < end; base += per_wave * (BLOCK / 64)) {
+        const int n = min(per_wave, end - base);
+        wave_sync();
+        if (lane < n) {
+            const int f = base + lane;
+            const Int3 v = load_triple(row_at<KIND>(facets, f, 3, 0));
+            const int a = in_range_or_zero(v.a, N), b = in_range_or_zero(v.b, N), c = in_range_or_zero(v.c, N);
+            float p[TT];
+            load_coefficients<NP>(p, row_at<KIND>(pi, f, T, t0), rows);
+            const Int2 oa = load_pair(at<KIND>(off, a)), ob = load_pair(at<KIND>(off, b)), oc = load_pair(at<KIND>(off, c));
+            const float na = (float)(oa.b - oa.a), nb = (float)(ob.b - ob.a), nc = (float)(oc.b - oc.a);
+            sv[w0 + lane] = make_int4(a, b, c, 0);
+            sn[w0 + lane] = make_float4(na, nb, nc, 0.0f);
+            sr[w0 + lane] = make_float4(1.0f / na, 1.0f / nb, 1.0f / nc, 0.0f);
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) g.v[k] = coef.v[k] * g.v[k];
-    store_pack<VEC>(gy + (size_t)f * C + co, g);
-}
-
-// dI_v/dw_t = (1 / |N(v)|) sum_f pi_ft J_f: rows t0 .. t0 + ROWS - 1 of gw.
-template <int ROWS>
-struct F2vWeightTerm {
-    const float* gx;
-    const float* y;
-    const float* pi;
-    const int* facets;
-    const int* off;
-    int N, C, T, t0;
-    template <int VEC>
-    __device__ __forceinline__ void add(int f, int q, float* acc) const {
-        const size_t co = (size_t)q * VEC;
-        const Pack<VEC> g = gathered_vertex_gradient<VEC>(gx, facets, off, N, C, f, co);
-        const Pack<VEC> yf = load_pack<VEC>(y + (size_t)f * C + co);
+            for (int g = 0; g < NP; ++g) sp[g * BLOCK + w0 + lane] = make_float4(p[4 * g], p[4 * g + 1], p[4 * g + 2], p[4 * g + 3]);
+        }
+        wave_sync();
+        // (with GPI every lane runs every step, for the sums across a row's lanes)
+        for (int i0 = 0; i0 < n; i0 += map.rw) {
+            const int i = i0 + l.r, f = base + i, at_i = w0 + min(i, n - 1);
+            const bool on = l.on && i < n;
+            if (!GPI && !on) break;
+            Pack gv[3] = {}, yf{};
+            if (!GPI || on) {
+                const int4 v = sv[at_i];
+                gv[0] = load_row<KIND>(row_at<KIND>(gx, v.x, C, c0), left);
+                gv[1] = load_row<KIND>(row_at<KIND>(gx, v.y, C, c0), left);
+                gv[2] = load_row<KIND>(row_at<KIND>(gx, v.z, C, c0), left);
+                yf = load_row<KIND>(row_at<KIND>(y, f, C, c0), left);
+            }
+            const float4 nn = sn[at_i], rr = sr[at_i];
+            Pack g, h, coef{};
 #pragma unroll
-        for (int row = 0; row < ROWS; ++row) {
-            const float p = (t0 + row < T) ? pi[(size_t)f * T + t0 + row] : 0.0f;
+            for (int k = 0; k < 4; ++k) {
+                g.v[k] = (quotient(gv[0].v[k], nn.x, rr.x) + quotient(gv[1].v[k], nn.y, rr.y)) + quotient(gv[2].v[k], nn.z, rr.z);
+                h.v[k] = on ? yf.v[k] * g.v[k] : 0.0f;
+            }
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) acc[row * VEC + k] = acc[row * VEC + k] + p * (yf.v[k] * g.v[k]);
+            for (int gq = 0; gq < NP; ++gq) {
+                const float4 p4 = sp[gq * BLOCK + at_i];
+                const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+                for (int tq = 0; tq < 4; ++tq) {
+                    const int t = 4 * gq + tq;
+                    if (slot_used<NP>(t, rows)) {
+                        const float4 wt = wl[t * 64 + lq];
+                        coef.v[0] = fmaf(p[tq], wt.x, coef.v[0]); coef.v[1] = fmaf(p[tq], wt.y, coef.v[1]);
+                        coef.v[2] = fmaf(p[tq], wt.z, coef.v[2]); coef.v[3] = fmaf(p[tq], wt.w, coef.v[3]);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) gw[t][k] = fmaf(p[tq], h.v[k], gw[t][k]);
+                        if constexpr (GPI) {
+                            float d = fmaf(wt.w, h.v[3], fmaf(wt.z, h.v[2], fmaf(wt.y, h.v[1], wt.x * h.v[0])));
+                            d = row_sum(d, lq, map.Q);
+                            if (on && lq == 0) gpi[(size_t)f * T + t0 + slot_component<NP>(t, rows)] = d;
+                        }
+                    }
+                }
+            }
+            if (gy && on) {
+                if (T > rows) coef = fuzzy_filter<KIND>(row_at<KIND>(pi, f, T, 0), w, rows, T, C, c0, coef);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) coef.v[k] = coef.v[k] * g.v[k];
+                store_row<KIND>(row_at<KIND>(gy, f, C, c0), coef, left);
+            }
         }
     }
-};
+    if (partial) rows_to_partial<KIND, NP>(gw, rows, map, l, C, wl, partial);
+}
 
-// dI_v/dpi_ft = w_t J_f / |N(v)|, summed over channels and the facet's corners: one lane per (f, t).
+// gpi alone, where a row has more channels than a wave's lanes take at once: a wave per facet.
+template <int KIND>
 __global__ __launch_bounds__(BLOCK) void f2v_backward_pi_kernel(const float* __restrict__ gx, const float* __restrict__ y,
                                                                 int C, int T, const float* __restrict__ w,
                                                                 const int* __restrict__ facets, int F,
                                                                 const int* __restrict__ off, int N,
                                                                 float* __restrict__ gpi) {
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int f = (int)(idx / T), t = (int)(idx % T);
-    if (f >= F) return;
-    float acc = 0.0f;
-    for (int c = 0; c < C; ++c) {
-        const Pack<1> g = gathered_vertex_gradient<1>(gx, facets, off, N, C, f, (size_t)c);
-        acc = acc + w[(size_t)t * C + c] * (y[(size_t)f * C + c] * g.v[0]);
+    constexpr int TT = 8;
+    const int lane = threadIdx.x & 63;
+    const int f = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
+    if (f >= F) return;  // (whole waves leave together)
+    const Int3 v = load_triple(row_at<KIND>(facets, f, 3, 0));
+    const int vs[3] = {in_range_or_zero(v.a, N), in_range_or_zero(v.b, N), in_range_or_zero(v.c, N)};
+    float n[3], r[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        const Int2 o = load_pair(at<KIND>(off, vs[s]));
+        n[s] = (float)(o.b - o.a);
+        r[s] = 1.0f / n[s];
     }
-    gpi[(size_t)f * T + t] = acc;
+    for (int t0 = 0; t0 < T; t0 += TT) {
+        float d[TT] = {};
+        for (int c0 = 4 * lane; c0 < C; c0 += 256) {
+            const Pack yf = load_row<KIND>(row_at<KIND>(y, f, C, c0), C - c0);
+            Pack h{};
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                const Pack gv = load_row<KIND>(row_at<KIND>(gx, vs[s], C, c0), C - c0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h.v[i] = h.v[i] + quotient(gv.v[i], n[s], r[s]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) h.v[i] = yf.v[i] * h.v[i];
+#pragma unroll
+            for (int t = 0; t < TT; ++t)
+                if (t0 + t < T) {
+                    const Pack wt = load_row<KIND>(row_at<KIND>(w, (t0 + t), C, c0), C - c0);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) d[t] = fmaf(wt.v[i], h.v[i], d[t]);
+                }
+        }
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+            if (t0 + t < T) {
+                const float sum = row_sum(d[t], lane, 64);
+                if (lane == 0) gpi[(size_t)f * T + t0 + t] = sum;
+            }
+    }
 }
 
 }  // namespace conv

@@ -1110,46 +1110,44 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     return warn;
 }
 
-// channels per lane for row-major [rows, C] features at these addresses
-inline bool conv_vec4(int C, std::initializer_list<const void*> ptrs) {
-    if (C % 4 != 0) return false;
-    for (const void* p : ptrs)
-        if ((uintptr_t)p % 16 != 0) return false;
-    return true;
-}
+// Filter gradients of the convolutions' backward passes: `rows` x C values summed over n_rows rows in two stages
+// (conv::rows_to_partial, conv::reduce_rows_stage2_kernel).  Stage 1's workgroups leave their partial sums in the
+// context's sort buffer.  As many workgroups as the chip holds at once (256 compute units; a workgroup takes several
+// turns of rows_per_turn rows, keeping their sums in registers), fewer where there are not so many turns or the
+// buffer does not hold their partials.
+struct FilterSplit {
+    int groups, chunk;
+    float* partial;
+};
+// CALL(kind) with the addressing that C channels and arrays of up to max_rows rows take
+#define PICASSO_ROW_KINDS(C, max_rows, CALL)                      \
+    do {                                                          \
+        switch (pool::row_kind((C), (max_rows))) {                \
+            case pool::ROW_EVEN: CALL(pool::ROW_EVEN); break;     \
+            case pool::ROW_TAIL: CALL(pool::ROW_TAIL); break;     \
+            default: CALL(pool::ROW_ANY);                         \
+        }                                                         \
+    } while (0)
 
-// 8 channels per lane where there are enough of them: indices, levels and fuzzy coefficients are then
-// read half as often per channel
-inline int conv_vec(int C, std::initializer_list<const void*> ptrs) {
-    if (!conv_vec4(C, ptrs)) return 1;
-    return (C % 8 == 0 && C >= 32) ? 8 : 4;
-}
-
-// Two-stage sum of ROWS x C filter-gradient rows over n_rows rows (conv::reduce_rows_stage1/2):
-// partial sums in the context's sort buffer.
-template <int ROWS, class Term>
-int reduce_filter_rows(picasso_ctx* c, hipStream_t s, Term term, int n_rows, int C, bool vec4, int rows_used,
-                       float* d_out) {
-    const int Q = vec4 ? C / 4 : C;  // channel packs; a stage-1 launch takes up to pool::BLOCK of them
+int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_turn, int blocks_per_cu, bool wanted,
+                      FilterSplit* out) {
     const size_t cap = (size_t)3 * (size_t)c->max_facets * sizeof(u64) / sizeof(float);  // floats in key64[0]
-    const size_t per_group = (size_t)ROWS * C;
-    if (per_group > cap) return PICASSO_ERR_WORKSPACE;
-    const int R = pool::BLOCK / std::min(Q, pool::BLOCK);
-    long long groups = std::min<long long>(1024, ((long long)n_rows + 4ll * R - 1) / (4ll * R));
-    groups = std::max<long long>(1, std::min<long long>(groups, (long long)(cap / per_group)));
-    const int chunk = (int)(((long long)n_rows + groups - 1) / groups);
-    float* partial = reinterpret_cast<float*>(c->key64[0]);
-    const size_t lds = (size_t)pool::BLOCK * ROWS * (vec4 ? 4 : 1) * sizeof(float);
-    for (int q0 = 0; q0 < Q; q0 += pool::BLOCK) {
-        const int qn = std::min(pool::BLOCK, Q - q0);
-        if (vec4)
-            conv::reduce_rows_stage1_kernel<ROWS, 4, Term><<<(int)groups, pool::BLOCK, lds, s>>>(term, n_rows, C, chunk, partial, q0, qn);
-        else
-            conv::reduce_rows_stage1_kernel<ROWS, 1, Term><<<(int)groups, pool::BLOCK, lds, s>>>(term, n_rows, C, chunk, partial, q0, qn);
-    }
-    conv::reduce_rows_stage2_kernel<<<pool::grid_for((long long)rows_used * C * 64), pool::BLOCK, 0, s>>>(
-        partial, (int)groups, ROWS, rows_used, C, d_out);
+    const size_t per_group = (size_t)rows * C;
+    if (wanted && per_group > cap) return PICASSO_ERR_WORKSPACE;
+    const long long turns = ((long long)n_rows + rows_per_turn - 1) / rows_per_turn;
+    long long most = 256ll * blocks_per_cu;
+    if (wanted) most = std::min<long long>(most, (long long)(cap / per_group));
+    const long long per_block = (turns + most - 1) / most;  // turns of a workgroup
+    long long groups = (turns + per_block - 1) / per_block;
+    if (groups >= 8 && (groups + 7) / 8 * 8 <= most) groups = (groups + 7) / 8 * 8;  // (see conv::xcd_block)
+    out->chunk = (int)std::min<long long>(per_block * rows_per_turn, 0x7FFFFFFFll / groups);
+    out->groups = (int)groups;
+    out->partial = wanted ? reinterpret_cast<float*>(c->key64[0]) : nullptr;
     return PICASSO_OK;
+}
+void sum_filter_rows(hipStream_t s, const FilterSplit& sp, int width, float* d_out) {
+    conv::reduce_rows_stage2_kernel<<<pool::grid_for((long long)width * 64), pool::BLOCK, 0, s>>>(sp.partial, sp.groups, width,
+                                                                                                  d_out);
 }
 
 }  // namespace
@@ -1552,13 +1550,13 @@ int picasso_v2f_forward(picasso_ctx* c, void* stream, const float* d_x, int32_t 
     if (!c || !d_x || N < 1 || C < 1 || !d_facets || F < 1 || !d_w || !d_y) return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const int vec = conv_vec(C, {d_x, d_w, d_y});
-    if (vec == 8)
-        conv::v2f_forward_kernel<8><<<pool::grid_for((long long)F * (C / 8)), pool::BLOCK, 0, s>>>(d_x, N, C, d_facets, F, d_level, d_w, d_y);
-    else if (vec == 4)
-        conv::v2f_forward_kernel<4><<<pool::grid_for((long long)F * (C / 4)), pool::BLOCK, 0, s>>>(d_x, N, C, d_facets, F, d_level, d_w, d_y);
-    else
-        conv::v2f_forward_kernel<1><<<pool::grid_for((long long)F * C), pool::BLOCK, 0, s>>>(d_x, N, C, d_facets, F, d_level, d_w, d_y);
+    const pool::RowMap m = pool::row_map(C);
+    const int per_wave = conv::facets_per_wave(m, F), per_block = per_wave * (pool::BLOCK / 64);
+    const dim3 grid = conv::xcd_grid(dim3((F + per_block - 1) / per_block, pool::row_parts(m)));
+#define PICASSO_CALL(K) \
+    conv::v2f_forward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_x, N, C, d_facets, F, d_level, d_w, d_y, per_wave, m)
+    PICASSO_ROW_KINDS(C, std::max(N, F), PICASSO_CALL);
+#undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -1571,20 +1569,17 @@ int picasso_v2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const bool vec4 = conv_vec4(C, {d_gy, d_x, d_w, d_gx});
-    if (d_gx) {
-        if (conv_vec(C, {d_gy, d_w, d_gx}) == 8)
-            conv::v2f_backward_x_kernel<8><<<pool::grid_for((long long)N * (C / 8)), pool::BLOCK, 0, s>>>(d_gy, C, d_level, d_w, d_offsets, d_corners, N, 3 * F, d_gx);
-        else if (vec4)
-            conv::v2f_backward_x_kernel<4><<<pool::grid_for((long long)N * (C / 4)), pool::BLOCK, 0, s>>>(d_gy, C, d_level, d_w, d_offsets, d_corners, N, 3 * F, d_gx);
-        else
-            conv::v2f_backward_x_kernel<1><<<pool::grid_for((long long)N * C), pool::BLOCK, 0, s>>>(d_gy, C, d_level, d_w, d_offsets, d_corners, N, 3 * F, d_gx);
-    }
-    if (d_gw) {
-        conv::V2fWeightTerm term{d_gy, d_x, d_facets, d_level, C, N};
-        const int rc = reduce_filter_rows<3>(c, s, term, F, C, vec4, 3, d_gw);
-        if (rc != PICASSO_OK) return rc;
-    }
+    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
+    FilterSplit sp;
+    const int rc = split_filter_rows(c, N, 3, C, m.per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
+    if (rc != PICASSO_OK) return rc;
+    const dim3 grid(sp.groups, pool::row_parts(m.row));
+#define PICASSO_CALL(K)                                                                                                     \
+    conv::v2f_backward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_gy, d_x, C, d_level, d_w, d_offsets, d_corners, N, 3 * F,     \
+                                                              sp.chunk, d_gx, sp.partial, m)
+    PICASSO_ROW_KINDS(C, std::max(N, F), PICASSO_CALL);
+#undef PICASSO_CALL
+    if (d_gw) sum_filter_rows(s, sp, 3 * C, d_gw);
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -1594,10 +1589,13 @@ int picasso_f2f_forward(picasso_ctx* c, void* stream, const float* d_tex, const 
     if (!c || !d_tex || !d_bary || !d_poff || F < 1 || P < 0 || C < 1 || !d_w || !d_y) return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    if (conv_vec4(C, {d_tex, d_w, d_y}))
-        conv::f2f_forward_kernel<4><<<pool::grid_for((long long)F * (C / 4)), pool::BLOCK, 0, s>>>(d_tex, d_bary, d_poff, F, P, C, d_w, d_y);
-    else
-        conv::f2f_forward_kernel<1><<<pool::grid_for((long long)F * C), pool::BLOCK, 0, s>>>(d_tex, d_bary, d_poff, F, P, C, d_w, d_y);
+    const conv::WalkMap m = conv::walk_map(C, F, (double)P / F);
+    const int per_block = m.per_wave * (pool::BLOCK / 64);
+    const dim3 grid = conv::xcd_grid(dim3((F + per_block - 1) / per_block, pool::row_parts(m.row)));
+#define PICASSO_CALL(K) \
+    conv::f2f_forward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_tex, d_bary, d_poff, F, P, C, d_w, d_y, m)
+    PICASSO_ROW_KINDS(C, std::max(F, P), PICASSO_CALL);
+#undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -1609,18 +1607,27 @@ int picasso_f2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const bool vec4 = conv_vec4(C, {d_gy, d_tex, d_w, d_gtex});
-    if (d_gtex) {
-        if (vec4)
-            conv::f2f_backward_tex_kernel<4><<<pool::grid_for((long long)F * (C / 4)), pool::BLOCK, 0, s>>>(d_gy, d_bary, d_poff, F, P, C, d_w, d_gtex);
-        else
-            conv::f2f_backward_tex_kernel<1><<<pool::grid_for((long long)F * C), pool::BLOCK, 0, s>>>(d_gy, d_bary, d_poff, F, P, C, d_w, d_gtex);
-    }
-    if (d_gw) {
-        conv::F2fWeightTerm term{d_gy, d_tex, d_bary, d_poff, C, P};
-        const int rc = reduce_filter_rows<3>(c, s, term, F, C, vec4, 3, d_gw);
-        if (rc != PICASSO_OK) return rc;
-    }
+    const pool::RowMap m = pool::row_map(C);
+    FilterSplit sp;
+    const int per_wave = (int)std::max<long long>(1, std::min<long long>(conv::WALK_WAVE_ROWS / 2, F / 4096));
+    const int rc = split_filter_rows(c, F, 3, C, per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
+    if (rc != PICASSO_OK) return rc;
+    const dim3 grid(sp.groups, pool::row_parts(m));
+#define PICASSO_CALL(K)                                                                                                     \
+    conv::f2f_backward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_gy, d_tex, d_bary, d_poff, F, P, C, d_w, sp.chunk, per_wave,    \
+                                                              d_gtex, sp.partial, m)
+    PICASSO_ROW_KINDS(C, std::max(F, P), PICASSO_CALL);
+#undef PICASSO_CALL
+    if (d_gw) sum_filter_rows(s, sp, 3 * C, d_gw);
+    HIP_TRY(c, hipGetLastError());
+    return PICASSO_OK;
+}
+
+int picasso_f2f_clear_unowned(picasso_ctx* c, void* stream, const int32_t* d_poff, int32_t F, int32_t P, int32_t C,
+                              float* d_gtex) {
+    if (!c || !d_poff || F < 1 || P < 0 || C < 1 || !d_gtex) return PICASSO_ERR_INVALID_ARG;
+    HIP_TRY(c, hipSetDevice(c->device));
+    conv::f2f_clear_kernel<<<256, pool::BLOCK, 0, (hipStream_t)stream>>>(d_poff, F, P, C, d_gtex);
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -1632,23 +1639,19 @@ int picasso_f2v_forward(picasso_ctx* c, void* stream, const float* d_y, int32_t 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const bool vec4 = conv_vec4(C, {d_y, d_w, d_x});
-    const bool lds = (long long)T * C <= conv::F2V_LDS_FLOATS;
-    const size_t lds_bytes = lds ? sizeof(float) * (size_t)T * C : 0;
-    const bool vec8 = conv_vec(C, {d_y, d_w, d_x}) == 8;
-    const int grid = conv::xcd_grid((long long)N * (vec8 ? C / 8 : (vec4 ? C / 4 : C)));
-#define PICASSO_F2V(VEC, LDS) \
-    conv::f2v_forward_kernel<VEC, LDS><<<grid, pool::BLOCK, lds_bytes, s>>>(d_y, C, d_pi, T, d_w, d_offsets, d_corners, N, 3 * F, d_x)
-    if (vec8) {
-        if (lds) PICASSO_F2V(8, true);
-        else PICASSO_F2V(8, false);
-    } else if (vec4) {
-        if (lds) PICASSO_F2V(4, true);
-        else PICASSO_F2V(4, false);
-    } else {
-        if (lds) PICASSO_F2V(1, true);
-        else PICASSO_F2V(1, false);
-    }
+    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
+    const int per_block = (T <= 16 ? m.per_wave : m.row.rw) * (pool::BLOCK / 64);
+    const dim3 grid = conv::xcd_grid(dim3((N + per_block - 1) / per_block, pool::row_parts(m.row)));
+#define PICASSO_F2V(NP, K) \
+    conv::f2v_forward_kernel<NP, K><<<grid, pool::BLOCK, 0, s>>>(d_y, C, d_pi, T, d_w, d_offsets, d_corners, N, 3 * F, d_x, m)
+#define PICASSO_CALL(K)                      \
+    if (T <= 4) PICASSO_F2V(1, K);           \
+    else if (T <= 8) PICASSO_F2V(2, K);      \
+    else if (T <= 12) PICASSO_F2V(3, K);     \
+    else if (T <= 16) PICASSO_F2V(4, K);     \
+    else conv::f2v_forward_many_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_y, C, d_pi, T, d_w, d_offsets, d_corners, N, 3 * F, d_x, m.row)
+    PICASSO_ROW_KINDS(std::max(C, T), std::max(N, F), PICASSO_CALL);
+#undef PICASSO_CALL
 #undef PICASSO_F2V
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
@@ -1662,25 +1665,46 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const bool vec4 = conv_vec4(C, {d_gx, d_y, d_w, d_gy});
-    if (d_gy) {
-        if (conv_vec(C, {d_gx, d_w, d_gy}) == 8)
-            conv::f2v_backward_y_kernel<8><<<pool::grid_for((long long)F * (C / 8)), pool::BLOCK, 0, s>>>(d_gx, C, d_pi, T, d_w, d_facets, F, d_offsets, N, d_gy);
-        else if (vec4)
-            conv::f2v_backward_y_kernel<4><<<pool::grid_for((long long)F * (C / 4)), pool::BLOCK, 0, s>>>(d_gx, C, d_pi, T, d_w, d_facets, F, d_offsets, N, d_gy);
-        else
-            conv::f2v_backward_y_kernel<1><<<pool::grid_for((long long)F * C), pool::BLOCK, 0, s>>>(d_gx, C, d_pi, T, d_w, d_facets, F, d_offsets, N, d_gy);
-    }
-    if (d_gw) {
-        constexpr int ROWS = 8;  // filter rows per pass
-        for (int t0 = 0; t0 < T; t0 += ROWS) {
-            conv::F2vWeightTerm<ROWS> term{d_gx, d_y, d_pi, d_facets, d_offsets, N, C, T, t0};
-            const int rc = reduce_filter_rows<ROWS>(c, s, term, F, C, vec4, std::min(ROWS, T - t0), d_gw + (size_t)t0 * C);
+    // one pass per 16 filter rows; gpi with it where a row's lanes fit a wave, else by a kernel of its own
+    const bool gpi_fused = d_gpi && C <= 256;
+    const pool::RowMap m = pool::row_map(C, gpi_fused);
+    const int per_wave = conv::facets_per_wave(m, F);
+    if (d_gy || d_gw || gpi_fused) {
+        for (int t0 = 0; t0 < T; t0 += 16) {
+            float* gy = t0 == 0 ? d_gy : nullptr;
+            if (!gy && !d_gw && !gpi_fused) break;
+            const int rows = std::min(16, T - t0);
+            FilterSplit sp;
+            const int rc = split_filter_rows(c, F, rows, C, per_wave * (pool::BLOCK / 64), rows <= 4 ? 6 : (rows <= 12 ? 4 : 3), d_gw != nullptr, &sp);
             if (rc != PICASSO_OK) return rc;
+            const dim3 grid(sp.groups, pool::row_parts(m));
+#define PICASSO_F2V_BACK(NP, K)                                                                                       \
+    do {                                                                                                              \
+        if (gpi_fused)                                                                                                \
+            conv::f2v_backward_kernel<NP, K, true><<<grid, pool::BLOCK, 0, s>>>(                                      \
+                d_gx, d_y, C, d_pi, T, t0, rows, d_w, d_facets, F, d_offsets, N, sp.chunk, per_wave, gy, sp.partial, d_gpi, m); \
+        else                                                                                                          \
+            conv::f2v_backward_kernel<NP, K, false><<<grid, pool::BLOCK, 0, s>>>(                                     \
+                d_gx, d_y, C, d_pi, T, t0, rows, d_w, d_facets, F, d_offsets, N, sp.chunk, per_wave, gy, sp.partial, d_gpi, m); \
+    } while (0)
+#define PICASSO_CALL(K)                         \
+    if (rows <= 4) PICASSO_F2V_BACK(1, K);      \
+    else if (rows <= 8) PICASSO_F2V_BACK(2, K); \
+    else if (rows <= 12) PICASSO_F2V_BACK(3, K);\
+    else PICASSO_F2V_BACK(4, K)
+            PICASSO_ROW_KINDS(std::max(C, T), std::max(N, F), PICASSO_CALL);
+#undef PICASSO_CALL
+#undef PICASSO_F2V_BACK
+            if (d_gw) sum_filter_rows(s, sp, rows * C, d_gw + (size_t)t0 * C);
         }
     }
-    if (d_gpi)
-        conv::f2v_backward_pi_kernel<<<pool::grid_for((long long)F * T), pool::BLOCK, 0, s>>>(d_gx, d_y, C, T, d_w, d_facets, F, d_offsets, N, d_gpi);
+    if (d_gpi && !gpi_fused) {
+        const int grid = (F + pool::BLOCK / 64 - 1) / (pool::BLOCK / 64);
+#define PICASSO_CALL(K) \
+    conv::f2v_backward_pi_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_gx, d_y, C, T, d_w, d_facets, F, d_offsets, N, d_gpi)
+        PICASSO_ROW_KINDS(C, std::max(N, F), PICASSO_CALL);
+#undef PICASSO_CALL
+    }
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -1740,9 +1764,9 @@ int picasso_pool_forward(picasso_ctx* c, void* stream, int mode, const float* d_
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const bool vec4 = (C % 4 == 0) && (((uintptr_t)d_x | (uintptr_t)d_y) % 16 == 0);
-    if (vec4) pool::launch_pool_forward<4>(s, mode, d_x, C, d_offsets, d_members, n_out, d_weight, d_y, d_argmax);
-    else pool::launch_pool_forward<1>(s, mode, d_x, C, d_offsets, d_members, n_out, d_weight, d_y, d_argmax);
+#define PICASSO_CALL(K) pool::launch_pool_forward<K>(s, mode, d_x, C, d_offsets, d_members, n_out, d_weight, d_y, d_argmax)
+    PICASSO_ROW_KINDS(C, std::max(n_in, n_out), PICASSO_CALL);
+#undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -1755,11 +1779,10 @@ int picasso_pool_backward(picasso_ctx* c, void* stream, int mode, const float* d
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const bool vec4 = (C % 4 == 0) && (((uintptr_t)d_gy | (uintptr_t)d_gx) % 16 == 0);
-    if (vec4)
-        pool::launch_pool_backward<4>(s, mode, d_gy, n_in, C, d_cluster_id, d_offsets, d_members, d_weight, d_argmax, d_gx);
-    else
-        pool::launch_pool_backward<1>(s, mode, d_gy, n_in, C, d_cluster_id, d_offsets, d_members, d_weight, d_argmax, d_gx);
+#define PICASSO_CALL(K) \
+    pool::launch_pool_backward<K>(s, mode, d_gy, n_in, C, d_cluster_id, d_offsets, d_members, d_weight, d_argmax, d_gx)
+    PICASSO_ROW_KINDS(C, std::max(n_in, n_out), PICASSO_CALL);
+#undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -1769,11 +1792,11 @@ int picasso_unpool_forward(picasso_ctx* c, void* stream, const float* d_y, int32
     if (!c || !d_y || !d_cluster_id || !d_x || n_in < 1 || C < 1) return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const bool vec4 = (C % 4 == 0) && (((uintptr_t)d_y | (uintptr_t)d_x) % 16 == 0);
-    if (vec4)
-        pool::unpool_forward_kernel<4><<<pool::grid_for((long long)n_in * (C / 4)), pool::BLOCK, 0, s>>>(d_y, n_in, C, d_cluster_id, d_x);
-    else
-        pool::unpool_forward_kernel<1><<<pool::grid_for((long long)n_in * C), pool::BLOCK, 0, s>>>(d_y, n_in, C, d_cluster_id, d_x);
+    const pool::RowMap m = pool::row_map(C);
+#define PICASSO_CALL(K) \
+    pool::unpool_forward_kernel<K><<<pool::row_grid(m, n_in), pool::BLOCK, 0, s>>>(d_y, n_in, C, d_cluster_id, d_x, m)
+    PICASSO_ROW_KINDS(C, n_in, PICASSO_CALL);
+#undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }

@@ -4,12 +4,14 @@
 // Features are fp32 [N, C] row-major.  A cluster's members are visited in
 // ascending vertex order (CSR built by a stable sort of (cluster_id, vertex)),
 // every sum is a left-to-right fp32 sum in that order and there are no fp
-// atomics, so results do not depend on scheduling.  One lane owns VEC
+// atomics, so results do not depend on scheduling.  One lane owns four
 // consecutive channels of one cluster (or of one vertex), so neighbouring
 // lanes read neighbouring addresses of the same feature row.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #pragma clang fp contract(off)
 
@@ -18,139 +20,242 @@ namespace pool {
 constexpr int BLOCK = 256;
 enum Mode { AVG = 0, MAX = 1, WEIGHTED = 2, SUM = 3 };
 
-template <int VEC>
+// Four consecutive channels of a feature row.  Loads and stores need 4-byte alignment only (the hardware takes
+// 16-byte accesses at any such address), so every channel count and address goes this way.
 struct Pack {
-    float v[VEC];
+    float v[4];
+};
+struct __attribute__((packed, aligned(4))) PackedFloat4 {
+    float v[4];
+};
+struct __attribute__((packed, aligned(4))) PackedInt4 {
+    int v[4];
 };
 
-template <int VEC>
-__device__ __forceinline__ Pack<VEC> load_pack(const float* __restrict__ p) {
-    Pack<VEC> r;
-    if (VEC == 4) {
-        const float4 t = *reinterpret_cast<const float4*>(p);
-        r.v[0] = t.x; r.v[1 % VEC] = t.y; r.v[2 % VEC] = t.z; r.v[3 % VEC] = t.w;
-    } else if (VEC == 8) {
-        const float4 t = *reinterpret_cast<const float4*>(p), u = *reinterpret_cast<const float4*>(p + 4);
-        r.v[0] = t.x; r.v[1 % VEC] = t.y; r.v[2 % VEC] = t.z; r.v[3 % VEC] = t.w;
-        r.v[4 % VEC] = u.x; r.v[5 % VEC] = u.y; r.v[6 % VEC] = u.z; r.v[7 % VEC] = u.w;
+// How the rows of a call are addressed, the same for all its arrays (row_kind):
+//   ROW_EVEN  the channel count is a multiple of 4, and every array's byte offsets fit 32 bits and its row numbers
+//             24: an address is one 24-bit multiply-add on top of a base in scalar registers;
+//   ROW_TAIL  the same, with a last pack of `left` < 4 channels per row (the others read as 0);
+//   ROW_ANY   any size (64-bit offsets) and channel count.
+// (With 64-bit offsets everywhere the address arithmetic alone took as many vector instructions as the
+// convolutions' sums.)
+enum RowKind { ROW_EVEN, ROW_TAIL, ROW_ANY };
+inline RowKind row_kind(int C, long long max_rows) {
+    const bool fits = max_rows < (1ll << 24) && 4ll * C < (1ll << 24) && 4ll * C * max_rows < (1ll << 32) && max_rows * 64 < (1ll << 32);
+    return !fits ? ROW_ANY : (C % 4 == 0 ? ROW_EVEN : ROW_TAIL);
+}
+
+// p + i elements
+template <int KIND, typename T>
+__device__ __forceinline__ T* at(T* p, int i) {
+    if constexpr (KIND == ROW_ANY) return p + (size_t)i;
+    using Bytes = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T*>(reinterpret_cast<Bytes*>(p) + (uint32_t)i * (uint32_t)sizeof(T));
+}
+// channel c0 of row i
+template <int KIND, typename T>
+__device__ __forceinline__ T* row_at(T* p, int i, int C, int c0) {
+    if constexpr (KIND == ROW_ANY) return p + ((size_t)i * C + c0);
+    using Bytes = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T*>(reinterpret_cast<Bytes*>(p) + (__umul24((uint32_t)i, 4u * (uint32_t)C) + 4u * (uint32_t)c0));
+}
+
+template <int KIND>
+__device__ __forceinline__ Pack load_row(const float* __restrict__ p, int left) {
+    Pack r;
+    if (KIND == ROW_EVEN || left >= 4) {
+        const PackedFloat4 t = *reinterpret_cast<const PackedFloat4*>(p);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r.v[k] = t.v[k];
     } else {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) r.v[k] = p[k];
+        for (int k = 0; k < 4; ++k) r.v[k] = k < left ? p[k] : 0.0f;
     }
     return r;
 }
 
-template <int VEC>
-__device__ __forceinline__ void store_pack(float* __restrict__ p, const Pack<VEC>& r) {
-    if (VEC == 4) {
-        *reinterpret_cast<float4*>(p) = make_float4(r.v[0], r.v[1 % VEC], r.v[2 % VEC], r.v[3 % VEC]);
-    } else if (VEC == 8) {
-        *reinterpret_cast<float4*>(p) = make_float4(r.v[0], r.v[1 % VEC], r.v[2 % VEC], r.v[3 % VEC]);
-        *reinterpret_cast<float4*>(p + 4) = make_float4(r.v[4 % VEC], r.v[5 % VEC], r.v[6 % VEC], r.v[7 % VEC]);
+// The values are in registers from here on.  Used on a batch of loads in front of the code that takes them one
+// by one under conditions: the compiler otherwise moves each load to its use, and none are in flight together.
+__device__ __forceinline__ void arrived(float& a) { asm volatile("" : "+v"(a)); }
+__device__ __forceinline__ void arrived(Pack& p) {
+    asm volatile("" : "+v"(p.v[0]), "+v"(p.v[1]), "+v"(p.v[2]), "+v"(p.v[3]));
+}
+
+template <int KIND>
+__device__ __forceinline__ void store_row(float* __restrict__ p, const Pack& r, int left) {
+    if (KIND == ROW_EVEN || left >= 4) {
+        PackedFloat4 t;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t.v[k] = r.v[k];
+        *reinterpret_cast<PackedFloat4*>(p) = t;
     } else {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) p[k] = r.v[k];
+        for (int k = 0; k < 4; ++k)
+            if (k < left) p[k] = r.v[k];
     }
 }
 
+// How a wave's lanes share out rows of C channels: Q = ceil(C / 4) packs per row, dealt to `parts` waves (blockIdx.y)
+// of qc lanes per row, and 64 / qc rows side by side in a wave.  A lane finds its row with one multiplication
+// instead of dividing a flat index by Q (a 64-bit division per lane took longer than the lane's loads).
+struct RowMap {
+    int Q, qc, rw, inv;  // rw = rows per wave and step; inv = ceil(65536 / qc)
+};
+inline int row_parts(const RowMap& m) { return (m.Q + m.qc - 1) / m.qc; }
+// one_wave: all lanes of a row in one wave, Q <= 64 (for sums across a row's lanes)
+inline RowMap row_map(int C, bool one_wave = false) {
+    RowMap best{}, m;
+    double best_use = -1.0;
+    m.Q = (C + 3) / 4;
+    const int least = (m.Q + 63) / 64;
+    for (int parts = least; parts <= (one_wave ? 1 : least + 3) && parts <= m.Q; ++parts) {
+        m.qc = (m.Q + parts - 1) / parts;
+        m.rw = 64 / m.qc;
+        m.inv = (65536 + m.qc - 1) / m.qc;
+        const double use = (double)m.rw * m.Q / (64.0 * row_parts(m)) - 0.04 * (parts - least);  // lanes at work
+        if (use > best_use) {
+            best_use = use;
+            best = m;
+        }
+    }
+    return best;
+}
+// workgroups so that every wave takes `steps` x rw rows
+inline dim3 row_grid(const RowMap& m, int rows, int steps = 1) {
+    const long long per_block = (long long)m.rw * steps * (BLOCK / 64);
+    return dim3((unsigned)((rows + per_block - 1) / per_block), (unsigned)row_parts(m));
+}
+
+struct RowLane {
+    int r, q;  // row within the wave's rows, channel pack of the row
+    bool on;
+};
+__device__ __forceinline__ RowLane row_lane(const RowMap& m, int part) {
+    const int u = (int)threadIdx.x & 63;
+    RowLane l;
+    l.r = (u * m.inv) >> 16;  // u / qc (exact for u, qc <= 64)
+    l.q = u - l.r * m.qc + part * m.qc;
+    l.on = l.r < m.rw && l.q < m.Q;
+    return l;
+}
+// first of the wave's rows, one step per wave
+__device__ __forceinline__ int wave_row(const RowMap& m, int block) {
+    return (block * (BLOCK / 64) + ((int)threadIdx.x >> 6)) * m.rw;
+}
+
 // y[c] = pooled feature of cluster c.  MAX also writes the first member that attains the maximum.
-template <int MODE, int VEC>
+template <int MODE, int KIND>
 __global__ __launch_bounds__(BLOCK) void pool_forward_kernel(const float* __restrict__ x, int C,
                                                              const int* __restrict__ off,
                                                              const int* __restrict__ mem, int n_out,
                                                              const float* __restrict__ w, float* __restrict__ y,
-                                                             int* __restrict__ argmax) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int c = (int)(idx / Q), q = (int)(idx % Q);
-    if (c >= n_out) return;
-    const int s = off[c], e = off[c + 1];
-    Pack<VEC> acc;
-    int arg[VEC];
+                                                             int* __restrict__ argmax, RowMap map) {
+    const RowLane l = row_lane(map, blockIdx.y);
+    const int c = wave_row(map, blockIdx.x) + l.r;
+    if (!l.on || c >= n_out) return;
+    const int c0 = 4 * l.q, left = C - c0;
+    const int s = *at<KIND>(off, c), e = *at<KIND>(off, c + 1);
+    Pack acc;
+    int arg[4];
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) {
+    for (int k = 0; k < 4; ++k) {
         acc.v[k] = 0.0f;
         arg[k] = -1;
     }
     float wsum = 0.0f;
     for (int m = s; m < e; ++m) {
-        const int v = mem[m];
-        const Pack<VEC> xv = load_pack<VEC>(x + (size_t)v * C + (size_t)q * VEC);
+        const int v = *at<KIND>(mem, m);
+        const Pack xv = load_row<KIND>(row_at<KIND>(x, v, C, c0), left);
         if (MODE == MAX) {
 #pragma unroll
-            for (int k = 0; k < VEC; ++k)
+            for (int k = 0; k < 4; ++k)
                 if (m == s || xv.v[k] > acc.v[k]) {
                     acc.v[k] = xv.v[k];
                     arg[k] = v;
                 }
         } else if (MODE == WEIGHTED) {
-            const float wv = w[v];
+            const float wv = *at<KIND>(w, v);
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) acc.v[k] = acc.v[k] + wv * xv.v[k];
+            for (int k = 0; k < 4; ++k) acc.v[k] = acc.v[k] + wv * xv.v[k];
             wsum = wsum + wv;
         } else {
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) acc.v[k] = acc.v[k] + xv.v[k];
+            for (int k = 0; k < 4; ++k) acc.v[k] = acc.v[k] + xv.v[k];
         }
     }
     if (MODE == AVG) {
         const float n = (float)(e - s);
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) acc.v[k] = (e > s) ? acc.v[k] / n : 0.0f;
+        for (int k = 0; k < 4; ++k) acc.v[k] = (e > s) ? acc.v[k] / n : 0.0f;
     }
     if (MODE == WEIGHTED) {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) acc.v[k] = (wsum != 0.0f) ? acc.v[k] / wsum : 0.0f;
+        for (int k = 0; k < 4; ++k) acc.v[k] = (wsum != 0.0f) ? acc.v[k] / wsum : 0.0f;
     }
-    store_pack<VEC>(y + (size_t)c * C + (size_t)q * VEC, acc);
+    store_row<KIND>(row_at<KIND>(y, c, C, c0), acc, left);
     if (MODE == MAX && argmax) {
+        int* a = row_at<KIND>(argmax, c, C, c0);
+        if (KIND == ROW_EVEN || left >= 4) {
+            *reinterpret_cast<PackedInt4*>(a) = PackedInt4{{arg[0], arg[1], arg[2], arg[3]}};
+        } else {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) argmax[(size_t)c * C + (size_t)q * VEC + k] = arg[k];
+            for (int k = 0; k < 4; ++k)
+                if (k < left) a[k] = arg[k];
+        }
     }
 }
 
 // gx[v] = adjoint of the pooling applied to gy, for the features (weights are constants)
-template <int MODE, int VEC>
+template <int MODE, int KIND>
 __global__ __launch_bounds__(BLOCK) void pool_backward_kernel(const float* __restrict__ gy, int n_in, int C,
                                                               const int* __restrict__ cid,
                                                               const int* __restrict__ off,
                                                               const int* __restrict__ mem,
                                                               const float* __restrict__ w,
                                                               const int* __restrict__ argmax,
-                                                              float* __restrict__ gx) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int v = (int)(idx / Q), q = (int)(idx % Q);
-    if (v >= n_in) return;
-    const int c = cid[v];
-    Pack<VEC> g = load_pack<VEC>(gy + (size_t)c * C + (size_t)q * VEC);
+                                                              float* __restrict__ gx, RowMap map) {
+    const RowLane l = row_lane(map, blockIdx.y);
+    const int v = wave_row(map, blockIdx.x) + l.r;
+    if (!l.on || v >= n_in) return;
+    const int c0 = 4 * l.q, left = C - c0;
+    const int c = *at<KIND>(cid, v);
+    Pack g = load_row<KIND>(row_at<KIND>(gy, c, C, c0), left);
     if (MODE == AVG) {
         const float n = (float)(off[c + 1] - off[c]);
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) g.v[k] = g.v[k] / n;
+        for (int k = 0; k < 4; ++k) g.v[k] = g.v[k] / n;
     } else if (MODE == MAX) {
+        const int* a = row_at<KIND>(argmax, c, C, c0);
+        PackedInt4 arg;
+        if (KIND == ROW_EVEN || left >= 4) {
+            arg = *reinterpret_cast<const PackedInt4*>(a);
+        } else {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k)
-            if (argmax[(size_t)c * C + (size_t)q * VEC + k] != v) g.v[k] = 0.0f;
+            for (int k = 0; k < 4; ++k) arg.v[k] = k < left ? a[k] : v;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (arg.v[k] != v) g.v[k] = 0.0f;
     } else if (MODE == WEIGHTED) {
         float wsum = 0.0f;
         for (int m = off[c]; m < off[c + 1]; ++m) wsum = wsum + w[mem[m]];
         const float wv = w[v];
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) g.v[k] = (wsum != 0.0f) ? (g.v[k] * wv) / wsum : 0.0f;
+        for (int k = 0; k < 4; ++k) g.v[k] = (wsum != 0.0f) ? (g.v[k] * wv) / wsum : 0.0f;
     }
-    store_pack<VEC>(gx + (size_t)v * C + (size_t)q * VEC, g);
+    store_row<KIND>(row_at<KIND>(gx, v, C, c0), g, left);
 }
 
 // Unpooling: every vertex takes its cluster's feature.
-template <int VEC>
+template <int KIND>
 __global__ __launch_bounds__(BLOCK) void unpool_forward_kernel(const float* __restrict__ y, int n_in, int C,
-                                                               const int* __restrict__ cid, float* __restrict__ x) {
-    const int Q = C / VEC;
-    const long long idx = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    const int v = (int)(idx / Q), q = (int)(idx % Q);
-    if (v >= n_in) return;
-    store_pack<VEC>(x + (size_t)v * C + (size_t)q * VEC, load_pack<VEC>(y + (size_t)cid[v] * C + (size_t)q * VEC));
+                                                               const int* __restrict__ cid, float* __restrict__ x,
+                                                               RowMap map) {
+    const RowLane l = row_lane(map, blockIdx.y);
+    const int v = wave_row(map, blockIdx.x) + l.r;
+    if (!l.on || v >= n_in) return;
+    const int c0 = 4 * l.q, left = C - c0;
+    store_row<KIND>(row_at<KIND>(x, v, C, c0), load_row<KIND>(row_at<KIND>(y, *at<KIND>(cid, v), C, c0), left), left);
 }
 
 // (cluster id, vertex) pairs for the CSR sort; flags ids outside [0, n_out)
@@ -222,29 +327,29 @@ __global__ __launch_bounds__(BLOCK) void replace_mapping_status_kernel(const int
 
 inline int grid_for(long long n) { return (int)((n + BLOCK - 1) / BLOCK > 0 ? (n + BLOCK - 1) / BLOCK : 1); }
 
-template <int VEC>
+template <int KIND>
 inline void launch_pool_forward(hipStream_t s, int mode, const float* x, int C, const int* off, const int* mem,
                                 int n_out, const float* w, float* y, int* argmax) {
-    const int g = grid_for((long long)n_out * (C / VEC));
+    const RowMap m = row_map(C);
+    const dim3 g = row_grid(m, n_out);
     switch (mode) {
-        case AVG: pool_forward_kernel<AVG, VEC><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax); break;
-        case MAX: pool_forward_kernel<MAX, VEC><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax); break;
-        case WEIGHTED: pool_forward_kernel<WEIGHTED, VEC><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax); break;
-        default: pool_forward_kernel<SUM, VEC><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax); break;
+        case AVG: pool_forward_kernel<AVG, KIND><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax, m); break;
+        case MAX: pool_forward_kernel<MAX, KIND><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax, m); break;
+        case WEIGHTED: pool_forward_kernel<WEIGHTED, KIND><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax, m); break;
+        default: pool_forward_kernel<SUM, KIND><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax, m); break;
     }
 }
 
-template <int VEC>
+template <int KIND>
 inline void launch_pool_backward(hipStream_t s, int mode, const float* gy, int n_in, int C, const int* cid,
                                  const int* off, const int* mem, const float* w, const int* argmax, float* gx) {
-    const int g = grid_for((long long)n_in * (C / VEC));
+    const RowMap m = row_map(C);
+    const dim3 g = row_grid(m, n_in);
     switch (mode) {
-        case AVG: pool_backward_kernel<AVG, VEC><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx); break;
-        case MAX: pool_backward_kernel<MAX, VEC><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx); break;
-        case WEIGHTED:
-            pool_backward_kernel<WEIGHTED, VEC><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx);
-            break;
-        default: pool_backward_kernel<SUM, VEC><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx); break;
+        case AVG: pool_backward_kernel<AVG, KIND><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx, m); break;
+        case MAX: pool_backward_kernel<MAX, KIND><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx, m); break;
+        case WEIGHTED: pool_backward_kernel<WEIGHTED, KIND><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx, m); break;
+        default: pool_backward_kernel<SUM, KIND><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx, m); break;
     }
 }
 

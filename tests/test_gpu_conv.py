@@ -302,3 +302,78 @@ def test_filter_gradients_with_many_channels(pk, ctx, oracle, C):
     _, gw2_r, _ = oracle.f2v_backward(x, gy, pi, wt, F)
     _, gw2_a, _ = oracle.f2v_backward(np.abs(x), np.abs(gy), pi, np.abs(wt), F)
     _close(gw2, gw2_r, _gw_terms(nF, 6), gw2_a, "gw (f2v)")
+
+
+@pytest.mark.parametrize("C,T", [(1, 2), (5, 4), (6, 5), (33, 8), (64, 9), (132, 12), (257, 16), (260, 17), (40, 33)])
+def test_convolutions_at_the_edges_of_their_row_and_component_splits(pk, ctx, oracle, C, T):
+    """Channel counts around whole packs of four, waves and workgroup parts; component counts around the
+    slots of four; rows that no window, step or workgroup divides evenly, one of them longer than a window."""
+    V, F = meshgen.noisy_grid(19, 21, seed=3, noise=0.02)
+    fan = np.stack([np.full(90, 7), np.arange(100, 190), np.arange(101, 191)], 1).astype(np.int32)  # 90 more corners at vertex 7
+    F = np.concatenate([F, fan, [[3, 3, 4]]]).astype(np.int32)
+    V = np.concatenate([V, np.zeros((3, 3), np.float32)])  # without facets
+    N, nF = V.shape[0], F.shape[0]
+    rng = np.random.default_rng(C * 100 + T)
+    x, gx = (rng.normal(size=(N, C)).astype(np.float32) for _ in range(2))
+    y, gy = (rng.normal(size=(nF, C)).astype(np.float32) for _ in range(2))
+    w3, wt = rng.normal(size=(3, C)).astype(np.float32), rng.normal(size=(T, C)).astype(np.float32)
+    pi = softmax(rng.normal(size=(nF, T)), axis=1).astype(np.float32)
+    level = rng.integers(1, 4, nF).astype(np.int32)
+    deg = int(np.bincount(F.reshape(-1), minlength=N).max())
+    print(f"row splits C={C} T={T}", flush=True)
+    off, cor = ctx.picasso_vertex_corner_csr(dev(F), N)
+    a = np.abs
+    _close(ctx.picasso_v2f_forward(dev(x), dev(F), dev(level), dev(w3)), oracle.v2f_forward(x, F, level, w3), 9,
+           oracle.v2f_forward(a(x), F, level, a(w3)), "y")
+    gxx, gw3 = ctx.picasso_v2f_backward(dev(gy), dev(x), dev(F), dev(level), dev(w3), off, cor)
+    gxx_r, gw3_r = oracle.v2f_backward(gy, x, F, level, w3)
+    gxx_a, gw3_a = oracle.v2f_backward(a(gy), a(x), F, level, a(w3))
+    _close(gxx, gxx_r, 4 * deg, gxx_a, "gx")
+    _close(gw3, gw3_r, _gw_terms(nF, 4), gw3_a, "gw (v2f)")
+    _close(ctx.picasso_f2v_forward(dev(y), dev(pi), dev(wt), off, cor, N), oracle.f2v_forward(y, pi, wt, F, N), (T + 2) * deg,
+           oracle.f2v_forward(a(y), pi, a(wt), F, N), "x")
+    g = ctx.picasso_f2v_backward(dev(gx), dev(y), dev(pi), dev(wt), dev(F), off)
+    r, s = oracle.f2v_backward(gx, y, pi, wt, F), oracle.f2v_backward(a(gx), a(y), pi, a(wt), F)
+    for got, want, abs_sum, n, what in zip(g, r, s, (T + 8, _gw_terms(nF, 6), 6 * C), ("gy", "gw (f2v)", "gpi")):
+        _close(got, want, n, abs_sum, what)
+    g2 = ctx.picasso_f2v_backward(dev(gx), dev(y), dev(pi), dev(wt), dev(F), off, want_gpi=False)
+    _close(g2[0], r[0], T + 8, s[0], "gy alone")
+    _close(g2[1], r[1], _gw_terms(nF, 6), s[1], "gw alone (f2v)")
+
+
+def test_rows_beyond_24_bit_numbers(pk, ctx):
+    """Vertex numbers at and above 2^24 (64-bit row addresses): the same mesh with its vertices behind 2^24 unused
+    ones gives the same features, and so do texture points beyond 2^24."""
+    V, F = meshgen.noisy_grid(23, 17, seed=5, noise=0.02)
+    N, C, T, shift = V.shape[0], 3, 5, 1 << 24
+    rng = np.random.default_rng(8)
+    x, gx = (dev(rng.normal(size=(N, C)).astype(np.float32)) for _ in range(2))
+    y = dev(rng.normal(size=(F.shape[0], C)).astype(np.float32))
+    w3, wt = dev(rng.normal(size=(3, C)).astype(np.float32)), dev(rng.normal(size=(T, C)).astype(np.float32))
+    pi = dev(softmax(rng.normal(size=(F.shape[0], T)), axis=1).astype(np.float32))
+
+    def behind(t):
+        return torch.cat([torch.zeros((shift, C), dtype=torch.float32, device="cuda:0"), t])
+
+    got = []
+    for s, x_, gx_ in ((0, x, gx), (shift, behind(x), behind(gx))):
+        f = dev((F + s).astype(np.int32))
+        print(f"rows from {s}", flush=True)
+        off, cor = ctx.picasso_vertex_corner_csr(f, N + s)
+        gxx, _ = ctx.picasso_v2f_backward(y, x_, f, None, w3, off, cor)
+        gy, _, gpi = ctx.picasso_f2v_backward(gx_, y, pi, wt, f, off)
+        got.append([ctx.picasso_v2f_forward(x_, f, None, w3), ctx.picasso_f2v_forward(y, pi, wt, off, cor, N + s)[s:], gxx[s:], gy, gpi])
+    for a, b in zip(*got):
+        assert torch.allclose(a, b, rtol=0, atol=float(16 * EPS * a.abs().max()))  # (a row's sum may be split otherwise)
+    tex = dev(rng.normal(size=(500, 1)).astype(np.float32))
+    bary = dev(rng.dirichlet(np.ones(3), size=500).astype(np.float32))
+    poff = np.sort(rng.integers(0, 501, 41)).astype(np.int32)
+    w, g = dev(rng.normal(size=(3, 1)).astype(np.float32)), dev(rng.normal(size=(40, 1)).astype(np.float32))
+    y0 = ctx.picasso_f2f_forward(tex, bary, dev(poff), w)
+    t0, _ = ctx.picasso_f2f_backward(g, tex, bary, dev(poff), w)
+    tex2, bary2 = (torch.cat([torch.zeros((shift, t.shape[1]), device="cuda:0"), t]) for t in (tex, bary))
+    print("points behind 2^24", flush=True)
+    y1 = ctx.picasso_f2f_forward(tex2, bary2, dev(poff + shift), w)
+    t1, _ = ctx.picasso_f2f_backward(g, tex2, bary2, dev(poff + shift), w)
+    assert torch.allclose(y0, y1, rtol=0, atol=float(16 * EPS * y0.abs().max())) and torch.equal(t0, t1[shift:])
+    assert not t1[:shift].any() and not t0[: poff[0]].any()
