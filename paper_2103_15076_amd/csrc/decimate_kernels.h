@@ -141,14 +141,14 @@ __device__ __forceinline__ u32 edge_of_priority(const TieBreak& tb, u64 p) {
 
 // Validates and copies the inputs into the workspace; emits the (vertex,
 // incidence) pairs whose stable sort is the vertex->facet CSR.
-enum { COUNT_NONE = 0, COUNT_SMALL = 1, COUNT_LARGE = 2 };
+enum { COUNT_NONE = 0, COUNT_SMALL = 1, COUNT_LARGE = 2, COUNT_XL = 3 };
 
 // Incidence key of corner i of the facet array: (vertex << fbits) | facet.
 struct IncidenceKeys {
     const int* fcur;
     int fbits;
     __device__ __forceinline__ u64 operator()(long long i) const {
-        return ((u64)(u32)fcur[i] << fbits) | (u64)(u32)(i / 3);
+        return ((u64)(u32)fcur[i] << fbits) | (u64)((u32)i / 3u);
     }
 };
 
@@ -159,9 +159,8 @@ struct EdgeKeys {
     int vbits;
     u64 sentinel;
     __device__ __forceinline__ u64 operator()(long long i) const {
-        const long long f = i / 3;
-        const int sl = (int)(i - 3 * f);
-        const int a = fcur[i], b = fcur[3 * f + (sl == 2 ? 0 : sl + 1)];
+        const u32 f = (u32)i / 3u, sl = (u32)i - 3u * f;  // (a corner's number fits 31 bits; 64-bit division is slow)
+        const int a = fcur[i], b = fcur[sl == 2u ? i - 2 : i + 1];
         const int lo = min(a, b), hi = max(a, b);
         return (lo == hi) ? sentinel : (((u64)(u32)lo << vbits) | (u64)(u32)hi);
     }
@@ -206,7 +205,8 @@ struct HeaderInit {
 // kernel also adds the keys' top 8- / 12-bit digits (bits [ishift, ...)) to ihist, the histogram
 // that the sort of the keys starts from (zero on entry; see quadric_rows_kernel); that sort makes
 // the keys again from the validated facet array (IncidenceKeys), so they are written out (ikey)
-// only for a sort that needs them in memory.
+// only for a sort that needs them in memory.  COUNT_XL: the digit is as wide as xl_mask says and counted in
+// memory (prim::bucket_sort_xl).
 template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
                                                      const int* __restrict__ facets, int F, int B,
@@ -215,9 +215,10 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                                                      int* __restrict__ fcur, u64* __restrict__ ikey, int fbits,
                                                      int ishift, u32* __restrict__ ihist, State* st,
                                                      u32* __restrict__ msd_hist, int s0_follows, HeaderInit init,
-                                                     float4* __restrict__ planes) {
+                                                     float4* __restrict__ planes, u32 xl_mask) {
     constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
-    __shared__ u32 hist[COUNT != COUNT_NONE ? RADIX : 1];
+    constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
+    __shared__ u32 hist[IN_LDS ? RADIX : 1];
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     const bool single = init.hdr != nullptr;  // one mesh, whose ranges are [0, N) and [0, F): the tables are not read here
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
     }
     // the edge-key sort's digit counts and cursors start every round at zero (see edge_keys_kernel)
     for (int i = g; i < 2 * prim::MSD_HIST_WORDS; i += stride) msd_hist[i] = 0;
-    if constexpr (COUNT != COUNT_NONE) {
+    if constexpr (IN_LDS) {
         for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = 0;
         __syncthreads();
     }
@@ -276,7 +277,9 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                 k = ((u64)(u32)a << fbits) | (u64)(u32)f;
                 if (ikey) ikey[3 * (size_t)f + c] = k;
             }
-            if constexpr (COUNT != COUNT_NONE) {
+            if constexpr (COUNT == COUNT_XL) {
+                prim::xl_count(ihist, ok, (u32)(k >> ishift) & xl_mask);
+            } else if constexpr (IN_LDS) {
                 // neighbouring facets mostly refer to vertices with the same leading bits: the lanes of a
                 // wave that share a digit count themselves with a single LDS atomic
                 const u32 d = (u32)(k >> ishift) & (u32)(RADIX - 1);
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         // the facet's plane, once per facet, for the vertex quadrics that S0 sums from it
         if (planes && ok) planes[f] = facet_plane(verts, corner[0], corner[1], corner[2]);
     }
-    if constexpr (COUNT != COUNT_NONE) {
+    if constexpr (IN_LDS) {
         __syncthreads();
         for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
             const u32 c = hist[i];
@@ -486,11 +489,12 @@ template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(const int* __restrict__ fcur, State* st, int cur, int vbits,
                                                           u64* __restrict__ keys, u64* __restrict__ vmin0,
                                                           u64* __restrict__ vmin1, int* __restrict__ mate,
-                                                          RoundTab R, int shift, u32* __restrict__ msd_hist) {
+                                                          RoundTab R, int shift, u32* __restrict__ msd_hist, u32 xl_mask) {
     constexpr int ITEMS = COUNT == COUNT_LARGE ? prim::SORT_ITEMS_BIG : prim::SORT_ITEMS_SMALL;
     constexpr int TILE = BLOCK * ITEMS;
     constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
-    __shared__ u32 hist[COUNT != COUNT_NONE ? RADIX : 1];
+    constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
+    __shared__ u32 hist[IN_LDS ? RADIX : 1];
     const int nf = st->nf[cur], nv = st->nv[cur];
     const long long n = 3ll * nf;
     const int stride = gridDim.x * BLOCK;
@@ -503,7 +507,7 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(const int* __restrict_
     }
     if (blockIdx.x == 0) round_begin_block(R, cur, st);
     for (long long tile = blockIdx.x; tile * TILE < n; tile += gridDim.x) {
-        if constexpr (COUNT != COUNT_NONE) {
+        if constexpr (IN_LDS) {
             for (int i = t; i < RADIX; i += BLOCK) hist[i] = 0;
             __syncthreads();
         }
@@ -516,7 +520,9 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(const int* __restrict_
                 k = EdgeKeys{fcur, vbits, sentinel}(idx);
                 if (keys) keys[idx] = k;  // (the counted sorts make the keys again from fcur)
             }
-            if constexpr (COUNT != COUNT_NONE) {
+            if constexpr (COUNT == COUNT_XL) {
+                prim::xl_count(msd_hist, ok, (u32)(k >> shift) & xl_mask);
+            } else if constexpr (IN_LDS) {
                 // the lower vertices of neighbouring corners mostly share their leading bits: the lanes of
                 // a wave that share a digit count themselves with a single LDS atomic
                 const u32 d = (u32)(k >> shift) & (u32)(RADIX - 1);
@@ -524,7 +530,7 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(const int* __restrict_
                 if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
             }
         }
-        if constexpr (COUNT != COUNT_NONE) {
+        if constexpr (IN_LDS) {
             __syncthreads();
             for (int i = t; i < RADIX; i += BLOCK) {
                 const u32 c = hist[i];

@@ -83,6 +83,7 @@ struct picasso_ctx {
     u64* s0_key[2] = {nullptr, nullptr};  // incidence keys (vertex, facet) of S0 and their sort's second buffer
     prim::SortScratch sort_sc_s0{};
     u32* hist12_s0 = nullptr;
+    prim::XlScratch xl{}, xl_s0{};  // the same for the sorts of very large inputs
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     int64_t opt_overlap = 1;
@@ -224,6 +225,14 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->sort_sc_s0.table = cv.take<u32>((size_t)256 * x->sort_sc_s0.T);
     x->sort_sc_s0.totals = cv.take<u32>(256);
     x->hist12_s0 = cv.take<u32>(3 * prim::MSD_HIST_WORDS);
+    if ((long long)h > prim::BUCKET_SORT_LARGE_MAX_KEYS) {
+        const size_t words = prim::xl_hist_words((long long)h);
+        for (prim::XlScratch* q : {&x->xl, &x->xl_s0}) {
+            q->hist = cv.take<u32>(words);
+            q->starts = cv.take<u32>(words);
+            q->cursor = cv.take<u32>(words);
+        }
+    }
     x->voff[1] = cv.take<int>(b + 1);
     x->nrem = cv.take<int>(b);
     x->segstart = cv.take<int>(b);
@@ -300,8 +309,9 @@ struct KernelBracket {
 inline int sort_by_vertex_path(long long n_max, int key_bits) {
     if (n_max <= 0) return COUNT_NONE;
     if (n_max <= prim::BUCKET_SORT_MAX_KEYS && key_bits > prim::BUCKET_MSD_BITS) return COUNT_SMALL;
-    if (n_max <= prim::BUCKET_SORT_LARGE_MAX_KEYS && key_bits > prim::BUCKET_LARGE_MSD_BITS) return COUNT_LARGE;
-    return COUNT_NONE;
+    if (n_max <= prim::BUCKET_SORT_LARGE_MAX_KEYS)
+        return key_bits > prim::BUCKET_LARGE_MSD_BITS ? COUNT_LARGE : COUNT_NONE;
+    return key_bits > prim::xl_digit_bits(n_max, key_bits) ? COUNT_XL : COUNT_NONE;
 }
 
 // `uq` (keys without values, bucket sorts only): the sort also does the count pass of the compaction
@@ -309,7 +319,8 @@ inline int sort_by_vertex_path(long long n_max, int key_bits) {
 template <typename K, bool HAS_VAL, class Src = prim::ArrayKeys<K>>
 int sort_by_vertex(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_ptr, int n_max, int key_bits,
                    const prim::SortScratch& sc, u32* hist12, prim::LaunchTimer* lt = nullptr, int tag = 0,
-                   bool counted = false, const Src* src = nullptr, const prim::UniqueCount<K>* uq = nullptr) {
+                   bool counted = false, const Src* src = nullptr, const prim::UniqueCount<K>* uq = nullptr,
+                   const prim::XlScratch* xl = nullptr) {
     const int how = sort_by_vertex_path(n_max, key_bits);
     if (how == COUNT_SMALL)
         return prim::bucket_sort<K, HAS_VAL, Src>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, lt, tag, counted,
@@ -317,6 +328,10 @@ int sort_by_vertex(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_p
     if (how == COUNT_LARGE)
         return prim::bucket_sort_large<K, HAS_VAL, Src>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, hist12, lt, tag,
                                                         counted, src, uq);
+    if constexpr (!HAS_VAL) {
+        if (how == COUNT_XL && xl)
+            return prim::bucket_sort_xl<K, Src>(s, k0, k1, n_ptr, n_max, key_bits, *xl, lt, tag, counted, src, uq);
+    }
     return prim::radix_sort<K, HAS_VAL>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, lt, tag);
 }
 
@@ -337,14 +352,20 @@ int issue_edge_prefix(picasso_ctx* c, hipStream_t st_, int B, int round_, int cu
     if (how == COUNT_SMALL)
         edge_keys_kernel<COUNT_SMALL><<<prim::sort_tiles(H_, prim::SORT_ITEMS_SMALL), BLOCK, 0, st_>>>(
             c->fbuf[cur_], c->st, cur_, vbits_, nullptr, c->vmin[0], c->vmin[1], c->mate, rt,
-            prim::bucket_sort_low_bits(kb), c->hist12);
+            prim::bucket_sort_low_bits(kb), c->hist12, 0u);
     else if (how == COUNT_LARGE)
         edge_keys_kernel<COUNT_LARGE><<<prim::sort_tiles(H_, prim::SORT_ITEMS_BIG), BLOCK, 0, st_>>>(
             c->fbuf[cur_], c->st, cur_, vbits_, nullptr, c->vmin[0], c->vmin[1], c->mate, rt,
-            kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12);
-    else
+            kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12, 0u);
+    else if (how == COUNT_XL) {
+        const int bits = prim::xl_digit_bits(H_, kb);
+        prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, st_>>>(c->xl.hist, 1 << bits, 0u);
+        edge_keys_kernel<COUNT_XL><<<grid_for(std::max(nfb, nvt), 8192), BLOCK, 0, st_>>>(
+            c->fbuf[cur_], c->st, cur_, vbits_, nullptr, c->vmin[0], c->vmin[1], c->mate, rt, kb - bits, c->xl.hist,
+            (1u << bits) - 1u);
+    } else
         edge_keys_kernel<COUNT_NONE><<<grid_for(std::max(3 * nfb, nvt), 8192), BLOCK, 0, st_>>>(
-            c->fbuf[cur_], c->st, cur_, vbits_, c->key64[0], c->vmin[0], c->vmin[1], c->mate, rt, 0, nullptr);
+            c->fbuf[cur_], c->st, cur_, vbits_, c->key64[0], c->vmin[0], c->vmin[1], c->mate, rt, 0, nullptr, 0u);
     skeys = c->key64[0];
     const u64 sentinel_ = (vbits_ >= 32) ? ~0ull : ((1ull << (2 * vbits_)) - 1ull);
     bool counted_firsts = false;  // the sort has left the unique step's tile counts
@@ -364,8 +385,9 @@ int issue_edge_prefix(picasso_ctx* c, hipStream_t st_, int B, int round_, int cu
         int where = sort_by_vertex<u64, false, EdgeKeys>(st_, c->key64[0], c->key64[1], nullptr, nullptr, &c->st->nh,
                                                          H_, 2 * vbits_, c->sort_sc, c->hist12,
                                                          c->kt_this_call ? &c->kt : nullptr, round_, counted, &src,
-                                                         counted ? &uq : nullptr);
+                                                         counted ? &uq : nullptr, &c->xl);
         if (where < 0) return PICASSO_ERR_HIP;
+        if (counted) prim::compact_scan_sums(st_, &c->st->nh, H_, c->tilesum);
         skeys = where ? c->key64[1] : c->key64[0];
     }
     if (!counted_firsts) {
@@ -399,16 +421,22 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     if (how == COUNT_SMALL)
         init_kernel<COUNT_SMALL><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0],
                                                         c->cid, c->fbuf[0], ikey, fbits, prim::bucket_sort_low_bits(kb),
-                                                        c->hist12_s0, c->st, c->hist12, s0, init, planes);
+                                                        c->hist12_s0, c->st, c->hist12, s0, init, planes, 0u);
     else if (how == COUNT_LARGE)
         init_kernel<COUNT_LARGE><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0],
                                                         c->cid, c->fbuf[0], ikey, fbits,
                                                         kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12_s0, c->st, c->hist12,
-                                                        s0, init, planes);
-    else
+                                                        s0, init, planes, 0u);
+    else if (how == COUNT_XL) {
+        const int bits = prim::xl_digit_bits(3ll * F, kb);
+        prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, s>>>(c->xl_s0.hist, 1 << bits, 0u);
+        init_kernel<COUNT_XL><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid,
+                                                     c->fbuf[0], ikey, fbits, kb - bits, c->xl_s0.hist, c->st, c->hist12,
+                                                     s0, init, planes, (1u << bits) - 1u);
+    } else
         init_kernel<COUNT_NONE><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0],
                                                        c->cid, c->fbuf[0], ikey, fbits, 0, nullptr, c->st, c->hist12,
-                                                       s0, init, planes);
+                                                       s0, init, planes, 0u);
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }
 
@@ -422,7 +450,8 @@ int run_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts, int
         int where = sort_by_vertex<u64, false, IncidenceKeys>(s, c->s0_key[0], c->s0_key[1], nullptr, nullptr,
                                                                   nullptr, H, kb, c->sort_sc_s0, c->hist12_s0,
                                                                   c->kt_this_call ? &c->kt : nullptr,
-                                                                  PICASSO_KERNEL_SORT_INCIDENCE << 8, counted, &src);
+                                                                  PICASSO_KERNEL_SORT_INCIDENCE << 8, counted, &src,
+                                                                  nullptr, &c->xl_s0);
         if (where < 0) return PICASSO_ERR_HIP;
         const u64* skey = where ? c->s0_key[1] : c->s0_key[0];
         const int tiles = (H + QR_TILE - 1) / QR_TILE;

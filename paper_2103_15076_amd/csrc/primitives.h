@@ -1405,6 +1405,179 @@ inline int bucket_sort_large(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, cons
 }
 
 // ---------------------------------------------------------------------------
+// Keys without values beyond BUCKET_SORT_LARGE_MAX_KEYS: the same two sweeps (partition on a top digit, then one workgroup
+// per bucket), with a digit as wide as the input needs for buckets of about a thousand keys.  Arrays with one word
+// per digit then no longer fit LDS; a tile of mesh keys holds few distinct digits, though, so it counts them in a small hash
+// table.  Bound by memory: 8 bytes read and 8 written per key and sweep (plus 4 where keys are made on the fly),
+// where plain radix passes read every key twice and wrote it once for every 8 bits (61 M keys of 48 bits: 6 passes,
+// 2.9 ms; this way 0.5 ms).
+// ---------------------------------------------------------------------------
+constexpr int XL_BITS_MIN = 13, XL_BITS_MAX = 22;
+constexpr long long XL_BUCKET_KEYS = 1024;  // keys per bucket aimed at (vertex ids need not fill their bit range: up to twice that)
+inline int xl_bits_for(long long n) {
+    int b = XL_BITS_MIN;
+    while (b < XL_BITS_MAX - 2 && (XL_BUCKET_KEYS << b) < n) ++b;
+    return b;
+}
+// Up to two bits more where the bits below the digit then fit the 32 that the per-bucket kernel keeps in LDS.
+inline int xl_digit_bits(long long n, int key_bits) {
+    const int b = xl_bits_for(n), want = key_bits - 32;
+    return want > b && want <= b + 2 ? want : b;
+}
+// words of the count, first-position and cursor arrays for inputs of up to n_cap keys
+inline size_t xl_hist_words(long long n_cap) { return (size_t)1 << (xl_bits_for(n_cap) + 2); }
+
+struct XlScratch {
+    u32* hist = nullptr;    // keys per digit
+    u32* starts = nullptr;  // first position of every digit's range
+    u32* cursor = nullptr;  // next free position in it
+};
+
+// hist[digit] += 1 for the lanes with `ok`, those of a wave that share a digit with one atomic.  By all lanes of a wave.
+__device__ __forceinline__ void xl_count(u32* __restrict__ hist, bool ok, u32 d) {
+    const u64 same = wave_same_digit_lanes(ok, d);
+    if (ok && (same & lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
+}
+
+template <typename K, class Src>
+__global__ __launch_bounds__(BLOCK) void xl_count_kernel(Src kin, const int* n_ptr, int n_host, int shift, u32 mask,
+                                                         u32* __restrict__ hist) {
+    constexpr int ITEMS = 4;
+    const int n = load_count(n_ptr, n_host);
+    const long long base = (long long)blockIdx.x * (BLOCK * ITEMS);
+    if (base >= n) return;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const long long idx = base + (long long)i * BLOCK + threadIdx.x;
+        const bool ok = idx < n;
+        xl_count(hist, ok, ok ? digit_of<K>(kin(idx), shift, mask) : 0u);
+    }
+}
+
+// starts = cursor = exclusive prefix sums of hist[0, R), R a multiple of XL_SCAN_DIGITS: every workgroup adds up what lies
+// in front of its digits by itself.  zero[0, n_zero) is cleared on the way (for the kernel after the next).
+constexpr int XL_SCAN_ITEMS = 16, XL_SCAN_DIGITS = BLOCK * XL_SCAN_ITEMS;
+__global__ __launch_bounds__(BLOCK) void xl_starts_kernel(const u32* __restrict__ hist, u32* __restrict__ starts,
+                                                          u32* __restrict__ cursor, int* __restrict__ zero, int n_zero) {
+    __shared__ u32 smem[WAVES];
+    const int t = threadIdx.x, d0 = blockIdx.x * XL_SCAN_DIGITS;
+    for (int i = blockIdx.x * BLOCK + t; i < n_zero; i += gridDim.x * BLOCK) zero[i] = 0;
+    const uint4* h4 = reinterpret_cast<const uint4*>(hist);
+    u32 before = 0;
+#pragma unroll 8
+    for (int i = t; i < d0 / 4; i += BLOCK) {
+        const uint4 q = h4[i];
+        before += (q.x + q.y) + (q.z + q.w);
+    }
+    before = block_sum(before, smem);
+    u32 c[XL_SCAN_ITEMS], sum = 0, tot;
+#pragma unroll
+    for (int j = 0; j < XL_SCAN_ITEMS; ++j) {
+        c[j] = hist[d0 + t * XL_SCAN_ITEMS + j];
+        sum += c[j];
+    }
+    u32 run = before + block_exclusive_scan(sum, smem, tot);
+#pragma unroll
+    for (int j = 0; j < XL_SCAN_ITEMS; ++j) {
+        const int d = d0 + t * XL_SCAN_ITEMS + j;
+        starts[d] = run;
+        cursor[d] = run;
+        run += c[j];
+    }
+}
+
+// The partition: a tile's distinct digits are entered into a hash table in LDS (the lanes of a wave that share a digit
+// by the first of them), which counts their keys and so ranks them; each digit then takes its share of
+// its range with one returning atomic.  A digit that finds no place within XL_PROBES steps (a tile without locality)
+// takes its places right away.  The order of the keys inside a range does not matter (see msd_scatter_kernel).
+constexpr int XL_ITEMS = 16, XL_SLOTS = 1024, XL_PROBES = 8;
+template <typename K, class Src>
+__global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(Src kin, K* __restrict__ kout, const int* n_ptr, int n_host, int shift,
+                                                           u32 mask, u32* __restrict__ cursor) {
+    constexpr int TILE = BLOCK * XL_ITEMS;
+    constexpr u32 NONE = 0xFFFFFFFFu;
+    __shared__ u32 digit[XL_SLOTS];
+    __shared__ u32 count[XL_SLOTS];  // keys of the tile with that digit, then where they go
+    const int n = load_count(n_ptr, n_host);
+    const long long base = (long long)blockIdx.x * TILE;
+    if (base >= n) return;
+    const int t = threadIdx.x, w = wave_id(), lane = lane_id();
+    const u64 lt = lanemask_lt();
+    for (int i = t; i < XL_SLOTS; i += BLOCK) {
+        digit[i] = NONE;
+        count[i] = 0;
+    }
+    K key[XL_ITEMS];
+    u32 place[XL_ITEMS], rank[XL_ITEMS];
+#pragma unroll
+    for (int i = 0; i < XL_ITEMS; ++i) {
+        const long long idx = base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane;
+        key[i] = idx < n ? kin(idx) : (K)0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < XL_ITEMS; ++i) {
+        const bool ok = base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n;
+        const u32 d = digit_of<K>(key[i], shift, mask);
+        const u64 same = wave_same_digit_lanes(ok, d);
+        u32 slot = NONE, b = 0;
+        if (ok && (same & lt) == 0) {
+            u32 h = (d * 0x9E3779B1u) >> 22;  // 10 bits
+            for (int p = 0; p < XL_PROBES; ++p) {
+                const u32 old = atomicCAS(&digit[h], NONE, d);
+                if (old == NONE || old == d) {
+                    slot = h;
+                    break;
+                }
+                h = (h + 1) & (XL_SLOTS - 1);
+            }
+            b = slot != NONE ? atomicAdd(&count[slot], (u32)__popcll(same)) : atomicAdd(&cursor[d], (u32)__popcll(same));
+        }
+        const int lead = ok ? __ffsll((long long)same) - 1 : lane;
+        place[i] = (u32)__shfl((int)slot, lead, 64);
+        rank[i] = (u32)__shfl((int)b, lead, 64) + (u32)__popcll(same & lt);
+    }
+    __syncthreads();
+    for (int i = t; i < XL_SLOTS; i += BLOCK)
+        if (digit[i] != NONE) count[i] = atomicAdd(&cursor[digit[i]], count[i]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < XL_ITEMS; ++i) {
+        if (base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n) {
+            const u32 pos = (place[i] != NONE ? count[place[i]] : 0u) + rank[i];
+            if (pos < (u32)n) kout[pos] = key[i];  // (always, when hist and cursor are as described)
+        }
+    }
+}
+
+// Result in k0 (returns 0; <0 on a launch error).  `counted`: hist holds the keys' digits already (xl_count), and the
+// keys come from *src; else they are in k0 and are counted here.
+template <typename K, class Src>
+inline int bucket_sort_xl(hipStream_t s, K* k0, K* k1, const int* n_ptr, int n_max, int key_bits, const XlScratch& xl,
+                          LaunchTimer* lt, int tag, bool counted, const Src* src, const UniqueCount<K>* uq) {
+    const int bits = xl_digit_bits(n_max, key_bits), low = key_bits - bits;
+    const u32 mask = (1u << bits) - 1u;
+    static_assert((1 << XL_BITS_MIN) % XL_SCAN_DIGITS == 0, "whole workgroups of the scan");
+    if (!counted) {
+        fill_u32_kernel<<<(1 << bits) / BLOCK, BLOCK, 0, s>>>(xl.hist, 1 << bits, 0u);
+        xl_count_kernel<K, ArrayKeys<K>><<<sort_tiles(n_max, 4), BLOCK, 0, s>>>(ArrayKeys<K>{k0}, n_ptr, n_max, low, mask, xl.hist);
+    }
+    const UniqueCount<K> none{};
+    const UniqueCount<K>& u = uq ? *uq : none;
+    xl_starts_kernel<<<(1 << bits) / XL_SCAN_DIGITS, BLOCK, 0, s>>>(xl.hist, xl.starts, xl.cursor, u.tilesum, u.tiles);
+    const int tiles = sort_tiles(n_max, XL_ITEMS);
+    if (src && counted)
+        xl_scatter_kernel<K, Src><<<tiles, BLOCK, 0, s>>>(*src, k1, n_ptr, n_max, low, mask, xl.cursor);
+    else
+        xl_scatter_kernel<K, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, mask, xl.cursor);
+    const bool timed = lt && lt->begin(s, tag);
+    launch_bucket_keys_kernel<K, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096>(1 << bits, s, k1, k0, xl.hist, low, xl.starts, u.sentinel, u.tilesum, u.tile_shift);
+    if (timed) lt->end(s);
+    if (hipGetLastError() != hipSuccess) return -1;
+    return 0;
+}
+
+// ---------------------------------------------------------------------------
 // Flag compaction.  count kernel: tilesum[tile] = number of i in the tile with
 // pred(i).  scatter kernel: calls out(i, rank) for every flagged i, rank = its
 // position among flagged items in index order; writes the grand total.
@@ -1463,18 +1636,36 @@ __global__ __launch_bounds__(BLOCK) void tile_count_kernel(Pred pred, const int*
     if (threadIdx.x == 0) tilesum[blockIdx.x] = (int)(smem[0] + smem[1] + smem[2] + smem[3]);
 }
 
-// In-place exclusive scan of a[0..T) by one workgroup (used when there are many tiles).
-__global__ __launch_bounds__(BLOCK) void scan_tilesums_kernel(int* __restrict__ a, const int* n_ptr, int n_host,
-                                                              int tile_items) {
-    __shared__ u32 smem[WAVES];
+// In-place exclusive scan of a[0..T) by one workgroup (used when there are many tiles): 8 consecutive sums per thread
+// and step, the next step's loads issued before the scan of this one.  (15,000 tiles: 36 us with one sum per thread.)
+constexpr int SCAN_TILES_THREADS = 1024, SCAN_TILES_ITEMS = 8;
+__global__ __launch_bounds__(SCAN_TILES_THREADS) void scan_tilesums_kernel(int* __restrict__ a, const int* n_ptr, int n_host,
+                                                                           int tile_items) {
+    constexpr int ITEMS = SCAN_TILES_ITEMS, STEP = SCAN_TILES_THREADS * ITEMS;
+    __shared__ u32 smem[SCAN_TILES_THREADS / 64];
     const int n = load_count(n_ptr, n_host);
     const int T = (int)(((long long)n + tile_items - 1) / tile_items);
+    const int t = threadIdx.x;
+    u32 v[ITEMS], next[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) next[j] = t * ITEMS + j < T ? (u32)a[t * ITEMS + j] : 0u;
     u32 carry = 0;
-    for (int c = 0; c < T; c += BLOCK) {
-        const int i = c + threadIdx.x;
-        u32 v = i < T ? (u32)a[i] : 0u, tot;
-        u32 ex = block_exclusive_scan(v, smem, tot);
-        if (i < T) a[i] = (int)(carry + ex);
+    for (int c = 0; c < T; c += STEP) {
+        u32 sum = 0, tot;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            v[j] = next[j];
+            sum += v[j];
+            const int i = c + STEP + t * ITEMS + j;
+            next[j] = i < T ? (u32)a[i] : 0u;
+        }
+        u32 run = carry + wide_block_exclusive_scan<SCAN_TILES_THREADS / 64>(sum, smem, tot);
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const int i = c + t * ITEMS + j;
+            if (i < T) a[i] = (int)run;
+            run += v[j];
+        }
         carry += tot;
     }
 }
@@ -1553,9 +1744,16 @@ inline void compact_impl(hipStream_t s, PredCount pc, PredScatter ps, Out out, c
     const int tiles = compact_tiles(n_max > 0 ? n_max : 1, CHUNKS);
     tile_count_kernel<PredCount, CHUNKS><<<tiles, BLOCK, 0, s>>>(pc, n_ptr, n_max, tilesum);
     const int prefixed = tiles > COMPACT_MAX_SUMMED_TILES;
-    if (prefixed) scan_tilesums_kernel<<<1, BLOCK, 0, s>>>(tilesum, n_ptr, n_max, BLOCK * CHUNKS);
+    if (prefixed) scan_tilesums_kernel<<<1, SCAN_TILES_THREADS, 0, s>>>(tilesum, n_ptr, n_max, BLOCK * CHUNKS);
     tile_scatter_kernel<PredScatter, Out, CHUNKS>
         <<<tiles, BLOCK, 0, s>>>(ps, out, n_ptr, n_max, tilesum, prefixed, total_out);
+}
+
+// What follows the count where the counts were made otherwise: the scan of the tile sums, where compact_scatter wants it.
+inline void compact_scan_sums(hipStream_t s, const int* n_ptr, int n_max, int* tilesum) {
+    const int chunks = compact_chunks_for(n_max);
+    if (compact_tiles(n_max > 0 ? n_max : 1, chunks) > COMPACT_MAX_SUMMED_TILES)
+        scan_tilesums_kernel<<<1, SCAN_TILES_THREADS, 0, s>>>(tilesum, n_ptr, n_max, BLOCK * chunks);
 }
 
 // The two halves of compact() on their own, for callers that put other work between them
@@ -1568,8 +1766,7 @@ inline void compact_count(hipStream_t s, PredCount pc, const int* n_ptr, int n_m
         case 4: tile_count_kernel<PredCount, 4><<<tiles, BLOCK, 0, s>>>(pc, n_ptr, n_max, tilesum); break;
         default: tile_count_kernel<PredCount, 16><<<tiles, BLOCK, 0, s>>>(pc, n_ptr, n_max, tilesum);
     }
-    if (tiles > COMPACT_MAX_SUMMED_TILES)
-        scan_tilesums_kernel<<<1, BLOCK, 0, s>>>(tilesum, n_ptr, n_max, BLOCK * compact_chunks_for(n_max));
+    compact_scan_sums(s, n_ptr, n_max, tilesum);
 }
 
 template <class PredScatter, class Out>

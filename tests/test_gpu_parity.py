@@ -519,6 +519,33 @@ def test_beyond_the_bucket_sorts(pk, oracle):
         c.close()
 
 
+@pytest.mark.parametrize("what", ["scrambled", "few_vertices"])
+def test_very_large_sorts_without_locality(pk, oracle, what):
+    """More than 2^23 half-edges where a tile of keys holds as many leading digits as keys (random vertex numbers and
+    facet order: digits that find no place in the tile's table), and on so few vertices that the keys have no
+    more bits than the digit (plain LSD passes)."""
+    rng = np.random.default_rng(5)
+    if what == "scrambled":
+        V, F, _ = meshgen.room_scene_sized(31, 1_500_000, room=(30.0, 20.0, 3.0), n_boxes=300)
+        perm = rng.permutation(V.shape[0])
+        V2 = np.empty_like(V)
+        V2[perm] = V
+        V, F = V2, perm[F].astype(np.int32)[rng.permutation(F.shape[0])]
+    else:
+        V = rng.normal(size=(60, 3)).astype(np.float32)
+        F = rng.integers(0, 60, size=(2_900_000, 3)).astype(np.int32)
+    assert 3 * F.shape[0] > (1 << 23)
+    target = V.shape[0] // 2
+    c = pk.Context(V.shape[0], F.shape[0], 1, device=0)
+    try:
+        print(f"{what}: N={V.shape[0]} F={F.shape[0]} target={target}", flush=True)
+        st, vo, fo, cid = c.picasso_decimate(dev(V), dev(F), target)
+        print("  gpu done; oracle...", flush=True)
+        assert_same_result(st, vo, fo, cid, oracle.decimate(V, F, target))
+    finally:
+        c.close()
+
+
 def test_config_batch_hierarchy(ctx, oracle):
     """16 room meshes through 4 successive levels, each to 40 % of the vertices;
     the cluster maps of all levels are kept and compared."""
