@@ -38,7 +38,7 @@ using pool::row_lane;
 using pool::store_row;
 
 // Index arrays come from the caller.  They are checked once, where the corner lists are built
-// (corner_keys_kernel reports a bad index); the kernels below only make sure that a bad one
+// (csr_count_kernel reports a bad index); the kernels below only make sure that a bad one
 // cannot reach outside the arrays: it is read as index 0.
 __device__ __forceinline__ int in_range_or_zero(int i, int n) { return ((unsigned)i < (unsigned)n) ? i : 0; }
 
@@ -56,6 +56,8 @@ inline dim3 xcd_grid(dim3 g) { return dim3((g.x + 7) / 8 * 8, g.y); }
 // The two indexes off[v], off[v + 1] and the three of a facet in one load each.
 struct __attribute__((packed, aligned(4))) Int2 { int a, b; };
 struct __attribute__((packed, aligned(4))) Int3 { int a, b, c; };
+struct __attribute__((packed, aligned(4))) Float3 { float a, b, c; };
+__device__ __forceinline__ Float3 load_point(const float* p, int i) { return *reinterpret_cast<const Float3*>(p + 3 * (size_t)i); }
 __device__ __forceinline__ Int2 load_pair(const int* p) { return *reinterpret_cast<const Int2*>(p); }
 __device__ __forceinline__ Int3 load_triple(const int* p) { return *reinterpret_cast<const Int3*>(p); }
 
@@ -72,10 +74,19 @@ __device__ __forceinline__ float quotient(float x, float n, float r) {
 // of Eq. "interpolate_num", k = floor((A - A_min) / (A_max - A_min)) * alpha +
 // beta with A_min, A_max over the facet's own mesh.  Areas are non-negative,
 // so their bit patterns order like their values and the per-mesh extremes are
-// taken with integer atomics (order-independent).
+// taken with integer atomics (order-independent), as the maxima of the pattern and of its complement.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int mesh_of_facet(const int* __restrict__ foff, int B, int f) {
-    int lo = 0, hi = B;  // invariant: foff[lo] <= f < foff[hi]
+// The meshes' facet offsets, up to MESH_OFFSETS meshes with the launch itself (no upload in front of it), else in memory.
+constexpr int MESH_OFFSETS = 64;
+struct MeshOffsets {
+    int B;
+    const int* far;  // null: here
+    int here[MESH_OFFSETS + 1];
+    __device__ __forceinline__ int operator[](int b) const { return far ? far[b] : here[b]; }
+};
+
+__device__ __forceinline__ int mesh_of_facet(const MeshOffsets& foff, int f) {
+    int lo = 0, hi = foff.B;  // invariant: foff[lo] <= f < foff[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (foff[mid] <= f) lo = mid; else hi = mid;
@@ -83,126 +94,160 @@ __device__ __forceinline__ int mesh_of_facet(const int* __restrict__ foff, int B
     return lo;
 }
 
+// The extremes of a mesh: its facets' workgroups spread over EXT_SLOTS cache lines, one atomic pair per workgroup (whose
+// facets nearly always belong to one mesh) after combining in LDS: atomics on one line, whichever words of it they
+// name, are served one after the other, about 10 ns each (1.9 M facets of 16 meshes: 143 us with a pair for every 256
+// facets on two words per mesh).
+constexpr int EXT_SLOTS = 8, EXT_PAD = 32;  // words: one 128-byte line per slot; word 0 = largest pattern, 1 = largest complement
+constexpr int GEO_ITEMS = 4;                // facets per lane
+__device__ __forceinline__ unsigned* ext_slot(unsigned* ext, int m) {
+    return ext + ((size_t)m * EXT_SLOTS + (blockIdx.x & (EXT_SLOTS - 1))) * EXT_PAD;
+}
+
 __global__ __launch_bounds__(BLOCK) void facet_geometry_kernel(const float* __restrict__ verts, int N,
-                                                               const int* __restrict__ facets, int F, int B,
-                                                               const int* __restrict__ foff,
+                                                               const int* __restrict__ facets, int F, MeshOffsets foff,
                                                                float* __restrict__ normals, float* __restrict__ areas,
-                                                               unsigned* __restrict__ amin, unsigned* __restrict__ amax,
+                                                               unsigned* __restrict__ ext /* or null */,
                                                                int* __restrict__ err) {
-    __shared__ unsigned smin, smax;
-    __shared__ int smesh, mixed;
-    const int f = blockIdx.x * BLOCK + threadIdx.x;
-    const bool in = f < F;
-    if (threadIdx.x == 0) {
-        smin = 0xFFFFFFFFu;
-        smax = 0u;
-        mixed = 0;
-        smesh = amin ? mesh_of_facet(foff, B, blockIdx.x * BLOCK) : 0;
-    }
-    __syncthreads();
-    int i0 = 0, i1 = 0, i2 = 0;
-    if (in) {
-        i0 = facets[3 * (size_t)f];
-        i1 = facets[3 * (size_t)f + 1];
-        i2 = facets[3 * (size_t)f + 2];
-        if (i0 < 0 || i0 >= N || i1 < 0 || i1 >= N || i2 < 0 || i2 >= N) {
-            atomicOr(err, 1);
-            i0 = i1 = i2 = 0;
+    __shared__ unsigned wmax[BLOCK / 64], wnmin[BLOCK / 64];
+    const int first = blockIdx.x * (BLOCK * GEO_ITEMS), last = min(first + BLOCK * GEO_ITEMS, F) - 1;
+    Int3 v[GEO_ITEMS];
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < GEO_ITEMS; ++j) {
+        const int f = first + j * BLOCK + (int)threadIdx.x;
+        v[j] = load_triple(facets + 3 * (size_t)min(f, last));
+        if (v[j].a < 0 || v[j].a >= N || v[j].b < 0 || v[j].b >= N || v[j].c < 0 || v[j].c >= N) {
+            bad = true;
+            v[j] = Int3{0, 0, 0};
         }
     }
-    const float* p0 = verts + 3 * (size_t)i0;
-    const float* p1 = verts + 3 * (size_t)i1;
-    const float* p2 = verts + 3 * (size_t)i2;
-    const float ax = p1[0] - p0[0], ay = p1[1] - p0[1], az = p1[2] - p0[2];
-    const float bx = p2[0] - p0[0], by = p2[1] - p0[1], bz = p2[2] - p0[2];
-    const float nx = ay * bz - az * by;
-    const float ny = az * bx - ax * bz;
-    const float nz = ax * by - ay * bx;
-    const float len = sqrtf((nx * nx + ny * ny) + nz * nz);
-    const float area = 0.5f * len;
-    if (in && areas) areas[f] = area;
-    if (in && normals) {
-        normals[3 * (size_t)f] = len > 0.0f ? nx / len : 0.0f;
-        normals[3 * (size_t)f + 1] = len > 0.0f ? ny / len : 0.0f;
-        normals[3 * (size_t)f + 2] = len > 0.0f ? nz / len : 0.0f;
+    if (bad) atomicOr(err, 1);
+    Float3 p[GEO_ITEMS][3];
+#pragma unroll
+    for (int j = 0; j < GEO_ITEMS; ++j) {
+        p[j][0] = load_point(verts, v[j].a);
+        p[j][1] = load_point(verts, v[j].b);
+        p[j][2] = load_point(verts, v[j].c);
     }
-    if (!amin) return;
-    // Extremes per mesh.  Thousands of atomics on one address queue up, so a workgroup whose facets
-    // all belong to one mesh (nearly every one) first combines them in LDS and issues one pair.
-    const bool counts = in && area == area;  // (a NaN area takes no part in the extremes)
-    const int m = counts ? mesh_of_facet(foff, B, f) : smesh;
-    if (m != smesh) mixed = 1;
-    __syncthreads();
-    if (mixed) {
-        if (counts) {
-            atomicMin(&amin[m], __float_as_uint(area));
-            atomicMax(&amax[m], __float_as_uint(area));
+    const int mesh0 = ext ? mesh_of_facet(foff, first) : 0;  // (the same in all lanes)
+    const bool one_mesh = !ext || foff[mesh0 + 1] > last;
+    unsigned hi = 0u, lo = 0u;
+#pragma unroll
+    for (int j = 0; j < GEO_ITEMS; ++j) {
+        const int f = first + j * BLOCK + (int)threadIdx.x;
+        const bool in = f <= last;
+        const float ax = p[j][1].a - p[j][0].a, ay = p[j][1].b - p[j][0].b, az = p[j][1].c - p[j][0].c;
+        const float bx = p[j][2].a - p[j][0].a, by = p[j][2].b - p[j][0].b, bz = p[j][2].c - p[j][0].c;
+        const float nx = ay * bz - az * by;
+        const float ny = az * bx - ax * bz;
+        const float nz = ax * by - ay * bx;
+        const float len = sqrtf((nx * nx + ny * ny) + nz * nz);
+        const float area = 0.5f * len;
+        if (in && areas) areas[f] = area;
+        if (in && normals) {
+            Float3 n;
+            n.a = len > 0.0f ? nx / len : 0.0f;
+            n.b = len > 0.0f ? ny / len : 0.0f;
+            n.c = len > 0.0f ? nz / len : 0.0f;
+            *reinterpret_cast<Float3*>(normals + 3 * (size_t)f) = n;
         }
-        return;
+        if (ext && in && area == area) {  // (a NaN area takes no part in the extremes)
+            const unsigned bits = __float_as_uint(area);
+            if (one_mesh) {
+                hi = max(hi, bits);
+                lo = max(lo, ~bits);
+            } else {
+                unsigned* e = ext_slot(ext, mesh_of_facet(foff, f));
+                atomicMax(&e[0], bits);
+                atomicMax(&e[1], ~bits);
+            }
+        }
     }
-    if (counts) {
-        atomicMin(&smin, __float_as_uint(area));
-        atomicMax(&smax, __float_as_uint(area));
+    if (!ext || !one_mesh) return;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        hi = max(hi, (unsigned)__shfl_xor((int)hi, d, 64));
+        lo = max(lo, (unsigned)__shfl_xor((int)lo, d, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        wmax[threadIdx.x >> 6] = hi;
+        wnmin[threadIdx.x >> 6] = lo;
     }
     __syncthreads();
-    if (threadIdx.x == 0 && smin <= smax) {
-        atomicMin(&amin[smesh], smin);
-        atomicMax(&amax[smesh], smax);
+    if (threadIdx.x < 2) {
+        const unsigned* wv = threadIdx.x ? wnmin : wmax;
+        atomicMax(ext_slot(ext, mesh0) + threadIdx.x, max(max(wv[0], wv[1]), max(wv[2], wv[3])));
     }
 }
 
-__global__ __launch_bounds__(BLOCK) void facet_level_kernel(const float* __restrict__ areas, int F, int B,
-                                                            const int* __restrict__ foff,
-                                                            const unsigned* __restrict__ amin,
-                                                            const unsigned* __restrict__ amax, int alpha, int beta,
+__device__ __forceinline__ void mesh_extremes(const unsigned* __restrict__ ext, int m, float& lo, float& hi) {
+    unsigned h = 0u, l = 0u;
+#pragma unroll
+    for (int k = 0; k < EXT_SLOTS; ++k) {
+        const unsigned* e = ext + ((size_t)m * EXT_SLOTS + k) * EXT_PAD;
+        h = max(h, e[0]);
+        l = max(l, e[1]);
+    }
+    lo = __uint_as_float(~l);
+    hi = __uint_as_float(h);
+}
+
+__global__ __launch_bounds__(BLOCK) void facet_level_kernel(const float* __restrict__ areas, int F, MeshOffsets foff,
+                                                            const unsigned* __restrict__ ext, int alpha, int beta,
                                                             int* __restrict__ level) {
-    const int f = blockIdx.x * BLOCK + threadIdx.x;
-    if (f >= F) return;
-    const int m = mesh_of_facet(foff, B, f);
-    const float lo = __uint_as_float(amin[m]), hi = __uint_as_float(amax[m]);
-    const float ratio = hi > lo ? (areas[f] - lo) / (hi - lo) : 0.0f;
-    level[f] = (int)floorf(ratio) * alpha + beta;
+    const int first = blockIdx.x * (BLOCK * GEO_ITEMS), last = min(first + BLOCK * GEO_ITEMS, F) - 1;
+    const int mesh0 = mesh_of_facet(foff, first);  // (the same in all lanes)
+    const bool one_mesh = foff[mesh0 + 1] > last;
+    float lo, hi;
+    mesh_extremes(ext, mesh0, lo, hi);
+#pragma unroll
+    for (int j = 0; j < GEO_ITEMS; ++j) {
+        const int f = first + j * BLOCK + (int)threadIdx.x;
+        if (f > last) break;
+        if (!one_mesh) mesh_extremes(ext, mesh_of_facet(foff, f), lo, hi);
+        const float ratio = hi > lo ? (areas[f] - lo) / (hi - lo) : 0.0f;
+        level[f] = (int)floorf(ratio) * alpha + beta;
+    }
 }
 
 // Fuzzy coefficients of the facets (Sec. 4.2): z_ft = |n_f - mu_t|^2 * inv_var_t,
-// pi_ft = exp(-z_ft) / sum_m exp(-z_fm).  One lane per facet, two passes over t.
+// pi_ft = exp(-z_ft) / sum_m exp(-z_fm).  One lane per facet; the workgroup's rows are made in LDS and written out
+// as one contiguous piece (up to FUZZY_LDS_T components; lanes writing T floats each at a stride of T, and
+// reading them back for the division, took 45 us for 1.9 M facets of 6 components).
+constexpr int FUZZY_LDS_T = 48;
+template <bool IN_LDS>
 __global__ __launch_bounds__(BLOCK) void fuzzy_kernel(const float* __restrict__ normals, int F,
                                                       const float* __restrict__ mu, const float* __restrict__ inv_var,
                                                       int T, float* __restrict__ pi) {
-    const int f = blockIdx.x * BLOCK + threadIdx.x;
-    if (f >= F) return;
-    const float nx = normals[3 * (size_t)f], ny = normals[3 * (size_t)f + 1], nz = normals[3 * (size_t)f + 2];
-    float sum = 0.0f;
-    for (int t = 0; t < T; ++t) {
-        const float dx = nx - mu[3 * t], dy = ny - mu[3 * t + 1], dz = nz - mu[3 * t + 2];
-        const float e = expf(-(((dx * dx + dy * dy) + dz * dz) * inv_var[t]));
-        pi[(size_t)f * T + t] = e;
-        sum = sum + e;
+    extern __shared__ float tile[];  // [BLOCK * T]
+    const int f0 = blockIdx.x * BLOCK, f = f0 + threadIdx.x;
+    if (f < F) {
+        const Float3 n = load_point(normals, f);
+        float* row = IN_LDS ? tile + threadIdx.x * T : pi + (size_t)f * T;
+        float sum = 0.0f;
+        for (int t = 0; t < T; ++t) {
+            const float dx = n.a - mu[3 * t], dy = n.b - mu[3 * t + 1], dz = n.c - mu[3 * t + 2];
+            const float e = expf(-(((dx * dx + dy * dy) + dz * dz) * inv_var[t]));
+            row[t] = e;
+            sum = sum + e;
+        }
+        const float r = 1.0f / sum;
+        for (int t = 0; t < T; ++t) row[t] = quotient(row[t], sum, r);
     }
-    for (int t = 0; t < T; ++t) pi[(size_t)f * T + t] = pi[(size_t)f * T + t] / sum;
-}
-
-// ---------------------------------------------------------------------------
-// Corners at every vertex: key (vertex << cbits) | corner for the sort, then the
-// corner list is the keys' low part.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void corner_keys_kernel(const int* __restrict__ facets, int H, int N, int cbits,
-                                                            unsigned long long* __restrict__ key,
-                                                            int* __restrict__ err) {
-    const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= H) return;
-    int v = facets[i];
-    if (v < 0 || v >= N) {
-        atomicOr(err, 1);
-        v = 0;
+    if constexpr (IN_LDS) {
+        __syncthreads();
+        const int n = min(BLOCK, F - f0) * T;
+        float* out = pi + (size_t)f0 * T;
+        for (int i = 4 * threadIdx.x; i < n; i += 4 * BLOCK) {
+            if (i + 4 <= n) {
+                const float4 q = *reinterpret_cast<const float4*>(tile + i);
+                store_row<pool::ROW_EVEN>(out + i, Pack{{q.x, q.y, q.z, q.w}}, 4);
+            } else {
+                for (int k = i; k < n; ++k) out[k] = tile[k];
+            }
+        }
     }
-    key[i] = ((unsigned long long)(unsigned)v << cbits) | (unsigned long long)(unsigned)i;
-}
-
-__global__ __launch_bounds__(BLOCK) void corner_list_kernel(const unsigned long long* __restrict__ skey, int H,
-                                                            int cbits, int* __restrict__ corners) {
-    const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i < H) corners[i] = (int)(skey[i] & ((1ull << cbits) - 1ull));
 }
 
 // ---------------------------------------------------------------------------
@@ -560,7 +605,6 @@ __global__ __launch_bounds__(BLOCK) void v2f_backward_kernel(const float* __rest
 // sum_k W_k T_k.  Points of facet f = poff[f] .. poff[f+1]; tex [P,C], bary [P,3].
 // One lane owns VEC channels of one facet and walks the facet's points in order.
 // ---------------------------------------------------------------------------
-struct __attribute__((packed, aligned(4))) Float3 { float a, b, c; };
 template <int KIND>
 __device__ __forceinline__ Float3 load_bary(const float* __restrict__ bary, int k) {
     return *reinterpret_cast<const Float3*>(row_at<KIND>(bary, k, 3, 0));

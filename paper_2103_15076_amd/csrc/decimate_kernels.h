@@ -300,17 +300,79 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
     if (err) atomicOr(&st->err, err);
 }
 
-// off[v] = first position of row v = key >> fbits in the sorted keys (CSR row starts)
-template <typename K>
-__global__ __launch_bounds__(BLOCK) void csr_offsets_kernel(const K* __restrict__ skey, int fbits, int H, int N,
-                                                            int* __restrict__ off) {
+// ---------------------------------------------------------------------------
+// Lists of items per row (corners of a vertex, members of a cluster) from an array that names every item's row:
+// the keys (row << ibits) | item are counted by their top digit, sorted (the partition makes them from the array again) and
+// taken apart.  Five launches with the one that tells the host.
+// ---------------------------------------------------------------------------
+struct RowKeys {
+    const int* row_of;  // [n]
+    int n_rows, ibits;
+    __device__ __forceinline__ u64 operator()(long long i) const {
+        const int r = row_of[i];
+        return ((u64)((u32)r < (u32)n_rows ? (u32)r : 0u) << ibits) | (u64)(u32)i;  // (a bad row counts as row 0 here)
+    }
+};
+
+// Adds the keys' digits to hist (COUNT as in init_kernel; COUNT_NONE: writes the keys out instead) and flags rows out
+// of range.
+constexpr int CSR_COUNT_ITEMS = 4;
+template <int COUNT>
+__global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, int shift, u32 xl_mask, u32* __restrict__ hist_out,
+                                                          u64* __restrict__ keys, int* __restrict__ err) {
+    constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
+    constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
+    constexpr int ITEMS = COUNT == COUNT_LARGE ? 16 : CSR_COUNT_ITEMS;
+    __shared__ u32 hist[IN_LDS ? RADIX : 1];
+    if constexpr (IN_LDS) {
+        for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = 0;
+        __syncthreads();
+    }
+    bool bad = false;
+#pragma unroll 4
+    for (int j = 0; j < ITEMS; ++j) {
+        const long long i = ((long long)blockIdx.x * ITEMS + j) * BLOCK + threadIdx.x;
+        const bool ok = i < n;
+        u64 k = 0;
+        if (ok) {
+            bad |= (u32)src.row_of[i] >= (u32)src.n_rows;
+            k = src(i);
+        }
+        const u32 d = (u32)(k >> shift);
+        if constexpr (COUNT == COUNT_XL) {
+            prim::xl_count(hist_out, ok, d & xl_mask);
+        } else if constexpr (IN_LDS) {
+            const u64 same = prim::wave_same_digit_lanes(ok, d & (u32)(RADIX - 1));
+            if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d & (u32)(RADIX - 1)], (u32)__popcll(same));
+        } else {
+            if (ok) keys[i] = k;
+        }
+    }
+    if constexpr (IN_LDS) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
+            const u32 c = hist[i];
+            if (c) atomicAdd(&hist_out[i], c);
+        }
+    }
+    if (bad) atomicOr(err, ERR_BIT_BAD_INDEX);
+}
+
+// off[r] = first position of row r in the sorted keys, items[i] = item at position i; the counting arrays of the sort go back
+// to zero for the next call.
+__global__ __launch_bounds__(BLOCK) void csr_finish_kernel(const u64* __restrict__ skey, int ibits, int n, int n_rows,
+                                                           int* __restrict__ off, int* __restrict__ items,
+                                                           u32* __restrict__ hist) {
     const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= H) return;
-    const int k = (int)(skey[i] >> fbits);
-    const int kp = i ? (int)(skey[i - 1] >> fbits) : -1;
-    for (int v = kp + 1; v <= k; ++v) off[v] = i;
-    if (i == H - 1)
-        for (int v = k + 1; v <= N; ++v) off[v] = H;
+    for (int h = i; h < 2 * prim::MSD_HIST_WORDS; h += gridDim.x * BLOCK) hist[h] = 0;
+    if (i >= n) return;
+    const u64 key = skey[i];
+    const int k = (int)(key >> ibits);
+    const int kp = i ? (int)(skey[i - 1] >> ibits) : -1;
+    items[i] = (int)(key & ((1ull << ibits) - 1ull));
+    for (int r = kp + 1; r <= k; ++r) off[r] = i;
+    if (i == n - 1)
+        for (int r = k + 1; r <= n_rows; ++r) off[r] = n;
 }
 
 // Ordered segmented reduction over the sorted incidence keys (vertex << fbits | facet): the keys of
@@ -2104,9 +2166,12 @@ struct FacetOut {
 // ---------------------------------------------------------------------------
 // The call's last kernel, one workgroup: the header's first n ints ([State][matched][foff_out])
 // copied to the host's read-back area, then the host is told.
+// zero[i * zero_stride] and the word behind it, i < n_zero: words that their users find zero, cleared on the way.
 __global__ __launch_bounds__(BLOCK) void publish_header_kernel(int* __restrict__ hdr, int n,
-                                                               int* __restrict__ host_img, HostSignal done) {
+                                                               int* __restrict__ host_img, HostSignal done,
+                                                               u32* __restrict__ zero, int n_zero, int zero_stride) {
     for (int i = threadIdx.x; i < n; i += BLOCK) host_img[i] = hdr[i];
+    for (int i = threadIdx.x; i < n_zero; i += BLOCK) zero[(size_t)i * zero_stride] = zero[(size_t)i * zero_stride + 1] = 0;
     // (the error flags are zero between calls: a single mesh's next call does not upload a header)
     if (threadIdx.x == 0) hdr[offsetof(State, err) / sizeof(int)] = 0;
     signal_host(done, threadIdx.x, (int)threadIdx.x < n);

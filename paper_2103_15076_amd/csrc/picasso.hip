@@ -127,6 +127,7 @@ struct picasso_ctx {
     int* acnt = nullptr;   // per vertex: how many vertices joined the cluster it represents
     int* acand = nullptr;  // per mesh: vertices that could join
     int* arem = nullptr;   // per mesh: budget left after the pairs
+    u32* area_ext = nullptr;  // per mesh: largest facet area and largest complement of one (conv::EXT_SLOTS; zero between calls)
     int64_t kt_calls = 0;           // decimate calls since the option was set
     bool kt_this_call = false;
     hipEvent_t kt_pool[512];
@@ -243,6 +244,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->acnt = cv.take<int>(n);
     x->acand = cv.take<int>(b);
     x->arem = cv.take<int>(b);
+    x->area_ext = cv.take<u32>(b * conv::EXT_SLOTS * conv::EXT_PAD);
     return cv.off;
 }
 
@@ -529,9 +531,10 @@ hipError_t wait_for_signal(picasso_ctx* c, hipStream_t s, const HostSignal& sig)
 
 // [State][matched][foff_out] brought to the pinned read-back area by a one-workgroup kernel that then
 // tells the host; returns when the host has them (and everything queued before has been executed).
-int read_header(picasso_ctx* c, hipStream_t s) {
+int read_header(picasso_ctx* c, hipStream_t s, u32* zero = nullptr, int n_zero = 0) {
     const HostSignal done = next_signal(c);
-    publish_header_kernel<<<1, BLOCK, 0, s>>>(c->hdr, HDR_STATE_INTS + 2 * c->cap_b + 1, c->h_pin_dev, done);
+    publish_header_kernel<<<1, BLOCK, 0, s>>>(c->hdr, HDR_STATE_INTS + 2 * c->cap_b + 1, c->h_pin_dev, done, zero, n_zero,
+                                             conv::EXT_PAD);
     HIP_TRY(c, wait_for_signal(c, s, done));
     return PICASSO_OK;
 }
@@ -1179,6 +1182,34 @@ void sum_filter_rows(hipStream_t s, const FilterSplit& sp, int width, float* d_o
                                                                                                   d_out);
 }
 
+// Items 0 .. n - 1 listed per row (d_row_of[i] in [0, n_rows)), ascending: d_off [n_rows + 1], d_items [n].
+int build_csr(picasso_ctx* c, hipStream_t s, const int32_t* d_row_of, int n, int n_rows, int32_t* d_off, int32_t* d_items) {
+    HIP_TRY(c, hipSetDevice(c->device));
+    const int ibits = ceil_log2(n), kb = ibits + ceil_log2(n_rows);
+    const RowKeys src{d_row_of, n_rows, ibits};
+    const int how = sort_by_vertex_path(n, kb);
+    int* err = &c->st->err;
+    if (how == COUNT_SMALL) {
+        csr_count_kernel<COUNT_SMALL><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, prim::bucket_sort_low_bits(kb), 0u, c->hist12_s0, nullptr, err);
+    } else if (how == COUNT_LARGE) {
+        csr_count_kernel<COUNT_LARGE><<<prim::sort_tiles(n, 16), BLOCK, 0, s>>>(src, n, kb - prim::BUCKET_LARGE_MSD_BITS, 0u, c->hist12_s0, nullptr, err);
+    } else if (how == COUNT_XL) {
+        const int bits = prim::xl_digit_bits(n, kb);
+        prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, s>>>(c->xl_s0.hist, 1 << bits, 0u);
+        csr_count_kernel<COUNT_XL><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, kb - bits, (1u << bits) - 1u, c->xl_s0.hist, nullptr, err);
+    } else {
+        csr_count_kernel<COUNT_NONE><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, 0, 0u, nullptr, c->key64[0], err);
+    }
+    const int where = sort_by_vertex<u64, false, RowKeys>(s, c->key64[0], c->key64[1], nullptr, nullptr, nullptr, n, kb, c->sort_sc,
+                                                         c->hist12_s0, nullptr, 0, how != COUNT_NONE, &src, nullptr, &c->xl_s0);
+    if (where < 0) return PICASSO_ERR_HIP;
+    csr_finish_kernel<<<grid_for(n), BLOCK, 0, s>>>(where ? c->key64[1] : c->key64[0], ibits, n, n_rows, d_off, d_items, c->hist12_s0);
+    const int rc = read_header(c, s);
+    if (rc != PICASSO_OK) return rc;
+    HIP_TRY(c, hipGetLastError());
+    return (reinterpret_cast<State*>(c->h_pin)->err & ERR_BIT_BAD_INDEX) ? PICASSO_ERR_BAD_INDEX : PICASSO_OK;
+}
+
 }  // namespace
 
 // Scratch of picasso_replace_mapping_static (the entry point for callers that cannot allocate):
@@ -1236,6 +1267,7 @@ int picasso_create(picasso_ctx** out, int device, int64_t max_verts, int64_t max
     // the incidence sort's digit counts start at zero; every S0 leaves them at zero again.  So do the
     // header's error flags (see HeaderInit).
     if (hipMemset(c->hist12_s0, 0, sizeof(u32) * 2 * prim::MSD_HIST_WORDS) != hipSuccess ||
+        hipMemset(c->area_ext, 0, sizeof(u32) * (size_t)max_meshes * conv::EXT_SLOTS * conv::EXT_PAD) != hipSuccess ||
         hipMemset(c->hdr, 0, sizeof(int) * (HDR_STATE_INTS + 8 * (size_t)max_meshes + 3)) != hipSuccess) {
         (void)hipHostFree(c->h_pin);
         (void)hipFree(c->ws);
@@ -1481,23 +1513,7 @@ int picasso_cluster_csr(picasso_ctx* c, void* stream, const int32_t* d_cluster_i
                         int32_t* d_offsets, int32_t* d_members) {
     if (!c || !d_cluster_id || n_in < 1 || n_out < 1 || !d_offsets || !d_members) return PICASSO_ERR_INVALID_ARG;
     if (n_in > 3 * c->max_facets || n_out > c->max_verts) return PICASSO_ERR_WORKSPACE;
-    hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(c, hipSetDevice(c->device));
-    u32* k0 = reinterpret_cast<u32*>(c->key64[0]);
-    u32* k1 = reinterpret_cast<u32*>(c->key64[1]);
-    prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
-    pool::emit_cluster_pairs_kernel<<<pool::grid_for(n_in), pool::BLOCK, 0, s>>>(d_cluster_id, n_in, n_out, k0,
-                                                                                 c->val32[0], &c->st->err);
-    const int where = sort_by_vertex<u32, true>(s, k0, k1, c->val32[0], c->val32[1], nullptr, n_in, ceil_log2(n_out),
-                                                c->sort_sc, c->hist12);
-    if (where < 0) return PICASSO_ERR_HIP;
-    csr_offsets_kernel<u32><<<grid_for(n_in), BLOCK, 0, s>>>(where ? k1 : k0, 0, n_in, n_out, d_offsets);
-    HIP_TRY(c, hipMemcpyAsync(d_members, where ? c->val32[1] : c->val32[0], sizeof(int32_t) * (size_t)n_in,
-                              hipMemcpyDeviceToDevice, s));
-    int rc = read_header(c, s);
-    if (rc != PICASSO_OK) return rc;
-    HIP_TRY(c, hipGetLastError());
-    return (reinterpret_cast<State*>(c->h_pin)->err & 1) ? PICASSO_ERR_BAD_INDEX : PICASSO_OK;
+    return build_csr(c, (hipStream_t)stream, d_cluster_id, n_in, n_out, d_offsets, d_members);
 }
 
 // ---- mesh convolutions, depth-wise (Sec. 4 "Mesh Convolution"; supplementary, backward propagations)
@@ -1506,21 +1522,7 @@ int picasso_vertex_corner_csr(picasso_ctx* c, void* stream, const int32_t* d_fac
                               int32_t* d_offsets, int32_t* d_corners) {
     if (!c || !d_facets || F < 1 || N < 1 || !d_offsets || !d_corners) return PICASSO_ERR_INVALID_ARG;
     if (F > c->max_facets) return PICASSO_ERR_WORKSPACE;
-    hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(c, hipSetDevice(c->device));
-    const int H = 3 * F, cbits = ceil_log2(H), vbits = ceil_log2(N);
-    prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
-    conv::corner_keys_kernel<<<pool::grid_for(H), pool::BLOCK, 0, s>>>(d_facets, H, N, cbits, c->key64[0], &c->st->err);
-    const int where = sort_by_vertex<u64, false>(s, c->key64[0], c->key64[1], nullptr, nullptr, nullptr, H,
-                                                 cbits + vbits, c->sort_sc, c->hist12);
-    if (where < 0) return PICASSO_ERR_HIP;
-    const u64* skey = where ? c->key64[1] : c->key64[0];
-    csr_offsets_kernel<u64><<<grid_for(H), BLOCK, 0, s>>>(skey, cbits, H, N, d_offsets);
-    conv::corner_list_kernel<<<pool::grid_for(H), pool::BLOCK, 0, s>>>(skey, H, cbits, d_corners);
-    int rc = read_header(c, s);
-    if (rc != PICASSO_OK) return rc;
-    HIP_TRY(c, hipGetLastError());
-    return (reinterpret_cast<State*>(c->h_pin)->err & 1) ? PICASSO_ERR_BAD_INDEX : PICASSO_OK;
+    return build_csr(c, (hipStream_t)stream, d_facets, 3 * F, N, d_offsets, d_corners);
 }
 
 int picasso_facet_geometry(picasso_ctx* c, void* stream, const float* d_verts, int32_t N, const int32_t* d_facets,
@@ -1532,8 +1534,11 @@ int picasso_facet_geometry(picasso_ctx* c, void* stream, const float* d_verts, i
     if (B > c->max_meshes || (d_level && !d_areas && F > 3 * c->max_facets)) return PICASSO_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    // facet offsets of the meshes, staged in pinned memory like the decimation's header
-    int* img = c->h_pin + c->h_up_off;
+    // facet offsets of the meshes: with the launch, or (very many meshes) staged in pinned memory like the decimation's header
+    conv::MeshOffsets foff{};
+    foff.B = B;
+    foff.far = B > conv::MESH_OFFSETS ? c->foff : nullptr;
+    int* img = foff.far ? c->h_pin + c->h_up_off : foff.here;
     long long acc = 0;
     for (int b = 0; b < B; ++b) {
         img[b] = (int)acc;
@@ -1543,22 +1548,15 @@ int picasso_facet_geometry(picasso_ctx* c, void* stream, const float* d_verts, i
     }
     img[B] = (int)acc;
     if (acc != F) return PICASSO_ERR_INVALID_ARG;
-    HIP_TRY(c, hipMemcpyAsync(c->foff, img, sizeof(int) * (B + 1), hipMemcpyHostToDevice, s));
-    unsigned* amin = reinterpret_cast<unsigned*>(c->acand);
-    unsigned* amax = reinterpret_cast<unsigned*>(c->arem);
+    if (foff.far) HIP_TRY(c, hipMemcpyAsync(c->foff, img, sizeof(int) * (B + 1), hipMemcpyHostToDevice, s));
+    const int geo_grid = (F + pool::BLOCK * conv::GEO_ITEMS - 1) / (pool::BLOCK * conv::GEO_ITEMS);
     float* areas = d_areas ? d_areas : reinterpret_cast<float*>(c->ecost);  // scratch when only levels are wanted
-    prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
-    if (d_level) {
-        prim::fill_u32_kernel<<<grid_for(B), BLOCK, 0, s>>>(amin, B, 0xFFFFFFFFu);
-        prim::fill_u32_kernel<<<grid_for(B), BLOCK, 0, s>>>(amax, B, 0u);
-    }
-    conv::facet_geometry_kernel<<<pool::grid_for(F), pool::BLOCK, 0, s>>>(
-        d_verts, N, d_facets, F, B, c->foff, d_normals, (d_areas || d_level) ? areas : nullptr,
-        d_level ? amin : nullptr, d_level ? amax : nullptr, &c->st->err);
+    conv::facet_geometry_kernel<<<geo_grid, pool::BLOCK, 0, s>>>(d_verts, N, d_facets, F, foff, d_normals,
+                                                                         (d_areas || d_level) ? areas : nullptr,
+                                                                         d_level ? c->area_ext : nullptr, &c->st->err);
     if (d_level)
-        conv::facet_level_kernel<<<pool::grid_for(F), pool::BLOCK, 0, s>>>(areas, F, B, c->foff, amin, amax, alpha, beta,
-                                                                          d_level);
-    int rc = read_header(c, s);
+        conv::facet_level_kernel<<<geo_grid, pool::BLOCK, 0, s>>>(areas, F, foff, c->area_ext, alpha, beta, d_level);
+    int rc = read_header(c, s, c->area_ext, d_level ? B * conv::EXT_SLOTS : 0);
     if (rc != PICASSO_OK) return rc;
     HIP_TRY(c, hipGetLastError());
     return (reinterpret_cast<State*>(c->h_pin)->err & 1) ? PICASSO_ERR_BAD_INDEX : PICASSO_OK;
@@ -1569,7 +1567,10 @@ int picasso_fuzzy_coefficients(picasso_ctx* c, void* stream, const float* d_norm
     if (!c || !d_normals || F < 1 || !d_mu || !d_inv_var || T < 1 || !d_pi) return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    conv::fuzzy_kernel<<<pool::grid_for(F), pool::BLOCK, 0, s>>>(d_normals, F, d_mu, d_inv_var, T, d_pi);
+    if (T <= conv::FUZZY_LDS_T)
+        conv::fuzzy_kernel<true><<<pool::grid_for(F), pool::BLOCK, sizeof(float) * pool::BLOCK * T, s>>>(d_normals, F, d_mu, d_inv_var, T, d_pi);
+    else
+        conv::fuzzy_kernel<false><<<pool::grid_for(F), pool::BLOCK, 0, s>>>(d_normals, F, d_mu, d_inv_var, T, d_pi);
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }

@@ -258,21 +258,6 @@ __global__ __launch_bounds__(BLOCK) void unpool_forward_kernel(const float* __re
     store_row<KIND>(row_at<KIND>(x, v, C, c0), load_row<KIND>(row_at<KIND>(y, *at<KIND>(cid, v), C, c0), left), left);
 }
 
-// (cluster id, vertex) pairs for the CSR sort; flags ids outside [0, n_out)
-__global__ __launch_bounds__(BLOCK) void emit_cluster_pairs_kernel(const int* __restrict__ cid, int n_in, int n_out,
-                                                                   uint32_t* __restrict__ key,
-                                                                   uint32_t* __restrict__ val, int* __restrict__ err) {
-    const int v = blockIdx.x * BLOCK + threadIdx.x;
-    if (v >= n_in) return;
-    int c = cid[v];
-    if (c < 0 || c >= n_out) {
-        atomicOr(err, 1);
-        c = 0;
-    }
-    key[v] = (uint32_t)c;
-    val[v] = (uint32_t)v;
-}
-
 // The two per-input-vertex tensors of Alg. 2's output list from cluster_id: first[c] = smallest
 // member of cluster c (first pass, atomicMin: the result does not depend on order), then
 // replace[v] = first[cluster_id[v]] and mapping[v] = cluster_id[v] for that member, -1 otherwise.
