@@ -97,9 +97,17 @@ __device__ __forceinline__ int mesh_of_facet(const MeshOffsets& foff, int f) {
 // The extremes of a mesh: its facets' workgroups spread over EXT_SLOTS cache lines, one atomic pair per workgroup (whose
 // facets nearly always belong to one mesh) after combining in LDS: atomics on one line, whichever words of it they
 // name, are served one after the other, about 10 ns each (1.9 M facets of 16 meshes: 143 us with a pair for every 256
-// facets on two words per mesh).
+// facets on two words per mesh). The few workgroups across a mesh's end take a pair per wave and mesh: with one per facet
+// those 15 workgroups alone held the kernel back (44.7 us, 19.3 with it).
 constexpr int EXT_SLOTS = 8, EXT_PAD = 32;  // words: one 128-byte line per slot; word 0 = largest pattern, 1 = largest complement
 constexpr int GEO_ITEMS = 4;                // facets per lane
+
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v = max(v, (unsigned)__shfl_xor((int)v, d, 64));
+    return v;
+}
+
 __device__ __forceinline__ unsigned* ext_slot(unsigned* ext, int m) {
     return ext + ((size_t)m * EXT_SLOTS + (blockIdx.x & (EXT_SLOTS - 1))) * EXT_PAD;
 }
@@ -152,24 +160,26 @@ __global__ __launch_bounds__(BLOCK) void facet_geometry_kernel(const float* __re
             n.c = len > 0.0f ? nz / len : 0.0f;
             *reinterpret_cast<Float3*>(normals + 3 * (size_t)f) = n;
         }
-        if (ext && in && area == area) {  // (a NaN area takes no part in the extremes)
-            const unsigned bits = __float_as_uint(area);
-            if (one_mesh) {
-                hi = max(hi, bits);
-                lo = max(lo, ~bits);
-            } else {
-                unsigned* e = ext_slot(ext, mesh_of_facet(foff, f));
-                atomicMax(&e[0], bits);
-                atomicMax(&e[1], ~bits);
+        const unsigned bits = __float_as_uint(area);
+        const bool counts = in && area == area;  // (a NaN area takes no part in the extremes)
+        if (!ext) continue;
+        if (one_mesh) {
+            hi = max(hi, counts ? bits : 0u);
+            lo = max(lo, counts ? ~bits : 0u);
+        } else {  // a workgroup across a mesh's end: an atomic pair per wave and mesh
+            const int m = counts ? mesh_of_facet(foff, f) : -1;
+            for (unsigned long long rest = __ballot(counts); rest;) {
+                const int m0 = __shfl(m, __ffsll((long long)rest) - 1, 64);
+                const bool mine = m == m0;
+                const unsigned h = wave_max(mine ? bits : 0u), n = wave_max(mine ? ~bits : 0u);
+                if ((threadIdx.x & 63) < 2) atomicMax(ext_slot(ext, m0) + (threadIdx.x & 1), (threadIdx.x & 1) ? n : h);
+                rest &= ~__ballot(mine);
             }
         }
     }
     if (!ext || !one_mesh) return;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        hi = max(hi, (unsigned)__shfl_xor((int)hi, d, 64));
-        lo = max(lo, (unsigned)__shfl_xor((int)lo, d, 64));
-    }
+    hi = wave_max(hi);
+    lo = wave_max(lo);
     if ((threadIdx.x & 63) == 0) {
         wmax[threadIdx.x >> 6] = hi;
         wnmin[threadIdx.x >> 6] = lo;

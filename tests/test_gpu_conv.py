@@ -377,3 +377,24 @@ def test_rows_beyond_24_bit_numbers(pk, ctx):
     t1, _ = ctx.picasso_f2f_backward(g, tex2, bary2, dev(poff + shift), w)
     assert torch.allclose(y0, y1, rtol=0, atol=float(16 * EPS * y0.abs().max())) and torch.equal(t0, t1[shift:])
     assert not t1[:shift].any() and not t0[: poff[0]].any()
+
+
+@pytest.mark.parametrize("sizes", [[1500, 1, 0, 3000, 7, 1024, 40], [5] * 300, [4096, 1]])
+def test_levels_of_meshes_across_workgroups(pk, oracle, sizes):
+    """Facet levels where meshes end inside a workgroup's facets, are empty, or more than a launch carries."""
+    rng = np.random.default_rng(len(sizes))
+    F = rng.integers(0, 500, size=(sum(sizes), 3)).astype(np.int32)
+    V = rng.normal(size=(500, 3)).astype(np.float32)
+    c = pk.Context(500, F.shape[0], len(sizes), device=0)
+    try:
+        for alpha in (1, 7):  # (twice: the extremes start afresh)
+            _, area, lev = c.picasso_facet_geometry(dev(V), dev(F), nf=sizes, alpha=alpha)
+            a_r = oracle.facet_geometry(V, F)[1]
+            assert np.array_equal(area.cpu().numpy().view(np.uint32), a_r.view(np.uint32))
+            foff = np.concatenate([[0], np.cumsum(sizes)])
+            for b, n in enumerate(sizes):
+                if n:
+                    want = oracle.facet_levels(a_r[foff[b]: foff[b + 1]], alpha=alpha)
+                    assert np.array_equal(lev.cpu().numpy()[foff[b]: foff[b + 1]], want), b
+    finally:
+        c.close()
