@@ -32,8 +32,8 @@ constexpr int ERR_BIT_BAD_INDEX = 1, ERR_BIT_NONFINITE = 2, ERR_BIT_INTERNAL = 4
 struct State {
     int err;       // bit0: bad facet index, bit1: non-finite coordinate, bit2: a kernel was launched for sizes it does not take
     int nv[2];     // vertex count, ping-pong by round parity
-    int nf[2];     // facet count, ping-pong
-    int nh;        // 3 * nf of the current round (half-edge keys to sort)
+    int nf;        // facets that go out
+    int nh;        // half-edge keys of the current round: 3 for every facet that has not collapsed
     int ne;        // distinct edges of the current round
     int live[3];   // worklist lengths of the selection sub-rounds (rotating)
     int trunc_n;   // matched edges entering the budget truncation
@@ -41,8 +41,8 @@ struct State {
     int absorb_n;  // edges through which an un-paired vertex would join a pair's cluster (Alg. 2 line 11)
     int nv_kept;   // output vertices that some output facet refers to (option: degenerated vertices dropped)
     // Written by every selection tail for kernels that the host queued behind it before looking
-    // (they run only if the tail finished the matching): 1 / nv / nf / ne of the round then, else zeros.
-    int go, guard_nv, guard_nf, guard_ne;
+    // (they run only if the tail finished the matching): 1 / nv / ne of the round then, else zeros.
+    int go, guard_nv, guard_ne;
 };
 
 // One vertex = 64 bytes: position and the 10 quadric coefficients.
@@ -150,20 +150,26 @@ struct IncidenceKeys {
     __device__ __forceinline__ u64 operator()(long long i) const {
         return ((u64)(u32)fcur[i] << fbits) | (u64)((u32)i / 3u);
     }
+    __device__ __forceinline__ bool keep(u64) const { return true; }
 };
 
 // Edge key of corner i of the facet array: the side from corner i to the facet's next corner as
-// (lower vertex << vbits) | higher vertex; a side with equal ends gets the all-ones key.
+// (lower vertex << vbits) | higher vertex; a side with equal ends, as all three of a collapsed facet (-1, -1, -1) are,
+// has none: it gets the all-ones key, which no sort keeps.
+__host__ __device__ __forceinline__ u64 edge_sentinel(int vbits) { return vbits >= 32 ? ~0ull : ((1ull << (2 * vbits)) - 1ull); }
+__device__ __forceinline__ u64 edge_key(int a, int b, int vbits) {
+    const int lo = min(a, b), hi = max(a, b);
+    return lo == hi ? edge_sentinel(vbits) : (((u64)(u32)lo << vbits) | (u64)(u32)hi);
+}
+
 struct EdgeKeys {
     const int* fcur;
     int vbits;
-    u64 sentinel;
     __device__ __forceinline__ u64 operator()(long long i) const {
         const u32 f = (u32)i / 3u, sl = (u32)i - 3u * f;  // (a corner's number fits 31 bits; 64-bit division is slow)
-        const int a = fcur[i], b = fcur[sl == 2u ? i - 2 : i + 1];
-        const int lo = min(a, b), hi = max(a, b);
-        return (lo == hi) ? sentinel : (((u64)(u32)lo << vbits) | (u64)(u32)hi);
+        return edge_key(fcur[i], fcur[sl == 2u ? i - 2 : i + 1], vbits);
     }
+    __device__ __forceinline__ bool keep(u64 k) const { return k != edge_sentinel(vbits); }
 };
 
 // Plane of a facet as (unit normal, d) with n . x + d = 0 (supplementary, facet quadric equation);
@@ -204,18 +210,18 @@ struct HeaderInit {
 // alone lists every vertex's facets in ascending facet order.  With COUNT_SMALL / COUNT_LARGE the
 // kernel also adds the keys' top 8- / 12-bit digits (bits [ishift, ...)) to ihist, the histogram
 // that the sort of the keys starts from (zero on entry; see quadric_rows_kernel); that sort makes
-// the keys again from the validated facet array (IncidenceKeys), so they are written out (ikey)
-// only for a sort that needs them in memory.  COUNT_XL: the digit is as wide as xl_mask says and counted in
+// the keys again from the validated facet array (IncidenceKeys), so they are written out
+// nowhere.  COUNT_XL: the digit is as wide as xl_mask says and counted in
 // memory (prim::bucket_sort_xl).
 template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
                                                      const int* __restrict__ facets, int F, int B,
                                                      const int* __restrict__ voff, const int* __restrict__ foff,
                                                      VRec* __restrict__ vrec, int* __restrict__ cid,
-                                                     int* __restrict__ fcur, u64* __restrict__ ikey, int fbits,
-                                                     int ishift, u32* __restrict__ ihist, State* st,
+                                                     int* __restrict__ fcur, int fbits, int ishift, u32* __restrict__ ihist, State* st,
                                                      u32* __restrict__ msd_hist, int s0_follows, HeaderInit init,
-                                                     float4* __restrict__ planes, u32 xl_mask) {
+                                                     float4* __restrict__ planes, u32 xl_mask, int* __restrict__ htab,
+                                                     int n_clear) {
     constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
     constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
     __shared__ u32 hist[IN_LDS ? RADIX : 1];
@@ -224,18 +230,19 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
     const bool single = init.hdr != nullptr;  // one mesh, whose ranges are [0, N) and [0, F): the tables are not read here
     if (single && blockIdx.x == 0) {
         constexpr int ERR = (int)(offsetof(State, err) / sizeof(int));
-        constexpr int NV0 = (int)(offsetof(State, nv) / sizeof(int)), NF0 = (int)(offsetof(State, nf) / sizeof(int));
+        constexpr int NV0 = (int)(offsetof(State, nv) / sizeof(int));
         for (int i = threadIdx.x; i < init.total; i += BLOCK) {
             if (i == ERR) continue;
             int v = 0;
             if (i == NV0 || i == init.at_voff0 + 1) v = init.N;
-            else if (i == NF0 || i == init.at_foff + 1) v = init.F;
+            else if (i == init.at_foff + 1) v = init.F;
             else if (i == init.at_target) v = init.target;
             init.hdr[i] = v;
         }
     }
     // the edge-key sort's digit counts and cursors start every round at zero (see edge_keys_kernel)
     for (int i = g; i < 2 * prim::MSD_HIST_WORDS; i += stride) msd_hist[i] = 0;
+    for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
     if constexpr (IN_LDS) {
         for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = 0;
         __syncthreads();
@@ -275,7 +282,6 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                 fcur[3 * (size_t)f + c] = a;
                 corner[c] = a;
                 k = ((u64)(u32)a << fbits) | (u64)(u32)f;
-                if (ikey) ikey[3 * (size_t)f + c] = k;
             }
             if constexpr (COUNT == COUNT_XL) {
                 prim::xl_count(ihist, ok, (u32)(k >> ishift) & xl_mask);
@@ -312,6 +318,7 @@ struct RowKeys {
         const int r = row_of[i];
         return ((u64)((u32)r < (u32)n_rows ? (u32)r : 0u) << ibits) | (u64)(u32)i;  // (a bad row counts as row 0 here)
     }
+    __device__ __forceinline__ bool keep(u64) const { return true; }
 };
 
 // Adds the keys' digits to hist (COUNT as in init_kernel; COUNT_NONE: writes the keys out instead) and flags rows out
@@ -516,7 +523,7 @@ struct RoundTab {
 };
 
 // Per-mesh budgets and the round's counters, by one workgroup.
-__device__ __forceinline__ void round_begin_block(const RoundTab& R, int cur, State* st) {
+__device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) {
     for (int i = threadIdx.x; i < R.B * MATCH_SLOTS; i += blockDim.x) R.mslots[(size_t)i * MATCH_PAD] = 0;
     for (int b = threadIdx.x; b < R.B; b += blockDim.x) {
         const int nvb = R.voff[b + 1] - R.voff[b];
@@ -527,7 +534,7 @@ __device__ __forceinline__ void round_begin_block(const RoundTab& R, int cur, St
         R.matched[b] = 0;
     }
     if (threadIdx.x == 0) {
-        st->nh = 3 * st->nf[cur];
+        st->nh = 0;
         st->ne = 0;
         st->live[0] = 0;
         st->live[1] = 0;
@@ -541,64 +548,107 @@ __device__ __forceinline__ void round_begin_block(const RoundTab& R, int cur, St
 // ---------------------------------------------------------------------------
 // S1: candidate pairs = distinct mesh edges (Alg. 2 line 1)
 //
-// First kernel of a round: the round's set-up (block 0), the per-vertex selection state, and one
-// 64-bit key (lower vertex, higher vertex) per half-edge, key i for corner i of the facet array.
-// With COUNT_SMALL / COUNT_LARGE the kernel also adds the keys' top 8- / 12-bit digits to the
-// histogram that the sort of the keys starts from (prim::bucket_sort / prim::bucket_sort_large
-// with `counted`; zeroed beforehand), so the sort needs no counting pass of its own.
+// First kernel of a round: the round's set-up (block 0), the per-vertex selection state, and the digits of the
+// 64-bit keys (lower vertex, higher vertex), one per half-edge: the kernel adds the keys' top digits (8 bits with
+// COUNT_SMALL, 12 with COUNT_LARGE, as xl_mask says with COUNT_XL) to the histogram that the sort of the keys starts from
+// (zeroed beforehand); the sort makes the keys again from the facets, so they are not written.
+//
+// With REINDEX the round before has contracted pairs and the facets still name its vertices: they are taken to
+// the new numbering in place (S5).  A facet that has collapsed is marked (-1, -1, -1) and stays where it is: facets keep
+// their places until the end of the call (a compaction each round read and wrote every facet twice more, in two
+// launches; 1.2 M vertices: 58 us of the rounds' facet work).  Facets that have become equal to another stay too:
+// they change no edge and no cost, are a few in ten thousand, and go at the end (final_facets_kernel).  Cluster labels follow
+// the numbering.  A lane takes FACETS facets at a time, all of whose loads are in flight together.
 // ---------------------------------------------------------------------------
-template <int COUNT>
-__global__ __launch_bounds__(BLOCK) void edge_keys_kernel(const int* __restrict__ fcur, State* st, int cur, int vbits,
-                                                          u64* __restrict__ keys, u64* __restrict__ vmin0,
-                                                          u64* __restrict__ vmin1, int* __restrict__ mate,
-                                                          RoundTab R, int shift, u32* __restrict__ msd_hist, u32 xl_mask) {
-    constexpr int ITEMS = COUNT == COUNT_LARGE ? prim::SORT_ITEMS_BIG : prim::SORT_ITEMS_SMALL;
-    constexpr int TILE = BLOCK * ITEMS;
+struct Corners {
+    int a, b, c;
+};
+__device__ __forceinline__ Corners load_corners(const int* __restrict__ facets, size_t f) {
+    return Corners{facets[3 * f], facets[3 * f + 1], facets[3 * f + 2]};
+}
+
+// A facet whose corners have met is dropped if its mesh has been contracted; a mesh that no round took part in
+// keeps its facets as they came.
+__device__ __forceinline__ bool facet_collapsed(const Corners& q, const int* __restrict__ voff, int B,
+                                                const int* __restrict__ done) {
+    return (q.a == q.b || q.b == q.c || q.a == q.c) && done[mesh_of(voff, B, q.a)] != 0;
+}
+
+template <int COUNT, bool REINDEX>
+__global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur, int F, State* st, int cur, int vbits,
+                                                          u64* __restrict__ vmin0, u64* __restrict__ vmin1,
+                                                          int* __restrict__ mate, RoundTab R, int shift,
+                                                          u32* __restrict__ msd_hist, u32 xl_mask,
+                                                          const int* __restrict__ vmap, const int* __restrict__ done,
+                                                          int* __restrict__ cid, int n_orig) {
+    constexpr int FACETS = COUNT == COUNT_SMALL ? 1 : 4;
     constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
-    constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
+    constexpr bool IN_LDS = COUNT != COUNT_XL;
     __shared__ u32 hist[IN_LDS ? RADIX : 1];
-    const int nf = st->nf[cur], nv = st->nv[cur];
-    const long long n = 3ll * nf;
+    const int nv = st->nv[cur];
     const int stride = gridDim.x * BLOCK;
     const int t = threadIdx.x, g = blockIdx.x * BLOCK + t;
-    const u64 sentinel = (vbits >= 32) ? ~0ull : ((1ull << (2 * vbits)) - 1ull);
     for (int w = g; w < nv; w += stride) {
         vmin0[w] = VMIN_NONE;
         vmin1[w] = VMIN_NONE;
         mate[w] = -1;
     }
-    if (blockIdx.x == 0) round_begin_block(R, cur, st);
-    for (long long tile = blockIdx.x; tile * TILE < n; tile += gridDim.x) {
-        if constexpr (IN_LDS) {
-            for (int i = t; i < RADIX; i += BLOCK) hist[i] = 0;
-            __syncthreads();
+    if (blockIdx.x == 0) round_begin_block(R, st);
+    if constexpr (IN_LDS) {
+        for (int i = t; i < RADIX; i += BLOCK) hist[i] = 0;
+        __syncthreads();
+    }
+    for (long long base = (long long)blockIdx.x * (BLOCK * FACETS); base < F; base += (long long)stride * FACETS) {
+        Corners q[FACETS];
+        bool ok[FACETS];
+#pragma unroll
+        for (int j = 0; j < FACETS; ++j) {
+            const long long f = base + j * BLOCK + t;
+            ok[j] = f < F;
+            q[j] = load_corners(fcur, (size_t)(ok[j] ? f : 0));
         }
-#pragma unroll 4
-        for (int i = 0; i < ITEMS; ++i) {
-            const long long idx = tile * TILE + (long long)i * BLOCK + t;
-            const bool ok = idx < n;
-            u64 k = 0;
-            if (ok) {
-                k = EdgeKeys{fcur, vbits, sentinel}(idx);
-                if (keys) keys[idx] = k;  // (the counted sorts make the keys again from fcur)
+        if constexpr (REINDEX) {
+            Corners m[FACETS];
+#pragma unroll
+            for (int j = 0; j < FACETS; ++j) {
+                ok[j] = ok[j] && q[j].a >= 0;
+                m[j] = Corners{vmap[max(q[j].a, 0)], vmap[max(q[j].b, 0)], vmap[max(q[j].c, 0)]};
             }
-            if constexpr (COUNT == COUNT_XL) {
-                prim::xl_count(msd_hist, ok, (u32)(k >> shift) & xl_mask);
-            } else if constexpr (IN_LDS) {
-                // the lower vertices of neighbouring corners mostly share their leading bits: the lanes of
-                // a wave that share a digit count themselves with a single LDS atomic
-                const u32 d = (u32)(k >> shift) & (u32)(RADIX - 1);
-                const u64 same = prim::wave_same_digit_lanes(ok, d);
-                if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
+#pragma unroll
+            for (int j = 0; j < FACETS; ++j) {
+                if (!ok[j]) continue;
+                q[j] = m[j];
+                if (facet_collapsed(q[j], R.voff, R.B, done)) q[j] = Corners{-1, -1, -1};
+                int* o = fcur + 3 * (size_t)(base + j * BLOCK + t);
+                o[0] = q[j].a; o[1] = q[j].b; o[2] = q[j].c;
             }
         }
-        if constexpr (IN_LDS) {
-            __syncthreads();
-            for (int i = t; i < RADIX; i += BLOCK) {
-                const u32 c = hist[i];
-                if (c) atomicAdd(&msd_hist[i], c);
+#pragma unroll
+        for (int j = 0; j < FACETS; ++j) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int a = c == 0 ? q[j].a : (c == 1 ? q[j].b : q[j].c), b = c == 0 ? q[j].b : (c == 1 ? q[j].c : q[j].a);
+                const bool has = ok[j] && a != b;
+                const u64 k = edge_key(a, b, vbits);
+                if constexpr (COUNT == COUNT_XL) {
+                    prim::xl_count(msd_hist, has, (u32)(k >> shift) & xl_mask);
+                } else {
+                    // the lower vertices of neighbouring corners mostly share their leading bits: the lanes of
+                    // a wave that share a digit count themselves with a single LDS atomic
+                    const u32 d = (u32)(k >> shift) & (u32)(RADIX - 1);
+                    const u64 same = prim::wave_same_digit_lanes(has, d);
+                    if (has && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
+                }
             }
-            __syncthreads();
+        }
+    }
+    if constexpr (REINDEX)
+        for (int o = g; o < n_orig; o += stride) cid[o] = vmap[cid[o]];
+    if constexpr (IN_LDS) {
+        __syncthreads();
+        for (int i = t; i < RADIX; i += BLOCK) {
+            const u32 c = hist[i];
+            if (c) atomicAdd(&msd_hist[i], c);
         }
     }
 }
@@ -1080,7 +1130,6 @@ __device__ __forceinline__ void tail_publish(const SelArgs& A, int tid) {
 __device__ __forceinline__ void tail_set_guard(const SelArgs& A, bool finished) {
     A.st->go = finished ? 1 : 0;
     A.st->guard_nv = finished ? A.st->nv[A.cur] : 0;
-    A.st->guard_nf = finished ? A.st->nf[A.cur] : 0;
     A.st->guard_ne = finished ? A.st->ne : 0;
 }
 
@@ -1916,52 +1965,91 @@ struct AlivePredT {
     }
 };
 
-struct AliveOut {
-    int* newid;
-    __device__ void operator()(int w, int pos) const { newid[w] = pos; }
-};
+// For every offset at[0..B] into a list of flagged and other items, how many flagged items lie in front of it: by every lane of the
+// waves that walk the list, whose lanes hold the items i0 + lane; incl = flagged items up to and including the lane's.
+__device__ __forceinline__ void flagged_before(const int* __restrict__ at, int B, long long i0, u32 incl, int* __restrict__ out) {
+    for (int b0 = 0; b0 <= B; b0 += 64) {
+        const int b = b0 + prim::lane_id();
+        const int p = b <= B ? at[b] : -1;
+        const bool here = p > i0 && p <= i0 + 64;
+        const u32 v = (u32)__shfl((int)incl, here ? (int)(p - 1 - i0) : 0, 64);
+        if (here) out[b] = (int)v;
+        else if (p == 0 && i0 == 0) out[b] = 0;
+    }
+}
 
-// Survivors move to their new slot; a pair's representative takes the summed
+// Survivors get their new number (the count pass of a compaction, AlivePredT, has left the survivors per tile of
+// BLOCK * chunks vertices) and move to their new slot; a pair's representative takes the summed
 // quadric and the pair's target position (the mean; with PLACE_INVERSE the
 // point of least error where there is one).  With ABSORB a cluster may have
 // more members than its pair: `akey` lists (representative, member) in
 // ascending order for the vertices that joined, and quadric and position are
 // summed over all members in ascending index order, the position sum divided
-// by their number.  vmap[w] = output slot of w's cluster.
+// by their number.  vmap[w] = output slot of w's cluster, written by its representative's lane for all its
+// members (numbering and contraction were two launches and an array between them; in one they cost what contracting did).
 template <int PLACE, bool ABSORB>
 __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict__ vin, VRec* __restrict__ vout,
-                                                         const int* __restrict__ mate, const int* __restrict__ newid,
-                                                         int* __restrict__ vmap, const State* st, int cur, int B,
-                                                         const int* __restrict__ voff_cur, int* __restrict__ voff_nxt,
-                                                         int* __restrict__ htab, int hsize,
-                                                         u32* __restrict__ msd_hist, float rcond_min,
-                                                         const int* __restrict__ arep, const int* __restrict__ acnt,
-                                                         const u64* __restrict__ akey, int vbits,
+                                                         const int* __restrict__ mate, int* __restrict__ vmap, State* st,
+                                                         int cur, int chunks, const int* __restrict__ tilesum, int prefixed,
+                                                         int B, const int* __restrict__ voff_cur, int* __restrict__ voff_nxt,
+                                                         const int* __restrict__ active, int* __restrict__ done,
+                                                         int* __restrict__ htab, int n_clear, u32* __restrict__ msd_hist,
+                                                         float rcond_min, const int* __restrict__ arep,
+                                                         const int* __restrict__ acnt, const u64* __restrict__ akey, int vbits,
                                                          const int* __restrict__ guard) {
     if (guard && *guard == 0) return;  // queued ahead of the host's look, and the selection was not finished
+    __shared__ u32 smem[prim::WAVES];
     const int nv = st->nv[cur];
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     // this round's edge keys are long sorted: their digit counts and cursors go back to zero for the next round
     for (int i = g; i < 2 * prim::MSD_HIST_WORDS; i += stride) msd_hist[i] = 0;
-    for (int w = g; w < nv; w += stride) {
-        const int m = mate[w];
-        if (m >= 0 && m < w) {
-            vmap[w] = newid[m];
-            continue;
-        }
-        if (ABSORB) {
-            const int r = arep[w];
-            if (r >= 0) {
-                vmap[w] = newid[r];
-                continue;
-            }
-        }
-        const int nw = newid[w];
+    for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
+    for (int b = g; b < B; b += stride)
+        if (active[b]) done[b] = 1;
+    const int t = threadIdx.x, w64 = prim::wave_id(), lane = prim::lane_id();
+    const int tile = blockIdx.x;
+    const long long base = (long long)tile * BLOCK * chunks;
+    if (base >= nv) return;
+    u32 before = 0;  // survivors in front of this tile
+    if (prefixed) {
+        before = (u32)tilesum[tile];
+    } else {
+        u32 part = 0;
+        for (int j = t; j < tile; j += BLOCK) part += (u32)tilesum[j];
+        before = prim::block_sum(part, smem);
+    }
+    const AlivePredT<ABSORB> survives{mate, arep};
+    const long long i0 = base + (long long)w64 * (64 * chunks);  // this wave's part of the tile
+    u32 cnt = 0;
+    for (int c = 0; c < chunks; ++c) {
+        const long long i = i0 + c * 64 + lane;
+        cnt += (u32)__popcll(__ballot(i < nv && survives((int)i)));
+    }
+    __syncthreads();
+    if (lane == 0) smem[w64] = cnt;
+    __syncthreads();
+    u32 run = before, tot = 0;
+#pragma unroll
+    for (int j = 0; j < prim::WAVES; ++j) {
+        if (j < w64) run += smem[j];
+        tot += smem[j];
+    }
+    if (base + (long long)BLOCK * chunks >= nv && t == 0) st->nv[cur ^ 1] = (int)(before + tot);
+    for (int c = 0; c < chunks; ++c) {
+        const long long i = i0 + c * 64 + lane;
+        const bool alive = i < nv && survives((int)i);
+        const u64 bal = __ballot(alive);
+        const u32 incl = run + (u32)__popcll(bal & (prim::lanemask_lt() | (1ull << lane)));
+        flagged_before(voff_cur, B, i0 + c * 64, incl, voff_nxt);  // a mesh starts behind the survivors of those in front of it
+        run += (u32)__popcll(bal);
+        if (!alive) continue;
+        const int w = (int)i, nw = (int)incl - 1, m = mate[w];
         vmap[w] = nw;
         const float4* a = reinterpret_cast<const float4*>(&vin[w]);
         float4 r0 = a[0], r1 = a[1], r2 = a[2], r3 = a[3];
         if (m >= 0) {
+            vmap[m] = nw;
             int j = 0, jend = 0;  // this cluster's part of akey
             if (ABSORB && acnt[w] > 0) {
                 const int n = st->absorb_n;
@@ -1985,7 +2073,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                 // merge w < m with the ascending list of joined vertices
                 const u64 low = (1ull << vbits) - 1ull;
                 bool done_w = false, done_m = false;
-                int cnt = 0;
+                int cnt_in = 0;
                 while (!done_w || !done_m || j < jend) {
                     int x = 0x7FFFFFFF, from = -1;
                     if (!done_w) { x = w; from = 0; }
@@ -1994,12 +2082,17 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                         const int y = (int)(akey[j] & low);
                         if (y < x) { x = y; from = 2; }
                     }
-                    if (from == 0) done_w = true;
-                    else if (from == 1) done_m = true;
-                    else ++j;
+                    if (from == 0) {
+                        done_w = true;
+                    } else if (from == 1) {
+                        done_m = true;
+                    } else {
+                        vmap[x] = nw;
+                        ++j;
+                    }
                     const float4* b = reinterpret_cast<const float4*>(&vin[x]);
                     const float4 s0 = b[0], s1 = b[1], s2 = b[2], s3 = b[3];
-                    if (cnt == 0) {
+                    if (cnt_in == 0) {
                         r0 = s0; r1 = s1; r2 = s2; r3 = s3;
                     } else {
                         r0.x = r0.x + s0.x; r0.y = r0.y + s0.y; r0.z = r0.z + s0.z;
@@ -2007,9 +2100,9 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                         r2.x = r2.x + s2.x; r2.y = r2.y + s2.y; r2.z = r2.z + s2.z; r2.w = r2.w + s2.w;
                         r3.x = r3.x + s3.x; r3.y = r3.y + s3.y;
                     }
-                    ++cnt;
+                    ++cnt_in;
                 }
-                const float k = (float)cnt;
+                const float k = (float)cnt_in;
                 r0.x = r0.x / k; r0.y = r0.y / k; r0.z = r0.z / k;
                 r0.w = 0.f; r3.z = 0.f; r3.w = 0.f;
             }
@@ -2019,24 +2112,10 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
         float4* o = reinterpret_cast<float4*>(&vout[nw]);
         o[0] = r0; o[1] = r1; o[2] = r2; o[3] = r3;
     }
-    // a mesh's first vertex always survives when only pairs are contracted (a removed vertex has a
-    // smaller partner in its own mesh); one that joined a cluster may not, and then the mesh starts
-    // at its first survivor (every cluster has one)
-    for (int b = g; b <= B; b += stride) {
-        int nb = st->nv[cur ^ 1];
-        if (b < B) {
-            int w = voff_cur[b];
-            if (ABSORB)
-                while (w + 1 < voff_cur[b + 1] && arep[w] >= 0) ++w;
-            nb = newid[w];
-        }
-        voff_nxt[b] = nb;
-    }
-    for (int h = g; h < hsize; h += stride) htab[h] = -1;
 }
 
 // ---------------------------------------------------------------------------
-// S5: facet re-indexing, removal of collapsed and repeated facets, compaction
+// End of the call: last re-indexing (S5), removal of collapsed and repeated facets, results out
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void sort3(int& a, int& b, int& c) {
     int t;
@@ -2062,7 +2141,8 @@ __device__ __forceinline__ u32 hash3(int a, int b, int c) {
 // vertices, so the lanes that handle them meet in the same cache lines of the table, where a uniform
 // hash would fetch, and later write back, a whole line for nearly every facet (and the keep test
 // that follows reads the table the same way).  Measured at 1.2 M vertices: 3 hash bits are best; with
-// none the facets of one vertex collide, with 6 or 9 the lines are shared by fewer facets.
+// none the facets of one vertex collide, with 6 or 9 the lines are shared by fewer facets.  Fewer than 8 slots per vertex
+// are worse (4: 5 times the time, collisions), atomics being served at about 25 per nanosecond and 64-byte line.
 constexpr int FACET_HOME_WINDOW_BITS = 3;
 constexpr int FACET_HOME_PROBES = 8;
 __device__ __forceinline__ u32 facet_home(int x, u32 hx, float slots_per_vertex) {
@@ -2070,45 +2150,51 @@ __device__ __forceinline__ u32 facet_home(int x, u32 hx, float slots_per_vertex)
     return (u32)at + (hx & ((1u << FACET_HOME_WINDOW_BITS) - 1u));
 }
 
-// Re-indexes every facet and enters the non-collapsed ones into an open-
+// Re-indexes every facet through vmap (null: they are up to date) and enters the
+// ones of contracted meshes that have not collapsed into an open-
 // addressing table keyed by the unordered vertex triple.  A slot stores a
 // facet index; the slot's identity is that facet's triple, and among equal
 // triples the slot converges to the smallest facet index (atomicMin), so the
-// survivor does not depend on the order in which lanes arrive.
+// survivor does not depend on the order in which lanes arrive.  The table has been cleared to -1.  Once per call: what of
+// equal facets remains is the first of them, in whichever round they became equal.
+// The output vertices' positions and the final labels go out on the way.
 constexpr int FSLOT_KEEP = -1, FSLOT_DROP = -2;
 
-__global__ __launch_bounds__(BLOCK) void facet_insert_kernel(const int* __restrict__ fcur, int* __restrict__ fmap,
+__global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restrict__ fcur, int F, int* __restrict__ fmap,
                                                              const int* __restrict__ vmap, const State* st, int cur,
-                                                             int* __restrict__ htab, u32 hmask, MeshTab mt,
-                                                             const int* __restrict__ voff_cur,
-                                                             int* __restrict__ cid, int n_orig,
-                                                             int* __restrict__ fslot, const int* __restrict__ guard) {
-    if (guard && *guard == 0) return;  // (as in contract_kernel)
-    const int nf = st->nf[cur];
+                                                             int* __restrict__ htab, u32 hmask, int B,
+                                                             const int* __restrict__ voff, const int* __restrict__ done,
+                                                             int* __restrict__ fslot, const int* cid_in, int* cid_out,
+                                                             int n_orig, const VRec* __restrict__ vrec,
+                                                             float* __restrict__ verts_out /* or null */) {
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
-    const int nv_new = st->nv[cur ^ 1];  // (the renumbering before this kernel has left the count there)
-    const float slots_per_vertex = ((float)hmask + 1.0f) / (float)(nv_new > 0 ? nv_new : 1);
-    // (the label of this thread's first original vertex is asked for now, so that it arrives while the
-    // facet is being worked on; it is composed with the new numbering at the end)
-    const int first_label = g < n_orig ? cid[g] : 0;
-    for (int f = g; f < nf; f += stride) {
-        const int a0 = fcur[3 * (size_t)f], b0 = fcur[3 * (size_t)f + 1], c0 = fcur[3 * (size_t)f + 2];
-        const int a = vmap[a0], b = vmap[b0], c = vmap[c0];
-        fmap[3 * (size_t)f] = a;
-        fmap[3 * (size_t)f + 1] = b;
-        fmap[3 * (size_t)f + 2] = c;
+    const int nv = st->nv[cur];
+    const float slots_per_vertex = ((float)hmask + 1.0f) / (float)(nv > 0 ? nv : 1);
+    auto corners_of = [&](int f) -> Corners {
+        const Corners q = load_corners(fcur, (size_t)f);
+        return vmap && q.a >= 0 ? Corners{vmap[q.a], vmap[q.b], vmap[q.c]} : q;
+    };
+    for (int f = g; f < F; f += stride) {
+        const Corners q = corners_of(f);
         // fslot[f]: the table slot that decides about the facet (it survives iff the slot ends up
         // holding f), or FSLOT_KEEP / FSLOT_DROP where no slot is involved
-        if (!mt.active[mesh_of(voff_cur, mt.B, a0)]) {  // mesh sits this round out: facets kept as they are
-            fslot[f] = FSLOT_KEEP;
-            continue;
-        }
-        if (a == b || b == c || a == c) {
+        if (q.a < 0) {
             fslot[f] = FSLOT_DROP;
             continue;
         }
-        int x = a, y = b, z = c;
+        fmap[3 * (size_t)f] = q.a;
+        fmap[3 * (size_t)f + 1] = q.b;
+        fmap[3 * (size_t)f + 2] = q.c;
+        if (!done[mesh_of(voff, B, q.a)]) {  // the mesh took part in no round: facets kept as they are
+            fslot[f] = FSLOT_KEEP;
+            continue;
+        }
+        if (q.a == q.b || q.b == q.c || q.a == q.c) {
+            fslot[f] = FSLOT_DROP;
+            continue;
+        }
+        int x = q.a, y = q.b, z = q.c;
         sort3(x, y, z);
         const u32 hx = hash3(x, y, z);
         u32 h = facet_home(x, hx, slots_per_vertex) & hmask;
@@ -2116,9 +2202,9 @@ __global__ __launch_bounds__(BLOCK) void facet_insert_kernel(const int* __restri
             const int old = atomicCAS(&htab[h], -1, f);
             if (old == -1) break;
             if (old == f) break;
-            int p = vmap[fcur[3 * (size_t)old]], q = vmap[fcur[3 * (size_t)old + 1]], r = vmap[fcur[3 * (size_t)old + 2]];
-            sort3(p, q, r);
-            if (p == x && q == y && r == z) {
+            Corners o = corners_of(old);
+            sort3(o.a, o.b, o.c);
+            if (o.a == x && o.b == y && o.c == z) {
                 atomicMin(&htab[h], f);
                 break;
             }
@@ -2128,12 +2214,21 @@ __global__ __launch_bounds__(BLOCK) void facet_insert_kernel(const int* __restri
         }
         fslot[f] = (int)h;
     }
-    if (g < n_orig) cid[g] = vmap[first_label];
-    for (int o = g + stride; o < n_orig; o += stride) cid[o] = vmap[cid[o]];
+    for (int o = g; o < n_orig; o += stride) {
+        const int c = cid_in[o];
+        cid_out[o] = vmap ? vmap[c] : c;
+    }
+    if (verts_out)
+        for (int w = g; w < nv; w += stride) {
+            const float4 p = *reinterpret_cast<const float4*>(&vrec[w]);
+            verts_out[3 * (size_t)w] = p.x;
+            verts_out[3 * (size_t)w + 1] = p.y;
+            verts_out[3 * (size_t)w + 2] = p.z;
+        }
 }
 
 // keep[f] = 1 iff the facet survives: not collapsed and the first of its triple (the slot that
-// facet_insert_kernel left for it holds the smallest facet index of the triple).
+// final_facets_kernel left for it holds the smallest facet index of the triple).
 struct FacetKeepPred {
     const int* fslot;
     const int* htab;
@@ -2151,13 +2246,20 @@ struct FlagPred {
     __device__ bool operator()(int f) const { return keep[f] != 0; }
 };
 
+// The surviving facets, in order; foff_out[b] = those in front of mesh b (whose facets came at foff[b] ...).
 struct FacetOut {
+    static constexpr bool WAVE_WIDE = true;
     const int* fmap;
-    int* fnxt;
-    __device__ void operator()(int f, int pos) const {
-        fnxt[3 * (size_t)pos] = fmap[3 * (size_t)f];
-        fnxt[3 * (size_t)pos + 1] = fmap[3 * (size_t)f + 1];
-        fnxt[3 * (size_t)pos + 2] = fmap[3 * (size_t)f + 2];
+    int* out;
+    const int* foff;
+    int B;
+    int* foff_out;
+    __device__ void wave(int f, bool, bool flagged, int pos) const {
+        flagged_before(foff, B, f - prim::lane_id(), (u32)pos + (flagged ? 1u : 0u), foff_out);
+        if (!flagged) return;
+        out[3 * (size_t)pos] = fmap[3 * (size_t)f];
+        out[3 * (size_t)pos + 1] = fmap[3 * (size_t)f + 1];
+        out[3 * (size_t)pos + 2] = fmap[3 * (size_t)f + 2];
     }
 };
 
@@ -2179,9 +2281,9 @@ __global__ __launch_bounds__(BLOCK) void publish_header_kernel(int* __restrict__
 
 // Degenerated vertices (option): ref[v] = 1 for every vertex that a facet of the final mesh refers to
 // (ref is cleared beforehand; all writers store the same value).
-__global__ __launch_bounds__(BLOCK) void mark_referenced_kernel(const int* __restrict__ fcur, const State* st, int cur,
+__global__ __launch_bounds__(BLOCK) void mark_referenced_kernel(const int* __restrict__ fcur, const State* st,
                                                                 int* __restrict__ ref) {
-    const long long n = 3ll * st->nf[cur];
+    const long long n = 3ll * st->nf;
     for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (long long)gridDim.x * BLOCK) ref[fcur[i]] = 1;
 }
 
@@ -2201,50 +2303,35 @@ struct RefOut {
     }
 };
 
-// DROP: only the vertices with ref[v] != 0 go out, at newid[v]; facets and cluster ids follow that
+// Only the vertices with ref[v] != 0 go out, at newid[v]; facets and cluster ids follow that
 // numbering, cluster ids of dropped vertices become -1, and kept_per_mesh[b] receives mesh b's count.
-template <bool DROP>
-__global__ __launch_bounds__(BLOCK) void copy_out_kernel(const VRec* __restrict__ vrec, const int* __restrict__ fcur,
+__global__ __launch_bounds__(BLOCK) void drop_out_kernel(const VRec* __restrict__ vrec, const int* __restrict__ fcur,
                                                          const int* __restrict__ cid, const State* st, int cur,
                                                          int n_orig, float* __restrict__ verts_out,
                                                          int* __restrict__ facets_out, int* __restrict__ cid_out,
-                                                         int B, const int* __restrict__ voff,
-                                                         int* __restrict__ foff_out, const int* __restrict__ ref,
+                                                         int B, const int* __restrict__ voff, const int* __restrict__ ref,
                                                          const int* __restrict__ newid,
                                                          int* __restrict__ kept_per_mesh) {
-    const int nv = st->nv[cur], nf = st->nf[cur];
+    const int nv = st->nv[cur], nf = st->nf;
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     for (int w = g; w < nv; w += stride) {
-        if (DROP && !ref[w]) continue;
-        const int o = DROP ? newid[w] : w;
+        if (!ref[w]) continue;
+        const int o = newid[w];
         const float4 p = *reinterpret_cast<const float4*>(&vrec[w]);
         verts_out[3 * (size_t)o] = p.x;
         verts_out[3 * (size_t)o + 1] = p.y;
         verts_out[3 * (size_t)o + 2] = p.z;
     }
-    for (long long i = g; i < 3ll * nf; i += stride) facets_out[i] = DROP ? newid[fcur[i]] : fcur[i];
+    for (long long i = g; i < 3ll * nf; i += stride) facets_out[i] = newid[fcur[i]];
     for (int o = g; o < n_orig; o += stride) {
         const int c = cid[o];
-        cid_out[o] = DROP ? (ref[c] ? newid[c] : -1) : c;
+        cid_out[o] = ref[c] ? newid[c] : -1;
     }
-    // facets stay grouped by mesh: first facet whose leading vertex is at or past the mesh's first vertex
-    for (int b = g; b <= B; b += stride) {
-        int lo = 0, hi = nf;
-        if (b == B) lo = nf;
-        else {
-            const int v0 = voff[b];
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (fcur[3 * (size_t)mid] >= v0) hi = mid; else lo = mid + 1;
-            }
-        }
-        foff_out[b] = lo;
-        if (DROP && b < B) {
-            const int before = voff[b] < nv ? newid[voff[b]] : st->nv_kept;
-            const int upto = voff[b + 1] < nv ? newid[voff[b + 1]] : st->nv_kept;
-            kept_per_mesh[b] = upto - before;
-        }
+    for (int b = g; b < B; b += stride) {
+        const int before = voff[b] < nv ? newid[voff[b]] : st->nv_kept;
+        const int upto = voff[b + 1] < nv ? newid[voff[b + 1]] : st->nv_kept;
+        kept_per_mesh[b] = upto - before;
     }
 }
 

@@ -57,8 +57,8 @@ struct picasso_ctx {
     int cap_b = 1;       // per-mesh capacity the header was laid out for
     State* st = nullptr;
     VRec* vrec[2] = {nullptr, nullptr};
-    int* fbuf[2] = {nullptr, nullptr};  // facet lists, ping-pong
-    int* fmap = nullptr;                // re-indexed facets before compaction
+    int* fcur = nullptr;                // the facets, re-indexed in place round by round
+    int* fmap = nullptr;                // ... after the last round, before compaction
     int* cid = nullptr;
     u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys); also hold 32-bit keys for S0
     u32* val32[2] = {nullptr, nullptr};
@@ -68,11 +68,9 @@ struct picasso_ctx {
     int* mate = nullptr;
     int* newid = nullptr;
     int* vmap = nullptr;
-    int* csr_off = nullptr;
     int* list = nullptr;
     unsigned char* estate = nullptr;
     int* htab = nullptr;
-    size_t hcap = 0;
     unsigned char* keep = nullptr;
     int* fslot = nullptr;  // per facet: the hash-table slot that decides about it
     int* tilesum = nullptr;
@@ -95,6 +93,7 @@ struct picasso_ctx {
     int* target = nullptr;
     int* active = nullptr;
     int* stuck = nullptr;
+    int* done = nullptr;   // mesh has taken part in a round that contracted
     int* nrem = nullptr;
     int* matched = nullptr;
     int* segstart = nullptr;
@@ -148,6 +147,7 @@ struct picasso_ctx {
 namespace {
 
 constexpr int HDR_STATE_INTS = (int)(sizeof(State) / sizeof(int));
+constexpr size_t hdr_ints(size_t b) { return HDR_STATE_INTS + 9 * b + 3; }  // for up to b meshes (see carve)
 constexpr int SEQ_CHECK_WORD = 16;  // within the sequence word's 32-int area: the selection tail's copy of the number (a cache line further)
 
 struct Carver {
@@ -167,6 +167,9 @@ size_t next_pow2(size_t x) {
     return p;
 }
 
+// Slots of the hash set that up to f facets are entered into.
+size_t facet_slots(size_t f) { return next_pow2(2 * std::max<size_t>(f, 1)); }
+
 // Lays the workspace out; with base == nullptr only measures it.
 size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     Carver cv;
@@ -176,9 +179,9 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     picasso_ctx dummy;
     picasso_ctx* x = c ? c : &dummy;
     // header: everything the host uploads or reads back, contiguous so that one copy moves it.
-    //   [State][matched B][foff_out B+1] | [voff0 B+1][foff B+1][target B][stuck B][active B]
+    //   [State][matched B][foff_out B+1] | [voff0 B+1][foff B+1][target B][stuck B][active B][done B]
     //   <-------- read back ----------->
-    int* hdr = cv.take<int>(HDR_STATE_INTS + 8 * b + 3);
+    int* hdr = cv.take<int>(hdr_ints(b));
     x->hdr = hdr;
     x->st = reinterpret_cast<State*>(hdr);
     if (hdr) {
@@ -190,11 +193,11 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
         x->target = q; q += b;
         x->stuck = q; q += b;
         x->active = q; q += b;
+        x->done = q; q += b;
     }
     x->vrec[0] = cv.take<VRec>(n);
     x->vrec[1] = cv.take<VRec>(n);
-    x->fbuf[0] = cv.take<int>(3 * f);
-    x->fbuf[1] = cv.take<int>(3 * f);
+    x->fcur = cv.take<int>(3 * f);
     x->fmap = cv.take<int>(3 * f);
     x->cid = cv.take<int>(n);
     x->key64[0] = cv.take<u64>(h);
@@ -207,11 +210,9 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->mate = cv.take<int>(n);
     x->newid = cv.take<int>(n);
     x->vmap = cv.take<int>(n);
-    x->csr_off = cv.take<int>(n + 1);
     x->list = cv.take<int>(h);
     x->estate = cv.take<unsigned char>(h);
-    x->hcap = next_pow2(2 * f);
-    x->htab = cv.take<int>(x->hcap);
+    x->htab = cv.take<int>(facet_slots(f));
     x->keep = cv.take<unsigned char>(f);
     x->fslot = cv.take<int>(f);
     x->tilesum = cv.take<int>((size_t)prim::compact_tilesum_capacity((long long)std::max(h, n)));
@@ -307,7 +308,8 @@ struct KernelBracket {
 
 // Sort for keys whose leading bits are vertex ids (evenly spread): bucket sort
 // when the input is small enough for it, plain LSD passes otherwise.
-// which sort sort_by_vertex takes, named by the counting a producer of the keys may do for it
+// which sort sort_by_vertex takes, named by the counting a producer of the keys may do for it (COUNT_NONE: plain radix passes,
+// for keys too narrow to have a top digit)
 inline int sort_by_vertex_path(long long n_max, int key_bits) {
     if (n_max <= 0) return COUNT_NONE;
     if (n_max <= prim::BUCKET_SORT_MAX_KEYS && key_bits > prim::BUCKET_MSD_BITS) return COUNT_SMALL;
@@ -337,74 +339,75 @@ int sort_by_vertex(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_p
     return prim::radix_sort<K, HAS_VAL>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, lt, tag);
 }
 
+// Bits of a vertex in the edge keys, of a vertex and of a facet in the incidence keys: what the largest number needs, but enough
+// for n_max keys to have a top digit (and so to be sorted by sort_by_vertex's bucket sorts, which the kernels count the digits for).
+inline int key_bits_wanted(long long n_max) {
+    if (n_max <= prim::BUCKET_SORT_MAX_KEYS) return prim::BUCKET_MSD_BITS + 2;
+    return n_max <= prim::BUCKET_SORT_LARGE_MAX_KEYS ? prim::BUCKET_LARGE_MSD_BITS + 2 : prim::XL_BITS_MAX + 2;
+}
+inline int edge_vertex_bits(int nv, long long n_keys) { return std::max(ceil_log2(nv), key_bits_wanted(n_keys) / 2); }
+inline int incidence_fbits(int N, int F) {
+    return std::max(ceil_log2(std::max(F, 1)), key_bits_wanted(3ll * F) - ceil_log2(N));
+}
+inline int incidence_key_bits(int N, int F) { return ceil_log2(N) + incidence_fbits(N, F); }
+
 // Edge keys, their sort and the count half of the unique step (S1 up to where costs are needed)
-// for the round that starts with `nvt` vertices and at most `nfb` facets, on stream `st_`.
-// *skeys_out = the sorted keys.
-int issue_edge_prefix(picasso_ctx* c, hipStream_t st_, int B, int round_, int cur_, int nvt, int nfb,
+// for the round that starts with `nvt` vertices and at most `nfb` facets that have not collapsed, of F, on stream `st_`.
+// Rounds after the first re-index the facets on the way.  *skeys_out = the sorted keys.
+int issue_edge_prefix(picasso_ctx* c, hipStream_t st_, int B, int round_, int cur_, int nvt, int nfb, int N, int F,
                       const u64** skeys_out) {
-    const u64* skeys = nullptr;
-    const int vbits_ = ceil_log2(nvt);
     const int H_ = 3 * nfb;
+    const int vbits_ = edge_vertex_bits(nvt, H_);
     const RoundTab rt{B, c->voff[cur_], c->target, c->active, c->stuck, c->nrem, c->matched, c->mslots, round_ == 0};
-    // the kernel that writes the keys also counts their top digits for the sort they go to (the
+    // the kernel also counts the keys' top digits for the sort they go to (the
     // histogram and the cursors were zeroed by init_kernel, or by the contraction of the round before)
     const int kb = 2 * vbits_;
-    const int how = sort_by_vertex_path(H_, kb);
-    const bool counted = how != COUNT_NONE;
-    if (how == COUNT_SMALL)
-        edge_keys_kernel<COUNT_SMALL><<<prim::sort_tiles(H_, prim::SORT_ITEMS_SMALL), BLOCK, 0, st_>>>(
-            c->fbuf[cur_], c->st, cur_, vbits_, nullptr, c->vmin[0], c->vmin[1], c->mate, rt,
-            prim::bucket_sort_low_bits(kb), c->hist12, 0u);
-    else if (how == COUNT_LARGE)
-        edge_keys_kernel<COUNT_LARGE><<<prim::sort_tiles(H_, prim::SORT_ITEMS_BIG), BLOCK, 0, st_>>>(
-            c->fbuf[cur_], c->st, cur_, vbits_, nullptr, c->vmin[0], c->vmin[1], c->mate, rt,
-            kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12, 0u);
-    else if (how == COUNT_XL) {
-        const int bits = prim::xl_digit_bits(H_, kb);
-        prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, st_>>>(c->xl.hist, 1 << bits, 0u);
-        edge_keys_kernel<COUNT_XL><<<grid_for(std::max(nfb, nvt), 8192), BLOCK, 0, st_>>>(
-            c->fbuf[cur_], c->st, cur_, vbits_, nullptr, c->vmin[0], c->vmin[1], c->mate, rt, kb - bits, c->xl.hist,
-            (1u << bits) - 1u);
-    } else
-        edge_keys_kernel<COUNT_NONE><<<grid_for(std::max(3 * nfb, nvt), 8192), BLOCK, 0, st_>>>(
-            c->fbuf[cur_], c->st, cur_, vbits_, c->key64[0], c->vmin[0], c->vmin[1], c->mate, rt, 0, nullptr, 0u);
-    skeys = c->key64[0];
-    const u64 sentinel_ = (vbits_ >= 32) ? ~0ull : ((1ull << (2 * vbits_)) - 1ull);
-    bool counted_firsts = false;  // the sort has left the unique step's tile counts
-    if (H_ > 0) {
-        const EdgeKeys src{c->fbuf[cur_], vbits_, sentinel_};  // (the counted sorts read the keys from here)
-        // the bucket sorts also count, per tile of the compaction that follows, the keys that differ from
-        // the key in front of them: the count pass of the unique step
-        prim::UniqueCount<u64> uq;
-        if (counted) {
-            const int chunks = prim::compact_chunks_for(H_);
-            uq.tilesum = c->tilesum;
-            uq.tiles = prim::compact_tiles(H_, chunks);
-            uq.tile_shift = ceil_log2((long long)BLOCK * chunks);
-            uq.sentinel = sentinel_;
-            counted_firsts = true;
-        }
-        int where = sort_by_vertex<u64, false, EdgeKeys>(st_, c->key64[0], c->key64[1], nullptr, nullptr, &c->st->nh,
-                                                         H_, 2 * vbits_, c->sort_sc, c->hist12,
-                                                         c->kt_this_call ? &c->kt : nullptr, round_, counted, &src,
-                                                         counted ? &uq : nullptr, &c->xl);
-        if (where < 0) return PICASSO_ERR_HIP;
-        if (counted) prim::compact_scan_sums(st_, &c->st->nh, H_, c->tilesum);
-        skeys = where ? c->key64[1] : c->key64[0];
+    const int how = H_ > 0 ? sort_by_vertex_path(H_, kb) : COUNT_SMALL;
+    const int bits = how == COUNT_XL ? prim::xl_digit_bits(H_, kb) : 0;
+    if (how == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, st_>>>(c->xl.hist, 1 << bits, 0u);
+    {
+        const KernelBracket timed(c, st_, PICASSO_KERNEL_FACET_INSERT, round_ - 1, round_ > 0);
+#define PICASSO_EDGE_KEYS(COUNT, GRID, SHIFT, HIST)                                                                     \
+    do {                                                                                                                 \
+        if (round_ > 0)                                                                                                  \
+            edge_keys_kernel<COUNT, true><<<GRID, BLOCK, 0, st_>>>(c->fcur, F, c->st, cur_, vbits_, c->vmin[0], c->vmin[1], \
+                                                                   c->mate, rt, SHIFT, HIST, (1u << bits) - 1u, c->vmap,   \
+                                                                   c->done, c->cid, N);                                    \
+        else                                                                                                             \
+            edge_keys_kernel<COUNT, false><<<GRID, BLOCK, 0, st_>>>(c->fcur, F, c->st, cur_, vbits_, c->vmin[0], c->vmin[1], \
+                                                                    c->mate, rt, SHIFT, HIST, (1u << bits) - 1u, nullptr,   \
+                                                                    nullptr, nullptr, 0);                                   \
+    } while (0)
+        // (a workgroup adds its whole histogram to the other's in the end: with 4096 digits it takes several turns)
+        if (how == COUNT_SMALL) PICASSO_EDGE_KEYS(COUNT_SMALL, grid_for(std::max(F, 1)), prim::bucket_sort_low_bits(kb), c->hist12);
+        else if (how == COUNT_LARGE) PICASSO_EDGE_KEYS(COUNT_LARGE, grid_for((F + 3) / 4, 2048), kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12);
+        else PICASSO_EDGE_KEYS(COUNT_XL, grid_for((F + 3) / 4, 8192), kb - bits, c->xl.hist);
+#undef PICASSO_EDGE_KEYS
     }
-    if (!counted_firsts) {
-        UniquePred up_{skeys, sentinel_};
-        prim::compact_count(st_, up_, &c->st->nh, H_, c->tilesum);
-    }
-    *skeys_out = skeys;
+    *skeys_out = c->key64[0];
+    if (H_ <= 0) return PICASSO_OK;
+    const EdgeKeys src{c->fcur, vbits_};  // (the sorts read the keys from here)
+    // the bucket sorts also count, per tile of the compaction that follows, the keys that differ from
+    // the key in front of them: the count pass of the unique step
+    prim::UniqueCount<u64> uq;
+    const int chunks = prim::compact_chunks_for(H_);
+    uq.tilesum = c->tilesum;
+    uq.tiles = prim::compact_tiles(H_, chunks);
+    uq.tile_shift = ceil_log2((long long)BLOCK * chunks);
+    uq.sentinel = edge_sentinel(vbits_);
+    uq.total = &c->st->nh;
+    uq.sources = 3 * F;
+    const int where = sort_by_vertex<u64, false, EdgeKeys>(st_, c->key64[0], c->key64[1], nullptr, nullptr, nullptr, H_, kb,
+                                                           c->sort_sc, c->hist12, c->kt_this_call ? &c->kt : nullptr, round_,
+                                                           true, &src, &uq, &c->xl);
+    if (where < 0) return PICASSO_ERR_HIP;
+    prim::compact_scan_sums(st_, &c->st->nh, H_, c->tilesum);
+    *skeys_out = where ? c->key64[1] : c->key64[0];
     return PICASSO_OK;
 }
 
 constexpr int64_t OVERLAP_MIN_FACETS = 1 << 18;
-
-// Bits of the incidence keys: vertex id above, facet id below.
-inline int incidence_fbits(int F) { return ceil_log2(std::max(F, 1)); }
-inline int incidence_key_bits(int N, int F) { return ceil_log2(N) + incidence_fbits(F); }
+constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 
 // Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
 // before the first round's costs are computed (24 bytes per facet there, 16 needed).
@@ -413,46 +416,37 @@ inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c
 // The validating kernel, instantiated for the sort the incidence keys go to.
 int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, const int32_t* d_facets, int F, int B,
                 bool with_keys, HeaderInit init = HeaderInit{nullptr, 0, 0, 0, 0, 0, 0, 0}) {
-    const int fbits = incidence_fbits(F), kb = incidence_key_bits(N, F);
+    const int fbits = incidence_fbits(N, F), kb = incidence_key_bits(N, F);
     const int how = with_keys ? sort_by_vertex_path(3ll * F, kb) : COUNT_NONE;
-    // only a sort that cannot make the keys itself (the plain LSD fallback) needs them written out
-    u64* ikey = (with_keys && how == COUNT_NONE) ? c->s0_key[0] : nullptr;
     const int s0 = with_keys ? 1 : 0;
     float4* planes = with_keys ? facet_planes(c) : nullptr;
     const int grid = grid_for(std::max(N, F), 4096);
-    if (how == COUNT_SMALL)
-        init_kernel<COUNT_SMALL><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0],
-                                                        c->cid, c->fbuf[0], ikey, fbits, prim::bucket_sort_low_bits(kb),
-                                                        c->hist12_s0, c->st, c->hist12, s0, init, planes, 0u);
-    else if (how == COUNT_LARGE)
-        init_kernel<COUNT_LARGE><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0],
-                                                        c->cid, c->fbuf[0], ikey, fbits,
-                                                        kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12_s0, c->st, c->hist12,
-                                                        s0, init, planes, 0u);
-    else if (how == COUNT_XL) {
-        const int bits = prim::xl_digit_bits(3ll * F, kb);
-        prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, s>>>(c->xl_s0.hist, 1 << bits, 0u);
-        init_kernel<COUNT_XL><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid,
-                                                     c->fbuf[0], ikey, fbits, kb - bits, c->xl_s0.hist, c->st, c->hist12,
-                                                     s0, init, planes, (1u << bits) - 1u);
-    } else
-        init_kernel<COUNT_NONE><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0],
-                                                       c->cid, c->fbuf[0], ikey, fbits, 0, nullptr, c->st, c->hist12,
-                                                       s0, init, planes, 0u);
+    const int bits = how == COUNT_XL ? prim::xl_digit_bits(3ll * F, kb) : 0;
+    // the facet set that the end of the call uses (larger ones are cleared by the last contraction, when fewer facets are left)
+    const int n_clear = F <= CLEAR_AHEAD_MAX_FACETS ? (int)facet_slots((size_t)F) : 0;
+    if (how == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, s>>>(c->xl_s0.hist, 1 << bits, 0u);
+#define PICASSO_INIT(COUNT, SHIFT, HIST)                                                                                     \
+    init_kernel<COUNT><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, \
+                                              fbits, SHIFT, HIST, c->st, c->hist12, s0, init, planes, (1u << bits) - 1u,    \
+                                              c->htab, n_clear)
+    if (how == COUNT_SMALL) PICASSO_INIT(COUNT_SMALL, prim::bucket_sort_low_bits(kb), c->hist12_s0);
+    else if (how == COUNT_LARGE) PICASSO_INIT(COUNT_LARGE, kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12_s0);
+    else if (how == COUNT_XL) PICASSO_INIT(COUNT_XL, kb - bits, c->xl_s0.hist);
+    else PICASSO_INIT(COUNT_NONE, 0, nullptr);
+#undef PICASSO_INIT
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }
 
 // S0 on the incidence keys written by init_kernel (whose digit counts are in hist12_s0).
 int run_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, int F) {
     const int H = 3 * F;
-    const int fbits = incidence_fbits(F), kb = incidence_key_bits(N, F);
+    const int fbits = incidence_fbits(N, F), kb = incidence_key_bits(N, F);
     if (F > 0) {
-        const bool counted = sort_by_vertex_path(H, kb) != COUNT_NONE;
-        const IncidenceKeys src{c->fbuf[0], fbits};  // (the counted sorts read the keys from here)
+        const IncidenceKeys src{c->fcur, fbits};  // (the sorts read the keys from here)
         int where = sort_by_vertex<u64, false, IncidenceKeys>(s, c->s0_key[0], c->s0_key[1], nullptr, nullptr,
                                                                   nullptr, H, kb, c->sort_sc_s0, c->hist12_s0,
                                                                   c->kt_this_call ? &c->kt : nullptr,
-                                                                  PICASSO_KERNEL_SORT_INCIDENCE << 8, counted, &src,
+                                                                  PICASSO_KERNEL_SORT_INCIDENCE << 8, true, &src,
                                                                   nullptr, &c->xl_s0);
         if (where < 0) return PICASSO_ERR_HIP;
         const u64* skey = where ? c->s0_key[1] : c->s0_key[0];
@@ -473,7 +467,7 @@ int upload_header(picasso_ctx* c, hipStream_t s, int B, const int32_t* nv_in, co
                   const int32_t* target, int64_t* N_out, int64_t* F_out, bool by_kernel = false) {
     const int cb = c->cap_b;
     int* img = c->h_pin + c->h_up_off;
-    const int total = HDR_STATE_INTS + 8 * cb + 3;
+    const int total = (int)hdr_ints((size_t)cb);
     memset(img, 0, sizeof(int) * total);
     int* hv = img + (c->voff[0] - c->hdr);
     int* hf = img + (c->foff - c->hdr);
@@ -492,7 +486,6 @@ int upload_header(picasso_ctx* c, hipStream_t s, int B, const int32_t* nv_in, co
     hf[B] = (int)facc;
     State* h = reinterpret_cast<State*>(img);
     h->nv[0] = (int)nacc;
-    h->nf[0] = (int)facc;
     *N_out = nacc;
     *F_out = facc;
     if (!by_kernel) HIP_TRY(c, hipMemcpyAsync(c->hdr, img, sizeof(int) * total, hipMemcpyHostToDevice, s));
@@ -699,7 +692,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     const int N = (int)N64, F = (int)F64;
     HeaderInit hinit{nullptr, 0, 0, 0, 0, 0, 0, 0};
     if (header_by_kernel)
-        hinit = HeaderInit{c->hdr, HDR_STATE_INTS + 8 * c->cap_b + 3, (int)(c->voff[0] - c->hdr), (int)(c->foff - c->hdr),
+        hinit = HeaderInit{c->hdr, (int)hdr_ints((size_t)c->cap_b), (int)(c->voff[0] - c->hdr), (int)(c->foff - c->hdr),
                            (int)(c->target - c->hdr), N, F, target_nv[0]};
 
     c->n_ev = 0;
@@ -753,7 +746,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     if (overlap) {
         HIP_TRY(c, hipEventRecord(c->ev_fork, s));
         HIP_TRY(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
-        rc = issue_edge_prefix(c, c->side, B, 0, 0, N, F, &skeys);
+        rc = issue_edge_prefix(c, c->side, B, 0, 0, N, F, N, F, &skeys);
         if (rc != PICASSO_OK) return rc;
         HIP_TRY(c, hipEventRecord(c->ev_join, c->side));
     }
@@ -769,24 +762,26 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 
     int cur = 0;        // ping-pong index of vrec / facets / voff / State counts
     int nv_total = N;   // exact (host mirror)
-    int nf_bound = F;   // upper bound on the current facet count
+    int nf_bound = F;   // upper bound on the facets that have not collapsed
+    size_t slots_clear = F <= CLEAR_AHEAD_MAX_FACETS ? facet_slots((size_t)F) : 0;  // leading slots of the facet set that are clear
     int round = 0;
     int ne_prev = 0, nv_prev = 0;  // edge and vertex counts of the round before
     bool validated = false;
+    bool renumbered = false;  // the facets and labels still have the numbers from before the last contraction
 
     while (work && (c->opt_max_rounds < 0 || round < c->opt_max_rounds)) {
-        const int vbits = ceil_log2(nv_total);
         const int H = 3 * nf_bound;
+        const int vbits = edge_vertex_bits(nv_total, H);
         MeshTab mt{B, c->voff[cur], c->target, c->active, c->nrem, c->matched, c->mslots};
 
         // ---- S1 (+S2): edges and costs
         tm.begin(round, PICASSO_ST_EDGES);
         if (!(round == 0 && overlap)) {
-            rc = issue_edge_prefix(c, s, B, round, cur, nv_total, nf_bound, &skeys);
+            rc = issue_edge_prefix(c, s, B, round, cur, nv_total, nf_bound, N, F, &skeys);
             if (rc != PICASSO_OK) return rc;
         }
-        const u64 sentinel = (vbits >= 32) ? ~0ull : ((1ull << (2 * vbits)) - 1ull);
-        UniquePred up{skeys, sentinel};
+        renumbered = false;
+        UniquePred up{skeys, edge_sentinel(vbits)};
 #define PICASSO_UNIQUE(PLACE, SHUFFLE, RCOND)                                                                       \
     do {                                                                                                             \
         UniqueOutT<PLACE, SHUFFLE> uo{skeys, c->ekey, c->ecost, c->vrec[cur], c->vmin[0], c->estate, vbits, mt,       \
@@ -804,29 +799,26 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 #undef PICASSO_UNIQUE
         tm.end();
 
-        // The kernels after the selection.  `guarded`: queued behind the selection tail before the host
-        // has looked; they then go by what the tail leaves in State (go, guard_nv, guard_nf) and do
-        // nothing unless it finished the matching.
-        auto issue_contract = [&](int nf_cap, int n_joined, const u64* akeys, bool guarded, HostSignal tell) {
+        // The contraction.  `guarded`: queued behind the selection tail before the host
+        // has looked; it then goes by what the tail leaves in State (go, guard_nv) and does
+        // nothing unless it finished the matching.  clear: slots of the facet set to clear on the way.
+        auto issue_contract = [&](int n_joined, const u64* akeys, size_t clear, bool guarded, HostSignal tell) {
             const int nxt = cur ^ 1;
             const int* guard = guarded ? &c->st->go : nullptr;
             const int* n_ptr = guarded ? &c->st->guard_nv : nullptr;
-            AliveOut ao{c->newid};
             if (n_joined > 0) {
-                AlivePredT<true> ap{c->mate, c->arep};
-                prim::compact(s, ap, ap, ao, n_ptr, nv_total, c->tilesum, &c->st->nv[nxt]);
+                prim::compact_count(s, AlivePredT<true>{c->mate, c->arep}, n_ptr, nv_total, c->tilesum);
             } else {
-                AlivePredT<false> ap{c->mate, nullptr};
-                SignalingPred<AlivePredT<false>> first{ap, tell};  // (`tell.word` may be null: nothing to tell)
-                prim::compact(s, first, ap, ao, n_ptr, nv_total, c->tilesum, &c->st->nv[nxt]);
+                SignalingPred<AlivePredT<false>> first{{c->mate, nullptr}, tell};  // (`tell.word` may be null: nothing to tell)
+                prim::compact_count(s, first, n_ptr, nv_total, c->tilesum);
             }
-            const size_t hsize = next_pow2((size_t)2 * std::max(nf_cap, 1));
-            const int cgrid = grid_for(std::max<long long>(nv_total, (long long)hsize), 8192);
+            const int chunks = prim::compact_chunks_for(nv_total), tiles = prim::compact_tiles(nv_total, chunks);
+            const int prefixed = tiles > prim::COMPACT_MAX_SUMMED_TILES;
 #define PICASSO_CONTRACT(PLACE, ABSORB, RCOND)                                                                       \
-    contract_kernel<PLACE, ABSORB><<<cgrid, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, c->newid, c->vmap,    \
-                                                           c->st, cur, B, c->voff[cur], c->voff[nxt], c->htab,        \
-                                                           (int)hsize, c->hist12, RCOND, c->arep, c->acnt, akeys,     \
-                                                           vbits, guard)
+    contract_kernel<PLACE, ABSORB><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, c->vmap, c->st, cur,  \
+                                                           chunks, c->tilesum, prefixed, B, c->voff[cur],             \
+                                                           c->voff[nxt], c->active, c->done, c->htab, (int)clear,     \
+                                                           c->hist12, RCOND, c->arep, c->acnt, akeys, vbits, guard)
             if (c->opt_placement == PLACE_INVERSE) {
                 if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, c->opt_rcond_min);
                 else PICASSO_CONTRACT(PLACE_INVERSE, false, c->opt_rcond_min);
@@ -836,29 +828,14 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             }
 #undef PICASSO_CONTRACT
         };
-        auto issue_facets = [&](int nf_cap, bool guarded) {
-            const int nxt = cur ^ 1;
-            const size_t hsize = next_pow2((size_t)2 * std::max(nf_cap, 1));
-            {
-                const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round);
-                facet_insert_kernel<<<grid_for(std::max(nf_cap, N), 8192), BLOCK, 0, s>>>(
-                    c->fbuf[cur], c->fmap, c->vmap, c->st, cur, c->htab, (u32)(hsize - 1), mt, c->voff[cur], c->cid, N,
-                    c->fslot, guarded ? &c->st->go : nullptr);
-            }
-            FacetKeepPred kp{c->fslot, c->htab, c->keep};
-            FlagPred fp{c->keep};
-            FacetOut fo{c->fmap, c->fbuf[nxt]};
-            prim::compact(s, kp, fp, fo, guarded ? &c->st->guard_nf : &c->st->nf[cur], nf_cap, c->tilesum, &c->st->nf[nxt]);
-        };
         // Where no mesh can form more pairs than its budget allows (a matching pairs at most half the
-        // vertices) and nothing else has to be decided after the selection, those kernels are queued
+        // vertices) and nothing else has to be decided after the selection, the contraction is queued
         // right behind the tail: the device does not idle while the host looks.
         // Where the budget will bind (a mesh has to stop below 40 % of its vertices; a matching on these
         // meshes pairs 85-95 % of them) and the per-mesh search can take every such mesh, the budget step
-        // is queued there too, in front of them: it finds on the device which meshes are over their
+        // is queued there too, in front of it: it finds on the device which meshes are over their
         // budgets, and does nothing where none is.  In between (40-50 %) nothing is queued ahead.
-        // Queued ahead, the kernels are sized by the facet bound of the round before (twice the hash
-        // table to clear, twice the tiles), which costs more than the idling from about a million facets.
+        // (Larger rounds take long enough for the idling not to count, and then know which contraction is the last.)
         constexpr int AHEAD_MAX_FACETS = 1 << 20;
         bool ahead_ok = !c->opt_absorb && !stats && c->opt_ahead && nf_bound <= AHEAD_MAX_FACETS;
         bool ahead_budget = false;
@@ -951,8 +928,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                                             c->nrem, true, tail_done);
                     if (rc != PICASSO_OK) return rc;
                 }
-                issue_contract(nf_bound, 0, nullptr, true, ahead_budget ? nothing : tail_done);
-                issue_facets(nf_bound, true);
+                issue_contract(0, nullptr, 0, true, ahead_budget ? nothing : tail_done);
             } else {
                 signal_kernel<<<1, 64, 0, s>>>(tail_done);
             }
@@ -988,9 +964,10 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             live_est = live;
         }
         for (int b = 0; b < B; ++b) h_matched[b] = c->h_pin[HDR_STATE_INTS + b];
-        nf_bound = std::min(nf_bound, hst->nf[cur]);
+        const int nf_now = round == 0 ? F : hst->nh / 3;
+        nf_bound = std::min(nf_bound, nf_now);
         if (c->n_rounds_noted < NF_ROUND_CAP) {
-            c->nf_round[c->n_rounds_noted] = hst->nf[cur];
+            c->nf_round[c->n_rounds_noted] = nf_now;
             c->nv_round[c->n_rounds_noted] = nv_total;
             c->ne_round[c->n_rounds_noted] = hst->ne;
             ++c->n_rounds_noted;
@@ -999,7 +976,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         nv_prev = nv_total;
         if (stats && round < PICASSO_STATS_ROUNDS) {
             stats->nv[round] = nv_total;
-            stats->nf[round] = hst->nf[cur];
+            stats->nf[round] = nf_now;
             stats->ne[round] = hst->ne;
             stats->subrounds[round] = launched;
         }
@@ -1048,22 +1025,21 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             break;
         }
 
-        // ---- S4 + S6: contraction and renumbering; S5: facets (already queued behind the tail, and run,
+        // ---- S4 + S6: contraction and renumbering (already queued behind the tail, and run,
         // where `ahead` is set)
-        const int nxt = cur ^ 1;
-        if (!ahead) {
-            tm.begin(round, PICASSO_ST_CONTRACT);
-            issue_contract(nf_bound, n_joined, akeys, false, HostSignal{nullptr, 0});
-            tm.end();
-            tm.begin(round, PICASSO_ST_FACETS);
-            issue_facets(nf_bound, false);
-            tm.end();
-        }
-
-        nv_total -= n_sel + n_joined;
-        cur = nxt;
-        ++round;
         work = any_active();
+        if (!ahead) {
+            const bool last = !work || (c->opt_max_rounds >= 0 && round + 1 >= c->opt_max_rounds);
+            const size_t clear = last && slots_clear == 0 ? facet_slots((size_t)nf_bound) : 0;
+            tm.begin(round, PICASSO_ST_CONTRACT);
+            issue_contract(n_joined, akeys, clear, false, HostSignal{nullptr, 0});
+            tm.end();
+            slots_clear = std::max(slots_clear, clear);
+        }
+        nv_total -= n_sel + n_joined;
+        cur ^= 1;
+        ++round;
+        renumbered = true;
     }
 
     if (!validated) {
@@ -1073,22 +1049,34 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         if (st_err != PICASSO_OK) return st_err;
     }
 
-    const int out_grid = grid_for(std::max(std::max(N, 3 * nf_bound), 1), 8192);
-    if (c->opt_drop_degenerated) {
+    // ---- the end: last re-indexing, collapsed and repeated facets out (S5), results
+    const size_t slots = facet_slots((size_t)nf_bound);
+    if (round > 0 && slots_clear < slots)  // (rounds ended without the contraction that was to be the last)
+        prim::fill_u32_kernel<<<grid_for((long long)slots), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->htab), (int)slots, ~0u);
+    const bool drop = c->opt_drop_degenerated != 0;
+    tm.begin(std::max(round - 1, 0), PICASSO_ST_FACETS);
+    {
+        const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round - 1, renumbered);
+        final_facets_kernel<<<grid_for(std::max(N, F), 8192), BLOCK, 0, s>>>(
+            c->fcur, F, c->fmap, renumbered ? c->vmap : nullptr, c->st, cur, c->htab, (u32)(slots - 1), B, c->voff[cur], c->done,
+            c->fslot, c->cid, drop ? c->cid : d_cluster_id, N, c->vrec[cur], drop ? nullptr : d_verts_out);
+    }
+    const FacetKeepPred kp{c->fslot, c->htab, c->keep};
+    const FlagPred fp{c->keep};
+    const FacetOut fo{c->fmap, drop ? c->fcur : d_facets_out, c->foff, B, c->foff_out};
+    if (F > 0) prim::compact(s, kp, fp, fo, nullptr, F, c->tilesum, &c->st->nf);
+    tm.end();
+    if (drop) {
         // output vertices that no output facet refers to are dropped: mark, number the others, copy out
         int* ref = c->mate;  // (free once the rounds are over)
+        const int out_grid = grid_for(std::max(std::max(N, 3 * nf_bound), 1), 8192);
         prim::fill_u32_kernel<<<grid_for(nv_total), BLOCK, 0, s>>>(reinterpret_cast<u32*>(ref), nv_total, 0u);
-        mark_referenced_kernel<<<grid_for(std::max(3 * nf_bound, 1), 8192), BLOCK, 0, s>>>(c->fbuf[cur], c->st, cur, ref);
+        mark_referenced_kernel<<<grid_for(std::max(3 * nf_bound, 1), 8192), BLOCK, 0, s>>>(c->fcur, c->st, ref);
         const RefPred rp{ref};
         const RefOut ro{c->newid};
         prim::compact(s, rp, rp, ro, &c->st->nv[cur], nv_total, c->tilesum, &c->st->nv_kept);
-        copy_out_kernel<true><<<out_grid, BLOCK, 0, s>>>(c->vrec[cur], c->fbuf[cur], c->cid, c->st, cur, N, d_verts_out,
-                                                         d_facets_out, d_cluster_id, B, c->voff[cur], c->foff_out, ref,
-                                                         c->newid, c->matched);
-    } else {
-        copy_out_kernel<false><<<out_grid, BLOCK, 0, s>>>(c->vrec[cur], c->fbuf[cur], c->cid, c->st, cur, N, d_verts_out,
-                                                          d_facets_out, d_cluster_id, B, c->voff[cur], c->foff_out,
-                                                          nullptr, nullptr, nullptr);
+        drop_out_kernel<<<out_grid, BLOCK, 0, s>>>(c->vrec[cur], c->fcur, c->cid, c->st, cur, N, d_verts_out, d_facets_out,
+                                                   d_cluster_id, B, c->voff[cur], ref, c->newid, c->matched);
     }
     if (stats) HIP_TRY(c, hipEventRecord(c->ev_total[1], s));
     rc = read_header(c, s);
@@ -1114,7 +1102,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                 case PICASSO_KERNEL_SORT: bytes = 16.0 * H; break;
                 case PICASSO_KERNEL_UNIQUE_COST: bytes = 8.0 * H + 13.0 * ne + 72.0 * nv; break;
                 case PICASSO_KERNEL_SUBROUND0: bytes = 14.0 * ne + 24.0 * nv; break;
-                case PICASSO_KERNEL_FACET_INSERT: bytes = 32.0 * nf + 4.0 * nv + 8.0 * (double)N; break;
+                case PICASSO_KERNEL_FACET_INSERT: bytes = 24.0 * nf + 4.0 * nv + 8.0 * (double)N; break;
                 case PICASSO_KERNEL_SORT_INCIDENCE: bytes = 48.0 * (double)F; break;
                 default: bytes = 24.0 * (double)F + 16.0 * (double)F + 76.0 * (double)N; break;  // QUADRIC_ROWS
             }
@@ -1134,7 +1122,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     if (stats) {
         stats->rounds = round;
         stats->nv_out = c->opt_drop_degenerated ? hst->nv_kept : hst->nv[cur];
-        stats->nf_out = hst->nf[cur];
+        stats->nf_out = hst->nf;
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, c->ev_total[0], c->ev_total[1]) == hipSuccess) stats->ms_total = ms;
         tm.collect(stats);
@@ -1254,7 +1242,7 @@ int picasso_create(picasso_ctx** out, int device, int64_t max_verts, int64_t max
         return PICASSO_ERR_HIP;
     }
     c->h_up_off = (size_t)HDR_STATE_INTS + 2 * (size_t)max_meshes + 16;
-    c->h_seq_off = (c->h_up_off + HDR_STATE_INTS + 8 * (size_t)max_meshes + 16 + 31) / 32 * 32;
+    c->h_seq_off = (c->h_up_off + hdr_ints((size_t)max_meshes) + 13 + 31) / 32 * 32;
     c->h_pin_ints = c->h_seq_off + 32;
     // (mapped into the device's address space and coherent with it: kernels store there what the host reads while they run)
     if (hipHostMalloc((void**)&c->h_pin, c->h_pin_ints * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
@@ -1268,7 +1256,7 @@ int picasso_create(picasso_ctx** out, int device, int64_t max_verts, int64_t max
     // header's error flags (see HeaderInit).
     if (hipMemset(c->hist12_s0, 0, sizeof(u32) * 2 * prim::MSD_HIST_WORDS) != hipSuccess ||
         hipMemset(c->area_ext, 0, sizeof(u32) * (size_t)max_meshes * conv::EXT_SLOTS * conv::EXT_PAD) != hipSuccess ||
-        hipMemset(c->hdr, 0, sizeof(int) * (HDR_STATE_INTS + 8 * (size_t)max_meshes + 3)) != hipSuccess) {
+        hipMemset(c->hdr, 0, sizeof(int) * hdr_ints((size_t)max_meshes)) != hipSuccess) {
         (void)hipHostFree(c->h_pin);
         (void)hipFree(c->ws);
         delete[] c->h_mesh;
@@ -1482,13 +1470,12 @@ int picasso_edge_costs(picasso_ctx* c, void* stream, const float* d_verts, int32
     }
     rc = run_vertex_quadrics(c, s, d_verts, N, F);
     if (rc != PICASSO_OK) return rc;
-    const int vbits = ceil_log2(N), H = 3 * F;
+    const int H = 3 * F, vbits = edge_vertex_bits(N, H);
     MeshTab mt{1, c->voff[0], c->target, c->active, c->nrem, c->matched, c->mslots};
     const u64* skeys = nullptr;
-    rc = issue_edge_prefix(c, s, 1, 0, 0, N, F, &skeys);
+    rc = issue_edge_prefix(c, s, 1, 0, 0, N, F, N, F, &skeys);
     if (rc != PICASSO_OK) return rc;
-    const u64 sentinel = (vbits >= 32) ? ~0ull : ((1ull << (2 * vbits)) - 1ull);
-    UniquePred up{skeys, sentinel};
+    UniquePred up{skeys, edge_sentinel(vbits)};
     if (c->opt_placement == PLACE_INVERSE) {
         UniqueOutT<PLACE_INVERSE, false> uo{skeys, c->ekey, c->ecost, c->vrec[0], c->vmin[0], c->estate, vbits, mt,
                                             c->opt_rcond_min, TieBreak{0u, 0u, 0u}};

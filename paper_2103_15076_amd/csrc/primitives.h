@@ -1120,6 +1120,8 @@ struct UniqueCount {
     int tile_shift = 0;
     int tiles = 0;
     K sentinel = (K)0;
+    int* total = nullptr;  // receives the number of keys (those of the source that it keeps)
+    int sources = 0;       // not 0: items of the source, of which it keeps at most as many as the sort is sized for
 };
 
 // Histogram of the top RBITS-bit digit (bits [shift, shift + RBITS)) over the whole input, added
@@ -1158,11 +1160,13 @@ __global__ __launch_bounds__(BLOCK) void msd_histogram_kernel(const K* __restric
 // final result does not depend on it.  The lanes of a wave whose keys share a digit (keys led by
 // mesh indices bring few distinct digits into a wave) rank themselves with one LDS atomic.
 // A key source gives key i of the input: an array, or a functor that makes the key on the fly (so
-// that keys which are a cheap function of other data need not be written out and read back).
+// that keys which are a cheap function of other data need not be written out and read back).  A key that the source
+// does not keep is left out (and is not in the histogram): the output is as many keys shorter.
 template <typename K>
 struct ArrayKeys {
     const K* p;
     __device__ __forceinline__ K operator()(long long i) const { return p[i]; }
+    __device__ __forceinline__ bool keep(K) const { return true; }
 };
 
 template <typename K, int RBITS, int ITEMS, class Src>
@@ -1170,7 +1174,7 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(Src kin, K* __restri
                                                             const int* n_ptr, int n_host, int shift,
                                                             const u32* __restrict__ hist, u32* __restrict__ cursor,
                                                             u32* __restrict__ starts, int* __restrict__ zero = nullptr,
-                                                            int n_zero = 0) {
+                                                            int n_zero = 0, int* __restrict__ total = nullptr) {
     constexpr int R = 1 << RBITS;
     constexpr int PER = R / BLOCK;  // digits per thread in the scan of the ranges' first positions
     // (an array that the kernel after this one adds to: zeroed here, by all workgroups together)
@@ -1208,12 +1212,13 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(Src kin, K* __restri
             if (blockIdx.x == 0) starts[t * PER + j] = run;  // for the kernel that sorts the ranges
             run += c[j];
         }
+        if (total && blockIdx.x == 0 && t == 0) *total = (int)tot;
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const long long idx = base + (long long)w * (64 * ITEMS) + i * 64 + lane;
-        const bool ok = idx < n;
+        const bool ok = idx < n && kin.keep(key[i]);
         const u32 d = digit_of<K>(key[i], shift, R - 1);
         // the lanes that share a digit rank themselves with one returning atomic, by the first of them
         const u64 same = wave_same_digit_lanes(ok, d);
@@ -1231,7 +1236,7 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(Src kin, K* __restri
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const long long idx = base + (long long)w * (64 * ITEMS) + i * 64 + lane;
-        if (idx < n) {
+        if (idx < n && kin.keep(key[i])) {
             const u32 pos = h[digit_of<K>(key[i], shift, R - 1)] + rk[i];
             if (pos < (u32)n) kout[pos] = key[i];  // (always, when hist and cursor are as described)
         }
@@ -1274,10 +1279,11 @@ inline int bucket_sort(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int*
             u32* starts = msd_hist + 2 * MSD_HIST_WORDS;
             const UniqueCount<K> none{};
             const UniqueCount<K>& u = uq ? *uq : none;
+            const int n_src = u.sources ? u.sources : n_max;
             if (src && counted)
-                msd_scatter_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL, Src><<<tiles, BLOCK, 0, s>>>(*src, k1, n_ptr, n_max, low, msd_hist, cursor, starts, u.tilesum, u.tiles);
+                msd_scatter_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL, Src><<<sort_tiles(n_src, SORT_ITEMS_SMALL), BLOCK, 0, s>>>(*src, k1, n_ptr, n_src, low, msd_hist, cursor, starts, u.tilesum, u.tiles, u.total);
             else
-                msd_scatter_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, msd_hist, cursor, starts, u.tilesum, u.tiles);
+                msd_scatter_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, msd_hist, cursor, starts, u.tilesum, u.tiles, u.total);
             const bool timed = lt && lt->begin(s, tag);
             launch_bucket_keys_kernel<K, BUCKET_KEYS_THREADS_256, BUCKET_KEYS_ITEMS_256>(1 << msd, s, k1, k0, msd_hist, low, starts, u.sentinel, u.tilesum, u.tile_shift);
             if (timed) lt->end(s);
@@ -1368,10 +1374,11 @@ inline int bucket_sort_large(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, cons
         u32* starts = hist12 + 2 * MSD_HIST_WORDS;
         const UniqueCount<K> none{};
         const UniqueCount<K>& u = uq ? *uq : none;
+        const int n_src = u.sources ? u.sources : n_max;
         if (src && counted)
-            msd_scatter_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG, Src><<<tiles, BLOCK, 0, s>>>(*src, k1, n_ptr, n_max, low, hist12, cursor, starts, u.tilesum, u.tiles);
+            msd_scatter_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG, Src><<<sort_tiles(n_src, SORT_ITEMS_BIG), BLOCK, 0, s>>>(*src, k1, n_ptr, n_src, low, hist12, cursor, starts, u.tilesum, u.tiles, u.total);
         else
-            msd_scatter_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, hist12, cursor, starts, u.tilesum, u.tiles);
+            msd_scatter_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, hist12, cursor, starts, u.tilesum, u.tiles, u.total);
         const bool timed = lt && lt->begin(s, tag);
         launch_bucket_keys_kernel<K, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096>(R, s, k1, k0, hist12, low, starts, u.sentinel, u.tilesum, u.tile_shift);
         if (timed) lt->end(s);
@@ -1450,7 +1457,8 @@ __global__ __launch_bounds__(BLOCK) void xl_count_kernel(Src kin, const int* n_p
     for (int i = 0; i < ITEMS; ++i) {
         const long long idx = base + (long long)i * BLOCK + threadIdx.x;
         const bool ok = idx < n;
-        xl_count(hist, ok, ok ? digit_of<K>(kin(idx), shift, mask) : 0u);
+        const K k = ok ? kin(idx) : (K)0;
+        xl_count(hist, ok && kin.keep(k), digit_of<K>(k, shift, mask));
     }
 }
 
@@ -1458,7 +1466,8 @@ __global__ __launch_bounds__(BLOCK) void xl_count_kernel(Src kin, const int* n_p
 // in front of its digits by itself.  zero[0, n_zero) is cleared on the way (for the kernel after the next).
 constexpr int XL_SCAN_ITEMS = 16, XL_SCAN_DIGITS = BLOCK * XL_SCAN_ITEMS;
 __global__ __launch_bounds__(BLOCK) void xl_starts_kernel(const u32* __restrict__ hist, u32* __restrict__ starts,
-                                                          u32* __restrict__ cursor, int* __restrict__ zero, int n_zero) {
+                                                          u32* __restrict__ cursor, int* __restrict__ zero, int n_zero,
+                                                          int* __restrict__ total) {
     __shared__ u32 smem[WAVES];
     const int t = threadIdx.x, d0 = blockIdx.x * XL_SCAN_DIGITS;
     for (int i = blockIdx.x * BLOCK + t; i < n_zero; i += gridDim.x * BLOCK) zero[i] = 0;
@@ -1484,6 +1493,7 @@ __global__ __launch_bounds__(BLOCK) void xl_starts_kernel(const u32* __restrict_
         cursor[d] = run;
         run += c[j];
     }
+    if (total && blockIdx.x == gridDim.x - 1 && t == BLOCK - 1) *total = (int)run;
 }
 
 // The partition: a tile's distinct digits are entered into a hash table in LDS (the lanes of a wave that share a digit
@@ -1517,7 +1527,7 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(Src kin, K* __restric
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < XL_ITEMS; ++i) {
-        const bool ok = base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n;
+        const bool ok = base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n && kin.keep(key[i]);
         const u32 d = digit_of<K>(key[i], shift, mask);
         const u64 same = wave_same_digit_lanes(ok, d);
         u32 slot = NONE, b = 0;
@@ -1543,7 +1553,7 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(Src kin, K* __restric
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < XL_ITEMS; ++i) {
-        if (base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n) {
+        if (base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n && kin.keep(key[i])) {
             const u32 pos = (place[i] != NONE ? count[place[i]] : 0u) + rank[i];
             if (pos < (u32)n) kout[pos] = key[i];  // (always, when hist and cursor are as described)
         }
@@ -1564,12 +1574,12 @@ inline int bucket_sort_xl(hipStream_t s, K* k0, K* k1, const int* n_ptr, int n_m
     }
     const UniqueCount<K> none{};
     const UniqueCount<K>& u = uq ? *uq : none;
-    xl_starts_kernel<<<(1 << bits) / XL_SCAN_DIGITS, BLOCK, 0, s>>>(xl.hist, xl.starts, xl.cursor, u.tilesum, u.tiles);
-    const int tiles = sort_tiles(n_max, XL_ITEMS);
+    xl_starts_kernel<<<(1 << bits) / XL_SCAN_DIGITS, BLOCK, 0, s>>>(xl.hist, xl.starts, xl.cursor, u.tilesum, u.tiles, u.total);
+    const int n_src = u.sources ? u.sources : n_max;
     if (src && counted)
-        xl_scatter_kernel<K, Src><<<tiles, BLOCK, 0, s>>>(*src, k1, n_ptr, n_max, low, mask, xl.cursor);
+        xl_scatter_kernel<K, Src><<<sort_tiles(n_src, XL_ITEMS), BLOCK, 0, s>>>(*src, k1, n_ptr, n_src, low, mask, xl.cursor);
     else
-        xl_scatter_kernel<K, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, mask, xl.cursor);
+        xl_scatter_kernel<K, ArrayKeys<K>><<<sort_tiles(n_max, XL_ITEMS), BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, mask, xl.cursor);
     const bool timed = lt && lt->begin(s, tag);
     launch_bucket_keys_kernel<K, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096>(1 << bits, s, k1, k0, xl.hist, low, xl.starts, u.sentinel, u.tilesum, u.tile_shift);
     if (timed) lt->end(s);
