@@ -57,12 +57,12 @@ enum picasso_option {
                                       launches of the path's largest kernels with hipEvents
                                       (see picasso_kernel_timing); an event pair costs several
                                       microseconds of queue time per launch, and such a call keeps
-                                      all its work on `stream` (as with PICASSO_OPT_OVERLAP 0), so
+                                      its sorts in launches of their own (as with
+                                      PICASSO_OPT_OVERLAP 0), so
                                       that a bracketed kernel runs alone on the chip; 0: off       */
-    PICASSO_OPT_OVERLAP = 4,       /* 1 (default): for inputs of 2^18 facets or more, the first
-                                      round's edge-key sort runs on a stream of the context's own
-                                      beside the vertex quadrics and joins `stream` before costs
-                                      are computed; 0: everything on `stream`                      */
+    PICASSO_OPT_OVERLAP = 4,       /* 1 (default): the first round's edge-key sort shares its
+                                      launches with the sort for the vertex quadrics; 0: one after
+                                      the other                                                    */
     PICASSO_OPT_TRUNC_BLOCK_MAX = 5,/* budget step (Alg. 2 lines 3-4 and 6): a mesh that formed more
                                       pairs than it may remove keeps its cheapest ones; while no
                                       such mesh formed more than this many pairs (default and
@@ -152,7 +152,8 @@ typedef struct picasso_stats {
     int32_t rounds;                          /* runs of the core algorithm executed                 */
     int32_t nv_out, nf_out;                  /* totals over all meshes                              */
     int32_t nv[PICASSO_STATS_ROUNDS];        /* vertices entering round r                           */
-    int32_t nf[PICASSO_STATS_ROUNDS];        /* facets entering round r                             */
+    int32_t nf[PICASSO_STATS_ROUNDS];        /* facets entering round r (after the first: those with three
+                                                distinct corners; repeated ones go at the end)      */
     int32_t ne[PICASSO_STATS_ROUNDS];        /* distinct edges in round r                           */
     int32_t nsel[PICASSO_STATS_ROUNDS];      /* vertices removed in round r (pairs; + joiners of line 11) */
     int32_t subrounds[PICASSO_STATS_ROUNDS]; /* selection sub-rounds launched in round r            */
@@ -178,17 +179,16 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  * bytes a launch of each is charged with (what the step has to move at least, from the sizes of the
  * round it runs in: nv vertices, nf facets, H = 3 nf half-edges, E distinct edges; N, F = the call's
  * input sizes):
- *   SORT          per-bucket kernel of the 64-bit edge-key sort (Alg. 2 line 1; the scatter passes
- *                 when an input beyond 2^23 keys falls back to plain radix passes): every 8-byte
+ *   SORT          per-bucket kernel of the 64-bit edge-key sort (Alg. 2 line 1): every 8-byte
  *                 key read and written once, 16 H.
  *   UNIQUE_COST   distinct edges, their costs (Alg. 2 line 2) and first bids: 8 H (sorted keys
  *                 read) + 13 E (edge key, cost key, state written) + 64 nv (every vertex record
  *                 read once) + 8 nv (one bid word per vertex).
  *   SUBROUND0     first grid-wide sub-round of the selection (Alg. 2 lines 3-10): 13 E read, E
  *                 written (edge states), 3 x 8 nv (bids read, next bids written, third array cleared).
- *   FACET_INSERT  facets re-indexed and entered into the hash set, cluster labels composed:
- *                 12 nf read + 12 nf re-indexed + 4 nf deciding slot + 4 nf table slot + 4 nv
- *                 (vertex map) + 8 N (labels read and written).
+ *   FACET_INSERT  facets re-indexed (after the last round also entered into the hash set), cluster
+ *                 labels composed: 12 nf read + 12 nf re-indexed + 4 nv (vertex map) + 8 N (labels
+ *                 read and written).
  *   QUADRIC_ROWS  vertex quadrics summed from the facets' planes (supplementary, vertex quadric
  *                 equation): 8 x 3F sorted incidences + 16 F planes + 12 N positions + 64 N records.
  *   SORT_INCIDENCE per-bucket kernel of the sort that brings the 3F (vertex, facet) incidence keys

@@ -135,6 +135,44 @@ __device__ __forceinline__ u32 edge_of_priority(const TieBreak& tb, u64 p) {
 }
 
 // ---------------------------------------------------------------------------
+// Round set-up
+// ---------------------------------------------------------------------------
+struct RoundTab {
+    int B;
+    const int* voff;
+    const int* target;
+    int* active;
+    int* stuck;
+    int* nrem;
+    int* matched;
+    int* mslots;
+    int first_round;
+};
+
+// Per-mesh budgets and the round's counters, by one workgroup.
+__device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) {
+    for (int i = threadIdx.x; i < R.B * MATCH_SLOTS; i += blockDim.x) R.mslots[(size_t)i * MATCH_PAD] = 0;
+    for (int b = threadIdx.x; b < R.B; b += blockDim.x) {
+        const int nvb = R.voff[b + 1] - R.voff[b];
+        if (!R.first_round && R.active[b] && R.matched[b] == 0) R.stuck[b] = 1;
+        const int act = (nvb > R.target[b]) && !R.stuck[b];
+        R.active[b] = act;
+        R.nrem[b] = act ? nvb - R.target[b] : 0;
+        R.matched[b] = 0;
+    }
+    if (threadIdx.x == 0) {
+        st->nh = 0;
+        st->ne = 0;
+        st->live[0] = 0;
+        st->live[1] = 0;
+        st->live[2] = 0;
+        st->trunc_n = 0;
+        st->sel_k = 0;
+        st->absorb_n = 0;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // S0: vertex quadrics (supplementary: facet quadric Q=(nn^T, dn, d^2); vertex
 // quadric = sum over adjacent facets, here in ascending facet order)
 // ---------------------------------------------------------------------------
@@ -207,24 +245,43 @@ struct HeaderInit {
 };
 
 // Incidence keys for S0: (vertex << fbits) | facet, one per facet corner, so that sorting the keys
-// alone lists every vertex's facets in ascending facet order.  With COUNT_SMALL / COUNT_LARGE the
-// kernel also adds the keys' top 8- / 12-bit digits (bits [ishift, ...)) to ihist, the histogram
-// that the sort of the keys starts from (zero on entry; see quadric_rows_kernel); that sort makes
-// the keys again from the validated facet array (IncidenceKeys), so they are written out
-// nowhere.  COUNT_XL: the digit is as wide as xl_mask says and counted in
-// memory (prim::bucket_sort_xl).
+// alone lists every vertex's facets in ascending facet order; edge keys for the first round (see edge_keys_kernel, which is
+// the first kernel of the others).  With COUNT_SMALL / COUNT_LARGE the
+// kernel also adds both keys' top 8- / 12-bit digits to the histograms that the sorts start from (zero on entry; left so
+// by quadric_rows_kernel and contract_kernel); the sorts make the keys again from the validated facets, so they are
+// written nowhere.  COUNT_XL: digits as wide as the masks say, counted in memory.  COUNT_NONE: no round follows.  edges: the
+// edges' digits are wanted, and the round's set-up is made.
+struct DigitCount {
+    u32* hist;
+    int shift;
+    u32 mask;
+};
+// One key per lane with `ok` counted, in the workgroup's LDS histogram or (COUNT_XL) in memory: the lanes of a wave that
+// share a digit, as the keys of neighbouring facets mostly do, with a single atomic.  By all lanes of a wave.
+template <int COUNT>
+__device__ __forceinline__ void count_digit(u32* lds, const DigitCount& D, bool ok, u64 k) {
+    const u32 d = (u32)(k >> D.shift) & D.mask;
+    if constexpr (COUNT == COUNT_XL) {
+        prim::xl_count(D.hist, ok, d);
+    } else if constexpr (COUNT != COUNT_NONE) {
+        const u64 same = prim::wave_same_digit_lanes(ok, d);
+        if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&lds[d], (u32)__popcll(same));
+    }
+}
+
 template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
                                                      const int* __restrict__ facets, int F, int B,
                                                      const int* __restrict__ voff, const int* __restrict__ foff,
                                                      VRec* __restrict__ vrec, int* __restrict__ cid,
-                                                     int* __restrict__ fcur, int fbits, int ishift, u32* __restrict__ ihist, State* st,
-                                                     u32* __restrict__ msd_hist, int s0_follows, HeaderInit init,
-                                                     float4* __restrict__ planes, u32 xl_mask, int* __restrict__ htab,
-                                                     int n_clear) {
+                                                     int* __restrict__ fcur, int fbits, DigitCount inc, DigitCount edge,
+                                                     int edges, int vbits, State* st, HeaderInit init,
+                                                     float4* __restrict__ planes, int* __restrict__ htab, int n_clear,
+                                                     u64* __restrict__ vmin0, u64* __restrict__ vmin1,
+                                                     int* __restrict__ mate, RoundTab R) {
     constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
     constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
-    __shared__ u32 hist[IN_LDS ? RADIX : 1];
+    __shared__ u32 hist[IN_LDS ? RADIX : 1], ehist[IN_LDS ? RADIX : 1];
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     const bool single = init.hdr != nullptr;  // one mesh, whose ranges are [0, N) and [0, F): the tables are not read here
@@ -240,24 +297,31 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
             init.hdr[i] = v;
         }
     }
-    // the edge-key sort's digit counts and cursors start every round at zero (see edge_keys_kernel)
-    for (int i = g; i < 2 * prim::MSD_HIST_WORDS; i += stride) msd_hist[i] = 0;
+    if (edges && blockIdx.x == 0) {
+        __syncthreads();  // (the header, where this workgroup has written it)
+        round_begin_block(R, st);
+    }
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
     if constexpr (IN_LDS) {
-        for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = 0;
+        for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = ehist[i] = 0;
         __syncthreads();
     }
     int err = 0;
     for (int w = g; w < N; w += stride) {
         float x = verts[3 * (size_t)w], y = verts[3 * (size_t)w + 1], z = verts[3 * (size_t)w + 2];
         if (!(isfinite(x) && isfinite(y) && isfinite(z))) err |= 2;
-        if (!s0_follows) {  // (else quadric_rows_kernel writes the whole record)
+        if (COUNT == COUNT_NONE) {  // (else quadric_rows_kernel writes the whole record)
             VRec r;
             r.x = x; r.y = y; r.z = z; r.w0 = 0.f;
             r.a00 = r.a01 = r.a02 = r.a11 = r.a12 = r.a22 = r.b0 = r.b1 = r.b2 = r.c = r.w1 = r.w2 = 0.f;
             vrec[w] = r;
         }
         cid[w] = w;
+        if (edges) {
+            vmin0[w] = VMIN_NONE;
+            vmin1[w] = VMIN_NONE;
+            mate[w] = -1;
+        }
     }
     for (int f0 = blockIdx.x * BLOCK; f0 < F; f0 += stride) {  // (whole waves, for the ballots below)
         const int f = f0 + threadIdx.x;
@@ -283,14 +347,13 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                 corner[c] = a;
                 k = ((u64)(u32)a << fbits) | (u64)(u32)f;
             }
-            if constexpr (COUNT == COUNT_XL) {
-                prim::xl_count(ihist, ok, (u32)(k >> ishift) & xl_mask);
-            } else if constexpr (IN_LDS) {
-                // neighbouring facets mostly refer to vertices with the same leading bits: the lanes of a
-                // wave that share a digit count themselves with a single LDS atomic
-                const u32 d = (u32)(k >> ishift) & (u32)(RADIX - 1);
-                const u64 same = prim::wave_same_digit_lanes(ok, d);
-                if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
+            count_digit<COUNT>(hist, inc, ok, k);
+        }
+        if (edges) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int a = corner[c], b = corner[c == 2 ? 0 : c + 1];
+                count_digit<COUNT>(ehist, edge, ok && a != b, edge_key(a, b, vbits));
             }
         }
         // the facet's plane, once per facet, for the vertex quadrics that S0 sums from it
@@ -299,8 +362,9 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
     if constexpr (IN_LDS) {
         __syncthreads();
         for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
-            const u32 c = hist[i];
-            if (c) atomicAdd(&ihist[i], c);
+            const u32 c = hist[i], e = ehist[i];
+            if (c) atomicAdd(&inc.hist[i], c);
+            if (e) atomicAdd(&edge.hist[i], e);
         }
     }
     if (err) atomicOr(&st->err, err);
@@ -321,14 +385,12 @@ struct RowKeys {
     __device__ __forceinline__ bool keep(u64) const { return true; }
 };
 
-// Adds the keys' digits to hist (COUNT as in init_kernel; COUNT_NONE: writes the keys out instead) and flags rows out
-// of range.
+// Adds the keys' digits to the sort's histogram (COUNT as in init_kernel) and flags rows out of range.
 constexpr int CSR_COUNT_ITEMS = 4;
 template <int COUNT>
-__global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, int shift, u32 xl_mask, u32* __restrict__ hist_out,
-                                                          u64* __restrict__ keys, int* __restrict__ err) {
+__global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, DigitCount rows, int* __restrict__ err) {
     constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
-    constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
+    constexpr bool IN_LDS = COUNT != COUNT_XL;
     constexpr int ITEMS = COUNT == COUNT_LARGE ? 16 : CSR_COUNT_ITEMS;
     __shared__ u32 hist[IN_LDS ? RADIX : 1];
     if constexpr (IN_LDS) {
@@ -345,21 +407,13 @@ __global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, in
             bad |= (u32)src.row_of[i] >= (u32)src.n_rows;
             k = src(i);
         }
-        const u32 d = (u32)(k >> shift);
-        if constexpr (COUNT == COUNT_XL) {
-            prim::xl_count(hist_out, ok, d & xl_mask);
-        } else if constexpr (IN_LDS) {
-            const u64 same = prim::wave_same_digit_lanes(ok, d & (u32)(RADIX - 1));
-            if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d & (u32)(RADIX - 1)], (u32)__popcll(same));
-        } else {
-            if (ok) keys[i] = k;
-        }
+        count_digit<COUNT>(hist, rows, ok, k);
     }
     if constexpr (IN_LDS) {
         __syncthreads();
         for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
             const u32 c = hist[i];
-            if (c) atomicAdd(&hist_out[i], c);
+            if (c) atomicAdd(&rows.hist[i], c);
         }
     }
     if (bad) atomicOr(err, ERR_BIT_BAD_INDEX);
@@ -508,52 +562,14 @@ __global__ __launch_bounds__(BLOCK) void quadric_rows_kernel(VRec* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Round set-up
-// ---------------------------------------------------------------------------
-struct RoundTab {
-    int B;
-    const int* voff;
-    const int* target;
-    int* active;
-    int* stuck;
-    int* nrem;
-    int* matched;
-    int* mslots;
-    int first_round;
-};
-
-// Per-mesh budgets and the round's counters, by one workgroup.
-__device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) {
-    for (int i = threadIdx.x; i < R.B * MATCH_SLOTS; i += blockDim.x) R.mslots[(size_t)i * MATCH_PAD] = 0;
-    for (int b = threadIdx.x; b < R.B; b += blockDim.x) {
-        const int nvb = R.voff[b + 1] - R.voff[b];
-        if (!R.first_round && R.active[b] && R.matched[b] == 0) R.stuck[b] = 1;
-        const int act = (nvb > R.target[b]) && !R.stuck[b];
-        R.active[b] = act;
-        R.nrem[b] = act ? nvb - R.target[b] : 0;
-        R.matched[b] = 0;
-    }
-    if (threadIdx.x == 0) {
-        st->nh = 0;
-        st->ne = 0;
-        st->live[0] = 0;
-        st->live[1] = 0;
-        st->live[2] = 0;
-        st->trunc_n = 0;
-        st->sel_k = 0;
-        st->absorb_n = 0;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // S1: candidate pairs = distinct mesh edges (Alg. 2 line 1)
 //
-// First kernel of a round: the round's set-up (block 0), the per-vertex selection state, and the digits of the
+// First kernel of every round but the first (whose part init_kernel takes): the round's set-up (block 0), the per-vertex selection state, and the digits of the
 // 64-bit keys (lower vertex, higher vertex), one per half-edge: the kernel adds the keys' top digits (8 bits with
 // COUNT_SMALL, 12 with COUNT_LARGE, as xl_mask says with COUNT_XL) to the histogram that the sort of the keys starts from
 // (zeroed beforehand); the sort makes the keys again from the facets, so they are not written.
 //
-// With REINDEX the round before has contracted pairs and the facets still name its vertices: they are taken to
+// The round before has contracted pairs and the facets still name its vertices: they are taken to
 // the new numbering in place (S5).  A facet that has collapsed is marked (-1, -1, -1) and stays where it is: facets keep
 // their places until the end of the call (a compaction each round read and wrote every facet twice more, in two
 // launches; 1.2 M vertices: 58 us of the rounds' facet work).  Facets that have become equal to another stay too:
@@ -574,11 +590,10 @@ __device__ __forceinline__ bool facet_collapsed(const Corners& q, const int* __r
     return (q.a == q.b || q.b == q.c || q.a == q.c) && done[mesh_of(voff, B, q.a)] != 0;
 }
 
-template <int COUNT, bool REINDEX>
+template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur, int F, State* st, int cur, int vbits,
                                                           u64* __restrict__ vmin0, u64* __restrict__ vmin1,
-                                                          int* __restrict__ mate, RoundTab R, int shift,
-                                                          u32* __restrict__ msd_hist, u32 xl_mask,
+                                                          int* __restrict__ mate, RoundTab R, DigitCount edge,
                                                           const int* __restrict__ vmap, const int* __restrict__ done,
                                                           int* __restrict__ cid, int n_orig) {
     constexpr int FACETS = COUNT == COUNT_SMALL ? 1 : 4;
@@ -607,48 +622,35 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
             ok[j] = f < F;
             q[j] = load_corners(fcur, (size_t)(ok[j] ? f : 0));
         }
-        if constexpr (REINDEX) {
-            Corners m[FACETS];
+        Corners m[FACETS];
 #pragma unroll
-            for (int j = 0; j < FACETS; ++j) {
-                ok[j] = ok[j] && q[j].a >= 0;
-                m[j] = Corners{vmap[max(q[j].a, 0)], vmap[max(q[j].b, 0)], vmap[max(q[j].c, 0)]};
-            }
+        for (int j = 0; j < FACETS; ++j) {
+            ok[j] = ok[j] && q[j].a >= 0;
+            m[j] = Corners{vmap[max(q[j].a, 0)], vmap[max(q[j].b, 0)], vmap[max(q[j].c, 0)]};
+        }
 #pragma unroll
-            for (int j = 0; j < FACETS; ++j) {
-                if (!ok[j]) continue;
-                q[j] = m[j];
-                if (facet_collapsed(q[j], R.voff, R.B, done)) q[j] = Corners{-1, -1, -1};
-                int* o = fcur + 3 * (size_t)(base + j * BLOCK + t);
-                o[0] = q[j].a; o[1] = q[j].b; o[2] = q[j].c;
-            }
+        for (int j = 0; j < FACETS; ++j) {
+            if (!ok[j]) continue;
+            q[j] = m[j];
+            if (facet_collapsed(q[j], R.voff, R.B, done)) q[j] = Corners{-1, -1, -1};
+            int* o = fcur + 3 * (size_t)(base + j * BLOCK + t);
+            o[0] = q[j].a; o[1] = q[j].b; o[2] = q[j].c;
         }
 #pragma unroll
         for (int j = 0; j < FACETS; ++j) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const int a = c == 0 ? q[j].a : (c == 1 ? q[j].b : q[j].c), b = c == 0 ? q[j].b : (c == 1 ? q[j].c : q[j].a);
-                const bool has = ok[j] && a != b;
-                const u64 k = edge_key(a, b, vbits);
-                if constexpr (COUNT == COUNT_XL) {
-                    prim::xl_count(msd_hist, has, (u32)(k >> shift) & xl_mask);
-                } else {
-                    // the lower vertices of neighbouring corners mostly share their leading bits: the lanes of
-                    // a wave that share a digit count themselves with a single LDS atomic
-                    const u32 d = (u32)(k >> shift) & (u32)(RADIX - 1);
-                    const u64 same = prim::wave_same_digit_lanes(has, d);
-                    if (has && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
-                }
+                count_digit<COUNT>(hist, edge, ok[j] && a != b, edge_key(a, b, vbits));
             }
         }
     }
-    if constexpr (REINDEX)
-        for (int o = g; o < n_orig; o += stride) cid[o] = vmap[cid[o]];
+    for (int o = g; o < n_orig; o += stride) cid[o] = vmap[cid[o]];
     if constexpr (IN_LDS) {
         __syncthreads();
         for (int i = t; i < RADIX; i += BLOCK) {
             const u32 c = hist[i];
-            if (c) atomicAdd(&msd_hist[i], c);
+            if (c) atomicAdd(&edge.hist[i], c);
         }
     }
 }

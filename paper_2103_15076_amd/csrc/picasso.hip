@@ -77,13 +77,12 @@ struct picasso_ctx {
     prim::SortScratch sort_sc{};
     u32* hist12 = nullptr;  // the bucket sorts' top-digit counts, cursors and first positions (3 x prim::MSD_HIST_WORDS)
     // The vertex->facet sort has buffers and scratch of its own, so that in the first round it can
-    // run beside the edge-key sort (neither depends on the other) on a second stream.
+    // share its launches with the edge-key sort (neither depends on the other).
     u64* s0_key[2] = {nullptr, nullptr};  // incidence keys (vertex, facet) of S0 and their sort's second buffer
     prim::SortScratch sort_sc_s0{};
     u32* hist12_s0 = nullptr;
     prim::XlScratch xl{}, xl_s0{};  // the same for the sorts of very large inputs
-    hipStream_t side = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    bool hist_dirty = true;  // hist12 may hold counts (it is zero between sorts otherwise)
     int64_t opt_overlap = 1;
     int64_t opt_trunc_block_max = TRUNC_BLOCK_CAP;
     // per-mesh tables
@@ -306,159 +305,143 @@ struct KernelBracket {
     KernelBracket& operator=(const KernelBracket&) = delete;
 };
 
-// Sort for keys whose leading bits are vertex ids (evenly spread): bucket sort
-// when the input is small enough for it, plain LSD passes otherwise.
-// which sort sort_by_vertex takes, named by the counting a producer of the keys may do for it (COUNT_NONE: plain radix passes,
-// for keys too narrow to have a top digit)
-inline int sort_by_vertex_path(long long n_max, int key_bits) {
-    if (n_max <= 0) return COUNT_NONE;
-    if (n_max <= prim::BUCKET_SORT_MAX_KEYS && key_bits > prim::BUCKET_MSD_BITS) return COUNT_SMALL;
-    if (n_max <= prim::BUCKET_SORT_LARGE_MAX_KEYS)
-        return key_bits > prim::BUCKET_LARGE_MSD_BITS ? COUNT_LARGE : COUNT_NONE;
-    return key_bits > prim::xl_digit_bits(n_max, key_bits) ? COUNT_XL : COUNT_NONE;
+// Bits of a vertex in the edge keys, of a facet in the incidence keys: what the largest number needs, but enough for as many
+// keys to have the top digit that prim::key_sort partitions them on.
+inline int edge_vertex_bits(int nv, long long n_keys) { return std::max(ceil_log2(nv), prim::key_bits_wanted(n_keys) / 2); }
+inline int item_bits(int n_rows, int n_items, long long n_keys) {
+    return std::max(ceil_log2(std::max(n_items, 1)), prim::key_bits_wanted(n_keys) - ceil_log2(n_rows));
 }
+inline int incidence_fbits(int N, int F) { return item_bits(N, F, 3ll * F); }
 
-// `uq` (keys without values, bucket sorts only): the sort also does the count pass of the compaction
-// that keeps one of every run of equal keys.
-template <typename K, bool HAS_VAL, class Src = prim::ArrayKeys<K>>
-int sort_by_vertex(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_ptr, int n_max, int key_bits,
-                   const prim::SortScratch& sc, u32* hist12, prim::LaunchTimer* lt = nullptr, int tag = 0,
-                   bool counted = false, const Src* src = nullptr, const prim::UniqueCount<K>* uq = nullptr,
-                   const prim::XlScratch* xl = nullptr) {
-    const int how = sort_by_vertex_path(n_max, key_bits);
-    if (how == COUNT_SMALL)
-        return prim::bucket_sort<K, HAS_VAL, Src>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, lt, tag, counted,
-                                                  hist12, src, uq);
-    if (how == COUNT_LARGE)
-        return prim::bucket_sort_large<K, HAS_VAL, Src>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, hist12, lt, tag,
-                                                        counted, src, uq);
-    if constexpr (!HAS_VAL) {
-        if (how == COUNT_XL && xl)
-            return prim::bucket_sort_xl<K, Src>(s, k0, k1, n_ptr, n_max, key_bits, *xl, lt, tag, counted, src, uq);
+// A sort of up to n keys made from `items` items (KeySort), with the context's first or second set of arrays.
+// Kernels that count the keys' digits for it go by COUNT_ (see init_kernel) and its DigitCount.
+prim::KeySort<u64> key_sort_for(picasso_ctx* c, bool second_set, long long n, int items, int key_bits) {
+    prim::KeySort<u64> S;
+    S.k0 = second_set ? c->s0_key[0] : c->key64[0];
+    S.k1 = second_set ? c->s0_key[1] : c->key64[1];
+    S.n = items;
+    S.key_bits = key_bits;
+    S.digit_bits = prim::key_digit_bits(n, key_bits);
+    if (S.digit_bits > prim::BUCKET_LARGE_MSD_BITS) {
+        const prim::XlScratch& x = second_set ? c->xl_s0 : c->xl;
+        S.hist = x.hist;
+        S.cursor = x.cursor;
+        S.starts = x.starts;
+    } else {
+        S.hist = second_set ? c->hist12_s0 : c->hist12;
+        S.cursor = S.hist + prim::MSD_HIST_WORDS;
+        S.starts = S.hist + 2 * prim::MSD_HIST_WORDS;
     }
-    return prim::radix_sort<K, HAS_VAL>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, lt, tag);
+    return S;
+}
+inline int count_kind(const prim::KeySort<u64>& S) {
+    return S.digit_bits == prim::BUCKET_MSD_BITS ? COUNT_SMALL : (S.digit_bits == prim::BUCKET_LARGE_MSD_BITS ? COUNT_LARGE : COUNT_XL);
+}
+inline DigitCount digit_count(const prim::KeySort<u64>& S) {
+    return DigitCount{S.hist, S.key_bits - S.digit_bits, (1u << S.digit_bits) - 1u};
+}
+// The arrays of the narrower digits are zero between sorts; the wide ones are cleared by this before their keys are counted.
+void clear_wide_counts(hipStream_t s, const prim::KeySort<u64>& S) {
+    if (count_kind(S) == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << S.digit_bits), BLOCK, 0, s>>>(S.hist, 1 << S.digit_bits, 0u);
 }
 
-// Bits of a vertex in the edge keys, of a vertex and of a facet in the incidence keys: what the largest number needs, but enough
-// for n_max keys to have a top digit (and so to be sorted by sort_by_vertex's bucket sorts, which the kernels count the digits for).
-inline int key_bits_wanted(long long n_max) {
-    if (n_max <= prim::BUCKET_SORT_MAX_KEYS) return prim::BUCKET_MSD_BITS + 2;
-    return n_max <= prim::BUCKET_SORT_LARGE_MAX_KEYS ? prim::BUCKET_LARGE_MSD_BITS + 2 : prim::XL_BITS_MAX + 2;
+// The sort of the edge keys of a round with nvt vertices and at most nfb facets that have not collapsed, of F.  It
+// also counts, per tile of the compaction that follows, the keys that differ from
+// the key in front of them: the count pass of the unique step.
+prim::KeySort<u64> edge_sort(picasso_ctx* c, int nvt, int nfb, int F) {
+    const int H = 3 * nfb, vbits = edge_vertex_bits(nvt, H), chunks = prim::compact_chunks_for(H);
+    prim::KeySort<u64> S = key_sort_for(c, false, H, 3 * F, 2 * vbits);
+    S.tilesum = c->tilesum;
+    S.tiles = prim::compact_tiles(H, chunks);
+    S.tile_shift = ceil_log2((long long)BLOCK * chunks);
+    S.sentinel = edge_sentinel(vbits);
+    S.total = &c->st->nh;
+    return S;
 }
-inline int edge_vertex_bits(int nv, long long n_keys) { return std::max(ceil_log2(nv), key_bits_wanted(n_keys) / 2); }
-inline int incidence_fbits(int N, int F) {
-    return std::max(ceil_log2(std::max(F, 1)), key_bits_wanted(3ll * F) - ceil_log2(N));
+// ... and of the incidence keys.
+prim::KeySort<u64> incidence_sort(picasso_ctx* c, int N, int F) {
+    return key_sort_for(c, true, 3ll * F, 3 * F, ceil_log2(N) + incidence_fbits(N, F));
 }
-inline int incidence_key_bits(int N, int F) { return ceil_log2(N) + incidence_fbits(N, F); }
 
-// Edge keys, their sort and the count half of the unique step (S1 up to where costs are needed)
-// for the round that starts with `nvt` vertices and at most `nfb` facets that have not collapsed, of F, on stream `st_`.
-// Rounds after the first re-index the facets on the way.  *skeys_out = the sorted keys.
-int issue_edge_prefix(picasso_ctx* c, hipStream_t st_, int B, int round_, int cur_, int nvt, int nfb, int N, int F,
-                      const u64** skeys_out) {
-    const int H_ = 3 * nfb;
-    const int vbits_ = edge_vertex_bits(nvt, H_);
-    const RoundTab rt{B, c->voff[cur_], c->target, c->active, c->stuck, c->nrem, c->matched, c->mslots, round_ == 0};
-    // the kernel also counts the keys' top digits for the sort they go to (the
-    // histogram and the cursors were zeroed by init_kernel, or by the contraction of the round before)
-    const int kb = 2 * vbits_;
-    const int how = H_ > 0 ? sort_by_vertex_path(H_, kb) : COUNT_SMALL;
-    const int bits = how == COUNT_XL ? prim::xl_digit_bits(H_, kb) : 0;
-    if (how == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, st_>>>(c->xl.hist, 1 << bits, 0u);
-    {
-        const KernelBracket timed(c, st_, PICASSO_KERNEL_FACET_INSERT, round_ - 1, round_ > 0);
-#define PICASSO_EDGE_KEYS(COUNT, GRID, SHIFT, HIST)                                                                     \
-    do {                                                                                                                 \
-        if (round_ > 0)                                                                                                  \
-            edge_keys_kernel<COUNT, true><<<GRID, BLOCK, 0, st_>>>(c->fcur, F, c->st, cur_, vbits_, c->vmin[0], c->vmin[1], \
-                                                                   c->mate, rt, SHIFT, HIST, (1u << bits) - 1u, c->vmap,   \
-                                                                   c->done, c->cid, N);                                    \
-        else                                                                                                             \
-            edge_keys_kernel<COUNT, false><<<GRID, BLOCK, 0, st_>>>(c->fcur, F, c->st, cur_, vbits_, c->vmin[0], c->vmin[1], \
-                                                                    c->mate, rt, SHIFT, HIST, (1u << bits) - 1u, nullptr,   \
-                                                                    nullptr, nullptr, 0);                                   \
-    } while (0)
-        // (a workgroup adds its whole histogram to the other's in the end: with 4096 digits it takes several turns)
-        if (how == COUNT_SMALL) PICASSO_EDGE_KEYS(COUNT_SMALL, grid_for(std::max(F, 1)), prim::bucket_sort_low_bits(kb), c->hist12);
-        else if (how == COUNT_LARGE) PICASSO_EDGE_KEYS(COUNT_LARGE, grid_for((F + 3) / 4, 2048), kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12);
-        else PICASSO_EDGE_KEYS(COUNT_XL, grid_for((F + 3) / 4, 8192), kb - bits, c->xl.hist);
+RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
+    return RoundTab{B, c->voff[cur_], c->target, c->active, c->stuck, c->nrem, c->matched, c->mslots, round_ == 0};
+}
+
+// First kernel of a round after the first: facets and labels follow the last contraction, the edges' digits are counted.
+void launch_edge_keys(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, const prim::KeySort<u64>& S, int N, int F) {
+    clear_wide_counts(s, S);
+    c->hist_dirty = true;
+    const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round_ - 1);
+#define PICASSO_EDGE_KEYS(COUNT, GRID)                                                                                        \
+    edge_keys_kernel<COUNT><<<GRID, BLOCK, 0, s>>>(c->fcur, F, c->st, cur_, S.key_bits / 2, c->vmin[0], c->vmin[1], c->mate, \
+                                                   round_tab(c, B, round_, cur_), digit_count(S), c->vmap, c->done, c->cid, N)
+    // (a workgroup adds its whole histogram to the other's in the end: with 4096 digits it takes several turns)
+    switch (count_kind(S)) {
+        case COUNT_SMALL: PICASSO_EDGE_KEYS(COUNT_SMALL, grid_for(std::max(F, 1))); break;
+        case COUNT_LARGE: PICASSO_EDGE_KEYS(COUNT_LARGE, grid_for((F + 3) / 4, 2048)); break;
+        default: PICASSO_EDGE_KEYS(COUNT_XL, grid_for((F + 3) / 4, 8192));
+    }
 #undef PICASSO_EDGE_KEYS
-    }
-    *skeys_out = c->key64[0];
-    if (H_ <= 0) return PICASSO_OK;
-    const EdgeKeys src{c->fcur, vbits_};  // (the sorts read the keys from here)
-    // the bucket sorts also count, per tile of the compaction that follows, the keys that differ from
-    // the key in front of them: the count pass of the unique step
-    prim::UniqueCount<u64> uq;
-    const int chunks = prim::compact_chunks_for(H_);
-    uq.tilesum = c->tilesum;
-    uq.tiles = prim::compact_tiles(H_, chunks);
-    uq.tile_shift = ceil_log2((long long)BLOCK * chunks);
-    uq.sentinel = edge_sentinel(vbits_);
-    uq.total = &c->st->nh;
-    uq.sources = 3 * F;
-    const int where = sort_by_vertex<u64, false, EdgeKeys>(st_, c->key64[0], c->key64[1], nullptr, nullptr, nullptr, H_, kb,
-                                                           c->sort_sc, c->hist12, c->kt_this_call ? &c->kt : nullptr, round_,
-                                                           true, &src, &uq, &c->xl);
-    if (where < 0) return PICASSO_ERR_HIP;
-    prim::compact_scan_sums(st_, &c->st->nh, H_, c->tilesum);
-    *skeys_out = where ? c->key64[1] : c->key64[0];
-    return PICASSO_OK;
 }
 
-constexpr int64_t OVERLAP_MIN_FACETS = 1 << 18;
+// Sorts the edge keys (whose digits have been counted): they end up in key64[0].
+bool sort_edges(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, int round_) {
+    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<EdgeKeys>{{c->fcur, S.key_bits / 2}},
+                          c->kt_this_call ? &c->kt : nullptr, round_);
+}
+bool sort_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, int N, int F) {
+    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<IncidenceKeys>{{c->fcur, incidence_fbits(N, F)}},
+                          c->kt_this_call ? &c->kt : nullptr, PICASSO_KERNEL_SORT_INCIDENCE << 8);
+}
+// Both sorts of the first round in the same launches.
+bool sort_edges_and_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& E, const prim::KeySort<u64>& I, int N, int F) {
+    return prim::key_sort(s, I, &E, prim::TwoSources<IncidenceKeys, EdgeKeys>{{c->fcur, incidence_fbits(N, F)}, {c->fcur, E.key_bits / 2}});
+}
+
 constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 
 // Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
 // before the first round's costs are computed (24 bytes per facet there, 16 needed).
 inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c->ekey); }
 
-// The validating kernel, instantiated for the sort the incidence keys go to.
+// The validating kernel, instantiated for the sorts its keys go to.  work: rounds (or S0) follow; edges: the first round's
+// set-up and edges as well.
 int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, const int32_t* d_facets, int F, int B,
-                bool with_keys, HeaderInit init = HeaderInit{nullptr, 0, 0, 0, 0, 0, 0, 0}) {
-    const int fbits = incidence_fbits(N, F), kb = incidence_key_bits(N, F);
-    const int how = with_keys ? sort_by_vertex_path(3ll * F, kb) : COUNT_NONE;
-    const int s0 = with_keys ? 1 : 0;
-    float4* planes = with_keys ? facet_planes(c) : nullptr;
-    const int grid = grid_for(std::max(N, F), 4096);
-    const int bits = how == COUNT_XL ? prim::xl_digit_bits(3ll * F, kb) : 0;
+                bool work, bool edges, HeaderInit init = HeaderInit{nullptr, 0, 0, 0, 0, 0, 0, 0}) {
+    const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F);
+    if (work && c->hist_dirty)  // (a call ended between a count of its edges and the contraction that clears it)
+        prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, 2 * prim::MSD_HIST_WORDS, 0u);
+    if (work) {
+        c->hist_dirty = edges;
+        clear_wide_counts(s, I);
+        if (edges) clear_wide_counts(s, E);
+    }
+    float4* planes = work ? facet_planes(c) : nullptr;
     // the facet set that the end of the call uses (larger ones are cleared by the last contraction, when fewer facets are left)
     const int n_clear = F <= CLEAR_AHEAD_MAX_FACETS ? (int)facet_slots((size_t)F) : 0;
-    if (how == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, s>>>(c->xl_s0.hist, 1 << bits, 0u);
-#define PICASSO_INIT(COUNT, SHIFT, HIST)                                                                                     \
-    init_kernel<COUNT><<<grid, BLOCK, 0, s>>>(d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, \
-                                              fbits, SHIFT, HIST, c->st, c->hist12, s0, init, planes, (1u << bits) - 1u,    \
-                                              c->htab, n_clear)
-    if (how == COUNT_SMALL) PICASSO_INIT(COUNT_SMALL, prim::bucket_sort_low_bits(kb), c->hist12_s0);
-    else if (how == COUNT_LARGE) PICASSO_INIT(COUNT_LARGE, kb - prim::BUCKET_LARGE_MSD_BITS, c->hist12_s0);
-    else if (how == COUNT_XL) PICASSO_INIT(COUNT_XL, kb - bits, c->xl_s0.hist);
-    else PICASSO_INIT(COUNT_NONE, 0, nullptr);
+#define PICASSO_INIT(COUNT)                                                                                                    \
+    init_kernel<COUNT><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
+        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, incidence_fbits(N, F), digit_count(I),   \
+        digit_count(E), edges ? 1 : 0, E.key_bits / 2, c->st, init, planes, c->htab, n_clear, c->vmin[0], c->vmin[1], c->mate, \
+        round_tab(c, B, 0, 0))
+    if (!work) PICASSO_INIT(COUNT_NONE);
+    else if (count_kind(I) == COUNT_SMALL) PICASSO_INIT(COUNT_SMALL);
+    else if (count_kind(I) == COUNT_LARGE) PICASSO_INIT(COUNT_LARGE);
+    else PICASSO_INIT(COUNT_XL);
 #undef PICASSO_INIT
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }
 
-// S0 on the incidence keys written by init_kernel (whose digit counts are in hist12_s0).
-int run_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, int F) {
+// The vertices' quadrics from the sorted incidence keys.
+void launch_quadric_rows(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& I, const float* d_verts, int N, int F) {
     const int H = 3 * F;
-    const int fbits = incidence_fbits(N, F), kb = incidence_key_bits(N, F);
     if (F > 0) {
-        const IncidenceKeys src{c->fcur, fbits};  // (the sorts read the keys from here)
-        int where = sort_by_vertex<u64, false, IncidenceKeys>(s, c->s0_key[0], c->s0_key[1], nullptr, nullptr,
-                                                                  nullptr, H, kb, c->sort_sc_s0, c->hist12_s0,
-                                                                  c->kt_this_call ? &c->kt : nullptr,
-                                                                  PICASSO_KERNEL_SORT_INCIDENCE << 8, true, &src,
-                                                                  nullptr, &c->xl_s0);
-        if (where < 0) return PICASSO_ERR_HIP;
-        const u64* skey = where ? c->s0_key[1] : c->s0_key[0];
-        const int tiles = (H + QR_TILE - 1) / QR_TILE;
         const KernelBracket timed(c, s, PICASSO_KERNEL_QUADRIC_ROWS, 0);
-        quadric_rows_kernel<<<tiles, BLOCK, 0, s>>>(c->vrec[0], d_verts, N, facet_planes(c), skey, H, fbits,
-                                                    c->hist12_s0);
+        quadric_rows_kernel<<<(H + QR_TILE - 1) / QR_TILE, BLOCK, 0, s>>>(c->vrec[0], d_verts, N, facet_planes(c), I.k0, H,
+                                                                         incidence_fbits(N, F), c->hist12_s0);
     } else {
-        quadric_rows_kernel<<<grid_for(N, 4096), BLOCK, 0, s>>>(c->vrec[0], d_verts, N, nullptr, nullptr, 0, 0,
-                                                               c->hist12_s0);
+        quadric_rows_kernel<<<grid_for(N, 4096), BLOCK, 0, s>>>(c->vrec[0], d_verts, N, nullptr, nullptr, 0, 0, c->hist12_s0);
     }
-    return PICASSO_OK;
 }
 
 // Fills the pinned image of the header (State + per-mesh tables) and sends it with one copy.
@@ -665,10 +648,10 @@ int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne,
     }
     absorb_keys_kernel<<<grid_for(n_list), BLOCK, 0, s>>>(c->list, c->st, c->ekey, c->ecost, vbits, c->mate, c->abid,
                                                          c->arep, c->acnt, c->key64[0], tb);
-    const int where = sort_by_vertex<u64, false>(s, c->key64[0], c->key64[1], nullptr, nullptr, &c->st->absorb_n,
-                                                 (int)n_list, 2 * vbits, c->sort_sc, c->hist12);
-    if (where < 0) return PICASSO_ERR_HIP;
-    *akeys = where ? c->key64[1] : c->key64[0];
+    prim::KeySort<u64> S = key_sort_for(c, false, n_list, (int)n_list, 2 * vbits);
+    S.n_ptr = &c->st->absorb_n;
+    if (!prim::key_sort_array(s, S)) return PICASSO_ERR_HIP;
+    *akeys = S.k0;
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -732,29 +715,23 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     };
     bool work = any_active() && c->opt_max_rounds != 0;
 
-    // In the first round the vertex quadrics (S0) and the edge keys (S1) depend only on the validated
-    // input, not on each other: S1's prefix goes to the context's side stream and joins before the
-    // costs are computed.  (Serial when stage times are being recorded, to keep them attributable, and in a
-    // call whose kernels are bracketed by events: a bracketed kernel then has the chip to itself, and its
-    // duration is its own.)
-    // The fork and join cost about as much as a few small kernels, so small inputs stay on one stream.
-    const u64* skeys = nullptr;
-    const bool overlap = work && c->opt_overlap && c->side && !tm.on && !c->kt_this_call && F >= OVERLAP_MIN_FACETS;
+    // In the first round the sorts of the incidence keys (S0) and of the edge keys (S1) depend only on the validated
+    // input, not on each other: they share their launches.  (Not when stage times are being recorded, to keep them
+    // attributable, and in a call whose kernels are bracketed by events: a bracketed kernel then has the chip to itself,
+    // and its duration is its own.)
+    const bool together = work && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call;
     tm.begin(0, PICASSO_ST_QUADRICS);
-    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, hinit);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, work, hinit);
     if (rc != PICASSO_OK) return rc;
-    if (overlap) {
-        HIP_TRY(c, hipEventRecord(c->ev_fork, s));
-        HIP_TRY(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
-        rc = issue_edge_prefix(c, c->side, B, 0, 0, N, F, N, F, &skeys);
-        if (rc != PICASSO_OK) return rc;
-        HIP_TRY(c, hipEventRecord(c->ev_join, c->side));
-    }
     if (work) {
-        rc = run_vertex_quadrics(c, s, d_verts, N, F);
-        if (rc != PICASSO_OK) return rc;
+        const prim::KeySort<u64> I = incidence_sort(c, N, F);
+        if (together) {
+            if (!sort_edges_and_incidences(c, s, edge_sort(c, N, F, F), I, N, F)) return PICASSO_ERR_HIP;
+        } else if (F > 0) {
+            if (!sort_incidences(c, s, I, N, F)) return PICASSO_ERR_HIP;
+        }
+        launch_quadric_rows(c, s, I, d_verts, N, F);
     }
-    if (overlap) HIP_TRY(c, hipStreamWaitEvent(s, c->ev_join, 0));
     tm.end();
 
     State* hst = reinterpret_cast<State*>(c->h_pin);  // read-back area
@@ -776,10 +753,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 
         // ---- S1 (+S2): edges and costs
         tm.begin(round, PICASSO_ST_EDGES);
-        if (!(round == 0 && overlap)) {
-            rc = issue_edge_prefix(c, s, B, round, cur, nv_total, nf_bound, N, F, &skeys);
-            if (rc != PICASSO_OK) return rc;
-        }
+        const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F);
+        const u64* skeys = E.k0;
+        if (round > 0) launch_edge_keys(c, s, B, round, cur, E, N, F);
+        if (!(round == 0 && together) && H > 0 && !sort_edges(c, s, E, round)) return PICASSO_ERR_HIP;
+        if (H > 0) prim::compact_scan_sums(s, &c->st->nh, H, c->tilesum);
         renumbered = false;
         UniquePred up{skeys, edge_sentinel(vbits)};
 #define PICASSO_UNIQUE(PLACE, SHUFFLE, RCOND)                                                                       \
@@ -1036,6 +1014,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             tm.end();
             slots_clear = std::max(slots_clear, clear);
         }
+        c->hist_dirty = false;
         nv_total -= n_sel + n_joined;
         cur ^= 1;
         ++round;
@@ -1130,6 +1109,21 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     return warn;
 }
 
+// S0 for the entry points that give its results out: behind init_kernel, if that has found nothing wrong.
+int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, int F) {
+    int rc = read_header(c, s);
+    if (rc != PICASSO_OK) return rc;
+    rc = status_from_err_bits(reinterpret_cast<State*>(c->h_pin)->err);
+    if (rc != PICASSO_OK) {  // S0 will not run: take back the digit counts the validating kernel has added
+        prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12_s0, 2 * prim::MSD_HIST_WORDS, 0u);
+        return rc;
+    }
+    const prim::KeySort<u64> I = incidence_sort(c, N, F);
+    if (F > 0 && !sort_incidences(c, s, I, N, F)) return PICASSO_ERR_HIP;
+    launch_quadric_rows(c, s, I, d_verts, N, F);
+    return PICASSO_OK;
+}
+
 // Filter gradients of the convolutions' backward passes: `rows` x C values summed over n_rows rows in two stages
 // (conv::rows_to_partial, conv::reduce_rows_stage2_kernel).  Stage 1's workgroups leave their partial sums in the
 // context's sort buffer.  As many workgroups as the chip holds at once (256 compute units; a workgroup takes several
@@ -1173,25 +1167,20 @@ void sum_filter_rows(hipStream_t s, const FilterSplit& sp, int width, float* d_o
 // Items 0 .. n - 1 listed per row (d_row_of[i] in [0, n_rows)), ascending: d_off [n_rows + 1], d_items [n].
 int build_csr(picasso_ctx* c, hipStream_t s, const int32_t* d_row_of, int n, int n_rows, int32_t* d_off, int32_t* d_items) {
     HIP_TRY(c, hipSetDevice(c->device));
-    const int ibits = ceil_log2(n), kb = ibits + ceil_log2(n_rows);
+    const int ibits = item_bits(n_rows, n, n);
     const RowKeys src{d_row_of, n_rows, ibits};
-    const int how = sort_by_vertex_path(n, kb);
+    prim::KeySort<u64> S = key_sort_for(c, true, n, n, ibits + ceil_log2(n_rows));
+    S.k0 = c->key64[0];
+    S.k1 = c->key64[1];
+    clear_wide_counts(s, S);
     int* err = &c->st->err;
-    if (how == COUNT_SMALL) {
-        csr_count_kernel<COUNT_SMALL><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, prim::bucket_sort_low_bits(kb), 0u, c->hist12_s0, nullptr, err);
-    } else if (how == COUNT_LARGE) {
-        csr_count_kernel<COUNT_LARGE><<<prim::sort_tiles(n, 16), BLOCK, 0, s>>>(src, n, kb - prim::BUCKET_LARGE_MSD_BITS, 0u, c->hist12_s0, nullptr, err);
-    } else if (how == COUNT_XL) {
-        const int bits = prim::xl_digit_bits(n, kb);
-        prim::fill_u32_kernel<<<grid_for(1 << bits), BLOCK, 0, s>>>(c->xl_s0.hist, 1 << bits, 0u);
-        csr_count_kernel<COUNT_XL><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, kb - bits, (1u << bits) - 1u, c->xl_s0.hist, nullptr, err);
-    } else {
-        csr_count_kernel<COUNT_NONE><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, 0, 0u, nullptr, c->key64[0], err);
+    switch (count_kind(S)) {
+        case COUNT_SMALL: csr_count_kernel<COUNT_SMALL><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, digit_count(S), err); break;
+        case COUNT_LARGE: csr_count_kernel<COUNT_LARGE><<<prim::sort_tiles(n, 16), BLOCK, 0, s>>>(src, n, digit_count(S), err); break;
+        default: csr_count_kernel<COUNT_XL><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, digit_count(S), err);
     }
-    const int where = sort_by_vertex<u64, false, RowKeys>(s, c->key64[0], c->key64[1], nullptr, nullptr, nullptr, n, kb, c->sort_sc,
-                                                         c->hist12_s0, nullptr, 0, how != COUNT_NONE, &src, nullptr, &c->xl_s0);
-    if (where < 0) return PICASSO_ERR_HIP;
-    csr_finish_kernel<<<grid_for(n), BLOCK, 0, s>>>(where ? c->key64[1] : c->key64[0], ibits, n, n_rows, d_off, d_items, c->hist12_s0);
+    if (!prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<RowKeys>{src})) return PICASSO_ERR_HIP;
+    csr_finish_kernel<<<grid_for(n), BLOCK, 0, s>>>(S.k0, ibits, n, n_rows, d_off, d_items, c->hist12_s0);
     const int rc = read_header(c, s);
     if (rc != PICASSO_OK) return rc;
     HIP_TRY(c, hipGetLastError());
@@ -1275,9 +1264,6 @@ int picasso_create(picasso_ctx** out, int device, int64_t max_verts, int64_t max
     (void)hipEventCreate(&c->ev_total[0]);
     (void)hipEventCreate(&c->ev_total[1]);
     for (hipEvent_t& e : c->kt_pool) (void)hipEventCreate(&e);
-    if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) c->side = nullptr;
-    (void)hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
-    (void)hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
     *out = c;
     return PICASSO_OK;
 }
@@ -1291,9 +1277,6 @@ void picasso_destroy(picasso_ctx* c) {
     (void)hipEventDestroy(c->ev_total[0]);
     (void)hipEventDestroy(c->ev_total[1]);
     for (hipEvent_t& e : c->kt_pool) (void)hipEventDestroy(e);
-    if (c->side) (void)hipStreamDestroy(c->side);
-    if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
-    if (c->ev_join) (void)hipEventDestroy(c->ev_join);
     if (c->h_pin) (void)hipHostFree(c->h_pin);
     if (c->ws) (void)hipFree(c->ws);
     delete[] c->h_mesh;
@@ -1429,17 +1412,9 @@ int picasso_vertex_quadrics(picasso_ctx* c, void* stream, const float* d_verts, 
     int64_t n64, f64;
     int rc = upload_header(c, s, 1, &N, &F, &big, &n64, &f64);
     if (rc != PICASSO_OK) return rc;
-    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true, false);
     if (rc != PICASSO_OK) return rc;
-    State* hst = reinterpret_cast<State*>(c->h_pin);
-    rc = read_header(c, s);
-    if (rc != PICASSO_OK) return rc;
-    rc = status_from_err_bits(hst->err);
-    if (rc != PICASSO_OK) {  // S0 will not run: take back the digit counts the validating kernel has added
-        prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12_s0, 2 * prim::MSD_HIST_WORDS, 0u);
-        return rc;
-    }
-    rc = run_vertex_quadrics(c, s, d_verts, N, F);
+    rc = checked_vertex_quadrics(c, s, d_verts, N, F);
     if (rc != PICASSO_OK) return rc;
     export_quadrics_kernel<<<grid_for(N), BLOCK, 0, s>>>(c->vrec[0], N, d_quadrics_out);
     HIP_TRY(c, hipStreamSynchronize(s));
@@ -1458,23 +1433,19 @@ int picasso_edge_costs(picasso_ctx* c, void* stream, const float* d_verts, int32
     int64_t n64, f64;
     int rc = upload_header(c, s, 1, &N, &F, &one, &n64, &f64);
     if (rc != PICASSO_OK) return rc;
-    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true, true);
     if (rc != PICASSO_OK) return rc;
     State* hst = reinterpret_cast<State*>(c->h_pin);
-    rc = read_header(c, s);
-    if (rc != PICASSO_OK) return rc;
-    rc = status_from_err_bits(hst->err);
-    if (rc != PICASSO_OK) {  // S0 will not run: take back the digit counts the validating kernel has added
-        prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12_s0, 2 * prim::MSD_HIST_WORDS, 0u);
-        return rc;
-    }
-    rc = run_vertex_quadrics(c, s, d_verts, N, F);
+    rc = checked_vertex_quadrics(c, s, d_verts, N, F);
     if (rc != PICASSO_OK) return rc;
     const int H = 3 * F, vbits = edge_vertex_bits(N, H);
     MeshTab mt{1, c->voff[0], c->target, c->active, c->nrem, c->matched, c->mslots};
-    const u64* skeys = nullptr;
-    rc = issue_edge_prefix(c, s, 1, 0, 0, N, F, N, F, &skeys);
-    if (rc != PICASSO_OK) return rc;
+    const prim::KeySort<u64> E = edge_sort(c, N, F, F);
+    const u64* skeys = E.k0;
+    if (F > 0) {
+        if (!sort_edges(c, s, E, 0)) return PICASSO_ERR_HIP;
+        prim::compact_scan_sums(s, &c->st->nh, H, c->tilesum);
+    }
     UniquePred up{skeys, edge_sentinel(vbits)};
     if (c->opt_placement == PLACE_INVERSE) {
         UniqueOutT<PLACE_INVERSE, false> uo{skeys, c->ekey, c->ecost, c->vrec[0], c->vmin[0], c->estate, vbits, mt,
@@ -1832,13 +1803,26 @@ int picasso_bucket_sort(picasso_ctx* c, void* stream, int key_bytes, void* d_key
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
     int rc;
+    c->hist_dirty = true;
+    auto large_keys = [&](auto* k0, auto* k1) -> int {
+        prim::KeySort<std::remove_pointer_t<decltype(k0)>> S;
+        S.k0 = k0;
+        S.k1 = k1;
+        S.n = (int)n;
+        S.key_bits = key_bits;
+        S.digit_bits = prim::BUCKET_LARGE_MSD_BITS;
+        S.hist = c->hist12;
+        S.cursor = S.hist + prim::MSD_HIST_WORDS;
+        S.starts = S.hist + 2 * prim::MSD_HIST_WORDS;
+        return prim::key_sort_array(s, S) ? 0 : -1;
+    };
     const bool large = n > prim::BUCKET_SORT_MAX_KEYS;
     if (large && key_bits <= prim::BUCKET_LARGE_MSD_BITS) return PICASSO_ERR_INVALID_ARG;
     if (key_bytes == 8) {
         u64* k1 = c->key64[1];
         if (large)
-            rc = d_vals ? prim::bucket_sort_large<u64, true>(s, (u64*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
-                        : prim::bucket_sort_large<u64, false>(s, (u64*)d_keys, k1, nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc, c->hist12);
+            rc = d_vals ? prim::bucket_sort_large<u64>(s, (u64*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
+                        : large_keys((u64*)d_keys, k1);
         else
             rc = d_vals ? prim::bucket_sort<u64, true>(s, (u64*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc)
                         : prim::bucket_sort<u64, false>(s, (u64*)d_keys, k1, nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc);
@@ -1846,8 +1830,8 @@ int picasso_bucket_sort(picasso_ctx* c, void* stream, int key_bytes, void* d_key
     } else {
         u32* k1 = reinterpret_cast<u32*>(c->key64[1]);
         if (large)
-            rc = d_vals ? prim::bucket_sort_large<u32, true>(s, (u32*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
-                        : prim::bucket_sort_large<u32, false>(s, (u32*)d_keys, k1, nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc, c->hist12);
+            rc = d_vals ? prim::bucket_sort_large<u32>(s, (u32*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
+                        : large_keys((u32*)d_keys, k1);
         else
             rc = d_vals ? prim::bucket_sort<u32, true>(s, (u32*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc)
                         : prim::bucket_sort<u32, false>(s, (u32*)d_keys, k1, nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc);

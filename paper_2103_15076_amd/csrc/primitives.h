@@ -283,8 +283,8 @@ struct SortScratch {
     int T;        // row stride = tiles at capacity
 };
 
-// Optional hipEvent bracket around the launches of the sort's main streaming
-// kernel (the per-bucket sort; the scatter passes when plain LSD is used), for
+// Optional hipEvent bracket around the launch of key_sort's main streaming
+// kernel (the per-bucket sort), for
 // the roofline measurement of the benchmark; `tag` travels to the record.
 struct LaunchTimer {
     hipEvent_t* pool = nullptr;
@@ -318,7 +318,7 @@ inline int sort_table_stride(long long n_cap) {
 
 template <typename K, bool HAS_VAL, int ITEMS>
 inline int radix_sort_impl(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_ptr, int n_max, int key_bits,
-                           const SortScratch& sc, LaunchTimer* lt, int tag) {
+                           const SortScratch& sc) {
     const int passes = (key_bits + 7) / 8;
     const int per = (key_bits + passes - 1) / passes;
     const int tiles = sort_tiles(n_max, ITEMS);
@@ -331,10 +331,8 @@ inline int radix_sort_impl(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const 
         u32* vout = cur ? v0 : v1;
         radix_upsweep_kernel<K, ITEMS><<<tiles, BLOCK, 0, s>>>(kin, n_ptr, n_max, sc.T, sc.table, shift, bits);
         radix_scan_kernel<<<1 << bits, BLOCK, 0, s>>>(sc.table, sc.totals, n_ptr, n_max, sc.T, BLOCK * ITEMS);
-        const bool timed = lt && lt->begin(s, tag);
         radix_downsweep_kernel<K, HAS_VAL, ITEMS>
             <<<tiles, BLOCK, 0, s>>>(kin, kout, vin, vout, n_ptr, n_max, sc.T, sc.table, sc.totals, shift, bits);
-        if (timed) lt->end(s);
         shift += bits;
         cur ^= 1;
     }
@@ -347,11 +345,11 @@ inline int radix_sort_impl(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const 
 // launch error.  n_max bounds the device-side count for the grid size.
 template <typename K, bool HAS_VAL>
 inline int radix_sort(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_ptr, int n_max, int key_bits,
-                      const SortScratch& sc, LaunchTimer* lt = nullptr, int tag = 0) {
+                      const SortScratch& sc) {
     if (n_max <= 0 || key_bits <= 0) return 0;
     if (sort_items_for(n_max) == SORT_ITEMS_SMALL)
-        return radix_sort_impl<K, HAS_VAL, SORT_ITEMS_SMALL>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, lt, tag);
-    return radix_sort_impl<K, HAS_VAL, SORT_ITEMS_BIG>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc, lt, tag);
+        return radix_sort_impl<K, HAS_VAL, SORT_ITEMS_SMALL>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc);
+    return radix_sort_impl<K, HAS_VAL, SORT_ITEMS_BIG>(s, k0, k1, v0, v1, n_ptr, n_max, key_bits, sc);
 }
 
 // ---------------------------------------------------------------------------
@@ -711,6 +709,25 @@ __global__ __launch_bounds__(BUCKET_THREADS) void bucket_sort_kernel(K* __restri
                                                                   low_bits);
 }
 
+// A sort of keys WITHOUT values by partition on their top digit and a sort of each bucket (key_sort).
+template <typename K>
+struct KeySort {
+    K* k0 = nullptr;  // receives the sorted keys
+    K* k1 = nullptr;  // ... the partitioned ones
+    const int* n_ptr = nullptr;
+    int n = 0;        // items of the source (at *n_ptr, where that is given, and n at most)
+    int key_bits = 0, digit_bits = 0;
+    u32* hist = nullptr;    // keys per digit
+    u32* cursor = nullptr;  // as much of each digit's range as is taken: zero (8-bit digits), or set by key_starts_kernel
+    u32* starts = nullptr;  // first position of each digit's range
+    // What the sort may do for a compaction that follows it: the count pass of "keep the first of every run of equal keys,
+    // `sentinel` excepted" with tiles of 2^tile_shift positions (tilesum is zeroed on the way).  tilesum == nullptr: nothing.
+    int* tilesum = nullptr;
+    int tiles = 0, tile_shift = 0;
+    K sentinel = (K)0;
+    int* total = nullptr;   // receives the number of keys (those that the source keeps)
+};
+
 // ---------------------------------------------------------------------------
 // The per-bucket kernel for keys WITHOUT values (the sorts of the decimation path: incidence keys
 // and edge keys).  Equal keys are indistinguishable, so nothing has to be stable:
@@ -787,10 +804,7 @@ __device__ __forceinline__ void group_sort_lds(K* skey, int gs, int g) {
 }
 
 template <typename K, typename LK, int THREADS, int ITEMS, bool COUNT_UNIQUE>
-__global__ __launch_bounds__(THREADS) void bucket_keys_kernel(K* __restrict__ kin, K* __restrict__ kout,
-                                                              const u32* __restrict__ totals,
-                                                              const u32* __restrict__ starts, int low_bits, K sentinel,
-                                                              int* __restrict__ tilesum, int tile_shift) {
+__global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int buckets_first) {
     constexpr int NW = THREADS / 64;
     constexpr int CAP = THREADS * ITEMS;
     constexpr int RMAX = 1 << BUCKET_GROUP_BITS;
@@ -807,12 +821,19 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(K* __restrict__ ki
     __shared__ int tcnt[COUNT_UNIQUE ? TALLY : 1];
     const int t = threadIdx.x, lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(wave_id());  // (in a scalar register: what follows from it is computed once per wave)
-    const int bkt = (int)blockIdx.x;
-    const int cnt = (int)totals[bkt];
+    const bool second = (int)blockIdx.x >= buckets_first;
+    const KeySort<K>& S = second ? second_sort : first_sort;
+    const int bkt = (int)blockIdx.x - (second ? buckets_first : 0);
+    const int cnt = (int)S.hist[bkt];
     if (cnt == 0) return;
-    const u32 start = starts[bkt];
-    kin += start;
-    kout += start;
+    const u32 start = S.starts[bkt];
+    K* __restrict__ kin = S.k1 + start;
+    K* __restrict__ kout = S.k0 + start;
+    const int low_bits = S.key_bits - S.digit_bits;
+    const K sentinel = S.sentinel;
+    int* __restrict__ tilesum = S.tilesum;
+    const int tile_shift = S.tile_shift;
+    const bool counting = COUNT_UNIQUE && tilesum != nullptr;
 
     // By every lane of a wave together: the wave's lanes hold the output positions start + idx0 + lane
     // (idx0 the same in all lanes), `first` says whether a lane's key is the first of its run; the
@@ -821,7 +842,7 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(K* __restrict__ ki
     const u32 tile0 = COUNT_UNIQUE ? start >> tile_shift : 0u;  // first tile this bucket's range touches
     auto count_firsts = [&](int idx0, bool first, int* tally) {
         const u64 bal = __ballot(first);
-        if (bal == 0) return;
+        if (bal == 0 || !counting) return;
         const u32 p0 = start + (u32)idx0;
         const u32 tile_a = p0 >> tile_shift, tile_b = (p0 + 63u) >> tile_shift;
         const u32 in_a = ((tile_a + 1u) << tile_shift) - p0;  // positions of the wave that lie in its first tile
@@ -1076,7 +1097,7 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(K* __restrict__ ki
             if constexpr (COUNT_UNIQUE) count_firsts(i * THREADS + w * 64, first, tcnt);
         }
     }
-    if constexpr (COUNT_UNIQUE) {
+    if (counting) {
         // A tile that lies wholly inside this bucket's range gets its count from this workgroup alone (a
         // plain store); the range's first and last tile may be shared with the neighbouring buckets.
         __syncthreads();
@@ -1090,39 +1111,6 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(K* __restrict__ ki
         }
     }
 }
-
-// Launch of that kernel, one workgroup per bucket, with the narrowest in-LDS key type that holds low_bits
-// bits.  tilesum == nullptr: no counting.
-template <typename K, int THREADS, int ITEMS>
-inline void launch_bucket_keys_kernel(int nbuckets, hipStream_t s, K* kin, K* kout, const u32* totals, int low_bits,
-                                      const u32* starts, K sentinel = (K)0, int* tilesum = nullptr, int tile_shift = 0) {
-    if constexpr (sizeof(K) == 8) {
-        if (low_bits <= 32) {
-            if (tilesum)
-                bucket_keys_kernel<K, u32, THREADS, ITEMS, true><<<nbuckets, THREADS, 0, s>>>(kin, kout, totals, starts, low_bits, sentinel, tilesum, tile_shift);
-            else
-                bucket_keys_kernel<K, u32, THREADS, ITEMS, false><<<nbuckets, THREADS, 0, s>>>(kin, kout, totals, starts, low_bits, sentinel, tilesum, tile_shift);
-            return;
-        }
-    }
-    if (tilesum)
-        bucket_keys_kernel<K, K, THREADS, ITEMS, true><<<nbuckets, THREADS, 0, s>>>(kin, kout, totals, starts, low_bits, sentinel, tilesum, tile_shift);
-    else
-        bucket_keys_kernel<K, K, THREADS, ITEMS, false><<<nbuckets, THREADS, 0, s>>>(kin, kout, totals, starts, low_bits, sentinel, tilesum, tile_shift);
-}
-
-// What a keys-only bucket sort may do for the compaction that follows it (see bucket_keys_kernel):
-// the count pass of "keep the first of every run of equal keys, `sentinel` excepted" with tiles of
-// 2^tile_shift positions; the partition kernel zeroes tilesum[0, tiles).  tilesum == nullptr: nothing.
-template <typename K>
-struct UniqueCount {
-    int* tilesum = nullptr;
-    int tile_shift = 0;
-    int tiles = 0;
-    K sentinel = (K)0;
-    int* total = nullptr;  // receives the number of keys (those of the source that it keeps)
-    int sources = 0;       // not 0: items of the source, of which it keeps at most as many as the sort is sized for
-};
 
 // Histogram of the top RBITS-bit digit (bits [shift, shift + RBITS)) over the whole input, added
 // to `hist` (which starts at zero); tiles of BLOCK * ITEMS keys.
@@ -1150,7 +1138,33 @@ __global__ __launch_bounds__(BLOCK) void msd_histogram_kernel(const K* __restric
     }
 }
 
-// Partition of keys WITHOUT values by their top digit (bits [shift, shift + RBITS)) in one pass.
+// A key source gives key i of the input: an array, or a functor that makes the key on the fly (so
+// that keys which are a cheap function of other data need not be written out and read back).  A key that the source
+// does not keep is left out (and is not in the histogram): the output is as many keys shorter.
+// Two sorts may share their launches (`second`: of the second one), where their inputs are there at the same time.
+template <typename K>
+struct ArrayKeys {
+    const K* p;
+    __device__ __forceinline__ K operator()(long long i) const { return p[i]; }
+    __device__ __forceinline__ bool keep(K) const { return true; }
+};
+template <class A>
+struct OneSource {
+    A a;
+    __device__ __forceinline__ auto get(bool, long long i) const { return a(i); }
+    template <typename K>
+    __device__ __forceinline__ bool keep(bool, K k) const { return a.keep(k); }
+};
+template <class A, class B>
+struct TwoSources {
+    A a;
+    B b;
+    __device__ __forceinline__ auto get(bool second, long long i) const { return second ? b(i) : a(i); }
+    template <typename K>
+    __device__ __forceinline__ bool keep(bool second, K k) const { return second ? b.keep(k) : a.keep(k); }
+};
+
+// Partition of keys WITHOUT values by their top 8-bit digit in one pass.
 // hist[d] = number of keys with digit d over the whole input (so digit d owns the output range
 // that starts at the sum of the counts before it; the first tile also writes these first
 // positions to `starts`); cursor[d] = how much of that range is taken, zero at the start.  Every tile counts its keys per digit in LDS, takes its share of each
@@ -1159,96 +1173,65 @@ __global__ __launch_bounds__(BLOCK) void msd_histogram_kernel(const K* __restric
 // for sorts that then order each range on the whole key; with equal keys indistinguishable the
 // final result does not depend on it.  The lanes of a wave whose keys share a digit (keys led by
 // mesh indices bring few distinct digits into a wave) rank themselves with one LDS atomic.
-// A key source gives key i of the input: an array, or a functor that makes the key on the fly (so
-// that keys which are a cheap function of other data need not be written out and read back).  A key that the source
-// does not keep is left out (and is not in the histogram): the output is as many keys shorter.
-template <typename K>
-struct ArrayKeys {
-    const K* p;
-    __device__ __forceinline__ K operator()(long long i) const { return p[i]; }
-    __device__ __forceinline__ bool keep(K) const { return true; }
-};
-
-template <typename K, int RBITS, int ITEMS, class Src>
-__global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(Src kin, K* __restrict__ kout,
-                                                            const int* n_ptr, int n_host, int shift,
-                                                            const u32* __restrict__ hist, u32* __restrict__ cursor,
-                                                            u32* __restrict__ starts, int* __restrict__ zero = nullptr,
-                                                            int n_zero = 0, int* __restrict__ total = nullptr) {
-    constexpr int R = 1 << RBITS;
-    constexpr int PER = R / BLOCK;  // digits per thread in the scan of the ranges' first positions
-    // (an array that the kernel after this one adds to: zeroed here, by all workgroups together)
-    for (int i = blockIdx.x * BLOCK + threadIdx.x; i < n_zero; i += gridDim.x * BLOCK) zero[i] = 0;
-    static_assert(R % BLOCK == 0, "whole digits per thread");
+template <typename K, int ITEMS, class Src>
+__global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src kin) {
+    constexpr int R = 1 << BUCKET_MSD_BITS;
+    static_assert(R == BLOCK, "one digit per thread");
     constexpr int TILE = BLOCK * ITEMS;
     __shared__ u32 h[R];  // per digit: this tile's count, then where the tile's keys of that digit go
-    __shared__ u32 first[R + R / 32];  // (one unused word after every 32: a thread's PER consecutive digits, written by the scan
-                                       // below, then fall into different banks from its neighbours')
     __shared__ u32 smem[WAVES];
-    const int n = load_count(n_ptr, n_host);
-    const long long base = (long long)blockIdx.x * TILE;
-    if (base >= n) return;
+    const bool second = (int)blockIdx.x >= tiles_first;
+    const KeySort<K>& S = second ? second_sort : first_sort;
+    const int tile = (int)blockIdx.x - (second ? tiles_first : 0), tiles = second ? (int)gridDim.x - tiles_first : tiles_first;
+    const int shift = S.key_bits - S.digit_bits;
     const int t = threadIdx.x, w = wave_id(), lane = lane_id();
+    // (an array that the kernel after this one adds to: zeroed here, by all workgroups together)
+    for (int i = tile * BLOCK + t; S.tilesum && i < S.tiles; i += tiles * BLOCK) S.tilesum[i] = 0;
+    const int n = load_count(S.n_ptr, S.n);
+    const long long base = (long long)tile * TILE;
+    if (base >= n) return;
     const u64 lt = lanemask_lt();
-    for (int i = t; i < R; i += BLOCK) h[i] = 0;
+    h[t] = 0;
     K key[ITEMS];
     u32 rk[ITEMS];
+    bool has[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const long long idx = base + (long long)w * (64 * ITEMS) + i * 64 + lane;
-        key[i] = idx < n ? kin(idx) : (K)0;
+        key[i] = idx < n ? kin.get(second, idx) : (K)0;
+        has[i] = idx < n && kin.keep(second, key[i]);
     }
-    {   // first position of every digit's range
-        u32 c[PER], sum = 0, tot;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            c[j] = hist[t * PER + j];
-            sum += c[j];
-        }
-        u32 run = block_exclusive_scan(sum, smem, tot);
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            first[(t * PER + j) + ((t * PER + j) >> 5)] = run;
-            if (blockIdx.x == 0) starts[t * PER + j] = run;  // for the kernel that sorts the ranges
-            run += c[j];
-        }
-        if (total && blockIdx.x == 0 && t == 0) *total = (int)tot;
+    u32 tot;
+    const u32 first = block_exclusive_scan(S.hist[t], smem, tot);  // first position of digit t's range
+    if (tile == 0) {
+        S.starts[t] = first;  // for the kernel that sorts the ranges
+        if (S.total && t == 0) *S.total = (int)tot;
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        const long long idx = base + (long long)w * (64 * ITEMS) + i * 64 + lane;
-        const bool ok = idx < n && kin.keep(key[i]);
         const u32 d = digit_of<K>(key[i], shift, R - 1);
         // the lanes that share a digit rank themselves with one returning atomic, by the first of them
-        const u64 same = wave_same_digit_lanes(ok, d);
+        const u64 same = wave_same_digit_lanes(has[i], d);
         u32 b = 0;
-        if (ok && (same & lt) == 0) b = atomicAdd(&h[d], (u32)__popcll(same));
-        b = (u32)__shfl((int)b, ok ? __ffsll((long long)same) - 1 : lane, 64);
+        if (has[i] && (same & lt) == 0) b = atomicAdd(&h[d], (u32)__popcll(same));
+        b = (u32)__shfl((int)b, has[i] ? __ffsll((long long)same) - 1 : lane, 64);
         rk[i] = b + (u32)__popcll(same & lt);
     }
     __syncthreads();
-    for (int d = t; d < R; d += BLOCK) {
-        const u32 c = h[d];
-        if (c) h[d] = first[d + (d >> 5)] + atomicAdd(&cursor[d], c);
-    }
+    const u32 c = h[t];
+    if (c) h[t] = first + atomicAdd(&S.cursor[t], c);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        const long long idx = base + (long long)w * (64 * ITEMS) + i * 64 + lane;
-        if (idx < n && kin.keep(key[i])) {
+        if (has[i]) {
             const u32 pos = h[digit_of<K>(key[i], shift, R - 1)] + rk[i];
-            if (pos < (u32)n) kout[pos] = key[i];  // (always, when hist and cursor are as described)
+            if (pos < (u32)n) S.k1[pos] = key[i];  // (always, when hist and cursor are as described)
         }
     }
 }
 
-// Keys without values are partitioned by msd_scatter_kernel, which works from a histogram of the
-// top digit in msd_hist[0, R) and cursors in msd_hist[MSD_HIST_WORDS, MSD_HIST_WORDS + R), both
-// zeroed beforehand; the ranges' first positions go to msd_hist[2 * MSD_HIST_WORDS, ...) (msd_hist
-// holds 3 * MSD_HIST_WORDS words).  `counted`: the producer of the
-// keys has already added the keys' digits to that (zeroed) histogram and left the cursors zero,
-// so the histogram pass over the keys is skipped.
+// Words of a sort's count array, of its cursors and of its first positions, for digits of up to 12 bits.
 constexpr int MSD_HIST_WORDS = 4096;
 inline int bucket_sort_msd_bits(int key_bits) { return key_bits < BUCKET_MSD_BITS ? key_bits : BUCKET_MSD_BITS; }
 inline int bucket_sort_low_bits(int key_bits) { return key_bits - bucket_sort_msd_bits(key_bits); }
@@ -1258,48 +1241,19 @@ __global__ __launch_bounds__(BLOCK) void fill_u32_kernel(u32* __restrict__ p, in
     if (i < n) p[i] = v;
 }
 
-// `src`: where the keys come from when not from k0 (keys without values, `counted`); k0 then only
-// receives the result.
-template <typename K, bool HAS_VAL, class Src = ArrayKeys<K>>
+template <typename K, bool HAS_VAL>
 inline int bucket_sort(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_ptr, int n_max, int key_bits,
-                       const SortScratch& sc, LaunchTimer* lt = nullptr, int tag = 0, bool counted = false,
-                       u32* msd_hist = nullptr, const Src* src = nullptr, const UniqueCount<K>* uq = nullptr) {
+                       const SortScratch& sc) {
     if (n_max <= 0 || key_bits <= 0) return 0;
     const int msd = bucket_sort_msd_bits(key_bits);
     const int low = key_bits - msd;
     const int tiles = sort_tiles(n_max, SORT_ITEMS_SMALL);
-    if constexpr (!HAS_VAL) {
-        if (msd == BUCKET_MSD_BITS && msd_hist) {
-            // keys only: one unordered partition pass (msd_scatter_kernel), then each bucket is ordered on the whole key
-            u32* cursor = msd_hist + MSD_HIST_WORDS;
-            if (!counted) {
-                fill_u32_kernel<<<2 * MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(msd_hist, 2 * MSD_HIST_WORDS, 0u);
-                msd_histogram_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL><<<tiles, BLOCK, 0, s>>>(k0, n_ptr, n_max, msd_hist, low);
-            }
-            u32* starts = msd_hist + 2 * MSD_HIST_WORDS;
-            const UniqueCount<K> none{};
-            const UniqueCount<K>& u = uq ? *uq : none;
-            const int n_src = u.sources ? u.sources : n_max;
-            if (src && counted)
-                msd_scatter_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL, Src><<<sort_tiles(n_src, SORT_ITEMS_SMALL), BLOCK, 0, s>>>(*src, k1, n_ptr, n_src, low, msd_hist, cursor, starts, u.tilesum, u.tiles, u.total);
-            else
-                msd_scatter_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, msd_hist, cursor, starts, u.tilesum, u.tiles, u.total);
-            const bool timed = lt && lt->begin(s, tag);
-            launch_bucket_keys_kernel<K, BUCKET_KEYS_THREADS_256, BUCKET_KEYS_ITEMS_256>(1 << msd, s, k1, k0, msd_hist, low, starts, u.sentinel, u.tilesum, u.tile_shift);
-            if (timed) lt->end(s);
-            if (hipGetLastError() != hipSuccess) return -1;
-            return 0;
-        }
-    }
-    (void)counted;
     radix_upsweep_kernel<K, SORT_ITEMS_SMALL><<<tiles, BLOCK, 0, s>>>(k0, n_ptr, n_max, sc.T, sc.table, low, msd);
     radix_scan_kernel<<<1 << msd, BLOCK, 0, s>>>(sc.table, sc.totals, n_ptr, n_max, sc.T, BLOCK * SORT_ITEMS_SMALL);
     radix_downsweep_kernel<K, HAS_VAL, SORT_ITEMS_SMALL>
         <<<tiles, BLOCK, 0, s>>>(k0, k1, v0, v1, n_ptr, n_max, sc.T, sc.table, sc.totals, low, msd);
-    const bool timed = lt && lt->begin(s, tag);
     bucket_sort_kernel<K, HAS_VAL, BUCKET_THREADS_256, 8>
         <<<1 << msd, BUCKET_THREADS_256, 0, s>>>(k1, k0, v1, v0, sc.totals, 1 << msd, low);
-    if (timed) lt->end(s);
     if (hipGetLastError() != hipSuccess) return -1;
     return 0;
 }
@@ -1355,37 +1309,13 @@ __global__ __launch_bounds__(BLOCK) void top_digit_histogram_kernel(const K* __r
     }
 }
 
-// Result is in (k1, v1): returns 1 (keys with values), or in k0: returns 0 (keys only); <0 on a
-// launch error.  hist12 holds 3 * MSD_HIST_WORDS words (counts, cursors, first positions).
-template <typename K, bool HAS_VAL, class Src = ArrayKeys<K>>
+// Keys with values.  Result is in (k1, v1): returns 1; <0 on a launch error.  hist12 holds MSD_HIST_WORDS words.
+template <typename K>
 inline int bucket_sort_large(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, const int* n_ptr, int n_max, int key_bits,
-                             const SortScratch& sc, u32* hist12, LaunchTimer* lt = nullptr, int tag = 0,
-                             bool counted = false, const Src* src = nullptr, const UniqueCount<K>* uq = nullptr) {
+                             const SortScratch& sc, u32* hist12) {
     constexpr int R = 1 << BUCKET_LARGE_MSD_BITS;
     const int low = key_bits - BUCKET_LARGE_MSD_BITS;
     const int tiles = sort_tiles(n_max, SORT_ITEMS_BIG);
-    if constexpr (!HAS_VAL) {
-        // keys only: one unordered partition pass (msd_scatter_kernel), then each bucket is ordered on the whole key
-        u32* cursor = hist12 + MSD_HIST_WORDS;
-        if (!counted) {
-            fill_u32_kernel<<<2 * MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(hist12, 2 * MSD_HIST_WORDS, 0u);
-            msd_histogram_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG><<<tiles, BLOCK, 0, s>>>(k0, n_ptr, n_max, hist12, low);
-        }
-        u32* starts = hist12 + 2 * MSD_HIST_WORDS;
-        const UniqueCount<K> none{};
-        const UniqueCount<K>& u = uq ? *uq : none;
-        const int n_src = u.sources ? u.sources : n_max;
-        if (src && counted)
-            msd_scatter_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG, Src><<<sort_tiles(n_src, SORT_ITEMS_BIG), BLOCK, 0, s>>>(*src, k1, n_ptr, n_src, low, hist12, cursor, starts, u.tilesum, u.tiles, u.total);
-        else
-            msd_scatter_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG, ArrayKeys<K>><<<tiles, BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, hist12, cursor, starts, u.tilesum, u.tiles, u.total);
-        const bool timed = lt && lt->begin(s, tag);
-        launch_bucket_keys_kernel<K, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096>(R, s, k1, k0, hist12, low, starts, u.sentinel, u.tilesum, u.tile_shift);
-        if (timed) lt->end(s);
-        if (hipGetLastError() != hipSuccess) return -1;
-        return 0;
-    }
-    (void)counted;
     fill_u32_kernel<<<R / BLOCK, BLOCK, 0, s>>>(hist12, R, 0u);
     top_digit_histogram_kernel<K><<<tiles, BLOCK, 0, s>>>(k0, n_ptr, n_max, hist12, low, sc.T, sc.table);
     K* kin = k0;
@@ -1397,27 +1327,25 @@ inline int bucket_sort_large(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, cons
         if (half == 1)  // (the histogram kernel has left the first pass's counts)
             radix_upsweep_kernel<K, SORT_ITEMS_BIG><<<tiles, BLOCK, 0, s>>>(kin, n_ptr, n_max, sc.T, sc.table, shift, 6);
         radix_scan_kernel<<<64, BLOCK, 0, s>>>(sc.table, sc.totals, n_ptr, n_max, sc.T, BLOCK * SORT_ITEMS_BIG);
-        radix_downsweep_kernel<K, HAS_VAL, SORT_ITEMS_BIG>
+        radix_downsweep_kernel<K, true, SORT_ITEMS_BIG>
             <<<tiles, BLOCK, 0, s>>>(kin, kout, vin, vout, n_ptr, n_max, sc.T, sc.table, sc.totals, shift, 6);
         K* tk = kin; kin = kout; kout = tk;
         u32* tv = vin; vin = vout; vout = tv;
     }
     // after two passes the partitioned keys are back in (k0, v0)
-    const bool timed = lt && lt->begin(s, tag);
-    bucket_sort_kernel<K, HAS_VAL, BUCKET_THREADS_4096, (HAS_VAL ? 16 : 8)>
+    bucket_sort_kernel<K, true, BUCKET_THREADS_4096, 16>
         <<<R, BUCKET_THREADS_4096, 0, s>>>(k0, k1, v0, v1, hist12, R, low);
-    if (timed) lt->end(s);
     if (hipGetLastError() != hipSuccess) return -1;
     return 1;
 }
 
 // ---------------------------------------------------------------------------
-// Keys without values beyond BUCKET_SORT_LARGE_MAX_KEYS: the same two sweeps (partition on a top digit, then one workgroup
-// per bucket), with a digit as wide as the input needs for buckets of about a thousand keys.  Arrays with one word
-// per digit then no longer fit LDS; a tile of mesh keys holds few distinct digits, though, so it counts them in a small hash
-// table.  Bound by memory: 8 bytes read and 8 written per key and sweep (plus 4 where keys are made on the fly),
-// where plain radix passes read every key twice and wrote it once for every 8 bits (61 M keys of 48 bits: 6 passes,
-// 2.9 ms; this way 0.5 ms).
+// Keys without values beyond BUCKET_SORT_MAX_KEYS: the same two sweeps (partition on a top digit, then one workgroup
+// per bucket), with a digit of 12 bits, beyond BUCKET_SORT_LARGE_MAX_KEYS as wide as the input needs for buckets of
+// about a thousand keys.  Arrays with one word per digit then do not fit LDS, or fill it; a tile of mesh keys holds few
+// distinct digits, though, so it counts them in a small hash table.  Bound by memory: 8 bytes read and 8 written per key and sweep
+// (less 4 read where keys are made on the fly), where plain radix passes read every key twice and wrote it once for
+// every 8 bits (61 M keys of 48 bits: 6 passes, 2.9 ms; this way 0.5 ms).
 // ---------------------------------------------------------------------------
 constexpr int XL_BITS_MIN = 13, XL_BITS_MAX = 22;
 constexpr long long XL_BUCKET_KEYS = 1024;  // keys per bucket aimed at (vertex ids need not fill their bit range: up to twice that)
@@ -1440,14 +1368,24 @@ struct XlScratch {
     u32* cursor = nullptr;  // next free position in it
 };
 
+// Bits of the digit that up to n keys of key_bits bits are partitioned on, and how many bits a key must have for it.
+inline int key_digit_bits(long long n, int key_bits) {
+    if (n <= BUCKET_SORT_MAX_KEYS) return BUCKET_MSD_BITS;
+    return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS : xl_digit_bits(n, key_bits);
+}
+inline int key_bits_wanted(long long n) {
+    if (n <= BUCKET_SORT_MAX_KEYS) return BUCKET_MSD_BITS + 2;
+    return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS + 2 : XL_BITS_MAX + 2;
+}
+
 // hist[digit] += 1 for the lanes with `ok`, those of a wave that share a digit with one atomic.  By all lanes of a wave.
 __device__ __forceinline__ void xl_count(u32* __restrict__ hist, bool ok, u32 d) {
     const u64 same = wave_same_digit_lanes(ok, d);
     if (ok && (same & lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
 }
 
-template <typename K, class Src>
-__global__ __launch_bounds__(BLOCK) void xl_count_kernel(Src kin, const int* n_ptr, int n_host, int shift, u32 mask,
+template <typename K>
+__global__ __launch_bounds__(BLOCK) void xl_count_kernel(const K* __restrict__ kin, const int* n_ptr, int n_host, int shift, u32 mask,
                                                          u32* __restrict__ hist) {
     constexpr int ITEMS = 4;
     const int n = load_count(n_ptr, n_host);
@@ -1456,61 +1394,59 @@ __global__ __launch_bounds__(BLOCK) void xl_count_kernel(Src kin, const int* n_p
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const long long idx = base + (long long)i * BLOCK + threadIdx.x;
-        const bool ok = idx < n;
-        const K k = ok ? kin(idx) : (K)0;
-        xl_count(hist, ok && kin.keep(k), digit_of<K>(k, shift, mask));
+        xl_count(hist, idx < n, digit_of<K>(idx < n ? kin[idx] : (K)0, shift, mask));
     }
 }
 
-// starts = cursor = exclusive prefix sums of hist[0, R), R a multiple of XL_SCAN_DIGITS: every workgroup adds up what lies
-// in front of its digits by itself.  zero[0, n_zero) is cleared on the way (for the kernel after the next).
-constexpr int XL_SCAN_ITEMS = 16, XL_SCAN_DIGITS = BLOCK * XL_SCAN_ITEMS;
-__global__ __launch_bounds__(BLOCK) void xl_starts_kernel(const u32* __restrict__ hist, u32* __restrict__ starts,
-                                                          u32* __restrict__ cursor, int* __restrict__ zero, int n_zero,
-                                                          int* __restrict__ total) {
-    __shared__ u32 smem[WAVES];
-    const int t = threadIdx.x, d0 = blockIdx.x * XL_SCAN_DIGITS;
-    for (int i = blockIdx.x * BLOCK + t; i < n_zero; i += gridDim.x * BLOCK) zero[i] = 0;
-    const uint4* h4 = reinterpret_cast<const uint4*>(hist);
-    u32 before = 0;
+// starts = cursor = exclusive prefix sums of hist[0, 2^digit_bits), a multiple of KEY_SCAN_DIGITS: every workgroup adds up what lies
+// in front of its digits by itself.
+constexpr int KEY_SCAN_THREADS = 1024, KEY_SCAN_ITEMS = 4, KEY_SCAN_DIGITS = KEY_SCAN_THREADS * KEY_SCAN_ITEMS;
+template <typename K>
+__global__ __launch_bounds__(KEY_SCAN_THREADS) void key_starts_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int blocks_first) {
+    __shared__ u32 smem[KEY_SCAN_THREADS / 64];
+    const bool second = (int)blockIdx.x >= blocks_first;
+    const KeySort<K>& S = second ? second_sort : first_sort;
+    const int block = (int)blockIdx.x - (second ? blocks_first : 0), blocks = second ? (int)gridDim.x - blocks_first : blocks_first;
+    const int t = threadIdx.x, d0 = block * KEY_SCAN_DIGITS;
+    for (int i = block * KEY_SCAN_THREADS + t; S.tilesum && i < S.tiles; i += blocks * KEY_SCAN_THREADS) S.tilesum[i] = 0;
+    const uint4* h4 = reinterpret_cast<const uint4*>(S.hist);
+    const uint4 c = h4[d0 / 4 + t];
+    u32 before = 0, in_front, tot;
 #pragma unroll 8
-    for (int i = t; i < d0 / 4; i += BLOCK) {
+    for (int i = t; i < d0 / 4; i += KEY_SCAN_THREADS) {
         const uint4 q = h4[i];
         before += (q.x + q.y) + (q.z + q.w);
     }
-    before = block_sum(before, smem);
-    u32 c[XL_SCAN_ITEMS], sum = 0, tot;
-#pragma unroll
-    for (int j = 0; j < XL_SCAN_ITEMS; ++j) {
-        c[j] = hist[d0 + t * XL_SCAN_ITEMS + j];
-        sum += c[j];
-    }
-    u32 run = before + block_exclusive_scan(sum, smem, tot);
-#pragma unroll
-    for (int j = 0; j < XL_SCAN_ITEMS; ++j) {
-        const int d = d0 + t * XL_SCAN_ITEMS + j;
-        starts[d] = run;
-        cursor[d] = run;
-        run += c[j];
-    }
-    if (total && blockIdx.x == gridDim.x - 1 && t == BLOCK - 1) *total = (int)run;
+    wide_block_exclusive_scan<KEY_SCAN_THREADS / 64>(before, smem, in_front);
+    const u32 sum = (c.x + c.y) + (c.z + c.w);
+    const u32 at = in_front + wide_block_exclusive_scan<KEY_SCAN_THREADS / 64>(sum, smem, tot);
+    const uint4 o = make_uint4(at, at + c.x, at + c.x + c.y, at + c.x + c.y + c.z);
+    reinterpret_cast<uint4*>(S.starts)[d0 / 4 + t] = o;
+    reinterpret_cast<uint4*>(S.cursor)[d0 / 4 + t] = o;
+    if (S.total && block == blocks - 1 && t == KEY_SCAN_THREADS - 1) *S.total = (int)(at + sum);
 }
 
 // The partition: a tile's distinct digits are entered into a hash table in LDS (the lanes of a wave that share a digit
 // by the first of them), which counts their keys and so ranks them; each digit then takes its share of
 // its range with one returning atomic.  A digit that finds no place within XL_PROBES steps (a tile without locality)
 // takes its places right away.  The order of the keys inside a range does not matter (see msd_scatter_kernel).
-constexpr int XL_ITEMS = 16, XL_SLOTS = 1024, XL_PROBES = 8;
+// Bound by the chain of a workgroup (keys, ranks, shares, stores), so 8 keys per lane: twice as many workgroups fit a
+// compute unit as with 16, at two thirds of the time (61 M keys 600 -> 350 us, 7 M 50 -> 35); 4 bring no more.
+constexpr int XL_ITEMS = 8, XL_SLOTS = 512, XL_PROBES = 8;
 template <typename K, class Src>
-__global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(Src kin, K* __restrict__ kout, const int* n_ptr, int n_host, int shift,
-                                                           u32 mask, u32* __restrict__ cursor) {
+__global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src kin) {
     constexpr int TILE = BLOCK * XL_ITEMS;
     constexpr u32 NONE = 0xFFFFFFFFu;
     __shared__ u32 digit[XL_SLOTS];
     __shared__ u32 count[XL_SLOTS];  // keys of the tile with that digit, then where they go
-    const int n = load_count(n_ptr, n_host);
-    const long long base = (long long)blockIdx.x * TILE;
+    const bool second = (int)blockIdx.x >= tiles_first;
+    const KeySort<K>& S = second ? second_sort : first_sort;
+    const int n = load_count(S.n_ptr, S.n);
+    const long long base = (long long)((int)blockIdx.x - (second ? tiles_first : 0)) * TILE;
     if (base >= n) return;
+    const int shift = S.key_bits - S.digit_bits;
+    const u32 mask = (1u << S.digit_bits) - 1u;
+    u32* __restrict__ cursor = S.cursor;
     const int t = threadIdx.x, w = wave_id(), lane = lane_id();
     const u64 lt = lanemask_lt();
     for (int i = t; i < XL_SLOTS; i += BLOCK) {
@@ -1519,20 +1455,21 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(Src kin, K* __restric
     }
     K key[XL_ITEMS];
     u32 place[XL_ITEMS], rank[XL_ITEMS];
+    bool has[XL_ITEMS];
 #pragma unroll
     for (int i = 0; i < XL_ITEMS; ++i) {
         const long long idx = base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane;
-        key[i] = idx < n ? kin(idx) : (K)0;
+        key[i] = idx < n ? kin.get(second, idx) : (K)0;
+        has[i] = idx < n && kin.keep(second, key[i]);
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < XL_ITEMS; ++i) {
-        const bool ok = base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n && kin.keep(key[i]);
         const u32 d = digit_of<K>(key[i], shift, mask);
-        const u64 same = wave_same_digit_lanes(ok, d);
+        const u64 same = wave_same_digit_lanes(has[i], d);
         u32 slot = NONE, b = 0;
-        if (ok && (same & lt) == 0) {
-            u32 h = (d * 0x9E3779B1u) >> 22;  // 10 bits
+        if (has[i] && (same & lt) == 0) {
+            u32 h = (d * 0x9E3779B1u) >> 23;  // 9 bits
             for (int p = 0; p < XL_PROBES; ++p) {
                 const u32 old = atomicCAS(&digit[h], NONE, d);
                 if (old == NONE || old == d) {
@@ -1543,48 +1480,86 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(Src kin, K* __restric
             }
             b = slot != NONE ? atomicAdd(&count[slot], (u32)__popcll(same)) : atomicAdd(&cursor[d], (u32)__popcll(same));
         }
-        const int lead = ok ? __ffsll((long long)same) - 1 : lane;
+        const int lead = has[i] ? __ffsll((long long)same) - 1 : lane;
         place[i] = (u32)__shfl((int)slot, lead, 64);
         rank[i] = (u32)__shfl((int)b, lead, 64) + (u32)__popcll(same & lt);
     }
     __syncthreads();
-    for (int i = t; i < XL_SLOTS; i += BLOCK)
-        if (digit[i] != NONE) count[i] = atomicAdd(&cursor[digit[i]], count[i]);
+    u32 share[XL_SLOTS / BLOCK];  // (all of a thread's atomics in flight together)
+#pragma unroll
+    for (int j = 0; j < XL_SLOTS / BLOCK; ++j) {
+        const u32 d = digit[j * BLOCK + t];
+        share[j] = d != NONE ? atomicAdd(&cursor[d], count[j * BLOCK + t]) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < XL_SLOTS / BLOCK; ++j) count[j * BLOCK + t] = share[j];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < XL_ITEMS; ++i) {
-        if (base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane < n && kin.keep(key[i])) {
+        if (has[i]) {
             const u32 pos = (place[i] != NONE ? count[place[i]] : 0u) + rank[i];
-            if (pos < (u32)n) kout[pos] = key[i];  // (always, when hist and cursor are as described)
+            if (pos < (u32)n) S.k1[pos] = key[i];  // (always, when hist and cursor are as described)
         }
     }
 }
 
-// Result in k0 (returns 0; <0 on a launch error).  `counted`: hist holds the keys' digits already (xl_count), and the
-// keys come from *src; else they are in k0 and are counted here.
+// Sorts the keys of `src` (whose digits are in a.hist); with b, a second sort of the same kind in the same launches.
+// false on a launch error.  `lt`: brackets the launch of the per-bucket kernel.
 template <typename K, class Src>
-inline int bucket_sort_xl(hipStream_t s, K* k0, K* k1, const int* n_ptr, int n_max, int key_bits, const XlScratch& xl,
-                          LaunchTimer* lt, int tag, bool counted, const Src* src, const UniqueCount<K>* uq) {
-    const int bits = xl_digit_bits(n_max, key_bits), low = key_bits - bits;
-    const u32 mask = (1u << bits) - 1u;
-    static_assert((1 << XL_BITS_MIN) % XL_SCAN_DIGITS == 0, "whole workgroups of the scan");
-    if (!counted) {
-        fill_u32_kernel<<<(1 << bits) / BLOCK, BLOCK, 0, s>>>(xl.hist, 1 << bits, 0u);
-        xl_count_kernel<K, ArrayKeys<K>><<<sort_tiles(n_max, 4), BLOCK, 0, s>>>(ArrayKeys<K>{k0}, n_ptr, n_max, low, mask, xl.hist);
+inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_null, const Src& src, LaunchTimer* lt = nullptr,
+                     int tag = 0) {
+    const KeySort<K> none{};
+    const KeySort<K>& b = b_or_null ? *b_or_null : none;
+    const int buckets_a = 1 << a.digit_bits, buckets_b = b_or_null ? 1 << b.digit_bits : 0;
+    const bool narrow = a.digit_bits == BUCKET_MSD_BITS;
+    if (narrow) {
+        const int tiles_a = sort_tiles(a.n, SORT_ITEMS_SMALL), tiles_b = b_or_null ? sort_tiles(b.n, SORT_ITEMS_SMALL) : 0;
+        msd_scatter_kernel<K, SORT_ITEMS_SMALL, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
+    } else {
+        const int blocks_a = buckets_a / KEY_SCAN_DIGITS, blocks_b = buckets_b / KEY_SCAN_DIGITS;
+        key_starts_kernel<K><<<blocks_a + blocks_b, KEY_SCAN_THREADS, 0, s>>>(a, b, blocks_a);
+        const int tiles_a = sort_tiles(a.n, XL_ITEMS), tiles_b = b_or_null ? sort_tiles(b.n, XL_ITEMS) : 0;
+        xl_scatter_kernel<K, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
     }
-    const UniqueCount<K> none{};
-    const UniqueCount<K>& u = uq ? *uq : none;
-    xl_starts_kernel<<<(1 << bits) / XL_SCAN_DIGITS, BLOCK, 0, s>>>(xl.hist, xl.starts, xl.cursor, u.tilesum, u.tiles, u.total);
-    const int n_src = u.sources ? u.sources : n_max;
-    if (src && counted)
-        xl_scatter_kernel<K, Src><<<sort_tiles(n_src, XL_ITEMS), BLOCK, 0, s>>>(*src, k1, n_ptr, n_src, low, mask, xl.cursor);
-    else
-        xl_scatter_kernel<K, ArrayKeys<K>><<<sort_tiles(n_max, XL_ITEMS), BLOCK, 0, s>>>(ArrayKeys<K>{k0}, k1, n_ptr, n_max, low, mask, xl.cursor);
+    // one workgroup per bucket, with the narrowest in-LDS key type that holds the bits below the digit
     const bool timed = lt && lt->begin(s, tag);
-    launch_bucket_keys_kernel<K, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096>(1 << bits, s, k1, k0, xl.hist, low, xl.starts, u.sentinel, u.tilesum, u.tile_shift);
+    const bool half = sizeof(K) == 8 && a.key_bits - a.digit_bits <= 32 && b.key_bits - b.digit_bits <= 32;
+    const bool counting = a.tilesum || b.tilesum;
+    auto launch = [&](auto lk, auto threads, auto items) {
+        using LK = decltype(lk);
+        constexpr int T = decltype(threads)::value, I = decltype(items)::value;
+        if (counting) bucket_keys_kernel<K, LK, T, I, true><<<buckets_a + buckets_b, T, 0, s>>>(a, b, buckets_a);
+        else bucket_keys_kernel<K, LK, T, I, false><<<buckets_a + buckets_b, T, 0, s>>>(a, b, buckets_a);
+    };
+    const std::integral_constant<int, BUCKET_KEYS_THREADS_256> t256{};
+    const std::integral_constant<int, BUCKET_KEYS_ITEMS_256> i256{};
+    const std::integral_constant<int, BUCKET_KEYS_THREADS_4096> t4096{};
+    const std::integral_constant<int, BUCKET_KEYS_ITEMS_4096> i4096{};
+    if (narrow) {
+        if (half) launch(u32{}, t256, i256);
+        else launch(K{}, t256, i256);
+    } else {
+        if (half) launch(u32{}, t4096, i4096);
+        else launch(K{}, t4096, i4096);
+    }
     if (timed) lt->end(s);
-    if (hipGetLastError() != hipSuccess) return -1;
-    return 0;
+    return hipGetLastError() == hipSuccess;
+}
+
+// The same for keys in a.k0 that have not been counted.
+template <typename K>
+inline bool key_sort_array(hipStream_t s, const KeySort<K>& a) {
+    const int low = a.key_bits - a.digit_bits, buckets = 1 << a.digit_bits;
+    fill_u32_kernel<<<(buckets + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(a.hist, buckets, 0u);
+    if (a.digit_bits == BUCKET_MSD_BITS) {
+        fill_u32_kernel<<<(buckets + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(a.cursor, buckets, 0u);
+        msd_histogram_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL><<<sort_tiles(a.n, SORT_ITEMS_SMALL), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, a.hist, low);
+    } else if (a.digit_bits == BUCKET_LARGE_MSD_BITS) {
+        msd_histogram_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG><<<sort_tiles(a.n, SORT_ITEMS_BIG), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, a.hist, low);
+    } else {
+        xl_count_kernel<K><<<sort_tiles(a.n, 4), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, low, (u32)buckets - 1u, a.hist);
+    }
+    return key_sort(s, a, (const KeySort<K>*)nullptr, OneSource<ArrayKeys<K>>{{a.k0}});
 }
 
 // ---------------------------------------------------------------------------
