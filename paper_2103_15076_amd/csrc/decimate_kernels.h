@@ -256,18 +256,43 @@ struct DigitCount {
     int shift;
     u32 mask;
 };
-// One key per lane with `ok` counted, in the workgroup's LDS histogram or (COUNT_XL) in memory: the lanes of a wave that
-// share a digit, as the keys of neighbouring facets mostly do, with a single atomic.  By all lanes of a wave.
+// A workgroup's counts of one sort's digits, in LDS: an array of all digits, kept until the workgroup ends, or (COUNT_XL) a
+// table of those that a tile holds.  The lanes of a wave that share a digit, as the keys of neighbouring facets mostly do,
+// are counted with a single atomic.  clear, count and flush by whole workgroups, with barriers between them.
 template <int COUNT>
-__device__ __forceinline__ void count_digit(u32* lds, const DigitCount& D, bool ok, u64 k) {
-    const u32 d = (u32)(k >> D.shift) & D.mask;
-    if constexpr (COUNT == COUNT_XL) {
-        prim::xl_count(D.hist, ok, d);
-    } else if constexpr (COUNT != COUNT_NONE) {
-        const u64 same = prim::wave_same_digit_lanes(ok, d);
-        if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&lds[d], (u32)__popcll(same));
+struct DigitTally {
+    static constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
+    u32 hist[RADIX];
+    __device__ __forceinline__ void clear() {
+        for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = 0;
     }
-}
+    __device__ __forceinline__ void count(const DigitCount& D, bool ok, u64 k) {
+        const u32 d = (u32)(k >> D.shift) & (u32)(RADIX - 1);
+        const u64 same = prim::wave_same_digit_lanes(ok, d);
+        if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
+    }
+    __device__ __forceinline__ void flush(const DigitCount& D) {
+        for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
+            const u32 c = hist[i];
+            if (c) atomicAdd(&D.hist[i], c);
+        }
+    }
+};
+template <>
+struct DigitTally<COUNT_XL> {
+    prim::DigitTable table;
+    __device__ __forceinline__ void clear() { table.clear(); }
+    __device__ __forceinline__ void count(const DigitCount& D, bool ok, u64 k) {
+        table.add(D.hist, ok, (u32)(k >> D.shift) & D.mask);
+    }
+    __device__ __forceinline__ void flush(const DigitCount& D) { table.flush(D.hist); }
+};
+template <>
+struct DigitTally<COUNT_NONE> {
+    __device__ __forceinline__ void clear() {}
+    __device__ __forceinline__ void count(const DigitCount&, bool, u64) {}
+    __device__ __forceinline__ void flush(const DigitCount&) {}
+};
 
 template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
@@ -279,9 +304,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                                                      float4* __restrict__ planes, int* __restrict__ htab, int n_clear,
                                                      u64* __restrict__ vmin0, u64* __restrict__ vmin1,
                                                      int* __restrict__ mate, RoundTab R) {
-    constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
-    constexpr bool IN_LDS = COUNT == COUNT_SMALL || COUNT == COUNT_LARGE;
-    __shared__ u32 hist[IN_LDS ? RADIX : 1], ehist[IN_LDS ? RADIX : 1];
+    __shared__ DigitTally<COUNT> corners, sides;
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     const bool single = init.hdr != nullptr;  // one mesh, whose ranges are [0, N) and [0, F): the tables are not read here
@@ -302,10 +325,9 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         round_begin_block(R, st);
     }
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
-    if constexpr (IN_LDS) {
-        for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = ehist[i] = 0;
-        __syncthreads();
-    }
+    corners.clear();
+    sides.clear();
+    __syncthreads();
     int err = 0;
     for (int w = g; w < N; w += stride) {
         float x = verts[3 * (size_t)w], y = verts[3 * (size_t)w + 1], z = verts[3 * (size_t)w + 2];
@@ -347,25 +369,31 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                 corner[c] = a;
                 k = ((u64)(u32)a << fbits) | (u64)(u32)f;
             }
-            count_digit<COUNT>(hist, inc, ok, k);
+            corners.count(inc, ok, k);
         }
         if (edges) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const int a = corner[c], b = corner[c == 2 ? 0 : c + 1];
-                count_digit<COUNT>(ehist, edge, ok && a != b, edge_key(a, b, vbits));
+                sides.count(edge, ok && a != b, edge_key(a, b, vbits));
             }
         }
         // the facet's plane, once per facet, for the vertex quadrics that S0 sums from it
         if (planes && ok) planes[f] = facet_plane(verts, corner[0], corner[1], corner[2]);
-    }
-    if constexpr (IN_LDS) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
-            const u32 c = hist[i], e = ehist[i];
-            if (c) atomicAdd(&inc.hist[i], c);
-            if (e) atomicAdd(&edge.hist[i], e);
+        if constexpr (COUNT == COUNT_XL) {
+            __syncthreads();
+            corners.flush(inc);
+            sides.flush(edge);
+            __syncthreads();
+            corners.clear();
+            sides.clear();
+            __syncthreads();
         }
+    }
+    if constexpr (COUNT != COUNT_XL) {
+        __syncthreads();
+        corners.flush(inc);
+        sides.flush(edge);
     }
     if (err) atomicOr(&st->err, err);
 }
@@ -389,14 +417,10 @@ struct RowKeys {
 constexpr int CSR_COUNT_ITEMS = 4;
 template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, DigitCount rows, int* __restrict__ err) {
-    constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
-    constexpr bool IN_LDS = COUNT != COUNT_XL;
     constexpr int ITEMS = COUNT == COUNT_LARGE ? 16 : CSR_COUNT_ITEMS;
-    __shared__ u32 hist[IN_LDS ? RADIX : 1];
-    if constexpr (IN_LDS) {
-        for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = 0;
-        __syncthreads();
-    }
+    __shared__ DigitTally<COUNT> digits;
+    digits.clear();
+    __syncthreads();
     bool bad = false;
 #pragma unroll 4
     for (int j = 0; j < ITEMS; ++j) {
@@ -407,15 +431,10 @@ __global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, Di
             bad |= (u32)src.row_of[i] >= (u32)src.n_rows;
             k = src(i);
         }
-        count_digit<COUNT>(hist, rows, ok, k);
+        digits.count(rows, ok, k);
     }
-    if constexpr (IN_LDS) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
-            const u32 c = hist[i];
-            if (c) atomicAdd(&rows.hist[i], c);
-        }
-    }
+    __syncthreads();
+    digits.flush(rows);
     if (bad) atomicOr(err, ERR_BIT_BAD_INDEX);
 }
 
@@ -597,9 +616,7 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
                                                           const int* __restrict__ vmap, const int* __restrict__ done,
                                                           int* __restrict__ cid, int n_orig) {
     constexpr int FACETS = COUNT == COUNT_SMALL ? 1 : 4;
-    constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
-    constexpr bool IN_LDS = COUNT != COUNT_XL;
-    __shared__ u32 hist[IN_LDS ? RADIX : 1];
+    __shared__ DigitTally<COUNT> sides;
     const int nv = st->nv[cur];
     const int stride = gridDim.x * BLOCK;
     const int t = threadIdx.x, g = blockIdx.x * BLOCK + t;
@@ -609,10 +626,8 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
         mate[w] = -1;
     }
     if (blockIdx.x == 0) round_begin_block(R, st);
-    if constexpr (IN_LDS) {
-        for (int i = t; i < RADIX; i += BLOCK) hist[i] = 0;
-        __syncthreads();
-    }
+    sides.clear();
+    __syncthreads();
     for (long long base = (long long)blockIdx.x * (BLOCK * FACETS); base < F; base += (long long)stride * FACETS) {
         Corners q[FACETS];
         bool ok[FACETS];
@@ -641,17 +656,21 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const int a = c == 0 ? q[j].a : (c == 1 ? q[j].b : q[j].c), b = c == 0 ? q[j].b : (c == 1 ? q[j].c : q[j].a);
-                count_digit<COUNT>(hist, edge, ok[j] && a != b, edge_key(a, b, vbits));
+                sides.count(edge, ok[j] && a != b, edge_key(a, b, vbits));
             }
+        }
+        if constexpr (COUNT == COUNT_XL) {
+            __syncthreads();
+            sides.flush(edge);
+            __syncthreads();
+            sides.clear();
+            __syncthreads();
         }
     }
     for (int o = g; o < n_orig; o += stride) cid[o] = vmap[cid[o]];
-    if constexpr (IN_LDS) {
+    if constexpr (COUNT != COUNT_XL) {
         __syncthreads();
-        for (int i = t; i < RADIX; i += BLOCK) {
-            const u32 c = hist[i];
-            if (c) atomicAdd(&edge.hist[i], c);
-        }
+        sides.flush(edge);
     }
 }
 

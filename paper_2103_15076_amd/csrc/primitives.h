@@ -1378,24 +1378,61 @@ inline int key_bits_wanted(long long n) {
     return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS + 2 : XL_BITS_MAX + 2;
 }
 
-// hist[digit] += 1 for the lanes with `ok`, those of a wave that share a digit with one atomic.  By all lanes of a wave.
-__device__ __forceinline__ void xl_count(u32* __restrict__ hist, bool ok, u32 d) {
-    const u64 same = wave_same_digit_lanes(ok, d);
-    if (ok && (same & lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
-}
+// A workgroup's counts of wide digits: a small hash table in LDS, as a tile of mesh keys holds few distinct digits.  clear,
+// add and flush by the whole workgroup, with barriers between them.  (Straight to memory, with an atomic per wave and digit,
+// counting took 270-400 us of a round of 61 M half-edges.)
+constexpr int XL_SLOTS = 512, XL_PROBES = 8;
+constexpr u32 XL_NONE = 0xFFFFFFFFu;
+struct DigitTable {
+    u32 digit[XL_SLOTS];
+    u32 count[XL_SLOTS];
+    __device__ __forceinline__ void clear() {
+        for (int i = threadIdx.x; i < XL_SLOTS; i += BLOCK) {
+            digit[i] = XL_NONE;
+            count[i] = 0;
+        }
+    }
+    // the digit's slot, or XL_NONE where it finds no place
+    __device__ __forceinline__ u32 slot_of(u32 d) {
+        u32 h = (d * 0x9E3779B1u) >> 23;  // 9 bits
+        for (int p = 0; p < XL_PROBES; ++p) {
+            const u32 old = atomicCAS(&digit[h], XL_NONE, d);
+            if (old == XL_NONE || old == d) return h;
+            h = (h + 1) & (XL_SLOTS - 1);
+        }
+        return XL_NONE;
+    }
+    // one key for every lane with `ok`: the lanes of a wave that share a digit by the first of them
+    __device__ __forceinline__ void add(u32* __restrict__ hist, bool ok, u32 d) {
+        const u64 same = wave_same_digit_lanes(ok, d);
+        if (ok && (same & lanemask_lt()) == 0) {
+            const u32 s = slot_of(d);
+            atomicAdd(s != XL_NONE ? &count[s] : &hist[d], (u32)__popcll(same));
+        }
+    }
+    __device__ __forceinline__ void flush(u32* __restrict__ hist) {
+        for (int i = threadIdx.x; i < XL_SLOTS; i += BLOCK)
+            if (digit[i] != XL_NONE) atomicAdd(&hist[digit[i]], count[i]);
+    }
+};
 
 template <typename K>
 __global__ __launch_bounds__(BLOCK) void xl_count_kernel(const K* __restrict__ kin, const int* n_ptr, int n_host, int shift, u32 mask,
                                                          u32* __restrict__ hist) {
     constexpr int ITEMS = 4;
+    __shared__ DigitTable table;
     const int n = load_count(n_ptr, n_host);
     const long long base = (long long)blockIdx.x * (BLOCK * ITEMS);
     if (base >= n) return;
+    table.clear();
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const long long idx = base + (long long)i * BLOCK + threadIdx.x;
-        xl_count(hist, idx < n, digit_of<K>(idx < n ? kin[idx] : (K)0, shift, mask));
+        table.add(hist, idx < n, digit_of<K>(idx < n ? kin[idx] : (K)0, shift, mask));
     }
+    __syncthreads();
+    table.flush(hist);
 }
 
 // starts = cursor = exclusive prefix sums of hist[0, 2^digit_bits), a multiple of KEY_SCAN_DIGITS: every workgroup adds up what lies
@@ -1432,13 +1469,11 @@ __global__ __launch_bounds__(KEY_SCAN_THREADS) void key_starts_kernel(KeySort<K>
 // takes its places right away.  The order of the keys inside a range does not matter (see msd_scatter_kernel).
 // Bound by the chain of a workgroup (keys, ranks, shares, stores), so 8 keys per lane: twice as many workgroups fit a
 // compute unit as with 16, at two thirds of the time (61 M keys 600 -> 350 us, 7 M 50 -> 35); 4 bring no more.
-constexpr int XL_ITEMS = 8, XL_SLOTS = 512, XL_PROBES = 8;
+constexpr int XL_ITEMS = 8;
 template <typename K, class Src>
 __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src kin) {
     constexpr int TILE = BLOCK * XL_ITEMS;
-    constexpr u32 NONE = 0xFFFFFFFFu;
-    __shared__ u32 digit[XL_SLOTS];
-    __shared__ u32 count[XL_SLOTS];  // keys of the tile with that digit, then where they go
+    __shared__ DigitTable T;  // (count: keys of the tile with that digit, then where they go)
     const bool second = (int)blockIdx.x >= tiles_first;
     const KeySort<K>& S = second ? second_sort : first_sort;
     const int n = load_count(S.n_ptr, S.n);
@@ -1449,10 +1484,7 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort
     u32* __restrict__ cursor = S.cursor;
     const int t = threadIdx.x, w = wave_id(), lane = lane_id();
     const u64 lt = lanemask_lt();
-    for (int i = t; i < XL_SLOTS; i += BLOCK) {
-        digit[i] = NONE;
-        count[i] = 0;
-    }
+    T.clear();
     K key[XL_ITEMS];
     u32 place[XL_ITEMS], rank[XL_ITEMS];
     bool has[XL_ITEMS];
@@ -1467,18 +1499,10 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort
     for (int i = 0; i < XL_ITEMS; ++i) {
         const u32 d = digit_of<K>(key[i], shift, mask);
         const u64 same = wave_same_digit_lanes(has[i], d);
-        u32 slot = NONE, b = 0;
+        u32 slot = XL_NONE, b = 0;
         if (has[i] && (same & lt) == 0) {
-            u32 h = (d * 0x9E3779B1u) >> 23;  // 9 bits
-            for (int p = 0; p < XL_PROBES; ++p) {
-                const u32 old = atomicCAS(&digit[h], NONE, d);
-                if (old == NONE || old == d) {
-                    slot = h;
-                    break;
-                }
-                h = (h + 1) & (XL_SLOTS - 1);
-            }
-            b = slot != NONE ? atomicAdd(&count[slot], (u32)__popcll(same)) : atomicAdd(&cursor[d], (u32)__popcll(same));
+            slot = T.slot_of(d);
+            b = slot != XL_NONE ? atomicAdd(&T.count[slot], (u32)__popcll(same)) : atomicAdd(&cursor[d], (u32)__popcll(same));
         }
         const int lead = has[i] ? __ffsll((long long)same) - 1 : lane;
         place[i] = (u32)__shfl((int)slot, lead, 64);
@@ -1488,16 +1512,16 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort
     u32 share[XL_SLOTS / BLOCK];  // (all of a thread's atomics in flight together)
 #pragma unroll
     for (int j = 0; j < XL_SLOTS / BLOCK; ++j) {
-        const u32 d = digit[j * BLOCK + t];
-        share[j] = d != NONE ? atomicAdd(&cursor[d], count[j * BLOCK + t]) : 0u;
+        const u32 d = T.digit[j * BLOCK + t];
+        share[j] = d != XL_NONE ? atomicAdd(&cursor[d], T.count[j * BLOCK + t]) : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < XL_SLOTS / BLOCK; ++j) count[j * BLOCK + t] = share[j];
+    for (int j = 0; j < XL_SLOTS / BLOCK; ++j) T.count[j * BLOCK + t] = share[j];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < XL_ITEMS; ++i) {
         if (has[i]) {
-            const u32 pos = (place[i] != NONE ? count[place[i]] : 0u) + rank[i];
+            const u32 pos = (place[i] != XL_NONE ? T.count[place[i]] : 0u) + rank[i];
             if (pos < (u32)n) S.k1[pos] = key[i];  // (always, when hist and cursor are as described)
         }
     }
