@@ -121,17 +121,13 @@ struct TieBreak {
     __device__ __forceinline__ u64 priority(u32 cost_key_, int e) const { return ((u64)cost_key_ << 32) | enc((u32)e); }
 };
 
-// The same for the kernels every round runs, where the choice is made at compile time so that
-// the path without shuffle carries no test of it.
+// An edge's bid on one of its ends: among the edges at one vertex, the order by edge index is the order by their other
+// ends (those below the vertex come first in both), so without shuffle the bid names that end instead: the best
+// bid on a vertex then tells its partner without a look at the edge.
 template <bool SHUFFLE>
-__device__ __forceinline__ u64 edge_priority(const TieBreak& tb, u32 cost_key_, int e) {
+__device__ __forceinline__ u64 edge_bid(const TieBreak& tb, u32 cost_key_, int e, int other) {
     if constexpr (SHUFFLE) return tb.priority(cost_key_, e);
-    return ((u64)cost_key_ << 32) | (u32)e;
-}
-template <bool SHUFFLE>
-__device__ __forceinline__ u32 edge_of_priority(const TieBreak& tb, u64 p) {
-    if constexpr (SHUFFLE) return tb.dec((u32)p);
-    return (u32)p;
+    return ((u64)cost_key_ << 32) | (u32)other;
 }
 
 // ---------------------------------------------------------------------------
@@ -674,15 +670,6 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
     }
 }
 
-struct UniquePred {
-    const u64* keys;
-    u64 sentinel;
-    __device__ bool operator()(int i) const {
-        const u64 k = keys[i];
-        return k != sentinel && (i == 0 || k != keys[i - 1]);
-    }
-};
-
 // Where a pair is contracted to.
 enum { PLACE_MEAN = 0, PLACE_INVERSE = 1 };
 
@@ -765,6 +752,138 @@ __device__ __forceinline__ float pair_cost(const VRec* __restrict__ vrec, int u,
     return (xAx + 2.0f * bx) + c;
 }
 
+// A workgroup's bids, put together in LDS before they go to memory.  Atomics are carried out at the memory side, about 25 per
+// nanosecond for the whole chip; one request covers a 64-byte line (8 vertices), but lanes of a wave that name the
+// same word take a request each.  The edges of a workgroup touch few vertices, and those lie in few lines, so the table
+// holds lines: each goes out as one request.  A line that finds no place (a mesh numbered without locality) goes out
+// by itself.  1.2 M vertices, first round: costs and bids 107 -> @@ us, sub-round 0 59 -> @@.
+template <int LINES>
+struct BidTable {
+    static constexpr int PROBES = 4;
+    int line[LINES];
+    u64 bid[8 * LINES];
+    __device__ __forceinline__ void clear() {
+        for (int i = threadIdx.x; i < LINES; i += BLOCK) line[i] = -1;
+        for (int i = threadIdx.x; i < 8 * LINES; i += BLOCK) bid[i] = VMIN_NONE;
+    }
+    // A bid p on vertex v.  rst: an array whose word of every vertex that is bid on is cleared (or null).
+    __device__ __forceinline__ void put(u64* __restrict__ vmin, u64* __restrict__ rst, int v, u64 p) {
+        const int l = v >> 3;
+        u32 h = ((u32)l * 0x9E3779B1u >> 16) & (u32)(LINES - 1);
+        for (int j = 0; j < PROBES; ++j) {
+            int old = *(volatile int*)&line[h];
+            if (old == -1) old = atomicCAS(&line[h], -1, l);
+            if (old == -1 || old == l) {
+                atomicMin(&bid[8 * h + (u32)(v & 7)], p);
+                return;
+            }
+            h = (h + 1) & (u32)(LINES - 1);
+        }
+        atomicMin(&vmin[v], p);
+        if (rst) rst[v] = VMIN_NONE;
+    }
+    __device__ __forceinline__ void flush(u64* __restrict__ vmin, u64* __restrict__ rst) {
+        for (int i = threadIdx.x; i < 8 * LINES; i += BLOCK) {
+            const u64 b = bid[i];
+            if (b == VMIN_NONE) continue;
+            const size_t v = 8 * (size_t)line[i >> 3] + (size_t)(i & 7);
+            atomicMin(&vmin[v], b);
+            if (rst) rst[v] = VMIN_NONE;
+        }
+    }
+};
+
+// Writes the distinct edges, their cost keys, and places each edge's first bid
+// (sub-round 0 of the selection) on both of its vertices.  The scatter pass of a compaction: the sort has left the first
+// keys of runs per tile of BLOCK * CHUNKS positions.  A wave lists its edges in LDS (most keys come twice), so that the
+// lanes that fetch two vertex records each are all at work.
+constexpr int unique_lines(int chunks) { return chunks == 16 ? 256 : 128; }
+template <int PLACE, bool SHUFFLE, int CHUNKS>
+__global__ __launch_bounds__(BLOCK) void unique_cost_kernel(const u64* __restrict__ keys, const int* __restrict__ n_ptr,
+                                                            const int* __restrict__ tilesum, int prefixed,
+                                                            u64* __restrict__ ekey, u32* __restrict__ ecost,
+                                                            unsigned char* __restrict__ estate, const VRec* __restrict__ vrec,
+                                                            u64* __restrict__ vmin0, int vbits, MeshTab mt, float rcond_min,
+                                                            TieBreak tb, int* __restrict__ ne_out) {
+    constexpr int BATCH = CHUNKS < 4 ? CHUNKS : 4;  // chunks listed at a time
+    __shared__ u32 smem[prim::WAVES];
+    __shared__ u64 slist[prim::WAVES][64 * BATCH];
+    __shared__ BidTable<unique_lines(CHUNKS)> bids;
+    const int n = *n_ptr, tile = blockIdx.x, t = threadIdx.x, w = prim::wave_id(), lane = prim::lane_id();
+    const long long base = (long long)tile * (BLOCK * CHUNKS);
+    if (n <= 0 && tile == 0 && t == 0) *ne_out = 0;
+    if (base >= n) return;
+    bids.clear();
+    u32 before;
+    if (prefixed) {
+        before = (u32)tilesum[tile];
+    } else {
+        u32 part = 0;
+        for (int j = t; j < tile; j += BLOCK) part += (u32)tilesum[j];
+        before = prim::block_sum(part, smem);
+    }
+    const long long i0 = base + (long long)w * (64 * CHUNKS);
+    u64 key[CHUNKS], bal[CHUNKS];
+    u32 cnt = 0;
+    const u64 sentinel = edge_sentinel(vbits);
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        const long long i = i0 + c * 64 + lane;
+        key[c] = i < n ? keys[i] : sentinel;
+    }
+    u64 front = i0 > 0 && i0 < n ? keys[i0 - 1] : sentinel;  // the key in front of a chunk
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        u64 prev = __shfl_up(key[c], 1, 64);
+        if (lane == 0) prev = front;
+        front = __shfl(key[c], 63, 64);
+        bal[c] = __ballot(key[c] != sentinel && key[c] != prev);
+        cnt += (u32)__popcll(bal[c]);
+    }
+    __syncthreads();
+    if (lane == 0) smem[w] = cnt;
+    __syncthreads();
+    u32 run = before, tot = 0;
+#pragma unroll
+    for (int j = 0; j < prim::WAVES; ++j) {
+        if (j < w) run += smem[j];
+        tot += smem[j];
+    }
+    if (base + BLOCK * CHUNKS >= n && t == 0) *ne_out = (int)(before + tot);
+    const u64 lt = prim::lanemask_lt(), vmask = (1ull << vbits) - 1ull;
+    u64* list = slist[w];
+#pragma unroll
+    for (int c0 = 0; c0 < CHUNKS; c0 += BATCH) {
+        int m = 0;
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const u64 b = bal[c0 + j];
+            if ((b >> lane) & 1ull) list[m + (int)__popcll(b & lt)] = key[c0 + j];
+            m += (int)__popcll(b);
+        }
+        __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations complete in order)
+        for (int q = 0; q < m; q += 64) {
+            if (q + lane < m) {
+                const u64 k = list[q + lane];
+                const int u = (int)(k >> vbits), v = (int)(k & vmask), e = (int)run + q + lane;
+                const u32 ck = cost_key(pair_cost<PLACE>(vrec, u, v, rcond_min));
+                const bool act = mt.active[mesh_of(mt.voff, mt.B, u)] != 0;
+                ekey[e] = k;
+                ecost[e] = ck;
+                estate[e] = act ? 0 : 1;
+                if (act) {
+                    bids.put(vmin0, nullptr, u, edge_bid<SHUFFLE>(tb, ck, e, v));
+                    bids.put(vmin0, nullptr, v, edge_bid<SHUFFLE>(tb, ck, e, u));
+                }
+            }
+        }
+        run += (u32)m;
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    bids.flush(vmin0, nullptr);
+}
+
 // Bids of the lanes of one wave on their vertices x, where lanes with equal x are neighbours among
 // the lanes that bid (edges are sorted by their lower vertex, so that end of consecutive edges is
 // often the same vertex).  Atomics of one wave on one address are served one after the other, so
@@ -792,42 +911,6 @@ __device__ __forceinline__ void bid_grouped(u64* __restrict__ vmin, bool on, int
     const bool tail = on && (above == 0 || ((hb >> (__ffsll((long long)above) - 1)) & 1ull));
     if (tail) atomicMin(&vmin[x], q);
 }
-
-// Writes the distinct edges, their cost keys, and places each edge's first bid
-// (sub-round 0 of the selection) on both of its vertices.
-template <int PLACE, bool SHUFFLE>
-struct UniqueOutT {
-    static constexpr bool WAVE_WIDE = true;
-    const u64* keys;
-    u64* ekey;
-    u32* ecost;
-    const VRec* vrec;
-    u64* vmin0;
-    unsigned char* estate;
-    int vbits;
-    MeshTab mt;
-    float rcond_min;
-    TieBreak tb;
-    __device__ void wave(int i, bool in_range, bool flagged, int e) const {
-        bool act = false;
-        int u = 0;
-        u64 p = 0;
-        if (flagged) {
-            const u64 k = keys[i];
-            u = (int)(k >> vbits);
-            const int v = (int)(k & ((1ull << vbits) - 1ull));
-            ekey[e] = k;
-            const u32 ck = cost_key(pair_cost<PLACE>(vrec, u, v, rcond_min));
-            ecost[e] = ck;
-            act = mt.active[mesh_of(mt.voff, mt.B, u)] != 0;
-            estate[e] = act ? 0 : 1;
-            p = edge_priority<SHUFFLE>(tb, ck, e);
-            if (act) atomicMin(&vmin0[v], p);
-        }
-        (void)in_range;
-        bid_grouped(vmin0, act, u, p);
-    }
-};
 
 // ---------------------------------------------------------------------------
 // S3: greedy disjoint grouping of Alg. 2 lines 3-10, computed in parallel.
@@ -886,45 +969,43 @@ struct SelArgs {
                        // the count pass of the gather that follows
 };
 
-// Bids are read with device-scope atomic loads where the same kernel also
-// changes them (the tail), with plain loads otherwise.
-template <bool COHERENT>
-__device__ __forceinline__ u64 load_bid(const u64* p) {
-    if (COHERENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return *p;
-}
-
-template <bool COHERENT, bool SHUFFLE>
+template <bool SHUFFLE>
 __device__ __forceinline__ bool vertex_pairs_now(const u64* __restrict__ cur, const u64* __restrict__ ekey, int vbits,
                                                  const TieBreak& tb, int x, u64 mx) {
     // The best live edge at x is accepted in this sub-round iff it is also the best at its other end.
     if (mx == VMIN_NONE) return false;  // no bid on x (cannot happen for an end of a live edge)
-    const u64 k = ekey[edge_of_priority<SHUFFLE>(tb, mx)];
-    const int a = (int)(k >> vbits), b = (int)(k & ((1ull << vbits) - 1ull));
-    const int other = (a == x) ? b : a;
-    return load_bid<COHERENT>(&cur[other]) == mx;
+    if constexpr (SHUFFLE) {
+        const u64 k = ekey[tb.dec((u32)mx)];
+        const int a = (int)(k >> vbits), b = (int)(k & ((1ull << vbits) - 1ull));
+        return cur[a == x ? b : a] == mx;
+    } else {
+        return cur[(u32)mx] == ((mx & 0xFFFFFFFF00000000ull) | (u32)x);
+    }
 }
 
-// One edge of one sub-round.  Returns true if the edge stays live.
-template <bool COHERENT, bool SHUFFLE>
+// One edge of one sub-round.  Returns true if the edge stays live; pu, pv = its bids on its ends.
+template <bool SHUFFLE>
 __device__ __forceinline__ bool subround_edge(const SelArgs& A, const u64* __restrict__ cur, int k, int e, int& u,
-                                              int& v, int& m, u64& p, bool& sel) {
+                                              int& v, int& m, u64& pu, u64& pv, bool& sel) {
     const u64 key = A.ekey[e];
+    const u32 ck = A.ecost[e];
     u = (int)(key >> A.vbits);
     v = (int)(key & ((1ull << A.vbits) - 1ull));
-    p = edge_priority<SHUFFLE>(A.tb, A.ecost[e], e);
+    pu = edge_bid<SHUFFLE>(A.tb, ck, e, v);
+    pv = edge_bid<SHUFFLE>(A.tb, ck, e, u);
     m = mesh_of(A.mt.voff, A.mt.B, u);
     sel = false;
     if (k == 0 && !A.mt.active[m]) return false;
-    const u64 mu = load_bid<COHERENT>(&cur[u]), mv = load_bid<COHERENT>(&cur[v]);
-    if (mu == p && mv == p) {
+    const u64 mu = cur[u], mv = cur[v];
+    if (mu == pu && mv == pv) {
         sel = true;
         A.mate[u] = v;
         A.mate[v] = u;
         return false;
     }
-    return !(vertex_pairs_now<COHERENT, SHUFFLE>(cur, A.ekey, A.vbits, A.tb, u, mu) ||
-             vertex_pairs_now<COHERENT, SHUFFLE>(cur, A.ekey, A.vbits, A.tb, v, mv));
+    const bool gone_u = vertex_pairs_now<SHUFFLE>(cur, A.ekey, A.vbits, A.tb, u, mu);
+    const bool gone_v = vertex_pairs_now<SHUFFLE>(cur, A.ekey, A.vbits, A.tb, v, mv);
+    return !(gone_u || gone_v);
 }
 
 // pairs formed, counted per mesh: one atomic per wave and mesh
@@ -941,6 +1022,27 @@ __device__ __forceinline__ void count_pairs(const SelArgs& A, bool sel, int m) {
         sb &= ~same;
     }
 }
+
+// The same for a workgroup whose pairs nearly all belong to one mesh (edges are in mesh order): that mesh's are put together in LDS
+// and added by one atomic in the end.  (The counters of a mesh lie in MATCH_SLOTS lines, and a line takes an atomic every
+// 10 ns: with one per wave they took longer than the rest of a sub-round, 150 of 420 us at 30 M edges.)
+struct PairTally {
+    int mesh, pairs;
+    // by one thread; e = the workgroup's first edge
+    __device__ __forceinline__ void begin(const SelArgs& A, long long e, int n) {
+        mesh = A.mt.B <= 1 || e >= n ? 0 : mesh_of(A.mt.voff, A.mt.B, (int)(A.ekey[e] >> A.vbits));
+        pairs = 0;
+    }
+    __device__ __forceinline__ void count(const SelArgs& A, bool sel, int m) {
+        const u64 mine = __ballot(sel && m == mesh);
+        if (mine && prim::lane_id() == 0) atomicAdd(&pairs, (int)__popcll(mine));
+        if (A.mt.B > 1) count_pairs(A, sel && m != mesh, m);
+    }
+    // by one thread, behind a barrier
+    __device__ __forceinline__ void end(const SelArgs& A) const {
+        if (pairs) atomicAdd(&A.mt.mslots[((size_t)mesh * MATCH_SLOTS + (blockIdx.x & (MATCH_SLOTS - 1))) * MATCH_PAD], pairs);
+    }
+};
 
 // The same into an LDS array (one workgroup's own tally).
 __device__ __forceinline__ void count_pairs_lds(int* pairs, bool sel, int m) {
@@ -959,6 +1061,7 @@ __device__ __forceinline__ void count_pairs_lds(int* pairs, bool sel, int m) {
 // their state byte.  No worklist is kept here: appending survivors would need
 // one returning atomic per workgroup on a single counter, and thousands of
 // those queue up for longer than the sub-round itself takes.
+constexpr int SUBROUND_LINES = 128;
 template <bool SHUFFLE>
 __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k) {
     const u64* __restrict__ cur = A.vmin[k % 3];
@@ -966,25 +1069,32 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
     u64* __restrict__ rst = A.vmin[(k + 2) % 3];
     const int n = A.st->ne;
     if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = k + 1;
+    __shared__ BidTable<SUBROUND_LINES> bids;
+    __shared__ PairTally tally;
+    if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * BLOCK, n);
     bool alive = false;
     for (long long base = (long long)blockIdx.x * BLOCK; base < n; base += (long long)gridDim.x * BLOCK) {
         const long long i = base + threadIdx.x;
+        bids.clear();
+        __syncthreads();
         bool sel = false;
         alive = false;
         int u = 0, v = 0, m = 0;
-        u64 p = 0;
+        u64 pu = 0, pv = 0;
         const bool live_in = (i < n) && A.estate[i] == 0;
-        if (live_in) alive = subround_edge<false, SHUFFLE>(A, cur, k, (int)i, u, v, m, p, sel);
-        count_pairs(A, sel, m);
+        if (live_in) alive = subround_edge<SHUFFLE>(A, cur, k, (int)i, u, v, m, pu, pv, sel);
+        tally.count(A, sel, m);
         if (alive) {
-            atomicMin(&nxt[v], p);
-            rst[u] = VMIN_NONE;
-            rst[v] = VMIN_NONE;
+            bids.put(nxt, rst, u, pu);
+            bids.put(nxt, rst, v, pv);
         } else if (live_in) {
             A.estate[i] = 1;
         }
-        bid_grouped(nxt, alive, u, p);
+        __syncthreads();
+        bids.flush(nxt, rst);
+        __syncthreads();
     }
+    if (threadIdx.x == 0) tally.end(A);
     if (A.tile_live) {  // (the host has made the grid cover every edge in one step)
         __shared__ int wave_live[BLOCK / 64];
         const u64 b = __ballot(alive);
@@ -1011,12 +1121,15 @@ __global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A
     static_assert(SPARSE_EDGES_PER_LANE == 4 || SPARSE_EDGES_PER_LANE == 16, "one 4- or 16-byte load per lane");
     constexpr int PER_WAVE = 64 * SPARSE_EDGES_PER_LANE;
     __shared__ int slist[prim::WAVES][PER_WAVE];
+    __shared__ PairTally tally;
     const u64* __restrict__ cur = A.vmin[k % 3];
     u64* __restrict__ nxt = A.vmin[(k + 1) % 3];
     u64* __restrict__ rst = A.vmin[(k + 2) % 3];
     const int n = A.st->ne;
     if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = k + 1;
     const int lane = prim::lane_id(), w = prim::wave_id();
+    if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * prim::WAVES * PER_WAVE, n);
+    __syncthreads();
     int* list = slist[w];
     for (long long cbase = ((long long)blockIdx.x * prim::WAVES + w) * PER_WAVE; cbase < n;
          cbase += (long long)gridDim.x * prim::WAVES * PER_WAVE) {
@@ -1057,20 +1170,22 @@ __global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A
             const int i = has ? list[q + lane] : 0;
             bool alive = false, sel = false;
             int u = 0, v = 0, m = 0;
-            u64 p = 0;
-            if (has) alive = subround_edge<false, SHUFFLE>(A, cur, k, i, u, v, m, p, sel);
-            count_pairs(A, sel, m);
+            u64 pu = 0, pv = 0;
+            if (has) alive = subround_edge<SHUFFLE>(A, cur, k, i, u, v, m, pu, pv, sel);
+            tally.count(A, sel, m);
             if (alive) {
-                atomicMin(&nxt[v], p);
+                atomicMin(&nxt[v], pv);
                 rst[u] = VMIN_NONE;
                 rst[v] = VMIN_NONE;
             } else if (has) {
                 A.estate[i] = 1;
             }
-            bid_grouped(nxt, alive, u, p);
+            bid_grouped(nxt, alive, u, pu);
         }
         __builtin_amdgcn_wave_barrier();
     }
+    __syncthreads();
+    if (threadIdx.x == 0) tally.end(A);
 }
 
 struct LivePred {

@@ -398,6 +398,32 @@ bool sort_edges_and_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySor
     return prim::key_sort(s, I, &E, prim::TwoSources<IncidenceKeys, EdgeKeys>{{c->fcur, incidence_fbits(N, F)}, {c->fcur, E.key_bits / 2}});
 }
 
+// Distinct edges, costs and first bids from the sorted keys of E, at most H of them.
+void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& E, int H, const MeshTab& mt, const TieBreak& tb,
+                        const VRec* vrec) {
+    const int chunks = prim::compact_chunks_for(H), tiles = prim::compact_tiles(std::max(H, 1), chunks);
+    const int prefixed = tiles > prim::COMPACT_MAX_SUMMED_TILES;
+#define PICASSO_UNIQUE(PLACE, SHUFFLE, CHUNKS)                                                                            \
+    unique_cost_kernel<PLACE, SHUFFLE, CHUNKS><<<tiles, BLOCK, 0, s>>>(E.k0, &c->st->nh, c->tilesum, prefixed, c->ekey,   \
+                                                                       c->ecost, c->estate, vrec, c->vmin[0], E.key_bits / 2, \
+                                                                       mt, c->opt_rcond_min, tb, &c->st->ne)
+#define PICASSO_UNIQUE_CHUNKS(PLACE, SHUFFLE)                     \
+    do {                                                          \
+        if (chunks == 1) PICASSO_UNIQUE(PLACE, SHUFFLE, 1);       \
+        else if (chunks == 4) PICASSO_UNIQUE(PLACE, SHUFFLE, 4);  \
+        else PICASSO_UNIQUE(PLACE, SHUFFLE, 16);                  \
+    } while (0)
+    if (c->opt_placement == PLACE_INVERSE) {
+        if (tb.on) PICASSO_UNIQUE_CHUNKS(PLACE_INVERSE, true);
+        else PICASSO_UNIQUE_CHUNKS(PLACE_INVERSE, false);
+    } else {
+        if (tb.on) PICASSO_UNIQUE_CHUNKS(PLACE_MEAN, true);
+        else PICASSO_UNIQUE_CHUNKS(PLACE_MEAN, false);
+    }
+#undef PICASSO_UNIQUE_CHUNKS
+#undef PICASSO_UNIQUE
+}
+
 constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 
 // Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
@@ -754,27 +780,14 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // ---- S1 (+S2): edges and costs
         tm.begin(round, PICASSO_ST_EDGES);
         const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F);
-        const u64* skeys = E.k0;
         if (round > 0) launch_edge_keys(c, s, B, round, cur, E, N, F);
         if (!(round == 0 && together) && H > 0 && !sort_edges(c, s, E, round)) return PICASSO_ERR_HIP;
         if (H > 0) prim::compact_scan_sums(s, &c->st->nh, H, c->tilesum);
         renumbered = false;
-        UniquePred up{skeys, edge_sentinel(vbits)};
-#define PICASSO_UNIQUE(PLACE, SHUFFLE, RCOND)                                                                       \
-    do {                                                                                                             \
-        UniqueOutT<PLACE, SHUFFLE> uo{skeys, c->ekey, c->ecost, c->vrec[cur], c->vmin[0], c->estate, vbits, mt,       \
-                                      RCOND, tb};                                                                    \
-        const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);                                          \
-        prim::compact_scatter(s, up, uo, &c->st->nh, H, c->tilesum, &c->st->ne);                                     \
-    } while (0)
-        if (c->opt_placement == PLACE_INVERSE) {
-            if (tb.on) PICASSO_UNIQUE(PLACE_INVERSE, true, c->opt_rcond_min);
-            else PICASSO_UNIQUE(PLACE_INVERSE, false, c->opt_rcond_min);
-        } else {
-            if (tb.on) PICASSO_UNIQUE(PLACE_MEAN, true, 0.0f);
-            else PICASSO_UNIQUE(PLACE_MEAN, false, 0.0f);
+        {
+            const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);
+            launch_unique_cost(c, s, E, H, mt, tb, c->vrec[cur]);
         }
-#undef PICASSO_UNIQUE
         tm.end();
 
         // The contraction.  `guarded`: queued behind the selection tail before the host
@@ -872,7 +885,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             // many workgroups as the gather has tiles: it counts its surviving edges for the gather.
             // (wide == 0: so few edges that the tail takes them all from the start)
             const bool counts_live = wide > 0 && ne_bound < SPARSE_MIN_EDGES && prim::compact_chunks_for(ne_bound) == 1 &&
-                                     grid_for(ne_bound, 1 << 16) == prim::compact_tiles(std::max(ne_bound, 1), 1);
+                                     grid_for(ne_bound, 1 << 14) == prim::compact_tiles(std::max(ne_bound, 1), 1);
             for (int j = 0; j < wide; ++j) {
                 sa.tile_live = (counts_live && j == wide - 1) ? c->tilesum : nullptr;
                 const int g4 = (ne_bound + BLOCK * 4 - 1) / (BLOCK * 4), g16 = (ne_bound + BLOCK * 16 - 1) / (BLOCK * 16);
@@ -884,8 +897,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                     else select_subround_sparse_kernel<16, false><<<g16, BLOCK, 0, s>>>(sa, sel_k + j);
                 } else {
                     const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, sel_k + j == 0);  // (the first only)
-                    if (tb.on) select_subround_kernel<true><<<grid_for(ne_bound, 1 << 16), BLOCK, 0, s>>>(sa, sel_k + j);
-                    else select_subround_kernel<false><<<grid_for(ne_bound, 1 << 16), BLOCK, 0, s>>>(sa, sel_k + j);
+                    if (tb.on) select_subround_kernel<true><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);
+                    else select_subround_kernel<false><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);
                 }
             }
             sel_k += wide;
@@ -1441,21 +1454,11 @@ int picasso_edge_costs(picasso_ctx* c, void* stream, const float* d_verts, int32
     const int H = 3 * F, vbits = edge_vertex_bits(N, H);
     MeshTab mt{1, c->voff[0], c->target, c->active, c->nrem, c->matched, c->mslots};
     const prim::KeySort<u64> E = edge_sort(c, N, F, F);
-    const u64* skeys = E.k0;
     if (F > 0) {
         if (!sort_edges(c, s, E, 0)) return PICASSO_ERR_HIP;
         prim::compact_scan_sums(s, &c->st->nh, H, c->tilesum);
     }
-    UniquePred up{skeys, edge_sentinel(vbits)};
-    if (c->opt_placement == PLACE_INVERSE) {
-        UniqueOutT<PLACE_INVERSE, false> uo{skeys, c->ekey, c->ecost, c->vrec[0], c->vmin[0], c->estate, vbits, mt,
-                                            c->opt_rcond_min, TieBreak{0u, 0u, 0u}};
-        prim::compact_scatter(s, up, uo, &c->st->nh, H, c->tilesum, &c->st->ne);
-    } else {
-        UniqueOutT<PLACE_MEAN, false> uo{skeys, c->ekey, c->ecost, c->vrec[0], c->vmin[0], c->estate, vbits, mt, 0.0f,
-                                         TieBreak{0u, 0u, 0u}};
-        prim::compact_scatter(s, up, uo, &c->st->nh, H, c->tilesum, &c->st->ne);
-    }
+    launch_unique_cost(c, s, E, H, mt, TieBreak{0u, 0u, 0u}, c->vrec[0]);
     export_edges_kernel<<<grid_for(std::max(H, 1)), BLOCK, 0, s>>>(c->ekey, c->ecost, c->st, vbits, d_edges_out,
                                                                    d_cost_out);
     rc = read_header(c, s);
