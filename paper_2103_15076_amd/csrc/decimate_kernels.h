@@ -1071,8 +1071,8 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
     if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = k + 1;
     __shared__ BidTable<SUBROUND_LINES> bids;
     __shared__ PairTally tally;
-    if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * BLOCK, n);
     bool alive = false;
+    if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * BLOCK, n);
     for (long long base = (long long)blockIdx.x * BLOCK; base < n; base += (long long)gridDim.x * BLOCK) {
         const long long i = base + threadIdx.x;
         bids.clear();
@@ -1128,11 +1128,12 @@ __global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A
     const int n = A.st->ne;
     if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = k + 1;
     const int lane = prim::lane_id(), w = prim::wave_id();
-    if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * prim::WAVES * PER_WAVE, n);
+    const int tile = prim::xcd_tile(n, prim::WAVES * PER_WAVE);
+    if (threadIdx.x == 0) tally.begin(A, (long long)tile * prim::WAVES * PER_WAVE, n);
     __syncthreads();
     int* list = slist[w];
-    for (long long cbase = ((long long)blockIdx.x * prim::WAVES + w) * PER_WAVE; cbase < n;
-         cbase += (long long)gridDim.x * prim::WAVES * PER_WAVE) {
+    const long long cbase = ((long long)tile * prim::WAVES + w) * PER_WAVE;  // (the grid covers every edge)
+    if (cbase < n) {
         const long long b0 = cbase + (long long)lane * SPARSE_EDGES_PER_LANE;
         u32 sw[4] = {0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u};  // "retired" beyond the end
         if (b0 + SPARSE_EDGES_PER_LANE <= n) {

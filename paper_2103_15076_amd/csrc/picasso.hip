@@ -890,11 +890,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                 sa.tile_live = (counts_live && j == wide - 1) ? c->tilesum : nullptr;
                 const int g4 = (ne_bound + BLOCK * 4 - 1) / (BLOCK * 4), g16 = (ne_bound + BLOCK * 16 - 1) / (BLOCK * 16);
                 if (sel_k + j == 1 && ne_bound >= SPARSE_MIN_EDGES) {
-                    if (tb.on) select_subround_sparse_kernel<4, true><<<g4, BLOCK, 0, s>>>(sa, sel_k + j);
-                    else select_subround_sparse_kernel<4, false><<<g4, BLOCK, 0, s>>>(sa, sel_k + j);
+                    if (tb.on) select_subround_sparse_kernel<4, true><<<prim::xcd_grid(g4), BLOCK, 0, s>>>(sa, sel_k + j);
+                    else select_subround_sparse_kernel<4, false><<<prim::xcd_grid(g4), BLOCK, 0, s>>>(sa, sel_k + j);
                 } else if (sel_k + j > 1 && ne_bound >= SPARSE_MIN_EDGES) {
-                    if (tb.on) select_subround_sparse_kernel<16, true><<<g16, BLOCK, 0, s>>>(sa, sel_k + j);
-                    else select_subround_sparse_kernel<16, false><<<g16, BLOCK, 0, s>>>(sa, sel_k + j);
+                    if (tb.on) select_subround_sparse_kernel<16, true><<<prim::xcd_grid(g16), BLOCK, 0, s>>>(sa, sel_k + j);
+                    else select_subround_sparse_kernel<16, false><<<prim::xcd_grid(g16), BLOCK, 0, s>>>(sa, sel_k + j);
                 } else {
                     const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, sel_k + j == 0);  // (the first only)
                     if (tb.on) select_subround_kernel<true><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);

@@ -40,6 +40,15 @@ __device__ __forceinline__ u64 wave_same_digit_lanes(bool ok, u32 d) {
     return mine;
 }
 
+// Workgroups are dealt out to the 8 XCDs in turn; so that neighbouring tiles of a list share an XCD's L2 (they refer to
+// the same vertices), an XCD takes one eighth of the n items' tiles in a row.  The tile of this workgroup; a workgroup too many gets the
+// number of tiles.  The grid: xcd_grid of the tiles at most.
+__device__ __forceinline__ int xcd_tile(long long n, int tile_items) {
+    const int tiles = (int)((n + tile_items - 1) / tile_items), per = (tiles + 7) >> 3, j = (int)(blockIdx.x >> 3);
+    return j < per ? min((int)(blockIdx.x & 7u) * per + j, tiles) : tiles;
+}
+inline int xcd_grid(int tiles) { return (tiles + 7) / 8 * 8; }
+
 // Reads a count that lives either on the device (n_ptr) or in the launch arguments.
 __device__ __forceinline__ int load_count(const int* n_ptr, int n_host) { return n_ptr ? *n_ptr : n_host; }
 
