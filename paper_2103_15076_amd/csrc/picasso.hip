@@ -1146,10 +1146,10 @@ struct FilterSplit {
     int groups, chunk;
     float* partial;
 };
-// CALL(kind) with the addressing that C channels and arrays of up to max_rows rows take
-#define PICASSO_ROW_KINDS(C, max_rows, CALL)                      \
+// CALL(kind) with the addressing that C channels and arrays of up to max_rows rows of up to `width` values take
+#define PICASSO_ROW_KINDS(C, width, max_rows, CALL)               \
     do {                                                          \
-        switch (pool::row_kind((C), (max_rows))) {                \
+        switch (pool::row_kind((C), (width), (max_rows))) {       \
             case pool::ROW_EVEN: CALL(pool::ROW_EVEN); break;     \
             case pool::ROW_TAIL: CALL(pool::ROW_TAIL); break;     \
             default: CALL(pool::ROW_ANY);                         \
@@ -1546,7 +1546,7 @@ int picasso_v2f_forward(picasso_ctx* c, void* stream, const float* d_x, int32_t 
     const dim3 grid = conv::xcd_grid(dim3((F + per_block - 1) / per_block, pool::row_parts(m)));
 #define PICASSO_CALL(K) \
     conv::v2f_forward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_x, N, C, d_facets, F, d_level, d_w, d_y, per_wave, m)
-    PICASSO_ROW_KINDS(C, std::max(N, F), PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, C, std::max(N, F), PICASSO_CALL);
 #undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
@@ -1568,7 +1568,7 @@ int picasso_v2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
 #define PICASSO_CALL(K)                                                                                                     \
     conv::v2f_backward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_gy, d_x, C, d_level, d_w, d_offsets, d_corners, N, 3 * F,     \
                                                               sp.chunk, d_gx, sp.partial, m)
-    PICASSO_ROW_KINDS(C, std::max(N, F), PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, C, std::max(N, F), PICASSO_CALL);
 #undef PICASSO_CALL
     if (d_gw) sum_filter_rows(s, sp, 3 * C, d_gw);
     HIP_TRY(c, hipGetLastError());
@@ -1585,7 +1585,7 @@ int picasso_f2f_forward(picasso_ctx* c, void* stream, const float* d_tex, const 
     const dim3 grid = conv::xcd_grid(dim3((F + per_block - 1) / per_block, pool::row_parts(m.row)));
 #define PICASSO_CALL(K) \
     conv::f2f_forward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_tex, d_bary, d_poff, F, P, C, d_w, d_y, m)
-    PICASSO_ROW_KINDS(C, std::max(F, P), PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, C, std::max(F, P), PICASSO_CALL);
 #undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
@@ -1607,7 +1607,7 @@ int picasso_f2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
 #define PICASSO_CALL(K)                                                                                                     \
     conv::f2f_backward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_gy, d_tex, d_bary, d_poff, F, P, C, d_w, sp.chunk, per_wave,    \
                                                               d_gtex, sp.partial, m)
-    PICASSO_ROW_KINDS(C, std::max(F, P), PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, C, std::max(F, P), PICASSO_CALL);
 #undef PICASSO_CALL
     if (d_gw) sum_filter_rows(s, sp, 3 * C, d_gw);
     HIP_TRY(c, hipGetLastError());
@@ -1641,7 +1641,7 @@ int picasso_f2v_forward(picasso_ctx* c, void* stream, const float* d_y, int32_t 
     else if (T <= 12) PICASSO_F2V(3, K);     \
     else if (T <= 16) PICASSO_F2V(4, K);     \
     else conv::f2v_forward_many_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_y, C, d_pi, T, d_w, d_offsets, d_corners, N, 3 * F, d_x, m.row)
-    PICASSO_ROW_KINDS(std::max(C, T), std::max(N, F), PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, std::max(C, T), std::max(N, F), PICASSO_CALL);
 #undef PICASSO_CALL
 #undef PICASSO_F2V
     HIP_TRY(c, hipGetLastError());
@@ -1683,7 +1683,7 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
     else if (rows <= 8) PICASSO_F2V_BACK(2, K); \
     else if (rows <= 12) PICASSO_F2V_BACK(3, K);\
     else PICASSO_F2V_BACK(4, K)
-            PICASSO_ROW_KINDS(std::max(C, T), std::max(N, F), PICASSO_CALL);
+            PICASSO_ROW_KINDS(C, std::max(C, T), std::max(N, F), PICASSO_CALL);
 #undef PICASSO_CALL
 #undef PICASSO_F2V_BACK
             if (d_gw) sum_filter_rows(s, sp, rows * C, d_gw + (size_t)t0 * C);
@@ -1693,7 +1693,7 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
         const int grid = (F + pool::BLOCK / 64 - 1) / (pool::BLOCK / 64);
 #define PICASSO_CALL(K) \
     conv::f2v_backward_pi_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_gx, d_y, C, T, d_w, d_facets, F, d_offsets, N, d_gpi)
-        PICASSO_ROW_KINDS(C, std::max(N, F), PICASSO_CALL);
+        PICASSO_ROW_KINDS(C, std::max(C, T), std::max(N, F), PICASSO_CALL);
 #undef PICASSO_CALL
     }
     HIP_TRY(c, hipGetLastError());
@@ -1756,7 +1756,7 @@ int picasso_pool_forward(picasso_ctx* c, void* stream, int mode, const float* d_
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
 #define PICASSO_CALL(K) pool::launch_pool_forward<K>(s, mode, d_x, C, d_offsets, d_members, n_out, d_weight, d_y, d_argmax)
-    PICASSO_ROW_KINDS(C, std::max(n_in, n_out), PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, C, std::max(n_in, n_out), PICASSO_CALL);
 #undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
@@ -1772,7 +1772,7 @@ int picasso_pool_backward(picasso_ctx* c, void* stream, int mode, const float* d
     HIP_TRY(c, hipSetDevice(c->device));
 #define PICASSO_CALL(K) \
     pool::launch_pool_backward<K>(s, mode, d_gy, n_in, C, d_cluster_id, d_offsets, d_members, d_weight, d_argmax, d_gx)
-    PICASSO_ROW_KINDS(C, std::max(n_in, n_out), PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, C, std::max(n_in, n_out), PICASSO_CALL);
 #undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
@@ -1786,7 +1786,7 @@ int picasso_unpool_forward(picasso_ctx* c, void* stream, const float* d_y, int32
     const pool::RowMap m = pool::row_map(C);
 #define PICASSO_CALL(K) \
     pool::unpool_forward_kernel<K><<<pool::row_grid(m, n_in), pool::BLOCK, 0, s>>>(d_y, n_in, C, d_cluster_id, d_x, m)
-    PICASSO_ROW_KINDS(C, n_in, PICASSO_CALL);
+    PICASSO_ROW_KINDS(C, C, n_in, PICASSO_CALL);
 #undef PICASSO_CALL
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;

@@ -33,15 +33,15 @@ struct __attribute__((packed, aligned(4))) PackedInt4 {
 };
 
 // How the rows of a call are addressed, the same for all its arrays (row_kind):
-//   ROW_EVEN  the channel count is a multiple of 4, and every array's byte offsets fit 32 bits and its row numbers
+//   ROW_EVEN  the channel count is a multiple of 4, and every array's byte offsets (rows of up to `width` values) fit 32 bits and its row numbers
 //             24: an address is one 24-bit multiply-add on top of a base in scalar registers;
 //   ROW_TAIL  the same, with a last pack of `left` < 4 channels per row (the others read as 0);
 //   ROW_ANY   any size (64-bit offsets) and channel count.
 // (With 64-bit offsets everywhere the address arithmetic alone took as many vector instructions as the
 // convolutions' sums.)
 enum RowKind { ROW_EVEN, ROW_TAIL, ROW_ANY };
-inline RowKind row_kind(int C, long long max_rows) {
-    const bool fits = max_rows < (1ll << 24) && 4ll * C < (1ll << 24) && 4ll * C * max_rows < (1ll << 32) && max_rows * 64 < (1ll << 32);
+inline RowKind row_kind(int C, int width, long long max_rows) {
+    const bool fits = max_rows < (1ll << 24) && 4ll * width < (1ll << 24) && 4ll * width * max_rows < (1ll << 32) && max_rows * 64 < (1ll << 32);
     return !fits ? ROW_ANY : (C % 4 == 0 ? ROW_EVEN : ROW_TAIL);
 }
 

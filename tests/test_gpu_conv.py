@@ -398,3 +398,19 @@ def test_levels_of_meshes_across_workgroups(pk, oracle, sizes):
                     assert np.array_equal(lev.cpu().numpy()[foff[b]: foff[b + 1]], want), b
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("C,T", [(1, 4), (3, 16), (5, 8), (6, 12), (13, 16), (3, 20)])
+def test_fewer_channels_than_components(pk, ctx, oracle, C, T):
+    """Rows of C channels, no multiple of 4, next to coefficients whose number is one, or above it."""
+    rng = np.random.default_rng(C + 100 * T)
+    V, F = meshgen.noisy_grid(40, 37, seed=C)
+    N, nF = V.shape[0], F.shape[0]
+    y, gx = rng.normal(size=(nF, C)).astype(np.float32), rng.normal(size=(N, C)).astype(np.float32)
+    pi, w = rng.random((nF, T)).astype(np.float32), rng.normal(size=(T, C)).astype(np.float32)
+    off, cor = ctx.picasso_vertex_corner_csr(dev(F), N)
+    x = ctx.picasso_f2v_forward(dev(y), dev(pi), dev(w), off, cor, N).cpu().numpy()
+    gy, gw, gpi = (t.cpu().numpy() for t in ctx.picasso_f2v_backward(dev(gx), dev(y), dev(pi), dev(w), dev(F), off))
+    refs = (oracle.f2v_forward(y, pi, w, F, N),) + tuple(oracle.f2v_backward(gx, y, pi, w, F))
+    for got, ref in zip((x, gy, gw, gpi), refs):
+        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
