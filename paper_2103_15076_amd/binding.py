@@ -93,6 +93,7 @@ class picasso_stats(ctypes.Structure):
 
 
 _lib = None
+_host = None
 
 
 class PicassoError(RuntimeError):
@@ -181,6 +182,29 @@ def load_library():
     return lib
 
 
+def _load_host():
+    """The compiled module through which the calls of every step go (checks, output tensors, the library's call)."""
+    global _host
+    if _host is not None:
+        return _host
+    import torch
+    try:
+        from . import _host as h
+    except ImportError as e:
+        raise RuntimeError("the package's _host module is missing or does not load: build it with "
+                           "`python -m paper_2103_15076_amd.build`") from e
+    h.set_callbacks(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _raise_status)
+    _host = h
+    return h
+
+
+def _raise_status(handle, st):
+    msg = picasso_strerror(st)
+    if st == PICASSO_ERR_HIP:
+        msg += ": " + load_library().picasso_last_hip_error(ctypes.c_void_p(handle)).decode()
+    raise PicassoError(st, msg)
+
+
 def picasso_strerror(status: int) -> str:
     return load_library().picasso_strerror(int(status)).decode()
 
@@ -233,18 +257,19 @@ class Context:
     """Owns a picasso_ctx (device workspace sized at creation)."""
 
     def __init__(self, max_verts: int, max_facets: int, max_meshes: int = 1, device: int = 0):
-        self._lib = load_library()
+        self._lib, self._n = load_library(), _load_host()
         self._h = ctypes.c_void_p(0)
         st = self._lib.picasso_create(ctypes.byref(self._h), int(device), int(max_verts), int(max_facets),
                                       int(max_meshes))
         if st != PICASSO_OK:
             raise PicassoError(st, picasso_strerror(st))
+        self._p = self._h.value
         self.max_verts, self.max_facets, self.max_meshes, self.device = max_verts, max_facets, max_meshes, device
 
     def close(self):
         if getattr(self, "_h", None) and self._h.value:
             self._lib.picasso_destroy(self._h)
-            self._h = ctypes.c_void_p(0)
+            self._h, self._p = ctypes.c_void_p(0), 0
 
     def __del__(self):
         try:
@@ -282,10 +307,7 @@ class Context:
         return self._lib.picasso_last_hip_error(self._h).decode()
 
     def _raise(self, st):
-        msg = picasso_strerror(st)
-        if st == PICASSO_ERR_HIP:
-            msg += ": " + self.last_hip_error()
-        raise PicassoError(st, msg)
+        _raise_status(self._h.value, st)
 
     # -- the calls of include/picasso.h, same names ---------------------------------------------
 
@@ -293,60 +315,29 @@ class Context:
                          stats=None, stream=None, check=True):
         """Returns (status, verts_out[:nv], facets_out[:nf], cluster_id).  Output
         tensors are allocated with torch when not supplied (capacity = input sizes)."""
-        import torch
-        N, F = int(verts.shape[0]), int(facets.shape[0])
-        dev = verts.device
-        if verts_out is None:
-            verts_out = torch.empty((max(N, 1), 3), dtype=torch.float32, device=dev)
-        if facets_out is None:
-            facets_out = torch.empty((max(F, 1), 3), dtype=torch.int32, device=dev)
-        if cluster_id is None:
-            cluster_id = torch.empty((max(N, 1),), dtype=torch.int32, device=dev)
-        nv, nf = ctypes.c_int32(0), ctypes.c_int32(0)
-        st = self._lib.picasso_decimate(
-            self._h, _stream_ptr(stream), _dev_ptr(verts, torch.float32, "verts"), N,
-            _dev_ptr(facets, torch.int32, "facets"), F, int(target_nv),
-            _dev_ptr(verts_out, torch.float32, "verts_out"), _dev_ptr(facets_out, torch.int32, "facets_out"),
-            _dev_ptr(cluster_id, torch.int32, "cluster_id"), ctypes.byref(nv), ctypes.byref(nf),
-            ctypes.byref(stats) if stats is not None else None)
-        if st < 0:
-            if check:
-                self._raise(st)
-            return st, None, None, None
-        return st, verts_out[: nv.value], facets_out[: nf.value], cluster_id[:N]
+        r = self._n.decimate(self._p, stream, verts, facets, target_nv, verts_out, facets_out, cluster_id,
+                             ctypes.addressof(stats) if stats is not None else 0)
+        if r[0] < 0 and check:
+            self._raise(r[0])
+        return r
 
     def picasso_decimate_batch(self, verts, facets, nv_in, nf_in, target_nv, verts_out=None, facets_out=None,
                                cluster_id=None, stats=None, stream=None, check=True):
         """nv_in / nf_in / target_nv: host int sequences [B].  Returns
         (status, verts_out[:sum nv], facets_out[:sum nf], cluster_id, nv_out[B], nf_out[B])."""
         import numpy as np
-        import torch
         nv_in = np.ascontiguousarray(nv_in, dtype=np.int32)
         nf_in = np.ascontiguousarray(nf_in, dtype=np.int32)
         target_nv = np.ascontiguousarray(target_nv, dtype=np.int32)
-        B = int(nv_in.shape[0])
-        N, F = int(verts.shape[0]), int(facets.shape[0])
-        dev = verts.device
-        if verts_out is None:
-            verts_out = torch.empty((max(N, 1), 3), dtype=torch.float32, device=dev)
-        if facets_out is None:
-            facets_out = torch.empty((max(F, 1), 3), dtype=torch.int32, device=dev)
-        if cluster_id is None:
-            cluster_id = torch.empty((max(N, 1),), dtype=torch.int32, device=dev)
-        nvo = np.zeros(B, np.int32)
-        nfo = np.zeros(B, np.int32)
-        hp = lambda a: a.ctypes.data_as(ctypes.c_void_p)
-        st = self._lib.picasso_decimate_batch(
-            self._h, _stream_ptr(stream), B, _dev_ptr(verts, torch.float32, "verts"),
-            _dev_ptr(facets, torch.int32, "facets"), hp(nv_in), hp(nf_in), hp(target_nv),
-            _dev_ptr(verts_out, torch.float32, "verts_out"), _dev_ptr(facets_out, torch.int32, "facets_out"),
-            _dev_ptr(cluster_id, torch.int32, "cluster_id"), hp(nvo), hp(nfo),
-            ctypes.byref(stats) if stats is not None else None)
-        if st < 0:
+        nvo = np.zeros(nv_in.shape[0], np.int32)
+        nfo = np.zeros(nv_in.shape[0], np.int32)
+        r = self._n.decimate_batch(self._p, stream, verts, facets, nv_in, nf_in, target_nv, verts_out, facets_out,
+                                   cluster_id, nvo, nfo, ctypes.addressof(stats) if stats is not None else 0)
+        if r[0] < 0:
             if check:
-                self._raise(st)
-            return st, None, None, None, None, None
-        return st, verts_out[: int(nvo.sum())], facets_out[: int(nfo.sum())], cluster_id[:N], nvo, nfo
+                self._raise(r[0])
+            return r + (None, None)
+        return r + (nvo, nfo)
 
     def picasso_vertex_quadrics(self, verts, facets, stream=None):
         import torch
@@ -390,208 +381,56 @@ class Context:
 
     def picasso_cluster_csr(self, cluster_id, n_out, stream=None):
         """Returns (offsets int32[n_out+1], members int32[n_in]) device tensors."""
-        import torch
-        n_in = int(cluster_id.shape[0])
-        off = torch.empty((n_out + 1,), dtype=torch.int32, device=cluster_id.device)
-        mem = torch.empty((n_in,), dtype=torch.int32, device=cluster_id.device)
-        st = self._lib.picasso_cluster_csr(self._h, _stream_ptr(stream), _dev_ptr(cluster_id, torch.int32, "cluster_id"),
-                                           n_in, int(n_out), _dev_ptr(off, torch.int32, "off"),
-                                           _dev_ptr(mem, torch.int32, "mem"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return off, mem
+        return self._n.cluster_csr(self._p, stream, cluster_id, n_out)
 
     def picasso_pool_forward(self, mode, x, offsets, members, weight=None, want_argmax=None, stream=None):
         """Returns y[n_out, C]; for PICASSO_POOL_MAX returns (y, argmax)."""
-        import torch
-        n_in, C = int(x.shape[0]), int(x.shape[1])
-        n_out = int(offsets.shape[0]) - 1
-        y = torch.empty((n_out, C), dtype=torch.float32, device=x.device)
         if want_argmax is None:
             want_argmax = mode == PICASSO_POOL_MAX
-        arg = torch.empty((n_out, C), dtype=torch.int32, device=x.device) if want_argmax else None
-        st = self._lib.picasso_pool_forward(self._h, _stream_ptr(stream), int(mode), _dev_ptr(x, torch.float32, "x"),
-                                            n_in, C, _dev_ptr(offsets, torch.int32, "offsets"),
-                                            _dev_ptr(members, torch.int32, "members"), n_out,
-                                            _dev_ptr(weight, torch.float32, "weight"), _dev_ptr(y, torch.float32, "y"),
-                                            _dev_ptr(arg, torch.int32, "argmax"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return (y, arg) if want_argmax else y
+        return self._n.pool_forward(self._p, stream, mode, x, offsets, members, weight, bool(want_argmax))
 
     def picasso_pool_backward(self, mode, gy, cluster_id, offsets, members, weight=None, argmax=None, stream=None):
-        import torch
-        n_in, C = int(cluster_id.shape[0]), int(gy.shape[1])
-        n_out = int(offsets.shape[0]) - 1
-        gx = torch.empty((n_in, C), dtype=torch.float32, device=gy.device)
-        st = self._lib.picasso_pool_backward(self._h, _stream_ptr(stream), int(mode), _dev_ptr(gy, torch.float32, "gy"),
-                                             n_in, C, _dev_ptr(cluster_id, torch.int32, "cluster_id"),
-                                             _dev_ptr(offsets, torch.int32, "offsets"),
-                                             _dev_ptr(members, torch.int32, "members"), n_out,
-                                             _dev_ptr(weight, torch.float32, "weight"),
-                                             _dev_ptr(argmax, torch.int32, "argmax"), _dev_ptr(gx, torch.float32, "gx"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return gx
+        return self._n.pool_backward(self._p, stream, mode, gy, cluster_id, offsets, members, weight, argmax)
 
     def picasso_unpool_forward(self, y, cluster_id, stream=None):
-        import torch
-        n_in, C = int(cluster_id.shape[0]), int(y.shape[1])
-        x = torch.empty((n_in, C), dtype=torch.float32, device=y.device)
-        st = self._lib.picasso_unpool_forward(self._h, _stream_ptr(stream), _dev_ptr(y, torch.float32, "y"), n_in, C,
-                                              _dev_ptr(cluster_id, torch.int32, "cluster_id"),
-                                              _dev_ptr(x, torch.float32, "x"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return x
+        return self._n.unpool_forward(self._p, stream, y, cluster_id)
 
     def picasso_unpool_backward(self, gx, offsets, members, stream=None):
-        import torch
-        n_in, C = int(gx.shape[0]), int(gx.shape[1])
-        n_out = int(offsets.shape[0]) - 1
-        gy = torch.empty((n_out, C), dtype=torch.float32, device=gx.device)
-        st = self._lib.picasso_unpool_backward(self._h, _stream_ptr(stream), _dev_ptr(gx, torch.float32, "gx"), n_in, C,
-                                               _dev_ptr(offsets, torch.int32, "offsets"),
-                                               _dev_ptr(members, torch.int32, "members"), n_out,
-                                               _dev_ptr(gy, torch.float32, "gy"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return gy
+        return self._n.unpool_backward(self._p, stream, gx, offsets, members)
 
     # ---- mesh convolutions, depth-wise (Sec. 4; supplementary, backward propagations)
 
     def picasso_vertex_corner_csr(self, facets, n_verts, stream=None):
         """Returns (offsets int32[N+1], corners int32[3F]) device tensors."""
-        import torch
-        F = int(facets.shape[0])
-        off = torch.empty((int(n_verts) + 1,), dtype=torch.int32, device=facets.device)
-        cor = torch.empty((3 * F,), dtype=torch.int32, device=facets.device)
-        st = self._lib.picasso_vertex_corner_csr(self._h, _stream_ptr(stream), _dev_ptr(facets, torch.int32, "facets"),
-                                                 F, int(n_verts), _dev_ptr(off, torch.int32, "off"),
-                                                 _dev_ptr(cor, torch.int32, "cor"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return off, cor
+        return self._n.vertex_corner_csr(self._p, stream, facets, n_verts)
 
     def picasso_facet_geometry(self, verts, facets, nf=None, alpha=1, beta=1, stream=None):
         """Returns (normals f32[F,3], areas f32[F], level int32[F]); nf = facets per mesh of a batch."""
-        import torch
-        N, F = int(verts.shape[0]), int(facets.shape[0])
-        nrm = torch.empty((F, 3), dtype=torch.float32, device=verts.device)
-        area = torch.empty((F,), dtype=torch.float32, device=verts.device)
-        lev = torch.empty((F,), dtype=torch.int32, device=verts.device)
-        B = 1 if nf is None else len(nf)
-        h_nf = None if nf is None else (ctypes.c_int32 * B)(*[int(v) for v in nf])
-        st = self._lib.picasso_facet_geometry(self._h, _stream_ptr(stream), _dev_ptr(verts, torch.float32, "verts"), N,
-                                              _dev_ptr(facets, torch.int32, "facets"), F, B, h_nf, int(alpha), int(beta),
-                                              _dev_ptr(nrm, torch.float32, "normals"),
-                                              _dev_ptr(area, torch.float32, "areas"), _dev_ptr(lev, torch.int32, "level"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return nrm, area, lev
+        return self._n.facet_geometry(self._p, stream, verts, facets, nf, alpha, beta)
 
     def picasso_fuzzy_coefficients(self, normals, mu, inv_var, stream=None):
-        import torch
-        F, T = int(normals.shape[0]), int(mu.shape[0])
-        pi = torch.empty((F, T), dtype=torch.float32, device=normals.device)
-        st = self._lib.picasso_fuzzy_coefficients(self._h, _stream_ptr(stream),
-                                                  _dev_ptr(normals, torch.float32, "normals"), F,
-                                                  _dev_ptr(mu, torch.float32, "mu"),
-                                                  _dev_ptr(inv_var, torch.float32, "inv_var"), T,
-                                                  _dev_ptr(pi, torch.float32, "pi"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return pi
+        return self._n.fuzzy_coefficients(self._p, stream, normals, mu, inv_var)
 
     def picasso_v2f_forward(self, x, facets, level, w, out=None, stream=None):
-        import torch
-        N, C, F = int(x.shape[0]), int(x.shape[1]), int(facets.shape[0])
-        y = out if out is not None else torch.empty((F, C), dtype=torch.float32, device=x.device)
-        st = self._lib.picasso_v2f_forward(self._h, _stream_ptr(stream), _dev_ptr(x, torch.float32, "x"), N, C,
-                                           _dev_ptr(facets, torch.int32, "facets"), F,
-                                           _dev_ptr(level, torch.int32, "level") if level is not None else None,
-                                           _dev_ptr(w, torch.float32, "w"), _dev_ptr(y, torch.float32, "y"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return y
+        return self._n.v2f_forward(self._p, stream, x, facets, level, w, out)
 
     def picasso_v2f_backward(self, gy, x, facets, level, w, offsets, corners, stream=None):
         """Returns (gx[N,C], gw[3,C])."""
-        import torch
-        N, C, F = int(x.shape[0]), int(x.shape[1]), int(facets.shape[0])
-        gx = torch.empty((N, C), dtype=torch.float32, device=x.device)
-        gw = torch.empty((3, C), dtype=torch.float32, device=x.device)
-        st = self._lib.picasso_v2f_backward(self._h, _stream_ptr(stream), _dev_ptr(gy, torch.float32, "gy"),
-                                            _dev_ptr(x, torch.float32, "x"), N, C,
-                                            _dev_ptr(facets, torch.int32, "facets"), F,
-                                            _dev_ptr(level, torch.int32, "level") if level is not None else None,
-                                            _dev_ptr(w, torch.float32, "w"), _dev_ptr(offsets, torch.int32, "offsets"),
-                                            _dev_ptr(corners, torch.int32, "corners"),
-                                            _dev_ptr(gx, torch.float32, "gx"), _dev_ptr(gw, torch.float32, "gw"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return gx, gw
+        return self._n.v2f_backward(self._p, stream, gy, x, facets, level, w, offsets, corners)
 
     def picasso_f2f_forward(self, tex, bary, poff, w, stream=None):
-        import torch
-        P, C, F = int(tex.shape[0]), int(tex.shape[1]), int(poff.shape[0]) - 1
-        y = torch.empty((F, C), dtype=torch.float32, device=tex.device)
-        st = self._lib.picasso_f2f_forward(self._h, _stream_ptr(stream), _dev_ptr(tex, torch.float32, "tex"),
-                                           _dev_ptr(bary, torch.float32, "bary"), _dev_ptr(poff, torch.int32, "poff"),
-                                           F, P, C, _dev_ptr(w, torch.float32, "w"), _dev_ptr(y, torch.float32, "y"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return y
+        return self._n.f2f_forward(self._p, stream, tex, bary, poff, w)
 
     def picasso_f2f_backward(self, gy, tex, bary, poff, w, stream=None):
         """Returns (gtex[P,C], gw[3,C])."""
-        import torch
-        P, C, F = int(tex.shape[0]), int(tex.shape[1]), int(poff.shape[0]) - 1
-        gtex = torch.empty((P, C), dtype=torch.float32, device=tex.device)
-        gw = torch.empty((3, C), dtype=torch.float32, device=tex.device)
-        # (rows of points that belong to no facet are zero; only they are written twice)
-        st = self._lib.picasso_f2f_clear_unowned(self._h, _stream_ptr(stream), _dev_ptr(poff, torch.int32, "poff"), F, P, C,
-                                                 _dev_ptr(gtex, torch.float32, "gtex"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        st = self._lib.picasso_f2f_backward(self._h, _stream_ptr(stream), _dev_ptr(gy, torch.float32, "gy"),
-                                            _dev_ptr(tex, torch.float32, "tex"), _dev_ptr(bary, torch.float32, "bary"),
-                                            _dev_ptr(poff, torch.int32, "poff"), F, P, C,
-                                            _dev_ptr(w, torch.float32, "w"), _dev_ptr(gtex, torch.float32, "gtex"),
-                                            _dev_ptr(gw, torch.float32, "gw"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return gtex, gw
+        return self._n.f2f_backward(self._p, stream, gy, tex, bary, poff, w)
 
     def picasso_f2v_forward(self, y, pi, w, offsets, corners, n_verts, out=None, stream=None):
-        import torch
-        F, C, T = int(y.shape[0]), int(y.shape[1]), int(pi.shape[1])
-        x = out if out is not None else torch.empty((int(n_verts), C), dtype=torch.float32, device=y.device)
-        st = self._lib.picasso_f2v_forward(self._h, _stream_ptr(stream), _dev_ptr(y, torch.float32, "y"), F, C,
-                                           _dev_ptr(pi, torch.float32, "pi"), T, _dev_ptr(w, torch.float32, "w"),
-                                           _dev_ptr(offsets, torch.int32, "offsets"),
-                                           _dev_ptr(corners, torch.int32, "corners"), int(n_verts),
-                                           _dev_ptr(x, torch.float32, "x"))
-        if st != PICASSO_OK:
-            self._raise(st)
-        return x
+        return self._n.f2v_forward(self._p, stream, y, pi, w, offsets, corners, n_verts, out)
 
     def picasso_f2v_backward(self, gx, y, pi, w, facets, offsets, want_gpi=True, stream=None):
         """Returns (gy[F,C], gw[T,C], gpi[F,T] or None)."""
-        import torch
-        F, C, T, N = int(y.shape[0]), int(y.shape[1]), int(pi.shape[1]), int(gx.shape[0])
-        gy = torch.empty((F, C), dtype=torch.float32, device=y.device)
-        gw = torch.empty((T, C), dtype=torch.float32, device=y.device)
-        gpi = torch.empty((F, T), dtype=torch.float32, device=y.device) if want_gpi else None
-        st = self._lib.picasso_f2v_backward(self._h, _stream_ptr(stream), _dev_ptr(gx, torch.float32, "gx"),
-                                            _dev_ptr(y, torch.float32, "y"), F, C, _dev_ptr(pi, torch.float32, "pi"), T,
-                                            _dev_ptr(w, torch.float32, "w"), _dev_ptr(facets, torch.int32, "facets"),
-                                            _dev_ptr(offsets, torch.int32, "offsets"), N,
-                                            _dev_ptr(gy, torch.float32, "gy"), _dev_ptr(gw, torch.float32, "gw"),
-                                            _dev_ptr(gpi, torch.float32, "gpi") if want_gpi else None)
-        if st != PICASSO_OK:
-            self._raise(st)
-        return gy, gw, gpi
+        return self._n.f2v_backward(self._p, stream, gx, y, pi, w, facets, offsets, bool(want_gpi))
 
     def picasso_bucket_sort(self, keys, vals=None, key_bits=None, stream=None):
         """Same as picasso_radix_sort, by top-digit partition + per-bucket LDS sort (n <= 2^20)."""
