@@ -142,12 +142,14 @@ struct RoundTab {
     int* nrem;
     int* matched;
     int* mslots;
+    int* live_n;  // see SelArgs
     int first_round;
 };
 
 // Per-mesh budgets and the round's counters, by one workgroup.
 __device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) {
     for (int i = threadIdx.x; i < R.B * MATCH_SLOTS; i += blockDim.x) R.mslots[(size_t)i * MATCH_PAD] = 0;
+    if (threadIdx.x < 32) R.live_n[threadIdx.x * MATCH_PAD] = 0;
     for (int b = threadIdx.x; b < R.B; b += blockDim.x) {
         const int nvb = R.voff[b + 1] - R.voff[b];
         if (!R.first_round && R.active[b] && R.matched[b] == 0) R.stuck[b] = 1;
@@ -924,8 +926,6 @@ __device__ __forceinline__ void bid_grouped(u64* __restrict__ vmin, bool on, int
 // sub-round k reads bids in vmin[k%3], places the survivors' bids in
 // vmin[(k+1)%3] and clears their slots in vmin[(k+2)%3].
 // ---------------------------------------------------------------------------
-constexpr int SEL_ITEMS = 1;
-constexpr int SEL_TILE = BLOCK * SEL_ITEMS;
 constexpr int TAIL_THREADS = 1024;
 constexpr int TAIL_MAX = 3584;  // live edges the single-workgroup tail takes over (sized by its LDS state)
 
@@ -946,14 +946,22 @@ __device__ __forceinline__ void signal_host(const HostSignal& h, int tid, bool w
     if (tid == 0) __hip_atomic_store(h.word, h.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// A live edge for the tail.
+struct __attribute__((aligned(16))) LiveEdge {
+    u64 key;
+    u32 cost;
+    int e;
+};
+constexpr int LIVE_SEGS = 32;  // (as the pair counters: the appending waves' atomics spread over cache lines)
+
 struct SelArgs {
     const u64* ekey;
     const u32* ecost;
     u64* vmin[3];
     int* mate;
-    int* list;              // live edges gathered for the tail,
-    const u64* lkey;        // ... their keys
-    const u32* lcost;       // ... and cost keys, in the same order
+    LiveEdge* live;         // the edges that the last grid-wide sub-round leaves live, for the tail: LIVE_SEGS segments of
+    int live_cap;           // ... live_cap places each,
+    int* live_n;            // ... filled up to live_n[segment * MATCH_PAD] (or fuller than full)
     unsigned char* estate;  // per edge: 0 = live, 1 = retired (paired, or an end was paired)
     State* st;
     MeshTab mt;
@@ -964,9 +972,6 @@ struct SelArgs {
     int host_seq;      // sequence word (the host compares the two before it trusts what it reads)
     TieBreak tb;       // order among edges of equal cost
     int cur;           // which of the ping-pong vertex / facet counts belong to this round
-    int* tile_live;    // not null (last grid-wide sub-round before the tail, one edge per lane and no
-                       // striding): workgroup b leaves here how many of its edges stay live, which is
-                       // the count pass of the gather that follows
 };
 
 template <bool SHUFFLE>
@@ -1057,12 +1062,22 @@ __device__ __forceinline__ void count_pairs_lds(int* pairs, bool sel, int m) {
     }
 }
 
+// The lanes' live edges appended to their workgroup's segment of the tail's list.  By all lanes of a wave.
+__device__ __forceinline__ void append_live(const SelArgs& A, bool alive, int e) {
+    const u64 b = __ballot(alive);
+    if (b == 0) return;
+    const int seg = blockIdx.x & (LIVE_SEGS - 1), first = __ffsll((long long)b) - 1;
+    int at = 0;
+    if (prim::lane_id() == first) at = atomicAdd(&A.live_n[seg * MATCH_PAD], (int)__popcll(b));
+    at = __shfl(at, first, 64) + (int)__popcll(b & prim::lanemask_lt());
+    if (alive && at < A.live_cap) A.live[(size_t)seg * A.live_cap + at] = LiveEdge{A.ekey[e], A.ecost[e], e};
+}
+
 // Grid-wide sub-round over ALL edges of the round; retired edges are skipped by
-// their state byte.  No worklist is kept here: appending survivors would need
-// one returning atomic per workgroup on a single counter, and thousands of
-// those queue up for longer than the sub-round itself takes.
+// their state byte.  No worklist is kept from one to the next (it would be appended to by every wave); the
+// last one before the tail (APPEND), which leaves a few thousand edges live, lists them for it.
 constexpr int SUBROUND_LINES = 128;
-template <bool SHUFFLE>
+template <bool SHUFFLE, bool APPEND>
 __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k) {
     const u64* __restrict__ cur = A.vmin[k % 3];
     u64* __restrict__ nxt = A.vmin[(k + 1) % 3];
@@ -1071,14 +1086,12 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
     if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = k + 1;
     __shared__ BidTable<SUBROUND_LINES> bids;
     __shared__ PairTally tally;
-    bool alive = false;
     if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * BLOCK, n);
     for (long long base = (long long)blockIdx.x * BLOCK; base < n; base += (long long)gridDim.x * BLOCK) {
         const long long i = base + threadIdx.x;
         bids.clear();
         __syncthreads();
-        bool sel = false;
-        alive = false;
+        bool sel = false, alive = false;
         int u = 0, v = 0, m = 0;
         u64 pu = 0, pv = 0;
         const bool live_in = (i < n) && A.estate[i] == 0;
@@ -1090,23 +1103,12 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
         } else if (live_in) {
             A.estate[i] = 1;
         }
+        if (APPEND) append_live(A, alive, (int)i);
         __syncthreads();
         bids.flush(nxt, rst);
         __syncthreads();
     }
     if (threadIdx.x == 0) tally.end(A);
-    if (A.tile_live) {  // (the host has made the grid cover every edge in one step)
-        __shared__ int wave_live[BLOCK / 64];
-        const u64 b = __ballot(alive);
-        if (prim::lane_id() == 0) wave_live[prim::wave_id()] = (int)__popcll(b);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int tot = 0;
-#pragma unroll
-            for (int j = 0; j < BLOCK / 64; ++j) tot += wave_live[j];
-            A.tile_live[blockIdx.x] = tot;
-        }
-    }
 }
 
 // The same sub-round for large rounds once most edges are retired (every sub-round but the
@@ -1116,7 +1118,7 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
 // list 64 edges at a time exactly as above.
 constexpr int SPARSE_MIN_EDGES = 1 << 20;  // below this the one-lane-per-edge kernel is at its launch floor anyway
 
-template <int SPARSE_EDGES_PER_LANE, bool SHUFFLE>  // 4 while about a third of the edges are live, 16 later
+template <int SPARSE_EDGES_PER_LANE, bool SHUFFLE, bool APPEND>  // 4 while about a third of the edges are live, 16 later
 __global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A, int k) {
     static_assert(SPARSE_EDGES_PER_LANE == 4 || SPARSE_EDGES_PER_LANE == 16, "one 4- or 16-byte load per lane");
     constexpr int PER_WAVE = 64 * SPARSE_EDGES_PER_LANE;
@@ -1182,6 +1184,7 @@ __global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A
                 A.estate[i] = 1;
             }
             bid_grouped(nxt, alive, u, pu);
+            if (APPEND) append_live(A, alive, i);
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -1189,37 +1192,18 @@ __global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A
     if (threadIdx.x == 0) tally.end(A);
 }
 
-struct LivePred {
-    const unsigned char* estate;
-    __device__ bool operator()(int e) const { return estate[e] == 0; }
-};
-
-// The gathered live edges, with their keys and cost keys beside them: the tail then reads three
-// contiguous arrays at once, not the list and then, through it, the edge arrays.
-struct LiveOut {
-    int* list;
-    const u64* ekey;
-    const u32* ecost;
-    u64* lkey;
-    u32* lcost;
-    __device__ void operator()(int e, int pos) const {
-        list[pos] = e;
-        lkey[pos] = ekey[e];
-        lcost[pos] = ecost[e];
-    }
-};
-
 // Tail: once few edges are live, one workgroup finishes the matching with all
 // of its state in LDS: the live edges' priorities, a hash map from the (at
 // most 2 x TAIL_MAX) vertices they touch to LDS slots, and one 64-bit bid per
-// slot.  A sub-round then costs four workgroup barriers instead of a kernel
-// launch and several trips to memory.  The live count falls in every
-// sub-round (the best live edge is always accepted), so the loop ends.
-// A slot's bid doubles as its "paired" mark (TAIL_PAIRED is below every real
-// priority: a finite cost never has cost key 0).
+// slot.  A sub-round then costs three workgroup barriers instead of a kernel
+// launch and several trips to memory, and none once one wave holds the edges that are left.  The live count falls in every
+// sub-round (the best live edge is always accepted), so the loop ends.  A slot whose vertex has been paired gives up its
+// vertex number (TAIL_PAIRED): nothing else needs it then.
+// (With six barriers, the list gathered by a launch of its own, and the loads of the end not started at the beginning:
+// 14-19 us of every round, now @@.)
 constexpr int TAIL_SLOTS = 8192;  // power of two, >= 2 * TAIL_MAX
 constexpr int TAIL_LDS_MESHES = 1024;
-constexpr u64 TAIL_PAIRED = 0ull;
+constexpr int TAIL_FREE = -1, TAIL_PAIRED = -2;
 
 struct TailLds {
     u64 prio[TAIL_MAX];
@@ -1227,15 +1211,16 @@ struct TailLds {
     int vkey[TAIL_SLOTS];
     unsigned short su[TAIL_MAX], sv[TAIL_MAX];
     unsigned short lst[2][TAIL_MAX];
-    int cnt[2];
+    int cnt[3];                  // live edges of the sub-round, of the next, of the one after that, in turn
+    int seg_at[LIVE_SEGS + 1];   // first place of each segment's edges
     int pairs[TAIL_LDS_MESHES];  // pairs this kernel formed, per mesh (batches of up to this many meshes)
 };
 
 __device__ __forceinline__ int tail_slot(int* vkey, int v) {
     u32 h = ((u32)v * 0x9E3779B1u) >> 19;  // 13 bits
     for (;;) {
-        const int old = atomicCAS(&vkey[h], -1, v);
-        if (old == -1 || old == v) return (int)h;
+        const int old = atomicCAS(&vkey[h], TAIL_FREE, v);
+        if (old == TAIL_FREE || old == v) return (int)h;
         h = (h + 1) & (TAIL_SLOTS - 1);
     }
 }
@@ -1272,103 +1257,151 @@ __device__ __forceinline__ void tail_set_guard(const SelArgs& A, bool finished) 
 
 __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     __shared__ TailLds L;
-    int n = A.st->live[0];     // live edges, gathered into A.list just before this kernel
-    const int tid = threadIdx.x, lane = prim::lane_id();
-    if (n > TAIL_MAX) {        // too many: the host runs more grid-wide sub-rounds
-        if (tid == 0) tail_set_guard(A, false);
-        tail_publish(A, tid);
-        tail_mark_published(A, tid);
-        return;
+    constexpr int NW = TAIL_THREADS / 64;
+    const int tid = threadIdx.x, lane = prim::lane_id(), w = prim::wave_id();
+    // what earlier kernels have left: asked for now, used at the end
+    constexpr int LIVE0 = (int)(offsetof(State, live) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int));
+    static_assert(GO0 <= TAIL_THREADS, "one thread per word");
+    const int hdr_word = tid < GO0 ? reinterpret_cast<const int*>(A.st)[tid] : 0;
+    const int slot_pairs = tid < A.mt.B * MATCH_SLOTS ? A.mt.mslots[(size_t)tid * MATCH_PAD] : 0;
+    if (w == 0) {  // the segments' places
+        const int c = lane < LIVE_SEGS ? A.live_n[lane * MATCH_PAD] : 0;
+        const bool full = __any(c > A.live_cap);
+        int incl = c;
+#pragma unroll
+        for (int d = 1; d < LIVE_SEGS; d <<= 1) {
+            const int o = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += o;
+        }
+        if (lane < LIVE_SEGS) L.seg_at[lane + 1] = incl;
+        if (lane == 0) L.seg_at[0] = 0;
+        if (lane == LIVE_SEGS - 1) L.cnt[0] = full ? max(incl, TAIL_MAX + 1) : incl;
     }
-    const u64 lt = prim::lanemask_lt();
-    const u64 vmask = (1ull << A.vbits) - 1ull;
-
+    if (tid == 0) L.cnt[1] = 0;
+    for (int h = tid; h < TAIL_SLOTS / 4; h += TAIL_THREADS)
+        reinterpret_cast<int4*>(L.vkey)[h] = make_int4(TAIL_FREE, TAIL_FREE, TAIL_FREE, TAIL_FREE);
     // Up to TAIL_LDS_MESHES meshes, the pairs formed here are tallied in LDS and added to the earlier
     // kernels' counters at the end; that way nothing this kernel writes to memory is read back by
     // it, and it needs no device-wide fence (which costs several microseconds here).
     const bool lds_pairs = A.mt.B <= TAIL_LDS_MESHES;
     if (lds_pairs)
         for (int b = tid; b < A.mt.B; b += TAIL_THREADS) L.pairs[b] = 0;
-    for (int h = tid; h < TAIL_SLOTS; h += TAIL_THREADS) L.vkey[h] = -1;
     __syncthreads();
-    for (int i = tid; i < n; i += TAIL_THREADS) {
-        const int e = A.list[i];
-        const u64 key = A.lkey[i];
-        L.prio[i] = A.tb.priority(A.lcost[i], e);
-        L.su[i] = (unsigned short)tail_slot(L.vkey, (int)(key >> A.vbits));
-        L.sv[i] = (unsigned short)tail_slot(L.vkey, (int)(key & vmask));
-        L.lst[0][i] = (unsigned short)i;
+    int n = L.cnt[0];
+    if (n > TAIL_MAX) {  // too many: the host runs more grid-wide sub-rounds, the last of which lists again
+        if (tid < LIVE_SEGS) A.live_n[tid * MATCH_PAD] = 0;
+        if (tid == 0) {
+            A.st->live[0] = n;
+            tail_set_guard(A, false);
+        }
+        if (tid < GO0 && tid < A.publish_ints) host_store(&A.host_img[tid], tid == LIVE0 ? n : hdr_word);
+        tail_mark_published(A, tid);
+        return;
     }
-    int side = 0;
+    const u64 lt = prim::lanemask_lt();
+    const u64 vmask = (1ull << A.vbits) - 1ull;
+    for (int seg = w; seg < LIVE_SEGS; seg += NW) {
+        const int s0 = L.seg_at[seg], m = L.seg_at[seg + 1] - s0;
+        for (int j = lane; j < m; j += 64) {
+            const LiveEdge E = A.live[(size_t)seg * A.live_cap + j];
+            const int i = s0 + j, su = tail_slot(L.vkey, (int)(E.key >> A.vbits)), sv = tail_slot(L.vkey, (int)(E.key & vmask));
+            L.prio[i] = A.tb.priority(E.cost, E.e);
+            L.su[i] = (unsigned short)su;
+            L.sv[i] = (unsigned short)sv;
+            L.lst[0][i] = (unsigned short)i;
+            L.bid[su] = VMIN_NONE;
+            L.bid[sv] = VMIN_NONE;
+        }
+    }
     __syncthreads();
 
-    while (n > 0) {
+    // an edge that holds the best bid at both ends is accepted
+    auto accept = [&](int i, u64 p, bool& sel, int& m) {
+        const int su = L.su[i], sv = L.sv[i];
+        sel = L.bid[su] == p && L.bid[sv] == p;
+        if (sel) {
+            const int u = L.vkey[su], v = L.vkey[sv];
+            A.mate[u] = v;
+            A.mate[v] = u;
+            m = mesh_of(A.mt.voff, A.mt.B, u);
+            L.vkey[su] = TAIL_PAIRED;
+            L.vkey[sv] = TAIL_PAIRED;
+        }
+    };
+    auto tally = [&](bool sel, int m) {
+        if (lds_pairs) count_pairs_lds(L.pairs, sel, m);
+        else count_pairs(A, sel, m);
+    };
+    int side = 0, now = 0;  // cnt[now] = live edges, in lst[side]
+    while (n > 64) {
+        const int nxt = now == 2 ? 0 : now + 1, after = nxt == 2 ? 0 : nxt + 1;
         const int padded = (n + 63) & ~63;  // whole waves run each step so that the ballots are uniform
-        // clear the bids of every vertex that still has a live edge
+        if (tid == 0) L.cnt[after] = 0;
         for (int j = tid; j < n; j += TAIL_THREADS) {
             const int i = L.lst[side][j];
-            L.bid[L.su[i]] = VMIN_NONE;
-            L.bid[L.sv[i]] = VMIN_NONE;
-        }
-        if (tid == 0) L.cnt[side ^ 1] = 0;
-        __syncthreads();
-        for (int j = tid; j < n; j += TAIL_THREADS) {
-            const int i = L.lst[side][j];
-            atomicMin(&L.bid[L.su[i]], L.prio[i]);
-            atomicMin(&L.bid[L.sv[i]], L.prio[i]);
+            const u64 p = L.prio[i];
+            atomicMin(&L.bid[L.su[i]], p);
+            atomicMin(&L.bid[L.sv[i]], p);
         }
         __syncthreads();
-        // accept the edges that hold the best bid at both ends
-        bool mine[(TAIL_MAX + TAIL_THREADS - 1) / TAIL_THREADS];
-        int q = 0;
-        for (int j = tid; j < padded; j += TAIL_THREADS, ++q) {
+        for (int j = tid; j < padded; j += TAIL_THREADS) {
             bool sel = false;
             int m = 0;
             if (j < n) {
                 const int i = L.lst[side][j];
-                const u64 p = L.prio[i];
-                sel = (L.bid[L.su[i]] == p) && (L.bid[L.sv[i]] == p);
-                if (sel) {
-                    const int u = L.vkey[L.su[i]], v = L.vkey[L.sv[i]];
-                    A.mate[u] = v;
-                    A.mate[v] = u;
-                    m = mesh_of(A.mt.voff, A.mt.B, u);
-                }
+                accept(i, L.prio[i], sel, m);
             }
-            mine[q] = sel;
-            if (lds_pairs) count_pairs_lds(L.pairs, sel, m);
-            else count_pairs(A, sel, m);
+            tally(sel, m);
         }
         __syncthreads();
-        q = 0;
-        for (int j = tid; j < n; j += TAIL_THREADS, ++q)
-            if (mine[q]) {
-                const int i = L.lst[side][j];
-                L.bid[L.su[i]] = TAIL_PAIRED;
-                L.bid[L.sv[i]] = TAIL_PAIRED;
-            }
-        __syncthreads();
-        // keep the edges whose ends are both still free
+        // keep the edges whose ends are both still free, and clear those ends' bids
         for (int j = tid; j < padded; j += TAIL_THREADS) {
             bool alive = false;
             int i = 0;
             if (j < n) {
                 i = L.lst[side][j];
-                alive = (L.bid[L.su[i]] != TAIL_PAIRED) && (L.bid[L.sv[i]] != TAIL_PAIRED);
+                const int su = L.su[i], sv = L.sv[i];
+                alive = L.vkey[su] != TAIL_PAIRED && L.vkey[sv] != TAIL_PAIRED;
+                if (alive) L.bid[su] = L.bid[sv] = VMIN_NONE;
             }
             const u64 ab = __ballot(alive);
             if (ab) {
                 int wbase = 0;
-                if (lane == 0) wbase = atomicAdd(&L.cnt[side ^ 1], (int)__popcll(ab));
+                if (lane == 0) wbase = atomicAdd(&L.cnt[nxt], (int)__popcll(ab));
                 wbase = __shfl(wbase, 0, 64);
                 if (alive) L.lst[side ^ 1][wbase + (int)__popcll(ab & lt)] = (unsigned short)i;
             }
         }
         __syncthreads();
         side ^= 1;
-        n = L.cnt[side];
-        __syncthreads();
+        now = nxt;
+        n = L.cnt[now];
     }
+    if (w == 0 && n > 0) {  // (a wave's LDS operations complete in order)
+        bool alive = lane < n;
+        const int i = alive ? L.lst[side][lane] : 0;
+        const u64 p = alive ? L.prio[i] : 0;
+        const int su = alive ? L.su[i] : 0, sv = alive ? L.sv[i] : 0;
+        while (__any(alive)) {
+            if (alive) {
+                atomicMin(&L.bid[su], p);
+                atomicMin(&L.bid[sv], p);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            bool sel = false;
+            int m = 0;
+            if (alive) accept(i, p, sel, m);
+            tally(sel, m);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            alive = alive && L.vkey[su] != TAIL_PAIRED && L.vkey[sv] != TAIL_PAIRED;
+            if (alive) L.bid[su] = L.bid[sv] = VMIN_NONE;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
 
     static_assert(MATCH_SLOTS == 32, "a mesh's slots fill half a wave");
     constexpr int STATE_INTS = (int)(sizeof(State) / sizeof(int));
@@ -1382,7 +1415,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         const int idx = base + tid;
         const bool ok = idx < A.mt.B * MATCH_SLOTS;
         int sum = 0;
-        if (ok) sum = __hip_atomic_load(&A.mt.mslots[(size_t)idx * MATCH_PAD], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ok)  // (only this kernel's own additions, in memory where there are many meshes, came after the first load)
+            sum = base == 0 && lds_pairs ? slot_pairs
+                                         : __hip_atomic_load(&A.mt.mslots[(size_t)idx * MATCH_PAD], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
         if (ok && (idx & (MATCH_SLOTS - 1)) == 0) {
@@ -1398,9 +1433,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     }
     if (lds_pairs) {
         // the host's copy of the counters: everything but live[0] was written by earlier kernels
-        constexpr int LIVE0 = (int)(offsetof(State, live) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int));
-        const int* hdr = reinterpret_cast<const int*>(A.st);
-        if (tid < GO0 && tid < A.publish_ints) host_store(&A.host_img[tid], (tid == LIVE0) ? 0 : hdr[tid]);
+        if (tid < GO0 && tid < A.publish_ints) host_store(&A.host_img[tid], (tid == LIVE0) ? 0 : hdr_word);
     } else {
         __threadfence();
         __syncthreads();

@@ -98,6 +98,8 @@ struct picasso_ctx {
     int* segstart = nullptr;
     SelectState* sel_state = nullptr;  // the budget step's radix select (one long run, see budget_step)
     int* mslots = nullptr;
+    LiveEdge* live = nullptr;  // the selection tail's list (see SelArgs) and its segments' lengths
+    int* live_n = nullptr;
     // pinned host staging
     // pinned host staging: read-back image of the header's front, then the upload image of the whole header
     int* h_pin = nullptr;
@@ -239,6 +241,8 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->segstart = cv.take<int>(b);
     x->sel_state = cv.take<SelectState>(1);
     x->mslots = cv.take<int>(b * MATCH_SLOTS * MATCH_PAD);
+    x->live = cv.take<LiveEdge>((size_t)LIVE_SEGS * TAIL_MAX);
+    x->live_n = cv.take<int>(LIVE_SEGS * MATCH_PAD);
     x->abid = cv.take<u64>(n);
     x->arep = cv.take<int>(n);
     x->acnt = cv.take<int>(n);
@@ -364,7 +368,7 @@ prim::KeySort<u64> incidence_sort(picasso_ctx* c, int N, int F) {
 }
 
 RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
-    return RoundTab{B, c->voff[cur_], c->target, c->active, c->stuck, c->nrem, c->matched, c->mslots, round_ == 0};
+    return RoundTab{B, c->voff[cur_], c->target, c->active, c->stuck, c->nrem, c->matched, c->mslots, c->live_n, round_ == 0};
 }
 
 // First kernel of a round after the first: facets and labels follow the last contraction, the edges' digits are counted.
@@ -853,9 +857,9 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         sa.ecost = c->ecost;
         for (int i = 0; i < 3; ++i) sa.vmin[i] = c->vmin[i];
         sa.mate = c->mate;
-        sa.list = c->list;
-        sa.lkey = c->key64[1];  // (the sort's arrays are free between the unique step and the budget step)
-        sa.lcost = c->val32[1];
+        sa.live = c->live;
+        sa.live_cap = TAIL_MAX;
+        sa.live_n = c->live_n;
         sa.estate = c->estate;
         sa.st = c->st;
         sa.mt = mt;
@@ -881,36 +885,34 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             int wide = 0;
             for (long long l = live_est; l > TAIL_MAX; ++wide) l = l * 10 / decay_x10[std::min(wide, 5)];
             wide = std::min<int>(wide, (int)std::max<int64_t>(1, c->opt_subround_batch));
-            // Below the sparse kernels' range the last of these sub-rounds has one lane per edge and as
-            // many workgroups as the gather has tiles: it counts its surviving edges for the gather.
-            // (wide == 0: so few edges that the tail takes them all from the start)
-            const bool counts_live = wide > 0 && ne_bound < SPARSE_MIN_EDGES && prim::compact_chunks_for(ne_bound) == 1 &&
-                                     grid_for(ne_bound, 1 << 14) == prim::compact_tiles(std::max(ne_bound, 1), 1);
+            wide = std::max(wide, 1);  // (the last of them lists what it leaves live for the tail)
             for (int j = 0; j < wide; ++j) {
-                sa.tile_live = (counts_live && j == wide - 1) ? c->tilesum : nullptr;
-                const int g4 = (ne_bound + BLOCK * 4 - 1) / (BLOCK * 4), g16 = (ne_bound + BLOCK * 16 - 1) / (BLOCK * 16);
-                if (sel_k + j == 1 && ne_bound >= SPARSE_MIN_EDGES) {
-                    if (tb.on) select_subround_sparse_kernel<4, true><<<prim::xcd_grid(g4), BLOCK, 0, s>>>(sa, sel_k + j);
-                    else select_subround_sparse_kernel<4, false><<<prim::xcd_grid(g4), BLOCK, 0, s>>>(sa, sel_k + j);
-                } else if (sel_k + j > 1 && ne_bound >= SPARSE_MIN_EDGES) {
-                    if (tb.on) select_subround_sparse_kernel<16, true><<<prim::xcd_grid(g16), BLOCK, 0, s>>>(sa, sel_k + j);
-                    else select_subround_sparse_kernel<16, false><<<prim::xcd_grid(g16), BLOCK, 0, s>>>(sa, sel_k + j);
-                } else {
-                    const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, sel_k + j == 0);  // (the first only)
-                    if (tb.on) select_subround_kernel<true><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);
-                    else select_subround_kernel<false><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);
-                }
+                const int g4 = prim::xcd_grid((ne_bound + BLOCK * 4 - 1) / (BLOCK * 4)), g16 = prim::xcd_grid((ne_bound + BLOCK * 16 - 1) / (BLOCK * 16));
+                const bool sparse = sel_k + j > 0 && ne_bound >= SPARSE_MIN_EDGES, last = j == wide - 1;
+#define PICASSO_SUBROUND(APPEND)                                                                                            \
+    do {                                                                                                                     \
+        if (sparse && sel_k + j == 1) {                                                                                      \
+            if (tb.on) select_subround_sparse_kernel<4, true, APPEND><<<g4, BLOCK, 0, s>>>(sa, sel_k + j);                    \
+            else select_subround_sparse_kernel<4, false, APPEND><<<g4, BLOCK, 0, s>>>(sa, sel_k + j);                         \
+        } else if (sparse) {                                                                                                 \
+            if (tb.on) select_subround_sparse_kernel<16, true, APPEND><<<g16, BLOCK, 0, s>>>(sa, sel_k + j);                  \
+            else select_subround_sparse_kernel<16, false, APPEND><<<g16, BLOCK, 0, s>>>(sa, sel_k + j);                       \
+        } else {                                                                                                             \
+            const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, sel_k + j == 0); /* (the first only) */         \
+            if (tb.on) select_subround_kernel<true, APPEND><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);     \
+            else select_subround_kernel<false, APPEND><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);          \
+        }                                                                                                                    \
+    } while (0)
+                if (last) PICASSO_SUBROUND(true);
+                else PICASSO_SUBROUND(false);
+#undef PICASSO_SUBROUND
             }
             sel_k += wide;
-            LivePred lp{c->estate};
-            LiveOut lo{c->list, c->ekey, c->ecost, c->key64[1], c->val32[1]};
-            if (counts_live) prim::compact_scatter(s, lp, lo, &c->st->ne, ne_bound, c->tilesum, &c->st->live[0]);
-            else prim::compact(s, lp, lp, lo, &c->st->ne, ne_bound, c->tilesum, &c->st->live[0]);
             // the kernel behind the tail tells the host that the tail's results are in the read-back area
             const HostSignal tail_done = next_signal(c);
             sa.host_seq = tail_done.seq;
             select_tail_kernel<<<1, TAIL_THREADS, 0, s>>>(sa);
-            launched += wide + 3;
+            launched += wide + 1;
             const HostSignal nothing{nullptr, 0};
             if (ahead_ok) {
                 if (ahead_budget) {
