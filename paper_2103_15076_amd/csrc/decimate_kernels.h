@@ -758,7 +758,7 @@ __device__ __forceinline__ float pair_cost(const VRec* __restrict__ vrec, int u,
 // nanosecond for the whole chip; one request covers a 64-byte line (8 vertices), but lanes of a wave that name the
 // same word take a request each.  The edges of a workgroup touch few vertices, and those lie in few lines, so the table
 // holds lines: each goes out as one request.  A line that finds no place (a mesh numbered without locality) goes out
-// by itself.  1.2 M vertices, first round: costs and bids 107 -> @@ us, sub-round 0 59 -> @@.
+// by itself.  1.2 M vertices, first round: costs and bids 106 -> 83 us, sub-round 0 59 -> 51.
 template <int LINES>
 struct BidTable {
     static constexpr int PROBES = 4;
@@ -1200,7 +1200,8 @@ __global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A
 // sub-round (the best live edge is always accepted), so the loop ends.  A slot whose vertex has been paired gives up its
 // vertex number (TAIL_PAIRED): nothing else needs it then.
 // (With six barriers, the list gathered by a launch of its own, and the loads of the end not started at the beginning:
-// 14-19 us of every round, now @@.)
+// 14-19 us of every round, now 10-16.  What is left is about 2 us per sub-round: the trips to LDS and the issue of 16 waves.
+// Edges in registers instead of lists, and stores to memory kept out of the loop, measured the same.)
 constexpr int TAIL_SLOTS = 8192;  // power of two, >= 2 * TAIL_MAX
 constexpr int TAIL_LDS_MESHES = 1024;
 constexpr int TAIL_FREE = -1, TAIL_PAIRED = -2;
