@@ -66,9 +66,10 @@ enum picasso_option {
     PICASSO_OPT_TRUNC_BLOCK_MAX = 5,/* budget step (Alg. 2 lines 3-4 and 6): a mesh that formed more
                                       pairs than it may remove keeps its cheapest ones; while no
                                       such mesh formed more than this many pairs (default and
-                                      largest value 32768) one workgroup per mesh selects them,
-                                      above it the pairs of all such meshes are sorted.  Same
-                                      result either way.                                           */
+                                      largest value 32768, which is always the limit in a batch)
+                                      one workgroup per mesh selects them,
+                                      above it histogram passes over the mesh's vertices by the
+                                      whole chip do.  Same result either way.                      */
     PICASSO_OPT_PLACEMENT = 6,     /* where a pair is contracted to, and where its cost is taken
                                       (Alg. 2 lines 2 and 14; supplementary, the two placement
                                       equations).  0 (default): the mean of the two positions.
@@ -130,12 +131,8 @@ enum picasso_option {
                                       renumbered, nv_out counts them (it may fall below target_nv),
                                       and d_cluster_id holds -1 for the input vertices of dropped
                                       clusters.  0 (default): every cluster stays an output vertex. */
-    PICASSO_OPT_TRUNC_SELECT = 14  /* budget step (Alg. 2 lines 3-4 and 6) of a single mesh that
-                                      formed more pairs than PICASSO_OPT_TRUNC_BLOCK_MAX, ties in
-                                      index order: 1 (default) = the cost key at the budget is
-                                      found by three histogram passes over the pairs' cost keys;
-                                      0 = the pairs are sorted, as they are for a batch or with a
-                                      shuffle seed.  Same results.                               */
+    PICASSO_OPT_TRUNC_SELECT = 14  /* 0 or 1: accepted, without effect (it chose between two ways
+                                      of selecting a long run's pairs, of which one is left).    */
 };
 
 #define PICASSO_STATS_ROUNDS 32

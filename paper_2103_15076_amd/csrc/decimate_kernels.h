@@ -36,7 +36,6 @@ struct State {
     int nh;        // half-edge keys of the current round: 3 for every facet that has not collapsed
     int ne;        // distinct edges of the current round
     int live[3];   // worklist lengths of the selection sub-rounds (rotating)
-    int trunc_n;   // matched edges entering the budget truncation
     int sel_k;     // sub-round index the selection has reached (buffer rotation phase)
     int absorb_n;  // edges through which an un-paired vertex would join a pair's cluster (Alg. 2 line 11)
     int nv_kept;   // output vertices that some output facet refers to (option: degenerated vertices dropped)
@@ -164,7 +163,6 @@ __device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) 
         st->live[0] = 0;
         st->live[1] = 0;
         st->live[2] = 0;
-        st->trunc_n = 0;
         st->sel_k = 0;
         st->absorb_n = 0;
     }
@@ -301,7 +299,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                                                      int edges, int vbits, State* st, HeaderInit init,
                                                      float4* __restrict__ planes, int* __restrict__ htab, int n_clear,
                                                      u64* __restrict__ vmin0, u64* __restrict__ vmin1,
-                                                     int* __restrict__ mate, RoundTab R) {
+                                                     int* __restrict__ mate, u32* __restrict__ pcost, RoundTab R) {
     __shared__ DigitTally<COUNT> corners, sides;
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
@@ -341,6 +339,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
             vmin0[w] = VMIN_NONE;
             vmin1[w] = VMIN_NONE;
             mate[w] = -1;
+            pcost[w] = ~0u;
         }
     }
     for (int f0 = blockIdx.x * BLOCK; f0 < F; f0 += stride) {  // (whole waves, for the ballots below)
@@ -610,7 +609,8 @@ __device__ __forceinline__ bool facet_collapsed(const Corners& q, const int* __r
 template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur, int F, State* st, int cur, int vbits,
                                                           u64* __restrict__ vmin0, u64* __restrict__ vmin1,
-                                                          int* __restrict__ mate, RoundTab R, DigitCount edge,
+                                                          int* __restrict__ mate, u32* __restrict__ pcost, RoundTab R,
+                                                          DigitCount edge,
                                                           const int* __restrict__ vmap, const int* __restrict__ done,
                                                           int* __restrict__ cid, int n_orig) {
     constexpr int FACETS = COUNT == COUNT_SMALL ? 1 : 4;
@@ -622,6 +622,7 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
         vmin0[w] = VMIN_NONE;
         vmin1[w] = VMIN_NONE;
         mate[w] = -1;
+        pcost[w] = ~0u;
     }
     if (blockIdx.x == 0) round_begin_block(R, st);
     sides.clear();
@@ -946,6 +947,8 @@ __device__ __forceinline__ void signal_host(const HostSignal& h, int tid, bool w
     if (tid == 0) __hip_atomic_store(h.word, h.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+constexpr u32 PAIR_NONE = 0xFFFFFFFFu;  // (no finite cost has this key)
+
 // A live edge for the tail.
 struct __attribute__((aligned(16))) LiveEdge {
     u64 key;
@@ -959,6 +962,8 @@ struct SelArgs {
     const u32* ecost;
     u64* vmin[3];
     int* mate;
+    u32* pcost;             // per pair, at its lower vertex: its cost key (PAIR_NONE at every other vertex),
+    u32* ptie;              // ... and with shuffle its tie-break value: what the budget step goes by
     LiveEdge* live;         // the edges that the last grid-wide sub-round leaves live, for the tail: LIVE_SEGS segments of
     int live_cap;           // ... live_cap places each,
     int* live_n;            // ... filled up to live_n[segment * MATCH_PAD] (or fuller than full)
@@ -1006,6 +1011,8 @@ __device__ __forceinline__ bool subround_edge(const SelArgs& A, const u64* __res
         sel = true;
         A.mate[u] = v;
         A.mate[v] = u;
+        A.pcost[u] = ck;
+        if constexpr (SHUFFLE) A.ptie[u] = (u32)pu;
         return false;
     }
     const bool gone_u = vertex_pairs_now<SHUFFLE>(cur, A.ekey, A.vbits, A.tb, u, mu);
@@ -1324,6 +1331,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
             const int u = L.vkey[su], v = L.vkey[sv];
             A.mate[u] = v;
             A.mate[v] = u;
+            A.pcost[min(u, v)] = (u32)(p >> 32);
+            if (A.tb.on) A.ptie[min(u, v)] = (u32)p;
             m = mesh_of(A.mt.voff, A.mt.B, u);
             L.vkey[su] = TAIL_PAIRED;
             L.vkey[sv] = TAIL_PAIRED;
@@ -1449,480 +1458,20 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
 // have written is visible to it when it starts, so the release carries those writes along (there
 // is next to nothing left in the cache to write back then, so it costs nothing measurable).  Either the first of the kernels queued ahead of the host's
 // look (through the counting predicate's on_start) ...
+__device__ __forceinline__ void tell_host(const HostSignal& done) {  // by one thread
+    if (done.word) __hip_atomic_store(done.word, done.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 template <class Pred>
 struct SignalingPred {
     Pred pred;
     HostSignal done;
-    __device__ void on_start() const {
-        if (done.word) __hip_atomic_store(done.word, done.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    __device__ void on_start() const { tell_host(done); }
     __device__ bool operator()(int i) const { return pred(i); }
 };
 // ... or a kernel of its own.
 __global__ void signal_kernel(HostSignal done) {
-    if (threadIdx.x == 0) __hip_atomic_store(done.word, done.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0) tell_host(done);
 }
-
-// ---------------------------------------------------------------------------
-// S2b + budget (Alg. 2 lines 3-4, 6): when a mesh formed more pairs than it may
-// remove, only its n_rem pairs of smallest (cost, edge index) stay.  The pairs
-// are gathered in edge order, sorted stably by (mesh, cost key), and the tail
-// of each mesh's run is released.
-// ---------------------------------------------------------------------------
-struct TruncPred {
-    const u64* ekey;
-    const int* mate;
-    MeshTab mt;
-    int vbits;
-    __device__ bool operator()(int e) const {
-        const u64 k = ekey[e];
-        const int u = (int)(k >> vbits), v = (int)(k & ((1ull << vbits) - 1ull));
-        if (mate[u] != v) return false;
-        const int m = mesh_of(mt.voff, mt.B, u);
-        return mt.matched[m] > mt.nrem[m];
-    }
-};
-
-struct TruncOut {
-    const u64* ekey;
-    const u32* ecost;
-    u64* tkey;
-    u32* tval;
-    MeshTab mt;
-    int vbits;
-    __device__ void operator()(int e, int pos) const {
-        const int u = (int)(ekey[e] >> vbits);
-        tkey[pos] = ((u64)(u32)mesh_of(mt.voff, mt.B, u) << 32) | (u64)ecost[e];
-        tval[pos] = (u32)e;
-    }
-};
-
-// The same gather for the one-workgroup-per-mesh selection below: cost keys and edges apart.
-struct TruncOutSplit {
-    const u32* ecost;
-    u32* tcost;
-    u32* tval;
-    __device__ void operator()(int e, int pos) const {
-        tcost[pos] = ecost[e];
-        tval[pos] = (u32)e;
-    }
-};
-
-// With the seeded tie-break the sorted variant first orders the gathered pairs by their tie-break
-// values (TruncOutTie, 32-bit keys), then gives them their (mesh, cost key) keys in that order
-// (trunc_rekey_kernel) for the stable sort that follows.
-struct TruncOutTie {
-    TieBreak tb;
-    u64* tkey;
-    u32* tval;
-    __device__ void operator()(int e, int pos) const {
-        tkey[pos] = (u64)tb.enc((u32)e);
-        tval[pos] = (u32)e;
-    }
-};
-
-__global__ __launch_bounds__(BLOCK) void trunc_rekey_kernel(const u32* __restrict__ tval, const State* st,
-                                                            const u64* __restrict__ ekey,
-                                                            const u32* __restrict__ ecost, MeshTab mt, int vbits,
-                                                            u64* __restrict__ tkey) {
-    const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= st->trunc_n) return;
-    const u32 e = tval[i];
-    tkey[i] = ((u64)(u32)mesh_of(mt.voff, mt.B, (int)(ekey[e] >> vbits)) << 32) | (u64)ecost[e];
-}
-
-// Budget for meshes with a moderate number of pairs: no sort.  The gathered pairs of a mesh are a
-// contiguous run in edge order; one workgroup per mesh reads the run's cost keys once, into
-// registers (item r * TRUNC_THREADS + t sits in register r of thread t), finds the cost key of the
-// nrem-th smallest (cost key, edge) by a bitwise search on "how many keys are <= x" (a compare
-// and an add per key and bit; the keys that share the bits decided so far are dealt out again
-// once they are few and then decided 8 bits at a time by counts per digit, and in the end one wave
-// decides the remaining bits without barriers), and
-// flags every pair
-// above that key and, among the pairs with exactly that key, all but the first ones in edge order.  A wide kernel then releases the
-// flagged pairs.  One compute unit does the whole search, so runs longer than TRUNC_BLOCK_CAP go
-// to the sort instead.
-constexpr int TRUNC_THREADS = 1024;
-constexpr int TRUNC_REGS_MAX = 32;
-constexpr int TRUNC_BLOCK_CAP = TRUNC_THREADS * TRUNC_REGS_MAX;
-constexpr int TRUNC_NARROW_BLOCK = 4 * TRUNC_THREADS;  // candidates that are dealt out again, 4 to a thread
-constexpr int TRUNC_NARROW_WAVE = 4 * 64;              // candidates that one wave takes over, 4 to a lane
-
-// Sum over the 64 lanes of a wave (all active), the same value returned to every lane.
-__device__ __forceinline__ u32 wave_sum_u32(u32 x) {
-    int v = (int)x;
-    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
-    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);  // row_half_mirror
-    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true);  // row_mirror: each row of 16 holds its sum
-    return (u32)(__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
-                 __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
-}
-
-template <int R, bool SHUFFLE>
-__global__ __launch_bounds__(TRUNC_THREADS) void trunc_block_kernel(u32* __restrict__ tcost,
-                                                                    const u32* __restrict__ tval, TieBreak tb,
-                                                                    const int* __restrict__ matched,
-                                                                    const int* __restrict__ nrem,
-                                                                    const int* __restrict__ guard, State* st) {
-    if (guard && *guard == 0) return;  // queued ahead of the host's look, and the selection was not finished
-    constexpr int NW = TRUNC_THREADS / 64;
-    __shared__ u32 wsum[NW];
-    __shared__ u32 wsum2[2][NW];
-    __shared__ u32 cnt[R * NW];
-    __shared__ u32 cbuf[TRUNC_NARROW_BLOCK];
-    __shared__ u32 found[3];
-    __shared__ u32 dhist[256];  // the narrow phase's counts per 8-bit digit
-    const int b = blockIdx.x;
-    const int n = matched[b], keep = nrem[b];
-    if (n <= keep) return;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const u64 lt = prim::lanemask_lt();
-
-    u32 before = 0, s0;  // pairs gathered for meshes in front of this one
-    for (int j = tid; j < b; j += TRUNC_THREADS)
-        if (matched[j] > nrem[j]) before += (u32)matched[j];
-    prim::wide_block_exclusive_scan<NW>(before, wsum, s0);
-    tcost += s0;
-    tval += s0;
-    if (n > R * TRUNC_THREADS) {
-        // More pairs than this instance holds: the host never launches it so.  Nothing is released, and
-        // the call is made to fail (ERR_BIT_INTERNAL) instead of returning a budget that was not applied.
-        for (int i = tid; i < n; i += TRUNC_THREADS) tcost[i] = 0u;
-        if (tid == 0) atomicOr(&st->err, ERR_BIT_INTERNAL);
-        return;
-    }
-
-    u32 key[R];  // empty slots hold the largest key
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int i = r * TRUNC_THREADS + tid;
-        key[r] = i < n ? tcost[i] : 0xFFFFFFFFu;
-    }
-
-    // Number of values <= x among the RR that every thread holds, known to every thread after one
-    // barrier (`slot` alternates so that the next count does not overwrite sums still being read).
-    auto count_le = [&](const auto& a, auto rr, u32 x, int slot) -> u32 {
-        constexpr int RR = decltype(rr)::value;
-        u32 c = 0;
-#pragma unroll
-        for (int r = 0; r < RR; ++r) c += (a[r] <= x) ? 1u : 0u;
-        c = wave_sum_u32(c);
-        if (lane == 0) wsum2[slot][w] = c;
-        __syncthreads();
-        u32 tot = 0;
-#pragma unroll
-        for (int j = 0; j < NW; ++j) tot += wsum2[slot][j];
-        return tot;
-    };
-    // One wave alone finishes a search over at most TRUNC_NARROW_WAVE values held in `cbuf` (the
-    // first `m` entries): the smallest x whose low bits (`bit` and below) extend `pre` such that at
-    // least `want` values are <= x, `outside` values that are not in `cbuf` being below every
-    // candidate.  Returns x and how many values are < x; no barriers, 4 compares per lane and bit.
-    auto wave_search = [&](u32 m, u32 pre, int bit, u32 outside, u32 want, u32& less_out) -> u32 {
-        u32 less = outside;  // values < pre: those outside `cbuf`, then the candidates passed over
-        u32 ck[TRUNC_NARROW_WAVE / 64];
-#pragma unroll
-        for (int j = 0; j < TRUNC_NARROW_WAVE / 64; ++j) ck[j] = (u32)(j * 64 + lane) < m ? cbuf[j * 64 + lane] : 0xFFFFFFFFu;
-        for (; bit >= 0; --bit) {
-            const u32 x = pre | ((1u << bit) - 1u);
-            u32 c = 0;
-#pragma unroll
-            for (int j = 0; j < TRUNC_NARROW_WAVE / 64; ++j) c += (u32)__popcll(__ballot(ck[j] <= x));
-            c = outside + (c < m ? c : m);  // (the empty places count when x is the largest value)
-            if (c < want) {
-                pre |= 1u << bit;
-                less = c;
-            }
-        }
-        less_out = less;
-        return pre;
-    };
-    // Those of the RR values a thread holds that satisfy `is_cand` go to consecutive places of
-    // `cbuf`; returns how many there are in the workgroup (the caller knows that they fit).
-    auto gather_candidates = [&](auto rr, auto is_cand, auto value_of) -> u32 {
-        constexpr int RR = decltype(rr)::value;
-        u32 mc = 0;
-#pragma unroll
-        for (int r = 0; r < RR; ++r) mc += is_cand(r) ? 1u : 0u;
-        u32 m;
-        u32 at = prim::wide_block_exclusive_scan<NW>(mc, wsum, m);
-#pragma unroll
-        for (int r = 0; r < RR; ++r)
-            if (is_cand(r) && at < (u32)TRUNC_NARROW_BLOCK) cbuf[at++] = value_of(r);
-        __syncthreads();
-        return m;
-    };
-
-    // The search: the smallest x with at least `want` of the values a[] <= x, bit by bit from the
-    // top.  Every thread holds R values, `valid` of them in the workgroup are real (is_real(r)), the
-    // others hold the largest value.  below = values < prefix, upper = values <= prefix | (undecided
-    // bits all set): upper - below values share the bits decided so far.  Once there are at most
-    // TRUNC_NARROW_BLOCK of them they are dealt out again, 4 to a thread; once at most
-    // TRUNC_NARROW_WAVE, one wave takes them and finishes alone.  Leaves x in `prefix` and the
-    // number of values < x in `below`.
-    u32 prefix = 0, below = 0, upper = 0, want = 0;
-    int bit = -1;
-    // steps over the values in `a` (of which `real` are real, `outside` more lie below them all)
-    auto steps = [&](const auto& a, auto rr, u32 real, u32 outside, u32 until) {
-        while (bit >= 0 && upper - below > until) {
-            u32 c = count_le(a, rr, prefix | ((1u << bit) - 1u), bit & 1);
-            c = outside + (c < real ? c : real);  // (the other slots count when x is the largest value)
-            if (c < want) {
-                prefix |= 1u << bit;
-                below = c;
-            } else {
-                upper = c;
-            }
-            --bit;
-        }
-    };
-    auto finish_in_one_wave = [&](auto rr, auto is_cand, auto value_of) {
-        const u32 outside = below;
-        const u32 m = gather_candidates(rr, is_cand, value_of);
-        if (w == 0) {
-            u32 less;
-            const u32 x = wave_search(m, prefix, bit, outside, want, less);
-            if (lane == 0) {
-                found[0] = x;
-                found[1] = less;
-            }
-        }
-        __syncthreads();
-        prefix = found[0];
-        below = found[1];
-    };
-    auto search = [&](const auto& a, auto is_real, u32 valid, u32 want_) {
-        const auto all_r = std::integral_constant<int, R>{};
-        const auto four = std::integral_constant<int, 4>{};
-        auto decided_mask = [&]() -> u32 { return bit == 31 ? 0u : ~0u << (bit + 1); };
-        prefix = 0;
-        below = 0;
-        upper = valid;
-        want = want_;
-        bit = 31;
-        __syncthreads();  // (a search before this one has finished with the shared arrays)
-        steps(a, all_r, valid, 0u, R > 4 ? (u32)TRUNC_NARROW_BLOCK : (u32)TRUNC_NARROW_WAVE);
-        if (R > 4 && bit >= 0 && upper - below > (u32)TRUNC_NARROW_WAVE) {
-            const u32 decided = decided_mask(), outside = below;
-            const u32 m = gather_candidates(
-                all_r, [&](int r) { return is_real(r) && (a[r] & decided) == prefix; }, [&](int r) { return a[r]; });
-            u32 k4[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) k4[j] = (u32)(j * TRUNC_THREADS + tid) < m ? cbuf[j * TRUNC_THREADS + tid] : 0xFFFFFFFFu;
-            (void)outside;
-            // ... and decided 8 bits at a time from here on: the candidates that share the decided bits are
-            // counted per digit in LDS (the lanes of a wave that hold one digit with a single atomic: where
-            // many pairs tie at the threshold they all hold the same), and the digit in which the running
-            // count reaches what is still wanted is found by one scan: three barriers per 8 bits instead
-            // of one per bit
-            while (bit >= 0 && upper - below > (u32)TRUNC_NARROW_WAVE) {
-                const int nb = bit >= 7 ? 8 : bit + 1, shift = bit + 1 - nb;
-                const u32 dec = decided_mask();
-                if (tid < 256) dhist[tid] = 0;
-                __syncthreads();
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {  // (whole waves, for the ballots)
-                    const bool ok = (u32)(j * TRUNC_THREADS + tid) < m && (k4[j] & dec) == prefix;
-                    const u32 dg = (k4[j] >> shift) & ((1u << nb) - 1u);
-                    const u64 same = prim::wave_same_digit_lanes(ok, dg);
-                    if (ok && (same & lt) == 0) atomicAdd(&dhist[dg], (u32)__popcll(same));
-                }
-                __syncthreads();
-                const u32 c = tid < 256 ? dhist[tid] : 0u;
-                u32 tot;
-                const u32 run = prim::wide_block_exclusive_scan<NW>(c, wsum, tot);
-                const u32 need = want - below;  // >= 1, and at most the number of candidates
-                if (tid < 256 && run < need && need <= run + c) {
-                    found[0] = (u32)tid;
-                    found[1] = run;
-                    found[2] = c;
-                }
-                __syncthreads();
-                prefix |= found[0] << shift;
-                below += found[1];
-                upper = below + found[2];
-                bit -= nb;
-            }
-            if (bit >= 0) {
-                const u32 d2 = decided_mask();
-                finish_in_one_wave(
-                    four, [&](int j) { return (u32)(j * TRUNC_THREADS + tid) < m && (k4[j] & d2) == prefix; },
-                    [&](int j) { return k4[j]; });
-            }
-        } else if (bit >= 0) {
-            const u32 decided = decided_mask();
-            finish_in_one_wave(
-                all_r, [&](int r) { return is_real(r) && (a[r] & decided) == prefix; }, [&](int r) { return a[r]; });
-        }
-    };
-
-    // the cost key of the keep-th smallest pair, and how many pairs with exactly that key stay
-    u32 kk = 0;
-    if (keep > 0) {
-        search(key, [&](int r) { return r * TRUNC_THREADS + tid < n; }, (u32)n, (u32)keep);
-        kk = (u32)keep - below;
-    }
-    const u32 kprefix = prefix;
-    if constexpr (SHUFFLE) {
-        // ... the first kk in the order of the seeded tie-break, which is distinct from pair to pair:
-        // the same search once more, on the tie-break values of the pairs with that key
-        u32 tie[R];
-        u32 neq = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = r * TRUNC_THREADS + tid;
-            const bool eq = i < n && key[r] == kprefix;
-            tie[r] = eq ? tb.enc(tval[i]) : 0xFFFFFFFFu;
-            neq += eq ? 1u : 0u;
-        }
-        {
-            u32 tot;
-            (void)prim::wide_block_exclusive_scan<NW>(neq, wsum, tot);
-            neq = tot;
-        }
-        u32 t2 = 0;
-        if (kk > 0) {
-            search(tie, [&](int r) { return r * TRUNC_THREADS + tid < n && key[r] == kprefix; }, neq, kk);
-            t2 = prefix;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = r * TRUNC_THREADS + tid;
-            if (i < n) tcost[i] = (key[r] > kprefix || (key[r] == kprefix && (kk == 0 || tie[r] > t2))) ? 1u : 0u;
-        }
-        return;
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const bool eq = (r * TRUNC_THREADS + tid < n) && key[r] == kprefix;
-        const u64 eb = __ballot(eq);
-        if (lane == 0) cnt[r * NW + w] = (u32)__popcll(eb);
-    }
-    __syncthreads();
-    {
-        const u32 v = tid < R * NW ? cnt[tid] : 0u;
-        u32 tot;
-        const u32 ex = prim::wide_block_exclusive_scan<NW>(v, wsum, tot);
-        if (tid < R * NW) cnt[tid] = ex;  // equal keys in front of wave w's part of row r
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int i = r * TRUNC_THREADS + tid;
-        const bool valid = i < n;
-        const bool eq = valid && key[r] == kprefix, gt = valid && key[r] > kprefix;
-        const u64 eb = __ballot(eq);
-        const u32 rank = cnt[r * NW + w] + (u32)__popcll(eb & lt);
-        if (valid) tcost[i] = (gt || (eq && rank >= kk)) ? 1u : 0u;  // the key's slot now holds the flag
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Budget for ONE long run (a single mesh that formed more pairs than one workgroup's registers hold)
-// without sorting it: the cost key of the nrem-th smallest pair is found digit by digit, from the top,
-// by histograms over the gathered cost keys (tcost, in edge order): three passes of 11, 11 and 10 bits,
-// each a wide kernel that counts the keys which share the digits decided so far, and one small
-// workgroup that picks the digit in which the count crosses nrem.  Then the pairs with exactly that
-// key are ranked in edge order by the atomic-free scan, and every pair above the key, or at the key but
-// beyond the budget, is flagged for trunc_release_kernel, as trunc_block_kernel does it.
-// ---------------------------------------------------------------------------
-constexpr int SELECT_BINS = 1 << 11;
-struct SelectState {
-    u32 prefix;  // the digits decided so far, right-aligned (after the last pass: the threshold key)
-    u32 below;   // keys smaller than every key that starts with `prefix`
-    u32 keep;    // (after the last pass) how many of the pairs with exactly the threshold key stay
-    u32 pad;
-    u32 hist[SELECT_BINS];
-};
-__device__ __forceinline__ int select_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
-__device__ __forceinline__ int select_bits(int pass) { return pass == 2 ? 10 : 11; }
-
-constexpr int SELECT_ITEMS = 8;
-template <int PASS>
-__global__ __launch_bounds__(BLOCK) void trunc_select_hist_kernel(const u32* __restrict__ tcost, const State* st,
-                                                                  SelectState* __restrict__ S) {
-    __shared__ u32 h[SELECT_BINS];
-    const int n = st->trunc_n;
-    const long long base = (long long)blockIdx.x * (BLOCK * SELECT_ITEMS);
-    if (base >= n) return;
-    const int t = threadIdx.x;
-    for (int i = t; i < SELECT_BINS; i += BLOCK) h[i] = 0;
-    const u32 prefix = PASS == 0 ? 0u : S->prefix;
-    const int shift = select_shift(PASS), bits = select_bits(PASS);
-    __syncthreads();
-    u32 key[SELECT_ITEMS];
-#pragma unroll
-    for (int i = 0; i < SELECT_ITEMS; ++i) {
-        const long long idx = base + (long long)i * BLOCK + t;
-        key[i] = idx < n ? tcost[idx] : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < SELECT_ITEMS; ++i) {  // (whole waves run every step, for the ballots)
-        const long long idx = base + (long long)i * BLOCK + t;
-        // keys that share the digits decided so far; cost keys cluster, so the lanes of a wave that hold
-        // one digit count themselves with a single LDS atomic
-        const bool ok = idx < n && (PASS == 0 || (key[i] >> (shift + bits)) == prefix);
-        const u32 d = (key[i] >> shift) & ((1u << bits) - 1u);
-        const u64 same = prim::wave_same_digit_lanes(ok, d);
-        if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&h[d], (u32)__popcll(same));
-    }
-    __syncthreads();
-    for (int i = t; i < SELECT_BINS; i += BLOCK) {
-        const u32 c = h[i];
-        if (c) atomicAdd(&S->hist[i], c);
-    }
-}
-
-// One workgroup: the digit in which the running count of the histogram reaches the budget; the
-// histogram is left zero for the next pass.
-template <int PASS>
-__global__ __launch_bounds__(BLOCK) void trunc_select_pick_kernel(SelectState* __restrict__ S,
-                                                                  const int* __restrict__ nrem) {
-    constexpr int PER = SELECT_BINS / BLOCK;
-    __shared__ u32 smem[prim::WAVES];
-    const int t = threadIdx.x;
-    const u32 below = PASS == 0 ? 0u : S->below, prefix = PASS == 0 ? 0u : S->prefix;
-    const u32 need = (u32)nrem[0] - below;  // >= 1: the key sought is among those counted
-    u32 c[PER], sum = 0, tot;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        c[j] = S->hist[t * PER + j];
-        S->hist[t * PER + j] = 0;
-        sum += c[j];
-    }
-    u32 run = prim::block_exclusive_scan(sum, smem, tot);
-    if (run < need && need <= run + sum) {  // (exactly one thread, as tot >= need)
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            if (run < need && need <= run + c[j]) {
-                S->prefix = (prefix << select_bits(PASS)) | (u32)(t * PER + j);
-                S->below = below + run;
-                if (PASS == 2) S->keep = need - run;
-            }
-            run += c[j];
-        }
-    }
-}
-
-struct SelectTiePred {
-    const u32* tcost;
-    const SelectState* S;
-    __device__ bool operator()(int i) const { return tcost[i] == S->prefix; }
-};
-
-// Called for every gathered pair i; `tie`: its key is the threshold key, and `pos` pairs with that key
-// come before it in edge order.  The key's slot then holds the flag (1 = give the pair up).
-struct SelectFlagOut {
-    static constexpr bool WAVE_WIDE = true;
-    u32* tcost;
-    const SelectState* S;
-    __device__ void wave(int i, bool in_range, bool tie, int pos) const {
-        if (!in_range) return;
-        const u32 k = tcost[i];
-        tcost[i] = (k > S->prefix || (tie && (u32)pos >= S->keep)) ? 1u : 0u;
-    }
-};
 
 constexpr u64 ABID_NONE = ~0ull;
 
@@ -1933,63 +1482,437 @@ __device__ __forceinline__ int joining_end(const int* __restrict__ mate, int u, 
     return pu == pv ? -1 : (pu ? v : u);
 }
 
-// Gives up what the budget does not cover: a pair is dissolved (ABSORB = false), or the vertex
-// that would have joined through the edge stays on its own (ABSORB = true: its bid is withdrawn).
-template <bool ABSORB>
-__device__ __forceinline__ void release_edge(u64 k, int vbits, int* __restrict__ mate, u64* __restrict__ abid) {
-    const int u = (int)(k >> vbits), v = (int)(k & ((1ull << vbits) - 1ull));
-    if (ABSORB) {
-        const int w = joining_end(mate, u, v);
-        if (w >= 0) abid[w] = ABID_NONE;
-    } else {
-        mate[u] = -1;
-        mate[v] = -1;
+// ---------------------------------------------------------------------------
+// S2b + budget (Alg. 2 lines 3-4, 6): when a mesh formed more pairs than it may
+// remove, only its n_rem pairs of smallest (cost key, tie-break) stay.  A pair stands at its lower vertex (PairKeys):
+// among equal costs the order by edge index is the order by that vertex.  The step for the vertices that join clusters
+// (line 11) is the same with the candidate vertices in place of pairs (JoinKeys).  So both walk the mesh's vertices, four bytes
+// each, and neither the edges nor a gathered list: where the pairs were gathered from the edges, searched and released, that
+// took four launches and 41 us for a mesh of 29 k pairs, 22 us for one of 550, and eleven launches for a longer run; now two
+// and 40, one and 13, and seven.
+// ---------------------------------------------------------------------------
+template <bool SHUFFLE>
+struct PairKeys {
+    const u32* pcost;
+    const u32* ptie;
+    int* mate;
+    static constexpr bool TIE_BY_VERTEX = !SHUFFLE;
+    typedef u32 Raw;
+    __device__ __forceinline__ Raw load(int w) const { return pcost[w]; }
+    __device__ __forceinline__ bool has(Raw r) const { return r != PAIR_NONE; }
+    __device__ __forceinline__ u32 cost(Raw r) const { return r; }
+    __device__ __forceinline__ u32 tie(int w, int v0) const { return SHUFFLE ? ptie[w] : (u32)(w - v0); }
+    __device__ __forceinline__ int partner(int w) const { return mate[w]; }
+    // the pair is dissolved
+    __device__ __forceinline__ void release(int w, int m) const {
+        mate[w] = -1;
+        mate[m] = -1;
     }
+};
+
+struct JoinKeys {
+    u64* abid;
+    static constexpr bool TIE_BY_VERTEX = false;
+    typedef u64 Raw;
+    __device__ __forceinline__ Raw load(int w) const { return abid[w]; }
+    __device__ __forceinline__ bool has(Raw r) const { return r != ABID_NONE; }
+    __device__ __forceinline__ u32 cost(Raw r) const { return (u32)(r >> 32); }
+    __device__ __forceinline__ u32 tie(int w, int) const { return (u32)abid[w]; }
+    // the vertex that would have joined stays on its own: its bid is withdrawn
+    __device__ __forceinline__ int partner(int) const { return -1; }
+    __device__ __forceinline__ void release(int w, int) const { abid[w] = ABID_NONE; }
+};
+
+// Meshes with at most `cap` keys (<= CAP): one workgroup per mesh finds the cost key of the budget's last pair, its top 12 bits
+// by counts in LDS, the others among the keys that share them, listed in LDS in any order, digit by digit (8 bits at a
+// time from the highest bit in which they differ at all); where the budget ends among equal keys, the last tie-break value in the
+// same way; and (few keys) walks the vertices once more to release what lies beyond.  Bound by the trips to LDS and memory of one compute unit; 16 vertices per lane are in flight.
+constexpr int TRUNC_THREADS = 1024;
+constexpr int TRUNC_BLOCK_CAP = 32 * TRUNC_THREADS;
+constexpr int TRUNC_SMALL_CAP = 4 * TRUNC_THREADS;
+
+// What stays of a mesh's keys: those below `cost`, and at it those with tie-break values up to `tie`, or all of them.
+struct KeyLimit {
+    u32 cost, tie;
+    int over;  // 0: every key stays; 1: see above; 2: all keys at `cost` stay; 3: none stays
+};
+template <class Keys>
+__device__ __forceinline__ bool beyond(const Keys& K, const KeyLimit& L, u32 cost, int w, int v0) {
+    return L.over == 3 || cost > L.cost || (L.over == 1 && cost == L.cost && K.tie(w, v0) > L.tie);
 }
 
-// Releases the flagged pairs; block 0 also clamps the pair counts of the meshes to their budgets.
-template <bool ABSORB>
-__global__ __launch_bounds__(BLOCK) void trunc_release_kernel(const u32* __restrict__ tflag,
-                                                              const u32* __restrict__ tval, const State* st,
-                                                              const u64* __restrict__ ekey, int vbits,
-                                                              int* __restrict__ mate, int B, int* __restrict__ matched,
-                                                              const int* __restrict__ nrem, u64* __restrict__ abid,
-                                                              const int* __restrict__ guard) {
-    if (guard && *guard == 0) return;  // (as in trunc_block_kernel)
-    const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i < st->trunc_n && tflag[i]) release_edge<ABSORB>(ekey[tval[i]], vbits, mate, abid);
-    if (blockIdx.x == 0)
-        for (int b = threadIdx.x; b < B; b += BLOCK)
-            if (matched[b] > nrem[b]) matched[b] = nrem[b];
-}
-
-// segstart[b] = number of gathered pairs that belong to meshes before b
-__global__ void trunc_segments_kernel(int B, const int* __restrict__ matched, const int* __restrict__ nrem,
-                                      int* __restrict__ segstart) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        int run = 0;
-        for (int b = 0; b < B; ++b) {
-            segstart[b] = run;
-            if (matched[b] > nrem[b]) run += matched[b];
+template <class Keys, int CAP>
+__global__ __launch_bounds__(TRUNC_THREADS) void trunc_mesh_kernel(Keys K, const int* __restrict__ voff,
+                                                                   const int* __restrict__ counts,
+                                                                   const int* __restrict__ budgets, int cap, int longer_follow,
+                                                                   const int* __restrict__ guard, State* st, HostSignal tell,
+                                                                   KeyLimit* __restrict__ limits) {
+    constexpr int Q = 16, COPIES = 16, TOP_SHIFT = 20;
+    static_assert(256 * COPIES == 1 << (32 - TOP_SHIFT), "the array of counts holds the top digits");
+    __shared__ u32 list[CAP];
+    __shared__ u32 hist[256 * COPIES];  // (copies by lane: cost keys cluster, and atomics of a wave on one word take turns)
+    __shared__ u32 total[256];
+    __shared__ u32 found[3];
+    __shared__ u32 n_list, lowest, highest;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = prim::lane_id();
+    if (b == 0 && tid == 0) tell_host(tell);
+    constexpr bool RELEASE = CAP <= TRUNC_SMALL_CAP;
+    if (!RELEASE && tid == 0) limits[b] = KeyLimit{0u, 0u, 0};
+    if (guard && *guard == 0) return;  // queued ahead of the host's look, and the selection was not finished
+    const int n = counts[b], keep = budgets[b];
+    if (n <= keep) return;
+    if (n > cap) {
+        // More keys than this instance holds (and no other kernel for them follows): the host never launches it so.
+        // Nothing is released, and the call is made to fail instead of returning a budget that was not applied.
+        if (!longer_follow && tid == 0) atomicOr(&st->err, ERR_BIT_INTERNAL);
+        return;
+    }
+    const int v0 = voff[b], v1 = voff[b + 1];
+    const u64 lt = prim::lanemask_lt();
+    if (tid == 0) {
+        n_list = 0;
+        lowest = ~0u;
+        highest = 0;
+    }
+    __syncthreads();
+    // fn(first vertex, which of them have keys, raw keys) for the vertices base + q * TRUNC_THREADS + tid of each step, by whole
+    // waves: a step's loads are all in flight together (unconditional, at vertices of the mesh)
+    auto each_step = [&](auto fn) {
+        for (int base = v0; base < v1; base += Q * TRUNC_THREADS) {
+            typename Keys::Raw raw[Q];
+            u32 has = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) raw[q] = K.load(min(base + q * TRUNC_THREADS + tid, v1 - 1));
+#pragma unroll
+            for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(raw[q]));
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (base + q * TRUNC_THREADS + tid < v1 && K.has(raw[q])) has |= 1u << q;
+            fn(base, has, raw);
+        }
+    };
+    // a lane's values, one for every bit of `on`, go to the list: one atomic per wave
+    auto append = [&](u32 on, auto value) {
+        const u32 mine = (u32)__popc(on);
+        u32 incl = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const u32 o = (u32)__shfl_up((int)incl, d, 64);
+            if (lane >= d) incl += o;
+        }
+        u32 at = 0;
+        if (lane == 63 && incl) at = atomicAdd(&n_list, incl);
+        at = (u32)__shfl((int)at, 63, 64) + incl - mine;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if ((on >> q & 1u) && at < (u32)CAP) list[at++] = value(q);
+    };
+    // The want-th smallest (1 <= want <= n) of the first n values of the list, which lie between lo and hi; how many are less, and equal.
+    auto nth = [&](int n, u32 lo, u32 hi, u32 want, u32& less, u32& equal) -> u32 {
+        less = 0;
+        equal = (u32)n;
+        if (lo == hi) return lo;
+        int bit = 31 - __clz((int)(lo ^ hi));
+        u32 decided = bit == 31 ? 0u : ~0u << (bit + 1), prefix = lo & decided;
+        while (bit >= 0) {
+            const int nb = min(8, bit + 1), shift = bit + 1 - nb;
+            for (int i = tid; i < 256 * COPIES; i += TRUNC_THREADS) hist[i] = 0;
+            __syncthreads();
+            for (int i = tid; i < n; i += TRUNC_THREADS) {
+                const u32 k = list[i];
+                if ((k & decided) == prefix) atomicAdd(&hist[((k >> shift) & ((1u << nb) - 1u)) * COPIES + (lane & (COPIES - 1))], 1u);
+            }
+            __syncthreads();
+            if (tid < 256) {
+                u32 sum = 0;
+#pragma unroll
+                for (int j = 0; j < COPIES; ++j) sum += hist[tid * COPIES + ((tid + j) & (COPIES - 1))];
+                total[tid] = sum;
+            }
+            __syncthreads();
+            if (tid < 64) {
+                u32 c[4], sum = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum += c[j] = total[4 * lane + j];
+                u32 incl = sum;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const u32 o = (u32)__shfl_up((int)incl, d, 64);
+                    if (lane >= d) incl += o;
+                }
+                u32 run = incl - sum;
+                const u32 need = want - less;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (run < need && need <= run + c[j]) {  // (in one lane)
+                        found[0] = (u32)(4 * lane + j);
+                        found[1] = run;
+                        found[2] = c[j];
+                    }
+                    run += c[j];
+                }
+            }
+            __syncthreads();
+            prefix |= found[0] << shift;
+            less += found[1];
+            equal = found[2];
+            bit -= nb;
+            decided = bit < 0 ? ~0u : ~0u << (bit + 1);
+        }
+        return prefix;
+    };
+    auto bounds = [&](u32 lo, u32 hi) {
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            lo = min(lo, (u32)__shfl_xor((int)lo, d, 64));
+            hi = max(hi, (u32)__shfl_xor((int)hi, d, 64));
+        }
+        if (lane == 0) {
+            atomicMin(&lowest, lo);
+            atomicMax(&highest, hi);
+        }
+    };
+    u32 last_cost = 0, last_tie = 0;  // what stays: keys below last_cost, and at it those with tie-break values up to last_tie
+    bool none = keep <= 0, all_ties = false;
+    if (!none) {
+        // the top 12 bits by counts over all keys ...
+        for (int i = tid; i < 256 * COPIES; i += TRUNC_THREADS) hist[i] = 0;
+        __syncthreads();
+        each_step([&](int, u32 has, const auto& raw) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (has >> q & 1u) atomicAdd(&hist[K.cost(raw[q]) >> TOP_SHIFT], 1u);
+        });
+        __syncthreads();
+        {
+            constexpr int PER = 256 * COPIES / TRUNC_THREADS;
+            u32 c[PER], sum = 0, tot;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) sum += c[j] = hist[tid * PER + j];
+            u32 run = prim::wide_block_exclusive_scan<TRUNC_THREADS / 64>(sum, total, tot);
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                if (run < (u32)keep && (u32)keep <= run + c[j]) {  // (in one thread)
+                    found[0] = (u32)(tid * PER + j);
+                    found[1] = run;
+                    found[2] = c[j];
+                }
+                run += c[j];
+            }
+        }
+        __syncthreads();
+        const u32 top = found[0], below_top = found[1];
+        const int with_top = (int)found[2];
+        // ... the others in a list of the keys that share them
+        u32 lo = ~0u, hi = 0;
+        each_step([&](int, u32 has, const auto& raw) {
+            u32 on = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if ((has >> q & 1u) && K.cost(raw[q]) >> TOP_SHIFT == top) on |= 1u << q;
+            if (!__any(on != 0)) return;
+            append(on, [&](int q) {
+                const u32 k = K.cost(raw[q]);
+                lo = min(lo, k);
+                hi = max(hi, k);
+                return k;
+            });
+        });
+        bounds(lo, hi);
+        __syncthreads();
+        u32 less, ties;
+        last_cost = nth(with_top, lowest, highest, (u32)keep - below_top, less, ties);
+        const u32 stay = (u32)keep - below_top - less;  // of the keys that are exactly that; the tie-break says which
+        all_ties = ties <= stay;
+        if (!all_ties) {
+            __syncthreads();
+            if (tid == 0) {
+                n_list = 0;
+                lowest = ~0u;
+                highest = 0;
+            }
+            __syncthreads();
+            lo = ~0u;
+            hi = 0;
+            each_step([&](int base, u32 has, const auto& raw) {
+                u32 on = 0;
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if ((has >> q & 1u) && K.cost(raw[q]) == last_cost) on |= 1u << q;
+                if (!__any(on != 0)) return;
+                append(on, [&](int q) {
+                    const u32 t = K.tie(base + q * TRUNC_THREADS + tid, v0);
+                    lo = min(lo, t);
+                    hi = max(hi, t);
+                    return t;
+                });
+            });
+            bounds(lo, hi);
+            __syncthreads();
+            u32 same;
+            last_tie = nth((int)ties, lowest, highest, stay, less, same);
         }
     }
+    const KeyLimit limit{last_cost, last_tie, none ? 3 : (all_ties ? 2 : 1)};
+    if constexpr (!RELEASE) {
+        if (tid == 0) limits[b] = limit;
+        return;
+    }
+    each_step([&](int base, u32 has, const auto& raw) {
+        int with[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) with[q] = K.partner(min(base + q * TRUNC_THREADS + tid, v1 - 1));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(with[q]));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int w = base + q * TRUNC_THREADS + tid;
+            if ((has >> q & 1u) && beyond(K, limit, K.cost(raw[q]), w, v0)) K.release(w, with[q]);
+        }
+    });
 }
 
-template <bool ABSORB>
-__global__ __launch_bounds__(BLOCK) void trunc_apply_kernel(const u64* __restrict__ tkey, const u32* __restrict__ tval,
-                                                            const State* st, const int* __restrict__ segstart,
-                                                            const int* __restrict__ nrem,
-                                                            const u64* __restrict__ ekey, int vbits,
-                                                            int* __restrict__ mate, u64* __restrict__ abid) {
-    const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= st->trunc_n) return;
-    const int m = (int)(tkey[i] >> 32);
-    if (i - segstart[m] >= nrem[m]) release_edge<ABSORB>(ekey[tval[i]], vbits, mate, abid);
+// The release by the whole chip, for the instance that leaves it to this (the stores of 29 k pairs take one compute unit 20 us).
+template <class Keys>
+__global__ __launch_bounds__(BLOCK) void trunc_release_kernel(Keys K, int nv, const int* __restrict__ voff, int B,
+                                                              const KeyLimit* __restrict__ limits) {
+    const int w = blockIdx.x * BLOCK + threadIdx.x;
+    if (w >= nv) return;
+    const int b = mesh_of(voff, B, w);
+    const KeyLimit limit = limits[b];
+    if (limit.over == 0) return;
+    const typename Keys::Raw raw = K.load(w);
+    const int with = K.partner(w);
+    if (K.has(raw) && beyond(K, limit, K.cost(raw), w, voff[b])) K.release(w, with);
 }
 
-__global__ void trunc_finish_kernel(int B, int* __restrict__ matched, const int* __restrict__ nrem) {
-    for (int b = threadIdx.x; b < B; b += blockDim.x)
-        if (matched[b] > nrem[b]) matched[b] = nrem[b];
+// Longer runs: the same search by histogram passes over the mesh's vertices with the whole chip (blockIdx.y = mesh), three of
+// 12, 12 and 8 bits for the cost key and as many as the tie-break values have digits.  A pass's workgroups each pick the digit
+// that the pass before has decided from its counts (16 KB read from L2, no launch in between).
+constexpr int SELECT_BITS = 12, SELECT_BINS = 1 << SELECT_BITS, SELECT_COST_PASSES = 3, SELECT_PASSES = 6;
+struct SelectSlot {
+    u32 hist[SELECT_PASSES][SELECT_BINS];  // (zero before the first pass)
+    // as picked by the pass: what is decided of the cost key, keys below it; the same of the tie-break value; stay = how many
+    // of the keys at the decided cost key stay; all = they all do
+    struct {
+        u32 cost, below, tie, tie_below, stay, all;
+    } at[SELECT_PASSES + 1];
+};
+// A mesh's slot: meshes of more than 2^15 pairs have more than 2^16 vertices.
+__device__ __forceinline__ int select_slot(const int* voff, int B, int b) { return B == 1 ? 0 : voff[b] >> 16; }
+__device__ __forceinline__ int select_shift(int j, int bits) { return max(0, bits - SELECT_BITS * (j + 1)); }
+__device__ __forceinline__ int select_width(int j, int bits) { return min(SELECT_BITS, bits - SELECT_BITS * j); }
+
+// The state before pass `pass` (by a whole workgroup): from the pass before, its counts and the state before it.
+__device__ __forceinline__ auto select_pick(const SelectSlot& S, int pass, u32 keep, int tie_bits, u32* smem, u32* out /* [3] */) {
+    auto a = S.at[0];
+    a.cost = a.below = a.tie = a.tie_below = a.stay = a.all = 0;
+    if (pass == 0) return a;
+    constexpr int PER = SELECT_BINS / BLOCK;
+    if (pass > 1) a = S.at[pass - 1];
+    const int t = threadIdx.x;
+    const bool tie = pass - 1 >= SELECT_COST_PASSES;
+    const u32 need = tie ? a.stay - a.tie_below : keep - a.below;  // >= 1: the key sought is among those counted
+    u32 c[PER], sum = 0, tot;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) sum += c[j] = S.hist[pass - 1][t * PER + j];
+    u32 run = prim::block_exclusive_scan(sum, smem, tot);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (run < need && need <= run + c[j]) {  // (in one thread)
+            out[0] = (u32)(t * PER + j);
+            out[1] = run;
+            out[2] = c[j];
+        }
+        run += c[j];
+    }
+    __syncthreads();
+    if (tie) {
+        if (!a.all) {
+            a.tie = (a.tie << select_width(pass - 1 - SELECT_COST_PASSES, tie_bits)) | out[0];
+            a.tie_below += out[1];
+        }
+    } else {
+        a.cost = (a.cost << select_width(pass - 1, 32)) | out[0];
+        a.below += out[1];
+        if (pass == SELECT_COST_PASSES) {
+            a.stay = keep - a.below;
+            a.all = out[2] <= a.stay ? 1u : 0u;
+        }
+    }
+    return a;
+}
+
+constexpr int SELECT_ITEMS = 8;
+template <class Keys>
+__global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* __restrict__ voff, int B,
+                                                            const int* __restrict__ counts, const int* __restrict__ budgets,
+                                                            int longer_than, SelectSlot* __restrict__ slots, int pass, int tie_bits) {
+    __shared__ u32 h[SELECT_BINS];
+    __shared__ u32 smem[prim::WAVES], picked[3];
+    const int b = blockIdx.y, n = counts[b], keep = budgets[b];
+    if (n <= keep || n <= longer_than || keep <= 0) return;
+    const int v0 = voff[b], v1 = voff[b + 1], t = threadIdx.x;
+    const long long base = (long long)v0 + (long long)blockIdx.x * (BLOCK * SELECT_ITEMS);
+    if (base >= v1) return;
+    SelectSlot& S = slots[select_slot(voff, B, b)];
+    const auto a = select_pick(S, pass, (u32)keep, tie_bits, smem, picked);
+    if (blockIdx.x == 0 && t == 0) S.at[pass] = a;
+    const bool tie = pass >= SELECT_COST_PASSES;
+    if (tie && a.all) return;
+    const int j = tie ? pass - SELECT_COST_PASSES : pass, bits = tie ? tie_bits : 32, shift = select_shift(j, bits), width = select_width(j, bits);
+    for (int i = t; i < SELECT_BINS; i += BLOCK) h[i] = 0;
+    typename Keys::Raw raw[SELECT_ITEMS];
+#pragma unroll
+    for (int i = 0; i < SELECT_ITEMS; ++i) raw[i] = K.load((int)min(base + i * BLOCK + t, (long long)v1 - 1));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SELECT_ITEMS; ++i) {  // (whole waves run every step, for the ballots)
+        bool ok = base + i * BLOCK + t < v1 && K.has(raw[i]);
+        u32 k = K.cost(raw[i]);
+        if (tie) {
+            ok = ok && k == a.cost;
+            k = ok ? K.tie((int)(base + i * BLOCK + t), v0) : 0u;
+        }
+        // keys that share the digits decided so far; cost keys cluster, so the lanes of a wave that hold
+        // one digit count themselves with a single LDS atomic
+        ok = ok && (j == 0 || (k >> (shift + width)) == (tie ? a.tie : a.cost));
+        const u32 d = (k >> shift) & ((1u << width) - 1u);
+        const u64 same = prim::wave_same_digit_lanes(ok, d);
+        if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&h[d], (u32)__popcll(same));
+    }
+    __syncthreads();
+    for (int i = t; i < SELECT_BINS; i += BLOCK) {
+        const u32 c = h[i];
+        if (c) atomicAdd(&S.hist[pass][i], c);
+    }
+}
+
+// ... and the release: `passes` = passes made.
+template <class Keys>
+__global__ __launch_bounds__(BLOCK) void select_release_kernel(Keys K, const int* __restrict__ voff, int B,
+                                                               const int* __restrict__ counts, const int* __restrict__ budgets,
+                                                               int longer_than, const SelectSlot* __restrict__ slots, int passes,
+                                                               int tie_bits) {
+    __shared__ u32 smem[prim::WAVES], picked[3];
+    const int b = blockIdx.y, n = counts[b], keep = budgets[b];
+    if (n <= keep || n <= longer_than) return;
+    const int v0 = voff[b], v1 = voff[b + 1];
+    const long long base = (long long)v0 + (long long)blockIdx.x * (BLOCK * SELECT_ITEMS);
+    if (base >= v1) return;
+    const bool none = keep <= 0;
+    const SelectSlot& S = slots[select_slot(voff, B, b)];
+    const auto a = select_pick(S, none ? 0 : passes, (u32)keep, tie_bits, smem, picked);
+#pragma unroll
+    for (int i = 0; i < SELECT_ITEMS; ++i) {
+        const long long w = base + i * BLOCK + threadIdx.x;
+        if (w >= v1) continue;
+        const typename Keys::Raw raw = K.load((int)w);
+        const u32 cost = K.cost(raw);
+        if (K.has(raw) &&
+            (none || cost > a.cost || (cost == a.cost && !a.all && K.tie((int)w, v0) > a.tie)))
+            K.release((int)w, K.partner((int)w));
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2052,19 +1975,6 @@ struct JoinPred {
 struct JoinListOut {
     int* list;
     __device__ void operator()(int e, int pos) const { list[pos] = e; }
-};
-
-// ... and its mesh has more such edges than budget left.
-struct JoinOverPred {
-    JoinPred jp;
-    MeshTab mt;
-    const int* acand;
-    const int* arem;
-    __device__ bool operator()(int e) const {
-        if (!jp(e)) return false;
-        const int m = mesh_of(mt.voff, mt.B, (int)(jp.ekey[e] >> jp.vbits));
-        return acand[m] > arem[m];
-    }
 };
 
 // The joining edges are listed in edge order, hence by mesh: acand[b] = how many belong to mesh b.

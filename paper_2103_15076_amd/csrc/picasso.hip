@@ -61,12 +61,14 @@ struct picasso_ctx {
     int* fmap = nullptr;                // ... after the last round, before compaction
     int* cid = nullptr;
     u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys); also hold 32-bit keys for S0
-    u32* val32[2] = {nullptr, nullptr};
+    u32* val32 = nullptr;
     u64* ekey = nullptr;
     u32* ecost = nullptr;
     u64* vmin[3] = {nullptr, nullptr, nullptr};
     int* mate = nullptr;
-    int* newid = nullptr;
+    int* newid = nullptr;                               // (free during the rounds: the pairs' cost keys)
+    u32* pcost() const { return reinterpret_cast<u32*>(newid); }
+    u32* ptie() const { return reinterpret_cast<u32*>(vmap); }  // (vmap is free between a round's first kernel and its contraction)
     int* vmap = nullptr;
     int* list = nullptr;
     unsigned char* estate = nullptr;
@@ -79,7 +81,6 @@ struct picasso_ctx {
     // The vertex->facet sort has buffers and scratch of its own, so that in the first round it can
     // share its launches with the edge-key sort (neither depends on the other).
     u64* s0_key[2] = {nullptr, nullptr};  // incidence keys (vertex, facet) of S0 and their sort's second buffer
-    prim::SortScratch sort_sc_s0{};
     u32* hist12_s0 = nullptr;
     prim::XlScratch xl{}, xl_s0{};  // the same for the sorts of very large inputs
     bool hist_dirty = true;  // hist12 may hold counts (it is zero between sorts otherwise)
@@ -95,8 +96,9 @@ struct picasso_ctx {
     int* done = nullptr;   // mesh has taken part in a round that contracted
     int* nrem = nullptr;
     int* matched = nullptr;
-    int* segstart = nullptr;
-    SelectState* sel_state = nullptr;  // the budget step's radix select (one long run, see budget_step)
+    SelectSlot* select_slots = nullptr;  // the budget step's counts (long runs, see budget_step)
+    int n_select_slots = 1;
+    KeyLimit* limits = nullptr;  // per mesh (see budget_step)
     int* mslots = nullptr;
     LiveEdge* live = nullptr;  // the selection tail's list (see SelArgs) and its segments' lengths
     int* live_n = nullptr;
@@ -110,9 +112,8 @@ struct picasso_ctx {
     int host_seq = 0;      // the last sequence number handed out
     int64_t opt_poll_us = 20000;  // for how long the host watches that word before it waits for the stream instead (0: not at all)
     int opt_ahead = 1;     // a round's contraction and facet kernels are queued before the host has looked
-    int opt_trunc_width = 0;  // test hook: keys per lane of the per-mesh budget search (0: as the sizes need)
+    int opt_trunc_width = 0;  // test hook: keys per lane that the per-mesh budget search takes (0: as the sizes need)
     int opt_drop_degenerated = 0;  // output vertices that no output facet refers to are dropped
-    int opt_trunc_select = 1;      // a single mesh's long run in the budget step: 1 = radix select, 0 = sort
     hipEvent_t ev[2 * PICASSO_STATS_ROUNDS * PICASSO_ST_COUNT + 4];
     int n_ev = 0;
     hipEvent_t ev_total[2];
@@ -203,8 +204,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->cid = cv.take<int>(n);
     x->key64[0] = cv.take<u64>(h);
     x->key64[1] = cv.take<u64>(h);
-    x->val32[0] = cv.take<u32>(h);
-    x->val32[1] = cv.take<u32>(h);
+    x->val32 = cv.take<u32>(h);
     x->ekey = cv.take<u64>(h);
     x->ecost = cv.take<u32>(h);
     for (int i = 0; i < 3; ++i) x->vmin[i] = cv.take<u64>(n);
@@ -224,9 +224,6 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     for (int i = 0; i < 2; ++i) {
         x->s0_key[i] = cv.take<u64>(h);
     }
-    x->sort_sc_s0.T = x->sort_sc.T;
-    x->sort_sc_s0.table = cv.take<u32>((size_t)256 * x->sort_sc_s0.T);
-    x->sort_sc_s0.totals = cv.take<u32>(256);
     x->hist12_s0 = cv.take<u32>(3 * prim::MSD_HIST_WORDS);
     if ((long long)h > prim::BUCKET_SORT_LARGE_MAX_KEYS) {
         const size_t words = prim::xl_hist_words((long long)h);
@@ -238,8 +235,9 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     }
     x->voff[1] = cv.take<int>(b + 1);
     x->nrem = cv.take<int>(b);
-    x->segstart = cv.take<int>(b);
-    x->sel_state = cv.take<SelectState>(1);
+    x->n_select_slots = B > 1 ? (int)(n >> 16) + 1 : 1;
+    x->select_slots = cv.take<SelectSlot>((size_t)x->n_select_slots);
+    x->limits = cv.take<KeyLimit>(b);
     x->mslots = cv.take<int>(b * MATCH_SLOTS * MATCH_PAD);
     x->live = cv.take<LiveEdge>((size_t)LIVE_SEGS * TAIL_MAX);
     x->live_n = cv.take<int>(LIVE_SEGS * MATCH_PAD);
@@ -378,7 +376,7 @@ void launch_edge_keys(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_
     const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round_ - 1);
 #define PICASSO_EDGE_KEYS(COUNT, GRID)                                                                                        \
     edge_keys_kernel<COUNT><<<GRID, BLOCK, 0, s>>>(c->fcur, F, c->st, cur_, S.key_bits / 2, c->vmin[0], c->vmin[1], c->mate, \
-                                                   round_tab(c, B, round_, cur_), digit_count(S), c->vmap, c->done, c->cid, N)
+                                                   c->pcost(), round_tab(c, B, round_, cur_), digit_count(S), c->vmap, c->done, c->cid, N)
     // (a workgroup adds its whole histogram to the other's in the end: with 4096 digits it takes several turns)
     switch (count_kind(S)) {
         case COUNT_SMALL: PICASSO_EDGE_KEYS(COUNT_SMALL, grid_for(std::max(F, 1))); break;
@@ -453,7 +451,7 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     init_kernel<COUNT><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
         d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, incidence_fbits(N, F), digit_count(I),   \
         digit_count(E), edges ? 1 : 0, E.key_bits / 2, c->st, init, planes, c->htab, n_clear, c->vmin[0], c->vmin[1], c->mate, \
-        round_tab(c, B, 0, 0))
+        c->pcost(), round_tab(c, B, 0, 0))
     if (!work) PICASSO_INIT(COUNT_NONE);
     else if (count_kind(I) == COUNT_SMALL) PICASSO_INIT(COUNT_SMALL);
     else if (count_kind(I) == COUNT_LARGE) PICASSO_INIT(COUNT_LARGE);
@@ -552,91 +550,51 @@ int status_from_err_bits(int bits) {
     return PICASSO_OK;
 }
 
-// Budget step: among the edges `over` selects (the formed pairs, or the joining edges of line 11, of
-// the meshes that have more of them than they may use: counts[b] > budgets[b]) each mesh keeps its
-// budgets[b] first ones in ascending (cost key, tie-break) order; the others are released
-// (release_edge<ABSORB>) and counts[] is clamped.  n_over = sum of those meshes' counts, seg_max
-// their largest.
-// `guarded` (per-mesh search only, i.e. seg_max <= the context's limit for it): queued behind the
-// selection tail before the host has looked; ne, n_over and seg_max are then upper bounds and the
-// kernels do nothing unless the tail finished the matching; `tell` is stored by the first of them.
-template <bool ABSORB, class Over>
-int budget_step(picasso_ctx* c, hipStream_t s, Over over, int B, int ne, int vbits, const MeshTab& mt,
-                const TieBreak& tb, long long n_over, int seg_max, int* counts, int* budgets, bool guarded = false,
-                HostSignal tell = HostSignal{nullptr, 0}) {
-    if (guarded && seg_max > c->opt_trunc_block_max) return PICASSO_ERR_INVALID_ARG;
-    if (seg_max <= c->opt_trunc_block_max) {
+// Budget step: among a mesh's keys (its formed pairs, or the vertices that could join clusters by line 11) where there are more
+// of them than it may use (counts[b] > budgets[b]) the budgets[b] first ones in ascending (cost key, tie-break) order stay;
+// the others are released.  most = the largest such count; nv_max = all meshes' vertices; least = the smallest.
+// `guarded` (most <= the limit of one workgroup per mesh only): queued behind the
+// selection tail before the host has looked; the counts are then upper bounds and the
+// kernel does nothing unless the tail finished the matching; it stores `tell` first.
+template <class Keys>
+int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* voff, int nv_max, int most, int least,
+                const int* counts, const int* budgets, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
+    // (in a batch the limit is what a workgroup holds, whatever the option says: see select_slot)
+    const int limit = B == 1 ? (int)c->opt_trunc_block_max : TRUNC_BLOCK_CAP;
+    const bool longer = most > limit;
+    if (guarded && longer) return PICASSO_ERR_INVALID_ARG;
+    if (least <= limit) {
         const int* guard = guarded ? &c->st->go : nullptr;
-        u32* tcost = reinterpret_cast<u32*>(c->key64[0]);
-        TruncOutSplit to{c->ecost, tcost, c->val32[0]};
-        // (`tell`: the first kernel also tells the host that the selection tail in front of it is done)
-        SignalingPred<Over> first{over, tell};
-        prim::compact(s, first, over, to, guarded ? &c->st->guard_ne : &c->st->ne, ne, c->tilesum, &c->st->trunc_n);
-#define PICASSO_TRUNC_BLOCK(R)                                                                                       \
-    do {                                                                                                             \
-        if (tb.on)                                                                                                   \
-            trunc_block_kernel<R, true><<<B, TRUNC_THREADS, 0, s>>>(tcost, c->val32[0], tb, counts, budgets, guard,   \
-                                                                    c->st);                                          \
-        else                                                                                                         \
-            trunc_block_kernel<R, false><<<B, TRUNC_THREADS, 0, s>>>(tcost, c->val32[0], tb, counts, budgets, guard,  \
-                                                                     c->st);                                         \
-    } while (0)
-        // keys per lane: what the largest mesh needs (or what the test hook says)
-        const int width = c->opt_trunc_width ? c->opt_trunc_width : (seg_max + TRUNC_THREADS - 1) / TRUNC_THREADS;
-        if (width <= 4) PICASSO_TRUNC_BLOCK(4);
-        else if (width <= 8) PICASSO_TRUNC_BLOCK(8);
-        else if (width <= 16) PICASSO_TRUNC_BLOCK(16);
-        else PICASSO_TRUNC_BLOCK(32);
-#undef PICASSO_TRUNC_BLOCK
-        trunc_release_kernel<ABSORB><<<grid_for(n_over), BLOCK, 0, s>>>(tcost, c->val32[0], c->st, c->ekey, vbits,
-                                                                        c->mate, B, counts, budgets, c->abid, guard);
-        return PICASSO_OK;
+        const int need = std::min(most, limit);
+        int cap = need <= TRUNC_SMALL_CAP ? TRUNC_SMALL_CAP : TRUNC_BLOCK_CAP;
+        if (c->opt_trunc_width) cap = c->opt_trunc_width * TRUNC_THREADS;  // (test hook)
+        if (cap <= TRUNC_SMALL_CAP)
+            trunc_mesh_kernel<Keys, TRUNC_SMALL_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer ? 1 : 0,
+                                                                                guard, c->st, tell, nullptr);
+        else {
+            trunc_mesh_kernel<Keys, TRUNC_BLOCK_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer ? 1 : 0,
+                                                                                guard, c->st, tell, c->limits);
+            trunc_release_kernel<Keys><<<grid_for(nv_max), BLOCK, 0, s>>>(K, nv_max, voff, B, c->limits);
+        }
     }
-    if (B == 1 && !tb.on && c->opt_trunc_select) {
-        // one long run, ties in edge order: no sort, the threshold key is found by three histogram passes
-        u32* tcost = reinterpret_cast<u32*>(c->key64[0]);
-        TruncOutSplit to{c->ecost, tcost, c->val32[0]};
-        prim::compact(s, over, over, to, &c->st->ne, ne, c->tilesum, &c->st->trunc_n);
-        SelectState* S = c->sel_state;
-        constexpr int state_words = (int)(sizeof(SelectState) / sizeof(u32));
-        prim::fill_u32_kernel<<<grid_for(state_words), BLOCK, 0, s>>>(reinterpret_cast<u32*>(S), state_words, 0u);
-        const int hgrid = grid_for((n_over + SELECT_ITEMS - 1) / SELECT_ITEMS);
-        trunc_select_hist_kernel<0><<<hgrid, BLOCK, 0, s>>>(tcost, c->st, S);
-        trunc_select_pick_kernel<0><<<1, BLOCK, 0, s>>>(S, budgets);
-        trunc_select_hist_kernel<1><<<hgrid, BLOCK, 0, s>>>(tcost, c->st, S);
-        trunc_select_pick_kernel<1><<<1, BLOCK, 0, s>>>(S, budgets);
-        trunc_select_hist_kernel<2><<<hgrid, BLOCK, 0, s>>>(tcost, c->st, S);
-        trunc_select_pick_kernel<2><<<1, BLOCK, 0, s>>>(S, budgets);
-        const SelectTiePred tie{tcost, S};
-        const SelectFlagOut flag{tcost, S};
-        prim::compact(s, tie, tie, flag, &c->st->trunc_n, (int)n_over, c->tilesum, nullptr);
-        trunc_release_kernel<ABSORB><<<grid_for(n_over), BLOCK, 0, s>>>(tcost, c->val32[0], c->st, c->ekey, vbits,
-                                                                        c->mate, B, counts, budgets, c->abid, nullptr);
-        return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
+    if (longer) {
+        SelectSlot* S = c->select_slots;
+        const long long words = (long long)(B == 1 ? 1 : c->n_select_slots) * (long long)(sizeof(SelectSlot) / sizeof(u32));
+        prim::fill_u32_kernel<<<grid_for(words), BLOCK, 0, s>>>(reinterpret_cast<u32*>(S), (int)words, 0u);
+        const int tie_bits = Keys::TIE_BY_VERTEX ? ceil_log2(nv_max) : 32;
+        const int passes = SELECT_COST_PASSES + (tie_bits + SELECT_BITS - 1) / SELECT_BITS;
+        const dim3 grid((unsigned)((nv_max + BLOCK * SELECT_ITEMS - 1) / (BLOCK * SELECT_ITEMS)), (unsigned)B);
+        for (int p = 0; p < passes; ++p)
+            select_pass_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, B, counts, budgets, limit, S, p, tie_bits);
+        select_release_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, B, counts, budgets, limit, S, passes, tie_bits);
     }
-    u64* k0 = c->key64[0];
-    u64* k1 = c->key64[1];
-    u32* v0 = c->val32[0];
-    u32* v1 = c->val32[1];
-    if (tb.on) {
-        TruncOutTie to{tb, k0, v0};
-        prim::compact(s, over, over, to, &c->st->ne, ne, c->tilesum, &c->st->trunc_n);
-        const int w0 = prim::radix_sort<u64, true>(s, k0, k1, v0, v1, &c->st->trunc_n, (int)n_over, 32, c->sort_sc);
-        if (w0 < 0) return PICASSO_ERR_HIP;
-        if (w0) { std::swap(k0, k1); std::swap(v0, v1); }
-        trunc_rekey_kernel<<<grid_for(n_over), BLOCK, 0, s>>>(v0, c->st, c->ekey, c->ecost, mt, vbits, k0);
-    } else {
-        TruncOut to{c->ekey, c->ecost, k0, v0, mt, vbits};
-        prim::compact(s, over, over, to, &c->st->ne, ne, c->tilesum, &c->st->trunc_n);
-    }
-    const int where = prim::radix_sort<u64, true>(s, k0, k1, v0, v1, &c->st->trunc_n, (int)n_over,
-                                                  32 + (B > 1 ? ceil_log2(B) : 0), c->sort_sc);
-    if (where < 0) return PICASSO_ERR_HIP;
-    trunc_segments_kernel<<<1, 64, 0, s>>>(B, counts, budgets, c->segstart);
-    trunc_apply_kernel<ABSORB><<<grid_for(n_over), BLOCK, 0, s>>>(where ? k1 : k0, where ? v1 : v0, c->st, c->segstart,
-                                                                  budgets, c->ekey, vbits, c->mate, c->abid);
-    trunc_finish_kernel<<<1, BLOCK, 0, s>>>(B, counts, budgets);
-    return PICASSO_OK;
+    return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
+}
+int pair_budget(picasso_ctx* c, hipStream_t s, const TieBreak& tb, int B, const int* voff, int nv_max, int most, int least,
+                bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
+    if (tb.on)
+        return budget_step(c, s, PairKeys<true>{c->pcost(), c->ptie(), c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, guarded, tell);
+    return budget_step(c, s, PairKeys<false>{c->pcost(), nullptr, c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, guarded, tell);
 }
 
 // Alg. 2 line 11 on the device for the round whose pairs are final (see the kernels).  nrem /
@@ -658,22 +616,21 @@ int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne,
                                             counted);
     HIP_TRY(c, wait_for_signal(c, s, counted));
     const int* h_cand = c->h_pin + HDR_STATE_INTS + c->cap_b;
-    long long n_list = 0, n_over = 0;
-    int seg_max = 0;
+    long long n_list = 0;
+    int most = 0, least = 0x7FFFFFFF;
     for (int b = 0; b < B; ++b) {
         const int left = (h_matched[b] > 0 && nrem[b] > h_matched[b]) ? nrem[b] - h_matched[b] : 0;
         const int cand = h_cand[b];
         n_list += cand;
         if (cand > left) {
-            n_over += cand;
-            seg_max = std::max(seg_max, cand);
+            most = std::max(most, cand);
+            least = std::min(least, cand);
         }
         h_joined[b] = std::min(cand, left);
     }
     if (n_list == 0) return PICASSO_OK;
-    if (n_over > 0) {  // the cheapest `left` candidates of each such mesh stay
-        JoinOverPred op{jp, mt, c->acand, c->arem};
-        const int rc = budget_step<true>(c, s, op, B, ne, vbits, mt, tb, n_over, seg_max, c->acand, c->arem);
+    if (most > 0) {  // the cheapest `left` candidates of each such mesh stay
+        const int rc = budget_step(c, s, JoinKeys{c->abid}, B, c->voff[cur], nv_total, most, least, c->acand, c->arem);
         if (rc != PICASSO_OK) return rc;
     }
     absorb_keys_kernel<<<grid_for(n_list), BLOCK, 0, s>>>(c->list, c->st, c->ekey, c->ecost, vbits, c->mate, c->abid,
@@ -834,13 +791,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         constexpr int AHEAD_MAX_FACETS = 1 << 20;
         bool ahead_ok = !c->opt_absorb && !stats && c->opt_ahead && nf_bound <= AHEAD_MAX_FACETS;
         bool ahead_budget = false;
-        long long over_bound = 0;  // pairs of the meshes that may exceed their budgets, at most
-        int seg_bound = 0;         // ... of the largest of them
+        int seg_bound = 0;  // pairs of the largest mesh that may exceed its budget, at most
         if (ahead_ok) {
             bool likely = false;
             for (int b = 0; b < B; ++b)
                 if (act[b] && 2ll * nrem[b] < nvb[b]) {
-                    over_bound += nvb[b] / 2;
                     seg_bound = std::max(seg_bound, nvb[b] / 2);
                     likely |= 5ll * nrem[b] < 2ll * nvb[b];
                 }
@@ -857,6 +812,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         sa.ecost = c->ecost;
         for (int i = 0; i < 3; ++i) sa.vmin[i] = c->vmin[i];
         sa.mate = c->mate;
+        sa.pcost = c->pcost();
+        sa.ptie = c->ptie();
         sa.live = c->live;
         sa.live_cap = TAIL_MAX;
         sa.live_n = c->live_n;
@@ -916,9 +873,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const HostSignal nothing{nullptr, 0};
             if (ahead_ok) {
                 if (ahead_budget) {
-                    TruncPred tp{c->ekey, c->mate, mt, vbits};
-                    rc = budget_step<false>(c, s, tp, B, ne_bound, vbits, mt, tb, over_bound, seg_bound, c->matched,
-                                            c->nrem, true, tail_done);
+                    rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_bound, 0, true, tail_done);
                     if (rc != PICASSO_OK) return rc;
                 }
                 issue_contract(0, nullptr, 0, true, ahead_budget ? nothing : tail_done);
@@ -975,22 +930,18 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         }
 
         // ---- budget truncation (only where a mesh formed more pairs than it may remove)
-        bool need_trunc = false;
-        long long n_trunc = 0;
-        int n_sel = 0, seg_max = 0;
+        int n_sel = 0, seg_max = 0, seg_min = 0x7FFFFFFF;  // pairs; of the meshes over their budgets, the most and the least
         for (int b = 0; b < B; ++b) {
             if (h_matched[b] > nrem[b]) {
-                need_trunc = true;
-                n_trunc += h_matched[b];
                 seg_max = std::max(seg_max, h_matched[b]);
+                seg_min = std::min(seg_min, h_matched[b]);
                 h_matched[b] = nrem[b];
             }
             n_sel += h_matched[b];
         }
-        if (need_trunc && ahead && !ahead_budget) return PICASSO_ERR_HIP;  // (cannot happen: a matching pairs at most half the vertices)
-        if (need_trunc && !ahead) {
-            TruncPred tp{c->ekey, c->mate, mt, vbits};
-            rc = budget_step<false>(c, s, tp, B, hst->ne, vbits, mt, tb, n_trunc, seg_max, c->matched, c->nrem);
+        if (seg_max > 0 && ahead && !ahead_budget) return PICASSO_ERR_HIP;  // (cannot happen: a matching pairs at most half the vertices)
+        if (seg_max > 0 && !ahead) {
+            rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_max, seg_min);
             if (rc != PICASSO_OK) return rc;
         }
 
@@ -1329,9 +1280,7 @@ int picasso_set_option(picasso_ctx* c, int option, int64_t value) {
             c->opt_drop_degenerated = (int)value;
             return PICASSO_OK;
         case PICASSO_OPT_TRUNC_SELECT:
-            if (value != 0 && value != 1) return PICASSO_ERR_INVALID_ARG;
-            c->opt_trunc_select = (int)value;
-            return PICASSO_OK;
+            return value == 0 || value == 1 ? PICASSO_OK : PICASSO_ERR_INVALID_ARG;  // (one way is left)
         case PICASSO_OPT_TRUNC_WIDTH:
             if (value != 0 && value != 4 && value != 8 && value != 16 && value != 32) return PICASSO_ERR_INVALID_ARG;
             c->opt_trunc_width = (int)value;
@@ -1826,24 +1775,24 @@ int picasso_bucket_sort(picasso_ctx* c, void* stream, int key_bytes, void* d_key
     if (key_bytes == 8) {
         u64* k1 = c->key64[1];
         if (large)
-            rc = d_vals ? prim::bucket_sort_large<u64>(s, (u64*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
+            rc = d_vals ? prim::bucket_sort_large<u64>(s, (u64*)d_keys, k1, d_vals, c->val32, nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
                         : large_keys((u64*)d_keys, k1);
         else
-            rc = d_vals ? prim::bucket_sort<u64, true>(s, (u64*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc)
+            rc = d_vals ? prim::bucket_sort<u64, true>(s, (u64*)d_keys, k1, d_vals, c->val32, nullptr, (int)n, key_bits, c->sort_sc)
                         : prim::bucket_sort<u64, false>(s, (u64*)d_keys, k1, nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc);
         if (rc == 1) HIP_TRY(c, hipMemcpyAsync(d_keys, k1, sizeof(u64) * n, hipMemcpyDeviceToDevice, s));
     } else {
         u32* k1 = reinterpret_cast<u32*>(c->key64[1]);
         if (large)
-            rc = d_vals ? prim::bucket_sort_large<u32>(s, (u32*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
+            rc = d_vals ? prim::bucket_sort_large<u32>(s, (u32*)d_keys, k1, d_vals, c->val32, nullptr, (int)n, key_bits, c->sort_sc, c->hist12)
                         : large_keys((u32*)d_keys, k1);
         else
-            rc = d_vals ? prim::bucket_sort<u32, true>(s, (u32*)d_keys, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc)
+            rc = d_vals ? prim::bucket_sort<u32, true>(s, (u32*)d_keys, k1, d_vals, c->val32, nullptr, (int)n, key_bits, c->sort_sc)
                         : prim::bucket_sort<u32, false>(s, (u32*)d_keys, k1, nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc);
         if (rc == 1) HIP_TRY(c, hipMemcpyAsync(d_keys, k1, sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
     }
     if (rc < 0) return PICASSO_ERR_HIP;
-    if (rc == 1 && d_vals) HIP_TRY(c, hipMemcpyAsync(d_vals, c->val32[1], sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
+    if (rc == 1 && d_vals) HIP_TRY(c, hipMemcpyAsync(d_vals, c->val32, sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
@@ -1860,22 +1809,22 @@ int picasso_radix_sort(picasso_ctx* c, void* stream, int key_bytes, void* d_keys
     int where;
     if (key_bytes == 8) {
         u64* k = (u64*)d_keys;
-        where = d_vals ? prim::radix_sort<u64, true>(s, k, c->key64[1], d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc)
+        where = d_vals ? prim::radix_sort<u64, true>(s, k, c->key64[1], d_vals, c->val32, nullptr, (int)n, key_bits, c->sort_sc)
                        : prim::radix_sort<u64, false>(s, k, c->key64[1], nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc);
         if (where < 0) return PICASSO_ERR_HIP;
         if (where == 1) {
             HIP_TRY(c, hipMemcpyAsync(k, c->key64[1], sizeof(u64) * n, hipMemcpyDeviceToDevice, s));
-            if (d_vals) HIP_TRY(c, hipMemcpyAsync(d_vals, c->val32[1], sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
+            if (d_vals) HIP_TRY(c, hipMemcpyAsync(d_vals, c->val32, sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
         }
     } else {
         u32* k = (u32*)d_keys;
         u32* k1 = reinterpret_cast<u32*>(c->key64[1]);
-        where = d_vals ? prim::radix_sort<u32, true>(s, k, k1, d_vals, c->val32[1], nullptr, (int)n, key_bits, c->sort_sc)
+        where = d_vals ? prim::radix_sort<u32, true>(s, k, k1, d_vals, c->val32, nullptr, (int)n, key_bits, c->sort_sc)
                        : prim::radix_sort<u32, false>(s, k, k1, nullptr, nullptr, nullptr, (int)n, key_bits, c->sort_sc);
         if (where < 0) return PICASSO_ERR_HIP;
         if (where == 1) {
             HIP_TRY(c, hipMemcpyAsync(k, k1, sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
-            if (d_vals) HIP_TRY(c, hipMemcpyAsync(d_vals, c->val32[1], sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
+            if (d_vals) HIP_TRY(c, hipMemcpyAsync(d_vals, c->val32, sizeof(u32) * n, hipMemcpyDeviceToDevice, s));
         }
     }
     HIP_TRY(c, hipStreamSynchronize(s));

@@ -958,3 +958,26 @@ def test_degenerated_vertices_dropped(pk, ctx, ctx16k, oracle):
     finally:
         for c in (ctx, ctx16k):
             c.set_option(pk.PICASSO_OPT_DROP_DEGENERATED, 0)
+
+
+@pytest.mark.parametrize("flat", [False, True])
+def test_budget_of_long_runs_in_a_batch(pk, oracle, flat):
+    """Two meshes of a batch form more pairs than one workgroup selects from (one keeps a single pair, one most of
+    them), next to meshes that form few; with distinct costs, and with nothing but ties."""
+    make = (lambda w, h, seed: meshgen.flat_grid(w, h, spacing=0.25)) if flat else (lambda w, h, seed: meshgen.noisy_grid(w, h, seed=seed))
+    parts = [make(30, 22, 1), make(330, 270, 2), make(12, 9, 3), make(300, 301, 4)]
+    nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
+    off = np.cumsum([0] + nv)
+    V = np.concatenate([p[0] for p in parts])
+    F = np.concatenate([p[1] + off[i] for i, p in enumerate(parts)]).astype(np.int32)
+    tg = [nv[0] - 40, nv[1] - 1, nv[2], nv[3] - 30000]
+    c = pk.Context(V.shape[0], F.shape[0], len(parts), device=0)
+    try:
+        st, vo, fo, cid, nvo, nfo = c.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg)
+        ref = oracle.decimate_batch(V, F, nv, nf, tg)
+        assert st == ref["status"] and nvo.tolist() == ref["nv"].tolist() and nfo.tolist() == ref["nf"].tolist()
+        assert np.array_equal(cid.cpu().numpy(), ref["cluster_id"])
+        assert np.array_equal(fo.cpu().numpy(), ref["facets"])
+        assert np.array_equal(vo.cpu().numpy().view(np.uint32), ref["verts"].view(np.uint32))
+    finally:
+        c.close()
