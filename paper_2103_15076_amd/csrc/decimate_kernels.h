@@ -1798,8 +1798,12 @@ struct SelectSlot {
         u32 cost, below, tie, tie_below, stay, all;
     } at[SELECT_PASSES + 1];
 };
-// A mesh's slot: meshes of more than 2^15 pairs have more than 2^16 vertices.
-__device__ __forceinline__ int select_slot(const int* voff, int B, int b) { return B == 1 ? 0 : voff[b] >> 16; }
+// A mesh's slot.  A key stands at a vertex of its own (a pair at its lower one, a vertex that could join at itself), so meshes
+// of more than 2^SELECT_SLOT_BITS keys start more than 2^SELECT_SLOT_BITS vertices apart: no two of them share a slot.
+constexpr int SELECT_SLOT_BITS = 15;
+static_assert(1 << SELECT_SLOT_BITS == TRUNC_BLOCK_CAP, "in a batch only meshes of more than TRUNC_BLOCK_CAP keys come here");
+inline int select_slots_for(size_t n_verts, int B) { return B > 1 ? (int)(n_verts >> SELECT_SLOT_BITS) + 1 : 1; }
+__device__ __forceinline__ int select_slot(const int* voff, int B, int b) { return B == 1 ? 0 : voff[b] >> SELECT_SLOT_BITS; }
 __device__ __forceinline__ int select_shift(int j, int bits) { return max(0, bits - SELECT_BITS * (j + 1)); }
 __device__ __forceinline__ int select_width(int j, int bits) { return min(SELECT_BITS, bits - SELECT_BITS * j); }
 

@@ -235,7 +235,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     }
     x->voff[1] = cv.take<int>(b + 1);
     x->nrem = cv.take<int>(b);
-    x->n_select_slots = B > 1 ? (int)(n >> 16) + 1 : 1;
+    x->n_select_slots = select_slots_for(n, B);
     x->select_slots = cv.take<SelectSlot>((size_t)x->n_select_slots);
     x->limits = cv.take<KeyLimit>(b);
     x->mslots = cv.take<int>(b * MATCH_SLOTS * MATCH_PAD);

@@ -213,3 +213,54 @@ def test_many_tiny_meshes_with_line_11(pk, oracle):
         assert st == worst
     finally:
         c.close()
+
+
+def _book(n, seed):
+    """n - 2 facets on one edge: one pair is formed, and every other vertex could join it."""
+    V = np.random.default_rng(seed).normal(size=(n, 3)).astype(np.float32)
+    V[0], V[1] = [0, 0, -1], [0, 0, 1]
+    F = np.stack([np.zeros(n - 2), np.ones(n - 2), np.arange(2, n)], 1).astype(np.int32)
+    return V, F
+
+
+def _spiked_lattice(w, h, seed):
+    """A lattice with a point above and one below every facet, joined to its corners: most vertices are such points,
+    which pair with nothing once the lattice's vertices are taken."""
+    V, F = meshgen.noisy_grid(w, h, seed=seed)
+    n, m, c = V.shape[0], F.shape[0], V[F].mean(1)
+    tips = [F] + [np.stack([F[:, a], F[:, b], base + np.arange(m)], 1) for base in (n, n + m) for a, b in ((0, 1), (1, 2), (2, 0))]
+    up = np.float32([0, 0, 0.3])
+    return np.concatenate([V, c + up, c - up]).astype(np.float32), np.concatenate(tips).astype(np.int32)
+
+
+@pytest.mark.parametrize("parts,left", [
+    ([_book(40000, 1), _book(40000, 2)], [20000, 1]),                 # 39,998 candidates from 40,000 vertices
+    ([_book(32771, 3), _book(32771, 4), _book(32771, 5)], [32768, 16000, 7]),   # 32,769: the fewest that take this path
+    ([_spiked_lattice(105, 105, 1), _spiked_lattice(108, 108, 3)], [9000, 30000]),
+], ids=["books", "smallest_books", "spiked_lattices"])
+def test_batch_of_meshes_with_more_candidates_than_one_workgroup_takes(pk, ctx, oracle, parts, left):
+    """Candidates stand at vertices, one each, so meshes not much larger than the limit of one workgroup exceed it: side by side
+    in a batch, each searched for its own budget by the whole chip."""
+    nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
+    off = np.cumsum([0] + nv)
+    V = np.concatenate([p[0] for p in parts])
+    F = np.concatenate([p[1] + off[i] for i, p in enumerate(parts)]).astype(np.int32)
+    tg = []
+    for (Vi, Fi), l in zip(parts, left):
+        pairs = Vi.shape[0] - oracle.decimate(Vi, Fi, 1, max_rounds=1)["verts"].shape[0]
+        joined = Vi.shape[0] - pairs - oracle.decimate(Vi, Fi, 1, max_rounds=1, absorb=True)["verts"].shape[0]
+        assert joined > max(1 << 15, l)
+        tg.append(Vi.shape[0] - pairs - l)
+    print(f"line11 batch nv={nv} targets={tg}", flush=True)
+    st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg)
+    assert st == 0 and nvo.tolist() == tg
+    vo, fo, cid = vo.cpu().numpy(), fo.cpu().numpy(), cid.cpu().numpy()
+    v0 = f0 = 0
+    for i, (Vi, Fi) in enumerate(parts):
+        ref = oracle.decimate(Vi, Fi, tg[i], absorb=True)
+        assert int(nvo[i]) == ref["verts"].shape[0] and int(nfo[i]) == ref["facets"].shape[0], i
+        assert np.array_equal(vo[v0:v0 + nvo[i]].view(np.uint32), ref["verts"].view(np.uint32)), i
+        assert np.array_equal(fo[f0:f0 + nfo[i]], ref["facets"] + v0), i
+        assert np.array_equal(cid[off[i]:off[i + 1]], ref["cluster_id"] + v0), i
+        v0 += int(nvo[i])
+        f0 += int(nfo[i])
