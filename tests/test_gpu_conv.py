@@ -115,6 +115,40 @@ def test_fuzzy_coefficients(pk, ctx, oracle):
         assert np.abs(pi.sum(1) - 1).max() <= 32 * EPS
 
 
+@pytest.mark.parametrize("inv_var", [26.0, 50.0, 100.0])
+@pytest.mark.parametrize("T", [2, 6, 50])
+def test_fuzzy_coefficients_of_sharp_components(pk, ctx, oracle, T, inv_var):
+    """Facets that are far from every component: the sum of the exponentials goes from 2^-90 down into the subnormal numbers
+    (z from 62 to 100; beyond 103 binary32 has nothing left to divide).
+
+    Bound: z has at most 6 roundings, exp 4, each relative to itself, and a subnormal exponential is off by up to 2 x 2^-149;
+    that error d_t of every exponential goes into its own coefficient and, through the sum, into all:
+    (d_t + pi_t sum d) / sum, and a few roundings of the quotient.  Whatever the exponentials are, the coefficients of a
+    facet are their shares: they add up to 1 to T roundings and the sum's T."""
+    rng = np.random.default_rng(T)
+    nF = 4096
+    spread = rng.normal(size=(T, 3)) * 0.5 / inv_var
+    mu = np.array([1.0, 0.0, 0.0]) + spread
+    mu = (mu / np.linalg.norm(mu, axis=1, keepdims=True)).astype(np.float32)
+    cos = 1.0 - rng.uniform(64.0, 98.0, nF) / (2.0 * inv_var)   # |n - mu|^2 = 2 - 2 cos
+    phi = rng.uniform(0, 2 * np.pi, nF)
+    sin = np.sqrt(1.0 - cos * cos)
+    n = np.stack([cos, sin * np.cos(phi), sin * np.sin(phi)], 1).astype(np.float32)
+    iv = np.full(T, inv_var, np.float32)
+    z = ((n[:, None].astype(np.float64) - mu[None].astype(np.float64)) ** 2).sum(2) * inv_var
+    keep = (z.min(1) > 62.0) & (z.min(1) < 100.0)
+    n, z = np.ascontiguousarray(n[keep]), z[keep]
+    assert (np.exp(-z).sum(1) < 2.0 ** -128).sum() > 200 and (np.exp(-z).min(1) > 2.0 ** -100).sum() > 20
+    pi = ctx.picasso_fuzzy_coefficients(dev(n), dev(mu), dev(iv)).cpu().numpy().astype(np.float64)
+    e = np.exp(-z)
+    d = e * (6 * z + 4) * EPS + 2 * 2.0 ** -149
+    ref = oracle.fuzzy(n, mu, iv)
+    bound = (d + ref * d.sum(1, keepdims=True)) / np.maximum(e.sum(1, keepdims=True) - d.sum(1, keepdims=True), 2.0 ** -149) + (T + 4) * EPS
+    assert np.isfinite(pi).all()
+    assert (np.abs(pi - ref) <= bound).all()
+    assert np.abs(pi.sum(1) - 1).max() <= 2 * T * EPS
+
+
 @pytest.mark.parametrize("name,mesh", list(_meshes()), ids=lambda x: x if isinstance(x, str) else "")
 @pytest.mark.parametrize("C", [3, 8, 100])
 def test_vertex2facet_forward_and_backward(pk, ctx, oracle, name, mesh, C):
