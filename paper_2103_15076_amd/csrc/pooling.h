@@ -32,7 +32,7 @@ struct __attribute__((packed, aligned(4))) PackedInt4 {
     int v[4];
 };
 
-// How the rows of a call are addressed, the same for all its arrays (row_kind):
+// How the rows of a call are addressed, the same for all its arrays whose rows the call knows (row_kind):
 //   ROW_EVEN  the channel count is a multiple of 4, and every array's byte offsets (rows of up to `width` values) fit 32 bits and its row numbers
 //             24: an address is one 24-bit multiply-add on top of a base in scalar registers;
 //   ROW_TAIL  the same, with a last pack of `left` < 4 channels per row (the others read as 0);
@@ -246,7 +246,8 @@ __global__ __launch_bounds__(BLOCK) void pool_backward_kernel(const float* __res
     store_row<KIND>(row_at<KIND>(gx, v, C, c0), g, left);
 }
 
-// Unpooling: every vertex takes its cluster's feature.
+// Unpooling: every vertex takes its cluster's feature.  KIND is that of x alone: how many rows y has the call does not know,
+// so those are addressed with 64 bits (one multiplication more per lane).
 template <int KIND>
 __global__ __launch_bounds__(BLOCK) void unpool_forward_kernel(const float* __restrict__ y, int n_in, int C,
                                                                const int* __restrict__ cid, float* __restrict__ x,
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(BLOCK) void unpool_forward_kernel(const float* __re
     const int v = wave_row(map, blockIdx.x) + l.r;
     if (!l.on || v >= n_in) return;
     const int c0 = 4 * l.q, left = C - c0;
-    store_row<KIND>(row_at<KIND>(x, v, C, c0), load_row<KIND>(row_at<KIND>(y, *at<KIND>(cid, v), C, c0), left), left);
+    store_row<KIND>(row_at<KIND>(x, v, C, c0), load_row<KIND>(row_at<ROW_ANY>(y, *at<KIND>(cid, v), C, c0), left), left);
 }
 
 // The two per-input-vertex tensors of Alg. 2's output list from cluster_id: first[c] = smallest

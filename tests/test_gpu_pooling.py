@@ -162,6 +162,17 @@ def test_features_at_addresses_that_are_not_16_byte_aligned(pk, ctx, oracle):
     assert np.all(np.abs(ya.astype(np.float64) - ref) <= _sum_bound(np.abs(x), cid, n_out, sizes) + U * np.abs(ref))
 
 
+@pytest.mark.parametrize("n_out,C", [((1 << 24) + 40, 4), ((1 << 24) + 40, 3), ((1 << 22) + 9, 256)])
+def test_unpooling_from_clusters_beyond_24_bit_numbers_and_4_gib(pk, ctx, n_out, C):
+    """Few vertices whose clusters lie at the end of a long feature array (the array's length is not an argument)."""
+    print(f"unpool n_out={n_out} C={C}", flush=True)
+    y = torch.zeros((n_out, C), dtype=torch.float32, device="cuda:0")
+    y[-41:] = torch.randn((41, C), device="cuda:0")
+    y[:41] = 7.0   # (where a wrapped address would lead)
+    cid = torch.arange(n_out - 1, n_out - 42, -1, dtype=torch.int32, device="cuda:0").repeat(7)
+    assert torch.equal(ctx.picasso_unpool_forward(y, cid), y[cid.long()])
+
+
 def test_bad_cluster_ids_are_rejected(pk, ctx):
     cid = np.array([0, 1, 5, 2], np.int32)
     with pytest.raises(pk.PicassoError) as e:
