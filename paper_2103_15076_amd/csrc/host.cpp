@@ -4,6 +4,7 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <vector>
@@ -123,15 +124,15 @@ PyObject* pack(std::initializer_list<PyObject*> items) {
 }
 PyObject* none() { Py_RETURN_NONE; }
 
-// Exceptions of C++ become Python's.
+// Exceptions of C++ become Python's, torch's (an allocation that fails, say) the ones that torch raises for them.
 template <PyObject* (*Body)(Args&)>
 PyObject* entry(PyObject*, PyObject* const* a, Py_ssize_t n) {
     try {
         Args args{a, n};
         return Body(args);
     } catch (const PyError&) {
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {
+        torch::translate_exception_to_python(std::current_exception());
     }
     return nullptr;
 }

@@ -87,3 +87,17 @@ def test_one_level_of_a_mesh_network(oracle, absorb):
         assert np.array_equal(up[rep_r], up)  # every vertex carries its representative's feature
     finally:
         ctx.close()
+
+
+def test_an_allocation_that_fails_raises_torchs_exception():
+    """A program that catches it frees memory and goes on: the next call works."""
+    import paper_2103_15076_amd as pk
+    ctx = pk.Context(1000, 1000, 1, device=0)
+    try:
+        y = torch.zeros((1, 1 << 20), device="cuda:0")
+        cid = torch.zeros(1 << 20, dtype=torch.int32, device="cuda:0")
+        with pytest.raises(torch.OutOfMemoryError):   # 4 TiB
+            ctx.picasso_unpool_forward(y, cid)
+        assert torch.equal(ctx.picasso_unpool_forward(y[:, :4].contiguous() + 1, cid), torch.ones((1 << 20, 4), device="cuda:0"))
+    finally:
+        ctx.close()
