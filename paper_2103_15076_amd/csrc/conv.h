@@ -370,7 +370,8 @@ __global__ __launch_bounds__(BLOCK) void v2f_forward_kernel(const float* __restr
 // lane, into the wave's LDS window.  2^split lane groups share a row's items (WalkMap), each taking every 2^split-th of
 // them from the window, UNROLL at a time: Op::load starts the gather of an item's feature row, Op::use adds it up.
 // Op::end makes the row from a group's sums; sums over a row's groups go through GroupSum.  Every sum has a fixed order.
-// Offsets are clipped to [0, n_items]; soff holds 65 ints of the wave's own.
+// Offsets are clipped to [0, n_items], and a row's end to the end of the wave's last row, behind which nothing is staged: whatever
+// the offsets (descending ones too), only staged items of the array are used.  soff holds 65 ints of the wave's own.
 // ---------------------------------------------------------------------------
 constexpr int WALK_WINDOW = 64;
 constexpr int WALK_WAVE_ROWS = 64;
@@ -417,7 +418,7 @@ __device__ __forceinline__ void walk_rows(Op& op, const int* __restrict__ off, i
     int w0 = 0, w1 = 0;  // the items in the window
     for (int g = 0; g < n; g += map.rows) {
         const bool on = on_row && g + r < n;
-        const int s = soff[min(g + r, n)], e = on ? soff[min(g + r + 1, n)] : s;
+        const int s = soff[min(g + r, n)], e = on ? min(soff[min(g + r + 1, n)], last) : s;
         const int ge = __builtin_amdgcn_readfirstlane(soff[min(g + map.rows, n)]);
         int from = __builtin_amdgcn_readfirstlane(soff[g]);
         op.begin(row0 + g + r, on, e - s);

@@ -413,6 +413,30 @@ def test_rows_beyond_24_bit_numbers(pk, ctx):
     assert not t1[:shift].any() and not t0[: poff[0]].any()
 
 
+@pytest.mark.parametrize("C,T", [(3, 2), (8, 6), (64, 6), (300, 13)])
+def test_offsets_that_descend_stay_inside_the_arrays(pk, ctx, C, T):
+    """Offsets are the caller's: past row 3000 they are random here.  Rows in front of these (by more than a wave's rows) are
+    as ever; the others are means of some of the items, no larger than the largest."""
+    V, F = meshgen.noisy_grid(80, 50, seed=4, noise=0.02)
+    N, nF, cut = V.shape[0], F.shape[0], 3000
+    rng = np.random.default_rng(C)
+    y, x, w3, wt, bary = (dev(rng.normal(size=s).astype(np.float32)) for s in ((nF, C), (N, C), (3, C), (T, C), (3 * nF, 3)))
+    tex = dev(rng.normal(size=(3 * nF, C)).astype(np.float32))
+    pi = dev(softmax(rng.normal(size=(nF, T)), axis=1).astype(np.float32))
+    off, cor = ctx.picasso_vertex_corner_csr(dev(F), N)
+    bad = off.clone()
+    bad[cut:] = dev(rng.integers(-9, 3 * nF + 9, N + 1 - cut).astype(np.int32))
+    print(f"descending offsets C={C} T={T}", flush=True)
+    good_x, bad_x = (ctx.picasso_f2v_forward(y, pi, wt, o, cor, N) for o in (off, bad))
+    (good_g, _), (bad_g, bad_gw) = (ctx.picasso_v2f_backward(y, x, dev(F), None, w3, o, cor) for o in (off, bad))
+    good_t, bad_t = (ctx.picasso_f2f_forward(tex, bary, o[:-1].contiguous(), w3) for o in (off, bad))   # (points in facets' place)
+    for good, got in ((good_x, bad_x), (good_g, bad_g), (good_t, bad_t)):
+        assert torch.equal(good[: cut - 64], got[: cut - 64]) and torch.isfinite(got).all()
+    assert torch.isfinite(bad_gw).all()
+    assert bad_x.abs().max() <= 1.001 * (pi @ wt.abs()).max() * y.abs().max()
+    assert bad_t.abs().max() <= 1.001 * (bary.abs() @ w3.abs()).max() * tex.abs().max()
+
+
 @pytest.mark.parametrize("sizes", [[1500, 1, 0, 3000, 7, 1024, 40], [5] * 300, [4096, 1]])
 def test_levels_of_meshes_across_workgroups(pk, oracle, sizes):
     """Facet levels where meshes end inside a workgroup's facets, are empty, or more than a launch carries."""
