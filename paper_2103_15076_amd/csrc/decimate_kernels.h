@@ -1523,7 +1523,7 @@ struct JoinKeys {
     __device__ __forceinline__ void release(int w, int) const { abid[w] = ABID_NONE; }
 };
 
-// Meshes with at most `cap` keys (<= CAP): one workgroup per mesh finds the cost key of the budget's last pair, its top 12 bits
+// Meshes with at most `longer_than` keys (<= cap <= CAP where any has more): one workgroup per mesh finds the cost key of the budget's last pair, its top 12 bits
 // by counts in LDS, the others among the keys that share them, listed in LDS in any order, digit by digit (8 bits at a
 // time from the highest bit in which they differ at all); where the budget ends among equal keys, the last tie-break value in the
 // same way; and (few keys) walks the vertices once more to release what lies beyond.  Bound by the trips to LDS and memory of one compute unit; 16 vertices per lane are in flight.
@@ -1544,7 +1544,7 @@ __device__ __forceinline__ bool beyond(const Keys& K, const KeyLimit& L, u32 cos
 template <class Keys, int CAP>
 __global__ __launch_bounds__(TRUNC_THREADS) void trunc_mesh_kernel(Keys K, const int* __restrict__ voff,
                                                                    const int* __restrict__ counts,
-                                                                   const int* __restrict__ budgets, int cap, int longer_follow,
+                                                                   const int* __restrict__ budgets, int cap, int longer_than,
                                                                    const int* __restrict__ guard, State* st, HostSignal tell,
                                                                    KeyLimit* __restrict__ limits) {
     constexpr int Q = 16, COPIES = 16, TOP_SHIFT = 20;
@@ -1561,10 +1561,11 @@ __global__ __launch_bounds__(TRUNC_THREADS) void trunc_mesh_kernel(Keys K, const
     if (guard && *guard == 0) return;  // queued ahead of the host's look, and the selection was not finished
     const int n = counts[b], keep = budgets[b];
     if (n <= keep) return;
+    if (n > longer_than) return;  // another kernel for these follows
     if (n > cap) {
-        // More keys than this instance holds (and no other kernel for them follows): the host never launches it so.
+        // More keys than this instance holds: the host never launches it so.
         // Nothing is released, and the call is made to fail instead of returning a budget that was not applied.
-        if (!longer_follow && tid == 0) atomicOr(&st->err, ERR_BIT_INTERNAL);
+        if (tid == 0) atomicOr(&st->err, ERR_BIT_INTERNAL);
         return;
     }
     const int v0 = voff[b], v1 = voff[b + 1];
@@ -1798,12 +1799,13 @@ struct SelectSlot {
         u32 cost, below, tie, tie_below, stay, all;
     } at[SELECT_PASSES + 1];
 };
-// A mesh's slot.  A key stands at a vertex of its own (a pair at its lower one, a vertex that could join at itself), so meshes
-// of more than 2^SELECT_SLOT_BITS keys start more than 2^SELECT_SLOT_BITS vertices apart: no two of them share a slot.
-constexpr int SELECT_SLOT_BITS = 15;
-static_assert(1 << SELECT_SLOT_BITS == TRUNC_BLOCK_CAP, "in a batch only meshes of more than TRUNC_BLOCK_CAP keys come here");
-inline int select_slots_for(size_t n_verts, int B) { return B > 1 ? (int)(n_verts >> SELECT_SLOT_BITS) + 1 : 1; }
-__device__ __forceinline__ int select_slot(const int* voff, int B, int b) { return B == 1 ? 0 : voff[b] >> SELECT_SLOT_BITS; }
+// A mesh's slot: its own for up to SELECT_MESHES meshes, else (98 KB a slot, cleared for every such step) by where it starts.
+// A key stands at a vertex of its own (a pair at its lower one, a vertex that could join at itself), so meshes of more than
+// 2^SELECT_SLOT_BITS keys start more than 2^SELECT_SLOT_BITS vertices apart, and no two of them share a slot.
+constexpr int SELECT_SLOT_BITS = 15, SELECT_MESHES = 64;
+static_assert(1 << SELECT_SLOT_BITS == TRUNC_BLOCK_CAP, "with slots by start only meshes of more than TRUNC_BLOCK_CAP keys come here");
+inline int select_slots_by_start(long long n_verts) { return (int)(n_verts >> SELECT_SLOT_BITS) + 1; }
+__device__ __forceinline__ int select_slot(const int* voff, int by_start, int b) { return by_start ? voff[b] >> SELECT_SLOT_BITS : b; }
 __device__ __forceinline__ int select_shift(int j, int bits) { return max(0, bits - SELECT_BITS * (j + 1)); }
 __device__ __forceinline__ int select_width(int j, int bits) { return min(SELECT_BITS, bits - SELECT_BITS * j); }
 
@@ -1849,9 +1851,10 @@ __device__ __forceinline__ auto select_pick(const SelectSlot& S, int pass, u32 k
 
 constexpr int SELECT_ITEMS = 8;
 template <class Keys>
-__global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* __restrict__ voff, int B,
+__global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* __restrict__ voff,
                                                             const int* __restrict__ counts, const int* __restrict__ budgets,
-                                                            int longer_than, SelectSlot* __restrict__ slots, int pass, int tie_bits) {
+                                                            int longer_than, SelectSlot* __restrict__ slots, int by_start, int pass,
+                                                            int tie_bits) {
     __shared__ u32 h[SELECT_BINS];
     __shared__ u32 smem[prim::WAVES], picked[3];
     const int b = blockIdx.y, n = counts[b], keep = budgets[b];
@@ -1859,7 +1862,7 @@ __global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* _
     const int v0 = voff[b], v1 = voff[b + 1], t = threadIdx.x;
     const long long base = (long long)v0 + (long long)blockIdx.x * (BLOCK * SELECT_ITEMS);
     if (base >= v1) return;
-    SelectSlot& S = slots[select_slot(voff, B, b)];
+    SelectSlot& S = slots[select_slot(voff, by_start, b)];
     const auto a = select_pick(S, pass, (u32)keep, tie_bits, smem, picked);
     if (blockIdx.x == 0 && t == 0) S.at[pass] = a;
     const bool tie = pass >= SELECT_COST_PASSES;
@@ -1894,10 +1897,10 @@ __global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* _
 
 // ... and the release: `passes` = passes made.
 template <class Keys>
-__global__ __launch_bounds__(BLOCK) void select_release_kernel(Keys K, const int* __restrict__ voff, int B,
+__global__ __launch_bounds__(BLOCK) void select_release_kernel(Keys K, const int* __restrict__ voff,
                                                                const int* __restrict__ counts, const int* __restrict__ budgets,
-                                                               int longer_than, const SelectSlot* __restrict__ slots, int passes,
-                                                               int tie_bits) {
+                                                               int longer_than, const SelectSlot* __restrict__ slots, int by_start,
+                                                               int passes, int tie_bits) {
     __shared__ u32 smem[prim::WAVES], picked[3];
     const int b = blockIdx.y, n = counts[b], keep = budgets[b];
     if (n <= keep || n <= longer_than) return;
@@ -1905,7 +1908,7 @@ __global__ __launch_bounds__(BLOCK) void select_release_kernel(Keys K, const int
     const long long base = (long long)v0 + (long long)blockIdx.x * (BLOCK * SELECT_ITEMS);
     if (base >= v1) return;
     const bool none = keep <= 0;
-    const SelectSlot& S = slots[select_slot(voff, B, b)];
+    const SelectSlot& S = slots[select_slot(voff, by_start, b)];
     const auto a = select_pick(S, none ? 0 : passes, (u32)keep, tie_bits, smem, picked);
 #pragma unroll
     for (int i = 0; i < SELECT_ITEMS; ++i) {

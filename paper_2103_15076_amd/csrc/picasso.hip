@@ -97,7 +97,6 @@ struct picasso_ctx {
     int* nrem = nullptr;
     int* matched = nullptr;
     SelectSlot* select_slots = nullptr;  // the budget step's counts (long runs, see budget_step)
-    int n_select_slots = 1;
     KeyLimit* limits = nullptr;  // per mesh (see budget_step)
     int* mslots = nullptr;
     LiveEdge* live = nullptr;  // the selection tail's list (see SelArgs) and its segments' lengths
@@ -235,8 +234,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     }
     x->voff[1] = cv.take<int>(b + 1);
     x->nrem = cv.take<int>(b);
-    x->n_select_slots = select_slots_for(n, B);
-    x->select_slots = cv.take<SelectSlot>((size_t)x->n_select_slots);
+    x->select_slots = cv.take<SelectSlot>(B > SELECT_MESHES ? (size_t)std::max(SELECT_MESHES, select_slots_by_start((long long)n)) : b);
     x->limits = cv.take<KeyLimit>(b);
     x->mslots = cv.take<int>(b * MATCH_SLOTS * MATCH_PAD);
     x->live = cv.take<LiveEdge>((size_t)LIVE_SEGS * TAIL_MAX);
@@ -559,34 +557,36 @@ int status_from_err_bits(int bits) {
 template <class Keys>
 int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* voff, int nv_max, int most, int least,
                 const int* counts, const int* budgets, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
-    // (in a batch the limit is what a workgroup holds, whatever the option says: see select_slot)
-    const int limit = B == 1 ? (int)c->opt_trunc_block_max : TRUNC_BLOCK_CAP;
+    // (where the slots of the counts go by the meshes' starts the limit is what a workgroup holds, whatever the option says: see select_slot)
+    const int by_start = B > SELECT_MESHES;
+    const int limit = by_start ? TRUNC_BLOCK_CAP : (int)c->opt_trunc_block_max;
     const bool longer = most > limit;
     if (guarded && longer) return PICASSO_ERR_INVALID_ARG;
     if (least <= limit) {
         const int* guard = guarded ? &c->st->go : nullptr;
         const int need = std::min(most, limit);
+        const int longer_than = longer ? limit : 0x7FFFFFFF;
         int cap = need <= TRUNC_SMALL_CAP ? TRUNC_SMALL_CAP : TRUNC_BLOCK_CAP;
         if (c->opt_trunc_width) cap = c->opt_trunc_width * TRUNC_THREADS;  // (test hook)
         if (cap <= TRUNC_SMALL_CAP)
-            trunc_mesh_kernel<Keys, TRUNC_SMALL_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer ? 1 : 0,
+            trunc_mesh_kernel<Keys, TRUNC_SMALL_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer_than,
                                                                                 guard, c->st, tell, nullptr);
         else {
-            trunc_mesh_kernel<Keys, TRUNC_BLOCK_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer ? 1 : 0,
+            trunc_mesh_kernel<Keys, TRUNC_BLOCK_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer_than,
                                                                                 guard, c->st, tell, c->limits);
             trunc_release_kernel<Keys><<<grid_for(nv_max), BLOCK, 0, s>>>(K, nv_max, voff, B, c->limits);
         }
     }
     if (longer) {
         SelectSlot* S = c->select_slots;
-        const long long words = (long long)(B == 1 ? 1 : c->n_select_slots) * (long long)(sizeof(SelectSlot) / sizeof(u32));
+        const long long words = (long long)(by_start ? select_slots_by_start(nv_max) : B) * (long long)(sizeof(SelectSlot) / sizeof(u32));
         prim::fill_u32_kernel<<<grid_for(words), BLOCK, 0, s>>>(reinterpret_cast<u32*>(S), (int)words, 0u);
         const int tie_bits = Keys::TIE_BY_VERTEX ? ceil_log2(nv_max) : 32;
         const int passes = SELECT_COST_PASSES + (tie_bits + SELECT_BITS - 1) / SELECT_BITS;
         const dim3 grid((unsigned)((nv_max + BLOCK * SELECT_ITEMS - 1) / (BLOCK * SELECT_ITEMS)), (unsigned)B);
         for (int p = 0; p < passes; ++p)
-            select_pass_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, B, counts, budgets, limit, S, p, tie_bits);
-        select_release_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, B, counts, budgets, limit, S, passes, tie_bits);
+            select_pass_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, p, tie_bits);
+        select_release_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, passes, tie_bits);
     }
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }

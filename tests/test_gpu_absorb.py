@@ -238,21 +238,32 @@ def _spiked_lattice(w, h, seed):
     ([_book(32771, 3), _book(32771, 4), _book(32771, 5)], [32768, 16000, 7]),   # 32,769: the fewest that take this path
     ([_spiked_lattice(105, 105, 1), _spiked_lattice(108, 108, 3)], [9000, 30000]),
 ], ids=["books", "smallest_books", "spiked_lattices"])
-def test_batch_of_meshes_with_more_candidates_than_one_workgroup_takes(pk, ctx, oracle, parts, left):
+@pytest.mark.parametrize("more", [0, 65])
+def test_batch_of_meshes_with_more_candidates_than_one_workgroup_takes(pk, oracle, parts, left, more):
     """Candidates stand at vertices, one each, so meshes not much larger than the limit of one workgroup exceed it: side by side
-    in a batch, each searched for its own budget by the whole chip."""
+    in a batch, each searched for its own budget by the whole chip.  more: tiny meshes behind them (beyond 64 meshes the
+    counts' places go by the meshes' starts)."""
+    parts, left = parts + [meshgen.noisy_grid(2, 2, seed=1)] * more, left + [-1] * more
     nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
     off = np.cumsum([0] + nv)
     V = np.concatenate([p[0] for p in parts])
     F = np.concatenate([p[1] + off[i] for i, p in enumerate(parts)]).astype(np.int32)
     tg = []
     for (Vi, Fi), l in zip(parts, left):
+        if l < 0:
+            tg.append(Vi.shape[0])
+            continue
         pairs = Vi.shape[0] - oracle.decimate(Vi, Fi, 1, max_rounds=1)["verts"].shape[0]
         joined = Vi.shape[0] - pairs - oracle.decimate(Vi, Fi, 1, max_rounds=1, absorb=True)["verts"].shape[0]
         assert joined > max(1 << 15, l)
         tg.append(Vi.shape[0] - pairs - l)
     print(f"line11 batch nv={nv} targets={tg}", flush=True)
-    st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg)
+    ctx = pk.Context(V.shape[0], F.shape[0], len(parts), device=0)
+    try:
+        ctx.set_option(pk.PICASSO_OPT_ABSORB, 1)
+        st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg)
+    finally:
+        ctx.close()
     assert st == 0 and nvo.tolist() == tg
     vo, fo, cid = vo.cpu().numpy(), fo.cpu().numpy(), cid.cpu().numpy()
     v0 = f0 = 0

@@ -227,6 +227,36 @@ def test_budget_step_every_way(pk, ctx, oracle, block_max, radix_select):
         ctx.set_option(pk.PICASSO_OPT_TRUNC_SELECT, 1)
 
 
+@pytest.mark.parametrize("meshes", [8, 64, 65])
+@pytest.mark.parametrize("block_max", [0, 40, 150, 1 << 15])
+def test_budget_step_of_a_batch_where_meshes_take_different_ways(pk, oracle, meshes, block_max):
+    """Meshes of about 10 to 480 pairs: with a limit in between, the short runs go to one workgroup each and the long ones
+    to the whole chip, in one call, and each is cut once.  (Beyond 64 meshes the option has no effect.)"""
+    kinds = [meshgen.noisy_grid(30, 34, seed=1), meshgen.flat_grid(9, 7, spacing=0.25), meshgen.icosphere(3, seed=2),
+             meshgen.flat_grid(25, 20, spacing=0.5), meshgen.noisy_grid(12, 12, seed=3), meshgen.icosphere(1, seed=5),
+             meshgen.noisy_grid(6, 9, seed=4), meshgen.flat_grid(18, 17, spacing=0.25)]
+    parts = [kinds[b % 8] for b in range(meshes)]
+    nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
+    off = np.cumsum([0] + nv)
+    V = np.concatenate([p[0] for p in parts])
+    F = np.concatenate([p[1] + off[i] for i, p in enumerate(parts)]).astype(np.int32)
+    ctx = pk.Context(V.shape[0], F.shape[0], meshes, device=0)
+    try:
+        ctx.set_option(pk.PICASSO_OPT_TRUNC_BLOCK_MAX, block_max)
+        for keep in (0.95, 0.7, 0.3):
+            tg = [int(n * keep) for n in nv]
+            print(f"budget of {meshes} meshes keep={keep} block_max={block_max}", flush=True)
+            st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg)
+            ref = oracle.decimate_batch(V, F, nv, nf, tg)
+            assert st == ref["status"]
+            assert nvo.tolist() == ref["nv"].tolist() == tg and nfo.tolist() == ref["nf"].tolist()
+            assert np.array_equal(cid.cpu().numpy(), ref["cluster_id"])
+            assert np.array_equal(fo.cpu().numpy(), ref["facets"])
+            assert np.array_equal(vo.cpu().numpy().view(np.uint32), ref["verts"].view(np.uint32))
+    finally:
+        ctx.close()
+
+
 def test_histogram_passes_of_the_budget_step_on_clustered_and_tied_cost_keys(pk, ctx, oracle):
     """A single mesh whose last round forms more pairs than the per-mesh search is allowed here: the
     cost key at the budget is found digit by digit.  Flat lattices (every cost key equal: the budget cuts

@@ -165,3 +165,32 @@ def test_budget_ends_inside_thousands_of_equal_costs(pk, ctx, oracle, seed, abso
         print(f"equal costs: N={V.shape[0]} target={target} seed={seed} absorb={absorb}", flush=True)
         st, vo, fo, cid = _run(pk, ctx, seed, lambda: ctx.picasso_decimate(dev(V), dev(F), target), absorb)
         _same(st, vo, fo, cid, oracle.decimate(V, F, target, shuffle_seed=seed, absorb=bool(absorb)))
+
+
+@pytest.mark.parametrize("absorb", [0, 1])
+def test_budget_steps_of_a_batch_under_the_shuffle_both_ways(pk, ctx, oracle, absorb):
+    """The tie-breaks of a batch go by its edge numbering, which is the first mesh's own for that mesh: every mesh comes first
+    once and is compared with the oracle, and by one workgroup per mesh and by the whole chip all of a batch is the same."""
+    parts = [meshgen.flat_grid(31, 27, spacing=0.25), meshgen.noisy_grid(30, 22, seed=1), meshgen.flat_grid(15, 15, spacing=0.5),
+             meshgen.room_scene(11, room=(3.0, 2.0, 1.5), n_boxes=2, spacing=0.1, jitter=0.0)]
+    for turn in range(4):
+        now = parts[turn:] + parts[:turn]
+        nv, nf = [p[0].shape[0] for p in now], [p[1].shape[0] for p in now]
+        off = np.cumsum([0] + nv)
+        V = np.concatenate([p[0] for p in now])
+        F = np.concatenate([p[1] + off[i] for i, p in enumerate(now)]).astype(np.int32)
+        for keep in (0.9, 0.6, 0.42):
+            tg = [int(n * keep) for n in nv]
+            ref = oracle.decimate(*now[0], tg[0], shuffle_seed=91, absorb=bool(absorb))
+            got = []
+            for block_max in (0, 60, 1 << 15):
+                print(f"shuffle batch budget turn={turn} keep={keep} block_max={block_max} absorb={absorb}", flush=True)
+                ctx.set_option(pk.PICASSO_OPT_TRUNC_BLOCK_MAX, block_max)
+                try:
+                    st, vo, fo, cid, nvo, nfo = _run(pk, ctx, 91, lambda: ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg), absorb)
+                finally:
+                    ctx.set_option(pk.PICASSO_OPT_TRUNC_BLOCK_MAX, 1 << 15)
+                assert st == 0 and nvo.tolist() == tg
+                _same(st, vo[: tg[0]], fo[: int(nfo[0])], cid[: nv[0]], ref)
+                got.append((vo, fo, cid))
+            assert all(torch.equal(a, b) for g in got[1:] for a, b in zip(got[0], g))
