@@ -1787,7 +1787,7 @@ __global__ __launch_bounds__(BLOCK) void trunc_release_kernel(Keys K, int nv, co
     if (K.has(raw) && beyond(K, limit, K.cost(raw), w, voff[b])) K.release(w, with);
 }
 
-// Longer runs: the same search by histogram passes over the mesh's vertices with the whole chip (blockIdx.y = mesh), three of
+// Longer runs: the same search by histogram passes over the mesh's vertices with the whole chip (blockIdx.y = mesh, from b0 on), three of
 // 12, 12 and 8 bits for the cost key and as many as the tie-break values have digits.  A pass's workgroups each pick the digit
 // that the pass before has decided from its counts (16 KB read from L2, no launch in between).
 constexpr int SELECT_BITS = 12, SELECT_BINS = 1 << SELECT_BITS, SELECT_COST_PASSES = 3, SELECT_PASSES = 6;
@@ -1803,6 +1803,7 @@ struct SelectSlot {
 // A key stands at a vertex of its own (a pair at its lower one, a vertex that could join at itself), so meshes of more than
 // 2^SELECT_SLOT_BITS keys start more than 2^SELECT_SLOT_BITS vertices apart, and no two of them share a slot.
 constexpr int SELECT_SLOT_BITS = 15, SELECT_MESHES = 64;
+constexpr int SELECT_GRID_MESHES = 1 << 15;  // meshes of a launch (a grid has at most 65,535 rows)
 static_assert(1 << SELECT_SLOT_BITS == TRUNC_BLOCK_CAP, "with slots by start only meshes of more than TRUNC_BLOCK_CAP keys come here");
 inline int select_slots_by_start(long long n_verts) { return (int)(n_verts >> SELECT_SLOT_BITS) + 1; }
 __device__ __forceinline__ int select_slot(const int* voff, int by_start, int b) { return by_start ? voff[b] >> SELECT_SLOT_BITS : b; }
@@ -1853,11 +1854,11 @@ constexpr int SELECT_ITEMS = 8;
 template <class Keys>
 __global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* __restrict__ voff,
                                                             const int* __restrict__ counts, const int* __restrict__ budgets,
-                                                            int longer_than, SelectSlot* __restrict__ slots, int by_start, int pass,
+                                                            int longer_than, SelectSlot* __restrict__ slots, int by_start, int b0, int pass,
                                                             int tie_bits) {
     __shared__ u32 h[SELECT_BINS];
     __shared__ u32 smem[prim::WAVES], picked[3];
-    const int b = blockIdx.y, n = counts[b], keep = budgets[b];
+    const int b = b0 + (int)blockIdx.y, n = counts[b], keep = budgets[b];
     if (n <= keep || n <= longer_than || keep <= 0) return;
     const int v0 = voff[b], v1 = voff[b + 1], t = threadIdx.x;
     const long long base = (long long)v0 + (long long)blockIdx.x * (BLOCK * SELECT_ITEMS);
@@ -1899,10 +1900,10 @@ __global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* _
 template <class Keys>
 __global__ __launch_bounds__(BLOCK) void select_release_kernel(Keys K, const int* __restrict__ voff,
                                                                const int* __restrict__ counts, const int* __restrict__ budgets,
-                                                               int longer_than, const SelectSlot* __restrict__ slots, int by_start,
+                                                               int longer_than, const SelectSlot* __restrict__ slots, int by_start, int b0,
                                                                int passes, int tie_bits) {
     __shared__ u32 smem[prim::WAVES], picked[3];
-    const int b = blockIdx.y, n = counts[b], keep = budgets[b];
+    const int b = b0 + (int)blockIdx.y, n = counts[b], keep = budgets[b];
     if (n <= keep || n <= longer_than) return;
     const int v0 = voff[b], v1 = voff[b + 1];
     const long long base = (long long)v0 + (long long)blockIdx.x * (BLOCK * SELECT_ITEMS);

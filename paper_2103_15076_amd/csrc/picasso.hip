@@ -583,10 +583,12 @@ int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* 
         prim::fill_u32_kernel<<<grid_for(words), BLOCK, 0, s>>>(reinterpret_cast<u32*>(S), (int)words, 0u);
         const int tie_bits = Keys::TIE_BY_VERTEX ? ceil_log2(nv_max) : 32;
         const int passes = SELECT_COST_PASSES + (tie_bits + SELECT_BITS - 1) / SELECT_BITS;
-        const dim3 grid((unsigned)((nv_max + BLOCK * SELECT_ITEMS - 1) / (BLOCK * SELECT_ITEMS)), (unsigned)B);
-        for (int p = 0; p < passes; ++p)
-            select_pass_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, p, tie_bits);
-        select_release_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, passes, tie_bits);
+        for (int b0 = 0; b0 < B; b0 += SELECT_GRID_MESHES) {
+            const dim3 grid((unsigned)((nv_max + BLOCK * SELECT_ITEMS - 1) / (BLOCK * SELECT_ITEMS)), (unsigned)std::min(B - b0, SELECT_GRID_MESHES));
+            for (int p = 0; p < passes; ++p)
+                select_pass_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, b0, p, tie_bits);
+            select_release_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, b0, passes, tie_bits);
+        }
     }
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }

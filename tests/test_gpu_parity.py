@@ -1011,3 +1011,25 @@ def test_budget_of_long_runs_in_a_batch(pk, oracle, flat):
         assert np.array_equal(vo.cpu().numpy().view(np.uint32), ref["verts"].view(np.uint32))
     finally:
         c.close()
+
+
+def test_budget_of_a_long_run_behind_more_meshes_than_a_grid_has_rows(pk, oracle):
+    """66,000 two-facet meshes and, behind them, one of 38,000 pairs whose budget binds."""
+    small, big = meshgen.noisy_grid(2, 2, seed=1), meshgen.noisy_grid(290, 285, seed=2)
+    k, (v, f) = 66000, small
+    nv, nf = [v.shape[0]] * k + [big[0].shape[0]], [f.shape[0]] * k + [big[1].shape[0]]
+    V = np.concatenate([np.tile(v, (k, 1)), big[0]])
+    F = np.concatenate([(f[None] + (4 * np.arange(k))[:, None, None]).reshape(-1, 3), big[1] + 4 * k]).astype(np.int32)
+    tg = [4] * k + [big[0].shape[0] - 36000]
+    ctx = pk.Context(V.shape[0], F.shape[0], len(nv), device=0)
+    try:
+        print(f"{len(nv)} meshes, {V.shape[0]} vertices", flush=True)
+        st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg)
+    finally:
+        ctx.close()
+    ref = oracle.decimate(*big, tg[-1])
+    assert st == ref["status"] == 0 and nvo.tolist() == tg and int(nfo[-1]) == ref["facets"].shape[0]
+    assert np.array_equal(vo.cpu().numpy()[4 * k:].view(np.uint32), ref["verts"].view(np.uint32))
+    assert np.array_equal(fo.cpu().numpy()[2 * k:], ref["facets"] + 4 * k)
+    assert np.array_equal(cid.cpu().numpy()[4 * k:], ref["cluster_id"] + 4 * k)
+    assert np.array_equal(vo.cpu().numpy()[: 4 * k], V[: 4 * k]) and np.array_equal(fo.cpu().numpy()[: 2 * k], F[: 2 * k])
