@@ -66,8 +66,7 @@ enum picasso_option {
     PICASSO_OPT_TRUNC_BLOCK_MAX = 5,/* budget step (Alg. 2 lines 3-4 and 6): a mesh that formed more
                                       pairs than it may remove keeps its cheapest ones; while no
                                       such mesh formed more than this many pairs (default and
-                                      largest value 32768, which is always the limit in a batch
-                                      of more than 64 meshes)
+                                      largest value 32768)
                                       one workgroup per mesh selects them,
                                       above it histogram passes over the mesh's vertices by the
                                       whole chip do.  Same result either way.                      */

@@ -1799,14 +1799,17 @@ struct SelectSlot {
         u32 cost, below, tie, tie_below, stay, all;
     } at[SELECT_PASSES + 1];
 };
-// A mesh's slot: its own for up to SELECT_MESHES meshes, else (98 KB a slot, cleared for every such step) by where it starts.
-// A key stands at a vertex of its own (a pair at its lower one, a vertex that could join at itself), so meshes of more than
-// 2^SELECT_SLOT_BITS keys start more than 2^SELECT_SLOT_BITS vertices apart, and no two of them share a slot.
-constexpr int SELECT_SLOT_BITS = 15, SELECT_MESHES = 64;
+// A mesh's slot.  A key stands at a vertex of its own (a pair at its lower one, a vertex that could join at itself), so meshes of
+// more than 2^SELECT_SLOT_BITS keys start more than 2^SELECT_SLOT_BITS vertices apart: they go by their starts, and no two share
+// a slot.  Where shorter runs come here too (the option that lowers the limit) the meshes take turns, SELECT_MESHES of
+// them at a time (98 KB a slot).
+constexpr int SELECT_SLOT_BITS = 15, SELECT_MESHES = 8;
 constexpr int SELECT_GRID_MESHES = 1 << 15;  // meshes of a launch (a grid has at most 65,535 rows)
-static_assert(1 << SELECT_SLOT_BITS == TRUNC_BLOCK_CAP, "with slots by start only meshes of more than TRUNC_BLOCK_CAP keys come here");
-inline int select_slots_by_start(long long n_verts) { return (int)(n_verts >> SELECT_SLOT_BITS) + 1; }
-__device__ __forceinline__ int select_slot(const int* voff, int by_start, int b) { return by_start ? voff[b] >> SELECT_SLOT_BITS : b; }
+static_assert(1 << SELECT_SLOT_BITS == TRUNC_BLOCK_CAP, "by default only meshes of more than TRUNC_BLOCK_CAP keys come here");
+inline int select_slots_by_start(int B, long long n_verts) { return B > 1 ? (int)(n_verts >> SELECT_SLOT_BITS) + 1 : 1; }
+__device__ __forceinline__ int select_slot(const int* voff, int by_start, int b) {
+    return by_start ? voff[b] >> SELECT_SLOT_BITS : (int)blockIdx.y;
+}
 __device__ __forceinline__ int select_shift(int j, int bits) { return max(0, bits - SELECT_BITS * (j + 1)); }
 __device__ __forceinline__ int select_width(int j, int bits) { return min(SELECT_BITS, bits - SELECT_BITS * j); }
 

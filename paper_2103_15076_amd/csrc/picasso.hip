@@ -234,7 +234,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     }
     x->voff[1] = cv.take<int>(b + 1);
     x->nrem = cv.take<int>(b);
-    x->select_slots = cv.take<SelectSlot>(B > SELECT_MESHES ? (size_t)std::max(SELECT_MESHES, select_slots_by_start((long long)n)) : b);
+    x->select_slots = cv.take<SelectSlot>((size_t)std::max(std::min((int)b, SELECT_MESHES), select_slots_by_start((int)b, (long long)n)));
     x->limits = cv.take<KeyLimit>(b);
     x->mslots = cv.take<int>(b * MATCH_SLOTS * MATCH_PAD);
     x->live = cv.take<LiveEdge>((size_t)LIVE_SEGS * TAIL_MAX);
@@ -557,9 +557,7 @@ int status_from_err_bits(int bits) {
 template <class Keys>
 int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* voff, int nv_max, int most, int least,
                 const int* counts, const int* budgets, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
-    // (where the slots of the counts go by the meshes' starts the limit is what a workgroup holds, whatever the option says: see select_slot)
-    const int by_start = B > SELECT_MESHES;
-    const int limit = by_start ? TRUNC_BLOCK_CAP : (int)c->opt_trunc_block_max;
+    const int limit = (int)c->opt_trunc_block_max;
     const bool longer = most > limit;
     if (guarded && longer) return PICASSO_ERR_INVALID_ARG;
     if (least <= limit) {
@@ -579,12 +577,16 @@ int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* 
     }
     if (longer) {
         SelectSlot* S = c->select_slots;
-        const long long words = (long long)(by_start ? select_slots_by_start(nv_max) : B) * (long long)(sizeof(SelectSlot) / sizeof(u32));
-        prim::fill_u32_kernel<<<grid_for(words), BLOCK, 0, s>>>(reinterpret_cast<u32*>(S), (int)words, 0u);
+        const int by_start = B == 1 || limit == TRUNC_BLOCK_CAP;  // (see select_slot)
+        const int slots = by_start ? select_slots_by_start(B, nv_max) : std::min(B, SELECT_MESHES);
+        const long long words = (long long)slots * (long long)(sizeof(SelectSlot) / sizeof(u32));
         const int tie_bits = Keys::TIE_BY_VERTEX ? ceil_log2(nv_max) : 32;
         const int passes = SELECT_COST_PASSES + (tie_bits + SELECT_BITS - 1) / SELECT_BITS;
-        for (int b0 = 0; b0 < B; b0 += SELECT_GRID_MESHES) {
-            const dim3 grid((unsigned)((nv_max + BLOCK * SELECT_ITEMS - 1) / (BLOCK * SELECT_ITEMS)), (unsigned)std::min(B - b0, SELECT_GRID_MESHES));
+        const int group = by_start ? SELECT_GRID_MESHES : SELECT_MESHES;
+        for (int b0 = 0; b0 < B; b0 += group) {
+            const dim3 grid((unsigned)((nv_max + BLOCK * SELECT_ITEMS - 1) / (BLOCK * SELECT_ITEMS)), (unsigned)std::min(B - b0, group));
+            if (b0 == 0 || !by_start)
+                prim::fill_u32_kernel<<<grid_for(words), BLOCK, 0, s>>>(reinterpret_cast<u32*>(S), (int)words, 0u);
             for (int p = 0; p < passes; ++p)
                 select_pass_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, b0, p, tie_bits);
             select_release_kernel<Keys><<<grid, BLOCK, 0, s>>>(K, voff, counts, budgets, limit, S, by_start, b0, passes, tie_bits);

@@ -241,8 +241,7 @@ def _spiked_lattice(w, h, seed):
 @pytest.mark.parametrize("more", [0, 65])
 def test_batch_of_meshes_with_more_candidates_than_one_workgroup_takes(pk, oracle, parts, left, more):
     """Candidates stand at vertices, one each, so meshes not much larger than the limit of one workgroup exceed it: side by side
-    in a batch, each searched for its own budget by the whole chip.  more: tiny meshes behind them (beyond 64 meshes the
-    counts' places go by the meshes' starts)."""
+    in a batch, each searched for its own budget by the whole chip.  more: tiny meshes behind them."""
     parts, left = parts + [meshgen.noisy_grid(2, 2, seed=1)] * more, left + [-1] * more
     nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
     off = np.cumsum([0] + nv)

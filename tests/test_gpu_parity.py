@@ -227,11 +227,11 @@ def test_budget_step_every_way(pk, ctx, oracle, block_max, radix_select):
         ctx.set_option(pk.PICASSO_OPT_TRUNC_SELECT, 1)
 
 
-@pytest.mark.parametrize("meshes", [8, 64, 65])
+@pytest.mark.parametrize("meshes", [7, 8, 9, 65])
 @pytest.mark.parametrize("block_max", [0, 40, 150, 1 << 15])
 def test_budget_step_of_a_batch_where_meshes_take_different_ways(pk, oracle, meshes, block_max):
     """Meshes of about 10 to 480 pairs: with a limit in between, the short runs go to one workgroup each and the long ones
-    to the whole chip, in one call, and each is cut once.  (Beyond 64 meshes the option has no effect.)"""
+    to the whole chip (eight meshes at a time), in one call, and each is cut once."""
     kinds = [meshgen.noisy_grid(30, 34, seed=1), meshgen.flat_grid(9, 7, spacing=0.25), meshgen.icosphere(3, seed=2),
              meshgen.flat_grid(25, 20, spacing=0.5), meshgen.noisy_grid(12, 12, seed=3), meshgen.icosphere(1, seed=5),
              meshgen.noisy_grid(6, 9, seed=4), meshgen.flat_grid(18, 17, spacing=0.25)]
