@@ -72,8 +72,8 @@ def test_decimate_with_line_11_matches_oracle(pk, ctx, oracle, name, mesh, frac,
 
 
 def test_budget_step_of_line_11_both_ways(pk, ctx, oracle):
-    """The joining vertices of a mesh are cut to the budget left by a per-mesh selection or by a
-    sort; both against the oracle, with distinct costs and with nothing but ties."""
+    """The joining vertices of a mesh are cut to the budget left by one workgroup or by histogram passes of the whole
+    chip; both against the oracle, with distinct costs and with nothing but ties."""
     for block_max in (0, 1 << 15):
         ctx.set_option(pk.PICASSO_OPT_TRUNC_BLOCK_MAX, block_max)
         try:

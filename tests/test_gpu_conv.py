@@ -10,9 +10,10 @@ with signed data, evaluated in binary32 in some fixed order, so
 which the oracle itself computes from the inputs' absolute values; n is the
 number of terms on the longest chain of additions (9 for a facet's bilinear
 form; the vertex degree times T for a vertex; for a filter gradient, which is
-summed in two stages -- up to 1,024 workgroups, each lane taking every R-th row
-of its workgroup's chunk, then a tree over the lanes and a serial sum over the
-workgroups -- at most 1,024 + rows / 1,024 + 64 times the 4-6 products of a row).
+summed in two stages -- up to some 1,500 workgroups, each lane taking every R-th row
+of its workgroup's chunk, then a tree over the lanes; a lane adding every 64th
+workgroup's sum, then a tree -- less than 1,024 + rows / 1,024 + 64 times the 4-6
+products of a row).
 """
 import numpy as np
 import pytest
@@ -235,7 +236,7 @@ def test_room115k_convolutions_at_full_size(pk, ctx, oracle):
 
 def test_features_at_addresses_that_are_not_16_byte_aligned(pk, ctx, oracle):
     """A channel count that is a multiple of 4 with feature arrays starting 4 bytes off a 16-byte
-    boundary: the entry points must fall back to one channel per lane."""
+    boundary: loads and stores ask for 4-byte alignment only."""
     V, F = meshgen.icosphere(3, seed=7, jitter=0.05)
     N, nF, C, T = V.shape[0], F.shape[0], 8, 3
     rng = np.random.default_rng(5)

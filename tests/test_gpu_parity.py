@@ -190,12 +190,12 @@ def test_decimate_matches_oracle(pk, ctx, oracle, name, mesh, frac, max_rounds):
 
 
 @pytest.mark.parametrize("block_max,radix_select", [(0, 0), (0, 1), (1 << 15, 1)],
-                         ids=["sorted", "histogram_passes", "per_mesh_search"])
+                         ids=["whole_chip", "whole_chip_old_option_on", "one_workgroup_per_mesh"])
 def test_budget_step_every_way(pk, ctx, oracle, block_max, radix_select):
-    """The last round keeps a mesh's cheapest pairs by a sort of all gathered pairs, by histogram passes
-    over their cost keys (a single mesh; the batch cases then take the sort) or by a search inside one
-    workgroup per mesh; all against the oracle, on meshes with distinct costs and with nothing but ties,
-    alone and in a batch (budgets of 1 pair, of all but 1 pair, and in between)."""
+    """The last round keeps a mesh's cheapest pairs by histogram passes of the whole chip over its vertices or by a
+    search inside one workgroup per mesh (PICASSO_OPT_TRUNC_SELECT is accepted and changes nothing); against the
+    oracle, on meshes with distinct costs and with nothing but ties, alone and in a batch (budgets of 1 pair, of
+    all but 1 pair, and in between)."""
     ctx.set_option(pk.PICASSO_OPT_TRUNC_BLOCK_MAX, block_max)
     ctx.set_option(pk.PICASSO_OPT_TRUNC_SELECT, radix_select)
     try:
@@ -455,8 +455,8 @@ def test_config_full_size(ctx, oracle, name):
 
 
 def test_single_stream_and_two_stream_first_round_agree(pk, ctx):
-    """Above 2^18 facets the first round's edge sort runs beside the quadric sums on a second
-    stream; both schedules must give the same bytes, call after call."""
+    """The first round's edge sort shares its launches with the sort for the vertex quadrics, or (option off) follows
+    it; both schedules must give the same bytes, call after call."""
     c = meshgen.config("scene1p2m")
     V, F, target = dev(c["verts"]), dev(c["facets"]), int(c["target"][0])
     res = []
@@ -533,9 +533,9 @@ def test_batch_of_more_meshes_than_the_tail_tallies_in_lds(pk, oracle):
 
 
 def test_beyond_the_bucket_sorts(pk, oracle):
-    """2.85 M facets = 8.5 M half-edges, more than the bucket sorts take (2^23 keys): the first round's
-    incidence and edge keys are written out and sorted by plain LSD passes, the later rounds drop
-    back into the bucket sorts.  Own context (the shared one is smaller)."""
+    """2.85 M facets = 8.5 M half-edges, more than are partitioned on 12 bits (2^23 keys): the first round's
+    incidence and edge keys are partitioned on a wider digit, whose counts lie in memory; the later rounds drop
+    back to 12 bits.  Own context (the shared one is smaller)."""
     V, F, _ = meshgen.room_scene_sized(31, 1_500_000, room=(30.0, 20.0, 3.0), n_boxes=300)
     assert 3 * F.shape[0] > (1 << 23)
     target = V.shape[0] // 2
@@ -552,8 +552,8 @@ def test_beyond_the_bucket_sorts(pk, oracle):
 @pytest.mark.parametrize("what", ["scrambled", "few_vertices"])
 def test_very_large_sorts_without_locality(pk, oracle, what):
     """More than 2^23 half-edges where a tile of keys holds as many leading digits as keys (random vertex numbers and
-    facet order: digits that find no place in the tile's table), and on so few vertices that the keys have no
-    more bits than the digit (plain LSD passes)."""
+    facet order: digits that find no place in the tile's table), and on so few vertices that the keys would have no
+    more bits than the digit (they are made wider)."""
     rng = np.random.default_rng(5)
     if what == "scrambled":
         V, F, _ = meshgen.room_scene_sized(31, 1_500_000, room=(30.0, 20.0, 3.0), n_boxes=300)
@@ -643,8 +643,8 @@ def test_on_a_stream_of_the_callers(pk, ctx, oracle):
 @pytest.mark.parametrize("w,h,what", [
     (419, 419, "just below 2^20 half-edges: 256-bucket sort, one lane per edge in every sub-round"),
     (420, 419, "just above 2^20 half-edges: 4096-bucket sort, sparse sub-rounds"),
-    (363, 362, "just below 2^18 facets: one stream"),
-    (364, 363, "just above 2^18 facets: the first round's edge sort on the second stream"),
+    (363, 362, "just below 2^18 facets"),
+    (364, 363, "just above 2^18 facets"),
 ])
 def test_sizes_on_either_side_of_the_path_switches(ctx, oracle, w, h, what):
     V, F = meshgen.noisy_grid(w, h, seed=w + h, noise=0.004)
@@ -656,8 +656,8 @@ def test_sizes_on_either_side_of_the_path_switches(ctx, oracle, w, h, what):
 
 @pytest.mark.parametrize("w,keys_per_lane", [(64, 4), (120, 8), (168, 16), (240, 32)])
 def test_every_width_of_the_per_mesh_budget_search(ctx, oracle, w, keys_per_lane):
-    """One run that forms about 0.45 N pairs and may keep a few hundred, or all but a few: the
-    search kernel holds 4, 8, 16 or 32 cost keys per lane depending on how many pairs formed."""
+    """One run that forms about 0.45 N pairs and may keep a few hundred, or all but a few, with up to 4, 8, 16 and 32 x 1024
+    pairs: one instance of the search releases them itself (up to 4,096), the other leaves it to a kernel of its own."""
     V, F = meshgen.noisy_grid(w, w, seed=w, noise=0.01)
     N = V.shape[0]
     E = oracle.edges(F)
@@ -811,7 +811,7 @@ def test_two_contexts_on_two_host_threads(pk, oracle):
 
 def test_ten_million_vertices(pk, oracle):
     """10.2 M vertices, 20.5 M facets, 61 M half-edges (a 6 GiB workspace): every index that is
-    multiplied by a record size goes beyond 2^31 bytes, the sorts run as plain radix passes over
+    multiplied by a record size goes beyond 2^31 bytes, the sorts partition on 16 bits and more over
     tens of thousands of tiles.  About 15 s of oracle time."""
     V, F = meshgen.noisy_grid(3200, 3200, seed=5, noise=0.004)
     target = V.shape[0] // 4
@@ -899,8 +899,7 @@ def test_hand_worked_fixtures_on_the_gpu(pk, ctx, fixture):
 
 
 def test_budget_search_refuses_sizes_it_was_not_launched_for(pk, ctx, oracle):
-    """The per-mesh budget step holds 4, 8, 16 or 32 cost keys per lane of a 1024-lane workgroup.  Forced
-    (test hook) to 4 on a mesh that forms more than 4096 pairs, the kernel must make the call fail with
+    """The per-mesh budget step is launched for up to 4,096 or 32,768 pairs a mesh.  Forced (test hook) to 4 x 1,024 on a mesh that forms more than 4096 pairs, the kernel must make the call fail with
     PICASSO_ERR_INTERNAL rather than return with the budget not applied; the context stays usable."""
     V, F = meshgen.noisy_grid(130, 120, seed=17)          # 15,600 vertices: about 7,000 pairs per round
     target = int(V.shape[0] * 0.62)                       # the budget binds in the first round

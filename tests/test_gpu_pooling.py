@@ -108,7 +108,7 @@ def test_cluster_csr_and_all_ops(pk, ctx, oracle, n_in, n_out, C):
 
 def test_empty_clusters_ties_and_unaligned_channels(pk, ctx, oracle):
     rng = np.random.default_rng(9)
-    n_in, n_out, C = 300, 200, 5            # C not a multiple of 4: scalar path; many empty clusters
+    n_in, n_out, C = 300, 200, 5            # C not a multiple of 4: a last pack of one channel; many empty clusters
     cid = _clusters(rng, n_in, n_out, empty=True)
     x = rng.integers(-2, 3, size=(n_in, C)).astype(np.float32)   # many exact ties for the argmax rule
     off, mem = ctx.picasso_cluster_csr(dev(cid), n_out)
@@ -123,9 +123,8 @@ def test_empty_clusters_ties_and_unaligned_channels(pk, ctx, oracle):
 
 
 def test_features_at_addresses_that_are_not_16_byte_aligned(pk, ctx, oracle):
-    """C a multiple of 4 with feature arrays 4 bytes off a 16-byte boundary: one channel per lane is
-    used instead of four; sums run in the same order either way, so the results are bit-identical
-    to those from aligned arrays."""
+    """C a multiple of 4 with feature arrays 4 bytes off a 16-byte boundary (loads and stores ask for 4-byte alignment
+    only): the results are bit-identical to those from aligned arrays."""
     rng = np.random.default_rng(21)
     n_in, n_out, C = 3001, 700, 8
     cid = _clusters(rng, n_in, n_out)

@@ -75,11 +75,11 @@ def test_decimate_with_shuffle_matches_oracle(pk, ctx, oracle, name, mesh, seed,
         assert not np.array_equal(ref["cluster_id"], oracle.decimate(V, F, target)["cluster_id"])
 
 
-@pytest.mark.parametrize("block_max", [0, 1 << 15], ids=["sorted", "per_mesh_select"])
+@pytest.mark.parametrize("block_max", [0, 1 << 15], ids=["whole_chip", "one_workgroup_per_mesh"])
 @pytest.mark.parametrize("absorb", [0, 1])
 def test_budget_steps_under_the_shuffle_both_ways(pk, ctx, oracle, block_max, absorb):
-    """Where the budget ends inside a run of equal costs the tie-break decides who stays: by the
-    per-mesh selection and by the sort, for the pairs and for the vertices of line 11."""
+    """Where the budget ends inside a run of equal costs the tie-break decides who stays: by
+    one workgroup and by the whole chip, for the pairs and for the vertices of line 11."""
     ctx.set_option(pk.PICASSO_OPT_TRUNC_BLOCK_MAX, block_max)
     try:
         for name, (V, F) in _meshes():
