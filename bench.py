@@ -89,7 +89,7 @@ def main():
                     help="the host waits by synchronising the stream (PICASSO_OPT_HOST_POLL = 0) instead of "
                          "watching the word its last kernel writes to pinned memory")
     ap.add_argument("--single-stream", action="store_true",
-                    help="keep the first round's edge sort on the caller's stream (PICASSO_OPT_OVERLAP = 0)")
+                    help="the first round's edge sort in launches of its own (PICASSO_OPT_OVERLAP = 0)")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py: this build measures ONE GPU only (the path shards by mesh: with more GPUs every rank "

@@ -17,8 +17,8 @@
  *     decimate calls return when everything they queued on that stream has been
  *     done: all outputs are complete (they wait for their last kernel, see
  *     PICASSO_OPT_HOST_POLL).
- *   - A context owns its scratch workspace, a small pinned host buffer that its
- *     kernels write counters into, and one internal stream of default priority;
+ *   - A context owns its scratch workspace and a small pinned host buffer that its
+ *     kernels write counters into; it creates no streams;
  *     it is bound to one device, which the calls make current; calls on one
  *     context must not overlap in time.  Contexts share no state: different
  *     contexts may be used from different host threads at the same time.
@@ -116,8 +116,8 @@ enum picasso_option {
                                       to need more passes.  0: queued after the look.  Same
                                       results.                                                   */
     PICASSO_OPT_TRUNC_WIDTH = 12,  /* test hook for the per-mesh budget step: 0 (default) = its
-                                      workgroups hold 4, 8, 16 or 32 cost keys per lane (x 1024
-                                      lanes) as the largest mesh needs; 4, 8, 16 or 32 = always
+                                      workgroups take up to 4,096 or 32,768 cost keys as the
+                                      largest mesh needs; 4, 8, 16 or 32 = always 1,024 times
                                       that many, so that a mesh with more pairs than fit makes
                                       the kernel report it and the call return
                                       PICASSO_ERR_INTERNAL instead of a wrong budget.            */
@@ -183,9 +183,12 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  *                 read once) + 8 nv (one bid word per vertex).
  *   SUBROUND0     first grid-wide sub-round of the selection (Alg. 2 lines 3-10): 13 E read, E
  *                 written (edge states), 3 x 8 nv (bids read, next bids written, third array cleared).
- *   FACET_INSERT  facets re-indexed (after the last round also entered into the hash set), cluster
- *                 labels composed: 12 nf read + 12 nf re-indexed + 4 nv (vertex map) + 8 N (labels
- *                 read and written).
+ *   FACET_INSERT  the kernel that takes the facets to the numbering a round leaves.  Behind every round but the
+ *                 last edge_keys_kernel (facets re-indexed in place, labels composed, the next round set up,
+ *                 edge keys' digits counted): 24 nf + 4 nv (vertex map) + 8 N (labels) + 24 nv' (two bid words,
+ *                 mate and pair cost for each of the nv' vertices left).  Behind the last final_facets_kernel
+ *                 (the same, facets entered into the hash set, positions written): 28 nf (a slot number
+ *                 each) + 4 nv + 8 N + 28 nv'.
  *   QUADRIC_ROWS  vertex quadrics summed from the facets' planes (supplementary, vertex quadric
  *                 equation): 8 x 3F sorted incidences + 16 F planes + 12 N positions + 64 N records.
  *   SORT_INCIDENCE per-bucket kernel of the sort that brings the 3F (vertex, facet) incidence keys
@@ -299,7 +302,7 @@ int picasso_replace_mapping_static(int device, void* stream, const int32_t* d_cl
 
 /* Member lists of the clusters: d_offsets [n_out+1], d_members [n_in] (members of
  * cluster c = d_members[d_offsets[c] .. d_offsets[c+1]), ascending).  Built with a
- * stable radix sort of (cluster_id, vertex).  Waits for its work on the stream (as
+ * sort of (cluster_id, vertex) keys.  Waits for its work on the stream (as
  * the decimate calls do); returns
  * PICASSO_ERR_BAD_INDEX if an id lies outside [0, n_out).  n_in <= 3*max_facets
  * and n_out <= max_verts of the context. */

@@ -1,6 +1,6 @@
 """MI355X-native QEM mesh decimation (the decimation hot path of the Picasso paper).
 
-``binding`` is the ctypes front end of the HIP library (include/picasso.h);
+``binding`` is the Python front end of the HIP library (include/picasso.h);
 ``meshgen`` holds the seeded synthetic inputs; ``build`` compiles the library.
 Importing the package does not load the library; the first call does, and it
 raises if the library is missing (there is no CPU fallback).

@@ -1,8 +1,9 @@
-"""Thin ctypes binding of include/picasso.h: argument marshalling only.
+"""Python binding of include/picasso.h: argument marshalling only.
 
-torch supplies device memory and the stream; every step of the path runs in
-libpicasso_hip.so.  There is no fallback: if the library is missing or cannot
-be loaded, ``load_library`` raises.
+The calls of a step (decimation, pooling, convolutions) go through the compiled
+module _host (csrc/host.cpp), the others through ctypes.  torch supplies device
+memory and the stream; every step of the path runs in libpicasso_hip.so.  There
+is no fallback: if the library is missing or cannot be loaded, ``load_library`` raises.
 """
 from __future__ import annotations
 
@@ -42,9 +43,9 @@ PICASSO_PLACE_MEAN, PICASSO_PLACE_INVERSE = 0, 1
  PICASSO_KERNEL_QUADRIC_ROWS, PICASSO_KERNEL_SORT_INCIDENCE, PICASSO_KERNEL_COUNT) = range(7)
 TIMED_KERNEL_NAMES = (
     "bucket_keys_kernel<u64> (edge-key sort, per-bucket LDS sort)",
-    "tile_scatter_kernel<UniquePred, UniqueOut> (distinct edges, costs, first bids)",
+    "unique_cost_kernel (distinct edges, costs, first bids)",
     "select_subround_kernel (first sub-round of the selection)",
-    "facet_insert_kernel (facet hash set, label compose)",
+    "edge_keys_kernel, final_facets_kernel (facets and labels re-indexed behind a round; behind the last: facet hash set)",
     "quadric_rows_kernel (vertex quadrics from facet planes)",
     "bucket_keys_kernel<u64> (incidence-key sort of the vertex quadrics, per-bucket LDS sort)",
 )

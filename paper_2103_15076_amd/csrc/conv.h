@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "pooling.h"
+#include "primitives.h"
 
 #pragma clang fp contract(off)
 
@@ -42,16 +43,14 @@ using pool::store_row;
 // cannot reach outside the arrays: it is read as index 0.
 __device__ __forceinline__ int in_range_or_zero(int i, int n) { return ((unsigned)i < (unsigned)n) ? i : 0; }
 
-// Workgroups are handed to the 8 accelerator dies in turn, and each die has its own L2.  The rows that
-// neighbouring vertices and facets gather overlap (mesh numbering has locality), so the kernels deal their work
-// out in 8 contiguous parts, one per die: workgroup b works as number (b % 8) * (G / 8) + b / 8 of a
-// grid of G workgroups, G a multiple of 8 (otherwise as number b).
+// The number a workgroup works as: the rows that neighbouring vertices and facets gather overlap (mesh numbering has locality), so
+// each of the 8 XCDs, to which workgroups go in turn, takes one eighth of the grid's work in a row.  For grids of
+// prim::xcd_grid workgroups; others are left in order (prim::xcd_tile: the same where the amount of work is known on the device only).
 __device__ __forceinline__ int xcd_block() {
     if (gridDim.x & 7u) return (int)blockIdx.x;
     const unsigned g8 = gridDim.x >> 3;
     return (int)((blockIdx.x & 7u) * g8 + (blockIdx.x >> 3));
 }
-inline dim3 xcd_grid(dim3 g) { return dim3((g.x + 7) / 8 * 8, g.y); }
 
 // The two indexes off[v], off[v + 1] and the three of a facet in one load each.
 struct __attribute__((packed, aligned(4))) Int2 { int a, b; };
@@ -623,7 +622,7 @@ __global__ __launch_bounds__(BLOCK) void v2f_backward_kernel(const float* __rest
 // Gamma_f texture points with features of their own and barycentric coordinates;
 // only the filter is interpolated, W_k = sum_s xi_ks w_s, and J_f = (1 / Gamma_f)
 // sum_k W_k T_k.  Points of facet f = poff[f] .. poff[f+1]; tex [P,C], bary [P,3].
-// One lane owns VEC channels of one facet and walks the facet's points in order.
+// A facet's points are walked as above (walk_rows), forward; backward they are rows of their own.
 // ---------------------------------------------------------------------------
 template <int KIND>
 __device__ __forceinline__ Float3 load_bary(const float* __restrict__ bary, int k) {

@@ -40,8 +40,8 @@ struct State {
     int absorb_n;  // edges through which an un-paired vertex would join a pair's cluster (Alg. 2 line 11)
     int nv_kept;   // output vertices that some output facet refers to (option: degenerated vertices dropped)
     // Written by every selection tail for kernels that the host queued behind it before looking
-    // (they run only if the tail finished the matching): 1 / nv / ne of the round then, else zeros.
-    int go, guard_nv, guard_ne;
+    // (they run only if the tail finished the matching): 1 / nv of the round then, else zeros.
+    int go, guard_nv;
 };
 
 // One vertex = 64 bytes: position and the 10 quadric coefficients.
@@ -1260,7 +1260,6 @@ __device__ __forceinline__ void tail_publish(const SelArgs& A, int tid) {
 __device__ __forceinline__ void tail_set_guard(const SelArgs& A, bool finished) {
     A.st->go = finished ? 1 : 0;
     A.st->guard_nv = finished ? A.st->nv[A.cur] : 0;
-    A.st->guard_ne = finished ? A.st->ne : 0;
 }
 
 __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
@@ -1527,6 +1526,11 @@ struct JoinKeys {
 // by counts in LDS, the others among the keys that share them, listed in LDS in any order, digit by digit (8 bits at a
 // time from the highest bit in which they differ at all); where the budget ends among equal keys, the last tie-break value in the
 // same way; and (few keys) walks the vertices once more to release what lies beyond.  Bound by the trips to LDS and memory of one compute unit; 16 vertices per lane are in flight.
+//
+// Up to TRUNC_BLOCK_CAP keys a mesh goes this way, because its search, one or two launches that know nothing of the host, can be queued
+// ahead of the host's look; the whole chip's (below) takes seven or eight.  Whole calls of one round with three quarters of the pairs
+// staying, this way / the other: one mesh of 539 pairs 92 / 116 us, 2,139 100 / 129, 8,576 119 / 147, 17,022 134 / 156; eight meshes of
+// 2,139 pairs 133 / 162, of 17,022 283 / 301.  Beyond the cap the keys of a mesh may not fit LDS.
 constexpr int TRUNC_THREADS = 1024;
 constexpr int TRUNC_BLOCK_CAP = 32 * TRUNC_THREADS;
 constexpr int TRUNC_SMALL_CAP = 4 * TRUNC_THREADS;

@@ -1051,7 +1051,10 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                 case PICASSO_KERNEL_SORT: bytes = 16.0 * H; break;
                 case PICASSO_KERNEL_UNIQUE_COST: bytes = 8.0 * H + 13.0 * ne + 72.0 * nv; break;
                 case PICASSO_KERNEL_SUBROUND0: bytes = 14.0 * ne + 24.0 * nv; break;
-                case PICASSO_KERNEL_FACET_INSERT: bytes = 24.0 * nf + 4.0 * nv + 8.0 * (double)N; break;
+                case PICASSO_KERNEL_FACET_INSERT:  // (the last round's is another kernel)
+                    if (rd + 1 < c->n_rounds_noted) bytes = 24.0 * nf + 4.0 * nv + 8.0 * (double)N + 24.0 * (double)c->nv_round[rd + 1];
+                    else bytes = 28.0 * nf + 4.0 * nv + 8.0 * (double)N + (drop ? 0.0 : 28.0 * (double)nv_total);
+                    break;
                 case PICASSO_KERNEL_SORT_INCIDENCE: bytes = 48.0 * (double)F; break;
                 default: bytes = 24.0 * (double)F + 16.0 * (double)F + 76.0 * (double)N; break;  // QUADRIC_ROWS
             }
@@ -1498,7 +1501,7 @@ int picasso_v2f_forward(picasso_ctx* c, void* stream, const float* d_x, int32_t 
     HIP_TRY(c, hipSetDevice(c->device));
     const pool::RowMap m = pool::row_map(C);
     const int per_wave = conv::facets_per_wave(m, F), per_block = per_wave * (pool::BLOCK / 64);
-    const dim3 grid = conv::xcd_grid(dim3((F + per_block - 1) / per_block, pool::row_parts(m)));
+    const dim3 grid(prim::xcd_grid((F + per_block - 1) / per_block), pool::row_parts(m));
 #define PICASSO_CALL(K) \
     conv::v2f_forward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_x, N, C, d_facets, F, d_level, d_w, d_y, per_wave, m)
     PICASSO_ROW_KINDS(C, C, std::max(N, F), PICASSO_CALL);
@@ -1537,7 +1540,7 @@ int picasso_f2f_forward(picasso_ctx* c, void* stream, const float* d_tex, const 
     HIP_TRY(c, hipSetDevice(c->device));
     const conv::WalkMap m = conv::walk_map(C, F, (double)P / F);
     const int per_block = m.per_wave * (pool::BLOCK / 64);
-    const dim3 grid = conv::xcd_grid(dim3((F + per_block - 1) / per_block, pool::row_parts(m.row)));
+    const dim3 grid(prim::xcd_grid((F + per_block - 1) / per_block), pool::row_parts(m.row));
 #define PICASSO_CALL(K) \
     conv::f2f_forward_kernel<K><<<grid, pool::BLOCK, 0, s>>>(d_tex, d_bary, d_poff, F, P, C, d_w, d_y, m)
     PICASSO_ROW_KINDS(C, C, std::max(F, P), PICASSO_CALL);
@@ -1587,7 +1590,7 @@ int picasso_f2v_forward(picasso_ctx* c, void* stream, const float* d_y, int32_t 
     HIP_TRY(c, hipSetDevice(c->device));
     const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
     const int per_block = (T <= 16 ? m.per_wave : m.row.rw) * (pool::BLOCK / 64);
-    const dim3 grid = conv::xcd_grid(dim3((N + per_block - 1) / per_block, pool::row_parts(m.row)));
+    const dim3 grid(prim::xcd_grid((N + per_block - 1) / per_block), pool::row_parts(m.row));
 #define PICASSO_F2V(NP, K) \
     conv::f2v_forward_kernel<NP, K><<<grid, pool::BLOCK, 0, s>>>(d_y, C, d_pi, T, d_w, d_offsets, d_corners, N, 3 * F, d_x, m)
 #define PICASSO_CALL(K)                      \

@@ -1767,15 +1767,15 @@ inline void compact_impl(hipStream_t s, PredCount pc, PredScatter ps, Out out, c
         <<<tiles, BLOCK, 0, s>>>(ps, out, n_ptr, n_max, tilesum, prefixed, total_out);
 }
 
-// What follows the count where the counts were made otherwise: the scan of the tile sums, where compact_scatter wants it.
+// What follows the count where the counts were made otherwise: the scan of the tile sums, where there are many (the kernels that use
+// them add up the sums in front of a tile themselves otherwise: `prefixed`).
 inline void compact_scan_sums(hipStream_t s, const int* n_ptr, int n_max, int* tilesum) {
     const int chunks = compact_chunks_for(n_max);
     if (compact_tiles(n_max > 0 ? n_max : 1, chunks) > COMPACT_MAX_SUMMED_TILES)
         scan_tilesums_kernel<<<1, SCAN_TILES_THREADS, 0, s>>>(tilesum, n_ptr, n_max, BLOCK * chunks);
 }
 
-// The two halves of compact() on their own, for callers that put other work between them
-// (or launch them on different streams).  Both must be given the same n_max.
+// The first half of compact() on its own, for kernels that find their own places from the tile sums.
 template <class PredCount>
 inline void compact_count(hipStream_t s, PredCount pc, const int* n_ptr, int n_max, int* tilesum) {
     const int tiles = compact_tiles(n_max > 0 ? n_max : 1, compact_chunks_for(n_max));
@@ -1785,19 +1785,6 @@ inline void compact_count(hipStream_t s, PredCount pc, const int* n_ptr, int n_m
         default: tile_count_kernel<PredCount, 16><<<tiles, BLOCK, 0, s>>>(pc, n_ptr, n_max, tilesum);
     }
     compact_scan_sums(s, n_ptr, n_max, tilesum);
-}
-
-template <class PredScatter, class Out>
-inline void compact_scatter(hipStream_t s, PredScatter ps, Out out, const int* n_ptr, int n_max, const int* tilesum,
-                            int* total_out) {
-    const int chunks = compact_chunks_for(n_max);
-    const int tiles = compact_tiles(n_max > 0 ? n_max : 1, chunks);
-    const int prefixed = tiles > COMPACT_MAX_SUMMED_TILES;
-    switch (chunks) {
-        case 1: tile_scatter_kernel<PredScatter, Out, 1><<<tiles, BLOCK, 0, s>>>(ps, out, n_ptr, n_max, tilesum, prefixed, total_out); break;
-        case 4: tile_scatter_kernel<PredScatter, Out, 4><<<tiles, BLOCK, 0, s>>>(ps, out, n_ptr, n_max, tilesum, prefixed, total_out); break;
-        default: tile_scatter_kernel<PredScatter, Out, 16><<<tiles, BLOCK, 0, s>>>(ps, out, n_ptr, n_max, tilesum, prefixed, total_out);
-    }
 }
 
 // count pass may use a different functor (e.g. one that also stores the flag)
