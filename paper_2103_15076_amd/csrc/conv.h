@@ -10,7 +10,7 @@
 // atomics, so results do not depend on scheduling.
 //
 // What bounds these kernels, apart from the feature rows' bytes, is the memory pipeline of a compute unit (16 bytes
-// for each of 64 lanes take it 16 cycles, whether they come from memory or all from one cached word): indices,
+// for each of 64 lanes take it 8 ns, whether they are a kilobyte in a row or all one cached word): indices,
 // levels and coefficients are therefore fetched once per item, one item per lane, and handed to the lanes of a row
 // through LDS, the filter stays in registers or LDS, several rows are gathered per lane before the first is
 // used, and one pass makes every gradient of a direction.

@@ -755,9 +755,9 @@ __device__ __forceinline__ float pair_cost(const VRec* __restrict__ vrec, int u,
     return (xAx + 2.0f * bx) + c;
 }
 
-// A workgroup's bids, put together in LDS before they go to memory.  Atomics are carried out at the memory side, about 25 per
-// nanosecond for the whole chip; one request covers a 64-byte line (8 vertices), but lanes of a wave that name the
-// same word take a request each.  The edges of a workgroup touch few vertices, and those lie in few lines, so the table
+// A workgroup's bids, put together in LDS before they go to memory.  Atomics are carried out at the memory side: of 64-bit minima
+// the whole chip does 27 lines of 64 bytes (8 vertices) per nanosecond, in 1 MB as in 256 MB and with 8 lanes of a wave on a line's 8
+// words (24) as with one, but lanes of a wave that name the same word take a request each (1.7 lines with 8 lanes per word).  The edges of a workgroup touch few vertices, and those lie in few lines, so the table
 // holds lines: each goes out as one request.  A line that finds no place (a mesh numbered without locality) goes out
 // by itself.  1.2 M vertices, first round: costs and bids 106 -> 83 us, sub-round 0 59 -> 51.
 template <int LINES>
@@ -1037,7 +1037,7 @@ __device__ __forceinline__ void count_pairs(const SelArgs& A, bool sel, int m) {
 
 // The same for a workgroup whose pairs nearly all belong to one mesh (edges are in mesh order): that mesh's are put together in LDS
 // and added by one atomic in the end.  (The counters of a mesh lie in MATCH_SLOTS lines, and a line takes an atomic every
-// 10 ns: with one per wave they took longer than the rest of a sub-round, 150 of 420 us at 30 M edges.)
+// 11 to 14 ns: with one per wave they took longer than the rest of a sub-round, 150 of 420 us at 30 M edges.)
 struct PairTally {
     int mesh, pairs;
     // by one thread; e = the workgroup's first edge
@@ -2238,7 +2238,7 @@ __device__ __forceinline__ u32 hash3(int a, int b, int c) {
 // hash would fetch, and later write back, a whole line for nearly every facet (and the keep test
 // that follows reads the table the same way).  Measured at 1.2 M vertices: 3 hash bits are best; with
 // none the facets of one vertex collide, with 6 or 9 the lines are shared by fewer facets.  Fewer than 8 slots per vertex
-// are worse (4: 5 times the time, collisions), atomics being served at about 25 per nanosecond and 64-byte line.
+// are worse (4: 5 times the time, collisions), atomics being served at 27 lines of 64 bytes per nanosecond.
 constexpr int FACET_HOME_WINDOW_BITS = 3;
 constexpr int FACET_HOME_PROBES = 8;
 __device__ __forceinline__ u32 facet_home(int x, u32 hx, float slots_per_vertex) {

@@ -60,8 +60,8 @@ struct picasso_ctx {
     int* fcur = nullptr;                // the facets, re-indexed in place round by round
     int* fmap = nullptr;                // ... after the last round, before compaction
     int* cid = nullptr;
-    u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys); also hold 32-bit keys for S0
-    u32* val32 = nullptr;
+    u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys); the filter gradients' partial sums lie in the first
+    u32* val32 = nullptr;                // ... for the values of the exported sorts
     u64* ekey = nullptr;
     u32* ecost = nullptr;
     u64* vmin[3] = {nullptr, nullptr, nullptr};
@@ -424,6 +424,7 @@ void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>&
 #undef PICASSO_UNIQUE
 }
 
+// Up to this many facets the facet set is cleared by the call's first kernel (see launch_init).
 constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 
 // Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
