@@ -317,14 +317,15 @@ int picasso_pool_forward(picasso_ctx* ctx, void* stream, int mode, const float* 
                          float* d_y, int32_t* d_argmax);
 
 /* d_gx [n_in, C] = gradient with respect to the input features given d_gy
- * [n_out, C] (the adjoint of the forward pass; weights are constants).
+ * [n_out, C] (the adjoint of the forward pass; weights are constants; 0 for a
+ * vertex with cluster id -1, see PICASSO_OPT_DROP_DEGENERATED).
  * PICASSO_POOL_MAX needs the d_argmax of the forward pass.  Asynchronous. */
 int picasso_pool_backward(picasso_ctx* ctx, void* stream, int mode, const float* d_gy, int32_t n_in, int32_t C,
                           const int32_t* d_cluster_id, const int32_t* d_offsets, const int32_t* d_members,
                           int32_t n_out, const float* d_weight, const int32_t* d_argmax, float* d_gx);
 
 /* Unpooling: d_x [n_in, C]: every vertex takes the feature of its cluster
- * (d_y [n_out, C]).  Its backward pass adds up the gradients of a cluster's
+ * (d_y [n_out, C]), one with cluster id -1 gets 0.  Its backward pass adds up the gradients of a cluster's
  * vertices (= PICASSO_POOL_SUM).  Asynchronous. */
 int picasso_unpool_forward(picasso_ctx* ctx, void* stream, const float* d_y, int32_t n_in, int32_t C,
                            const int32_t* d_cluster_id, float* d_x);

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(BLOCK) void pool_forward_kernel(const float* __rest
     }
 }
 
-// gx[v] = adjoint of the pooling applied to gy, for the features (weights are constants)
+// gx[v] = adjoint of the pooling applied to gy, for the features (weights are constants); zeros for a vertex in no cluster (id -1)
 template <int MODE, int KIND>
 __global__ __launch_bounds__(BLOCK) void pool_backward_kernel(const float* __restrict__ gy, int n_in, int C,
                                                               const int* __restrict__ cid,
@@ -219,6 +219,10 @@ __global__ __launch_bounds__(BLOCK) void pool_backward_kernel(const float* __res
     if (!l.on || v >= n_in) return;
     const int c0 = 4 * l.q, left = C - c0;
     const int c = *at<KIND>(cid, v);
+    if (c < 0) {
+        store_row<KIND>(row_at<KIND>(gx, v, C, c0), Pack{}, left);
+        return;
+    }
     Pack g = load_row<KIND>(row_at<KIND>(gy, c, C, c0), left);
     if (MODE == AVG) {
         const float n = (float)(off[c + 1] - off[c]);
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(BLOCK) void pool_backward_kernel(const float* __res
     store_row<KIND>(row_at<KIND>(gx, v, C, c0), g, left);
 }
 
-// Unpooling: every vertex takes its cluster's feature.  KIND is that of x alone: how many rows y has the call does not know,
+// Unpooling: every vertex takes its cluster's feature (zeros where its cluster was dropped, id -1).  KIND is that of x alone: how many rows y has the call does not know,
 // so those are addressed with 64 bits (one multiplication more per lane).
 template <int KIND>
 __global__ __launch_bounds__(BLOCK) void unpool_forward_kernel(const float* __restrict__ y, int n_in, int C,
@@ -255,8 +259,8 @@ __global__ __launch_bounds__(BLOCK) void unpool_forward_kernel(const float* __re
     const RowLane l = row_lane(map, blockIdx.y);
     const int v = wave_row(map, blockIdx.x) + l.r;
     if (!l.on || v >= n_in) return;
-    const int c0 = 4 * l.q, left = C - c0;
-    store_row<KIND>(row_at<KIND>(x, v, C, c0), load_row<KIND>(row_at<ROW_ANY>(y, *at<KIND>(cid, v), C, c0), left), left);
+    const int c0 = 4 * l.q, left = C - c0, c = *at<KIND>(cid, v);
+    store_row<KIND>(row_at<KIND>(x, v, C, c0), c >= 0 ? load_row<KIND>(row_at<ROW_ANY>(y, c, C, c0), left) : Pack{}, left);
 }
 
 // The two per-input-vertex tensors of Alg. 2's output list from cluster_id: first[c] = smallest

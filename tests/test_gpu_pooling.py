@@ -172,6 +172,27 @@ def test_unpooling_from_clusters_beyond_24_bit_numbers_and_4_gib(pk, ctx, n_out,
     assert torch.equal(ctx.picasso_unpool_forward(y, cid), y[cid.long()])
 
 
+@pytest.mark.parametrize("C", [4, 7])
+def test_vertices_whose_cluster_was_dropped(pk, ctx, C):
+    """Cluster id -1, as a decimation with degenerated vertices dropped leaves it: unpooled features and gradients are zero
+    there and as without those vertices elsewhere."""
+    rng = np.random.default_rng(C)
+    n_in, n_out = 1000, 300
+    cid = _clusters(rng, n_in, n_out)
+    gone = rng.random(n_in) < 0.3
+    y, g = dev(rng.normal(size=(n_out, C)).astype(np.float32)), dev(rng.normal(size=(n_out, C)).astype(np.float32))
+    x, w = dev(rng.normal(size=(n_in, C)).astype(np.float32)), dev(rng.uniform(0.1, 2.0, n_in).astype(np.float32))
+    off, mem = ctx.picasso_cluster_csr(dev(cid), n_out)
+    _, arg = ctx.picasso_pool_forward(pk.PICASSO_POOL_MAX, x, off, mem)
+    some = dev(np.where(gone, -1, cid).astype(np.int32))
+    print(f"dropped clusters C={C}", flush=True)
+    calls = [lambda c: ctx.picasso_unpool_forward(y, c)]
+    calls += [lambda c, m=m: ctx.picasso_pool_backward(m, g, c, off, mem, weight=w, argmax=arg) for m in range(4)]
+    for f in calls:
+        whole, part = f(dev(cid)).cpu().numpy(), f(some).cpu().numpy()
+        assert not part[gone].any() and np.array_equal(part[~gone], whole[~gone])
+
+
 def test_bad_cluster_ids_are_rejected(pk, ctx):
     cid = np.array([0, 1, 5, 2], np.int32)
     with pytest.raises(pk.PicassoError) as e:
