@@ -92,7 +92,7 @@ def main():
                     help="the first round's edge sort in launches of its own (PICASSO_OPT_OVERLAP = 0)")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
-        print("bench.py: this build measures ONE GPU only (the path shards by mesh: with more GPUs every rank "
+        print("bench.py measures ONE GPU only (the path shards by mesh: with more GPUs every rank "
               "would decimate its own meshes, with no exchange); run with --gpus 1", file=sys.stderr)
         sys.exit(2)
 
