@@ -176,11 +176,10 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  * bytes a launch of each is charged with (what the step has to move at least, from the sizes of the
  * round it runs in: nv vertices, nf facets, H = 3 nf half-edges, E distinct edges; N, F = the call's
  * input sizes):
- *   SORT          per-bucket kernel of the 64-bit edge-key sort (Alg. 2 line 1): every 8-byte
- *                 key read and written once, 16 H.
- *   UNIQUE_COST   distinct edges, their costs (Alg. 2 line 2) and first bids: 8 H (sorted keys
- *                 read) + 13 E (edge key, cost key, state written) + 64 nv (every vertex record
- *                 read once) + 8 nv (one bid word per vertex).
+ *   SORT          per-bucket kernel of the edge-key sort (Alg. 2 line 1): every key read once as a 4-byte
+ *                 word, 4 H, the distinct ones written, 4 E.
+ *   UNIQUE_COST   costs (Alg. 2 line 2) and first bids of the distinct edges: 4 E read + 13 E (edge key, cost
+ *                 key, state written) + 64 nv (every vertex record read once) + 8 nv (one bid word per vertex).
  *   SUBROUND0     first grid-wide sub-round of the selection (Alg. 2 lines 3-10): 13 E read, E
  *                 written (edge states), 3 x 8 nv (bids read, next bids written, third array cleared).
  *   FACET_INSERT  the kernel that takes the facets to the numbering a round leaves.  Behind every round but the
@@ -189,10 +188,10 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  *                 mate and pair cost for each of the nv' vertices left).  Behind the last final_facets_kernel
  *                 (the same, facets entered into the hash set, positions written): 28 nf (a slot number
  *                 each) + 4 nv + 8 N + 28 nv'.
- *   QUADRIC_ROWS  vertex quadrics summed from the facets' planes (supplementary, vertex quadric
- *                 equation): 8 x 3F sorted incidences + 16 F planes + 12 N positions + 64 N records.
- *   SORT_INCIDENCE per-bucket kernel of the sort that brings the 3F (vertex, facet) incidence keys
- *                 into vertex order for the vertex quadrics (once per call): 16 x 3F. */
+ *   QUADRIC_ROWS  per-bucket kernel of the sort of the (vertex, facet) incidence keys, which sums the vertices' quadrics
+ *                 from the facets' planes (supplementary, vertex quadric equation): 4 x 3F keys + 16 F planes
+ *                 + 12 N positions + 64 N records.
+ *   SORT_INCIDENCE partition of the incidence keys on their top digit (once per call): 12 F (facets) + 4 x 3F. */
 enum picasso_timed_kernel {
     PICASSO_KERNEL_SORT = 0,
     PICASSO_KERNEL_UNIQUE_COST = 1,

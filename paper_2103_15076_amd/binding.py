@@ -42,12 +42,12 @@ PICASSO_PLACE_MEAN, PICASSO_PLACE_INVERSE = 0, 1
 (PICASSO_KERNEL_SORT, PICASSO_KERNEL_UNIQUE_COST, PICASSO_KERNEL_SUBROUND0, PICASSO_KERNEL_FACET_INSERT,
  PICASSO_KERNEL_QUADRIC_ROWS, PICASSO_KERNEL_SORT_INCIDENCE, PICASSO_KERNEL_COUNT) = range(7)
 TIMED_KERNEL_NAMES = (
-    "bucket_keys_kernel<u64> (edge-key sort, per-bucket LDS sort)",
-    "unique_cost_kernel (distinct edges, costs, first bids)",
+    "bucket_keys_kernel (edge-key sort, per-bucket LDS sort, distinct edges)",
+    "unique_cost_kernel (costs, first bids)",
     "select_subround_kernel (first sub-round of the selection)",
     "edge_keys_kernel, final_facets_kernel (facets and labels re-indexed behind a round; behind the last: facet hash set)",
-    "quadric_rows_kernel (vertex quadrics from facet planes)",
-    "bucket_keys_kernel<u64> (incidence-key sort of the vertex quadrics, per-bucket LDS sort)",
+    "bucket_keys_kernel (incidence-key sort, per-bucket LDS sort, vertex quadrics from facet planes)",
+    "msd_scatter_kernel, xl_scatter_kernel (incidence-key sort, partition)",
 )
 
 PICASSO_STATS_ROUNDS = 32

@@ -177,17 +177,26 @@ __device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) 
 // incidence) pairs whose stable sort is the vertex->facet CSR.
 enum { COUNT_NONE = 0, COUNT_SMALL = 1, COUNT_LARGE = 2, COUNT_XL = 3 };
 
-// Incidence key of corner i of the facet array: (vertex << fbits) | facet.
+struct Corners {
+    int a, b, c;
+};
+__device__ __forceinline__ Corners load_corners(const int* __restrict__ facets, size_t f) {
+    return Corners{facets[3 * f], facets[3 * f + 1], facets[3 * f + 2]};
+}
+__device__ __forceinline__ int corner(const Corners& q, int c) { return c == 0 ? q.a : (c == 1 ? q.b : q.c); }
+
+// Incidence keys of a facet, one per corner: (vertex << fbits) | facet.
 struct IncidenceKeys {
     const int* fcur;
     int fbits;
-    __device__ __forceinline__ u64 operator()(long long i) const {
-        return ((u64)(u32)fcur[i] << fbits) | (u64)((u32)i / 3u);
-    }
+    static constexpr int PER = 3;
+    typedef Corners Raw;
+    __device__ __forceinline__ Corners load(int f) const { return load_corners(fcur, (size_t)f); }
+    __device__ __forceinline__ u64 key(const Corners& q, int f, int c) const { return ((u64)(u32)corner(q, c) << fbits) | (u64)(u32)f; }
     __device__ __forceinline__ bool keep(u64) const { return true; }
 };
 
-// Edge key of corner i of the facet array: the side from corner i to the facet's next corner as
+// Edge keys of a facet: the sides from its corners to the next ones as
 // (lower vertex << vbits) | higher vertex; a side with equal ends, as all three of a collapsed facet (-1, -1, -1) are,
 // has none: it gets the all-ones key, which no sort keeps.
 __host__ __device__ __forceinline__ u64 edge_sentinel(int vbits) { return vbits >= 32 ? ~0ull : ((1ull << (2 * vbits)) - 1ull); }
@@ -199,10 +208,10 @@ __device__ __forceinline__ u64 edge_key(int a, int b, int vbits) {
 struct EdgeKeys {
     const int* fcur;
     int vbits;
-    __device__ __forceinline__ u64 operator()(long long i) const {
-        const u32 f = (u32)i / 3u, sl = (u32)i - 3u * f;  // (a corner's number fits 31 bits; 64-bit division is slow)
-        return edge_key(fcur[i], fcur[sl == 2u ? i - 2 : i + 1], vbits);
-    }
+    static constexpr int PER = 3;
+    typedef Corners Raw;
+    __device__ __forceinline__ Corners load(int f) const { return load_corners(fcur, (size_t)f); }
+    __device__ __forceinline__ u64 key(const Corners& q, int, int c) const { return edge_key(corner(q, c), corner(q, c == 2 ? 0 : c + 1), vbits); }
     __device__ __forceinline__ bool keep(u64 k) const { return k != edge_sentinel(vbits); }
 };
 
@@ -244,7 +253,7 @@ struct HeaderInit {
 // alone lists every vertex's facets in ascending facet order; edge keys for the first round (see edge_keys_kernel, which is
 // the first kernel of the others).  With COUNT_SMALL / COUNT_LARGE the
 // kernel also adds both keys' top 8- / 12-bit digits to the histograms that the sorts start from (zero on entry; left so
-// by quadric_rows_kernel and contract_kernel); the sorts make the keys again from the validated facets, so they are
+// by the sorts); the sorts make the keys again from the validated facets, so they are
 // written nowhere.  COUNT_XL: digits as wide as the masks say, counted in memory.  COUNT_NONE: no round follows.  edges: the
 // edges' digits are wanted, and the round's set-up is made.
 struct DigitCount {
@@ -264,8 +273,8 @@ struct DigitTally {
     }
     __device__ __forceinline__ void count(const DigitCount& D, bool ok, u64 k) {
         const u32 d = (u32)(k >> D.shift) & (u32)(RADIX - 1);
-        const u64 same = prim::wave_same_digit_lanes(ok, d);
-        if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&hist[d], (u32)__popcll(same));
+        const prim::SameDigit same = prim::wave_same_digit(ok, d);
+        if (ok && same.below == 0) atomicAdd(&hist[d], same.count);
     }
     __device__ __forceinline__ void flush(const DigitCount& D) {
         for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
@@ -328,7 +337,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
     for (int w = g; w < N; w += stride) {
         float x = verts[3 * (size_t)w], y = verts[3 * (size_t)w + 1], z = verts[3 * (size_t)w + 2];
         if (!(isfinite(x) && isfinite(y) && isfinite(z))) err |= 2;
-        if (COUNT == COUNT_NONE) {  // (else quadric_rows_kernel writes the whole record)
+        if (COUNT == COUNT_NONE || F == 0) {  // (else QuadricRows writes the whole record)
             VRec r;
             r.x = x; r.y = y; r.z = z; r.w0 = 0.f;
             r.a00 = r.a01 = r.a02 = r.a11 = r.a12 = r.a22 = r.b0 = r.b1 = r.b2 = r.c = r.w1 = r.w2 = 0.f;
@@ -355,28 +364,26 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                 hi = voff[m + 1];
             }
         }
-        int corner[3] = {0, 0, 0};
+        const Corners given = load_corners(facets, (size_t)(ok ? f : 0));
+        int at[3] = {given.a, given.b, given.c};
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            u64 k = 0;
-            if (ok) {
-                int a = facets[3 * (size_t)f + c];
-                if (a < lo || a >= hi) { err |= 1; a = lo; }
-                fcur[3 * (size_t)f + c] = a;
-                corner[c] = a;
-                k = ((u64)(u32)a << fbits) | (u64)(u32)f;
-            }
-            corners.count(inc, ok, k);
+            const bool bad = ok && (at[c] < lo || at[c] >= hi);
+            if (bad) err |= 1;
+            if (bad || !ok) at[c] = lo;
+            if (ok) fcur[3 * (size_t)f + c] = at[c];
         }
+        // the facet's plane, once per facet, for the vertex quadrics that S0 sums from it
+        if (planes && ok) planes[f] = facet_plane(verts, at[0], at[1], at[2]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) corners.count(inc, ok, ((u64)(u32)at[c] << fbits) | (u64)(u32)f);
         if (edges) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const int a = corner[c], b = corner[c == 2 ? 0 : c + 1];
+                const int a = at[c], b = at[c == 2 ? 0 : c + 1];
                 sides.count(edge, ok && a != b, edge_key(a, b, vbits));
             }
         }
-        // the facet's plane, once per facet, for the vertex quadrics that S0 sums from it
-        if (planes && ok) planes[f] = facet_plane(verts, corner[0], corner[1], corner[2]);
         if constexpr (COUNT == COUNT_XL) {
             __syncthreads();
             corners.flush(inc);
@@ -397,14 +404,16 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
 
 // ---------------------------------------------------------------------------
 // Lists of items per row (corners of a vertex, members of a cluster) from an array that names every item's row:
-// the keys (row << ibits) | item are counted by their top digit, sorted (the partition makes them from the array again) and
-// taken apart.  Five launches with the one that tells the host.
+// the keys (row << ibits) | item are counted by their top digit and sorted (the partition makes them from the array again; the
+// per-bucket kernel writes the lists).  Four launches with the one that tells the host, a fifth for wide digits.
 // ---------------------------------------------------------------------------
 struct RowKeys {
     const int* row_of;  // [n]
     int n_rows, ibits;
-    __device__ __forceinline__ u64 operator()(long long i) const {
-        const int r = row_of[i];
+    static constexpr int PER = 1;
+    typedef int Raw;
+    __device__ __forceinline__ int load(int i) const { return row_of[i]; }
+    __device__ __forceinline__ u64 key(int r, int i, int) const {
         return ((u64)((u32)r < (u32)n_rows ? (u32)r : 0u) << ibits) | (u64)(u32)i;  // (a bad row counts as row 0 here)
     }
     __device__ __forceinline__ bool keep(u64) const { return true; }
@@ -419,53 +428,67 @@ __global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, Di
     digits.clear();
     __syncthreads();
     bool bad = false;
-#pragma unroll 4
+    int row[ITEMS];
+    const int base = (int)blockIdx.x * (ITEMS * BLOCK) + (int)threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) row[j] = src.load(min(base + j * BLOCK, n - 1));
+#pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
-        const long long i = ((long long)blockIdx.x * ITEMS + j) * BLOCK + threadIdx.x;
-        const bool ok = i < n;
-        u64 k = 0;
-        if (ok) {
-            bad |= (u32)src.row_of[i] >= (u32)src.n_rows;
-            k = src(i);
-        }
-        digits.count(rows, ok, k);
+        bad |= (u32)row[j] >= (u32)src.n_rows;
+        digits.count(rows, base + j * BLOCK < n, src.key(row[j], base + j * BLOCK, 0));
     }
     __syncthreads();
     digits.flush(rows);
     if (bad) atomicOr(err, ERR_BIT_BAD_INDEX);
 }
 
-// off[r] = first position of row r in the sorted keys, items[i] = item at position i; the counting arrays of the sort go back
-// to zero for the next call.
-__global__ __launch_bounds__(BLOCK) void csr_finish_kernel(const u64* __restrict__ skey, int ibits, int n, int n_rows,
-                                                           int* __restrict__ off, int* __restrict__ items,
-                                                           u32* __restrict__ hist) {
-    const int i = blockIdx.x * BLOCK + threadIdx.x;
-    for (int h = i; h < 2 * prim::MSD_HIST_WORDS; h += gridDim.x * BLOCK) hist[h] = 0;
-    if (i >= n) return;
-    const u64 key = skey[i];
-    const int k = (int)(key >> ibits);
-    const int kp = i ? (int)(skey[i - 1] >> ibits) : -1;
-    items[i] = (int)(key & ((1ull << ibits) - 1ull));
-    for (int r = kp + 1; r <= k; ++r) off[r] = i;
-    if (i == n - 1)
-        for (int r = k + 1; r <= n_rows; ++r) off[r] = n;
-}
+// off[r] = first position of row r, items[i] = item at position i: made by the sort's per-bucket kernel from the keys in LDS.  Where
+// the digit ends within the row's bits a bucket holds whole rows, of which it writes the offsets, also of those without items;
+// where it takes in bits of the item (fewer rows than buckets) a row starts with its first bucket.
+// (With the sorted keys written out and taken apart by a launch of its own: 16 bytes per item more.)
+struct RowLists {
+    int* off;
+    int* items;
+    int n, n_rows, ibits, digit_bits;
+    template <int THREADS, int ITEMS>
+    struct Lds {};
+    template <int THREADS, int ITEMS, class L, typename LK, class KeyAt>
+    __device__ __forceinline__ void emit(bool, L&, const prim::Bucket& b, LK*, LK*, KeyAt key_at) const {
+        const int t = threadIdx.x, start = (int)b.start;
+        if (b.number == 0 && t == 0) off[n_rows] = n;
+        if (b.low_bits < ibits) {
+            const int within = ibits - b.low_bits, r = b.number >> within;
+            if (t == 0 && r < n_rows && (b.number & ((1 << within) - 1)) == 0) off[r] = start;
+            for (int i = t; i < b.cnt; i += THREADS) items[start + i] = (int)(b.whole(key_at(i)) & ((1ull << ibits) - 1ull));
+            return;
+        }
+        const int per = b.low_bits - ibits;
+        const long long lo64 = (long long)b.number << per;
+        if (lo64 >= n_rows) return;
+        const int lo = (int)lo64, hi = (int)min(lo64 + (1ll << per), (long long)n_rows);  // the bucket's rows
+        for (int i = t; i < b.cnt; i += THREADS) {
+            const auto key = key_at(i), prev = key_at(max(i - 1, 0));
+            items[start + i] = (int)b.item(key, ibits);
+            if (i == 0 || b.row_in(key, ibits) != b.row_in(prev, ibits)) {
+                const int k = b.row(key, ibits);
+                for (int r = i ? b.row(prev, ibits) + 1 : lo; r <= k; ++r) off[r] = start + i;
+            }
+        }
+        const int last = b.cnt > 0 ? b.row(key_at(b.cnt - 1), ibits) : lo - 1;
+        for (int r = last + 1 + t; r < hi; r += THREADS) off[r] = start + b.cnt;
+    }
+};
 
-// Ordered segmented reduction over the sorted incidence keys (vertex << fbits | facet): the keys of
-// one vertex are consecutive and ascend in facet index, which is the order of the sum.  A
-// workgroup takes a tile of the keys; every lane fetches the planes of its share of the tile's
-// incidences into LDS (16 bytes gathered per incidence, all of a tile's gathers in flight together:
-// the plane was computed once per facet by init_kernel); the positions where a new vertex starts
-// are listed, and every such row goes to one lane, which adds up the facets' quadrics
+// Ordered segmented reduction over the sorted incidence keys (vertex << fbits | facet), by the sort's per-bucket kernel from
+// the keys in LDS (a bucket holds whole vertices): the keys of one vertex are consecutive and ascend in facet index, which is the
+// order of the sum.  A wave lists where the vertices start in QR_WINDOW keys at a time; every such row goes to one lane, which
+// fetches the facets' planes (computed once per facet by init_kernel), eight in flight, adds up their quadrics
 // Q = (n n^T, d n, d^2) left to right and writes the vertex's whole 64-byte record, position
-// included.  A row that runs past the end of its tile is followed into the next one (whose first
-// keys are then no row start).  Vertices without any facet appear in no key: the row of the next
-// vertex that has one notes the run of them in front of it (the last row also the run behind it),
+// included.  Vertices without any facet appear in no key: the row of the next
+// vertex that has one notes the run of them in front of it (a bucket's last row also the run behind it),
 // and the workgroup writes their records (zero quadric) together.
-constexpr int QR_ITEMS = 4;
-constexpr int QR_TILE = BLOCK * QR_ITEMS;
-constexpr int QR_GAPS = 64;  // runs of facet-less vertices a tile lists (further ones are written by the lane that meets them)
+constexpr int QR_CHUNKS = 4, QR_WINDOW = 64 * QR_CHUNKS;
+constexpr int QR_GAPS = 64;  // runs of facet-less vertices a bucket lists (further ones are written by the lane that meets them)
 
 __device__ __forceinline__ void write_vertex_record(VRec* __restrict__ vrec, const float* __restrict__ verts, int v,
                                                     const float (&acc)[10]) {
@@ -485,97 +508,89 @@ __device__ __forceinline__ void add_plane_quadric(float (&acc)[10], const float4
     acc[8] = acc[8] + q8; acc[9] = acc[9] + q9;
 }
 
-__global__ __launch_bounds__(BLOCK) void quadric_rows_kernel(VRec* __restrict__ vrec, const float* __restrict__ verts,
-                                                             int N, const float4* __restrict__ planes,
-                                                             const u64* __restrict__ inc, int H, int fbits,
-                                                             u32* __restrict__ ihist) {
-    __shared__ float4 splane[QR_TILE];         // plane of the facet of the key at position base + i
-    __shared__ int svert[QR_TILE + 1];         // svert[i + 1] = vertex of that key; svert[0] = of the key in front of the tile (-1: none)
-    __shared__ unsigned short hpos[QR_TILE];   // positions (within the tile) where a vertex's row starts, ascending
-    __shared__ u32 smem[prim::WAVES];
-    __shared__ int gap[2 * QR_GAPS];           // runs [first, end) of vertices without facets met by this tile's rows
-    __shared__ int n_gaps;
-    const int t = threadIdx.x;
-    // last kernel of S0: the incidence sort's digit counts and cursors go back to zero for the next call
-    for (int i = blockIdx.x * BLOCK + t; i < 2 * prim::MSD_HIST_WORDS; i += gridDim.x * BLOCK) ihist[i] = 0;
-    const float zero[10] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (H <= 0) {  // no facets at all: every vertex gets the zero quadric
-        for (int v = blockIdx.x * BLOCK + t; v < N; v += gridDim.x * BLOCK) write_vertex_record(vrec, verts, v, zero);
-        return;
-    }
-    const long long tile = blockIdx.x;
-    const long long base = tile * QR_TILE;
-    if (base >= H) return;
-    const int tile_n = (int)((long long)H - base < QR_TILE ? (long long)H - base : QR_TILE);
-    const u64 fmask = (1ull << fbits) - 1ull;
-#pragma unroll
-    for (int j = 0; j < QR_ITEMS; ++j) {
-        const int i = j * BLOCK + t;
-        if (i < tile_n) {
-            const u64 key = inc[base + i];
-            svert[i + 1] = (int)(key >> fbits);
-            splane[i] = planes[(size_t)(key & fmask)];
-        }
-    }
-    if (t == 0) {
-        svert[0] = base > 0 ? (int)(inc[base - 1] >> fbits) : -1;
-        n_gaps = 0;
-    }
-    __syncthreads();
-    // thread t looks at positions t * QR_ITEMS .. + QR_ITEMS - 1, so that the list of starts is in order
-    u32 mine = 0;
-    int cnt = 0;
-#pragma unroll
-    for (int j = 0; j < QR_ITEMS; ++j) {
-        const int i = t * QR_ITEMS + j;
-        if (i < tile_n && svert[i + 1] != svert[i]) {
-            mine |= 1u << j;
-            ++cnt;
-        }
-    }
-    u32 n_rows;
-    u32 at = prim::block_exclusive_scan((u32)cnt, smem, n_rows);
-#pragma unroll
-    for (int j = 0; j < QR_ITEMS; ++j)
-        if (mine & (1u << j)) hpos[at++] = (unsigned short)(t * QR_ITEMS + j);
-    __syncthreads();
-    auto note_gap = [&](int first, int end) {
-        const int slot = atomicAdd(&n_gaps, 1);
-        if (slot < QR_GAPS) {
-            gap[2 * slot] = first;
-            gap[2 * slot + 1] = end;
-        } else {
-            for (int g = first; g < end; ++g) write_vertex_record(vrec, verts, g, zero);
-        }
+struct QuadricRows {
+    VRec* vrec;
+    const float* verts;
+    const float4* planes;
+    int N, fbits;
+    template <int THREADS, int ITEMS>
+    struct Lds {
+        unsigned short start[THREADS / 64][QR_WINDOW];  // (within the window)
+        int gap[2 * QR_GAPS];  // runs [first, end) of vertices without facets
+        int n_gaps;
     };
-    for (int r = t; r < (int)n_rows; r += BLOCK) {
-        const int hp = hpos[r];
-        const int row_end = r + 1 < (int)n_rows ? (int)hpos[r + 1] : tile_n;  // (within the tile)
-        const int v = svert[hp + 1];
-        const int pv = svert[hp];  // vertices between the row in front of this one and this one have no facet
-        if (pv + 1 < v) note_gap(pv + 1, v);
-        float acc[10];
-#pragma unroll
-        for (int k = 0; k < 10; ++k) acc[k] = 0.0f;
-        for (int j = hp; j < row_end; ++j) add_plane_quadric(acc, splane[j]);
-        bool last_of_all = false;
-        if (row_end == tile_n) {  // the tile's last row may go on in the next tile
-            long long j = base + tile_n;
-            for (; j < H; ++j) {
-                const u64 key = inc[j];
-                if ((int)(key >> fbits) != v) break;
-                add_plane_quadric(acc, planes[(size_t)(key & fmask)]);
-            }
-            last_of_all = j >= H;
+    template <int THREADS, int ITEMS, class L, typename LK, class KeyAt>
+    __device__ __forceinline__ void emit(bool, L& lds, const prim::Bucket& b, LK*, LK*, KeyAt key_at) const {
+        const int t = threadIdx.x, lane = prim::lane_id(), w = prim::wave_id(), n = b.cnt;
+        const int per = b.low_bits - fbits;
+        const long long lo64 = (long long)b.number << per;
+        if (lo64 >= N) return;
+        const int lo = (int)lo64, hi = (int)min(lo64 + (1ll << per), (long long)N);  // the bucket's vertices
+        const float zero[10] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (n == 0) {
+            for (int v = lo + t; v < hi; v += THREADS) write_vertex_record(vrec, verts, v, zero);
+            return;
         }
-        write_vertex_record(vrec, verts, v, acc);
-        if (last_of_all && v + 1 < N) note_gap(v + 1, N);  // the vertices behind the last row have no facet either
+        if (t == 0) lds.n_gaps = 0;
+        __syncthreads();
+        auto vertex_at = [&](int i) { return b.row(key_at(i), fbits); };
+        auto row_at = [&](int i) { return b.row_in(key_at(i), fbits); };
+        auto note_gap = [&](int first, int end) {
+            const int slot = atomicAdd(&lds.n_gaps, 1);
+            if (slot < QR_GAPS) {
+                lds.gap[2 * slot] = first;
+                lds.gap[2 * slot + 1] = end;
+            } else {
+                for (int g = first; g < end; ++g) write_vertex_record(vrec, verts, g, zero);
+            }
+        };
+        unsigned short* list = lds.start[w];
+        for (int base = w * QR_WINDOW; base < n; base += (THREADS / 64) * QR_WINDOW) {
+            int m = 0;
+#pragma unroll
+            for (int c = 0; c < QR_CHUNKS; ++c) {
+                const int i = base + c * 64 + lane;
+                const int at = min(i, n - 1);
+                const bool head = i < n && (i == 0 || row_at(at) != row_at(max(at - 1, 0)));
+                const u64 bal = prim::ballot(head);
+                if (head) list[m + (int)prim::mask_below(bal)] = (unsigned short)(c * 64 + lane);
+                m += (int)__popcll(bal);
+            }
+            __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations complete in order)
+            for (int r = lane; r < m; r += 64) {
+                const int hp = base + (int)list[r], v = vertex_at(hp);
+                int end;
+                if (r + 1 < m) {
+                    end = base + (int)list[r + 1];
+                } else {
+                    end = min(base + QR_WINDOW, n);
+                    while (end < n && vertex_at(end) == v) ++end;
+                }
+                const int pv = hp > 0 ? vertex_at(hp - 1) : lo - 1;
+                if (pv + 1 < v) note_gap(pv + 1, v);
+                float acc[10];
+#pragma unroll
+                for (int k = 0; k < 10; ++k) acc[k] = 0.0f;
+                for (int j0 = hp; j0 < end; j0 += 8) {
+                    float4 p[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (j0 + j < end) p[j] = planes[b.item(key_at(j0 + j), fbits)];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (j0 + j < end) add_plane_quadric(acc, p[j]);
+                }
+                write_vertex_record(vrec, verts, v, acc);
+                if (end == n && v + 1 < hi) note_gap(v + 1, hi);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        const int ng = min(lds.n_gaps, QR_GAPS);
+        for (int i = 0; i < ng; ++i)
+            for (int g = lds.gap[2 * i] + t; g < lds.gap[2 * i + 1]; g += THREADS) write_vertex_record(vrec, verts, g, zero);
     }
-    __syncthreads();
-    const int ng = n_gaps < QR_GAPS ? n_gaps : QR_GAPS;
-    for (int i = 0; i < ng; ++i)
-        for (int g = gap[2 * i] + t; g < gap[2 * i + 1]; g += BLOCK) write_vertex_record(vrec, verts, g, zero);
-}
+};
 
 // ---------------------------------------------------------------------------
 // S1: candidate pairs = distinct mesh edges (Alg. 2 line 1)
@@ -592,13 +607,6 @@ __global__ __launch_bounds__(BLOCK) void quadric_rows_kernel(VRec* __restrict__ 
 // they change no edge and no cost, are a few in ten thousand, and go at the end (final_facets_kernel).  Cluster labels follow
 // the numbering.  A lane takes FACETS facets at a time, all of whose loads are in flight together.
 // ---------------------------------------------------------------------------
-struct Corners {
-    int a, b, c;
-};
-__device__ __forceinline__ Corners load_corners(const int* __restrict__ facets, size_t f) {
-    return Corners{facets[3 * f], facets[3 * f + 1], facets[3 * f + 2]};
-}
-
 // A facet whose corners have met is dropped if its mesh has been contracted; a mesh that no round took part in
 // keeps its facets as they came.
 __device__ __forceinline__ bool facet_collapsed(const Corners& q, const int* __restrict__ voff, int B,
@@ -654,7 +662,7 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
         for (int j = 0; j < FACETS; ++j) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const int a = c == 0 ? q[j].a : (c == 1 ? q[j].b : q[j].c), b = c == 0 ? q[j].b : (c == 1 ? q[j].c : q[j].a);
+                const int a = corner(q[j], c), b = corner(q[j], c == 2 ? 0 : c + 1);
                 sides.count(edge, ok[j] && a != b, edge_key(a, b, vbits));
             }
         }
@@ -796,92 +804,72 @@ struct BidTable {
     }
 };
 
+// The distinct keys of an edge sort, as its per-bucket kernel has left them (DistinctKeys): per bucket at the front of its range of `keys`.
+struct EdgeList {
+    const void* keys;  // 32-bit (low bits) or 64-bit words
+    const u32* starts;
+    const u32* per_bucket;
+    const u32* per_group;
+    int buckets, low_bits;
+    int split_shift, join_shift;  // 2^split_shift workgroups share a bucket, or a workgroup takes 2^join_shift buckets in a row
+};
+
 // Writes the distinct edges, their cost keys, and places each edge's first bid
-// (sub-round 0 of the selection) on both of its vertices.  The scatter pass of a compaction: the sort has left the first
-// keys of runs per tile of BLOCK * CHUNKS positions.  A wave lists its edges in LDS (most keys come twice), so that the
-// lanes that fetch two vertex records each are all at work.
-constexpr int unique_lines(int chunks) { return chunks == 16 ? 256 : 128; }
-template <int PLACE, bool SHUFFLE, int CHUNKS>
-__global__ __launch_bounds__(BLOCK) void unique_cost_kernel(const u64* __restrict__ keys, const int* __restrict__ n_ptr,
-                                                            const int* __restrict__ tilesum, int prefixed,
-                                                            u64* __restrict__ ekey, u32* __restrict__ ecost,
+// (sub-round 0 of the selection) on both of its vertices.  Bound by the two vertex records gathered per edge and what a workgroup does
+// besides (numbering, its table of bids): a workgroup has 384 edges where there are few, for the chip's sake, and up to 1,536, with twice
+// the table, where there are many (10.2 M vertices, 31 M edges: 384 edges 510 us, 1,536 392; workgroups are dealt to the XCDs in eighths
+// of the buckets in use, so that the far ends' records are found in their L2).
+constexpr int UNIQUE_EDGES_MIN = 384, UNIQUE_EDGES_MAX = 1536, UNIQUE_EDGES_NARROW = 1000;  // edges of a workgroup (about)
+constexpr int UNIQUE_GROUPS_MIN = 4096;
+constexpr int UNIQUE_JOIN_MAX = 2;
+template <int PLACE, bool SHUFFLE, typename LK, int LINES>
+__global__ __launch_bounds__(BLOCK) void unique_cost_kernel(EdgeList E, u64* __restrict__ ekey, u32* __restrict__ ecost,
                                                             unsigned char* __restrict__ estate, const VRec* __restrict__ vrec,
                                                             u64* __restrict__ vmin0, int vbits, MeshTab mt, float rcond_min,
                                                             TieBreak tb, int* __restrict__ ne_out) {
-    constexpr int BATCH = CHUNKS < 4 ? CHUNKS : 4;  // chunks listed at a time
     __shared__ u32 smem[prim::WAVES];
-    __shared__ u64 slist[prim::WAVES][64 * BATCH];
-    __shared__ BidTable<unique_lines(CHUNKS)> bids;
-    const int n = *n_ptr, tile = blockIdx.x, t = threadIdx.x, w = prim::wave_id(), lane = prim::lane_id();
-    const long long base = (long long)tile * (BLOCK * CHUNKS);
-    if (n <= 0 && tile == 0 && t == 0) *ne_out = 0;
-    if (base >= n) return;
+    __shared__ BidTable<LINES> bids;
+    const int t = threadIdx.x;
+    if (E.buckets == 0) {  // no facets
+        if (t == 0) *ne_out = 0;
+        return;
+    }
+    const int item = prim::xcd_tile(((((long long)E.buckets - 1) >> E.join_shift) + 1) << E.split_shift, 1);
+    const int first = item >> E.split_shift << E.join_shift, part = item & ((1 << E.split_shift) - 1), joined = 1 << E.join_shift;
+    if (first >= E.buckets) return;  // (a workgroup too many)
+    // distinct edges of the workgroup's buckets, up to and including each
+    int upto[1 << UNIQUE_JOIN_MAX], n = 0;
+#pragma unroll
+    for (int j = 0; j < 1 << UNIQUE_JOIN_MAX; ++j) upto[j] = n += j < joined && first + j < E.buckets ? (int)E.per_bucket[first + j] : 0;
+    const bool last = first + joined >= E.buckets && part == 0;
+    if (part * BLOCK >= n && !last) return;
+    const LK* __restrict__ keys = reinterpret_cast<const LK*>(E.keys);
     bids.clear();
-    u32 before;
-    if (prefixed) {
-        before = (u32)tilesum[tile];
-    } else {
-        u32 part = 0;
-        for (int j = t; j < tile; j += BLOCK) part += (u32)tilesum[j];
-        before = prim::block_sum(part, smem);
-    }
-    const long long i0 = base + (long long)w * (64 * CHUNKS);
-    u64 key[CHUNKS], bal[CHUNKS];
-    u32 cnt = 0;
-    const u64 sentinel = edge_sentinel(vbits);
+    const int before = (int)prim::distinct_in_front(E.per_bucket, E.per_group, first, smem);  // (barriers)
+    if (last && t == 0) *ne_out = before + n;
+    const u64 vmask = (1ull << vbits) - 1ull;
+    for (int q = part * BLOCK + t; q < n; q += BLOCK << E.split_shift) {
+        prim::Bucket b;
+        b.number = first;
+        b.low_bits = E.low_bits;
+        int at = q;
 #pragma unroll
-    for (int c = 0; c < CHUNKS; ++c) {
-        const long long i = i0 + c * 64 + lane;
-        key[c] = i < n ? keys[i] : sentinel;
-    }
-    u64 front = i0 > 0 && i0 < n ? keys[i0 - 1] : sentinel;  // the key in front of a chunk
-#pragma unroll
-    for (int c = 0; c < CHUNKS; ++c) {
-        u64 prev = __shfl_up(key[c], 1, 64);
-        if (lane == 0) prev = front;
-        front = __shfl(key[c], 63, 64);
-        bal[c] = __ballot(key[c] != sentinel && key[c] != prev);
-        cnt += (u32)__popcll(bal[c]);
-    }
-    __syncthreads();
-    if (lane == 0) smem[w] = cnt;
-    __syncthreads();
-    u32 run = before, tot = 0;
-#pragma unroll
-    for (int j = 0; j < prim::WAVES; ++j) {
-        if (j < w) run += smem[j];
-        tot += smem[j];
-    }
-    if (base + BLOCK * CHUNKS >= n && t == 0) *ne_out = (int)(before + tot);
-    const u64 lt = prim::lanemask_lt(), vmask = (1ull << vbits) - 1ull;
-    u64* list = slist[w];
-#pragma unroll
-    for (int c0 = 0; c0 < CHUNKS; c0 += BATCH) {
-        int m = 0;
-#pragma unroll
-        for (int j = 0; j < BATCH; ++j) {
-            const u64 b = bal[c0 + j];
-            if ((b >> lane) & 1ull) list[m + (int)__popcll(b & lt)] = key[c0 + j];
-            m += (int)__popcll(b);
-        }
-        __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations complete in order)
-        for (int q = 0; q < m; q += 64) {
-            if (q + lane < m) {
-                const u64 k = list[q + lane];
-                const int u = (int)(k >> vbits), v = (int)(k & vmask), e = (int)run + q + lane;
-                const u32 ck = cost_key(pair_cost<PLACE>(vrec, u, v, rcond_min));
-                const bool act = mt.active[mesh_of(mt.voff, mt.B, u)] != 0;
-                ekey[e] = k;
-                ecost[e] = ck;
-                estate[e] = act ? 0 : 1;
-                if (act) {
-                    bids.put(vmin0, nullptr, u, edge_bid<SHUFFLE>(tb, ck, e, v));
-                    bids.put(vmin0, nullptr, v, edge_bid<SHUFFLE>(tb, ck, e, u));
-                }
+        for (int j = 0; j + 1 < 1 << UNIQUE_JOIN_MAX; ++j)
+            if (q >= upto[j]) {  // (beyond the joined ones upto is n)
+                b.number = first + j + 1;
+                at = q - upto[j];
             }
+        const u64 k = b.whole(keys[E.starts[b.number] + (u32)at]);
+        const int u = (int)(k >> vbits), v = (int)(k & vmask), e = before + q;
+        const u32 ck = cost_key(pair_cost<PLACE>(vrec, u, v, rcond_min));
+        const bool act = mt.active[mesh_of(mt.voff, mt.B, u)] != 0;
+        ekey[e] = k;
+        ecost[e] = ck;
+        estate[e] = act ? 0 : 1;
+        if (act) {
+            bids.put(vmin0, nullptr, u, edge_bid<SHUFFLE>(tb, ck, e, v));
+            bids.put(vmin0, nullptr, v, edge_bid<SHUFFLE>(tb, ck, e, u));
         }
-        run += (u32)m;
-        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     bids.flush(vmin0, nullptr);
@@ -894,14 +882,14 @@ __global__ __launch_bounds__(BLOCK) void unique_cost_kernel(const u64* __restric
 // the group's single atomicMin.  Every lane of the wave must call this.
 __device__ __forceinline__ void bid_grouped(u64* __restrict__ vmin, bool on, int x, u64 p) {
     const int lane = prim::lane_id();
-    const u64 ab = __ballot(on);
+    const u64 ab = prim::ballot(on);
     if (ab == 0) return;
     const u64 lt = prim::lanemask_lt();
     const u64 below = ab & lt;
     const int prev = below ? 63 - __clzll((long long)below) : lane;
     const int xprev = __shfl(x, prev, 64);
     const bool head = on && (below == 0 || xprev != x);
-    const u64 hb = __ballot(head);
+    const u64 hb = prim::ballot(head);
     const u64 hle = hb & (lt | (1ull << lane));
     const int dist = hle ? lane - (63 - __clzll((long long)hle)) : 0;  // lanes back to the group's head
     u64 q = on ? p : ~0ull;
@@ -1023,11 +1011,11 @@ __device__ __forceinline__ bool subround_edge(const SelArgs& A, const u64* __res
 // pairs formed, counted per mesh: one atomic per wave and mesh
 __device__ __forceinline__ void count_pairs(const SelArgs& A, bool sel, int m) {
     const int lane = prim::lane_id();
-    u64 sb = __ballot(sel);
+    u64 sb = prim::ballot(sel);
     while (sb) {
         const int leader = __ffsll((long long)sb) - 1;
         const int m0 = __shfl(m, leader, 64);
-        const u64 same = __ballot(sel && m == m0);
+        const u64 same = prim::ballot(sel && m == m0);
         if (lane == leader)
             atomicAdd(&A.mt.mslots[((size_t)m0 * MATCH_SLOTS + (blockIdx.x & (MATCH_SLOTS - 1))) * MATCH_PAD],
                       (int)__popcll(same));
@@ -1046,7 +1034,7 @@ struct PairTally {
         pairs = 0;
     }
     __device__ __forceinline__ void count(const SelArgs& A, bool sel, int m) {
-        const u64 mine = __ballot(sel && m == mesh);
+        const u64 mine = prim::ballot(sel && m == mesh);
         if (mine && prim::lane_id() == 0) atomicAdd(&pairs, (int)__popcll(mine));
         if (A.mt.B > 1) count_pairs(A, sel && m != mesh, m);
     }
@@ -1059,11 +1047,11 @@ struct PairTally {
 // The same into an LDS array (one workgroup's own tally).
 __device__ __forceinline__ void count_pairs_lds(int* pairs, bool sel, int m) {
     const int lane = prim::lane_id();
-    u64 sb = __ballot(sel);
+    u64 sb = prim::ballot(sel);
     while (sb) {
         const int leader = __ffsll((long long)sb) - 1;
         const int m0 = __shfl(m, leader, 64);
-        const u64 same = __ballot(sel && m == m0);
+        const u64 same = prim::ballot(sel && m == m0);
         if (lane == leader) atomicAdd(&pairs[m0], (int)__popcll(same));
         sb &= ~same;
     }
@@ -1071,7 +1059,7 @@ __device__ __forceinline__ void count_pairs_lds(int* pairs, bool sel, int m) {
 
 // The lanes' live edges appended to their workgroup's segment of the tail's list.  By all lanes of a wave.
 __device__ __forceinline__ void append_live(const SelArgs& A, bool alive, int e) {
-    const u64 b = __ballot(alive);
+    const u64 b = prim::ballot(alive);
     if (b == 0) return;
     const int seg = blockIdx.x & (LIVE_SEGS - 1), first = __ffsll((long long)b) - 1;
     int at = 0;
@@ -1373,7 +1361,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
                 alive = L.vkey[su] != TAIL_PAIRED && L.vkey[sv] != TAIL_PAIRED;
                 if (alive) L.bid[su] = L.bid[sv] = VMIN_NONE;
             }
-            const u64 ab = __ballot(alive);
+            const u64 ab = prim::ballot(alive);
             if (ab) {
                 int wbase = 0;
                 if (lane == 0) wbase = atomicAdd(&L.cnt[nxt], (int)__popcll(ab));
@@ -1893,8 +1881,8 @@ __global__ __launch_bounds__(BLOCK) void select_pass_kernel(Keys K, const int* _
         // one digit count themselves with a single LDS atomic
         ok = ok && (j == 0 || (k >> (shift + width)) == (tie ? a.tie : a.cost));
         const u32 d = (k >> shift) & ((1u << width) - 1u);
-        const u64 same = prim::wave_same_digit_lanes(ok, d);
-        if (ok && (same & prim::lanemask_lt()) == 0) atomicAdd(&h[d], (u32)__popcll(same));
+        const prim::SameDigit same = prim::wave_same_digit(ok, d);
+        if (ok && same.below == 0) atomicAdd(&h[d], same.count);
     }
     __syncthreads();
     for (int i = t; i < SELECT_BINS; i += BLOCK) {
@@ -2089,7 +2077,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                                                          int cur, int chunks, const int* __restrict__ tilesum, int prefixed,
                                                          int B, const int* __restrict__ voff_cur, int* __restrict__ voff_nxt,
                                                          const int* __restrict__ active, int* __restrict__ done,
-                                                         int* __restrict__ htab, int n_clear, u32* __restrict__ msd_hist,
+                                                         int* __restrict__ htab, int n_clear,
                                                          float rcond_min, const int* __restrict__ arep,
                                                          const int* __restrict__ acnt, const u64* __restrict__ akey, int vbits,
                                                          const int* __restrict__ guard) {
@@ -2098,8 +2086,6 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
     const int nv = st->nv[cur];
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
-    // this round's edge keys are long sorted: their digit counts and cursors go back to zero for the next round
-    for (int i = g; i < 2 * prim::MSD_HIST_WORDS; i += stride) msd_hist[i] = 0;
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
     for (int b = g; b < B; b += stride)
         if (active[b]) done[b] = 1;
@@ -2120,7 +2106,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
     u32 cnt = 0;
     for (int c = 0; c < chunks; ++c) {
         const long long i = i0 + c * 64 + lane;
-        cnt += (u32)__popcll(__ballot(i < nv && survives((int)i)));
+        cnt += (u32)__popcll(prim::ballot(i < nv && survives((int)i)));
     }
     __syncthreads();
     if (lane == 0) smem[w64] = cnt;
@@ -2135,7 +2121,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
     for (int c = 0; c < chunks; ++c) {
         const long long i = i0 + c * 64 + lane;
         const bool alive = i < nv && survives((int)i);
-        const u64 bal = __ballot(alive);
+        const u64 bal = prim::ballot(alive);
         const u32 incl = run + (u32)__popcll(bal & (prim::lanemask_lt() | (1ull << lane)));
         flagged_before(voff_cur, B, i0 + c * 64, incl, voff_nxt);  // a mesh starts behind the survivors of those in front of it
         run += (u32)__popcll(bal);

@@ -76,6 +76,8 @@ struct picasso_ctx {
     unsigned char* keep = nullptr;
     int* fslot = nullptr;  // per facet: the hash-table slot that decides about it
     int* tilesum = nullptr;
+    u32* distinct = nullptr;  // the edge sort's distinct keys per bucket, then per prim::UNIQUE_GROUP buckets
+    size_t distinct_cap = 0;  // ... buckets
     prim::SortScratch sort_sc{};
     u32* hist12 = nullptr;  // the bucket sorts' top-digit counts, cursors and first positions (3 x prim::MSD_HIST_WORDS)
     // The vertex->facet sort has buffers and scratch of its own, so that in the first round it can
@@ -83,7 +85,7 @@ struct picasso_ctx {
     u64* s0_key[2] = {nullptr, nullptr};  // incidence keys (vertex, facet) of S0 and their sort's second buffer
     u32* hist12_s0 = nullptr;
     prim::XlScratch xl{}, xl_s0{};  // the same for the sorts of very large inputs
-    bool hist_dirty = true;  // hist12 may hold counts (it is zero between sorts otherwise)
+    bool hist_dirty = true;  // hist12 may hold counts (the sorts leave it zero)
     int64_t opt_overlap = 1;
     int64_t opt_trunc_block_max = TRUNC_BLOCK_CAP;
     // per-mesh tables
@@ -216,6 +218,8 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->keep = cv.take<unsigned char>(f);
     x->fslot = cv.take<int>(f);
     x->tilesum = cv.take<int>((size_t)prim::compact_tilesum_capacity((long long)std::max(h, n)));
+    x->distinct_cap = prim::bucket_capacity((long long)h);
+    x->distinct = cv.take<u32>(x->distinct_cap + x->distinct_cap / prim::UNIQUE_GROUP * prim::UNIQUE_PAD);
     x->sort_sc.T = prim::sort_table_stride((long long)h);
     x->sort_sc.table = cv.take<u32>((size_t)256 * x->sort_sc.T);
     x->sort_sc.totals = cv.take<u32>(256);
@@ -305,15 +309,30 @@ struct KernelBracket {
     KernelBracket& operator=(const KernelBracket&) = delete;
 };
 
-// Bits of a vertex in the edge keys, of a facet in the incidence keys: what the largest number needs, but enough for as many
-// keys to have the top digit that prim::key_sort partitions them on.
+// Bits of a vertex in the edge keys, of an item in the keys of row lists: what the largest number needs, but enough for as many
+// keys to have the top digit that prim::key_sort partitions them on.  Of a vertex in the incidence keys: the digit lies
+// within them, so that a bucket holds whole vertices.
 inline int edge_vertex_bits(int nv, long long n_keys) { return std::max(ceil_log2(nv), prim::key_bits_wanted(n_keys) / 2); }
 inline int item_bits(int n_rows, int n_items, long long n_keys) {
     return std::max(ceil_log2(std::max(n_items, 1)), prim::key_bits_wanted(n_keys) - ceil_log2(n_rows));
 }
-inline int incidence_fbits(int N, int F) { return item_bits(N, F, 3ll * F); }
+inline int incidence_fbits(int F) { return ceil_log2(std::max(F, 1)); }
+inline int incidence_key_bits(int N, int F) {
+    const int vbits = ceil_log2(N), fbits = incidence_fbits(F);
+    return std::max(vbits, prim::key_digit_bits(3ll * F, vbits + fbits)) + fbits;
+}
 
 // A sort of up to n keys made from `items` items (KeySort), with the context's first or second set of arrays.
+// Keys (row << item_bits) | item of n_rows rows: only so many digits occur, and, where rows are short, the bits of the row below
+// the digit make the groups that the per-bucket kernel sorts in registers.  (Nine bits always: every other group of a lattice of 10 M
+// vertices empty.)
+void rows_of(prim::KeySort<u64>& S, int n_rows, int item_bits, long long n) {
+    const int within = S.low_bits() - item_bits;  // bits of the row below the digit
+    if (within < 0) return;
+    S.buckets = (int)(((long long)n_rows + (1ll << within) - 1) >> within);
+    if (within >= 1 && within < S.group_bits && n <= 8ll * n_rows) S.group_bits = within;
+}
+
 // Kernels that count the keys' digits for it go by COUNT_ (see init_kernel) and its DigitCount.
 prim::KeySort<u64> key_sort_for(picasso_ctx* c, bool second_set, long long n, int items, int key_bits) {
     prim::KeySort<u64> S;
@@ -322,6 +341,8 @@ prim::KeySort<u64> key_sort_for(picasso_ctx* c, bool second_set, long long n, in
     S.n = items;
     S.key_bits = key_bits;
     S.digit_bits = prim::key_digit_bits(n, key_bits);
+    S.half = S.fits_half();
+    S.buckets = 1 << S.digit_bits;
     if (S.digit_bits > prim::BUCKET_LARGE_MSD_BITS) {
         const prim::XlScratch& x = second_set ? c->xl_s0 : c->xl;
         S.hist = x.hist;
@@ -345,22 +366,29 @@ void clear_wide_counts(hipStream_t s, const prim::KeySort<u64>& S) {
     if (count_kind(S) == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << S.digit_bits), BLOCK, 0, s>>>(S.hist, 1 << S.digit_bits, 0u);
 }
 
-// The sort of the edge keys of a round with nvt vertices and at most nfb facets that have not collapsed, of F.  It
-// also counts, per tile of the compaction that follows, the keys that differ from
-// the key in front of them: the count pass of the unique step.
+// The sort of the edge keys of a round with nvt vertices and at most nfb facets that have not collapsed, of F.
 prim::KeySort<u64> edge_sort(picasso_ctx* c, int nvt, int nfb, int F) {
-    const int H = 3 * nfb, vbits = edge_vertex_bits(nvt, H), chunks = prim::compact_chunks_for(H);
-    prim::KeySort<u64> S = key_sort_for(c, false, H, 3 * F, 2 * vbits);
-    S.tilesum = c->tilesum;
-    S.tiles = prim::compact_tiles(H, chunks);
-    S.tile_shift = ceil_log2((long long)BLOCK * chunks);
-    S.sentinel = edge_sentinel(vbits);
+    const int H = 3 * nfb, vbits = edge_vertex_bits(nvt, H);
+    prim::KeySort<u64> S = key_sort_for(c, false, H, F, 2 * vbits);
+    rows_of(S, nvt, vbits, H);
+    S.zero = c->distinct + c->distinct_cap;  // (the counts per group of buckets)
+    S.n_zero = (1 << S.digit_bits) / prim::UNIQUE_GROUP * prim::UNIQUE_PAD;
     S.total = &c->st->nh;
     return S;
 }
+prim::DistinctKeys distinct_keys(picasso_ctx* c) { return prim::DistinctKeys{c->distinct, c->distinct + c->distinct_cap}; }
 // ... and of the incidence keys.
 prim::KeySort<u64> incidence_sort(picasso_ctx* c, int N, int F) {
-    return key_sort_for(c, true, 3ll * F, 3 * F, ceil_log2(N) + incidence_fbits(N, F));
+    prim::KeySort<u64> S = key_sort_for(c, true, 3ll * F, F, incidence_key_bits(N, F));
+    rows_of(S, N, incidence_fbits(F), 3ll * F);
+    return S;
+}
+
+// Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
+// before the first round's costs are computed (24 bytes per facet there, 16 needed).
+inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c->ekey); }
+QuadricRows quadric_rows(picasso_ctx* c, const float* d_verts, int N, int F) {
+    return QuadricRows{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F)};
 }
 
 RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
@@ -384,62 +412,73 @@ void launch_edge_keys(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_
 #undef PICASSO_EDGE_KEYS
 }
 
-// Sorts the edge keys (whose digits have been counted): they end up in key64[0].
+// Sorts the edge keys (whose digits have been counted) and lists the distinct ones (edge_list).
 bool sort_edges(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, int round_) {
-    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<EdgeKeys>{{c->fcur, S.key_bits / 2}},
+    c->hist_dirty = false;
+    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<EdgeKeys>{{c->fcur, S.key_bits / 2}}, distinct_keys(c),
                           c->kt_this_call ? &c->kt : nullptr, round_);
 }
-bool sort_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, int N, int F) {
-    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<IncidenceKeys>{{c->fcur, incidence_fbits(N, F)}},
-                          c->kt_this_call ? &c->kt : nullptr, PICASSO_KERNEL_SORT_INCIDENCE << 8);
+// Sorts the incidence keys and sums the vertices' quadrics.
+bool sort_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, const float* d_verts, int N, int F) {
+    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<IncidenceKeys>{{c->fcur, incidence_fbits(F)}},
+                          quadric_rows(c, d_verts, N, F), c->kt_this_call ? &c->kt : nullptr, PICASSO_KERNEL_QUADRIC_ROWS << 8,
+                          PICASSO_KERNEL_SORT_INCIDENCE << 8);
 }
-// Both sorts of the first round in the same launches.
-bool sort_edges_and_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& E, const prim::KeySort<u64>& I, int N, int F) {
-    return prim::key_sort(s, I, &E, prim::TwoSources<IncidenceKeys, EdgeKeys>{{c->fcur, incidence_fbits(N, F)}, {c->fcur, E.key_bits / 2}});
+// Both in the same launches.
+bool sort_edges_and_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& E, const prim::KeySort<u64>& I,
+                               const float* d_verts, int N, int F) {
+    c->hist_dirty = false;
+    return prim::key_sort(s, I, &E, prim::TwoSources<IncidenceKeys, EdgeKeys>{{c->fcur, incidence_fbits(F)}, {c->fcur, E.key_bits / 2}},
+                          prim::TwoOuts<QuadricRows, prim::DistinctKeys>{quadric_rows(c, d_verts, N, F), distinct_keys(c)});
 }
 
-// Distinct edges, costs and first bids from the sorted keys of E, at most H of them.
+// Costs and first bids of the distinct edges that sort E of at most H keys has left.
 void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& E, int H, const MeshTab& mt, const TieBreak& tb,
                         const VRec* vrec) {
-    const int chunks = prim::compact_chunks_for(H), tiles = prim::compact_tiles(std::max(H, 1), chunks);
-    const int prefixed = tiles > prim::COMPACT_MAX_SUMMED_TILES;
-#define PICASSO_UNIQUE(PLACE, SHUFFLE, CHUNKS)                                                                            \
-    unique_cost_kernel<PLACE, SHUFFLE, CHUNKS><<<tiles, BLOCK, 0, s>>>(E.k0, &c->st->nh, c->tilesum, prefixed, c->ekey,   \
-                                                                       c->ecost, c->estate, vrec, c->vmin[0], E.key_bits / 2, \
-                                                                       mt, c->opt_rcond_min, tb, &c->st->ne)
-#define PICASSO_UNIQUE_CHUNKS(PLACE, SHUFFLE)                     \
-    do {                                                          \
-        if (chunks == 1) PICASSO_UNIQUE(PLACE, SHUFFLE, 1);       \
-        else if (chunks == 4) PICASSO_UNIQUE(PLACE, SHUFFLE, 4);  \
-        else PICASSO_UNIQUE(PLACE, SHUFFLE, 16);                  \
+    EdgeList L{E.k1, E.starts, c->distinct, c->distinct + c->distinct_cap, H > 0 ? E.buckets : 0, E.low_bits(), 0, 0};
+    // workgroups (edges are about half the keys): few edges each while there are few, for the chip's sake, then as many as their bids' table takes
+    const long long wanted = std::max<long long>((long long)H / 2 / UNIQUE_EDGES_MAX, std::min<long long>((long long)H / 2 / UNIQUE_EDGES_MIN, UNIQUE_GROUPS_MIN));
+    while (L.split_shift < 6 && (long long)L.buckets << L.split_shift < wanted) ++L.split_shift;
+    while (L.split_shift == 0 && L.join_shift < UNIQUE_JOIN_MAX && L.buckets >> (L.join_shift + 1) >= wanted) ++L.join_shift;
+    const int grid = L.buckets > 0 ? prim::xcd_grid((((L.buckets - 1) >> L.join_shift) + 1) << L.split_shift) : 1;
+    const bool wide = (long long)H / 2 > (long long)grid * UNIQUE_EDGES_NARROW;
+#define PICASSO_UNIQUE_LINES(PLACE, SHUFFLE, LK, LINES)                                                                       \
+    unique_cost_kernel<PLACE, SHUFFLE, LK, LINES><<<grid, BLOCK, 0, s>>>(L, c->ekey, c->ecost, c->estate, vrec, c->vmin[0],          \
+                                                                  E.key_bits / 2, mt, c->opt_rcond_min, tb, &c->st->ne)
+#define PICASSO_UNIQUE_LK(PLACE, SHUFFLE, LK)                      \
+    do {                                                           \
+        if (wide) PICASSO_UNIQUE_LINES(PLACE, SHUFFLE, LK, 256);   \
+        else PICASSO_UNIQUE_LINES(PLACE, SHUFFLE, LK, 128);        \
+    } while (0)
+#define PICASSO_UNIQUE(PLACE, SHUFFLE)                             \
+    do {                                                           \
+        if (E.half) PICASSO_UNIQUE_LK(PLACE, SHUFFLE, u32);        \
+        else PICASSO_UNIQUE_LK(PLACE, SHUFFLE, u64);               \
     } while (0)
     if (c->opt_placement == PLACE_INVERSE) {
-        if (tb.on) PICASSO_UNIQUE_CHUNKS(PLACE_INVERSE, true);
-        else PICASSO_UNIQUE_CHUNKS(PLACE_INVERSE, false);
+        if (tb.on) PICASSO_UNIQUE(PLACE_INVERSE, true);
+        else PICASSO_UNIQUE(PLACE_INVERSE, false);
     } else {
-        if (tb.on) PICASSO_UNIQUE_CHUNKS(PLACE_MEAN, true);
-        else PICASSO_UNIQUE_CHUNKS(PLACE_MEAN, false);
+        if (tb.on) PICASSO_UNIQUE(PLACE_MEAN, true);
+        else PICASSO_UNIQUE(PLACE_MEAN, false);
     }
-#undef PICASSO_UNIQUE_CHUNKS
 #undef PICASSO_UNIQUE
+#undef PICASSO_UNIQUE_LK
+#undef PICASSO_UNIQUE_LINES
 }
 
 // Up to this many facets the facet set is cleared by the call's first kernel (see launch_init).
 constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
-
-// Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
-// before the first round's costs are computed (24 bytes per facet there, 16 needed).
-inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c->ekey); }
 
 // The validating kernel, instantiated for the sorts its keys go to.  work: rounds (or S0) follow; edges: the first round's
 // set-up and edges as well.
 int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, const int32_t* d_facets, int F, int B,
                 bool work, bool edges, HeaderInit init = HeaderInit{nullptr, 0, 0, 0, 0, 0, 0, 0}) {
     const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F);
-    if (work && c->hist_dirty)  // (a call ended between a count of its edges and the contraction that clears it)
+    if (work && c->hist_dirty)  // (a call ended between a count of its edges and their sort)
         prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, 2 * prim::MSD_HIST_WORDS, 0u);
     if (work) {
-        c->hist_dirty = edges;
+        c->hist_dirty = edges && F > 0;
         clear_wide_counts(s, I);
         if (edges) clear_wide_counts(s, E);
     }
@@ -448,7 +487,7 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     const int n_clear = F <= CLEAR_AHEAD_MAX_FACETS ? (int)facet_slots((size_t)F) : 0;
 #define PICASSO_INIT(COUNT)                                                                                                    \
     init_kernel<COUNT><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
-        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, incidence_fbits(N, F), digit_count(I),   \
+        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, incidence_fbits(F), digit_count(I),   \
         digit_count(E), edges ? 1 : 0, E.key_bits / 2, c->st, init, planes, c->htab, n_clear, c->vmin[0], c->vmin[1], c->mate, \
         c->pcost(), round_tab(c, B, 0, 0))
     if (!work) PICASSO_INIT(COUNT_NONE);
@@ -457,18 +496,6 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     else PICASSO_INIT(COUNT_XL);
 #undef PICASSO_INIT
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
-}
-
-// The vertices' quadrics from the sorted incidence keys.
-void launch_quadric_rows(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& I, const float* d_verts, int N, int F) {
-    const int H = 3 * F;
-    if (F > 0) {
-        const KernelBracket timed(c, s, PICASSO_KERNEL_QUADRIC_ROWS, 0);
-        quadric_rows_kernel<<<(H + QR_TILE - 1) / QR_TILE, BLOCK, 0, s>>>(c->vrec[0], d_verts, N, facet_planes(c), I.k0, H,
-                                                                         incidence_fbits(N, F), c->hist12_s0);
-    } else {
-        quadric_rows_kernel<<<grid_for(N, 4096), BLOCK, 0, s>>>(c->vrec[0], d_verts, N, nullptr, nullptr, 0, 0, c->hist12_s0);
-    }
 }
 
 // Fills the pinned image of the header (State + per-mesh tables) and sends it with one copy.
@@ -711,18 +738,18 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // input, not on each other: they share their launches.  (Not when stage times are being recorded, to keep them
     // attributable, and in a call whose kernels are bracketed by events: a bracketed kernel then has the chip to itself,
     // and its duration is its own.)
-    const bool together = work && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call;
+    const bool together = work && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
+                          edge_sort(c, N, F, F).half == incidence_sort(c, N, F).half;
     tm.begin(0, PICASSO_ST_QUADRICS);
     rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, work, hinit);
     if (rc != PICASSO_OK) return rc;
     if (work) {
         const prim::KeySort<u64> I = incidence_sort(c, N, F);
         if (together) {
-            if (!sort_edges_and_incidences(c, s, edge_sort(c, N, F, F), I, N, F)) return PICASSO_ERR_HIP;
+            if (!sort_edges_and_incidences(c, s, edge_sort(c, N, F, F), I, d_verts, N, F)) return PICASSO_ERR_HIP;
         } else if (F > 0) {
-            if (!sort_incidences(c, s, I, N, F)) return PICASSO_ERR_HIP;
+            if (!sort_incidences(c, s, I, d_verts, N, F)) return PICASSO_ERR_HIP;
         }
-        launch_quadric_rows(c, s, I, d_verts, N, F);
     }
     tm.end();
 
@@ -748,7 +775,6 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F);
         if (round > 0) launch_edge_keys(c, s, B, round, cur, E, N, F);
         if (!(round == 0 && together) && H > 0 && !sort_edges(c, s, E, round)) return PICASSO_ERR_HIP;
-        if (H > 0) prim::compact_scan_sums(s, &c->st->nh, H, c->tilesum);
         renumbered = false;
         {
             const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);
@@ -775,7 +801,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     contract_kernel<PLACE, ABSORB><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, c->vmap, c->st, cur,  \
                                                            chunks, c->tilesum, prefixed, B, c->voff[cur],             \
                                                            c->voff[nxt], c->active, c->done, c->htab, (int)clear,     \
-                                                           c->hist12, RCOND, c->arep, c->acnt, akeys, vbits, guard)
+                                                           RCOND, c->arep, c->acnt, akeys, vbits, guard)
             if (c->opt_placement == PLACE_INVERSE) {
                 if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, c->opt_rcond_min);
                 else PICASSO_CONTRACT(PLACE_INVERSE, false, c->opt_rcond_min);
@@ -985,7 +1011,6 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             tm.end();
             slots_clear = std::max(slots_clear, clear);
         }
-        c->hist_dirty = false;
         nv_total -= n_sel + n_joined;
         cur ^= 1;
         ++round;
@@ -1049,15 +1074,15 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const double nv = c->nv_round[rd], nf = c->nf_round[rd], ne = c->ne_round[rd], H = 3.0 * nf;
             double bytes = 0.0;
             switch (kernel) {
-                case PICASSO_KERNEL_SORT: bytes = 16.0 * H; break;
-                case PICASSO_KERNEL_UNIQUE_COST: bytes = 8.0 * H + 13.0 * ne + 72.0 * nv; break;
+                case PICASSO_KERNEL_SORT: bytes = 4.0 * H + 4.0 * ne; break;
+                case PICASSO_KERNEL_UNIQUE_COST: bytes = 17.0 * ne + 72.0 * nv; break;
                 case PICASSO_KERNEL_SUBROUND0: bytes = 14.0 * ne + 24.0 * nv; break;
                 case PICASSO_KERNEL_FACET_INSERT:  // (the last round's is another kernel)
                     if (rd + 1 < c->n_rounds_noted) bytes = 24.0 * nf + 4.0 * nv + 8.0 * (double)N + 24.0 * (double)c->nv_round[rd + 1];
                     else bytes = 28.0 * nf + 4.0 * nv + 8.0 * (double)N + (drop ? 0.0 : 28.0 * (double)nv_total);
                     break;
-                case PICASSO_KERNEL_SORT_INCIDENCE: bytes = 48.0 * (double)F; break;
-                default: bytes = 24.0 * (double)F + 16.0 * (double)F + 76.0 * (double)N; break;  // QUADRIC_ROWS
+                case PICASSO_KERNEL_SORT_INCIDENCE: bytes = 24.0 * (double)F; break;
+                default: bytes = 12.0 * (double)F + 16.0 * (double)F + 76.0 * (double)N; break;  // QUADRIC_ROWS
             }
             c->kt_launches[kernel] += 1;
             c->kt_ms[kernel] += ms;
@@ -1093,8 +1118,7 @@ int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts,
         return rc;
     }
     const prim::KeySort<u64> I = incidence_sort(c, N, F);
-    if (F > 0 && !sort_incidences(c, s, I, N, F)) return PICASSO_ERR_HIP;
-    launch_quadric_rows(c, s, I, d_verts, N, F);
+    if (F > 0 && !sort_incidences(c, s, I, d_verts, N, F)) return PICASSO_ERR_HIP;
     return PICASSO_OK;
 }
 
@@ -1146,6 +1170,7 @@ int build_csr(picasso_ctx* c, hipStream_t s, const int32_t* d_row_of, int n, int
     prim::KeySort<u64> S = key_sort_for(c, true, n, n, ibits + ceil_log2(n_rows));
     S.k0 = c->key64[0];
     S.k1 = c->key64[1];
+    rows_of(S, n_rows, ibits, n);
     clear_wide_counts(s, S);
     int* err = &c->st->err;
     switch (count_kind(S)) {
@@ -1153,8 +1178,8 @@ int build_csr(picasso_ctx* c, hipStream_t s, const int32_t* d_row_of, int n, int
         case COUNT_LARGE: csr_count_kernel<COUNT_LARGE><<<prim::sort_tiles(n, 16), BLOCK, 0, s>>>(src, n, digit_count(S), err); break;
         default: csr_count_kernel<COUNT_XL><<<prim::sort_tiles(n, CSR_COUNT_ITEMS), BLOCK, 0, s>>>(src, n, digit_count(S), err);
     }
-    if (!prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<RowKeys>{src})) return PICASSO_ERR_HIP;
-    csr_finish_kernel<<<grid_for(n), BLOCK, 0, s>>>(S.k0, ibits, n, n_rows, d_off, d_items, c->hist12_s0);
+    const RowLists out{d_off, d_items, n, n_rows, ibits, S.digit_bits};
+    if (!prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<RowKeys>{src}, out)) return PICASSO_ERR_HIP;
     const int rc = read_header(c, s);
     if (rc != PICASSO_OK) return rc;
     HIP_TRY(c, hipGetLastError());
@@ -1415,7 +1440,6 @@ int picasso_edge_costs(picasso_ctx* c, void* stream, const float* d_verts, int32
     const prim::KeySort<u64> E = edge_sort(c, N, F, F);
     if (F > 0) {
         if (!sort_edges(c, s, E, 0)) return PICASSO_ERR_HIP;
-        prim::compact_scan_sums(s, &c->st->nh, H, c->tilesum);
     }
     launch_unique_cost(c, s, E, H, mt, TieBreak{0u, 0u, 0u}, c->vrec[0]);
     export_edges_kernel<<<grid_for(std::max(H, 1)), BLOCK, 0, s>>>(c->ekey, c->ecost, c->st, vbits, d_edges_out,

@@ -19,25 +19,52 @@ __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 __device__ __forceinline__ int wave_id() { return (int)(threadIdx.x >> 6); }
 __device__ __forceinline__ u64 lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
-// For a lane with `ok`: the lanes of its wave (itself included) that hold the same digit `d`, worked out
+// (the builtin: HIP's __ballot takes an int, which costs two vector instructions more)
+__device__ __forceinline__ u64 ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// lanes of the mask below this one
+__device__ __forceinline__ u32 mask_below(u64 m) {
+    return __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u));
+}
+
+// Inclusive prefix sums over the lanes of a wave, all of which must be active: rows of 16 by shifts, then each row's last lane into the
+// rows behind it (six additions with the lane moves in them, where shuffles take about 40 instructions and six trips to LDS).
+__device__ __forceinline__ u32 wave_inclusive_scan(u32 v) {
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// The lanes with `ok` of a wave that hold the same digit `d`, worked out
 // for the first WAVE_DIGIT_PEEL distinct digits among the wave's lanes; a lane whose digit comes after
-// those is left alone in its mask.  Lanes without `ok` get 0.  Keys in mesh order mostly bring one to
-// three distinct leading digits into a wave, so one LDS atomic per digit (by the first lane of each
-// mask, adding the mask's population) replaces up to 64 atomics on the same address.  By all lanes.
+// those is left alone.  Keys in mesh order mostly bring one to
+// three distinct leading digits into a wave, so one LDS atomic per digit (by the lane with below = 0,
+// adding the count) replaces up to 64 atomics on the same address.  By all lanes.
 constexpr int WAVE_DIGIT_PEEL = 4;
-__device__ __forceinline__ u64 wave_same_digit_lanes(bool ok, u32 d) {
-    u64 rem = __ballot(ok);
-    u64 mine = ok ? (1ull << lane_id()) : 0ull;
+struct SameDigit {
+    u32 below, count;  // lanes with the digit in front of this one, and all of them
+    int lead;          // the first of them
+};
+__device__ __forceinline__ SameDigit wave_same_digit(bool ok, u32 d) {
+    SameDigit r{0u, 1u, lane_id()};
+    u64 rem = ballot(ok);
 #pragma unroll
     for (int j = 0; j < WAVE_DIGIT_PEEL; ++j) {
         if (rem == 0) break;
-        const int lead = __ffsll((long long)rem) - 1;
-        const u32 d0 = (u32)__builtin_amdgcn_readlane((int)d, lead);
-        const u64 m = __ballot(ok && d == d0);
-        if (ok && d == d0) mine = m;
+        const int lead = (int)__builtin_ctzll(rem);
+        const bool in = ok && d == (u32)__builtin_amdgcn_readlane((int)d, lead);
+        const u64 m = ballot(in);
+        if (in) {
+            r.below = mask_below(m);
+            r.count = (u32)__popcll(m);
+            r.lead = lead;
+        }
         rem &= ~m;
     }
-    return mine;
+    return r;
 }
 
 // Workgroups are dealt out to the 8 XCDs in turn; so that neighbouring tiles of a list share an XCD's L2 (they refer to
@@ -56,12 +83,7 @@ __device__ __forceinline__ int load_count(const int* n_ptr, int n_host) { return
 // `total` receives the block sum.  smem must hold WAVES words.  Contains barriers.
 __device__ __forceinline__ u32 block_exclusive_scan(u32 v, u32* smem, u32& total) {
     const int lane = lane_id(), w = wave_id();
-    u32 incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        u32 o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
+    const u32 incl = wave_inclusive_scan(v);
     __syncthreads();  // smem may still be in use by a previous call
     if (lane == 63) smem[w] = incl;
     __syncthreads();
@@ -78,10 +100,9 @@ __device__ __forceinline__ u32 block_exclusive_scan(u32 v, u32* smem, u32& total
 
 __device__ __forceinline__ u32 block_sum(u32 v, u32* smem) {
     const int lane = lane_id(), w = wave_id();
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    v = wave_inclusive_scan(v);
     __syncthreads();
-    if (lane == 0) smem[w] = v;
+    if (lane == 63) smem[w] = v;
     __syncthreads();
     u32 tot = 0;
 #pragma unroll
@@ -136,7 +157,7 @@ __device__ __forceinline__ void wave_rank_digits(const u32 (&digit)[ITEMS], int 
                 for (int b = 0; b < WAVE_RANK_MAX_BITS; ++b) {
                     if (b < bits) {
                         const int own = (int)(d << (31 - b)) >> 31;  // 0 or -1
-                        const u64 bal = __ballot(own != 0);
+                        const u64 bal = ballot(own != 0);
                         dlo |= (u32)bal ^ (u32)own;
                         dhi |= (u32)(bal >> 32) ^ (u32)own;
                     }
@@ -384,12 +405,7 @@ constexpr long long BUCKET_SORT_MAX_KEYS = 1ll << 20;  // average bucket <= half
 template <int NW>
 __device__ __forceinline__ u32 wide_block_exclusive_scan(u32 v, u32* smem, u32& total) {
     const int lane = lane_id(), w = wave_id();
-    u32 incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        u32 o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
+    const u32 incl = wave_inclusive_scan(v);
     __syncthreads();
     if (lane == 63) smem[w] = incl;
     __syncthreads();
@@ -442,10 +458,10 @@ __device__ void bucket_sort_oversize(K* a, K* b, u32* va, u32* vb, int cnt, int 
                 const bool ok = i < cnt;
                 const K k = ok ? coherent_load(&src[i]) : (K)0;
                 const u32 d = ok ? digit_of<K>(k, shift, dmask) : 0xFFFFFFFFu;
-                u64 m = __ballot(ok);
+                u64 m = ballot(ok);
                 for (int bb = 0; bb < bits; ++bb) {
                     const bool bit = (d >> bb) & 1u;
-                    const u64 bal = __ballot(bit);
+                    const u64 bal = ballot(bit);
                     m &= bit ? bal : ~bal;
                 }
                 if (ok) {
@@ -721,43 +737,54 @@ __global__ __launch_bounds__(BUCKET_THREADS) void bucket_sort_kernel(K* __restri
 // A sort of keys WITHOUT values by partition on their top digit and a sort of each bucket (key_sort).
 template <typename K>
 struct KeySort {
-    K* k0 = nullptr;  // receives the sorted keys
-    K* k1 = nullptr;  // ... the partitioned ones
+    K* k0 = nullptr;  // receives the sorted keys (PlainKeys), or is scratch for buckets that do not fit LDS
+    K* k1 = nullptr;  // receives the partitioned keys
     const int* n_ptr = nullptr;
     int n = 0;        // items of the source (at *n_ptr, where that is given, and n at most)
     int key_bits = 0, digit_bits = 0;
-    u32* hist = nullptr;    // keys per digit
-    u32* cursor = nullptr;  // as much of each digit's range as is taken: zero (8-bit digits), or set by key_starts_kernel
+    int buckets = 0;     // digits that occur are below this
+    int group_bits = BUCKET_GROUP_BITS;  // bits below the digit that make a group (see sort_bucket)
+    // Behind the partition the keys are 32-bit words (in k1, and in k0 where that is scratch): their low 32 bits, which hold
+    // all that a bucket's keys differ in.  Half the bytes of three sweeps.
+    bool half = false;
+    u32* hist = nullptr;    // keys per digit (zero again behind the sort)
+    u32* cursor = nullptr;  // as much of each digit's range as is taken: zero (8-bit digits; again behind the sort), or set by key_starts_kernel
     u32* starts = nullptr;  // first position of each digit's range
-    // What the sort may do for a compaction that follows it: the count pass of "keep the first of every run of equal keys,
-    // `sentinel` excepted" with tiles of 2^tile_shift positions (tilesum is zeroed on the way).  tilesum == nullptr: nothing.
-    int* tilesum = nullptr;
-    int tiles = 0, tile_shift = 0;
-    K sentinel = (K)0;
+    u32* zero = nullptr;    // n_zero words that the per-bucket kernel adds to: cleared by the kernel in front of it
+    int n_zero = 0;
     int* total = nullptr;   // receives the number of keys (those that the source keeps)
+    int low_bits() const { return key_bits - digit_bits; }
+    bool fits_half() const { return sizeof(K) == 8 && low_bits() <= 32; }
 };
 
 // ---------------------------------------------------------------------------
-// The per-bucket kernel for keys WITHOUT values (the sorts of the decimation path: incidence keys
-// and edge keys).  Equal keys are indistinguishable, so nothing has to be stable:
+// The per-bucket kernel for keys WITHOUT values (incidence keys, edge keys, lists of items per row).  Equal keys are
+// indistinguishable, so nothing has to be stable:
 //   1. the keys of the bucket are read once; each takes its place in its group (the keys that agree
-//      on the top 9 of the bucket's low bits: with vertex-pair keys the half-edges of one lower
-//      vertex) from one returning LDS atomic on the group's counter;
+//      on the top group_bits, 9 at most, of the bucket's low bits: the half-edges of one lower
+//      vertex, the items of one row) from one returning LDS atomic on the group's counter;
 //   2. one scan of the (up to 512) group counters gives the groups' first positions;
 //   3. one lane per group sorts its group on the whole key in registers with a sorting network of
 //      minimal size for 4, 6, 8, 12 or 16 keys (a wave runs every size that occurs among its 64
-//      groups, so the sizes are graded finely), by insertion up to 64 keys;
-//   4. the bucket is written out in order; optionally (COUNT_UNIQUE) the kernel also does the count
-//      pass of the compaction that keeps the first of every run of equal keys (the all-ones
-//      `sentinel` not counted): it adds, per tile of 2^tile_shift positions of the whole output, the
-//      number of such keys to tilesum[tile] (zero on entry), which is what tile_count_kernel would
-//      leave there.
+//      groups, so the sizes are graded finely), by ranks up to 64 keys;
+//   4. what the sort is for is made of the sorted keys while they are in LDS (`Out`: distinct keys, sums over rows, lists of
+//      rows), so that the sorted keys themselves are written nowhere.
 // A bucket with a group of more than 64 keys (a vertex of very high degree) is sorted as a whole by
 // a bitonic network over the LDS array.  A bucket beyond the LDS capacity (uneven vertex numbering:
 // up to 16 times the capacity) is sorted in parts, runs of whole groups that fit, each read out of the
-// bucket by the workgroup; if it also has a group of more than 64 keys, or is larger still, it
-// takes the slow global-memory route of bucket_sort_oversize.  Workgroups are small (256 lanes for the 4096-bucket
-// sorts) so that eight of them share a compute unit and cover each other's barriers.
+// bucket by the workgroup and written to k0; if it also has a group of more than 64 keys, or is larger still, it
+// takes the slow global-memory route of bucket_sort_oversize.  Out then gets the keys from there.  Workgroups are small (256
+// lanes for the 4096-bucket sorts) so that several of them share a compute unit and cover each other's barriers.
+// Bound by vector issue (three quarters of its time at 10.2 M vertices), so: lane counts and prefix sums by the instructions that
+// make them, no 64-bit arithmetic on 32-bit keys, groups that are the rows (not every other one empty), no workgroups for
+// digits that cannot occur.  First round of 10.2 M vertices / 61 M facet corners, incidence and edge keys: 611 us for the sorts, 472 for the
+// quadrics by a launch that read the sorted keys again, 437 for costs with the search for distinct edges; now 616 and 392.  1.2 M: 53 + 65 + 68
+// -> 63 + 52; 115 k: 12.5 + 10.4 + 14.4 -> 13.3 + 10.4; lists of 5.7 M corners 22.9 + 15.0 -> 19.7.
+// Bound by vector issue (three quarters of its time at 10.2 M vertices), so: lane counts and prefix sums by the instructions that
+// make them, no 64-bit arithmetic on 32-bit keys, groups that are the rows (not every other one empty), no workgroups for
+// digits that cannot occur.  First round of 10.2 M vertices, 61 M incidence and 61 M edge keys: 611 us for the sorts, 472 for the
+// quadrics by a launch that read the sorted keys again, 437 for costs with the search for distinct edges; now 616 and 392.  1.2 M:
+// 53 + 65 + 68 -> 63 + 52; 115 k: 12.5 + 10.4 + 14.4 -> 13.3 + 10.4; lists of 5.7 M corners 22.9 + 15.0 -> 19.7.
 // ---------------------------------------------------------------------------
 #define PRIM_CE(a, b)                       \
     {                                       \
@@ -812,80 +839,49 @@ __device__ __forceinline__ void group_sort_lds(K* skey, int gs, int g) {
         if (j < g) skey[gs + j] = k[j];
 }
 
-template <typename K, typename LK, int THREADS, int ITEMS, bool COUNT_UNIQUE>
-__global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int buckets_first) {
+
+template <typename LK, int THREADS, int ITEMS>
+struct BucketLds {
+    static constexpr int NW = THREADS / 64, CAP = THREADS * ITEMS, RMAX = 1 << BUCKET_GROUP_BITS;
+    LK skey[CAP];
+    u32 gcnt[RMAX];
+    u32 gstart[RMAX + 1];
+    u32 smem[NW];
+    u32 nlong;
+};
+
+// The cnt keys at kin sorted on their low_bits low bits by one workgroup; then emit(key_at), key_at(i) = the i-th of them (from LDS, or,
+// where they did not fit, from kout).  For cnt = 0 only emit is called.
+template <typename LK, int THREADS, int ITEMS, class Emit>
+__device__ __forceinline__ void sort_bucket(BucketLds<LK, THREADS, ITEMS>& L, LK* kin, LK* kout, const int cnt,
+                                            const int low_bits, const int group_bits, Emit emit) {
     constexpr int NW = THREADS / 64;
     constexpr int CAP = THREADS * ITEMS;
     constexpr int RMAX = 1 << BUCKET_GROUP_BITS;
     constexpr int PER = RMAX / THREADS > 0 ? RMAX / THREADS : 1;  // group counters per thread in the scan
     static_assert((CAP & (CAP - 1)) == 0, "the whole-bucket network pads to a power of two within the LDS array");
     static_assert(THREADS >= 64 && THREADS % 64 == 0 && (THREADS >= RMAX || RMAX % THREADS == 0), "whole counters per thread");
-    __shared__ LK skey[CAP];
-    __shared__ u32 gcnt[RMAX];
-    __shared__ u32 gstart[RMAX + 1];
-    __shared__ u32 smem[NW];
-    __shared__ u32 nlong;
-    constexpr int TALLY = (CAP >> 8) + 2;  // tiles (of at least 256 positions) that CAP consecutive positions can touch
-    static_assert(TALLY <= THREADS, "one thread per tile of the tally");
-    __shared__ int tcnt[COUNT_UNIQUE ? TALLY : 1];
+    LK* skey = L.skey;
+    u32* gcnt = L.gcnt;
+    u32* gstart = L.gstart;
     const int t = threadIdx.x, lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(wave_id());  // (in a scalar register: what follows from it is computed once per wave)
-    const bool second = (int)blockIdx.x >= buckets_first;
-    const KeySort<K>& S = second ? second_sort : first_sort;
-    const int bkt = (int)blockIdx.x - (second ? buckets_first : 0);
-    const int cnt = (int)S.hist[bkt];
-    if (cnt == 0) return;
-    const u32 start = S.starts[bkt];
-    K* __restrict__ kin = S.k1 + start;
-    K* __restrict__ kout = S.k0 + start;
-    const int low_bits = S.key_bits - S.digit_bits;
-    const K sentinel = S.sentinel;
-    int* __restrict__ tilesum = S.tilesum;
-    const int tile_shift = S.tile_shift;
-    const bool counting = COUNT_UNIQUE && tilesum != nullptr;
-
-    // By every lane of a wave together: the wave's lanes hold the output positions start + idx0 + lane
-    // (idx0 the same in all lanes), `first` says whether a lane's key is the first of its run; the
-    // counts go to the one or two tiles the 64 positions lie in: to the workgroup's tally in LDS
-    // (`tally`), or straight to memory.
-    const u32 tile0 = COUNT_UNIQUE ? start >> tile_shift : 0u;  // first tile this bucket's range touches
-    auto count_firsts = [&](int idx0, bool first, int* tally) {
-        const u64 bal = __ballot(first);
-        if (bal == 0 || !counting) return;
-        const u32 p0 = start + (u32)idx0;
-        const u32 tile_a = p0 >> tile_shift, tile_b = (p0 + 63u) >> tile_shift;
-        const u32 in_a = ((tile_a + 1u) << tile_shift) - p0;  // positions of the wave that lie in its first tile
-        const u64 mask_a = in_a >= 64u ? ~0ull : ((1ull << in_a) - 1ull);
-        if (lane == 0) {
-            const int ca = (int)__popcll(bal & mask_a), cb = (int)__popcll(bal & ~mask_a);
-            if (tally) {
-                if (ca) atomicAdd(&tally[tile_a - tile0], ca);
-                if (cb) atomicAdd(&tally[tile_b - tile0], cb);
-            } else {
-                if (ca) atomicAdd(&tilesum[tile_a], ca);
-                if (cb) atomicAdd(&tilesum[tile_b], cb);
-            }
-        }
-    };
-
-    const int gbits = low_bits < BUCKET_GROUP_BITS ? (low_bits > 0 ? low_bits : 0) : BUCKET_GROUP_BITS;
-    const int rest = low_bits - gbits;
+    const int gbits = min(group_bits, max(low_bits, 0));
+    const int rest = low_bits > gbits ? low_bits - gbits : 0;
     const u32 R = 1u << gbits, dmask = R - 1;
-    K upper = 0;  // what the keys of this bucket share above their low_bits bits
-    if constexpr (sizeof(LK) < sizeof(K)) upper = (K)(u32)bkt << low_bits;
 
     // The groups g0 .. g1 - 1, whose keys lie at [gstart[g] - gstart[g0], ...) of the LDS array, each sorted on
     // the whole key: one lane per group of up to 16 keys (a sorting network), then a wave per longer group.
     // By the whole workgroup; no group may exceed 64 keys; uses gcnt (as the list of long groups) and nlong.
     auto sort_groups = [&](int g0, int g1) {
         const int lds0 = (int)gstart[g0];
-        if (t == 0) nlong = 0;
+        if (t == 0) L.nlong = 0;
         __syncthreads();
         for (int gi = g0 + t; gi < g1; gi += THREADS) {
             const int gs = (int)gstart[gi] - lds0;
             const int g = (int)gstart[gi + 1] - (int)gstart[gi];
             if (g > 16) {  // listed for the waves (the counters are no longer needed: the list goes there)
-                gcnt[atomicAdd(&nlong, 1u)] = (u32)gi;
+                gcnt[atomicAdd(&L.nlong, 1u)] = (u32)gi;
             } else if (g > 12) {
                 group_sort_lds<LK, 16>(skey, gs, g);
             } else if (g > 8) {
@@ -903,7 +899,7 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
         // keys of the group that go before it (every lane reads the same address, one read after the
         // other with nothing waiting in between, where an insertion sort by one lane would wait for
         // LDS at every step)
-        const int n_long = (int)nlong;
+        const int n_long = (int)L.nlong;
         if (n_long > 0) {
             for (int li = w; li < n_long; li += NW) {
                 const int gi = (int)gcnt[li];
@@ -921,30 +917,8 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
             __syncthreads();
         }
     };
-
-    if (cnt > CAP && low_bits > 0) {
-        // More keys than the LDS array holds.  If no group is long, the bucket is sorted in parts: runs of
-        // whole groups of at most CAP keys each, every part fetched from the bucket (which is read once per
-        // part, and once more for the groups' sizes) and sorted like a bucket that fits.
-        for (int i = t; i < (int)R; i += THREADS) gcnt[i] = 0;
-        __syncthreads();
-        // fn(key) for every key of the bucket; a thread's loads go out ITEMS at a time, so that a pass over
-        // the bucket waits for memory once per CAP keys and not once per key of the thread
-        auto for_each_key = [&](auto fn) {
-            for (int base = 0; base < cnt; base += CAP) {
-                LK kreg[ITEMS];
-#pragma unroll
-                for (int i = 0; i < ITEMS; ++i) {
-                    const int idx = base + i * THREADS + t;
-                    kreg[i] = idx < cnt ? (LK)kin[idx] : (LK)0;
-                }
-#pragma unroll
-                for (int i = 0; i < ITEMS; ++i)
-                    if (base + i * THREADS + t < cnt) fn(kreg[i]);
-            }
-        };
-        for_each_key([&](LK k) { atomicAdd(&gcnt[digit_of<LK>(k, rest, dmask)], 1u); });
-        __syncthreads();
+    // the groups' first positions from their counters; is any group longer than the lanes and waves sort?  By the whole workgroup.
+    auto scan_groups = [&]() -> bool {
         u32 c[PER], sum = 0, tot;
         int too_long = 0;
 #pragma unroll
@@ -954,7 +928,7 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
             sum += c[j];
             too_long |= c[j] > (u32)BUCKET_GROUP_MAX ? 1 : 0;
         }
-        u32 run = wide_block_exclusive_scan<NW>(sum, smem, tot);
+        u32 run = wide_block_exclusive_scan<NW>(sum, L.smem, tot);
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const u32 d = (u32)(t * PER + j);
@@ -962,164 +936,256 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
             run += c[j];
         }
         if (t == 0) gstart[R] = (u32)cnt;
-        if (!__syncthreads_or(too_long) && rest > 0 && cnt <= 16 * CAP) {
-            for (int g0 = 0; g0 < (int)R;) {
-                // the longest run of whole groups from g0 on with at most CAP keys (a group has at most 64
-                // keys, so at least one fits): gstart ascends, the run's end is found by bisection
-                int g1 = g0 + 1, g_hi = (int)R;
-                const u32 part_end = gstart[g0] + (u32)CAP;
-                while (g1 < g_hi) {
-                    const int mid = (g1 + g_hi + 1) >> 1;
-                    if (gstart[mid] <= part_end) g1 = mid;
-                    else g_hi = mid - 1;
-                }
-                const int part0 = (int)gstart[g0], part_n = (int)gstart[g1] - part0;
-                if (part_n > 0) {
-                    for (int i = g0 + t; i < g1; i += THREADS) gcnt[i] = 0;
-                    __syncthreads();
-                    for_each_key([&](LK k) {
-                        const int d = (int)digit_of<LK>(k, rest, dmask);
-                        if (d >= g0 && d < g1) skey[gstart[d] - (u32)part0 + atomicAdd(&gcnt[d], 1u)] = k;
-                    });
-                    __syncthreads();
-                    sort_groups(g0, g1);
-                    for (int i0 = w * 64; i0 < part_n; i0 += THREADS) {  // (whole waves, for the ballot)
-                        const int i = i0 + lane;
-                        bool first = false;
-                        if (i < part_n) {
-                            const LK k = skey[i];
-                            const K full = upper | (K)k;
-                            kout[part0 + i] = full;
-                            if constexpr (COUNT_UNIQUE) first = full != sentinel && (i == 0 || skey[i - 1] != k);
-                        }
-                        if constexpr (COUNT_UNIQUE) count_firsts(part0 + i0, first, nullptr);
-                    }
-                    __syncthreads();
-                }
-                g0 = g1;
-            }
-            return;
-        }
-    }
-    if (cnt > CAP) {  // ... else pass by pass through global memory
-        bucket_sort_oversize<K, false, THREADS>(kout, kin, nullptr, nullptr, cnt, low_bits, gcnt, smem);
-        if constexpr (COUNT_UNIQUE) {
-            __threadfence();
+        return __syncthreads_or(too_long) != 0;
+    };
+
+    if (cnt > CAP) {
+        // More keys than the LDS array holds.  If no group is long, the bucket is sorted in parts: runs of
+        // whole groups of at most CAP keys each, every part fetched from the bucket (which is read once per
+        // part, and once more for the groups' sizes) and sorted like a bucket that fits.
+        bool done = false;
+        if (rest > 0 && cnt <= 16 * CAP) {
+            for (int i = t; i < (int)R; i += THREADS) gcnt[i] = 0;
             __syncthreads();
-            for (int i0 = w * 64; i0 < cnt; i0 += THREADS) {  // (whole waves, for the ballot)
-                const int i = i0 + lane;
-                bool first = false;
-                if (i < cnt) {
-                    const K k = coherent_load(&kout[i]);
-                    first = k != sentinel && (i == 0 || coherent_load(&kout[i - 1]) != k);
+            // fn(key) for every key of the bucket; a thread's loads go out ITEMS at a time, so that a pass over
+            // the bucket waits for memory once per CAP keys and not once per key of the thread
+            auto for_each_key = [&](auto fn) {
+                for (int base = 0; base < cnt; base += CAP) {
+                    LK kreg[ITEMS];
+#pragma unroll
+                    for (int i = 0; i < ITEMS; ++i) {
+                        const int idx = base + i * THREADS + t;
+                        kreg[i] = idx < cnt ? kin[idx] : (LK)0;
+                    }
+#pragma unroll
+                    for (int i = 0; i < ITEMS; ++i)
+                        if (base + i * THREADS + t < cnt) fn(kreg[i]);
                 }
-                count_firsts(i0, first, nullptr);
+            };
+            for_each_key([&](LK k) { atomicAdd(&gcnt[digit_of<LK>(k, rest, dmask)], 1u); });
+            __syncthreads();
+            if (!scan_groups()) {
+                for (int g0 = 0; g0 < (int)R;) {
+                    // the longest run of whole groups from g0 on with at most CAP keys (a group has at most 64
+                    // keys, so at least one fits): gstart ascends, the run's end is found by bisection
+                    int g1 = g0 + 1, g_hi = (int)R;
+                    const u32 part_end = gstart[g0] + (u32)CAP;
+                    while (g1 < g_hi) {
+                        const int mid = (g1 + g_hi + 1) >> 1;
+                        if (gstart[mid] <= part_end) g1 = mid;
+                        else g_hi = mid - 1;
+                    }
+                    const int part0 = (int)gstart[g0], part_n = (int)gstart[g1] - part0;
+                    if (part_n > 0) {
+                        for (int i = g0 + t; i < g1; i += THREADS) gcnt[i] = 0;
+                        __syncthreads();
+                        for_each_key([&](LK k) {
+                            const int d = (int)digit_of<LK>(k, rest, dmask);
+                            if (d >= g0 && d < g1) skey[gstart[d] - (u32)part0 + atomicAdd(&gcnt[d], 1u)] = k;
+                        });
+                        __syncthreads();
+                        sort_groups(g0, g1);
+                        for (int i = t; i < part_n; i += THREADS) kout[part0 + i] = skey[i];
+                        __syncthreads();
+                    }
+                    g0 = g1;
+                }
+                done = true;
             }
+            __syncthreads();
         }
-        return;
-    }
-    if (low_bits <= 0) {  // nothing below the bucket's digit: all keys equal
-        for (int i = t; i < cnt; i += THREADS) kout[i] = kin[i];
-        if constexpr (COUNT_UNIQUE) {
-            if (w == 0) count_firsts(0, lane == 0 && kin[0] != sentinel, nullptr);
-        }
+        if (!done)  // ... else pass by pass through global memory
+            bucket_sort_oversize<LK, false, THREADS>(kout, kin, nullptr, nullptr, cnt, low_bits, gcnt, L.smem);
+        __threadfence();
+        __syncthreads();
+        emit([&](int i) { return coherent_load(&kout[i]); });
         return;
     }
 
-    for (int i = t; i < (int)R; i += THREADS) gcnt[i] = 0;
-    if constexpr (COUNT_UNIQUE) {
-        if (t < TALLY) tcnt[t] = 0;
-    }
-    const int items = (cnt + THREADS - 1) / THREADS;  // <= ITEMS, the same in every thread
-    LK key[ITEMS];
-    u32 pos[ITEMS];
+    if (cnt > 0) {
+        for (int i = t; i < (int)R; i += THREADS) gcnt[i] = 0;
+        const int items = (cnt + THREADS - 1) / THREADS;  // <= ITEMS, the same in every thread
+        LK key[ITEMS];
+        u32 pos[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        key[i] = (LK)0;
-        pos[i] = 0;
-        if (i < items) {
-            const int idx = i * THREADS + t;
-            if (idx < cnt) key[i] = (LK)kin[idx];
+        for (int i = 0; i < ITEMS; ++i) {
+            key[i] = (LK)0;
+            pos[i] = 0;
+            if (i < items) {
+                const int idx = i * THREADS + t;
+                key[i] = kin[min(idx, cnt - 1)];  // (unconditional: all in flight together)
+            }
         }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-        if (i < items && i * THREADS + t < cnt) pos[i] = atomicAdd(&gcnt[digit_of<LK>(key[i], rest, dmask)], 1u);
-    __syncthreads();
-    u32 c[PER], sum = 0, tot;
-    int too_long = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const u32 d = (u32)(t * PER + j);
-        c[j] = d < R ? gcnt[d] : 0u;
-        sum += c[j];
-        too_long |= c[j] > (u32)BUCKET_GROUP_MAX ? 1 : 0;
-    }
-    u32 run = wide_block_exclusive_scan<NW>(sum, smem, tot);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const u32 d = (u32)(t * PER + j);
-        if (d < R) gstart[d] = run;
-        run += c[j];
-    }
-    if (t == 0) gstart[R] = (u32)cnt;
-    const int any_long = __syncthreads_or(too_long);
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-        if (i < items && i * THREADS + t < cnt) skey[gstart[digit_of<LK>(key[i], rest, dmask)] + pos[i]] = key[i];
-    __syncthreads();
-    if (rest > 0 && !any_long) {
-        sort_groups(0, (int)R);
-    } else if (rest > 0) {
-        // some group is longer still: the whole bucket through a bitonic network, padded to a power of two
-        int P = 64;
-        while (P < cnt) P <<= 1;
-        for (int i = cnt + t; i < P; i += THREADS) skey[i] = (LK) ~(LK)0;
         __syncthreads();
-        for (int size = 2; size <= P; size <<= 1) {
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                for (int q = t; q < P / 2; q += THREADS) {
-                    const int i = 2 * q - (q & (stride - 1)), l = i + stride;
-                    const bool up = (i & size) == 0;
-                    const LK a = skey[i], b = skey[l];
-                    if ((a > b) == up) {
-                        skey[i] = b;
-                        skey[l] = a;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (i < items && i * THREADS + t < cnt) pos[i] = atomicAdd(&gcnt[digit_of<LK>(key[i], rest, dmask)], 1u);
+        __syncthreads();
+        const bool any_long = scan_groups();
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (i < items && i * THREADS + t < cnt) skey[gstart[digit_of<LK>(key[i], rest, dmask)] + pos[i]] = key[i];
+        __syncthreads();
+        if (rest > 0 && !any_long) {
+            sort_groups(0, (int)R);
+        } else if (rest > 0) {
+            // some group is longer still: the whole bucket through a bitonic network, padded to a power of two
+            int P = 64;
+            while (P < cnt) P <<= 1;
+            for (int i = cnt + t; i < P; i += THREADS) skey[i] = (LK) ~(LK)0;
+            __syncthreads();
+            for (int size = 2; size <= P; size <<= 1) {
+                for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                    for (int q = t; q < P / 2; q += THREADS) {
+                        const int i = 2 * q - (q & (stride - 1)), l = i + stride;
+                        const bool up = (i & size) == 0;
+                        const LK a = skey[i], b = skey[l];
+                        if ((a > b) == up) {
+                            skey[i] = b;
+                            skey[l] = a;
+                        }
                     }
+                    __syncthreads();
                 }
-                __syncthreads();
             }
         }
     }
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        if (i < items) {
-            const int idx = i * THREADS + t;
-            bool first = false;
-            if (idx < cnt) {
-                const LK k = skey[idx];
-                const K full = upper | (K)k;
-                kout[idx] = full;
-                if constexpr (COUNT_UNIQUE) first = full != sentinel && (idx == 0 || skey[idx - 1] != k);
-            }
-            if constexpr (COUNT_UNIQUE) count_firsts(i * THREADS + w * 64, first, tcnt);
-        }
-    }
-    if (counting) {
-        // A tile that lies wholly inside this bucket's range gets its count from this workgroup alone (a
-        // plain store); the range's first and last tile may be shared with the neighbouring buckets.
-        __syncthreads();
-        const u32 last_tile = (start + (u32)cnt - 1u) >> tile_shift;
-        if ((u32)t <= last_tile - tile0) {
-            const u32 tile = tile0 + (u32)t;
-            const int v = tcnt[t];
-            const bool inside = (tile << tile_shift) >= start && ((tile + 1u) << tile_shift) <= start + (u32)cnt;
-            if (inside) tilesum[tile] = v;
-            else if (v) atomicAdd(&tilesum[tile], v);
-        }
-    }
+    emit([&](int i) { return skey[i]; });
 }
+
+// What a workgroup makes of its bucket's sorted keys goes by an Out: emit(LDS, bucket, key_at) by the whole workgroup.
+struct Bucket {
+    int number, cnt, low_bits;
+    u32 start;  // position of its first key among all keys
+    // Keys are (row << shift) | item.  Of a key of this bucket: its item; its row; its row where only differences count.
+    template <typename LK>
+    __device__ __forceinline__ u32 item(LK k, int shift) const {
+        return (u32)k & (u32)((1ull << shift) - 1ull);
+    }
+    template <typename LK>
+    __device__ __forceinline__ u32 row_in(LK k, int shift) const {
+        return (u32)(k >> shift);
+    }
+    template <typename LK>
+    __device__ __forceinline__ int row(LK k, int shift) const {
+        if constexpr (sizeof(LK) == 8) return (int)(k >> shift);
+        const int within = low_bits - shift;  // 0 to 31: bits of the row below the bucket's number
+        return (int)(((u32)number << within) | ((u32)(k >> shift) & ((1u << within) - 1u)));
+    }
+    template <typename LK>
+    __device__ __forceinline__ u64 whole(LK k) const {
+        if constexpr (sizeof(LK) == 8) return k;
+        return ((u64)(u32)number << low_bits) | (u64)(low_bits >= 32 ? (u32)k : (u32)k & ((1u << low_bits) - 1u));
+    }
+};
+
+template <typename K, typename LK, int THREADS, int ITEMS, class Out>
+__global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int buckets_first, Out out) {
+    __shared__ BucketLds<LK, THREADS, ITEMS> L;
+    __shared__ typename Out::template Lds<THREADS, ITEMS> O;
+    const bool second = (int)blockIdx.x >= buckets_first;
+    const KeySort<K>& S = second ? second_sort : first_sort;
+    Bucket b;
+    b.number = (int)blockIdx.x - (second ? buckets_first : 0);
+    b.cnt = (int)S.hist[b.number];
+    b.start = S.starts[b.number];
+    b.low_bits = S.key_bits - S.digit_bits;
+    LK* kin = reinterpret_cast<LK*>(S.k1) + b.start;
+    LK* kout = reinterpret_cast<LK*>(S.k0) + b.start;
+    sort_bucket<LK, THREADS, ITEMS>(L, kin, kout, b.cnt, b.low_bits, S.group_bits, [&](auto key_at) {
+        if (threadIdx.x == 0 && b.cnt > 0) S.hist[b.number] = S.cursor[b.number] = 0;  // (every thread has read its count: barriers lie between)
+        out.template emit<THREADS, ITEMS>(second, O, b, kin, kout, key_at);
+    });
+}
+
+// The sorted keys themselves (LK = K: what does not fit LDS is in its place already).
+template <typename K>
+struct PlainKeys {
+    template <int THREADS, int ITEMS>
+    struct Lds {};
+    template <int THREADS, int ITEMS, class L, typename LK, class KeyAt>
+    __device__ __forceinline__ void emit(bool, L&, const Bucket& b, LK*, LK* kout, KeyAt key_at) const {
+        if (b.cnt <= THREADS * ITEMS)
+            for (int i = threadIdx.x; i < b.cnt; i += THREADS) kout[i] = key_at(i);
+    }
+};
+
+// The distinct keys, in order, at the front of the bucket's range of the partitioned array (whose keys have all been read),
+// and how many they are: per bucket and, for whoever wants the number in front of a bucket, per UNIQUE_GROUP buckets (zero beforehand;
+// a cache line each: a line takes an atomic every 11 to 14 ns, and 4,096 of them on the line of 16 such counters took 45 us).
+constexpr int UNIQUE_GROUP = 256, UNIQUE_PAD = 32;
+struct DistinctKeys {
+    u32* per_bucket;
+    u32* per_group;
+    template <int THREADS, int ITEMS>
+    struct Lds {
+        u32 wave[THREADS / 64];
+    };
+    // A wave takes 64 * ITEMS keys in a row, so that one barrier does for the whole bucket.
+    template <int THREADS, int ITEMS, class L, typename LK, class KeyAt>
+    __device__ __forceinline__ void emit(bool, L& lds, const Bucket& b, LK* kin, LK*, KeyAt key_at) const {
+        constexpr int NW = THREADS / 64;
+        const int lane = lane_id(), w = wave_id();
+        u32 total = 0;
+        for (int base = 0; base < b.cnt; base += THREADS * ITEMS) {  // (once where the bucket is in LDS)
+            const int n = min(b.cnt - base, THREADS * ITEMS);
+            const int items = (n + THREADS - 1) / THREADS, i0 = base + w * 64 * items;
+            u32 firsts = 0, cnt = 0;  // bit i: the lane's key i is the first of its kind
+            for (int i = 0; i < items; ++i) {
+                const int idx = i0 + i * 64 + lane, at = min(idx, b.cnt - 1);
+                const bool first = idx < base + n && (idx == 0 || key_at(at) != key_at(max(at - 1, 0)));
+                cnt += (u32)__popcll(ballot(first));
+                firsts |= first ? 1u << i : 0u;
+            }
+            __syncthreads();
+            if (lane == 0) lds.wave[w] = cnt;
+            __syncthreads();
+            u32 run = total;
+#pragma unroll
+            for (int j = 0; j < NW; ++j) {
+                const u32 c = lds.wave[j];
+                if (j < w) run += c;
+                total += c;
+            }
+            for (int i = 0; i < items; ++i) {
+                const bool first = (firsts >> i & 1u) != 0;
+                const u64 bal = ballot(first);
+                if (first) kin[run + mask_below(bal)] = key_at(i0 + i * 64 + lane);
+                run += (u32)__popcll(bal);
+            }
+        }
+        if (threadIdx.x == 0) {
+            per_bucket[b.number] = total;
+            if (total) atomicAdd(&per_group[(b.number / UNIQUE_GROUP) * UNIQUE_PAD], total);
+        }
+    }
+};
+
+// Distinct keys in front of a bucket, by a whole workgroup.  smem: WAVES words.
+__device__ __forceinline__ u32 distinct_in_front(const u32* __restrict__ per_bucket, const u32* __restrict__ per_group, int bucket, u32* smem) {
+    const int group = bucket / UNIQUE_GROUP;
+    u32 part = 0;
+    for (int j = threadIdx.x; j < group; j += BLOCK) part += per_group[j * UNIQUE_PAD];
+    for (int j = group * UNIQUE_GROUP + (int)threadIdx.x; j < bucket; j += BLOCK) part += per_bucket[j];
+    return block_sum(part, smem);
+}
+
+// Two sorts in one launch.
+template <class A, class B>
+struct TwoOuts {
+    A a;
+    B b;
+    template <int THREADS, int ITEMS>
+    union Lds {
+        typename A::template Lds<THREADS, ITEMS> a;
+        typename B::template Lds<THREADS, ITEMS> b;
+    };
+    template <int THREADS, int ITEMS, class L, typename LK, class KeyAt>
+    __device__ __forceinline__ void emit(bool second, L& lds, const Bucket& bk, LK* kin, LK* kout, KeyAt key_at) const {
+        if (second) b.template emit<THREADS, ITEMS>(second, lds.b, bk, kin, kout, key_at);
+        else a.template emit<THREADS, ITEMS>(second, lds.a, bk, kin, kout, key_at);
+    }
+};
 
 // Histogram of the top RBITS-bit digit (bits [shift, shift + RBITS)) over the whole input, added
 // to `hist` (which starts at zero); tiles of BLOCK * ITEMS keys.
@@ -1147,28 +1213,39 @@ __global__ __launch_bounds__(BLOCK) void msd_histogram_kernel(const K* __restric
     }
 }
 
-// A key source gives key i of the input: an array, or a functor that makes the key on the fly (so
-// that keys which are a cheap function of other data need not be written out and read back).  A key that the source
+// A key source gives the keys of item i of the input, PER of them: an array (PER = 1), or a functor that makes the keys on the fly (so
+// that keys which are a cheap function of other data need not be written out and read back): load(i) fetches what they are made of,
+// without conditions, so that all of a lane's loads are in flight together; key(raw, i, c) is the c-th.  A key that the source
 // does not keep is left out (and is not in the histogram): the output is as many keys shorter.
 // Two sorts may share their launches (`second`: of the second one), where their inputs are there at the same time.
 template <typename K>
 struct ArrayKeys {
     const K* p;
-    __device__ __forceinline__ K operator()(long long i) const { return p[i]; }
+    static constexpr int PER = 1;
+    typedef K Raw;
+    __device__ __forceinline__ K load(int i) const { return p[i]; }
+    __device__ __forceinline__ K key(K raw, int, int) const { return raw; }
     __device__ __forceinline__ bool keep(K) const { return true; }
 };
 template <class A>
 struct OneSource {
     A a;
-    __device__ __forceinline__ auto get(bool, long long i) const { return a(i); }
+    static constexpr int PER = A::PER;
+    typedef typename A::Raw Raw;
+    __device__ __forceinline__ Raw load(int i) const { return a.load(i); }
+    __device__ __forceinline__ auto key(bool, const Raw& raw, int i, int c) const { return a.key(raw, i, c); }
     template <typename K>
     __device__ __forceinline__ bool keep(bool, K k) const { return a.keep(k); }
 };
+// (of the same items)
 template <class A, class B>
 struct TwoSources {
     A a;
     B b;
-    __device__ __forceinline__ auto get(bool second, long long i) const { return second ? b(i) : a(i); }
+    static constexpr int PER = A::PER;
+    typedef typename A::Raw Raw;
+    __device__ __forceinline__ Raw load(int i) const { return a.load(i); }
+    __device__ __forceinline__ auto key(bool second, const Raw& raw, int i, int c) const { return second ? b.key(raw, i, c) : a.key(raw, i, c); }
     template <typename K>
     __device__ __forceinline__ bool keep(bool second, K k) const { return second ? b.keep(k) : a.keep(k); }
 };
@@ -1182,9 +1259,9 @@ struct TwoSources {
 // for sorts that then order each range on the whole key; with equal keys indistinguishable the
 // final result does not depend on it.  The lanes of a wave whose keys share a digit (keys led by
 // mesh indices bring few distinct digits into a wave) rank themselves with one LDS atomic.
-template <typename K, int ITEMS, class Src>
-__global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src kin) {
-    constexpr int R = 1 << BUCKET_MSD_BITS;
+template <typename K, typename LK, int ITEMS, class Src>
+__global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src src) {
+    constexpr int R = 1 << BUCKET_MSD_BITS, PER = Src::PER, KEYS = ITEMS * PER;
     static_assert(R == BLOCK, "one digit per thread");
     constexpr int TILE = BLOCK * ITEMS;
     __shared__ u32 h[R];  // per digit: this tile's count, then where the tile's keys of that digit go
@@ -1195,47 +1272,45 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sor
     const int shift = S.key_bits - S.digit_bits;
     const int t = threadIdx.x, w = wave_id(), lane = lane_id();
     // (an array that the kernel after this one adds to: zeroed here, by all workgroups together)
-    for (int i = tile * BLOCK + t; S.tilesum && i < S.tiles; i += tiles * BLOCK) S.tilesum[i] = 0;
+    for (int i = tile * BLOCK + t; i < S.n_zero; i += tiles * BLOCK) S.zero[i] = 0;
     const int n = load_count(S.n_ptr, S.n);
-    const long long base = (long long)tile * TILE;
-    if (base >= n) return;
-    const u64 lt = lanemask_lt();
-    h[t] = 0;
-    K key[ITEMS];
-    u32 rk[ITEMS];
-    bool has[ITEMS];
+    const int base = tile * TILE + w * (64 * ITEMS) + lane;
+    if (tile * TILE >= n) return;
+    typename Src::Raw raw[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const long long idx = base + (long long)w * (64 * ITEMS) + i * 64 + lane;
-        key[i] = idx < n ? kin.get(second, idx) : (K)0;
-        has[i] = idx < n && kin.keep(second, key[i]);
-    }
+    for (int i = 0; i < ITEMS; ++i) raw[i] = src.load(min(base + i * 64, n - 1));
+    h[t] = 0;
     u32 tot;
     const u32 first = block_exclusive_scan(S.hist[t], smem, tot);  // first position of digit t's range
     if (tile == 0) {
         S.starts[t] = first;  // for the kernel that sorts the ranges
         if (S.total && t == 0) *S.total = (int)tot;
     }
+    K key[KEYS];
+    u32 rk[KEYS];
+    bool has[KEYS];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
+    for (int i = 0; i < KEYS; ++i) {
+        const int item = base + i / PER * 64;
+        key[i] = src.key(second, raw[i / PER], item, i % PER);
+        has[i] = item < n && src.keep(second, key[i]);
         const u32 d = digit_of<K>(key[i], shift, R - 1);
         // the lanes that share a digit rank themselves with one returning atomic, by the first of them
-        const u64 same = wave_same_digit_lanes(has[i], d);
+        const SameDigit same = wave_same_digit(has[i], d);
         u32 b = 0;
-        if (has[i] && (same & lt) == 0) b = atomicAdd(&h[d], (u32)__popcll(same));
-        b = (u32)__shfl((int)b, has[i] ? __ffsll((long long)same) - 1 : lane, 64);
-        rk[i] = b + (u32)__popcll(same & lt);
+        if (has[i] && same.below == 0) b = atomicAdd(&h[d], same.count);
+        rk[i] = (u32)__shfl((int)b, same.lead, 64) + same.below;
     }
     __syncthreads();
     const u32 c = h[t];
     if (c) h[t] = first + atomicAdd(&S.cursor[t], c);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
+    for (int i = 0; i < KEYS; ++i) {
         if (has[i]) {
             const u32 pos = h[digit_of<K>(key[i], shift, R - 1)] + rk[i];
-            if (pos < (u32)n) S.k1[pos] = key[i];  // (always, when hist and cursor are as described)
+            if (pos < (u32)n * PER) reinterpret_cast<LK*>(S.k1)[pos] = (LK)key[i];  // (always, when hist and cursor are as described)
         }
     }
 }
@@ -1297,10 +1372,10 @@ __global__ __launch_bounds__(BLOCK) void top_digit_histogram_kernel(const K* __r
         const long long idx = base + (long long)i * BLOCK + t;
         const bool ok = idx < n;
         const u32 d = ok ? digit_of<K>(kin[idx], shift, R - 1) : 0u;
-        const u64 on = __ballot(ok);
+        const u64 on = ballot(ok);
         if (on == 0) continue;
         const u32 d0 = (u32)__builtin_amdgcn_readfirstlane((int)d);  // (of the first lane with a key)
-        if (__ballot(ok && d == d0) == on) {
+        if (ballot(ok && d == d0) == on) {
             if (ok && (on & lanemask_lt()) == 0) atomicAdd(&h[d0], (u32)__popcll(on));
         } else if (ok) {
             atomicAdd(&h[d], 1u);
@@ -1382,6 +1457,11 @@ inline int key_digit_bits(long long n, int key_bits) {
     if (n <= BUCKET_SORT_MAX_KEYS) return BUCKET_MSD_BITS;
     return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS : xl_digit_bits(n, key_bits);
 }
+// buckets of inputs of up to n_cap keys, at most
+inline size_t bucket_capacity(long long n_cap) {
+    const size_t narrow = (size_t)1 << BUCKET_LARGE_MSD_BITS;
+    return n_cap <= BUCKET_SORT_LARGE_MAX_KEYS ? narrow : xl_hist_words(n_cap);
+}
 inline int key_bits_wanted(long long n) {
     if (n <= BUCKET_SORT_MAX_KEYS) return BUCKET_MSD_BITS + 2;
     return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS + 2 : XL_BITS_MAX + 2;
@@ -1413,10 +1493,10 @@ struct DigitTable {
     }
     // one key for every lane with `ok`: the lanes of a wave that share a digit by the first of them
     __device__ __forceinline__ void add(u32* __restrict__ hist, bool ok, u32 d) {
-        const u64 same = wave_same_digit_lanes(ok, d);
-        if (ok && (same & lanemask_lt()) == 0) {
+        const SameDigit same = wave_same_digit(ok, d);
+        if (ok && same.below == 0) {
             const u32 s = slot_of(d);
-            atomicAdd(s != XL_NONE ? &count[s] : &hist[d], (u32)__popcll(same));
+            atomicAdd(s != XL_NONE ? &count[s] : &hist[d], same.count);
         }
     }
     __device__ __forceinline__ void flush(u32* __restrict__ hist) {
@@ -1454,7 +1534,7 @@ __global__ __launch_bounds__(KEY_SCAN_THREADS) void key_starts_kernel(KeySort<K>
     const KeySort<K>& S = second ? second_sort : first_sort;
     const int block = (int)blockIdx.x - (second ? blocks_first : 0), blocks = second ? (int)gridDim.x - blocks_first : blocks_first;
     const int t = threadIdx.x, d0 = block * KEY_SCAN_DIGITS;
-    for (int i = block * KEY_SCAN_THREADS + t; S.tilesum && i < S.tiles; i += blocks * KEY_SCAN_THREADS) S.tilesum[i] = 0;
+    for (int i = block * KEY_SCAN_THREADS + t; i < S.n_zero; i += blocks * KEY_SCAN_THREADS) S.zero[i] = 0;
     const uint4* h4 = reinterpret_cast<const uint4*>(S.hist);
     const uint4 c = h4[d0 / 4 + t];
     u32 before = 0, in_front, tot;
@@ -1476,46 +1556,54 @@ __global__ __launch_bounds__(KEY_SCAN_THREADS) void key_starts_kernel(KeySort<K>
 // by the first of them), which counts their keys and so ranks them; each digit then takes its share of
 // its range with one returning atomic.  A digit that finds no place within XL_PROBES steps (a tile without locality)
 // takes its places right away.  The order of the keys inside a range does not matter (see msd_scatter_kernel).
-// Bound by the chain of a workgroup (keys, ranks, shares, stores), so 8 keys per lane: twice as many workgroups fit a
-// compute unit as with 16, at two thirds of the time (61 M keys 600 -> 350 us, 7 M 50 -> 35); 4 bring no more.
-constexpr int XL_ITEMS = 8;
-template <typename K, class Src>
-__global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src kin) {
-    constexpr int TILE = BLOCK * XL_ITEMS;
+// Bound by the chain of a workgroup (keys, ranks, shares, stores) and by vector issue, so 8 or 9 keys per lane (with 16 half as many
+// workgroups fit a compute unit, at 1.5 times the time), the three keys of a facet from one load of it, and every load of a lane in flight
+// before the first key is made (a branch around each had them wait for one another).  Both sorts of 10.2 M vertices, 123 M keys: 401 -> 224 us;
+// 1.2 M: 44 -> 38; with the narrow digits (msd_scatter_kernel) 115 k: 9.6 -> 7.9, 4 k: 6.0 -> 4.5.
+constexpr int xl_items(int per) { return per == 3 ? 3 : 8; }
+template <typename K, typename LK, class Src>
+__global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src src) {
+    constexpr int PER = Src::PER, ITEMS = xl_items(PER), KEYS = PER * ITEMS, TILE = BLOCK * ITEMS;
+    static_assert(BLOCK * KEYS <= 0xFFFF && XL_SLOTS <= 0x7FFF, "a slot and a rank in one word");
     __shared__ DigitTable T;  // (count: keys of the tile with that digit, then where they go)
     const bool second = (int)blockIdx.x >= tiles_first;
     const KeySort<K>& S = second ? second_sort : first_sort;
     const int n = load_count(S.n_ptr, S.n);
-    const long long base = (long long)((int)blockIdx.x - (second ? tiles_first : 0)) * TILE;
-    if (base >= n) return;
+    const int tile = (int)blockIdx.x - (second ? tiles_first : 0);
+    const int t = threadIdx.x, w = wave_id(), lane = lane_id();
+    const int base = tile * TILE + w * (64 * ITEMS) + lane;
+    if (tile * TILE >= n) return;
+    typename Src::Raw raw[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) raw[i] = src.load(min(base + i * 64, n - 1));
     const int shift = S.key_bits - S.digit_bits;
     const u32 mask = (1u << S.digit_bits) - 1u;
     u32* __restrict__ cursor = S.cursor;
-    const int t = threadIdx.x, w = wave_id(), lane = lane_id();
-    const u64 lt = lanemask_lt();
     T.clear();
-    K key[XL_ITEMS];
-    u32 place[XL_ITEMS], rank[XL_ITEMS];
-    bool has[XL_ITEMS];
-#pragma unroll
-    for (int i = 0; i < XL_ITEMS; ++i) {
-        const long long idx = base + (long long)w * (64 * XL_ITEMS) + i * 64 + lane;
-        key[i] = idx < n ? kin.get(second, idx) : (K)0;
-        has[i] = idx < n && kin.keep(second, key[i]);
-    }
+    K key[KEYS];
+    u32 at[KEYS];  // slot and rank within the tile's keys of the digit, or its place (then slot XL_NONE)
+    bool has[KEYS], alone[KEYS];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < XL_ITEMS; ++i) {
+    for (int i = 0; i < KEYS; ++i) {
+        const int item = base + i / PER * 64;
+        key[i] = src.key(second, raw[i / PER], item, i % PER);
+        has[i] = item < n && src.keep(second, key[i]);
         const u32 d = digit_of<K>(key[i], shift, mask);
-        const u64 same = wave_same_digit_lanes(has[i], d);
-        u32 slot = XL_NONE, b = 0;
-        if (has[i] && (same & lt) == 0) {
-            slot = T.slot_of(d);
-            b = slot != XL_NONE ? atomicAdd(&T.count[slot], (u32)__popcll(same)) : atomicAdd(&cursor[d], (u32)__popcll(same));
+        const SameDigit same = wave_same_digit(has[i], d);
+        u32 b = 0, place = 0;
+        if (has[i] && same.below == 0) {
+            const u32 slot = T.slot_of(d);
+            if (slot != XL_NONE) b = (slot << 16) | atomicAdd(&T.count[slot], same.count);
+            else {
+                b = XL_NONE;
+                place = atomicAdd(&cursor[d], same.count);
+            }
         }
-        const int lead = has[i] ? __ffsll((long long)same) - 1 : lane;
-        place[i] = (u32)__shfl((int)slot, lead, 64);
-        rank[i] = (u32)__shfl((int)b, lead, 64) + (u32)__popcll(same & lt);
+        b = (u32)__shfl((int)b, same.lead, 64);
+        alone[i] = b == XL_NONE;
+        if (__any(alone[i])) place = (u32)__shfl((int)place, same.lead, 64);
+        at[i] = (alone[i] ? place : b) + same.below;
     }
     __syncthreads();
     u32 share[XL_SLOTS / BLOCK];  // (all of a thread's atomics in flight together)
@@ -1528,54 +1616,51 @@ __global__ __launch_bounds__(BLOCK) void xl_scatter_kernel(KeySort<K> first_sort
     for (int j = 0; j < XL_SLOTS / BLOCK; ++j) T.count[j * BLOCK + t] = share[j];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < XL_ITEMS; ++i) {
+    for (int i = 0; i < KEYS; ++i) {
         if (has[i]) {
-            const u32 pos = (place[i] != XL_NONE ? T.count[place[i]] : 0u) + rank[i];
-            if (pos < (u32)n) S.k1[pos] = key[i];  // (always, when hist and cursor are as described)
+            const u32 pos = alone[i] ? at[i] : T.count[at[i] >> 16] + (at[i] & 0xFFFFu);
+            if (pos < (u32)n * PER) reinterpret_cast<LK*>(S.k1)[pos] = (LK)key[i];  // (always, when hist and cursor are as described)
         }
     }
 }
 
-// Sorts the keys of `src` (whose digits are in a.hist); with b, a second sort of the same kind in the same launches.
-// false on a launch error.  `lt`: brackets the launch of the per-bucket kernel.
-template <typename K, class Src>
-inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_null, const Src& src, LaunchTimer* lt = nullptr,
-                     int tag = 0) {
+// Sorts the keys of `src` (whose digits are in a.hist) for `out`; with b, a second sort of the same kind in the same launches
+// (both with 32-bit keys behind the partition, or neither).  false on a launch error.  `lt`: brackets the launch of the partition
+// (part_tag >= 0) and of the per-bucket kernel.
+template <typename K, class Src, class Out>
+inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_null, const Src& src, const Out& out,
+                     LaunchTimer* lt = nullptr, int tag = 0, int part_tag = -1) {
     const KeySort<K> none{};
     const KeySort<K>& b = b_or_null ? *b_or_null : none;
-    const int buckets_a = 1 << a.digit_bits, buckets_b = b_or_null ? 1 << b.digit_bits : 0;
+    const int digits_a = 1 << a.digit_bits, digits_b = b_or_null ? 1 << b.digit_bits : 0;
+    const int buckets_a = a.buckets ? a.buckets : digits_a, buckets_b = b.buckets ? b.buckets : digits_b;
+    constexpr int NARROW_ITEMS = Src::PER == 3 ? 1 : SORT_ITEMS_SMALL;
     const bool narrow = a.digit_bits == BUCKET_MSD_BITS;
-    if (narrow) {
-        const int tiles_a = sort_tiles(a.n, SORT_ITEMS_SMALL), tiles_b = b_or_null ? sort_tiles(b.n, SORT_ITEMS_SMALL) : 0;
-        msd_scatter_kernel<K, SORT_ITEMS_SMALL, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
-    } else {
-        const int blocks_a = buckets_a / KEY_SCAN_DIGITS, blocks_b = buckets_b / KEY_SCAN_DIGITS;
-        key_starts_kernel<K><<<blocks_a + blocks_b, KEY_SCAN_THREADS, 0, s>>>(a, b, blocks_a);
-        const int tiles_a = sort_tiles(a.n, XL_ITEMS), tiles_b = b_or_null ? sort_tiles(b.n, XL_ITEMS) : 0;
-        xl_scatter_kernel<K, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
-    }
-    // one workgroup per bucket, with the narrowest in-LDS key type that holds the bits below the digit
-    const bool timed = lt && lt->begin(s, tag);
-    const bool half = sizeof(K) == 8 && a.key_bits - a.digit_bits <= 32 && b.key_bits - b.digit_bits <= 32;
-    const bool counting = a.tilesum || b.tilesum;
-    auto launch = [&](auto lk, auto threads, auto items) {
+    auto launch = [&](auto lk) {
         using LK = decltype(lk);
-        constexpr int T = decltype(threads)::value, I = decltype(items)::value;
-        if (counting) bucket_keys_kernel<K, LK, T, I, true><<<buckets_a + buckets_b, T, 0, s>>>(a, b, buckets_a);
-        else bucket_keys_kernel<K, LK, T, I, false><<<buckets_a + buckets_b, T, 0, s>>>(a, b, buckets_a);
+        bool timed = lt && part_tag >= 0 && lt->begin(s, part_tag);
+        if (narrow) {
+            const int tiles_a = sort_tiles(a.n, NARROW_ITEMS), tiles_b = b_or_null ? sort_tiles(b.n, NARROW_ITEMS) : 0;
+            msd_scatter_kernel<K, LK, NARROW_ITEMS, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
+        } else {
+            const int blocks_a = digits_a / KEY_SCAN_DIGITS, blocks_b = digits_b / KEY_SCAN_DIGITS;
+            key_starts_kernel<K><<<blocks_a + blocks_b, KEY_SCAN_THREADS, 0, s>>>(a, b, blocks_a);
+            const int tiles_a = sort_tiles(a.n, xl_items(Src::PER)), tiles_b = b_or_null ? sort_tiles(b.n, xl_items(Src::PER)) : 0;
+            xl_scatter_kernel<K, LK, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
+        }
+        if (timed) lt->end(s);
+        timed = lt && lt->begin(s, tag);
+        if (narrow)
+            bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS_256, BUCKET_KEYS_ITEMS_256, Out>
+                <<<buckets_a + buckets_b, BUCKET_KEYS_THREADS_256, 0, s>>>(a, b, buckets_a, out);
+        else
+            bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096, Out>
+                <<<buckets_a + buckets_b, BUCKET_KEYS_THREADS_4096, 0, s>>>(a, b, buckets_a, out);
+        if (timed) lt->end(s);
     };
-    const std::integral_constant<int, BUCKET_KEYS_THREADS_256> t256{};
-    const std::integral_constant<int, BUCKET_KEYS_ITEMS_256> i256{};
-    const std::integral_constant<int, BUCKET_KEYS_THREADS_4096> t4096{};
-    const std::integral_constant<int, BUCKET_KEYS_ITEMS_4096> i4096{};
-    if (narrow) {
-        if (half) launch(u32{}, t256, i256);
-        else launch(K{}, t256, i256);
-    } else {
-        if (half) launch(u32{}, t4096, i4096);
-        else launch(K{}, t4096, i4096);
-    }
-    if (timed) lt->end(s);
+    if constexpr (std::is_same<Out, PlainKeys<K>>::value) launch(K{});
+    else if (a.half) launch(u32{});
+    else launch(K{});
     return hipGetLastError() == hipSuccess;
 }
 
@@ -1592,7 +1677,7 @@ inline bool key_sort_array(hipStream_t s, const KeySort<K>& a) {
     } else {
         xl_count_kernel<K><<<sort_tiles(a.n, 4), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, low, (u32)buckets - 1u, a.hist);
     }
-    return key_sort(s, a, (const KeySort<K>*)nullptr, OneSource<ArrayKeys<K>>{{a.k0}});
+    return key_sort(s, a, (const KeySort<K>*)nullptr, OneSource<ArrayKeys<K>>{{a.k0}}, PlainKeys<K>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -1647,7 +1732,7 @@ __global__ __launch_bounds__(BLOCK) void tile_count_kernel(Pred pred, const int*
     for (int c = 0; c < CHUNKS; ++c) {
         const long long i = base + (long long)w * (64 * CHUNKS) + c * 64 + lane;
         const bool f = (i < n) && pred((int)i);
-        cnt += (u32)__popcll(__ballot(f));
+        cnt += (u32)__popcll(ballot(f));
     }
     if (lane == 0) smem[w] = cnt;
     __syncthreads();
@@ -1727,7 +1812,7 @@ __global__ __launch_bounds__(BLOCK) void tile_scatter_kernel(Pred pred, Out out,
     for (int c = 0; c < CHUNKS; ++c) {
         const long long i = base + (long long)w * (64 * CHUNKS) + c * 64 + lane;
         const bool f = (i < n) && pred((int)i);
-        bal[c] = __ballot(f);
+        bal[c] = ballot(f);
         cnt += (u32)__popcll(bal[c]);
     }
     __syncthreads();

@@ -168,6 +168,38 @@ def test_edges_and_costs_bit_exact(ctx, oracle, name, mesh):
     assert np.array_equal(cost.view(np.uint32), cr.view(np.uint32))
 
 
+@pytest.mark.parametrize("n,f", [(3, 1), (5, 30_000), (129, 70_000), (257, 9_000), (3_000, 400_000)])
+def test_quadrics_and_edges_of_facet_soups(ctx, oracle, n, f):
+    """Vertices with more facets than a bucket of the sort holds in LDS, with less bits than the sort's digit; unused vertices."""
+    rng = np.random.default_rng(n + f)
+    V = rng.standard_normal((n, 3)).astype(np.float32)
+    F = rng.integers(0, n, size=(f, 3)).astype(np.int32)
+    F[F == n // 2] = 0  # ... which is in no facet then
+    print(f"soup N={n} F={f}", flush=True)
+    Q = ctx.picasso_vertex_quadrics(dev(V), dev(F)).cpu().numpy()
+    ref = oracle.vertex_quadrics(V, F)
+    assert np.array_equal(Q.view(np.uint32), ref.view(np.uint32))
+    E, cost = ctx.picasso_edge_costs(dev(V), dev(F))
+    Er = oracle.edges(F)
+    assert np.array_equal(E.cpu().numpy(), Er)
+    cr, _ = oracle.edge_costs(V, ref, Er)
+    assert np.array_equal(cost.cpu().numpy().view(np.uint32), cr.view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 1, 1_250_000])
+def test_few_facets_among_very_many_vertices(ctx, oracle, n):
+    """Beyond 2^20 vertices the bits of an edge key below an 8-bit digit do not fit 32 bits."""
+    Vg, Fg = meshgen.noisy_grid(50, 40, seed=9)
+    at = np.sort(np.random.default_rng(n).choice(n, size=Vg.shape[0], replace=False))
+    at[-1] = n - 1
+    V = np.zeros((n, 3), np.float32)
+    V[at] = Vg
+    F = at[Fg].astype(np.int32)
+    print(f"sparse N={n}", flush=True)
+    st, vo, fo, cid = ctx.picasso_decimate(dev(V), dev(F), n - 1200)
+    assert_same_result(st, vo, fo, cid, oracle.decimate(V, F, n - 1200))
+
+
 # ----------------------------------------------------------------------------
 # whole path
 # ----------------------------------------------------------------------------

@@ -161,6 +161,21 @@ def test_features_at_addresses_that_are_not_16_byte_aligned(pk, ctx, oracle):
     assert np.all(np.abs(ya.astype(np.float64) - ref) <= _sum_bound(np.abs(x), cid, n_out, sizes) + U * np.abs(ref))
 
 
+@pytest.mark.parametrize("n_in,n_out,every", [
+    (70_000, 1, 1), (70_000, 3, 1), (70_000, 129, 1), (70_000, 257, 3),                  # 256 digits: rows of one digit and of many,
+    (1_200_000, 1, 1), (1_200_000, 16, 1), (1_200_000, 4097, 5), (1_200_000, 1_000_000, 7),  # 4,096 digits, rows without members,
+    (7_400_000, 40, 3), (7_400_000, 600_000, 1),                                         # ... beyond what a list of one sort takes
+])
+def test_lists_of_rows_of_any_length(ctx, n_in, n_out, every):
+    """Offsets and members where a digit of the sort holds many rows, one, or a part of one; rows without members in between."""
+    rng = np.random.default_rng(n_in + n_out)
+    row = (rng.integers(0, (n_out + every - 1) // every, size=n_in) * every).astype(np.int32)
+    print(f"lists n_in={n_in} n_out={n_out}", flush=True)
+    off, mem = ctx.picasso_cluster_csr(dev(row), n_out)
+    assert np.array_equal(off.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n_out))]))
+    assert np.array_equal(mem.cpu().numpy(), np.argsort(row, kind="stable"))
+
+
 @pytest.mark.parametrize("n_out,C", [((1 << 24) + 40, 4), ((1 << 24) + 40, 3), ((1 << 22) + 9, 256)])
 def test_unpooling_from_clusters_beyond_24_bit_numbers_and_4_gib(pk, ctx, n_out, C):
     """Few vertices whose clusters lie at the end of a long feature array (the array's length is not an argument)."""
