@@ -875,34 +875,6 @@ __global__ __launch_bounds__(BLOCK) void unique_cost_kernel(EdgeList E, u64* __r
     bids.flush(vmin0, nullptr);
 }
 
-// Bids of the lanes of one wave on their vertices x, where lanes with equal x are neighbours among
-// the lanes that bid (edges are sorted by their lower vertex, so that end of consecutive edges is
-// often the same vertex).  Atomics of one wave on one address are served one after the other, so
-// each such group first takes the minimum of its priorities across lanes and its last lane issues
-// the group's single atomicMin.  Every lane of the wave must call this.
-__device__ __forceinline__ void bid_grouped(u64* __restrict__ vmin, bool on, int x, u64 p) {
-    const int lane = prim::lane_id();
-    const u64 ab = prim::ballot(on);
-    if (ab == 0) return;
-    const u64 lt = prim::lanemask_lt();
-    const u64 below = ab & lt;
-    const int prev = below ? 63 - __clzll((long long)below) : lane;
-    const int xprev = __shfl(x, prev, 64);
-    const bool head = on && (below == 0 || xprev != x);
-    const u64 hb = prim::ballot(head);
-    const u64 hle = hb & (lt | (1ull << lane));
-    const int dist = hle ? lane - (63 - __clzll((long long)hle)) : 0;  // lanes back to the group's head
-    u64 q = on ? p : ~0ull;
-    for (int d = 1; d < 64; d <<= 1) {
-        if (!__any(dist >= d)) break;
-        const u64 o = __shfl_up(q, d, 64);
-        if (dist >= d) q = (o < q) ? o : q;
-    }
-    const u64 above = ab & ~(lt | (1ull << lane));
-    const bool tail = on && (above == 0 || ((hb >> (__ffsll((long long)above) - 1)) & 1ull));
-    if (tail) atomicMin(&vmin[x], q);
-}
-
 // ---------------------------------------------------------------------------
 // S3: greedy disjoint grouping of Alg. 2 lines 3-10, computed in parallel.
 //
@@ -955,7 +927,12 @@ struct SelArgs {
     LiveEdge* live;         // the edges that the last grid-wide sub-round leaves live, for the tail: LIVE_SEGS segments of
     int live_cap;           // ... live_cap places each,
     int* live_n;            // ... filled up to live_n[segment * MATCH_PAD] (or fuller than full)
-    unsigned char* estate;  // per edge: 0 = live, 1 = retired (paired, or an end was paired)
+    unsigned char* estate;  // per edge: 0 = live, 1 = retired (paired, or an end was paired); in listed rounds only before sub-round 0
+    int bound;              // edges of this round at most (no less than 1)
+    u64* lkey;              // listed rounds: the live edges (key, cost key, number), see select_listed_kernel
+    u32* lcost;
+    int* lidx;
+    int* lcount;
     State* st;
     MeshTab mt;
     int vbits;
@@ -967,45 +944,71 @@ struct SelArgs {
     int cur;           // which of the ping-pong vertex / facet counts belong to this round
 };
 
+// N edges of one lane in one sub-round.  on: the edge is live (its ends' bids are then those of live edges); what the others hold is not looked
+// at.  alive: it stays live, sel: it is accepted (both ends noted).  The best live edge at an end is accepted in this sub-round iff it
+// is also the best at its other end.  Without branches: all lanes' loads of a step are in flight together.
 template <bool SHUFFLE>
-__device__ __forceinline__ bool vertex_pairs_now(const u64* __restrict__ cur, const u64* __restrict__ ekey, int vbits,
-                                                 const TieBreak& tb, int x, u64 mx) {
-    // The best live edge at x is accepted in this sub-round iff it is also the best at its other end.
-    if (mx == VMIN_NONE) return false;  // no bid on x (cannot happen for an end of a live edge)
+struct JudgedEdge {
+    u64 key;
+    u32 cost;
+    int e, u, v;
+    bool on, alive, sel;
+    u64 pu, pv;  // its bids on its ends
+};
+template <bool SHUFFLE, int N>
+__device__ __forceinline__ void judge_edges(const SelArgs& A, const u64* __restrict__ cur, JudgedEdge<SHUFFLE> (&E)[N]) {
+    const u64 vmask = (1ull << A.vbits) - 1ull;
+    u64 mu[N], mv[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        E[j].u = E[j].on ? (int)(E[j].key >> A.vbits) : 0;
+        E[j].v = E[j].on ? (int)(E[j].key & vmask) : 0;
+        mu[j] = cur[E[j].u];
+        mv[j] = cur[E[j].v];
+    }
+    int au[N], av[N];  // the ends' best edges' other ends
     if constexpr (SHUFFLE) {
-        const u64 k = ekey[tb.dec((u32)mx)];
-        const int a = (int)(k >> vbits), b = (int)(k & ((1ull << vbits) - 1ull));
-        return cur[a == x ? b : a] == mx;
+        u64 ku[N], kv[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            ku[j] = A.ekey[E[j].on && mu[j] != VMIN_NONE ? A.tb.dec((u32)mu[j]) : 0u];
+            kv[j] = A.ekey[E[j].on && mv[j] != VMIN_NONE ? A.tb.dec((u32)mv[j]) : 0u];
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int a = (int)(ku[j] >> A.vbits), b = (int)(kv[j] >> A.vbits);
+            au[j] = E[j].on ? (a == E[j].u ? (int)(ku[j] & vmask) : a) : 0;
+            av[j] = E[j].on ? (b == E[j].v ? (int)(kv[j] & vmask) : b) : 0;
+        }
     } else {
-        return cur[(u32)mx] == ((mx & 0xFFFFFFFF00000000ull) | (u32)x);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            au[j] = E[j].on && mu[j] != VMIN_NONE ? (int)(u32)mu[j] : 0;
+            av[j] = E[j].on && mv[j] != VMIN_NONE ? (int)(u32)mv[j] : 0;
+        }
     }
-}
-
-// One edge of one sub-round.  Returns true if the edge stays live; pu, pv = its bids on its ends.
-template <bool SHUFFLE>
-__device__ __forceinline__ bool subround_edge(const SelArgs& A, const u64* __restrict__ cur, int k, int e, int& u,
-                                              int& v, int& m, u64& pu, u64& pv, bool& sel) {
-    const u64 key = A.ekey[e];
-    const u32 ck = A.ecost[e];
-    u = (int)(key >> A.vbits);
-    v = (int)(key & ((1ull << A.vbits) - 1ull));
-    pu = edge_bid<SHUFFLE>(A.tb, ck, e, v);
-    pv = edge_bid<SHUFFLE>(A.tb, ck, e, u);
-    m = mesh_of(A.mt.voff, A.mt.B, u);
-    sel = false;
-    if (k == 0 && !A.mt.active[m]) return false;
-    const u64 mu = cur[u], mv = cur[v];
-    if (mu == pu && mv == pv) {
-        sel = true;
-        A.mate[u] = v;
-        A.mate[v] = u;
-        A.pcost[u] = ck;
-        if constexpr (SHUFFLE) A.ptie[u] = (u32)pu;
-        return false;
+    u64 bu[N], bv[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        bu[j] = cur[au[j]];
+        bv[j] = cur[av[j]];
     }
-    const bool gone_u = vertex_pairs_now<SHUFFLE>(cur, A.ekey, A.vbits, A.tb, u, mu);
-    const bool gone_v = vertex_pairs_now<SHUFFLE>(cur, A.ekey, A.vbits, A.tb, v, mv);
-    return !(gone_u || gone_v);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        JudgedEdge<SHUFFLE>& x = E[j];
+        x.pu = edge_bid<SHUFFLE>(A.tb, x.cost, x.e, x.v);
+        x.pv = edge_bid<SHUFFLE>(A.tb, x.cost, x.e, x.u);
+        x.sel = x.on && mu[j] == x.pu && mv[j] == x.pv;
+        const bool gone_u = SHUFFLE ? bu[j] == mu[j] : bu[j] == ((mu[j] & 0xFFFFFFFF00000000ull) | (u32)x.u);
+        const bool gone_v = SHUFFLE ? bv[j] == mv[j] : bv[j] == ((mv[j] & 0xFFFFFFFF00000000ull) | (u32)x.v);
+        x.alive = x.on && !x.sel && !gone_u && !gone_v;
+        if (x.sel) {
+            A.mate[x.u] = x.v;
+            A.mate[x.v] = x.u;
+            A.pcost[x.u] = x.cost;
+            if constexpr (SHUFFLE) A.ptie[x.u] = (u32)x.pu;
+        }
+    }
 }
 
 // pairs formed, counted per mesh: one atomic per wave and mesh
@@ -1033,7 +1036,9 @@ struct PairTally {
         mesh = A.mt.B <= 1 || e >= n ? 0 : mesh_of(A.mt.voff, A.mt.B, (int)(A.ekey[e] >> A.vbits));
         pairs = 0;
     }
-    __device__ __forceinline__ void count(const SelArgs& A, bool sel, int m) {
+    // by all lanes of a wave; u = an end of the pair
+    __device__ __forceinline__ void count(const SelArgs& A, bool sel, int u) {
+        const int m = A.mt.B > 1 && sel ? mesh_of(A.mt.voff, A.mt.B, u) : 0;
         const u64 mine = prim::ballot(sel && m == mesh);
         if (mine && prim::lane_id() == 0) atomicAdd(&pairs, (int)__popcll(mine));
         if (A.mt.B > 1) count_pairs(A, sel && m != mesh, m);
@@ -1058,133 +1063,241 @@ __device__ __forceinline__ void count_pairs_lds(int* pairs, bool sel, int m) {
 }
 
 // The lanes' live edges appended to their workgroup's segment of the tail's list.  By all lanes of a wave.
-__device__ __forceinline__ void append_live(const SelArgs& A, bool alive, int e) {
+__device__ __forceinline__ void append_live(const SelArgs& A, bool alive, u64 key, u32 cost, int e) {
     const u64 b = prim::ballot(alive);
     if (b == 0) return;
     const int seg = blockIdx.x & (LIVE_SEGS - 1), first = __ffsll((long long)b) - 1;
     int at = 0;
     if (prim::lane_id() == first) at = atomicAdd(&A.live_n[seg * MATCH_PAD], (int)__popcll(b));
     at = __shfl(at, first, 64) + (int)__popcll(b & prim::lanemask_lt());
-    if (alive && at < A.live_cap) A.live[(size_t)seg * A.live_cap + at] = LiveEdge{A.ekey[e], A.ecost[e], e};
+    if (alive && at < A.live_cap) A.live[(size_t)seg * A.live_cap + at] = LiveEdge{key, cost, e};
 }
 
-// Grid-wide sub-round over ALL edges of the round; retired edges are skipped by
-// their state byte.  No worklist is kept from one to the next (it would be appended to by every wave); the
-// last one before the tail (APPEND), which leaves a few thousand edges live, lists them for it.
+// Grid-wide sub-round over ALL edges of a round of less than LISTED_MIN_EDGES; retired edges are skipped by
+// their state byte.  The last one before the tail (APPEND), which leaves a few thousand edges live, lists them for it.
+// Bound by the launch and the chain of loads (count, key, cost and state; the ends' bids; their best edges' other ends' bids): each is
+// asked for without waiting for the one in front of it where it can be (115 k: the eight of them 54 -> 45 us).
 constexpr int SUBROUND_LINES = 128;
 template <bool SHUFFLE, bool APPEND>
 __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k) {
     const u64* __restrict__ cur = A.vmin[k % 3];
     u64* __restrict__ nxt = A.vmin[(k + 1) % 3];
     u64* __restrict__ rst = A.vmin[(k + 2) % 3];
-    const int n = A.st->ne;
-    if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = k + 1;
     __shared__ BidTable<SUBROUND_LINES> bids;
     __shared__ PairTally tally;
+    const int i = (int)blockIdx.x * BLOCK + (int)threadIdx.x, at = min(i, A.bound - 1);  // (the grid covers the bound)
+    const u64 key = A.ekey[at];  // (not yet known to be an edge: the loads do not wait for one another)
+    const u32 cost = A.ecost[at];
+    const bool retired = A.estate[at] != 0;
+    const int n = A.st->ne;
+    if (i == 0) A.st->sel_k = k + 1;
+    if ((int)blockIdx.x * BLOCK >= n) return;
+    bids.clear();
     if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * BLOCK, n);
-    for (long long base = (long long)blockIdx.x * BLOCK; base < n; base += (long long)gridDim.x * BLOCK) {
-        const long long i = base + threadIdx.x;
-        bids.clear();
-        __syncthreads();
-        bool sel = false, alive = false;
-        int u = 0, v = 0, m = 0;
-        u64 pu = 0, pv = 0;
-        const bool live_in = (i < n) && A.estate[i] == 0;
-        if (live_in) alive = subround_edge<SHUFFLE>(A, cur, k, (int)i, u, v, m, pu, pv, sel);
-        tally.count(A, sel, m);
-        if (alive) {
-            bids.put(nxt, rst, u, pu);
-            bids.put(nxt, rst, v, pv);
-        } else if (live_in) {
-            A.estate[i] = 1;
-        }
-        if (APPEND) append_live(A, alive, (int)i);
-        __syncthreads();
-        bids.flush(nxt, rst);
-        __syncthreads();
+    JudgedEdge<SHUFFLE> E[1];
+    E[0].key = key;
+    E[0].cost = cost;
+    E[0].e = i;
+    E[0].on = i < n && !retired;
+    judge_edges<SHUFFLE, 1>(A, cur, E);
+    const JudgedEdge<SHUFFLE>& x = E[0];
+    __syncthreads();
+    tally.count(A, x.sel, x.u);
+    if (x.alive) {
+        bids.put(nxt, rst, x.u, x.pu);
+        bids.put(nxt, rst, x.v, x.pv);
+    } else if (x.on) {
+        A.estate[i] = 1;
     }
+    if (APPEND) append_live(A, x.alive, key, cost, i);
+    __syncthreads();
+    bids.flush(nxt, rst);
     if (threadIdx.x == 0) tally.end(A);
 }
 
-// The same sub-round for large rounds once most edges are retired (every sub-round but the
-// first).  One lane per edge would then spend a wave, and a trip to memory, on every 64 state
-// bytes; here a lane reads the state of 16 consecutive edges at once, the wave lists its live
-// edges in LDS in ascending order (1024 edges per wave), and the lanes then work through that
-// list 64 edges at a time exactly as above.
-constexpr int SPARSE_MIN_EDGES = 1 << 20;  // below this the one-lane-per-edge kernel is at its launch floor anyway
+// Large rounds: every sub-round lists the edges it leaves live (key, cost key, number) for the next, so that each reads
+// 16 bytes per live edge in a row, where a walk over all edges' states fetched the keys and costs of a few per cent of them
+// line by line.  A workgroup has a part of the edges to itself, its part of the lists is the same places of lkey, lcost and lidx, and
+// it leaves their number in lcount: no counter is shared.  Sub-round 0 takes all edges, LISTED_TILE to a workgroup; a
+// later one takes the `group` parts of 2^span_shift edges in front of it together and joins what is left of them (in place: a live
+// edge's new place is never behind its old one).  Bound by memory and by the bids' atomics; sub-round 0 has four edges per lane in
+// flight, the others two.  10.2 M vertices, 31 M edges: the first round's seven sub-rounds 967 -> 740 us, all three rounds' 1,800 -> 1,380;
+// 1.2 M: 117 -> 95 and 253 -> 205.  Bids put together in LDS in the first three sub-rounds, while several live edges share a line of vertices
+// (the third: 126 -> 122 us, 1.2 M 16.1 -> 13.9; the fourth no faster).
+constexpr int LISTED_MIN_EDGES = 1 << 20;  // below this the sub-rounds are at their launch floor anyway
+constexpr int LISTED_TILE_SHIFT = 10, LISTED_TILE = 1 << LISTED_TILE_SHIFT, LISTED_PER_LANE = LISTED_TILE / BLOCK;
+constexpr int LISTED_GROUP_MAX = 4;
+constexpr int LISTED_LINES = 256;
+// Parts that sub-round k >= 1 joins, and their size (bits): a workgroup has a few hundred live edges every time.
+constexpr int LISTED_SPAN_MAX = 16;
+inline int listed_group_shift(int k) { return k <= 3 ? 1 : 2; }
+inline int listed_span(int k) {
+    int span = LISTED_TILE_SHIFT;
+    for (int j = 1; j < k && span < LISTED_SPAN_MAX; ++j) span += listed_group_shift(j);
+    return span;
+}
+inline int listed_group(int k) { return listed_span(k) >= LISTED_SPAN_MAX ? 1 : 1 << listed_group_shift(k); }
 
-template <int SPARSE_EDGES_PER_LANE, bool SHUFFLE, bool APPEND>  // 4 while about a third of the edges are live, 16 later
-__global__ __launch_bounds__(BLOCK) void select_subround_sparse_kernel(SelArgs A, int k) {
-    static_assert(SPARSE_EDGES_PER_LANE == 4 || SPARSE_EDGES_PER_LANE == 16, "one 4- or 16-byte load per lane");
-    constexpr int PER_WAVE = 64 * SPARSE_EDGES_PER_LANE;
-    __shared__ int slist[prim::WAVES][PER_WAVE];
+// Places of the lanes' live edges among the workgroup's (N per lane, wave by wave); total = their number.  Contains barriers.
+template <int N>
+__device__ __forceinline__ void live_places(const bool (&alive)[N], u32* smem, int (&place)[N], int& total) {
+    const int w = prim::wave_id();
+    u32 run = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const u64 b = prim::ballot(alive[j]);
+        place[j] = (int)(run + prim::mask_below(b));
+        run += (u32)__popcll(b);
+    }
+    __syncthreads();
+    if (prim::lane_id() == 0) smem[w] = run;
+    __syncthreads();
+    u32 before = 0, all = 0;
+#pragma unroll
+    for (int j = 0; j < prim::WAVES; ++j) {
+        const u32 c = smem[j];
+        if (j < w) before += c;
+        all += c;
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) place[j] += (int)before;
+    total = (int)all;
+}
+
+template <bool SHUFFLE, bool APPEND>
+__global__ __launch_bounds__(BLOCK) void select_first_kernel(SelArgs A) {
+    constexpr int N = LISTED_PER_LANE;
+    const u64* __restrict__ cur = A.vmin[0];
+    u64* __restrict__ nxt = A.vmin[1];
+    u64* __restrict__ rst = A.vmin[2];
+    __shared__ BidTable<LISTED_LINES> bids;
     __shared__ PairTally tally;
+    __shared__ u32 smem[prim::WAVES];
+    const int n = A.st->ne;
+    if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = 1;
+    const int tile = prim::xcd_tile(n, LISTED_TILE);
+    const long long base = (long long)tile << LISTED_TILE_SHIFT;
+    if (base >= n) return;
+    const int i0 = (int)base + prim::wave_id() * (64 * N) + prim::lane_id();
+    JudgedEdge<SHUFFLE> E[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int i = i0 + j * 64, at = min(i, n - 1);
+        E[j].e = i;
+        E[j].key = A.ekey[at];
+        E[j].cost = A.ecost[at];
+        E[j].on = A.estate[at] == 0;
+        E[j].on = E[j].on && i < n;
+    }
+    bids.clear();
+    if (threadIdx.x == 0) tally.begin(A, base, n);
+    judge_edges<SHUFFLE, N>(A, cur, E);
+    bool alive[N];
+    int place[N], total;
+#pragma unroll
+    for (int j = 0; j < N; ++j) alive[j] = E[j].alive;
+    live_places<N>(alive, smem, place, total);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const JudgedEdge<SHUFFLE>& x = E[j];
+        tally.count(A, x.sel, x.u);
+        if (x.alive) {
+            const size_t p = (size_t)base + (size_t)place[j];
+            A.lkey[p] = x.key;
+            A.lcost[p] = x.cost;
+            A.lidx[p] = x.e;
+            bids.put(nxt, rst, x.u, x.pu);
+            bids.put(nxt, rst, x.v, x.pv);
+        }
+        if (APPEND) append_live(A, x.alive, x.key, x.cost, x.e);
+    }
+    __syncthreads();
+    bids.flush(nxt, rst);
+    if (threadIdx.x == 0) {
+        A.lcount[tile] = total;
+        tally.end(A);
+    }
+}
+
+// TABLE: bids are put together in LDS (many live edges per line of vertices), else they go out as they are.
+template <bool SHUFFLE, bool APPEND, bool TABLE>
+__global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, int span_shift, int group) {
+    constexpr int N = 2;
     const u64* __restrict__ cur = A.vmin[k % 3];
     u64* __restrict__ nxt = A.vmin[(k + 1) % 3];
     u64* __restrict__ rst = A.vmin[(k + 2) % 3];
-    const int n = A.st->ne;
-    if (blockIdx.x == 0 && threadIdx.x == 0) A.st->sel_k = k + 1;
-    const int lane = prim::lane_id(), w = prim::wave_id();
-    const int tile = prim::xcd_tile(n, prim::WAVES * PER_WAVE);
-    if (threadIdx.x == 0) tally.begin(A, (long long)tile * prim::WAVES * PER_WAVE, n);
-    __syncthreads();
-    int* list = slist[w];
-    const long long cbase = ((long long)tile * prim::WAVES + w) * PER_WAVE;  // (the grid covers every edge)
-    if (cbase < n) {
-        const long long b0 = cbase + (long long)lane * SPARSE_EDGES_PER_LANE;
-        u32 sw[4] = {0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u};  // "retired" beyond the end
-        if (b0 + SPARSE_EDGES_PER_LANE <= n) {
-            if constexpr (SPARSE_EDGES_PER_LANE == 16) {
-                const uint4 q = *reinterpret_cast<const uint4*>(A.estate + b0);
-                sw[0] = q.x; sw[1] = q.y; sw[2] = q.z; sw[3] = q.w;
-            } else {
-                sw[0] = *reinterpret_cast<const u32*>(A.estate + b0);
-            }
-        } else {
-            for (int j = 0; j < SPARSE_EDGES_PER_LANE; ++j)
-                if (b0 + j < n && A.estate[b0 + j] == 0) sw[j >> 2] &= ~(0xFFu << (8 * (j & 3)));
-        }
-        u32 livebits = 0;
+    __shared__ BidTable<TABLE ? LISTED_LINES : 1> bids;
+    __shared__ PairTally tally;
+    __shared__ u32 smem[prim::WAVES];
+    const int n = A.st->ne, t = threadIdx.x;
+    if (blockIdx.x == 0 && t == 0) A.st->sel_k = k + 1;
+    const int parts = (int)(((long long)n + (1ll << span_shift) - 1) >> span_shift);
+    const int first = prim::xcd_tile(parts, group) * group;  // (the first of the workgroup's parts)
+    if (first >= parts) return;
+    const size_t base = (size_t)first << span_shift;
+    int upto[LISTED_GROUP_MAX], n_live = 0;
 #pragma unroll
-        for (int j = 0; j < SPARSE_EDGES_PER_LANE; ++j)
-            if (((sw[j >> 2] >> (8 * (j & 3))) & 0xFFu) == 0) livebits |= 1u << j;
-        const int c = __popc(livebits);
-        int incl = c;
+    for (int g = 0; g < LISTED_GROUP_MAX; ++g)
+        upto[g] = n_live += g < group && first + g < parts ? A.lcount[(size_t)(first + g) << (span_shift - LISTED_TILE_SHIFT)] : 0;
+    if (n_live == 0) {
+        if (t == 0) A.lcount[base >> LISTED_TILE_SHIFT] = 0;
+        return;
+    }
+    if (TABLE) bids.clear();
+    int left = 0;
+    for (int q0 = 0; q0 < n_live; q0 += N * BLOCK) {
+        JudgedEdge<SHUFFLE> E[N];
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int o = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += o;
+        for (int j = 0; j < N; ++j) {
+            const int q = q0 + j * BLOCK + t, at = min(q, n_live - 1);
+            size_t p = base + (size_t)at;
+#pragma unroll
+            for (int g = 0; g + 1 < LISTED_GROUP_MAX; ++g)
+                if (at >= upto[g]) p = base + ((size_t)(g + 1) << span_shift) + (size_t)(at - upto[g]);
+            E[j].key = A.lkey[p];
+            E[j].cost = A.lcost[p];
+            E[j].e = A.lidx[p];
+            E[j].on = q < n_live;
         }
-        const int total = __shfl(incl, 63, 64);
-        int pos = incl - c;
-        while (livebits) {
-            const int j = __ffs((int)livebits) - 1;
-            livebits &= livebits - 1;
-            list[pos++] = (int)(b0 + j);
+        if (q0 == 0 && t == 0) {
+            tally.mesh = A.mt.B <= 1 ? 0 : mesh_of(A.mt.voff, A.mt.B, (int)(E[0].key >> A.vbits));
+            tally.pairs = 0;
         }
-        __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations complete in order)
-        for (int q = 0; q < total; q += 64) {
-            const bool has = q + lane < total;
-            const int i = has ? list[q + lane] : 0;
-            bool alive = false, sel = false;
-            int u = 0, v = 0, m = 0;
-            u64 pu = 0, pv = 0;
-            if (has) alive = subround_edge<SHUFFLE>(A, cur, k, i, u, v, m, pu, pv, sel);
-            tally.count(A, sel, m);
-            if (alive) {
-                atomicMin(&nxt[v], pv);
-                rst[u] = VMIN_NONE;
-                rst[v] = VMIN_NONE;
-            } else if (has) {
-                A.estate[i] = 1;
+        judge_edges<SHUFFLE, N>(A, cur, E);
+        bool alive[N];
+        int place[N], total;
+#pragma unroll
+        for (int j = 0; j < N; ++j) alive[j] = E[j].alive;
+        live_places<N>(alive, smem, place, total);  // (behind its barriers all of this turn's edges have been read)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const JudgedEdge<SHUFFLE>& x = E[j];
+            tally.count(A, x.sel, x.u);
+            if (x.alive) {
+                const size_t p = base + (size_t)(left + place[j]);
+                A.lkey[p] = x.key;
+                A.lcost[p] = x.cost;
+                A.lidx[p] = x.e;
+                if (TABLE) {
+                    bids.put(nxt, rst, x.u, x.pu);
+                    bids.put(nxt, rst, x.v, x.pv);
+                } else {
+                    atomicMin(&nxt[x.u], x.pu);
+                    atomicMin(&nxt[x.v], x.pv);
+                    rst[x.u] = VMIN_NONE;
+                    rst[x.v] = VMIN_NONE;
+                }
             }
-            bid_grouped(nxt, alive, u, pu);
-            if (APPEND) append_live(A, alive, i);
+            if (APPEND) append_live(A, x.alive, x.key, x.cost, x.e);
         }
-        __builtin_amdgcn_wave_barrier();
+        left += total;
     }
     __syncthreads();
-    if (threadIdx.x == 0) tally.end(A);
+    if (TABLE) bids.flush(nxt, rst);
+    if (t == 0) {
+        A.lcount[base >> LISTED_TILE_SHIFT] = left;
+        tally.end(A);
+    }
 }
 
 // Tail: once few edges are live, one workgroup finishes the matching with all

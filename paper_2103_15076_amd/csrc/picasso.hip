@@ -629,6 +629,34 @@ int pair_budget(picasso_ctx* c, hipStream_t s, const TieBreak& tb, int B, const 
     return budget_step(c, s, PairKeys<false>{c->pcost(), nullptr, c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, guarded, tell);
 }
 
+// Sub-round k of the selection.  last: it lists the edges it leaves live for the tail.
+void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bool last, int round) {
+    const bool listed = sa.bound >= LISTED_MIN_EDGES;
+    const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, k == 0); /* (the first only) */
+#define PICASSO_SUBROUND(SHUFFLE, APPEND)                                                                                   \
+    do {                                                                                                                     \
+        if (!listed) {                                                                                                       \
+            select_subround_kernel<SHUFFLE, APPEND><<<grid_for(sa.bound), BLOCK, 0, s>>>(sa, k);                             \
+        } else if (k == 0) {                                                                                                 \
+            select_first_kernel<SHUFFLE, APPEND><<<prim::xcd_grid((sa.bound + LISTED_TILE - 1) / LISTED_TILE), BLOCK, 0, s>>>(sa); \
+        } else {                                                                                                             \
+            const int span = listed_span(k), group = listed_group(k);                                                        \
+            const long long parts = (((long long)sa.bound - 1) >> span) + 1;                                                 \
+            const int grid = prim::xcd_grid((int)((parts + group - 1) / group));                                             \
+            if (k <= 2) select_listed_kernel<SHUFFLE, APPEND, true><<<grid, BLOCK, 0, s>>>(sa, k, span, group);              \
+            else select_listed_kernel<SHUFFLE, APPEND, false><<<grid, BLOCK, 0, s>>>(sa, k, span, group);                    \
+        }                                                                                                                    \
+    } while (0)
+    if (sa.tb.on) {
+        if (last) PICASSO_SUBROUND(true, true);
+        else PICASSO_SUBROUND(true, false);
+    } else {
+        if (last) PICASSO_SUBROUND(false, true);
+        else PICASSO_SUBROUND(false, false);
+    }
+#undef PICASSO_SUBROUND
+}
+
 // Alg. 2 line 11 on the device for the round whose pairs are final (see the kernels).  nrem /
 // h_matched: per-mesh budget and pairs kept (host mirrors); h_joined receives the vertices that
 // join per mesh; *akeys the sorted (representative, vertex) keys, st->absorb_n of them.  Waits for
@@ -849,6 +877,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         sa.live_cap = TAIL_MAX;
         sa.live_n = c->live_n;
         sa.estate = c->estate;
+        sa.bound = std::max(H, 1);
+        sa.lkey = c->key64[0];  // (between the edges' sort and line 11 these four are free)
+        sa.lcost = c->val32;
+        sa.lidx = c->list;
+        sa.lcount = c->fslot;
         sa.st = c->st;
         sa.mt = mt;
         sa.vbits = vbits;
@@ -874,27 +907,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             for (long long l = live_est; l > TAIL_MAX; ++wide) l = l * 10 / decay_x10[std::min(wide, 5)];
             wide = std::min<int>(wide, (int)std::max<int64_t>(1, c->opt_subround_batch));
             wide = std::max(wide, 1);  // (the last of them lists what it leaves live for the tail)
-            for (int j = 0; j < wide; ++j) {
-                const int g4 = prim::xcd_grid((ne_bound + BLOCK * 4 - 1) / (BLOCK * 4)), g16 = prim::xcd_grid((ne_bound + BLOCK * 16 - 1) / (BLOCK * 16));
-                const bool sparse = sel_k + j > 0 && ne_bound >= SPARSE_MIN_EDGES, last = j == wide - 1;
-#define PICASSO_SUBROUND(APPEND)                                                                                            \
-    do {                                                                                                                     \
-        if (sparse && sel_k + j == 1) {                                                                                      \
-            if (tb.on) select_subround_sparse_kernel<4, true, APPEND><<<g4, BLOCK, 0, s>>>(sa, sel_k + j);                    \
-            else select_subround_sparse_kernel<4, false, APPEND><<<g4, BLOCK, 0, s>>>(sa, sel_k + j);                         \
-        } else if (sparse) {                                                                                                 \
-            if (tb.on) select_subround_sparse_kernel<16, true, APPEND><<<g16, BLOCK, 0, s>>>(sa, sel_k + j);                  \
-            else select_subround_sparse_kernel<16, false, APPEND><<<g16, BLOCK, 0, s>>>(sa, sel_k + j);                       \
-        } else {                                                                                                             \
-            const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, sel_k + j == 0); /* (the first only) */         \
-            if (tb.on) select_subround_kernel<true, APPEND><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);     \
-            else select_subround_kernel<false, APPEND><<<grid_for(ne_bound, 1 << 14), BLOCK, 0, s>>>(sa, sel_k + j);          \
-        }                                                                                                                    \
-    } while (0)
-                if (last) PICASSO_SUBROUND(true);
-                else PICASSO_SUBROUND(false);
-#undef PICASSO_SUBROUND
-            }
+            for (int j = 0; j < wide; ++j) launch_subround(c, s, sa, sel_k + j, j == wide - 1, round);
             sel_k += wide;
             // the kernel behind the tail tells the host that the tail's results are in the read-back area
             const HostSignal tail_done = next_signal(c);

@@ -719,6 +719,42 @@ def test_few_sub_rounds_between_looks_of_the_host(pk, ctx, oracle, batch):
         ctx.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, 16)
 
 
+@pytest.mark.parametrize("flat", [False, True])
+@pytest.mark.parametrize("seed", [0, 77])
+@pytest.mark.parametrize("batch", [1, 3, 16])
+def test_listed_sub_rounds(pk, ctx, oracle, flat, seed, batch):
+    """Rounds of more than 2^20 half-edges list their live edges from sub-round to sub-round: many of them (every cost equal), one or three
+    to a look of the host, with the seeded order; parts of the list that end within a tile."""
+    V, F = meshgen.noisy_grid(601, 397, seed=3)
+    if flat:
+        V = V.copy()
+        V[:, 2] = 0
+    ctx.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, batch)
+    ctx.set_option(pk.PICASSO_OPT_SHUFFLE_SEED, seed)
+    try:
+        for target in (V.shape[0] * 7 // 10, V.shape[0] // 3):
+            print(f"listed flat={flat} seed={seed} batch={batch} target={target}", flush=True)
+            st, vo, fo, cid = ctx.picasso_decimate(dev(V), dev(F), target)
+            assert_same_result(st, vo, fo, cid, oracle.decimate(V, F, target, shuffle_seed=seed))
+    finally:
+        ctx.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, 16)
+        ctx.set_option(pk.PICASSO_OPT_SHUFFLE_SEED, 0)
+
+
+def test_listed_sub_rounds_of_a_batch_with_meshes_that_rest(ctx, oracle):
+    """The edges of meshes that take no part stay out of the lists from the start."""
+    parts = [meshgen.noisy_grid(w, h, seed=w) for w, h in ((300, 200), (7, 9), (411, 300), (2, 2), (350, 250))]
+    nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
+    base = np.concatenate([[0], np.cumsum(nv)])
+    V, F = np.concatenate([p[0] for p in parts]), np.concatenate([p[1] + np.int32(b) for p, b in zip(parts, base)])
+    target = [nv[0] // 2, nv[1], nv[2], 1, nv[4] // 5]
+    print("listed batch", flush=True)
+    st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
+    ref = oracle.decimate_batch(V, F, nv, nf, target)
+    assert list(nvo) == list(ref["nv"]) and list(nfo) == list(ref["nf"])
+    assert_same_result(st, vo, fo, cid, ref)
+
+
 def test_statistics_and_timing_options_do_not_change_the_result(pk, ctx, oracle):
     """The per-round statistics agree with the oracle's bookkeeping; stage events and the kernel's
     launch events are measurement only."""
