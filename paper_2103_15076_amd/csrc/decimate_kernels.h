@@ -1598,7 +1598,12 @@ struct PairKeys {
     int* mate;
     static constexpr bool TIE_BY_VERTEX = !SHUFFLE;
     typedef u32 Raw;
+    static constexpr Raw NONE = PAIR_NONE;
     __device__ __forceinline__ Raw load(int w) const { return pcost[w]; }
+    __device__ __forceinline__ void load4(int w, Raw* r) const {  // (w: a multiple of 4)
+        const uint4 q = *reinterpret_cast<const uint4*>(pcost + w);
+        r[0] = q.x; r[1] = q.y; r[2] = q.z; r[3] = q.w;
+    }
     __device__ __forceinline__ bool has(Raw r) const { return r != PAIR_NONE; }
     __device__ __forceinline__ u32 cost(Raw r) const { return r; }
     __device__ __forceinline__ u32 tie(int w, int v0) const { return SHUFFLE ? ptie[w] : (u32)(w - v0); }
@@ -1614,7 +1619,13 @@ struct JoinKeys {
     u64* abid;
     static constexpr bool TIE_BY_VERTEX = false;
     typedef u64 Raw;
+    static constexpr Raw NONE = ABID_NONE;
     __device__ __forceinline__ Raw load(int w) const { return abid[w]; }
+    __device__ __forceinline__ void load4(int w, Raw* r) const {
+        const ulonglong2* q = reinterpret_cast<const ulonglong2*>(abid + w);
+        const ulonglong2 a = q[0], b = q[1];
+        r[0] = a.x; r[1] = a.y; r[2] = b.x; r[3] = b.y;
+    }
     __device__ __forceinline__ bool has(Raw r) const { return r != ABID_NONE; }
     __device__ __forceinline__ u32 cost(Raw r) const { return (u32)(r >> 32); }
     __device__ __forceinline__ u32 tie(int w, int) const { return (u32)abid[w]; }
@@ -1623,48 +1634,57 @@ struct JoinKeys {
     __device__ __forceinline__ void release(int w, int) const { abid[w] = ABID_NONE; }
 };
 
-// Meshes with at most `longer_than` keys (<= cap <= CAP where any has more): one workgroup per mesh finds the cost key of the budget's last pair, its top 12 bits
-// by counts in LDS, the others among the keys that share them, listed in LDS in any order, digit by digit (8 bits at a
-// time from the highest bit in which they differ at all); where the budget ends among equal keys, the last tie-break value in the
-// same way; and (few keys) walks the vertices once more to release what lies beyond.  Bound by the trips to LDS and memory of one compute unit; 16 vertices per lane are in flight.
+// Meshes with at most `longer_than` keys (<= cap where any has more): one workgroup per mesh finds the budget's last key, ordered by
+// (cost key, tie-break value).  What may be it is listed in LDS in any order: all keys of up to TRUNC_DIRECT, of more those whose costs
+// lie about where a sample of 4,096 vertices has the budget's last one; should the sample mislead, or too many costs be equal, the
+// range is narrowed by counts of all keys instead, 12 bits a walk.  Of the list, counts of 12 bits a time from the highest bit
+// in which its costs can differ leave 64 or less, which one wave ranks.  What lies beyond is released by the kernel that counts the survivors
+// (ReleasingPred), or, where something else reads the pairs before it, by trunc_release_kernel or (few keys) here.
+// Bound by the issue of one compute unit (a vector instruction per vertex is 0.4 us for 62 k of them; the walk itself takes 3.4, 16 bytes a
+// load, the next step's ahead) and by LDS atomics of clustered costs, which take turns: hence a walk that only compares, and counts
+// of the listed keys alone.  115 k vertices (62 k and 28 k pairs in the last round): 35 us with counts of all keys, the others and the ties
+// listed by walks of their own, and 5 for the release; now 21.  4 k vertices (550 pairs): 12.7, now 5.8; 16 meshes of 32 k vertices: 24 + 5, now 17.
 //
-// Up to TRUNC_BLOCK_CAP keys a mesh goes this way, because its search, one or two launches that know nothing of the host, can be queued
+// Up to TRUNC_BLOCK_CAP keys a mesh goes this way, because its search, one launch that knows nothing of the host, can be queued
 // ahead of the host's look; the whole chip's (below) takes seven or eight.  Whole calls of one round with three quarters of the pairs
 // staying, this way / the other: one mesh of 539 pairs 92 / 116 us, 2,139 100 / 129, 8,576 119 / 147, 17,022 134 / 156; eight meshes of
 // 2,139 pairs 133 / 162, of 17,022 283 / 301.  Beyond the cap the keys of a mesh may not fit LDS.
 constexpr int TRUNC_THREADS = 1024;
 constexpr int TRUNC_BLOCK_CAP = 32 * TRUNC_THREADS;
-constexpr int TRUNC_SMALL_CAP = 4 * TRUNC_THREADS;
+constexpr int TRUNC_SMALL_CAP = 4 * TRUNC_THREADS;  // up to here the release is made here, where the count does not make it
+constexpr int TRUNC_LIST = 16 * TRUNC_THREADS, TRUNC_DIRECT = 2 * TRUNC_THREADS;
 
 // What stays of a mesh's keys: those below `cost`, and at it those with tie-break values up to `tie`, or all of them.
 struct KeyLimit {
     u32 cost, tie;
-    int over;  // 0: every key stays; 1: see above; 2: all keys at `cost` stay; 3: none stays
+    int over;  // 0: every key stays; 1: see above; 3: none stays
 };
 template <class Keys>
 __device__ __forceinline__ bool beyond(const Keys& K, const KeyLimit& L, u32 cost, int w, int v0) {
-    return L.over == 3 || cost > L.cost || (L.over == 1 && cost == L.cost && K.tie(w, v0) > L.tie);
+    return L.over == 3 || cost > L.cost || (cost == L.cost && K.tie(w, v0) > L.tie);
 }
 
-template <class Keys, int CAP>
+template <class Keys>
 __global__ __launch_bounds__(TRUNC_THREADS) void trunc_mesh_kernel(Keys K, const int* __restrict__ voff,
                                                                    const int* __restrict__ counts,
                                                                    const int* __restrict__ budgets, int cap, int longer_than,
                                                                    const int* __restrict__ guard, State* st, HostSignal tell,
                                                                    KeyLimit* __restrict__ limits) {
-    constexpr int Q = 16, COPIES = 16, TOP_SHIFT = 20;
-    static_assert(256 * COPIES == 1 << (32 - TOP_SHIFT), "the array of counts holds the top digits");
-    __shared__ u32 list[CAP];
-    __shared__ u32 hist[256 * COPIES];  // (copies by lane: cost keys cluster, and atomics of a wave on one word take turns)
-    __shared__ u32 total[256];
-    __shared__ u32 found[3];
-    __shared__ u32 n_list, lowest, highest;
+    constexpr int Q = 16, STEP = Q * TRUNC_THREADS, WALK_BITS = 12;
+    static_assert(1 << WALK_BITS == 4 * TRUNC_THREADS, "four digits per thread");
+    __shared__ u64 list[TRUNC_LIST];
+    __shared__ uint4 hist4[TRUNC_THREADS];  // counts per digit
+    __shared__ u32 smem[TRUNC_THREADS / 64];
+    __shared__ u64 found_key, few[64];
+    __shared__ u32 found[4];
+    __shared__ u32 n_list, n_below;
+    u32* hist = reinterpret_cast<u32*>(hist4);
     const int b = blockIdx.x, tid = threadIdx.x, lane = prim::lane_id();
     if (b == 0 && tid == 0) tell_host(tell);
-    constexpr bool RELEASE = CAP <= TRUNC_SMALL_CAP;
-    if (!RELEASE && tid == 0) limits[b] = KeyLimit{0u, 0u, 0};
-    if (guard && *guard == 0) return;  // queued ahead of the host's look, and the selection was not finished
-    const int n = counts[b], keep = budgets[b];
+    // (all of these loads are in flight together)
+    const int go = guard ? *guard : 1, n = counts[b], keep = budgets[b], v0 = voff[b], v1 = voff[b + 1];
+    if (limits && tid == 0) limits[b] = KeyLimit{0u, 0u, 0};
+    if (go == 0) return;  // queued ahead of the host's look, and the selection was not finished
     if (n <= keep) return;
     if (n > longer_than) return;  // another kernel for these follows
     if (n > cap) {
@@ -1673,212 +1693,254 @@ __global__ __launch_bounds__(TRUNC_THREADS) void trunc_mesh_kernel(Keys K, const
         if (tid == 0) atomicOr(&st->err, ERR_BIT_INTERNAL);
         return;
     }
-    const int v0 = voff[b], v1 = voff[b + 1];
-    const u64 lt = prim::lanemask_lt();
-    if (tid == 0) {
-        n_list = 0;
-        lowest = ~0u;
-        highest = 0;
-    }
-    __syncthreads();
-    // fn(first vertex, which of them have keys, raw keys) for the vertices base + q * TRUNC_THREADS + tid of each step, by whole
-    // waves: a step's loads are all in flight together (unconditional, at vertices of the mesh)
+    typedef typename Keys::Raw Raw;
+    const int first = v0 & ~3;
+    const int at = 4 * tid;
+    auto vertex_of = [&](int q) { return (q >> 2) * (4 * TRUNC_THREADS) + at + (q & 3); };
+    // fn(first vertex, keys of the vertices first + vertex_of(q), Keys::NONE outside the mesh) step by step, by whole waves; the next step's
+    // keys are fetched meanwhile
     auto each_step = [&](auto fn) {
-        for (int base = v0; base < v1; base += Q * TRUNC_THREADS) {
-            typename Keys::Raw raw[Q];
-            u32 has = 0;
+        Raw next[Q];
+        auto fetch = [&](int base) {
 #pragma unroll
-            for (int q = 0; q < Q; ++q) raw[q] = K.load(min(base + q * TRUNC_THREADS + tid, v1 - 1));
+            for (int q = 0; q < Q; q += 4) K.load4(min(base + vertex_of(q), (v1 - 1) & ~3), &next[q]);
+        };
+        fetch(first);
+        for (int base = first; base < v1; base += STEP) {
+            Raw raw[Q];
 #pragma unroll
-            for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(raw[q]));
+            for (int q = 0; q < Q; ++q) raw[q] = next[q];
+            if (base + STEP < v1) fetch(base + STEP);
+            if (base < v0 || base + STEP > v1) {
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (base + q * TRUNC_THREADS + tid < v1 && K.has(raw[q])) has |= 1u << q;
-            fn(base, has, raw);
-        }
-    };
-    // a lane's values, one for every bit of `on`, go to the list: one atomic per wave
-    auto append = [&](u32 on, auto value) {
-        const u32 mine = (u32)__popc(on);
-        u32 incl = mine;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const u32 o = (u32)__shfl_up((int)incl, d, 64);
-            if (lane >= d) incl += o;
-        }
-        u32 at = 0;
-        if (lane == 63 && incl) at = atomicAdd(&n_list, incl);
-        at = (u32)__shfl((int)at, 63, 64) + incl - mine;
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if ((on >> q & 1u) && at < (u32)CAP) list[at++] = value(q);
-    };
-    // The want-th smallest (1 <= want <= n) of the first n values of the list, which lie between lo and hi; how many are less, and equal.
-    auto nth = [&](int n, u32 lo, u32 hi, u32 want, u32& less, u32& equal) -> u32 {
-        less = 0;
-        equal = (u32)n;
-        if (lo == hi) return lo;
-        int bit = 31 - __clz((int)(lo ^ hi));
-        u32 decided = bit == 31 ? 0u : ~0u << (bit + 1), prefix = lo & decided;
-        while (bit >= 0) {
-            const int nb = min(8, bit + 1), shift = bit + 1 - nb;
-            for (int i = tid; i < 256 * COPIES; i += TRUNC_THREADS) hist[i] = 0;
-            __syncthreads();
-            for (int i = tid; i < n; i += TRUNC_THREADS) {
-                const u32 k = list[i];
-                if ((k & decided) == prefix) atomicAdd(&hist[((k >> shift) & ((1u << nb) - 1u)) * COPIES + (lane & (COPIES - 1))], 1u);
-            }
-            __syncthreads();
-            if (tid < 256) {
-                u32 sum = 0;
-#pragma unroll
-                for (int j = 0; j < COPIES; ++j) sum += hist[tid * COPIES + ((tid + j) & (COPIES - 1))];
-                total[tid] = sum;
-            }
-            __syncthreads();
-            if (tid < 64) {
-                u32 c[4], sum = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sum += c[j] = total[4 * lane + j];
-                u32 incl = sum;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const u32 o = (u32)__shfl_up((int)incl, d, 64);
-                    if (lane >= d) incl += o;
-                }
-                u32 run = incl - sum;
-                const u32 need = want - less;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (run < need && need <= run + c[j]) {  // (in one lane)
-                        found[0] = (u32)(4 * lane + j);
-                        found[1] = run;
-                        found[2] = c[j];
-                    }
-                    run += c[j];
+                for (int q = 0; q < Q; ++q) {
+                    const int w = base + vertex_of(q);
+                    if (w < v0 || w >= v1) raw[q] = Keys::NONE;
                 }
             }
-            __syncthreads();
-            prefix |= found[0] << shift;
-            less += found[1];
-            equal = found[2];
-            bit -= nb;
-            decided = bit < 0 ? ~0u : ~0u << (bit + 1);
+            fn(base, raw);
         }
-        return prefix;
     };
-    auto bounds = [&](u32 lo, u32 hi) {
+    // Lists (cost key << 32) | vertex of the costs from lo to hi; n_list of them (the list may hold less), n_below in front of lo.
+    auto list_range = [&](u32 lo, u32 hi) {
+        if (tid == 0) n_list = n_below = 0;
+        __syncthreads();
+        u32 less = 0;
+        each_step([&](int base, const Raw (&raw)[Q]) {
+            u32 mine = 0;
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            lo = min(lo, (u32)__shfl_xor((int)lo, d, 64));
-            hi = max(hi, (u32)__shfl_xor((int)hi, d, 64));
-        }
-        if (lane == 0) {
-            atomicMin(&lowest, lo);
-            atomicMax(&highest, hi);
-        }
+            for (int q = 0; q < Q; ++q) {
+                const u32 cost = K.cost(raw[q]);  // (of Keys::NONE: above every hi)
+                less += cost < lo ? 1u : 0u;
+                mine += cost - lo <= hi - lo ? 1u : 0u;
+            }
+            if (!__any(mine != 0)) return;
+            const u32 incl = prim::wave_inclusive_scan(mine);
+            u32 p = 0;
+            if (lane == 63) p = atomicAdd(&n_list, incl);
+            p = (u32)__builtin_amdgcn_readlane((int)p, 63) + incl - mine;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const u32 cost = K.cost(raw[q]);
+                if (cost - lo <= hi - lo) {
+                    if (p < (u32)TRUNC_LIST) list[p] = ((u64)cost << 32) | (u32)(base + vertex_of(q));
+                    ++p;
+                }
+            }
+        });
+        less = prim::wave_inclusive_scan(less);
+        if (lane == 63 && less) atomicAdd(&n_below, less);
+        __syncthreads();
     };
-    u32 last_cost = 0, last_tie = 0;  // what stays: keys below last_cost, and at it those with tie-break values up to last_tie
-    bool none = keep <= 0, all_ties = false;
+    // From the counts, the digits of 12 bits in which the want-th and the want2-th of those counted lie, want and want2 from the number
+    // of all: found[0] (found[1] in front of it, found[2] in it) and found[3].
+    auto pick = [&](auto wants) {
+        const uint4 c4 = hist4[tid];
+        const u32 c[4] = {c4.x, c4.y, c4.z, c4.w};
+        u32 tot, run = prim::wide_block_exclusive_scan<TRUNC_THREADS / 64>((c[0] + c[1]) + (c[2] + c[3]), smem, tot);
+        u32 want, want2;
+        wants(tot, want, want2);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (run < want && want <= run + c[j]) {  // (in one thread)
+                found[0] = (u32)(tid * 4 + j);
+                found[1] = run;
+                found[2] = c[j];
+            }
+            if (run < want2 && want2 <= run + c[j]) found[3] = (u32)(tid * 4 + j);
+            run += c[j];
+        }
+        __syncthreads();
+        return tot;
+    };
+    auto clear_counts = [&]() {
+        hist4[tid] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+    };
+    u64 last = 0;  // the last key that stays
+    const bool none = keep <= 0;
     if (!none) {
-        // the top 12 bits by counts over all keys ...
-        for (int i = tid; i < 256 * COPIES; i += TRUNC_THREADS) hist[i] = 0;
-        __syncthreads();
-        each_step([&](int, u32 has, const auto& raw) {
+        constexpr u32 HIGHEST = 0xFFFFFFFEu;  // (a key has a finite cost)
+        u32 lo = 0, hi = HIGHEST;
+        if (n > TRUNC_DIRECT) {
+            Raw some[4];  // four vertices in a row per lane, evenly over the mesh
+            const int w0 = (int)(((long long)(v1 - first) * tid) >> 10) / 4 * 4 + first;
+            K.load4(w0, some);
+            clear_counts();
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (has >> q & 1u) atomicAdd(&hist[K.cost(raw[q]) >> TOP_SHIFT], 1u);
-        });
-        __syncthreads();
-        {
-            constexpr int PER = 256 * COPIES / TRUNC_THREADS;
-            u32 c[PER], sum = 0, tot;
-#pragma unroll
-            for (int j = 0; j < PER; ++j) sum += c[j] = hist[tid * PER + j];
-            u32 run = prim::wide_block_exclusive_scan<TRUNC_THREADS / 64>(sum, total, tot);
-#pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                if (run < (u32)keep && (u32)keep <= run + c[j]) {  // (in one thread)
-                    found[0] = (u32)(tid * PER + j);
-                    found[1] = run;
-                    found[2] = c[j];
-                }
-                run += c[j];
-            }
-        }
-        __syncthreads();
-        const u32 top = found[0], below_top = found[1];
-        const int with_top = (int)found[2];
-        // ... the others in a list of the keys that share them
-        u32 lo = ~0u, hi = 0;
-        each_step([&](int, u32 has, const auto& raw) {
-            u32 on = 0;
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if ((has >> q & 1u) && K.cost(raw[q]) >> TOP_SHIFT == top) on |= 1u << q;
-            if (!__any(on != 0)) return;
-            append(on, [&](int q) {
-                const u32 k = K.cost(raw[q]);
-                lo = min(lo, k);
-                hi = max(hi, k);
-                return k;
+            for (int q = 0; q < 4; ++q)
+                if (w0 + q >= v0 && w0 + q < v1 && K.has(some[q])) atomicAdd(&hist[K.cost(some[q]) >> (32 - WALK_BITS)], 1u);
+            __syncthreads();
+            // (six standard deviations of a rank in the middle of a sample of `all`: neighbours are alike)
+            u32 r0 = 0, r1 = 0;
+            const u32 all = pick([&](u32 all, u32& want, u32& want2) {
+                const float rank = (float)all * (float)keep / (float)n, margin = 3.0f * sqrtf((float)all) + 4.0f;
+                r0 = want = rank > margin ? (u32)(rank - margin) : 0u;
+                r1 = want2 = min((u32)(rank + margin), all + 1u);
             });
-        });
-        bounds(lo, hi);
-        __syncthreads();
-        u32 less, ties;
-        last_cost = nth(with_top, lowest, highest, (u32)keep - below_top, less, ties);
-        const u32 stay = (u32)keep - below_top - less;  // of the keys that are exactly that; the tie-break says which
-        all_ties = ties <= stay;
-        if (!all_ties) {
+            if (r0 > 0) lo = found[0] << (32 - WALK_BITS);
+            if (r1 > 0 && r1 <= all) hi = min(HIGHEST, (found[3] << (32 - WALK_BITS)) | ((1u << (32 - WALK_BITS)) - 1u));
             __syncthreads();
-            if (tid == 0) {
-                n_list = 0;
-                lowest = ~0u;
-                highest = 0;
-            }
-            __syncthreads();
-            lo = ~0u;
-            hi = 0;
-            each_step([&](int base, u32 has, const auto& raw) {
-                u32 on = 0;
-#pragma unroll
-                for (int q = 0; q < Q; ++q)
-                    if ((has >> q & 1u) && K.cost(raw[q]) == last_cost) on |= 1u << q;
-                if (!__any(on != 0)) return;
-                append(on, [&](int q) {
-                    const u32 t = K.tie(base + q * TRUNC_THREADS + tid, v0);
-                    lo = min(lo, t);
-                    hi = max(hi, t);
-                    return t;
+        }
+        list_range(lo, hi);
+        int bit = 32 - __clz((int)(lo ^ hi));  // bits of the listed costs from here on are the same (-1 .. : none differ)
+        u32 tie_prefix = 0;  // what their tie-break values share from tie_bit on, where one cost is listed
+        int tie_bit = Keys::TIE_BY_VERTEX ? 32 - __clz(v1 - v0) : 32;
+        if (!(n_below < (u32)keep && (u32)keep <= n_below + n_list && n_list <= (u32)TRUNC_LIST)) {
+            // digit by digit by counts of all keys: of the cost key, then of the tie-break values at that cost
+            u32 cost = 0, tie = 0, below = 0;
+            int undecided = 64;
+            for (;;) {
+                const int nb = undecided == 40 || undecided == 8 ? 8 : WALK_BITS;  // (12, 12 and 8 bits of either)
+                undecided -= nb;
+                __syncthreads();
+                clear_counts();
+                each_step([&](int base, const Raw (&raw)[Q]) {
+#pragma unroll 4
+                    for (int q = 0; q < Q; ++q) {
+                        if (!K.has(raw[q])) continue;
+                        u32 k = K.cost(raw[q]), decided = cost;
+                        int above = undecided + nb - 32;
+                        if (undecided < 32) {
+                            if (k != cost) continue;
+                            k = K.tie(base + vertex_of(q), v0);
+                            decided = tie;
+                            above += 32;
+                        }
+                        if (above < 32 && k >> above != decided >> above) continue;
+                        atomicAdd(&hist[(k >> (above - nb)) & ((1u << nb) - 1u)], 1u);
+                    }
                 });
-            });
-            bounds(lo, hi);
+                __syncthreads();
+                pick([&](u32, u32& want, u32& want2) {
+                    want = (u32)keep - below;
+                    want2 = 0;
+                });
+                if (undecided >= 32) cost |= found[0] << (undecided - 32);
+                else tie |= found[0] << undecided;
+                below += found[1];
+                if (found[2] <= (u32)TRUNC_LIST) break;
+            }
             __syncthreads();
-            u32 same;
-            last_tie = nth((int)ties, lowest, highest, stay, less, same);
+            lo = cost;
+            hi = undecided > 32 ? cost | ((1u << (undecided - 32)) - 1u) : cost;
+            bit = undecided > 32 ? undecided - 32 : 0;
+            if (undecided >= 32) {
+                list_range(lo, hi);
+            } else {  // at that cost only the ones with the tie-break values' leading digits
+                tie_prefix = tie;
+                tie_bit = undecided;
+                if (tid == 0) {
+                    n_list = 0;
+                    n_below = below;
+                }
+                __syncthreads();
+                each_step([&](int base, const Raw (&raw)[Q]) {
+#pragma unroll 4
+                    for (int q = 0; q < Q; ++q) {
+                        const int w = base + vertex_of(q);
+                        if (!K.has(raw[q]) || K.cost(raw[q]) != cost || K.tie(w, v0) >> tie_bit != tie >> tie_bit) continue;
+                        const u32 place = atomicAdd(&n_list, 1u);
+                        if (place < (u32)TRUNC_LIST) list[place] = ((u64)cost << 32) | (u32)w;
+                    }
+                });
+                __syncthreads();
+            }
         }
+        const int m = (int)min(n_list, (u32)TRUNC_LIST);
+        u32 want = (u32)keep - n_below;
+        u32* half = reinterpret_cast<u32*>(list);  // (tie-break value or vertex, cost) of entry i at 2 i
+        for (int i = tid; i < m; i += TRUNC_THREADS) half[2 * i] = K.tie((int)half[2 * i], v0);
+        __syncthreads();
+        // of the list, by the costs and then the tie-break values: until 64 or less are left, which one wave ranks
+        u32 equal = (u32)m, prefix[2] = {0, 0};
+        int from[2] = {32, 32};  // the word's bits from here on are decided
+#pragma unroll
+        for (int word = 1; word >= 0; --word) {
+            from[word] = word == 1 ? bit : tie_bit;
+            if (word == 1) prefix[1] = bit >= 32 ? 0u : lo & (~0u << bit);
+            else prefix[0] = tie_prefix;
+            while (equal > 64u && from[word] > 0) {
+                const int nb = min(WALK_BITS, from[word]), shift = from[word] - nb;
+                const u32 decided = from[word] >= 32 ? 0u : ~0u << from[word];
+                clear_counts();
+                for (int i = tid; i < m; i += TRUNC_THREADS) {
+                    const u32 k = half[2 * i + word];
+                    if ((k & decided) == prefix[word] && (word == 1 || half[2 * i + 1] == prefix[1]))
+                        atomicAdd(&hist[(k >> shift) & ((1u << nb) - 1u)], 1u);
+                }
+                __syncthreads();
+                pick([&](u32, u32& first_want, u32& second_want) {
+                    first_want = want;
+                    second_want = 0;
+                });
+                prefix[word] |= found[0] << shift;
+                want -= found[1];
+                equal = found[2];
+                from[word] = shift;
+                __syncthreads();
+            }
+        }
+        if (tid == 0) n_list = 0;
+        __syncthreads();
+        const u32 d1 = from[1] >= 32 ? 0u : ~0u << from[1], d0 = from[0] >= 32 ? 0u : ~0u << from[0];
+        for (int i = tid; i < m; i += TRUNC_THREADS)
+            if ((half[2 * i + 1] & d1) == prefix[1] && (half[2 * i] & d0) == prefix[0]) {
+                const u32 p = atomicAdd(&n_list, 1u);
+                if (p < 64u) few[p] = list[i];
+            }
+        __syncthreads();
+        if (tid < 64) {
+            const int c = (int)min(n_list, 64u);
+            const u64 k = few[min(tid, c - 1)];
+            u32 rank = 0;
+            for (int i = 0; i < c; ++i) rank += few[i] < k ? 1u : 0u;
+            if (tid < c && rank + 1u == want) found_key = k;
+        }
+        __syncthreads();
+        last = found_key;
     }
-    const KeyLimit limit{last_cost, last_tie, none ? 3 : (all_ties ? 2 : 1)};
-    if constexpr (!RELEASE) {
+    const KeyLimit limit{(u32)(last >> 32), (u32)last, none ? 3 : 1};
+    if (limits) {
         if (tid == 0) limits[b] = limit;
         return;
     }
-    each_step([&](int base, u32 has, const auto& raw) {
+    each_step([&](int base, const Raw (&raw)[Q]) {
+        u32 out = 0;
         int with[Q];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) with[q] = K.partner(min(base + q * TRUNC_THREADS + tid, v1 - 1));
-#pragma unroll
-        for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(with[q]));
-#pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const int w = base + q * TRUNC_THREADS + tid;
-            if ((has >> q & 1u) && beyond(K, limit, K.cost(raw[q]), w, v0)) K.release(w, with[q]);
+            const int w = base + vertex_of(q);
+            if (K.has(raw[q]) && beyond(K, limit, K.cost(raw[q]), w, v0)) out |= 1u << q;
+            with[q] = K.partner(max(min(w, v1 - 1), v0));
         }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (out >> q & 1u) K.release(base + vertex_of(q), with[q]);
     });
 }
 
-// The release by the whole chip, for the instance that leaves it to this (the stores of 29 k pairs take one compute unit 20 us).
+// The release by the whole chip, where the search leaves it to this (the stores of 29 k pairs take one compute unit 20 us).
 template <class Keys>
 __global__ __launch_bounds__(BLOCK) void trunc_release_kernel(Keys K, int nv, const int* __restrict__ voff, int B,
                                                               const KeyLimit* __restrict__ limits) {
@@ -2159,6 +2221,26 @@ struct AlivePredT {
         const int m = mate[w];
         if (m >= 0 && m < w) return false;  // the larger index of a pair is replaced by the smaller
         return !(ABSORB && arep[w] >= 0);   // as is a vertex that joined a pair's cluster
+    }
+};
+
+// The same where a budget step has left the meshes' limits: a pair beyond its mesh's is dissolved on the way, each end by its own lane.
+template <bool SHUFFLE>
+struct ReleasingPred {
+    PairKeys<SHUFFLE> K;
+    const int* voff;
+    int B;
+    const KeyLimit* limits;
+    __device__ bool operator()(int w) const {
+        const int m = K.mate[w];
+        if (m < 0) return true;
+        const int b = mesh_of(voff, B, w), lo = min(m, w);
+        const KeyLimit limit = limits[b];
+        if (limit.over != 0 && beyond(K, limit, K.cost(K.load(lo)), lo, voff[b])) {
+            K.mate[w] = -1;
+            return true;
+        }
+        return m > w;
     }
 };
 

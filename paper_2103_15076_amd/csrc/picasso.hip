@@ -582,9 +582,10 @@ int status_from_err_bits(int bits) {
 // `guarded` (most <= the limit of one workgroup per mesh only): queued behind the
 // selection tail before the host has looked; the counts are then upper bounds and the
 // kernel does nothing unless the tail finished the matching; it stores `tell` first.
+// by_count: the kernel that counts the survivors releases what the search of one workgroup per mesh leaves beyond its limits.
 template <class Keys>
 int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* voff, int nv_max, int most, int least,
-                const int* counts, const int* budgets, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
+                const int* counts, const int* budgets, bool by_count, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
     const int limit = (int)c->opt_trunc_block_max;
     const bool longer = most > limit;
     if (guarded && longer) return PICASSO_ERR_INVALID_ARG;
@@ -594,14 +595,10 @@ int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* 
         const int longer_than = longer ? limit : 0x7FFFFFFF;
         int cap = need <= TRUNC_SMALL_CAP ? TRUNC_SMALL_CAP : TRUNC_BLOCK_CAP;
         if (c->opt_trunc_width) cap = c->opt_trunc_width * TRUNC_THREADS;  // (test hook)
-        if (cap <= TRUNC_SMALL_CAP)
-            trunc_mesh_kernel<Keys, TRUNC_SMALL_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer_than,
-                                                                                guard, c->st, tell, nullptr);
-        else {
-            trunc_mesh_kernel<Keys, TRUNC_BLOCK_CAP><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer_than,
-                                                                                guard, c->st, tell, c->limits);
-            trunc_release_kernel<Keys><<<grid_for(nv_max), BLOCK, 0, s>>>(K, nv_max, voff, B, c->limits);
-        }
+        const bool here = cap <= TRUNC_SMALL_CAP && !by_count;  // (few keys: released by the search itself)
+        KeyLimit* limits = here ? nullptr : c->limits;
+        trunc_mesh_kernel<Keys><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer_than, guard, c->st, tell, limits);
+        if (!here && !by_count) trunc_release_kernel<Keys><<<grid_for(nv_max), BLOCK, 0, s>>>(K, nv_max, voff, B, c->limits);
     }
     if (longer) {
         SelectSlot* S = c->select_slots;
@@ -623,10 +620,10 @@ int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* 
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }
 int pair_budget(picasso_ctx* c, hipStream_t s, const TieBreak& tb, int B, const int* voff, int nv_max, int most, int least,
-                bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
+                bool by_count, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
     if (tb.on)
-        return budget_step(c, s, PairKeys<true>{c->pcost(), c->ptie(), c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, guarded, tell);
-    return budget_step(c, s, PairKeys<false>{c->pcost(), nullptr, c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, guarded, tell);
+        return budget_step(c, s, PairKeys<true>{c->pcost(), c->ptie(), c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, by_count, guarded, tell);
+    return budget_step(c, s, PairKeys<false>{c->pcost(), nullptr, c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, by_count, guarded, tell);
 }
 
 // Sub-round k of the selection.  last: it lists the edges it leaves live for the tail.
@@ -690,7 +687,7 @@ int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne,
     }
     if (n_list == 0) return PICASSO_OK;
     if (most > 0) {  // the cheapest `left` candidates of each such mesh stay
-        const int rc = budget_step(c, s, JoinKeys{c->abid}, B, c->voff[cur], nv_total, most, least, c->acand, c->arem);
+        const int rc = budget_step(c, s, JoinKeys{c->abid}, B, c->voff[cur], nv_total, most, least, c->acand, c->arem, false);
         if (rc != PICASSO_OK) return rc;
     }
     absorb_keys_kernel<<<grid_for(n_list), BLOCK, 0, s>>>(c->list, c->st, c->ekey, c->ecost, vbits, c->mate, c->abid,
@@ -813,12 +810,19 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // The contraction.  `guarded`: queued behind the selection tail before the host
         // has looked; it then goes by what the tail leaves in State (go, guard_nv) and does
         // nothing unless it finished the matching.  clear: slots of the facet set to clear on the way.
-        auto issue_contract = [&](int n_joined, const u64* akeys, size_t clear, bool guarded, HostSignal tell) {
+        // releases: a budget step has left limits that the count applies.
+        auto issue_contract = [&](int n_joined, const u64* akeys, size_t clear, bool releases, bool guarded, HostSignal tell) {
             const int nxt = cur ^ 1;
             const int* guard = guarded ? &c->st->go : nullptr;
             const int* n_ptr = guarded ? &c->st->guard_nv : nullptr;
             if (n_joined > 0) {
                 prim::compact_count(s, AlivePredT<true>{c->mate, c->arep}, n_ptr, nv_total, c->tilesum);
+            } else if (releases && tb.on) {
+                const ReleasingPred<true> pred{{c->pcost(), c->ptie(), c->mate}, c->voff[cur], B, c->limits};
+                prim::compact_count(s, SignalingPred<ReleasingPred<true>>{pred, tell}, n_ptr, nv_total, c->tilesum);
+            } else if (releases) {
+                const ReleasingPred<false> pred{{c->pcost(), nullptr, c->mate}, c->voff[cur], B, c->limits};
+                prim::compact_count(s, SignalingPred<ReleasingPred<false>>{pred, tell}, n_ptr, nv_total, c->tilesum);
             } else {
                 SignalingPred<AlivePredT<false>> first{{c->mate, nullptr}, tell};  // (`tell.word` may be null: nothing to tell)
                 prim::compact_count(s, first, n_ptr, nv_total, c->tilesum);
@@ -917,10 +921,10 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const HostSignal nothing{nullptr, 0};
             if (ahead_ok) {
                 if (ahead_budget) {
-                    rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_bound, 0, true, tail_done);
+                    rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_bound, 0, true, true, tail_done);
                     if (rc != PICASSO_OK) return rc;
                 }
-                issue_contract(0, nullptr, 0, true, ahead_budget ? nothing : tail_done);
+                issue_contract(0, nullptr, 0, ahead_budget, true, ahead_budget ? nothing : tail_done);
             } else {
                 signal_kernel<<<1, 64, 0, s>>>(tail_done);
             }
@@ -984,8 +988,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             n_sel += h_matched[b];
         }
         if (seg_max > 0 && ahead && !ahead_budget) return PICASSO_ERR_HIP;  // (cannot happen: a matching pairs at most half the vertices)
+        bool releases = false;
         if (seg_max > 0 && !ahead) {
-            rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_max, seg_min);
+            // (line 11 reads the pairs before they are counted)
+            releases = !c->opt_absorb && seg_min <= c->opt_trunc_block_max;
+            rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_max, seg_min, releases);
             if (rc != PICASSO_OK) return rc;
         }
 
@@ -1020,7 +1027,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const bool last = !work || (c->opt_max_rounds >= 0 && round + 1 >= c->opt_max_rounds);
             const size_t clear = last && slots_clear == 0 ? facet_slots((size_t)nf_bound) : 0;
             tm.begin(round, PICASSO_ST_CONTRACT);
-            issue_contract(n_joined, akeys, clear, false, HostSignal{nullptr, 0});
+            issue_contract(n_joined, akeys, clear, releases, false, HostSignal{nullptr, 0});
             tm.end();
             slots_clear = std::max(slots_clear, clear);
         }

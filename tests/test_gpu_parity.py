@@ -703,6 +703,29 @@ def test_every_width_of_the_per_mesh_budget_search(ctx, oracle, w, keys_per_lane
         assert vo.shape[0] == N - keep
 
 
+@pytest.mark.parametrize("flat", ["all", "half", "none"])
+@pytest.mark.parametrize("seed,absorb", [(0, 0), (91, 0), (0, 1), (91, 1)])
+def test_per_mesh_budget_search_of_more_keys_than_it_lists(pk, ctx, oracle, flat, seed, absorb):
+    """28 k pairs where 16 k are listed: a sample of the costs tells which, unless they are all equal, or half of them are and lie together."""
+    V, F = meshgen.noisy_grid(251, 249, seed=6)
+    V = V.copy()
+    if flat == "all":
+        V[:, 2] = 0
+    elif flat == "half":
+        V[: V.shape[0] // 2, 2] = 0
+    ctx.set_option(pk.PICASSO_OPT_SHUFFLE_SEED, seed)
+    ctx.set_option(pk.PICASSO_OPT_ABSORB, absorb)
+    try:
+        n = V.shape[0]
+        for remove in (1, n // 5, n // 3, n * 45 // 100 if absorb else n * 2 // 5):
+            print(f"search flat={flat} seed={seed} absorb={absorb} remove={remove}", flush=True)
+            st, vo, fo, cid = ctx.picasso_decimate(dev(V), dev(F), n - remove)
+            assert_same_result(st, vo, fo, cid, oracle.decimate(V, F, n - remove, shuffle_seed=seed, absorb=bool(absorb)))
+    finally:
+        ctx.set_option(pk.PICASSO_OPT_SHUFFLE_SEED, 0)
+        ctx.set_option(pk.PICASSO_OPT_ABSORB, 0)
+
+
 @pytest.mark.parametrize("batch", [1, 2])
 def test_few_sub_rounds_between_looks_of_the_host(pk, ctx, oracle, batch):
     """With only one or two grid-wide sub-rounds per batch the single-workgroup tail finds more live
