@@ -356,7 +356,7 @@ prim::KeySort<u64> key_sort_for(picasso_ctx* c, bool second_set, long long n, in
     return S;
 }
 inline int count_kind(const prim::KeySort<u64>& S) {
-    return S.digit_bits == prim::BUCKET_MSD_BITS ? COUNT_SMALL : (S.digit_bits == prim::BUCKET_LARGE_MSD_BITS ? COUNT_LARGE : COUNT_XL);
+    return S.digit_bits == prim::BUCKET_MSD_BITS ? COUNT_SMALL : (S.digit_bits <= prim::BUCKET_LARGE_MSD_BITS ? COUNT_LARGE : COUNT_XL);
 }
 inline DigitCount digit_count(const prim::KeySort<u64>& S) {
     return DigitCount{S.hist, S.key_bits - S.digit_bits, (1u << S.digit_bits) - 1u};
@@ -369,7 +369,8 @@ void clear_wide_counts(hipStream_t s, const prim::KeySort<u64>& S) {
 // The sort of the edge keys of a round with nvt vertices and at most nfb facets that have not collapsed, of F.
 prim::KeySort<u64> edge_sort(picasso_ctx* c, int nvt, int nfb, int F) {
     const int H = 3 * nfb, vbits = edge_vertex_bits(nvt, H);
-    prim::KeySort<u64> S = key_sort_for(c, false, H, F, 2 * vbits);
+    // (half-edges are six per vertex, some more on coarse meshes; the facets that are left are not known yet)
+    prim::KeySort<u64> S = key_sort_for(c, false, std::min<long long>(H, 7ll * nvt), F, 2 * vbits);
     rows_of(S, nvt, vbits, H);
     S.zero = c->distinct + c->distinct_cap;  // (the counts per group of buckets)
     S.n_zero = (1 << S.digit_bits) / prim::UNIQUE_GROUP * prim::UNIQUE_PAD;
@@ -1817,6 +1818,7 @@ int picasso_bucket_sort(picasso_ctx* c, void* stream, int key_bytes, void* d_key
         S.n = (int)n;
         S.key_bits = key_bits;
         S.digit_bits = prim::BUCKET_LARGE_MSD_BITS;
+        S.buckets = 1 << S.digit_bits;
         S.hist = c->hist12;
         S.cursor = S.hist + prim::MSD_HIST_WORDS;
         S.starts = S.hist + 2 * prim::MSD_HIST_WORDS;

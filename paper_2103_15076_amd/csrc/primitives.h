@@ -70,9 +70,12 @@ __device__ __forceinline__ SameDigit wave_same_digit(bool ok, u32 d) {
 // Workgroups are dealt out to the 8 XCDs in turn; so that neighbouring tiles of a list share an XCD's L2 (they refer to
 // the same vertices), an XCD takes one eighth of the n items' tiles in a row.  The tile of this workgroup; a workgroup too many gets the
 // number of tiles.  The grid: xcd_grid of the tiles at most.
+__device__ __forceinline__ int xcd_item(int block, int tiles) {
+    const int per = (tiles + 7) >> 3, j = block >> 3;
+    return j < per ? min((block & 7) * per + j, tiles) : tiles;
+}
 __device__ __forceinline__ int xcd_tile(long long n, int tile_items) {
-    const int tiles = (int)((n + tile_items - 1) / tile_items), per = (tiles + 7) >> 3, j = (int)(blockIdx.x >> 3);
-    return j < per ? min((int)(blockIdx.x & 7u) * per + j, tiles) : tiles;
+    return xcd_item((int)blockIdx.x, (int)((n + tile_items - 1) / tile_items));
 }
 inline int xcd_grid(int tiles) { return (tiles + 7) / 8 * 8; }
 
@@ -1080,13 +1083,14 @@ struct Bucket {
 };
 
 template <typename K, typename LK, int THREADS, int ITEMS, class Out>
-__global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int buckets_first, Out out) {
+__global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int blocks_first, Out out) {
     __shared__ BucketLds<LK, THREADS, ITEMS> L;
     __shared__ typename Out::template Lds<THREADS, ITEMS> O;
-    const bool second = (int)blockIdx.x >= buckets_first;
+    const bool second = (int)blockIdx.x >= blocks_first;
     const KeySort<K>& S = second ? second_sort : first_sort;
     Bucket b;
-    b.number = (int)blockIdx.x - (second ? buckets_first : 0);
+    b.number = xcd_item((int)blockIdx.x - (second ? blocks_first : 0), S.buckets);
+    if (b.number >= S.buckets) return;  // (a workgroup too many)
     b.cnt = (int)S.hist[b.number];
     b.start = S.starts[b.number];
     b.low_bits = S.key_bits - S.digit_bits;
@@ -1432,10 +1436,13 @@ inline int bucket_sort_large(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, cons
 // every 8 bits (61 M keys of 48 bits: 6 passes, 2.9 ms; this way 0.5 ms).
 // ---------------------------------------------------------------------------
 constexpr int XL_BITS_MIN = 13, XL_BITS_MAX = 22;
-constexpr long long XL_BUCKET_KEYS = 1024;  // keys per bucket aimed at (vertex ids need not fill their bit range: up to twice that)
+// Keys per bucket aimed at, 1,000 to 2,000 then or, where ids do not fill their bit range, up to twice that: a workgroup's own part (counters, their
+// prefix sums, what is made of the keys) costs as much as 700 keys do (33 M keys of the second round of 10.2 M vertices: 711 to a bucket 230 us,
+// 1,422 to a bucket 140).
+constexpr long long BUCKET_KEYS_AIM = 2048;
 inline int xl_bits_for(long long n) {
     int b = XL_BITS_MIN;
-    while (b < XL_BITS_MAX - 2 && (XL_BUCKET_KEYS << b) < n) ++b;
+    while (b < XL_BITS_MAX - 2 && (BUCKET_KEYS_AIM << b) < n) ++b;
     return b;
 }
 // Up to two bits more where the bits below the digit then fit the 32 that the per-bucket kernel keeps in LDS.
@@ -1455,6 +1462,7 @@ struct XlScratch {
 // Bits of the digit that up to n keys of key_bits bits are partitioned on, and how many bits a key must have for it.
 inline int key_digit_bits(long long n, int key_bits) {
     if (n <= BUCKET_SORT_MAX_KEYS) return BUCKET_MSD_BITS;
+    if (n <= BUCKET_KEYS_AIM << (BUCKET_LARGE_MSD_BITS - 1)) return BUCKET_LARGE_MSD_BITS - 1;
     return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS : xl_digit_bits(n, key_bits);
 }
 // buckets of inputs of up to n_cap keys, at most
@@ -1633,7 +1641,7 @@ inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_
     const KeySort<K> none{};
     const KeySort<K>& b = b_or_null ? *b_or_null : none;
     const int digits_a = 1 << a.digit_bits, digits_b = b_or_null ? 1 << b.digit_bits : 0;
-    const int buckets_a = a.buckets ? a.buckets : digits_a, buckets_b = b.buckets ? b.buckets : digits_b;
+    const int blocks_sort_a = xcd_grid(a.buckets), blocks_sort_b = xcd_grid(b.buckets);
     constexpr int NARROW_ITEMS = Src::PER == 3 ? 1 : SORT_ITEMS_SMALL;
     const bool narrow = a.digit_bits == BUCKET_MSD_BITS;
     auto launch = [&](auto lk) {
@@ -1643,7 +1651,8 @@ inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_
             const int tiles_a = sort_tiles(a.n, NARROW_ITEMS), tiles_b = b_or_null ? sort_tiles(b.n, NARROW_ITEMS) : 0;
             msd_scatter_kernel<K, LK, NARROW_ITEMS, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
         } else {
-            const int blocks_a = digits_a / KEY_SCAN_DIGITS, blocks_b = digits_b / KEY_SCAN_DIGITS;
+            // (arrays of the narrower digits have KEY_SCAN_DIGITS words)
+            const int blocks_a = (digits_a + KEY_SCAN_DIGITS - 1) / KEY_SCAN_DIGITS, blocks_b = (digits_b + KEY_SCAN_DIGITS - 1) / KEY_SCAN_DIGITS;
             key_starts_kernel<K><<<blocks_a + blocks_b, KEY_SCAN_THREADS, 0, s>>>(a, b, blocks_a);
             const int tiles_a = sort_tiles(a.n, xl_items(Src::PER)), tiles_b = b_or_null ? sort_tiles(b.n, xl_items(Src::PER)) : 0;
             xl_scatter_kernel<K, LK, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
@@ -1652,10 +1661,10 @@ inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_
         timed = lt && lt->begin(s, tag);
         if (narrow)
             bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS_256, BUCKET_KEYS_ITEMS_256, Out>
-                <<<buckets_a + buckets_b, BUCKET_KEYS_THREADS_256, 0, s>>>(a, b, buckets_a, out);
+                <<<blocks_sort_a + blocks_sort_b, BUCKET_KEYS_THREADS_256, 0, s>>>(a, b, blocks_sort_a, out);
         else
             bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096, Out>
-                <<<buckets_a + buckets_b, BUCKET_KEYS_THREADS_4096, 0, s>>>(a, b, buckets_a, out);
+                <<<blocks_sort_a + blocks_sort_b, BUCKET_KEYS_THREADS_4096, 0, s>>>(a, b, blocks_sort_a, out);
         if (timed) lt->end(s);
     };
     if constexpr (std::is_same<Out, PlainKeys<K>>::value) launch(K{});
