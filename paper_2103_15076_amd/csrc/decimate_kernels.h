@@ -238,15 +238,21 @@ __device__ __forceinline__ float4 facet_plane(const float* __restrict__ verts, i
     return make_float4(nx, ny, nz, d);
 }
 
-// A single mesh's header (State and the per-mesh tables) written by init_kernel itself instead of
-// a copy from the host in front of it: everything zero except the counts, the mesh's vertex and
-// facet ranges and its target.  State::err is left alone (other workgroups of the same kernel flag
+// The header (State and the per-mesh tables) of up to HEADER_MESHES meshes is written by init_kernel itself instead of
+// a copy from the host in front of it (6 us of a call): everything zero except the counts, the meshes' vertex and
+// facet ranges and their targets, which come with the launch.  State::err is left alone (other workgroups of the same kernel flag
 // errors there): it is zero between calls.  hdr == nullptr: the header has been uploaded.
+constexpr int HEADER_MESHES = 32;
 struct HeaderInit {
     int* hdr;
     int total;                           // ints in the header
     int at_voff0, at_foff, at_target;    // where the tables start
-    int N, F, target;
+};
+struct OneMesh {  // (no tables in the launch: 400 bytes of arguments cost a microsecond in front of the first kernel)
+    int target;
+};
+struct FewMeshes {
+    int voff[HEADER_MESHES + 1], foff[HEADER_MESHES + 1], target[HEADER_MESHES];
 };
 
 // Incidence keys for S0: (vertex << fbits) | facet, one per facet corner, so that sorting the keys
@@ -266,18 +272,18 @@ struct DigitCount {
 // are counted with a single atomic.  clear, count and flush by whole workgroups, with barriers between them.
 template <int COUNT>
 struct DigitTally {
-    static constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::BUCKET_MSD_BITS);
+    static constexpr int RADIX = COUNT == COUNT_LARGE ? (1 << prim::BUCKET_LARGE_MSD_BITS) : (1 << prim::NARROW_BITS_MAX);
     u32 hist[RADIX];
-    __device__ __forceinline__ void clear() {
-        for (int i = threadIdx.x; i < RADIX; i += BLOCK) hist[i] = 0;
+    __device__ __forceinline__ void clear(const DigitCount& D) {
+        for (int i = threadIdx.x; i <= (int)D.mask; i += BLOCK) hist[i] = 0;
     }
     __device__ __forceinline__ void count(const DigitCount& D, bool ok, u64 k) {
-        const u32 d = (u32)(k >> D.shift) & (u32)(RADIX - 1);
+        const u32 d = (u32)(k >> D.shift) & D.mask;
         const prim::SameDigit same = prim::wave_same_digit(ok, d);
         if (ok && same.below == 0) atomicAdd(&hist[d], same.count);
     }
     __device__ __forceinline__ void flush(const DigitCount& D) {
-        for (int i = threadIdx.x; i < RADIX; i += BLOCK) {
+        for (int i = threadIdx.x; i <= (int)D.mask; i += BLOCK) {
             const u32 c = hist[i];
             if (c) atomicAdd(&D.hist[i], c);
         }
@@ -286,7 +292,7 @@ struct DigitTally {
 template <>
 struct DigitTally<COUNT_XL> {
     prim::DigitTable table;
-    __device__ __forceinline__ void clear() { table.clear(); }
+    __device__ __forceinline__ void clear(const DigitCount&) { table.clear(); }
     __device__ __forceinline__ void count(const DigitCount& D, bool ok, u64 k) {
         table.add(D.hist, ok, (u32)(k >> D.shift) & D.mask);
     }
@@ -294,34 +300,42 @@ struct DigitTally<COUNT_XL> {
 };
 template <>
 struct DigitTally<COUNT_NONE> {
-    __device__ __forceinline__ void clear() {}
+    __device__ __forceinline__ void clear(const DigitCount&) {}
     __device__ __forceinline__ void count(const DigitCount&, bool, u64) {}
     __device__ __forceinline__ void flush(const DigitCount&) {}
 };
 
-template <int COUNT>
+template <int COUNT, class Tables>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
                                                      const int* __restrict__ facets, int F, int B,
                                                      const int* __restrict__ voff, const int* __restrict__ foff,
                                                      VRec* __restrict__ vrec, int* __restrict__ cid,
                                                      int* __restrict__ fcur, int fbits, DigitCount inc, DigitCount edge,
-                                                     int edges, int vbits, State* st, HeaderInit init,
+                                                     int edges, int vbits, State* st, HeaderInit init, Tables tables,
                                                      float4* __restrict__ planes, int* __restrict__ htab, int n_clear,
                                                      u64* __restrict__ vmin0, u64* __restrict__ vmin1,
                                                      int* __restrict__ mate, u32* __restrict__ pcost, RoundTab R) {
     __shared__ DigitTally<COUNT> corners, sides;
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
-    const bool single = init.hdr != nullptr;  // one mesh, whose ranges are [0, N) and [0, F): the tables are not read here
-    if (single && blockIdx.x == 0) {
+    constexpr bool ONE = std::is_same<Tables, OneMesh>::value;
+    const bool here = init.hdr != nullptr;  // (the tables in memory are then not to be read: this kernel writes them)
+    if (here && blockIdx.x == 0) {
         constexpr int ERR = (int)(offsetof(State, err) / sizeof(int));
         constexpr int NV0 = (int)(offsetof(State, nv) / sizeof(int));
         for (int i = threadIdx.x; i < init.total; i += BLOCK) {
             if (i == ERR) continue;
             int v = 0;
-            if (i == NV0 || i == init.at_voff0 + 1) v = init.N;
-            else if (i == init.at_foff + 1) v = init.F;
-            else if (i == init.at_target) v = init.target;
+            if constexpr (ONE) {
+                if (i == NV0 || i == init.at_voff0 + 1) v = N;
+                else if (i == init.at_foff + 1) v = F;
+                else if (i == init.at_target) v = tables.target;
+            } else {
+                if (i == NV0) v = N;
+                else if (i >= init.at_voff0 && i <= init.at_voff0 + B) v = tables.voff[i - init.at_voff0];
+                else if (i >= init.at_foff && i <= init.at_foff + B) v = tables.foff[i - init.at_foff];
+                else if (i >= init.at_target && i < init.at_target + B) v = tables.target[i - init.at_target];
+            }
             init.hdr[i] = v;
         }
     }
@@ -330,8 +344,8 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         round_begin_block(R, st);
     }
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
-    corners.clear();
-    sides.clear();
+    corners.clear(inc);
+    sides.clear(edge);
     __syncthreads();
     int err = 0;
     for (int w = g; w < N; w += stride) {
@@ -356,8 +370,12 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         const bool ok = f < F;
         int lo = 0, hi = 0;
         if (ok) {
-            if (single) {
+            if constexpr (ONE) {
                 hi = N;
+            } else if (here) {
+                const int m = mesh_of(tables.foff, B, f);
+                lo = tables.voff[m];
+                hi = tables.voff[m + 1];
             } else {
                 const int m = mesh_of(foff, B, f);
                 lo = voff[m];
@@ -389,8 +407,8 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
             corners.flush(inc);
             sides.flush(edge);
             __syncthreads();
-            corners.clear();
-            sides.clear();
+            corners.clear(inc);
+            sides.clear(edge);
             __syncthreads();
         }
     }
@@ -425,7 +443,7 @@ template <int COUNT>
 __global__ __launch_bounds__(BLOCK) void csr_count_kernel(RowKeys src, int n, DigitCount rows, int* __restrict__ err) {
     constexpr int ITEMS = COUNT == COUNT_LARGE ? 16 : CSR_COUNT_ITEMS;
     __shared__ DigitTally<COUNT> digits;
-    digits.clear();
+    digits.clear(rows);
     __syncthreads();
     bool bad = false;
     int row[ITEMS];
@@ -633,7 +651,7 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
         pcost[w] = ~0u;
     }
     if (blockIdx.x == 0) round_begin_block(R, st);
-    sides.clear();
+    sides.clear(edge);
     __syncthreads();
     for (long long base = (long long)blockIdx.x * (BLOCK * FACETS); base < F; base += (long long)stride * FACETS) {
         Corners q[FACETS];
@@ -670,7 +688,7 @@ __global__ __launch_bounds__(BLOCK) void edge_keys_kernel(int* __restrict__ fcur
             __syncthreads();
             sides.flush(edge);
             __syncthreads();
-            sides.clear();
+            sides.clear(edge);
             __syncthreads();
         }
     }

@@ -356,7 +356,7 @@ prim::KeySort<u64> key_sort_for(picasso_ctx* c, bool second_set, long long n, in
     return S;
 }
 inline int count_kind(const prim::KeySort<u64>& S) {
-    return S.digit_bits == prim::BUCKET_MSD_BITS ? COUNT_SMALL : (S.digit_bits <= prim::BUCKET_LARGE_MSD_BITS ? COUNT_LARGE : COUNT_XL);
+    return S.digit_bits <= prim::NARROW_BITS_MAX ? COUNT_SMALL : (S.digit_bits <= prim::BUCKET_LARGE_MSD_BITS ? COUNT_LARGE : COUNT_XL);
 }
 inline DigitCount digit_count(const prim::KeySort<u64>& S) {
     return DigitCount{S.hist, S.key_bits - S.digit_bits, (1u << S.digit_bits) - 1u};
@@ -474,7 +474,7 @@ constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 // The validating kernel, instantiated for the sorts its keys go to.  work: rounds (or S0) follow; edges: the first round's
 // set-up and edges as well.
 int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, const int32_t* d_facets, int F, int B,
-                bool work, bool edges, HeaderInit init = HeaderInit{nullptr, 0, 0, 0, 0, 0, 0, 0}) {
+                bool work, bool edges, const HeaderInit& init = HeaderInit{}, const FewMeshes& tables = FewMeshes{}) {
     const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F);
     if (work && c->hist_dirty)  // (a call ended between a count of its edges and their sort)
         prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, 2 * prim::MSD_HIST_WORDS, 0u);
@@ -486,21 +486,27 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     float4* planes = work ? facet_planes(c) : nullptr;
     // the facet set that the end of the call uses (larger ones are cleared by the last contraction, when fewer facets are left)
     const int n_clear = F <= CLEAR_AHEAD_MAX_FACETS ? (int)facet_slots((size_t)F) : 0;
-#define PICASSO_INIT(COUNT)                                                                                                    \
+#define PICASSO_INIT_TABLES(COUNT, TABLES)                                                                                     \
     init_kernel<COUNT><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
-        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, incidence_fbits(F), digit_count(I),   \
-        digit_count(E), edges ? 1 : 0, E.key_bits / 2, c->st, init, planes, c->htab, n_clear, c->vmin[0], c->vmin[1], c->mate, \
-        c->pcost(), round_tab(c, B, 0, 0))
+        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, incidence_fbits(F), digit_count(I),      \
+        digit_count(E), edges ? 1 : 0, E.key_bits / 2, c->st, init, TABLES, planes, c->htab, n_clear, c->vmin[0], c->vmin[1],   \
+        c->mate, c->pcost(), round_tab(c, B, 0, 0))
+#define PICASSO_INIT(COUNT)                                             \
+    do {                                                                \
+        if (B == 1) PICASSO_INIT_TABLES(COUNT, OneMesh{tables.target[0]}); \
+        else PICASSO_INIT_TABLES(COUNT, tables);                        \
+    } while (0)
     if (!work) PICASSO_INIT(COUNT_NONE);
     else if (count_kind(I) == COUNT_SMALL) PICASSO_INIT(COUNT_SMALL);
     else if (count_kind(I) == COUNT_LARGE) PICASSO_INIT(COUNT_LARGE);
     else PICASSO_INIT(COUNT_XL);
 #undef PICASSO_INIT
+#undef PICASSO_INIT_TABLES
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }
 
 // Fills the pinned image of the header (State + per-mesh tables) and sends it with one copy.
-// `by_kernel`: only the checks; the first kernel writes the header itself (a single mesh, see HeaderInit).
+// `by_kernel`: only the image; the first kernel writes the header itself (few meshes, see HeaderInit).
 int upload_header(picasso_ctx* c, hipStream_t s, int B, const int32_t* nv_in, const int32_t* nf_in,
                   const int32_t* target, int64_t* N_out, int64_t* F_out, bool by_kernel = false) {
     const int cb = c->cap_b;
@@ -713,15 +719,24 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     if (stats) memset(stats, 0, sizeof(*stats));
 
     int64_t N64 = 0, F64 = 0;
-    const bool header_by_kernel = B == 1;  // one mesh: no copy in front of the first kernel
+    const bool header_by_kernel = B <= HEADER_MESHES;  // few meshes: no copy in front of the first kernel
     int rc = upload_header(c, s, B, nv_in, nf_in, target_nv, &N64, &F64, header_by_kernel);
     if (rc != PICASSO_OK) return rc;
     if (F64 > 0 && !d_facets) return PICASSO_ERR_INVALID_ARG;
     const int N = (int)N64, F = (int)F64;
-    HeaderInit hinit{nullptr, 0, 0, 0, 0, 0, 0, 0};
-    if (header_by_kernel)
-        hinit = HeaderInit{c->hdr, (int)hdr_ints((size_t)c->cap_b), (int)(c->voff[0] - c->hdr), (int)(c->foff - c->hdr),
-                           (int)(c->target - c->hdr), N, F, target_nv[0]};
+    HeaderInit hinit{};
+    FewMeshes tables{};
+    if (header_by_kernel) {
+        hinit.hdr = c->hdr;
+        hinit.total = (int)hdr_ints((size_t)c->cap_b);
+        hinit.at_voff0 = (int)(c->voff[0] - c->hdr);
+        hinit.at_foff = (int)(c->foff - c->hdr);
+        hinit.at_target = (int)(c->target - c->hdr);
+        const int* img = c->h_pin + c->h_up_off;
+        memcpy(tables.voff, img + hinit.at_voff0, sizeof(int) * (B + 1));
+        memcpy(tables.foff, img + hinit.at_foff, sizeof(int) * (B + 1));
+        memcpy(tables.target, img + hinit.at_target, sizeof(int) * B);
+    }
 
     c->n_ev = 0;
     c->kt.pool = c->kt_pool;
@@ -767,7 +782,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     const bool together = work && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
                           edge_sort(c, N, F, F).half == incidence_sort(c, N, F).half;
     tm.begin(0, PICASSO_ST_QUADRICS);
-    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, work, hinit);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, work, hinit, tables);
     if (rc != PICASSO_OK) return rc;
     if (work) {
         const prim::KeySort<u64> I = incidence_sort(c, N, F);
@@ -851,8 +866,9 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // meshes pairs 85-95 % of them) and the per-mesh search can take every such mesh, the budget step
         // is queued there too, in front of it: it finds on the device which meshes are over their
         // budgets, and does nothing where none is.  In between (40-50 %) nothing is queued ahead.
-        // (Larger rounds take long enough for the idling not to count, and then know which contraction is the last.)
-        constexpr int AHEAD_MAX_FACETS = 1 << 20;
+        // (Rounds larger still take long enough for the idling not to count, and then know which contraction is the last, which clears
+        // the facet set on its way.)
+        constexpr int AHEAD_MAX_FACETS = 1 << 22;
         bool ahead_ok = !c->opt_absorb && !stats && c->opt_ahead && nf_bound <= AHEAD_MAX_FACETS;
         bool ahead_budget = false;
         int seg_bound = 0;  // pairs of the largest mesh that may exceed its budget, at most

@@ -400,9 +400,8 @@ constexpr int BUCKET_THREADS_4096 = 512;  // 4096 buckets: up to 4096 keys (8 pe
                                           // pairs (16 per lane: vertex incidences run to ~6 per vertex and
                                           // vertex ids need not fill their bit range, so those buckets run fuller)
 // keys without values (bucket_keys_kernel): lanes and keys per lane of a bucket's workgroup
-constexpr int BUCKET_KEYS_THREADS_256 = 512, BUCKET_KEYS_ITEMS_256 = 16;   // 256 buckets: up to 8192 keys in LDS
-constexpr int BUCKET_KEYS_THREADS_4096 = 256, BUCKET_KEYS_ITEMS_4096 = 16;  // 4096 buckets: up to 4096 keys in LDS
-constexpr int BUCKET_MSD_BITS = 8;
+constexpr int BUCKET_KEYS_THREADS = 256, BUCKET_KEYS_ITEMS = 16;  // up to 4096 keys in LDS
+constexpr int BUCKET_MSD_BITS = 8, NARROW_BITS_MAX = 10;  // (bits of a narrow digit: 8 to 10)
 constexpr long long BUCKET_SORT_MAX_KEYS = 1ll << 20;  // average bucket <= half of what LDS holds
 
 template <int NW>
@@ -1255,7 +1254,7 @@ struct TwoSources {
 };
 
 // Partition of keys WITHOUT values by their top 8-bit digit in one pass.
-// hist[d] = number of keys with digit d over the whole input (so digit d owns the output range
+// Digits of 8 to 10 bits, 2^(BITS - 8) of them to a thread.  hist[d] = number of keys with digit d over the whole input (so digit d owns the output range
 // that starts at the sum of the counts before it; the first tile also writes these first
 // positions to `starts`); cursor[d] = how much of that range is taken, zero at the start.  Every tile counts its keys per digit in LDS, takes its share of each
 // digit's range with one returning atomic per digit it holds, and writes its keys there.  The
@@ -1263,10 +1262,10 @@ struct TwoSources {
 // for sorts that then order each range on the whole key; with equal keys indistinguishable the
 // final result does not depend on it.  The lanes of a wave whose keys share a digit (keys led by
 // mesh indices bring few distinct digits into a wave) rank themselves with one LDS atomic.
-template <typename K, typename LK, int ITEMS, class Src>
+template <typename K, typename LK, int BITS, int ITEMS, class Src>
 __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int tiles_first, Src src) {
-    constexpr int R = 1 << BUCKET_MSD_BITS, PER = Src::PER, KEYS = ITEMS * PER;
-    static_assert(R == BLOCK, "one digit per thread");
+    constexpr int R = 1 << BITS, DIGITS = R / BLOCK, PER = Src::PER, KEYS = ITEMS * PER;
+    static_assert(DIGITS * BLOCK == R, "whole digits per thread");
     constexpr int TILE = BLOCK * ITEMS;
     __shared__ u32 h[R];  // per digit: this tile's count, then where the tile's keys of that digit go
     __shared__ u32 smem[WAVES];
@@ -1283,13 +1282,25 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sor
     typename Src::Raw raw[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) raw[i] = src.load(min(base + i * 64, n - 1));
-    h[t] = 0;
-    u32 tot;
-    const u32 first = block_exclusive_scan(S.hist[t], smem, tot);  // first position of digit t's range
-    if (tile == 0) {
-        S.starts[t] = first;  // for the kernel that sorts the ranges
-        if (S.total && t == 0) *S.total = (int)tot;
+    u32 first[DIGITS], sum = 0, tot;  // first position of the ranges of the digits DIGITS * t ..
+#pragma unroll
+    for (int j = 0; j < DIGITS; ++j) {
+        first[j] = S.hist[DIGITS * t + j];
+        h[DIGITS * t + j] = 0;
     }
+#pragma unroll
+    for (int j = 0; j < DIGITS; ++j) {
+        const u32 c = first[j];
+        first[j] = sum;
+        sum += c;
+    }
+    const u32 in_front = block_exclusive_scan(sum, smem, tot);
+#pragma unroll
+    for (int j = 0; j < DIGITS; ++j) {
+        first[j] += in_front;
+        if (tile == 0) S.starts[DIGITS * t + j] = first[j];  // for the kernel that sorts the ranges
+    }
+    if (tile == 0 && S.total && t == 0) *S.total = (int)tot;
     K key[KEYS];
     u32 rk[KEYS];
     bool has[KEYS];
@@ -1307,8 +1318,15 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sor
         rk[i] = (u32)__shfl((int)b, same.lead, 64) + same.below;
     }
     __syncthreads();
-    const u32 c = h[t];
-    if (c) h[t] = first + atomicAdd(&S.cursor[t], c);
+    u32 c[DIGITS];
+#pragma unroll
+    for (int j = 0; j < DIGITS; ++j) {
+        c[j] = h[DIGITS * t + j];
+        if (c[j]) first[j] += atomicAdd(&S.cursor[DIGITS * t + j], c[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < DIGITS; ++j)
+        if (c[j]) h[DIGITS * t + j] = first[j];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < KEYS; ++i) {
@@ -1440,6 +1458,10 @@ constexpr int XL_BITS_MIN = 13, XL_BITS_MAX = 22;
 // prefix sums, what is made of the keys) costs as much as 700 keys do (33 M keys of the second round of 10.2 M vertices: 711 to a bucket 230 us,
 // 1,422 to a bucket 140).
 constexpr long long BUCKET_KEYS_AIM = 2048;
+// Below 2^20 keys the chip also has to be filled: a bucket's keys by one workgroup of 256 lanes, edge and incidence keys of the first round with
+// 8 bits and workgroups of 512 / 9 / 10 bits: 682 k keys 13.3 / 12.7 / 15.3 us, 920 k 22.9 / - / 16.3, 368 k 11.5 / 12.1 / -, the second round's
+// 147 k 9.4 / 10.0 / -.
+constexpr long long NARROW_8_BITS_MAX_KEYS = 1 << 16, NARROW_9_BITS_MAX_KEYS = 3 << 18;
 inline int xl_bits_for(long long n) {
     int b = XL_BITS_MIN;
     while (b < XL_BITS_MAX - 2 && (BUCKET_KEYS_AIM << b) < n) ++b;
@@ -1461,7 +1483,7 @@ struct XlScratch {
 
 // Bits of the digit that up to n keys of key_bits bits are partitioned on, and how many bits a key must have for it.
 inline int key_digit_bits(long long n, int key_bits) {
-    if (n <= BUCKET_SORT_MAX_KEYS) return BUCKET_MSD_BITS;
+    if (n <= BUCKET_SORT_MAX_KEYS) return n <= NARROW_8_BITS_MAX_KEYS ? 8 : (n <= NARROW_9_BITS_MAX_KEYS ? 9 : 10);
     if (n <= BUCKET_KEYS_AIM << (BUCKET_LARGE_MSD_BITS - 1)) return BUCKET_LARGE_MSD_BITS - 1;
     return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS : xl_digit_bits(n, key_bits);
 }
@@ -1471,7 +1493,7 @@ inline size_t bucket_capacity(long long n_cap) {
     return n_cap <= BUCKET_SORT_LARGE_MAX_KEYS ? narrow : xl_hist_words(n_cap);
 }
 inline int key_bits_wanted(long long n) {
-    if (n <= BUCKET_SORT_MAX_KEYS) return BUCKET_MSD_BITS + 2;
+    if (n <= BUCKET_SORT_MAX_KEYS) return NARROW_BITS_MAX + 2;
     return n <= BUCKET_SORT_LARGE_MAX_KEYS ? BUCKET_LARGE_MSD_BITS + 2 : XL_BITS_MAX + 2;
 }
 
@@ -1643,13 +1665,15 @@ inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_
     const int digits_a = 1 << a.digit_bits, digits_b = b_or_null ? 1 << b.digit_bits : 0;
     const int blocks_sort_a = xcd_grid(a.buckets), blocks_sort_b = xcd_grid(b.buckets);
     constexpr int NARROW_ITEMS = Src::PER == 3 ? 1 : SORT_ITEMS_SMALL;
-    const bool narrow = a.digit_bits == BUCKET_MSD_BITS;
+    const bool narrow = a.digit_bits <= NARROW_BITS_MAX;
     auto launch = [&](auto lk) {
         using LK = decltype(lk);
         bool timed = lt && part_tag >= 0 && lt->begin(s, part_tag);
         if (narrow) {
             const int tiles_a = sort_tiles(a.n, NARROW_ITEMS), tiles_b = b_or_null ? sort_tiles(b.n, NARROW_ITEMS) : 0;
-            msd_scatter_kernel<K, LK, NARROW_ITEMS, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
+            if (a.digit_bits == 8) msd_scatter_kernel<K, LK, 8, NARROW_ITEMS, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
+            else if (a.digit_bits == 9) msd_scatter_kernel<K, LK, 9, NARROW_ITEMS, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
+            else msd_scatter_kernel<K, LK, 10, NARROW_ITEMS, Src><<<tiles_a + tiles_b, BLOCK, 0, s>>>(a, b, tiles_a, src);
         } else {
             // (arrays of the narrower digits have KEY_SCAN_DIGITS words)
             const int blocks_a = (digits_a + KEY_SCAN_DIGITS - 1) / KEY_SCAN_DIGITS, blocks_b = (digits_b + KEY_SCAN_DIGITS - 1) / KEY_SCAN_DIGITS;
@@ -1659,12 +1683,8 @@ inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_
         }
         if (timed) lt->end(s);
         timed = lt && lt->begin(s, tag);
-        if (narrow)
-            bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS_256, BUCKET_KEYS_ITEMS_256, Out>
-                <<<blocks_sort_a + blocks_sort_b, BUCKET_KEYS_THREADS_256, 0, s>>>(a, b, blocks_sort_a, out);
-        else
-            bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS_4096, BUCKET_KEYS_ITEMS_4096, Out>
-                <<<blocks_sort_a + blocks_sort_b, BUCKET_KEYS_THREADS_4096, 0, s>>>(a, b, blocks_sort_a, out);
+        bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS, BUCKET_KEYS_ITEMS, Out>
+            <<<blocks_sort_a + blocks_sort_b, BUCKET_KEYS_THREADS, 0, s>>>(a, b, blocks_sort_a, out);
         if (timed) lt->end(s);
     };
     if constexpr (std::is_same<Out, PlainKeys<K>>::value) launch(K{});
@@ -1678,9 +1698,9 @@ template <typename K>
 inline bool key_sort_array(hipStream_t s, const KeySort<K>& a) {
     const int low = a.key_bits - a.digit_bits, buckets = 1 << a.digit_bits;
     fill_u32_kernel<<<(buckets + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(a.hist, buckets, 0u);
-    if (a.digit_bits == BUCKET_MSD_BITS) {
+    if (a.digit_bits <= NARROW_BITS_MAX) {
         fill_u32_kernel<<<(buckets + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(a.cursor, buckets, 0u);
-        msd_histogram_kernel<K, BUCKET_MSD_BITS, SORT_ITEMS_SMALL><<<sort_tiles(a.n, SORT_ITEMS_SMALL), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, a.hist, low);
+        msd_histogram_kernel<K, NARROW_BITS_MAX, SORT_ITEMS_SMALL><<<sort_tiles(a.n, SORT_ITEMS_SMALL), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, a.hist, low);
     } else if (a.digit_bits == BUCKET_LARGE_MSD_BITS) {
         msd_histogram_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG><<<sort_tiles(a.n, SORT_ITEMS_BIG), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, a.hist, low);
     } else {
