@@ -1067,19 +1067,6 @@ struct PairTally {
     }
 };
 
-// The same into an LDS array (one workgroup's own tally).
-__device__ __forceinline__ void count_pairs_lds(int* pairs, bool sel, int m) {
-    const int lane = prim::lane_id();
-    u64 sb = prim::ballot(sel);
-    while (sb) {
-        const int leader = __ffsll((long long)sb) - 1;
-        const int m0 = __shfl(m, leader, 64);
-        const u64 same = prim::ballot(sel && m == m0);
-        if (lane == leader) atomicAdd(&pairs[m0], (int)__popcll(same));
-        sb &= ~same;
-    }
-}
-
 // The lanes' live edges appended to their workgroup's segment of the tail's list.  By all lanes of a wave.
 __device__ __forceinline__ void append_live(const SelArgs& A, bool alive, u64 key, u32 cost, int e) {
     const u64 b = prim::ballot(alive);
@@ -1090,6 +1077,35 @@ __device__ __forceinline__ void append_live(const SelArgs& A, bool alive, u64 ke
     at = __shfl(at, first, 64) + (int)__popcll(b & prim::lanemask_lt());
     if (alive && at < A.live_cap) A.live[(size_t)seg * A.live_cap + at] = LiveEdge{key, cost, e};
 }
+
+// The same for the small rounds: one mesh's pairs put together in LDS, a batch's counted in memory by one atomic per wave and mesh; the
+// meshes' first vertices are fetched beforehand, as the search among them is a chain of loads.
+constexpr int TALLY_MESHES = 64;
+struct SmallTally {
+    int pairs, voff[TALLY_MESHES + 1];
+    // by the workgroup, in front of a barrier
+    __device__ __forceinline__ void begin(const SelArgs& A) {
+        const int t = threadIdx.x;
+        if (t == 0) pairs = 0;
+        if (A.mt.B > 1 && A.mt.B <= TALLY_MESHES && t <= A.mt.B) voff[t] = A.mt.voff[t];
+    }
+    // by all lanes of a wave; u = an end of the pair
+    __device__ __forceinline__ void count(const SelArgs& A, bool sel, int u) {
+        const u64 mine = prim::ballot(sel);
+        if (mine == 0) return;
+        if (A.mt.B == 1) {
+            if (prim::lane_id() == 0) atomicAdd(&pairs, (int)__popcll(mine));
+        } else {
+            int m = 0;
+            if (sel) m = A.mt.B <= TALLY_MESHES ? mesh_of(voff, A.mt.B, u) : mesh_of(A.mt.voff, A.mt.B, u);
+            count_pairs(A, sel, m);
+        }
+    }
+    // by one thread, behind a barrier
+    __device__ __forceinline__ void end(const SelArgs& A) const {
+        if (pairs) atomicAdd(&A.mt.mslots[(size_t)(blockIdx.x & (MATCH_SLOTS - 1)) * MATCH_PAD], pairs);
+    }
+};
 
 // Grid-wide sub-round over ALL edges of a round of less than LISTED_MIN_EDGES; retired edges are skipped by
 // their state byte.  The last one before the tail (APPEND), which leaves a few thousand edges live, lists them for it.
@@ -1102,7 +1118,7 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
     u64* __restrict__ nxt = A.vmin[(k + 1) % 3];
     u64* __restrict__ rst = A.vmin[(k + 2) % 3];
     __shared__ BidTable<SUBROUND_LINES> bids;
-    __shared__ PairTally tally;
+    __shared__ SmallTally tally;
     const int i = (int)blockIdx.x * BLOCK + (int)threadIdx.x, at = min(i, A.bound - 1);  // (the grid covers the bound)
     const u64 key = A.ekey[at];  // (not yet known to be an edge: the loads do not wait for one another)
     const u32 cost = A.ecost[at];
@@ -1111,7 +1127,7 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
     if (i == 0) A.st->sel_k = k + 1;
     if ((int)blockIdx.x * BLOCK >= n) return;
     bids.clear();
-    if (threadIdx.x == 0) tally.begin(A, (long long)blockIdx.x * BLOCK, n);
+    tally.begin(A);
     JudgedEdge<SHUFFLE> E[1];
     E[0].key = key;
     E[0].cost = cost;
@@ -1323,14 +1339,15 @@ __global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, 
 // most 2 x TAIL_MAX) vertices they touch to LDS slots, and one 64-bit bid per
 // slot.  A sub-round then costs three workgroup barriers instead of a kernel
 // launch and several trips to memory, and none once one wave holds the edges that are left.  The live count falls in every
-// sub-round (the best live edge is always accepted), so the loop ends.  A slot whose vertex has been paired gives up its
-// vertex number (TAIL_PAIRED): nothing else needs it then.
+// sub-round (the best live edge is always accepted), so the loop ends.  The bid of a slot whose vertex has been paired is TAIL_PAIRED from then on;
+// a batch's pairs are listed and counted by mesh at the end (mesh by mesh in the loop it took 16 meshes up to 2 us more per sub-round).
 // (With six barriers, the list gathered by a launch of its own, and the loads of the end not started at the beginning:
 // 14-19 us of every round, now 10-16.  What is left is about 2 us per sub-round: the trips to LDS and the issue of 16 waves.
 // Edges in registers instead of lists, and stores to memory kept out of the loop, measured the same.)
 constexpr int TAIL_SLOTS = 8192;  // power of two, >= 2 * TAIL_MAX
 constexpr int TAIL_LDS_MESHES = 1024;
-constexpr int TAIL_FREE = -1, TAIL_PAIRED = -2;
+constexpr int TAIL_FREE = -1;
+constexpr u64 TAIL_PAIRED = 0;  // (less than any bid)
 
 struct TailLds {
     u64 prio[TAIL_MAX];
@@ -1341,6 +1358,8 @@ struct TailLds {
     int cnt[3];                  // live edges of the sub-round, of the next, of the one after that, in turn
     int seg_at[LIVE_SEGS + 1];   // first place of each segment's edges
     int pairs[TAIL_LDS_MESHES];  // pairs this kernel formed, per mesh (batches of up to this many meshes)
+    int n_pairs;
+    unsigned short pair_slot[TAIL_MAX / 2];  // an end of each
 };
 
 __device__ __forceinline__ int tail_slot(int* vkey, int v) {
@@ -1403,7 +1422,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         if (lane == 0) L.seg_at[0] = 0;
         if (lane == LIVE_SEGS - 1) L.cnt[0] = full ? max(incl, TAIL_MAX + 1) : incl;
     }
-    if (tid == 0) L.cnt[1] = 0;
+    if (tid == 0) L.cnt[1] = L.n_pairs = 0;
     for (int h = tid; h < TAIL_SLOTS / 4; h += TAIL_THREADS)
         reinterpret_cast<int4*>(L.vkey)[h] = make_int4(TAIL_FREE, TAIL_FREE, TAIL_FREE, TAIL_FREE);
     // Up to TAIL_LDS_MESHES meshes, the pairs formed here are tallied in LDS and added to the earlier
@@ -1442,23 +1461,26 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     __syncthreads();
 
     // an edge that holds the best bid at both ends is accepted
-    auto accept = [&](int i, u64 p, bool& sel, int& m) {
+    auto accept = [&](int i, u64 p, bool& sel, int& u) {
         const int su = L.su[i], sv = L.sv[i];
         sel = L.bid[su] == p && L.bid[sv] == p;
         if (sel) {
-            const int u = L.vkey[su], v = L.vkey[sv];
+            u = L.vkey[su];
+            const int v = L.vkey[sv];
             A.mate[u] = v;
             A.mate[v] = u;
             A.pcost[min(u, v)] = (u32)(p >> 32);
             if (A.tb.on) A.ptie[min(u, v)] = (u32)p;
-            m = mesh_of(A.mt.voff, A.mt.B, u);
-            L.vkey[su] = TAIL_PAIRED;
-            L.vkey[sv] = TAIL_PAIRED;
+            L.bid[su] = TAIL_PAIRED;  // (any other edge's bid differs from both values)
+            L.bid[sv] = TAIL_PAIRED;
+            if (A.mt.B > 1 && lds_pairs) L.pair_slot[atomicAdd(&L.n_pairs, 1)] = (unsigned short)su;
         }
     };
-    auto tally = [&](bool sel, int m) {
-        if (lds_pairs) count_pairs_lds(L.pairs, sel, m);
-        else count_pairs(A, sel, m);
+    int wave_pairs = 0;  // (one mesh)
+    // by all lanes of a wave (very many meshes: counted in memory)
+    auto tally = [&](bool sel, int u) {
+        if (A.mt.B == 1) wave_pairs += (int)__popcll(prim::ballot(sel));
+        else if (!lds_pairs) count_pairs(A, sel, sel ? mesh_of(A.mt.voff, A.mt.B, u) : 0);
     };
     int side = 0, now = 0;  // cnt[now] = live edges, in lst[side]
     while (n > 64) {
@@ -1474,12 +1496,12 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         __syncthreads();
         for (int j = tid; j < padded; j += TAIL_THREADS) {
             bool sel = false;
-            int m = 0;
+            int u = 0;
             if (j < n) {
                 const int i = L.lst[side][j];
-                accept(i, L.prio[i], sel, m);
+                accept(i, L.prio[i], sel, u);
             }
-            tally(sel, m);
+            tally(sel, u);
         }
         __syncthreads();
         // keep the edges whose ends are both still free, and clear those ends' bids
@@ -1489,7 +1511,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
             if (j < n) {
                 i = L.lst[side][j];
                 const int su = L.su[i], sv = L.sv[i];
-                alive = L.vkey[su] != TAIL_PAIRED && L.vkey[sv] != TAIL_PAIRED;
+                alive = L.bid[su] != TAIL_PAIRED && L.bid[sv] != TAIL_PAIRED;
                 if (alive) L.bid[su] = L.bid[sv] = VMIN_NONE;
             }
             const u64 ab = prim::ballot(alive);
@@ -1518,12 +1540,12 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             __builtin_amdgcn_wave_barrier();
             bool sel = false;
-            int m = 0;
-            if (alive) accept(i, p, sel, m);
-            tally(sel, m);
+            int u = 0;
+            if (alive) accept(i, p, sel, u);
+            tally(sel, u);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             __builtin_amdgcn_wave_barrier();
-            alive = alive && L.vkey[su] != TAIL_PAIRED && L.vkey[sv] != TAIL_PAIRED;
+            alive = alive && L.bid[su] != TAIL_PAIRED && L.bid[sv] != TAIL_PAIRED;
             if (alive) L.bid[su] = L.bid[sv] = VMIN_NONE;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             __builtin_amdgcn_wave_barrier();
@@ -1533,10 +1555,14 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
 
     static_assert(MATCH_SLOTS == 32, "a mesh's slots fill half a wave");
     constexpr int STATE_INTS = (int)(sizeof(State) / sizeof(int));
-    if (!lds_pairs) {
+    if (A.mt.B == 1) {
+        if (lane == 0 && wave_pairs) atomicAdd(&L.pairs[0], wave_pairs);
+    } else if (lds_pairs) {
+        for (int i = tid; i < L.n_pairs; i += TAIL_THREADS) atomicAdd(&L.pairs[mesh_of(A.mt.voff, A.mt.B, L.vkey[L.pair_slot[i]])], 1);
+    } else {
         __threadfence();  // the pair counts added above are at the L2 before they are summed
-        __syncthreads();
     }
+    __syncthreads();
     // one lane per counter slot (a mesh's MATCH_SLOTS slots sit in neighbouring lanes), so that the
     // loads are in flight together; whole waves run each step for the shuffles
     for (int base = 0; base < A.mt.B * MATCH_SLOTS; base += TAIL_THREADS) {
