@@ -2471,6 +2471,18 @@ __device__ __forceinline__ u32 facet_home(int x, u32 hx, float slots_per_vertex)
     return (u32)at + (hx & ((1u << FACET_HOME_WINDOW_BITS) - 1u));
 }
 
+// A slot of the table: the facet's index in its low `fbits` bits (all ones are no facet's index), bits of its triple's hash above: facets
+// whose bits differ have different triples, so that a search passes the slots of others without a look at their corners (a facet and three
+// gathers, one after the other, for every fourth facet), and among equal triples the smaller word is the smaller index.
+__host__ __device__ __forceinline__ int facet_index_bits(int F) {
+    int bits = 1;
+    while (bits < 31 && (1ll << bits) - 1 < (long long)F) ++bits;
+    return bits;
+}
+constexpr u32 FACET_SLOT_FREE = ~0u;
+__device__ __forceinline__ u32 facet_slot_word(u32 hx, int f, int fbits) { return (hx >> fbits << fbits) | (u32)f; }
+__device__ __forceinline__ u32 facet_slot_index(u32 word, int fbits) { return word & ((1u << fbits) - 1u); }
+
 // Re-indexes every facet through vmap (null: they are up to date) and enters the
 // ones of contracted meshes that have not collapsed into an open-
 // addressing table keyed by the unordered vertex triple.  A slot stores a
@@ -2479,11 +2491,16 @@ __device__ __forceinline__ u32 facet_home(int x, u32 hx, float slots_per_vertex)
 // survivor does not depend on the order in which lanes arrive.  The table has been cleared to -1.  Once per call: what of
 // equal facets remains is the first of them, in whichever round they became equal.
 // The output vertices' positions and the final labels go out on the way.
+//
+// Bound by the table: 27 lines of 64 bytes per nanosecond for its atomics, and the trips of a search, one after the other.  20 M facets
+// (6.7 M left of them): 305 us, 390 without the bits of the hash in the slots and with a branch around the gathers of vmap; 2.4 M: 43 -> 36;
+// 226 k: 13.6 -> 10.5.  Several facets, or a facet and a vertex, per lane and turn take longer (445-500 us): the parts' lines push each
+// other out of the L2.
 constexpr int FSLOT_KEEP = -1, FSLOT_DROP = -2;
 
 __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restrict__ fcur, int F, int* __restrict__ fmap,
                                                              const int* __restrict__ vmap, const State* st, int cur,
-                                                             int* __restrict__ htab, u32 hmask, int B,
+                                                             u32* __restrict__ htab, u32 hmask, int fbits, int B,
                                                              const int* __restrict__ voff, const int* __restrict__ done,
                                                              int* __restrict__ fslot, const int* cid_in, int* cid_out,
                                                              int n_orig, const VRec* __restrict__ vrec,
@@ -2492,49 +2509,41 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     const int nv = st->nv[cur];
     const float slots_per_vertex = ((float)hmask + 1.0f) / (float)(nv > 0 ? nv : 1);
-    auto corners_of = [&](int f) -> Corners {
-        const Corners q = load_corners(fcur, (size_t)f);
-        return vmap && q.a >= 0 ? Corners{vmap[q.a], vmap[q.b], vmap[q.c]} : q;
+    auto renumbered = [&](const Corners& q) -> Corners {  // (a collapsed facet's corners are -1)
+        if (!vmap) return q;
+        const Corners m{vmap[max(q.a, 0)], vmap[max(q.b, 0)], vmap[max(q.c, 0)]};
+        return q.a >= 0 ? m : q;
     };
-    for (int f = g; f < F; f += stride) {
-        const Corners q = corners_of(f);
-        // fslot[f]: the table slot that decides about the facet (it survives iff the slot ends up
-        // holding f), or FSLOT_KEEP / FSLOT_DROP where no slot is involved
-        if (q.a < 0) {
-            fslot[f] = FSLOT_DROP;
-            continue;
-        }
+    // fslot[f]: the table slot that decides about the facet (it survives iff the slot ends up
+    // holding f), or FSLOT_KEEP / FSLOT_DROP where no slot is involved
+    auto enter = [&](int f, Corners q) -> int {
+        if (q.a < 0) return FSLOT_DROP;
         fmap[3 * (size_t)f] = q.a;
         fmap[3 * (size_t)f + 1] = q.b;
         fmap[3 * (size_t)f + 2] = q.c;
-        if (!done[mesh_of(voff, B, q.a)]) {  // the mesh took part in no round: facets kept as they are
-            fslot[f] = FSLOT_KEEP;
-            continue;
-        }
-        if (q.a == q.b || q.b == q.c || q.a == q.c) {
-            fslot[f] = FSLOT_DROP;
-            continue;
-        }
-        int x = q.a, y = q.b, z = q.c;
-        sort3(x, y, z);
-        const u32 hx = hash3(x, y, z);
-        u32 h = facet_home(x, hx, slots_per_vertex) & hmask;
+        if (!done[mesh_of(voff, B, q.a)]) return FSLOT_KEEP;  // the mesh took part in no round: facets kept as they are
+        if (q.a == q.b || q.b == q.c || q.a == q.c) return FSLOT_DROP;
+        sort3(q.a, q.b, q.c);
+        const u32 hx = hash3(q.a, q.b, q.c), mine = facet_slot_word(hx, f, fbits);
+        u32 h = facet_home(q.a, hx, slots_per_vertex) & hmask;
         for (int probe = 1;; ++probe) {
-            const int old = atomicCAS(&htab[h], -1, f);
-            if (old == -1) break;
-            if (old == f) break;
-            Corners o = corners_of(old);
-            sort3(o.a, o.b, o.c);
-            if (o.a == x && o.b == y && o.c == z) {
-                atomicMin(&htab[h], f);
-                break;
+            const u32 old = atomicCAS(&htab[h], FACET_SLOT_FREE, mine);
+            if (old == FACET_SLOT_FREE) break;
+            if ((old ^ mine) >> fbits == 0) {
+                Corners o = renumbered(load_corners(fcur, facet_slot_index(old, fbits)));
+                sort3(o.a, o.b, o.c);
+                if (o.a == q.a && o.b == q.b && o.c == q.c) {
+                    atomicMin(&htab[h], mine);
+                    break;
+                }
             }
             // a few steps along the line, then (a crowded stretch: a vertex with very many facets) on from
             // a place that the whole triple decides
             h = (probe == FACET_HOME_PROBES ? hx : h + 1u) & hmask;
         }
-        fslot[f] = (int)h;
-    }
+        return (int)h;
+    };
+    for (int f = g; f < F; f += stride) fslot[f] = enter(f, renumbered(load_corners(fcur, (size_t)f)));
     for (int o = g; o < n_orig; o += stride) {
         const int c = cid_in[o];
         cid_out[o] = vmap ? vmap[c] : c;
@@ -2552,11 +2561,12 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
 // final_facets_kernel left for it holds the smallest facet index of the triple).
 struct FacetKeepPred {
     const int* fslot;
-    const int* htab;
+    const u32* htab;
+    int fbits;
     unsigned char* keep;
     __device__ bool operator()(int f) const {
         const int h = fslot[f];
-        const bool k = h >= 0 ? htab[h] == f : h == FSLOT_KEEP;
+        const bool k = h >= 0 ? facet_slot_index(htab[h], fbits) == (u32)f : h == FSLOT_KEEP;
         keep[f] = k ? 1 : 0;
         return k;
     }

@@ -1066,14 +1066,16 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     if (round > 0 && slots_clear < slots)  // (rounds ended without the contraction that was to be the last)
         prim::fill_u32_kernel<<<grid_for((long long)slots), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->htab), (int)slots, ~0u);
     const bool drop = c->opt_drop_degenerated != 0;
+    u32* const htab = reinterpret_cast<u32*>(c->htab);
+    const int fbits = facet_index_bits(F);
     tm.begin(std::max(round - 1, 0), PICASSO_ST_FACETS);
     {
         const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round - 1, renumbered);
         final_facets_kernel<<<grid_for(std::max(N, F), 8192), BLOCK, 0, s>>>(
-            c->fcur, F, c->fmap, renumbered ? c->vmap : nullptr, c->st, cur, c->htab, (u32)(slots - 1), B, c->voff[cur], c->done,
+            c->fcur, F, c->fmap, renumbered ? c->vmap : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur], c->done,
             c->fslot, c->cid, drop ? c->cid : d_cluster_id, N, c->vrec[cur], drop ? nullptr : d_verts_out);
     }
-    const FacetKeepPred kp{c->fslot, c->htab, c->keep};
+    const FacetKeepPred kp{c->fslot, htab, fbits, c->keep};
     const FlagPred fp{c->keep};
     const FacetOut fo{c->fmap, drop ? c->fcur : d_facets_out, c->foff, B, c->foff_out};
     if (F > 0) prim::compact(s, kp, fp, fo, nullptr, F, c->tilesum, &c->st->nf);

@@ -186,6 +186,21 @@ def test_quadrics_and_edges_of_facet_soups(ctx, oracle, n, f):
     assert np.array_equal(cost.cpu().numpy().view(np.uint32), cr.view(np.uint32))
 
 
+@pytest.mark.parametrize("n,f", [(12, 1), (12, 2), (12, 3), (40, 255), (40, 256), (300, 4_095), (300, 4_096), (9_000, 65_535), (9_000, 65_537)])
+def test_repeated_facets_of_any_number(ctx, oracle, n, f):
+    """The first of equal facets stays, in whichever order they name the corners; a third have one vertex in common.
+    The final facets' table keeps a facet's index in as many bits as their number takes."""
+    rng = np.random.default_rng(n + f)
+    V = rng.standard_normal((n, 3)).astype(np.float32)
+    F = rng.integers(0, n, size=(max(f // 2, 1), 3)).astype(np.int32)
+    F[::3, 1] = 0
+    again = rng.integers(0, F.shape[0], size=f - F.shape[0])
+    F = np.concatenate([F, rng.permuted(F[again], axis=1)])[rng.permutation(f)]
+    print(f"repeated N={n} F={f}", flush=True)
+    st, vo, fo, cid = ctx.picasso_decimate(dev(V), dev(F), n - max(n // 6, 1))
+    assert_same_result(st, vo, fo, cid, oracle.decimate(V, F, n - max(n // 6, 1)))
+
+
 @pytest.mark.parametrize("n", [1 << 20, (1 << 20) + 1, 1_250_000])
 def test_few_facets_among_very_many_vertices(ctx, oracle, n):
     """Beyond 2^20 vertices the bits of an edge key below an 8-bit digit do not fit 32 bits."""
