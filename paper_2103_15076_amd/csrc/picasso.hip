@@ -831,7 +831,9 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const int nxt = cur ^ 1;
             const int* guard = guarded ? &c->st->go : nullptr;
             const int* n_ptr = guarded ? &c->st->guard_nv : nullptr;
-            if (n_joined > 0) {
+            const bool counts = n_joined == 0 && !releases && nv_total <= CONTRACT_COUNTS_MAX;
+            if (counts) {
+            } else if (n_joined > 0) {
                 prim::compact_count(s, AlivePredT<true>{c->mate, c->arep}, n_ptr, nv_total, c->tilesum);
             } else if (releases && tb.on) {
                 const ReleasingPred<true> pred{{c->pcost(), c->ptie(), c->mate}, c->voff[cur], B, c->limits};
@@ -845,17 +847,20 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             }
             const int chunks = prim::compact_chunks_for(nv_total), tiles = prim::compact_tiles(nv_total, chunks);
             const int prefixed = tiles > prim::COMPACT_MAX_SUMMED_TILES;
-#define PICASSO_CONTRACT(PLACE, ABSORB, RCOND)                                                                       \
-    contract_kernel<PLACE, ABSORB><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, c->vmap, c->st, cur,  \
+            static_assert(CONTRACT_COUNTS_MAX <= BLOCK * prim::COMPACT_MAX_SUMMED_TILES, "tiles of one chunk");
+#define PICASSO_CONTRACT(PLACE, ABSORB, COUNTS, RCOND)                                                               \
+    contract_kernel<PLACE, ABSORB, COUNTS><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, c->vmap, c->st, cur,  \
                                                            chunks, c->tilesum, prefixed, B, c->voff[cur],             \
                                                            c->voff[nxt], c->active, c->done, c->htab, (int)clear,     \
-                                                           RCOND, c->arep, c->acnt, akeys, vbits, guard)
+                                                           RCOND, c->arep, c->acnt, akeys, vbits, guard, tell)
             if (c->opt_placement == PLACE_INVERSE) {
-                if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, c->opt_rcond_min);
-                else PICASSO_CONTRACT(PLACE_INVERSE, false, c->opt_rcond_min);
+                if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, false, c->opt_rcond_min);
+                else if (counts) PICASSO_CONTRACT(PLACE_INVERSE, false, true, c->opt_rcond_min);
+                else PICASSO_CONTRACT(PLACE_INVERSE, false, false, c->opt_rcond_min);
             } else {
-                if (n_joined > 0) PICASSO_CONTRACT(PLACE_MEAN, true, 0.0f);
-                else PICASSO_CONTRACT(PLACE_MEAN, false, 0.0f);
+                if (n_joined > 0) PICASSO_CONTRACT(PLACE_MEAN, true, false, 0.0f);
+                else if (counts) PICASSO_CONTRACT(PLACE_MEAN, false, true, 0.0f);
+                else PICASSO_CONTRACT(PLACE_MEAN, false, false, 0.0f);
             }
 #undef PICASSO_CONTRACT
         };

@@ -793,6 +793,31 @@ def test_listed_sub_rounds_of_a_batch_with_meshes_that_rest(ctx, oracle):
     assert_same_result(st, vo, fo, cid, ref)
 
 
+@pytest.mark.parametrize("sizes", [[(16, 16)], [(2, 129)], [(127, 129)], [(128, 128)], [(5, 3277)],
+                                   [(100, 81), (3, 3), (16, 16), (7, 1143), (2, 2)], [(100, 81), (3, 3), (16, 16), (7, 1145), (2, 2)]])
+def test_contraction_that_counts_for_itself(pk, ctx, oracle, sizes):
+    """Up to 16,384 vertices (of a round) no count pass runs in front of the contraction."""
+    parts = [meshgen.noisy_grid(w, h, seed=w) for w, h in sizes]
+    nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
+    base = np.concatenate([[0], np.cumsum(nv)])
+    V, F = np.concatenate([p[0] for p in parts]), np.concatenate([p[1] + np.int32(b) for p, b in zip(parts, base)])
+    print(f"counts for itself {sum(nv)}", flush=True)
+    for part in (0.55, 0.2):  # one round that its budget binds a little; several
+        target = [max(int(n * part), 1) for n in nv]
+        st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
+        ref = oracle.decimate_batch(V, F, nv, nf, target)
+        assert list(nvo) == list(ref["nv"]) and list(nfo) == list(ref["nf"])
+        assert_same_result(st, vo, fo, cid, ref)
+    if len(parts) > 1:
+        return
+    ctx.set_placement(pk.PICASSO_PLACE_INVERSE, 1e-3)
+    try:
+        st, vo, fo, cid = ctx.picasso_decimate(dev(V), dev(F), target[0])
+        assert_same_result(st, vo, fo, cid, oracle.decimate(V, F, target[0], placement=1, rcond_min=1e-3))
+    finally:
+        ctx.set_placement(pk.PICASSO_PLACE_MEAN)
+
+
 def test_statistics_and_timing_options_do_not_change_the_result(pk, ctx, oracle):
     """The per-round statistics agree with the oracle's bookkeeping; stage events and the kernel's
     launch events are measurement only."""
