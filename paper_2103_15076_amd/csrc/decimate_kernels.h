@@ -2507,20 +2507,38 @@ __device__ __forceinline__ u32 facet_slot_index(u32 word, int fbits) { return wo
 // The output vertices' positions and the final labels go out on the way.
 //
 // Bound by the table: 27 lines of 64 bytes per nanosecond for its atomics, and the trips of a search, one after the other.  20 M facets
-// (6.7 M left of them): 305 us, 390 without the bits of the hash in the slots and with a branch around the gathers of vmap; 2.4 M: 43 -> 36;
-// 226 k: 13.6 -> 10.5.  Several facets, or a facet and a vertex, per lane and turn take longer (445-500 us): the parts' lines push each
-// other out of the L2.
-constexpr int FSLOT_KEEP = -1, FSLOT_DROP = -2;
+// (6.7 M left of them): 287 us, 390 without the bits of the hash in the slots, with a branch around the gathers of vmap and an entry
+// written per facet; 2.4 M: 43 -> 37; 226 k: 13.6 -> 10.2.  Several facets, or a facet and a vertex, per lane and turn take longer
+// (445-500 us): the parts' lines push each other out of the L2.
+//
+// The facets that may remain are listed: a wave takes segments of 64 * SEG facets and leaves what it enters of each, in order, at
+// the segment's start (FacetList), so that the two kernels behind this one read those alone, densely.  (With an entry per facet, dead
+// or not, those two took 209 us of 20 M facets and 29 of 2.4 M, now 96 and 21.)  Longer segments are denser but make fewer waves:
+// 2.4 M facets took 64, 59 and 59 us in all three kernels with segments of 64, 128 and 256 facets; of 20 M, 256 leave 4 for each wave.
+// Tiles of 256 facets up to 2^19 of them, 1,024 beyond: a tile adds up the sums of all in front of it (1.9 M facets in 7,365 tiles: 23 us
+// for the last kernel, 10 in 1,842).
+constexpr int FSLOT_KEEP = -1;  // no slot decides about the facet: it stays
+constexpr int facet_segment(int chunks) { return chunks == 1 ? 1 : chunks == 4 ? 2 : 4; }
+inline int facet_chunks_for(int F) { return F <= 1 << 19 ? 1 : std::max(4, prim::compact_chunks_for(F)); }
+struct FacetList {
+    int* corners;          // the facet's corners,
+    int* slot;             // the table slot that decides about it (it survives iff the slot ends up holding it) or FSLOT_KEEP,
+    int* facet;            // the facet,
+    unsigned char* keep;   // whether it survives;
+    int* n;                // per segment: its entries
+    int* wave_n;           // per wave of the two kernels' tiles: its survivors
+};
 
-__global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restrict__ fcur, int F, int* __restrict__ fmap,
+template <int SEG>
+__global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restrict__ fcur, int F, FacetList L,
                                                              const int* __restrict__ vmap, const State* st, int cur,
                                                              u32* __restrict__ htab, u32 hmask, int fbits, int B,
                                                              const int* __restrict__ voff, const int* __restrict__ done,
-                                                             int* __restrict__ fslot, const int* cid_in, int* cid_out,
+                                                             const int* cid_in, int* cid_out,
                                                              int n_orig, const VRec* __restrict__ vrec,
                                                              float* __restrict__ verts_out /* or null */) {
     const int stride = gridDim.x * BLOCK;
-    const int g = blockIdx.x * BLOCK + threadIdx.x;
+    const int g = blockIdx.x * BLOCK + threadIdx.x, lane = prim::lane_id();
     const int nv = st->nv[cur];
     const float slots_per_vertex = ((float)hmask + 1.0f) / (float)(nv > 0 ? nv : 1);
     auto renumbered = [&](const Corners& q) -> Corners {  // (a collapsed facet's corners are -1)
@@ -2528,15 +2546,11 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
         const Corners m{vmap[max(q.a, 0)], vmap[max(q.b, 0)], vmap[max(q.c, 0)]};
         return q.a >= 0 ? m : q;
     };
-    // fslot[f]: the table slot that decides about the facet (it survives iff the slot ends up
-    // holding f), or FSLOT_KEEP / FSLOT_DROP where no slot is involved
-    auto enter = [&](int f, Corners q) -> int {
-        if (q.a < 0) return FSLOT_DROP;
-        fmap[3 * (size_t)f] = q.a;
-        fmap[3 * (size_t)f + 1] = q.b;
-        fmap[3 * (size_t)f + 2] = q.c;
-        if (!done[mesh_of(voff, B, q.a)]) return FSLOT_KEEP;  // the mesh took part in no round: facets kept as they are
-        if (q.a == q.b || q.b == q.c || q.a == q.c) return FSLOT_DROP;
+    auto enter = [&](int f, Corners q, int& slot) -> bool {
+        if (q.a < 0) return false;
+        slot = FSLOT_KEEP;
+        if (!done[mesh_of(voff, B, q.a)]) return true;  // the mesh took part in no round: facets kept as they are
+        if (q.a == q.b || q.b == q.c || q.a == q.c) return false;
         sort3(q.a, q.b, q.c);
         const u32 hx = hash3(q.a, q.b, q.c), mine = facet_slot_word(hx, f, fbits);
         u32 h = facet_home(q.a, hx, slots_per_vertex) & hmask;
@@ -2555,9 +2569,31 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
             // a place that the whole triple decides
             h = (probe == FACET_HOME_PROBES ? hx : h + 1u) & hmask;
         }
-        return (int)h;
+        slot = (int)h;
+        return true;
     };
-    for (int f = g; f < F; f += stride) fslot[f] = enter(f, renumbered(load_corners(fcur, (size_t)f)));
+    const int wave = __builtin_amdgcn_readfirstlane(g >> 6);
+    for (long long s0 = (long long)wave * (64 * SEG); s0 < F; s0 += (long long)stride * SEG) {
+        int n = 0;
+        for (int c = 0; c < SEG; ++c) {
+            const long long f = s0 + c * 64 + lane;
+            Corners q{-1, -1, -1};
+            if (f < F) q = renumbered(load_corners(fcur, (size_t)f));
+            int slot = 0;
+            const bool in = enter((int)f, q, slot);
+            const u64 all = prim::ballot(in);
+            if (in) {
+                const size_t p = (size_t)s0 + n + prim::mask_below(all);
+                L.corners[3 * p] = q.a;
+                L.corners[3 * p + 1] = q.b;
+                L.corners[3 * p + 2] = q.c;
+                L.slot[p] = slot;
+                L.facet[p] = (int)f;
+            }
+            n += (int)__popcll(all);
+        }
+        if (lane == 0) L.n[s0 / (64 * SEG)] = n;
+    }
     for (int o = g; o < n_orig; o += stride) {
         const int c = cid_in[o];
         cid_out[o] = vmap ? vmap[c] : c;
@@ -2571,42 +2607,95 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
         }
 }
 
-// keep[f] = 1 iff the facet survives: not collapsed and the first of its triple (the slot that
-// final_facets_kernel left for it holds the smallest facet index of the triple).
-struct FacetKeepPred {
-    const int* fslot;
-    const u32* htab;
-    int fbits;
-    unsigned char* keep;
-    __device__ bool operator()(int f) const {
-        const int h = fslot[f];
-        const bool k = h >= 0 ? facet_slot_index(htab[h], fbits) == (u32)f : h == FSLOT_KEEP;
-        keep[f] = k ? 1 : 0;
-        return k;
+// The survivors among the listed facets, counted per tile of BLOCK * CHUNKS facets (as a compaction's count pass does) and wave of it:
+// a facet survives if it is the first of its triple, the one that its slot holds.
+template <int CHUNKS>
+__global__ __launch_bounds__(BLOCK) void count_facets_kernel(FacetList L, int F, const u32* __restrict__ htab, int fbits,
+                                                             int* __restrict__ tilesum) {
+    constexpr int SEG = facet_segment(CHUNKS), SEGS = CHUNKS / SEG, SPAN = 64 * SEG;
+    __shared__ u32 smem[prim::WAVES];
+    const int w = prim::wave_id(), lane = prim::lane_id();
+    const long long at = (long long)blockIdx.x * (BLOCK * CHUNKS) + (long long)w * (64 * CHUNKS);
+    int n[SEGS];
+#pragma unroll
+    for (int j = 0; j < SEGS; ++j) n[j] = at + j * SPAN < F ? L.n[at / SPAN + j] : 0;
+    u32 kept = 0;
+#pragma unroll
+    for (int j = 0; j < SEGS; ++j)
+        for (int i0 = 0; i0 < SPAN && (i0 == 0 || i0 < n[j]); i0 += 64) {  // (the first entries are asked for together with their number)
+            const long long p = min(at + j * SPAN + i0 + lane, (long long)F - 1);
+            const int h = L.slot[p], f = L.facet[p];
+            bool k = false;
+            if (i0 + lane < n[j]) {
+                k = h == FSLOT_KEEP || facet_slot_index(htab[max(h, 0)], fbits) == (u32)f;
+                L.keep[p] = k ? 1 : 0;
+            }
+            kept += (u32)__popcll(prim::ballot(k));
+        }
+    if (lane == 0) {
+        smem[w] = kept;
+        L.wave_n[blockIdx.x * prim::WAVES + w] = (int)kept;
     }
-};
+    __syncthreads();
+    if (threadIdx.x == 0) tilesum[blockIdx.x] = (int)(smem[0] + smem[1] + smem[2] + smem[3]);
+}
 
-struct FlagPred {
-    const unsigned char* keep;
-    __device__ bool operator()(int f) const { return keep[f] != 0; }
-};
-
-// The surviving facets, in order; foff_out[b] = those in front of mesh b (whose facets came at foff[b] ...).
-struct FacetOut {
-    static constexpr bool WAVE_WIDE = true;
-    const int* fmap;
-    int* out;
-    const int* foff;
-    int B;
-    int* foff_out;
-    __device__ void wave(int f, bool, bool flagged, int pos) const {
-        flagged_before(foff, B, f - prim::lane_id(), (u32)pos + (flagged ? 1u : 0u), foff_out);
-        if (!flagged) return;
-        out[3 * (size_t)pos] = fmap[3 * (size_t)f];
-        out[3 * (size_t)pos + 1] = fmap[3 * (size_t)f + 1];
-        out[3 * (size_t)pos + 2] = fmap[3 * (size_t)f + 2];
+// ... and written out, in order.  foff_out[b] = those in front of mesh b, whose facets came at foff[b] ...
+template <int CHUNKS>
+__global__ __launch_bounds__(BLOCK) void facets_out_kernel(FacetList L, int F, const int* __restrict__ tilesum, int prefixed,
+                                                           const int* __restrict__ foff, int B, int* __restrict__ out,
+                                                           int* __restrict__ foff_out, int* __restrict__ nf_out) {
+    constexpr int SEG = facet_segment(CHUNKS), SEGS = CHUNKS / SEG, SPAN = 64 * SEG;
+    __shared__ u32 smem[prim::WAVES];
+    const int t = threadIdx.x, w = prim::wave_id(), lane = prim::lane_id(), tile = blockIdx.x;
+    const long long at = (long long)tile * (BLOCK * CHUNKS) + (long long)w * (64 * CHUNKS);
+    int n[SEGS];
+#pragma unroll
+    for (int j = 0; j < SEGS; ++j) n[j] = at + j * SPAN < F ? L.n[at / SPAN + j] : 0;
+    const int4 waves = reinterpret_cast<const int4*>(L.wave_n)[tile];
+    u32 run;
+    if (prefixed) {
+        run = (u32)tilesum[tile];
+    } else {
+        u32 part = 0;
+        for (int j = t; j < tile; j += BLOCK) part += (u32)tilesum[j];
+        run = prim::block_sum(part, smem);
     }
-};
+    if (tile == (int)gridDim.x - 1 && t == 0) *nf_out = (int)run + ((waves.x + waves.y) + (waves.z + waves.w));
+    run += (u32)((w > 0 ? waves.x : 0) + (w > 1 ? waves.y : 0) + (w > 2 ? waves.z : 0));
+#pragma unroll
+    for (int j = 0; j < SEGS; ++j) {
+        const long long s0 = at + j * SPAN;
+        if (s0 >= F) break;
+        for (int b0 = 0; b0 <= B; b0 += 64) {  // meshes that start in the segment
+            const int p = b0 + lane <= B ? foff[b0 + lane] : -1;
+            u64 here = prim::ballot((p > s0 && p <= s0 + SPAN) || (p == 0 && s0 == 0));
+            for (; here; here &= here - 1) {
+                const int b = __ffsll((long long)here) - 1, end = __shfl(p, b, 64);
+                u32 front = run;
+                for (int i0 = 0; i0 < n[j]; i0 += 64) {
+                    const bool in = i0 + lane < n[j];
+                    front += (u32)__popcll(prim::ballot(in && L.keep[s0 + i0 + lane] != 0 && L.facet[s0 + i0 + lane] < end));
+                }
+                if (lane == 0) foff_out[b0 + b] = (int)front;
+            }
+        }
+        for (int i0 = 0; i0 < SPAN && (i0 == 0 || i0 < n[j]); i0 += 64) {
+            const long long p = min(s0 + i0 + lane, (long long)F - 1);
+            const unsigned char flag = L.keep[p];
+            const Corners q = load_corners(L.corners, (size_t)p);
+            const bool kept = i0 + lane < n[j] && flag != 0;
+            const u64 all = prim::ballot(kept);
+            if (kept) {
+                const size_t o = 3 * ((size_t)run + prim::mask_below(all));
+                out[o] = q.a;
+                out[o + 1] = q.b;
+                out[o + 2] = q.c;
+            }
+            run += (u32)__popcll(all);
+        }
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Results

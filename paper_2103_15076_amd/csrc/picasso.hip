@@ -1072,18 +1072,40 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         prim::fill_u32_kernel<<<grid_for((long long)slots), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->htab), (int)slots, ~0u);
     const bool drop = c->opt_drop_degenerated != 0;
     u32* const htab = reinterpret_cast<u32*>(c->htab);
-    const int fbits = facet_index_bits(F);
+    const int fbits = facet_index_bits(F), chunks = facet_chunks_for(F);
+    // (the sorts' first buffer is free: 6 ints a facet, and at least 64; 1.1 a facet and up to 11 more are taken)
+    int* const spare = reinterpret_cast<int*>(c->key64[0]);
+    const size_t wave_at = ((size_t)F + 3) / 4 * 4, n_at = wave_at + prim::WAVES * (size_t)prim::compact_tiles(std::max(F, 1), chunks);
+    const FacetList fl{c->fmap, c->fslot, spare, c->keep, spare + n_at, spare + wave_at};
     tm.begin(std::max(round - 1, 0), PICASSO_ST_FACETS);
     {
         const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round - 1, renumbered);
-        final_facets_kernel<<<grid_for(std::max(N, F), 8192), BLOCK, 0, s>>>(
-            c->fcur, F, c->fmap, renumbered ? c->vmap : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur], c->done,
-            c->fslot, c->cid, drop ? c->cid : d_cluster_id, N, c->vrec[cur], drop ? nullptr : d_verts_out);
+#define PICASSO_FINAL_FACETS(SEG)                                                                                       \
+    final_facets_kernel<SEG><<<grid_for(std::max(N, F), 8192), BLOCK, 0, s>>>(                                          \
+        c->fcur, F, fl, renumbered ? c->vmap : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur],     \
+        c->done, c->cid, drop ? c->cid : d_cluster_id, N, c->vrec[cur], drop ? nullptr : d_verts_out)
+        switch (facet_segment(chunks)) {
+            case 1: PICASSO_FINAL_FACETS(1); break;
+            case 2: PICASSO_FINAL_FACETS(2); break;
+            default: PICASSO_FINAL_FACETS(4);
+        }
+#undef PICASSO_FINAL_FACETS
     }
-    const FacetKeepPred kp{c->fslot, htab, fbits, c->keep};
-    const FlagPred fp{c->keep};
-    const FacetOut fo{c->fmap, drop ? c->fcur : d_facets_out, c->foff, B, c->foff_out};
-    if (F > 0) prim::compact(s, kp, fp, fo, nullptr, F, c->tilesum, &c->st->nf);
+    if (F > 0) {
+        const int tiles = prim::compact_tiles(F, chunks);
+        int* const out = drop ? c->fcur : d_facets_out;
+#define PICASSO_FACETS_OUT(CHUNKS)                                                                                      \
+    count_facets_kernel<CHUNKS><<<tiles, BLOCK, 0, s>>>(fl, F, htab, fbits, c->tilesum);                                \
+    prim::compact_scan_sums(s, nullptr, F, c->tilesum);                                                                 \
+    facets_out_kernel<CHUNKS><<<tiles, BLOCK, 0, s>>>(fl, F, c->tilesum, tiles > prim::COMPACT_MAX_SUMMED_TILES,        \
+                                                      c->foff, B, out, c->foff_out, &c->st->nf)
+        switch (chunks) {
+            case 1: PICASSO_FACETS_OUT(1); break;
+            case 4: PICASSO_FACETS_OUT(4); break;
+            default: PICASSO_FACETS_OUT(16);
+        }
+#undef PICASSO_FACETS_OUT
+    }
     tm.end();
     if (drop) {
         // output vertices that no output facet refers to are dropped: mark, number the others, copy out

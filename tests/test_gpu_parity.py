@@ -793,6 +793,27 @@ def test_listed_sub_rounds_of_a_batch_with_meshes_that_rest(ctx, oracle):
     assert_same_result(st, vo, fo, cid, ref)
 
 
+@pytest.mark.parametrize("w,h", [(511, 512), (514, 515), (2_055, 2_053)])
+def test_facets_of_a_batch_go_out_from_lists(pk, oracle, w, h):
+    """Final facets are listed in segments of 64 to 256, by their number; meshes start within segments, some have no facets left."""
+    parts = [meshgen.noisy_grid(a, b, seed=a) for a, b in ((5, 4), (30, 41), (w, h), (2, 2), (3, 2), (71, 50), (2, 3))]
+    nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
+    base = np.concatenate([[0], np.cumsum(nv)])
+    V, F = np.concatenate([p[0] for p in parts]), np.concatenate([p[1] + np.int32(b) for p, b in zip(parts, base)])
+    target = [2, nv[1] // 3, nv[2], 1, 2, nv[5] // 2, nv[6]]  # the large one rests
+    if w < 1000:
+        target[2] = nv[2] // 2
+    print(f"lists {sum(nf)}", flush=True)
+    ctx = pk.Context(V.shape[0], F.shape[0], len(parts), device=0)
+    try:
+        st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
+    finally:
+        ctx.close()
+    ref = oracle.decimate_batch(V, F, nv, nf, target)
+    assert list(nvo) == list(ref["nv"]) and list(nfo) == list(ref["nf"])
+    assert_same_result(st, vo, fo, cid, ref)
+
+
 @pytest.mark.parametrize("sizes", [[(16, 16)], [(2, 129)], [(127, 129)], [(128, 128)], [(5, 3277)],
                                    [(100, 81), (3, 3), (16, 16), (7, 1143), (2, 2)], [(100, 81), (3, 3), (16, 16), (7, 1145), (2, 2)]])
 def test_contraction_that_counts_for_itself(pk, ctx, oracle, sizes):
