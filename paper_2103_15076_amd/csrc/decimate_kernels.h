@@ -615,7 +615,7 @@ struct QuadricRows {
 //
 // First kernel of every round but the first (whose part init_kernel takes): the round's set-up (block 0), the per-vertex selection state, and the digits of the
 // 64-bit keys (lower vertex, higher vertex), one per half-edge: the kernel adds the keys' top digits (8 bits with
-// COUNT_SMALL, 12 with COUNT_LARGE, as xl_mask says with COUNT_XL) to the histogram that the sort of the keys starts from
+// COUNT_SMALL, 12 with COUNT_LARGE, as xl_digit_bits says with COUNT_XL) to the histogram that the sort of the keys starts from
 // (zeroed beforehand); the sort makes the keys again from the facets, so they are not written.
 //
 // The round before has contracted pairs and the facets still name its vertices: they are taken to
@@ -1340,9 +1340,9 @@ __global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, 
 // slot.  A sub-round then costs three workgroup barriers instead of a kernel
 // launch and several trips to memory, and none once one wave holds the edges that are left.  The live count falls in every
 // sub-round (the best live edge is always accepted), so the loop ends.  The bid of a slot whose vertex has been paired is TAIL_PAIRED from then on;
-// a batch's pairs are listed and counted by mesh at the end (mesh by mesh in the loop it took 16 meshes up to 2 us more per sub-round).
+// a batch's pairs are listed and counted by mesh at the end (mesh by mesh in the loop the tails of 16 meshes took 13-22 us, now 9-15).
 // (With six barriers, the list gathered by a launch of its own, and the loads of the end not started at the beginning:
-// 14-19 us of every round, now 10-16.  What is left is about 2 us per sub-round: the trips to LDS and the issue of 16 waves.
+// 14-19 us of every round of one mesh, now 9-16.  What is left is about 2 us per sub-round: the trips to LDS and the issue of 16 waves.
 // Edges in registers instead of lists, and stores to memory kept out of the loop, measured the same.)
 constexpr int TAIL_SLOTS = 8192;  // power of two, >= 2 * TAIL_MAX
 constexpr int TAIL_LDS_MESHES = 1024;

@@ -1340,7 +1340,6 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sor
 // Words of a sort's count array, of its cursors and of its first positions, for digits of up to 12 bits.
 constexpr int MSD_HIST_WORDS = 4096;
 inline int bucket_sort_msd_bits(int key_bits) { return key_bits < BUCKET_MSD_BITS ? key_bits : BUCKET_MSD_BITS; }
-inline int bucket_sort_low_bits(int key_bits) { return key_bits - bucket_sort_msd_bits(key_bits); }
 
 __global__ __launch_bounds__(BLOCK) void fill_u32_kernel(u32* __restrict__ p, int n, u32 v) {
     const int i = blockIdx.x * BLOCK + threadIdx.x;
