@@ -883,7 +883,7 @@ __global__ __launch_bounds__(BLOCK) void unique_cost_kernel(EdgeList E, u64* __r
         const bool act = mt.active[mesh_of(mt.voff, mt.B, u)] != 0;
         ekey[e] = k;
         ecost[e] = ck;
-        estate[e] = act ? 0 : 1;
+        if (estate) estate[e] = act ? 0 : 1;
         if (act) {
             bids.put(vmin0, nullptr, u, edge_bid<SHUFFLE>(tb, ck, e, v));
             bids.put(vmin0, nullptr, v, edge_bid<SHUFFLE>(tb, ck, e, u));
@@ -945,7 +945,8 @@ struct SelArgs {
     LiveEdge* live;         // the edges that the last grid-wide sub-round leaves live, for the tail: LIVE_SEGS segments of
     int live_cap;           // ... live_cap places each,
     int* live_n;            // ... filled up to live_n[segment * MATCH_PAD] (or fuller than full)
-    unsigned char* estate;  // per edge: 0 = live, 1 = retired (paired, or an end was paired); in listed rounds only before sub-round 0
+    unsigned char* estate;  // per edge: 0 = live, 1 = retired (paired, or an end was paired); in listed rounds only before sub-round 0,
+                            // of one mesh, all of whose edges are live then, not at all (null: the kernels of a call of 10.2 M vertices 5,431 -> 5,384 us)
     int bound;              // edges of this round at most (no less than 1)
     u64* lkey;              // listed rounds: the live edges (key, cost key, number), see select_listed_kernel
     u32* lcost;
@@ -1220,9 +1221,11 @@ __global__ __launch_bounds__(BLOCK) void select_first_kernel(SelArgs A) {
         E[j].e = i;
         E[j].key = A.ekey[at];
         E[j].cost = A.ecost[at];
-        E[j].on = A.estate[at] == 0;
-        E[j].on = E[j].on && i < n;
+        E[j].on = i < n;
     }
+    if (A.estate)
+#pragma unroll
+        for (int j = 0; j < N; ++j) E[j].on = A.estate[min(i0 + j * 64, n - 1)] == 0 && E[j].on;
     bids.clear();
     if (threadIdx.x == 0) tally.begin(A, base, n);
     judge_edges<SHUFFLE, N>(A, cur, E);

@@ -433,6 +433,9 @@ bool sort_edges_and_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySor
                           prim::TwoOuts<QuadricRows, prim::DistinctKeys>{quadric_rows(c, d_verts, N, F), distinct_keys(c)});
 }
 
+// Whether a round of one or several meshes, of at most `edges` edges, keeps a state for each.
+bool has_edge_states(int B, int edges) { return B > 1 || edges < LISTED_MIN_EDGES; }
+
 // Costs and first bids of the distinct edges that sort E of at most H keys has left.
 void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& E, int H, const MeshTab& mt, const TieBreak& tb,
                         const VRec* vrec) {
@@ -442,9 +445,10 @@ void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>&
     while (L.split_shift < 6 && (long long)L.buckets << L.split_shift < wanted) ++L.split_shift;
     while (L.split_shift == 0 && L.join_shift < UNIQUE_JOIN_MAX && L.buckets >> (L.join_shift + 1) >= wanted) ++L.join_shift;
     const int grid = L.buckets > 0 ? prim::xcd_grid((((L.buckets - 1) >> L.join_shift) + 1) << L.split_shift) : 1;
+    unsigned char* const estate = has_edge_states(mt.B, H) ? c->estate : nullptr;
     const bool wide = (long long)H / 2 > (long long)grid * UNIQUE_EDGES_NARROW;
 #define PICASSO_UNIQUE_LINES(PLACE, SHUFFLE, LK, LINES)                                                                       \
-    unique_cost_kernel<PLACE, SHUFFLE, LK, LINES><<<grid, BLOCK, 0, s>>>(L, c->ekey, c->ecost, c->estate, vrec, c->vmin[0],          \
+    unique_cost_kernel<PLACE, SHUFFLE, LK, LINES><<<grid, BLOCK, 0, s>>>(L, c->ekey, c->ecost, estate, vrec, c->vmin[0],          \
                                                                   E.key_bits / 2, mt, c->opt_rcond_min, tb, &c->st->ne)
 #define PICASSO_UNIQUE_LK(PLACE, SHUFFLE, LK)                      \
     do {                                                           \
@@ -902,7 +906,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         sa.live = c->live;
         sa.live_cap = TAIL_MAX;
         sa.live_n = c->live_n;
-        sa.estate = c->estate;
+        sa.estate = has_edge_states(B, H) ? c->estate : nullptr;
         sa.bound = std::max(H, 1);
         sa.lkey = c->key64[0];  // (between the edges' sort and line 11 these four are free)
         sa.lcost = c->val32;
