@@ -79,13 +79,13 @@ struct picasso_ctx {
     u32* distinct = nullptr;  // the edge sort's distinct keys per bucket, then per prim::UNIQUE_GROUP buckets
     size_t distinct_cap = 0;  // ... buckets
     prim::SortScratch sort_sc{};
-    u32* hist12 = nullptr;  // the bucket sorts' top-digit counts, cursors and first positions (3 x prim::MSD_HIST_WORDS)
+    u32* hist12 = nullptr;  // the key sorts' arrays of a word per digit (prim::KeySort; prim::MSD_WORDS)
     // The vertex->facet sort has buffers and scratch of its own, so that in the first round it can
     // share its launches with the edge-key sort (neither depends on the other).
     u64* s0_key[2] = {nullptr, nullptr};  // incidence keys (vertex, facet) of S0 and their sort's second buffer
     u32* hist12_s0 = nullptr;
     prim::XlScratch xl{}, xl_s0{};  // the same for the sorts of very large inputs
-    bool hist_dirty = true;  // hist12 may hold counts (the sorts leave it zero)
+    bool hist_dirty = true;  // hist12's counts may not be zero (the key sorts leave them so)
     int64_t opt_overlap = 1;
     int64_t opt_trunc_block_max = TRUNC_BLOCK_CAP;
     // per-mesh tables
@@ -223,11 +223,11 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->sort_sc.T = prim::sort_table_stride((long long)h);
     x->sort_sc.table = cv.take<u32>((size_t)256 * x->sort_sc.T);
     x->sort_sc.totals = cv.take<u32>(256);
-    x->hist12 = cv.take<u32>(3 * prim::MSD_HIST_WORDS);
+    x->hist12 = cv.take<u32>(prim::MSD_WORDS);
     for (int i = 0; i < 2; ++i) {
         x->s0_key[i] = cv.take<u64>(h);
     }
-    x->hist12_s0 = cv.take<u32>(3 * prim::MSD_HIST_WORDS);
+    x->hist12_s0 = cv.take<u32>(prim::MSD_WORDS);
     if ((long long)h > prim::BUCKET_SORT_LARGE_MAX_KEYS) {
         const size_t words = prim::xl_hist_words((long long)h);
         for (prim::XlScratch* q : {&x->xl, &x->xl_s0}) {
@@ -349,9 +349,7 @@ prim::KeySort<u64> key_sort_for(picasso_ctx* c, bool second_set, long long n, in
         S.cursor = x.cursor;
         S.starts = x.starts;
     } else {
-        S.hist = second_set ? c->hist12_s0 : c->hist12;
-        S.cursor = S.hist + prim::MSD_HIST_WORDS;
-        S.starts = S.hist + 2 * prim::MSD_HIST_WORDS;
+        prim::use_arrays(S, second_set ? c->hist12_s0 : c->hist12);
     }
     return S;
 }
@@ -361,7 +359,7 @@ inline int count_kind(const prim::KeySort<u64>& S) {
 inline DigitCount digit_count(const prim::KeySort<u64>& S) {
     return DigitCount{S.hist, S.key_bits - S.digit_bits, (1u << S.digit_bits) - 1u};
 }
-// The arrays of the narrower digits are zero between sorts; the wide ones are cleared by this before their keys are counted.
+// The counts of digits of up to 12 bits are zero between sorts (KeySort); wider ones are cleared by this before their keys are counted.
 void clear_wide_counts(hipStream_t s, const prim::KeySort<u64>& S) {
     if (count_kind(S) == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << S.digit_bits), BLOCK, 0, s>>>(S.hist, 1 << S.digit_bits, 0u);
 }
@@ -481,7 +479,7 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
                 bool work, bool edges, const HeaderInit& init = HeaderInit{}, const FewMeshes& tables = FewMeshes{}) {
     const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F);
     if (work && c->hist_dirty)  // (a call ended between a count of its edges and their sort)
-        prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, 2 * prim::MSD_HIST_WORDS, 0u);
+        prim::fill_u32_kernel<<<prim::MSD_ZERO_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, prim::MSD_ZERO_WORDS, 0u);
     if (work) {
         c->hist_dirty = edges && F > 0;
         clear_wide_counts(s, I);
@@ -1184,7 +1182,7 @@ int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts,
     if (rc != PICASSO_OK) return rc;
     rc = status_from_err_bits(reinterpret_cast<State*>(c->h_pin)->err);
     if (rc != PICASSO_OK) {  // S0 will not run: take back the digit counts the validating kernel has added
-        prim::fill_u32_kernel<<<2 * prim::MSD_HIST_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12_s0, 2 * prim::MSD_HIST_WORDS, 0u);
+        prim::fill_u32_kernel<<<prim::MSD_ZERO_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12_s0, prim::MSD_ZERO_WORDS, 0u);
         return rc;
     }
     const prim::KeySort<u64> I = incidence_sort(c, N, F);
@@ -1312,7 +1310,7 @@ int picasso_create(picasso_ctx** out, int device, int64_t max_verts, int64_t max
     memset(c->h_pin, 0, c->h_pin_ints * sizeof(int));
     // the incidence sort's digit counts start at zero; every S0 leaves them at zero again.  So do the
     // header's error flags (see HeaderInit).
-    if (hipMemset(c->hist12_s0, 0, sizeof(u32) * 2 * prim::MSD_HIST_WORDS) != hipSuccess ||
+    if (hipMemset(c->hist12_s0, 0, sizeof(u32) * prim::MSD_ZERO_WORDS) != hipSuccess ||
         hipMemset(c->area_ext, 0, sizeof(u32) * (size_t)max_meshes * conv::EXT_SLOTS * conv::EXT_PAD) != hipSuccess ||
         hipMemset(c->hdr, 0, sizeof(int) * hdr_ints((size_t)max_meshes)) != hipSuccess) {
         (void)hipHostFree(c->h_pin);
@@ -1868,9 +1866,7 @@ int picasso_bucket_sort(picasso_ctx* c, void* stream, int key_bytes, void* d_key
         S.key_bits = key_bits;
         S.digit_bits = prim::BUCKET_LARGE_MSD_BITS;
         S.buckets = 1 << S.digit_bits;
-        S.hist = c->hist12;
-        S.cursor = S.hist + prim::MSD_HIST_WORDS;
-        S.starts = S.hist + 2 * prim::MSD_HIST_WORDS;
+        prim::use_arrays(S, c->hist12);
         return prim::key_sort_array(s, S) ? 0 : -1;
     };
     const bool large = n > prim::BUCKET_SORT_MAX_KEYS;

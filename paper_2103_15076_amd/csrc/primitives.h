@@ -749,9 +749,19 @@ struct KeySort {
     // Behind the partition the keys are 32-bit words (in k1, and in k0 where that is scratch): their low 32 bits, which hold
     // all that a bucket's keys differ in.  Half the bytes of three sweeps.
     bool half = false;
-    u32* hist = nullptr;    // keys per digit (zero again behind the sort)
-    u32* cursor = nullptr;  // as much of each digit's range as is taken: zero (8-bit digits; again behind the sort), or set by key_starts_kernel
-    u32* starts = nullptr;  // first position of each digit's range
+    // One array each of a word per digit.  Which route a sort takes (narrow: msd_scatter_kernel, wide: key_starts_kernel and
+    // xl_scatter_kernel) goes by the first sort of a launch, so a sort of few digits can take the wide one beside a sort of many.
+    //            in front of the sort                         behind it
+    //   hist     keys per digit                               zero (what the next count of digits of up to 12 bits starts from)
+    //   taken    zero; narrow: part of each range in use      zero (the digits without keys have not been touched)
+    //   cursor   anything; wide: next free position           anything
+    //   starts   anything; first position of each range       that
+    // taken and cursor are two arrays because key_starts_kernel stores a position for every digit: left where a narrow sort looks for
+    // zeros, those of digits that no bucket has would send its keys to other places.
+    u32* hist = nullptr;
+    u32* taken = nullptr;  // (null where the digits are always wide)
+    u32* cursor = nullptr;
+    u32* starts = nullptr;
     u32* zero = nullptr;    // n_zero words that the per-bucket kernel adds to: cleared by the kernel in front of it
     int n_zero = 0;
     int* total = nullptr;   // receives the number of keys (those that the source keeps)
@@ -1096,7 +1106,10 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
     LK* kin = reinterpret_cast<LK*>(S.k1) + b.start;
     LK* kout = reinterpret_cast<LK*>(S.k0) + b.start;
     sort_bucket<LK, THREADS, ITEMS>(L, kin, kout, b.cnt, b.low_bits, S.group_bits, [&](auto key_at) {
-        if (threadIdx.x == 0 && b.cnt > 0) S.hist[b.number] = S.cursor[b.number] = 0;  // (every thread has read its count: barriers lie between)
+        if (threadIdx.x == 0 && b.cnt > 0) {  // (every thread has read its count: barriers lie between)
+            S.hist[b.number] = 0;
+            if (S.taken) S.taken[b.number] = 0;
+        }
         out.template emit<THREADS, ITEMS>(second, O, b, kin, kout, key_at);
     });
 }
@@ -1256,7 +1269,7 @@ struct TwoSources {
 // Partition of keys WITHOUT values by their top 8-bit digit in one pass.
 // Digits of 8 to 10 bits, 2^(BITS - 8) of them to a thread.  hist[d] = number of keys with digit d over the whole input (so digit d owns the output range
 // that starts at the sum of the counts before it; the first tile also writes these first
-// positions to `starts`); cursor[d] = how much of that range is taken, zero at the start.  Every tile counts its keys per digit in LDS, takes its share of each
+// positions to `starts`); taken[d] = how much of that range is in use, zero at the start.  Every tile counts its keys per digit in LDS, takes its share of each
 // digit's range with one returning atomic per digit it holds, and writes its keys there.  The
 // order of the keys inside a digit's range depends on the order in which tiles arrive, so this is
 // for sorts that then order each range on the whole key; with equal keys indistinguishable the
@@ -1322,7 +1335,7 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sor
 #pragma unroll
     for (int j = 0; j < DIGITS; ++j) {
         c[j] = h[DIGITS * t + j];
-        if (c[j]) first[j] += atomicAdd(&S.cursor[DIGITS * t + j], c[j]);
+        if (c[j]) first[j] += atomicAdd(&S.taken[DIGITS * t + j], c[j]);
     }
 #pragma unroll
     for (int j = 0; j < DIGITS; ++j)
@@ -1332,13 +1345,21 @@ __global__ __launch_bounds__(BLOCK) void msd_scatter_kernel(KeySort<K> first_sor
     for (int i = 0; i < KEYS; ++i) {
         if (has[i]) {
             const u32 pos = h[digit_of<K>(key[i], shift, R - 1)] + rk[i];
-            if (pos < (u32)n * PER) reinterpret_cast<LK*>(S.k1)[pos] = (LK)key[i];  // (always, when hist and cursor are as described)
+            if (pos < (u32)n * PER) reinterpret_cast<LK*>(S.k1)[pos] = (LK)key[i];  // (always, when hist and taken are as described)
         }
     }
 }
 
-// Words of a sort's count array, of its cursors and of its first positions, for digits of up to 12 bits.
-constexpr int MSD_HIST_WORDS = 4096;
+// Words of each of a sort's arrays (KeySort) for digits of up to 12 bits, and the arrays: hist, taken, cursor, starts, in a row.  The
+// first MSD_ZERO_WORDS are zero between sorts.
+constexpr int MSD_HIST_WORDS = 4096, MSD_WORDS = 4 * MSD_HIST_WORDS, MSD_ZERO_WORDS = 2 * MSD_HIST_WORDS;
+template <typename K>
+inline void use_arrays(KeySort<K>& S, u32* arrays) {
+    S.hist = arrays;
+    S.taken = arrays + MSD_HIST_WORDS;
+    S.cursor = arrays + 2 * MSD_HIST_WORDS;
+    S.starts = arrays + 3 * MSD_HIST_WORDS;
+}
 inline int bucket_sort_msd_bits(int key_bits) { return key_bits < BUCKET_MSD_BITS ? key_bits : BUCKET_MSD_BITS; }
 
 __global__ __launch_bounds__(BLOCK) void fill_u32_kernel(u32* __restrict__ p, int n, u32 v) {
@@ -1698,7 +1719,7 @@ inline bool key_sort_array(hipStream_t s, const KeySort<K>& a) {
     const int low = a.key_bits - a.digit_bits, buckets = 1 << a.digit_bits;
     fill_u32_kernel<<<(buckets + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(a.hist, buckets, 0u);
     if (a.digit_bits <= NARROW_BITS_MAX) {
-        fill_u32_kernel<<<(buckets + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(a.cursor, buckets, 0u);
+        fill_u32_kernel<<<(buckets + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(a.taken, buckets, 0u);
         msd_histogram_kernel<K, NARROW_BITS_MAX, SORT_ITEMS_SMALL><<<sort_tiles(a.n, SORT_ITEMS_SMALL), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, a.hist, low);
     } else if (a.digit_bits == BUCKET_LARGE_MSD_BITS) {
         msd_histogram_kernel<K, BUCKET_LARGE_MSD_BITS, SORT_ITEMS_BIG><<<sort_tiles(a.n, SORT_ITEMS_BIG), BLOCK, 0, s>>>(a.k0, a.n_ptr, a.n, a.hist, low);

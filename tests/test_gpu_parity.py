@@ -596,6 +596,23 @@ def test_beyond_the_bucket_sorts(pk, oracle):
         c.close()
 
 
+def test_smaller_meshes_behind_one_with_a_run_of_vertices_without_facets(pk, oracle):
+    """A cropped scan that keeps its vertices: the digits of the run (11 bits, 256 vertices each) are empty in its first round's
+    sorts, and hold keys in those of the meshes (9 and 10 bits) that follow on the context, and of its own later rounds."""
+    V, F = meshgen.noisy_grid(600, 500, seed=5)
+    F = F[~((F >= 50_000) & (F < 100_000)).any(1)]
+    assert 3 * F.shape[0] > 1 << 20
+    c = pk.Context(V.shape[0], F.shape[0], 1, device=0)
+    try:
+        for w, h in ((400, 300), (500, 300)):
+            for name, (Vi, Fi), target in (("cropped", (V, F), 100_000), ("smaller", meshgen.noisy_grid(w, h, seed=w), w * h // 3)):
+                print(f"{name}: N={Vi.shape[0]} F={Fi.shape[0]} target={target}", flush=True)
+                st, vo, fo, cid = c.picasso_decimate(dev(Vi), dev(Fi), target)
+                assert_same_result(st, vo, fo, cid, oracle.decimate(Vi, Fi, target))
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("what", ["scrambled", "few_vertices"])
 def test_very_large_sorts_without_locality(pk, oracle, what):
     """More than 2^23 half-edges where a tile of keys holds as many leading digits as keys (random vertex numbers and

@@ -176,6 +176,23 @@ def test_lists_of_rows_of_any_length(ctx, n_in, n_out, every):
     assert np.array_equal(mem.cpu().numpy(), np.argsort(row, kind="stable"))
 
 
+@pytest.mark.parametrize("wide_rows,wide_out", [(1, 1), (100, 4096)])
+def test_short_lists_behind_long_ones(pk, wide_rows, wide_out):
+    """Lists sorted on 11 bits, most of whose digits are empty, and then ones of 8, 9 and 10 bits that have such digits, on one
+    context: what the first sort has left in its arrays does not reach the second."""
+    rng = np.random.default_rng(wide_out)
+    c = pk.Context(900_000, 400_000, 1, device=0)
+    try:
+        for n in (60_000, 700_000, 900_000):
+            for row, n_out in ((rng.integers(0, wide_rows, 1_200_000), wide_out), (rng.permutation(n), n)):
+                print(f"lists n_in={row.size} n_out={n_out}", flush=True)
+                off, mem = c.picasso_cluster_csr(dev(row.astype(np.int32)), n_out)
+                assert np.array_equal(off.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n_out))]))
+                assert np.array_equal(mem.cpu().numpy(), np.argsort(row, kind="stable"))
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("n_out,C", [((1 << 24) + 40, 4), ((1 << 24) + 40, 3), ((1 << 22) + 9, 256)])
 def test_unpooling_from_clusters_beyond_24_bit_numbers_and_4_gib(pk, ctx, n_out, C):
     """Few vertices whose clusters lie at the end of a long feature array (the array's length is not an argument)."""
