@@ -1343,14 +1343,15 @@ __global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, 
 // slot.  A sub-round then costs three workgroup barriers instead of a kernel
 // launch and several trips to memory, and none once one wave holds the edges that are left.  The live count falls in every
 // sub-round (the best live edge is always accepted), so the loop ends.  The bid of a slot whose vertex has been paired is TAIL_PAIRED from then on;
-// a batch's pairs are listed and counted by mesh at the end (mesh by mesh in the loop the tails of 16 meshes took 13-22 us, now 9-15).
+// a batch's pairs, of which there can be as many as edges came in, are marked and counted by mesh at the end (mesh by mesh in the loop the
+// tails of 16 meshes took 13-22 us, now 9-15).
 // (With six barriers, the list gathered by a launch of its own, and the loads of the end not started at the beginning:
 // 14-19 us of every round of one mesh, now 9-16.  What is left is about 2 us per sub-round: the trips to LDS and the issue of 16 waves.
 // Edges in registers instead of lists, and stores to memory kept out of the loop, measured the same.)
 constexpr int TAIL_SLOTS = 8192;  // power of two, >= 2 * TAIL_MAX
 constexpr int TAIL_LDS_MESHES = 1024;
 constexpr int TAIL_FREE = -1;
-constexpr u64 TAIL_PAIRED = 0;  // (less than any bid)
+constexpr u64 TAIL_PAIRED = 0;  // (less than any bid; also the priority of an edge that has been accepted, which is not looked at again)
 
 struct TailLds {
     u64 prio[TAIL_MAX];
@@ -1361,9 +1362,8 @@ struct TailLds {
     int cnt[3];                  // live edges of the sub-round, of the next, of the one after that, in turn
     int seg_at[LIVE_SEGS + 1];   // first place of each segment's edges
     int pairs[TAIL_LDS_MESHES];  // pairs this kernel formed, per mesh (batches of up to this many meshes)
-    int n_pairs;
-    unsigned short pair_slot[TAIL_MAX / 2];  // an end of each
 };
+static_assert(sizeof(TailLds) <= 160 * 1024, "one workgroup's LDS");
 
 __device__ __forceinline__ int tail_slot(int* vkey, int v) {
     u32 h = ((u32)v * 0x9E3779B1u) >> 19;  // 13 bits
@@ -1425,7 +1425,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         if (lane == 0) L.seg_at[0] = 0;
         if (lane == LIVE_SEGS - 1) L.cnt[0] = full ? max(incl, TAIL_MAX + 1) : incl;
     }
-    if (tid == 0) L.cnt[1] = L.n_pairs = 0;
+    if (tid == 0) L.cnt[1] = 0;
     for (int h = tid; h < TAIL_SLOTS / 4; h += TAIL_THREADS)
         reinterpret_cast<int4*>(L.vkey)[h] = make_int4(TAIL_FREE, TAIL_FREE, TAIL_FREE, TAIL_FREE);
     // Up to TAIL_LDS_MESHES meshes, the pairs formed here are tallied in LDS and added to the earlier
@@ -1446,6 +1446,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         tail_mark_published(A, tid);
         return;
     }
+    const int n_in = n;
     const u64 lt = prim::lanemask_lt();
     const u64 vmask = (1ull << A.vbits) - 1ull;
     for (int seg = w; seg < LIVE_SEGS; seg += NW) {
@@ -1476,7 +1477,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
             if (A.tb.on) A.ptie[min(u, v)] = (u32)p;
             L.bid[su] = TAIL_PAIRED;  // (any other edge's bid differs from both values)
             L.bid[sv] = TAIL_PAIRED;
-            if (A.mt.B > 1 && lds_pairs) L.pair_slot[atomicAdd(&L.n_pairs, 1)] = (unsigned short)su;
+            if (A.mt.B > 1) L.prio[i] = TAIL_PAIRED;
         }
     };
     int wave_pairs = 0;  // (one mesh)
@@ -1561,7 +1562,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     if (A.mt.B == 1) {
         if (lane == 0 && wave_pairs) atomicAdd(&L.pairs[0], wave_pairs);
     } else if (lds_pairs) {
-        for (int i = tid; i < L.n_pairs; i += TAIL_THREADS) atomicAdd(&L.pairs[mesh_of(A.mt.voff, A.mt.B, L.vkey[L.pair_slot[i]])], 1);
+        for (int i = tid; i < n_in; i += TAIL_THREADS)
+            if (L.prio[i] == TAIL_PAIRED) atomicAdd(&L.pairs[mesh_of(A.mt.voff, A.mt.B, L.vkey[L.su[i]])], 1);
     } else {
         __threadfence();  // the pair counts added above are at the L2 before they are summed
     }

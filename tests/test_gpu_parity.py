@@ -579,6 +579,41 @@ def test_batch_of_more_meshes_than_the_tail_tallies_in_lds(pk, oracle):
         c.close()
 
 
+def _unwelded_quads(n):
+    """n flat squares of two triangles and four vertices of their own."""
+    x, y = 2.0 * (np.arange(n) % 50), 2.0 * (np.arange(n) // 50)
+    V = np.zeros((n, 4, 3), np.float32)
+    for i, (a, b) in enumerate(((0, 0), (1, 0), (0, 1), (1, 1))):
+        V[:, i, 0], V[:, i, 1] = x + a, y + b
+    F = np.array([[0, 1, 2], [1, 3, 2]]) + 4 * np.arange(n)[:, None, None]
+    return V.reshape(-1, 3), F.reshape(-1, 3).astype(np.int32)
+
+
+@pytest.mark.parametrize("quads", [(950, 950), (1250, 1249, 1), (1792, 1792), (1793, 1792)])
+@pytest.mark.parametrize("keep", [0.5, 0.7])
+def test_tail_in_which_every_edge_becomes_a_pair(pk, oracle, quads, keep):
+    """The first sub-round pairs two corners of every square and leaves the edge between the others, alone: the tail of a batch
+    forms as many pairs as it takes edges, up to 3,584 (one more goes back to the host)."""
+    parts = [_unwelded_quads(n) for n in quads]
+    nv, nf = [p[0].shape[0] for p in parts], [p[1].shape[0] for p in parts]
+    base = np.concatenate([[0], np.cumsum(nv)])
+    V, F = np.concatenate([p[0] for p in parts]), np.concatenate([p[1] + np.int32(b) for p, b in zip(parts, base)])
+    tg = [max(1, int(n * keep)) for n in nv]
+    c = pk.Context(V.shape[0], F.shape[0], len(parts), device=0)
+    try:
+        c.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, 1)
+        print(f"squares {quads} targets={tg}", flush=True)
+        st, vo, fo, cid, nvo, nfo = c.picasso_decimate_batch(dev(V), dev(F), nv, nf, tg)
+    finally:
+        c.close()
+    ref = oracle.decimate_batch(V, F, nv, nf, tg)
+    assert st == ref["status"]
+    assert nvo.tolist() == ref["nv"].tolist() and nfo.tolist() == ref["nf"].tolist()
+    assert np.array_equal(cid.cpu().numpy(), ref["cluster_id"])
+    assert np.array_equal(fo.cpu().numpy(), ref["facets"])
+    assert np.array_equal(vo.cpu().numpy().view(np.uint32), ref["verts"].view(np.uint32))
+
+
 def test_beyond_the_bucket_sorts(pk, oracle):
     """2.85 M facets = 8.5 M half-edges, more than are partitioned on 12 bits (2^23 keys): the first round's
     incidence and edge keys are partitioned on a wider digit, whose counts lie in memory; the later rounds drop
