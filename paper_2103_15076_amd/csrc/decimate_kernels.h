@@ -2235,8 +2235,9 @@ __global__ __launch_bounds__(ABSORB_COUNT_THREADS) void absorb_count_kernel(cons
             acand[b0 + t] = count;
             host_out[b0 + t] = count;
         }
+        const int last = ends[ABSORB_ENDS];  // (in front of the barrier: behind it the next turn's ends are stored)
         __syncthreads();
-        if (t == 0) ends[0] = ends[ABSORB_ENDS];
+        if (t == 0) ends[0] = last;  // (read by this thread only)
     }
     signal_host(done, t, t < min(B, ABSORB_ENDS));
 }
