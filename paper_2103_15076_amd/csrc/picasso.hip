@@ -364,11 +364,23 @@ void clear_wide_counts(hipStream_t s, const prim::KeySort<u64>& S) {
     if (count_kind(S) == COUNT_XL) prim::fill_u32_kernel<<<grid_for(1 << S.digit_bits), BLOCK, 0, s>>>(S.hist, 1 << S.digit_bits, 0u);
 }
 
-// The sort of the edge keys of a round with nvt vertices and at most nfb facets that have not collapsed, of F.
-prim::KeySort<u64> edge_sort(picasso_ctx* c, int nvt, int nfb, int F) {
+// Half-edges to expect of a round whose facets have not been counted yet, from the round before: its half-edges and distinct edges,
+// and the vertices it has removed.  A removed vertex takes along the facets at its edge, of which there are half_edges / edges,
+// three half-edges each; a sixth more, for pairs on open edges.  Ordinary surfaces: 54 to 55 % are left, the figure is 10 to 18 % above what comes.
+// (Seven per vertex are the same there, but half of what two-sided surfaces have, and less with more facets to a vertex, whose buckets then do
+// not fit LDS.  To a quarter of the vertices: two-sided surfaces of 593 k 894 -> 722 us, 1.12 M 1426 -> 1101; 25 facets to a vertex, any three
+// vertices: 20 k 2339 -> 1697, 100 k 5700 -> 3796.)
+long long expected_half_edges(long long half_edges, long long edges, long long removed) {
+    if (edges <= 0) return half_edges;
+    const long long left = std::max(edges - 3 * removed, 0ll);
+    return std::min(half_edges, std::max(half_edges / 4, half_edges * left / edges * 7 / 6));
+}
+
+// The sort of the edge keys of a round with nvt vertices and at most nfb facets that have not collapsed, of F; about n_keys keys (all
+// of the first round's are known).
+prim::KeySort<u64> edge_sort(picasso_ctx* c, int nvt, int nfb, int F, long long n_keys) {
     const int H = 3 * nfb, vbits = edge_vertex_bits(nvt, H);
-    // (half-edges are six per vertex, some more on coarse meshes; the facets that are left are not known yet)
-    prim::KeySort<u64> S = key_sort_for(c, false, std::min<long long>(H, 7ll * nvt), F, 2 * vbits);
+    prim::KeySort<u64> S = key_sort_for(c, false, n_keys, F, 2 * vbits);
     rows_of(S, nvt, vbits, H);
     S.zero = c->distinct + c->distinct_cap;  // (the counts per group of buckets)
     S.n_zero = (1 << S.digit_bits) / prim::UNIQUE_GROUP * prim::UNIQUE_PAD;
@@ -477,7 +489,7 @@ constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 // set-up and edges as well.
 int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, const int32_t* d_facets, int F, int B,
                 bool work, bool edges, const HeaderInit& init = HeaderInit{}, const FewMeshes& tables = FewMeshes{}) {
-    const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F);
+    const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F, 3ll * F);
     if (work && c->hist_dirty)  // (a call ended between a count of its edges and their sort)
         prim::fill_u32_kernel<<<prim::MSD_ZERO_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, prim::MSD_ZERO_WORDS, 0u);
     if (work) {
@@ -782,14 +794,14 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // attributable, and in a call whose kernels are bracketed by events: a bracketed kernel then has the chip to itself,
     // and its duration is its own.)
     const bool together = work && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
-                          edge_sort(c, N, F, F).half == incidence_sort(c, N, F).half;
+                          edge_sort(c, N, F, F, 3ll * F).half == incidence_sort(c, N, F).half;
     tm.begin(0, PICASSO_ST_QUADRICS);
     rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, work, hinit, tables);
     if (rc != PICASSO_OK) return rc;
     if (work) {
         const prim::KeySort<u64> I = incidence_sort(c, N, F);
         if (together) {
-            if (!sort_edges_and_incidences(c, s, edge_sort(c, N, F, F), I, d_verts, N, F)) return PICASSO_ERR_HIP;
+            if (!sort_edges_and_incidences(c, s, edge_sort(c, N, F, F, 3ll * F), I, d_verts, N, F)) return PICASSO_ERR_HIP;
         } else if (F > 0) {
             if (!sort_incidences(c, s, I, d_verts, N, F)) return PICASSO_ERR_HIP;
         }
@@ -815,7 +827,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 
         // ---- S1 (+S2): edges and costs
         tm.begin(round, PICASSO_ST_EDGES);
-        const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F);
+        const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F, round > 0 ? expected_half_edges(H, ne_prev, nv_prev - nv_total) : H);
         if (round > 0) launch_edge_keys(c, s, B, round, cur, E, N, F);
         if (!(round == 0 && together) && H > 0 && !sort_edges(c, s, E, round)) return PICASSO_ERR_HIP;
         renumbered = false;
@@ -1505,7 +1517,7 @@ int picasso_edge_costs(picasso_ctx* c, void* stream, const float* d_verts, int32
     if (rc != PICASSO_OK) return rc;
     const int H = 3 * F, vbits = edge_vertex_bits(N, H);
     MeshTab mt{1, c->voff[0], c->target, c->active, c->nrem, c->matched, c->mslots};
-    const prim::KeySort<u64> E = edge_sort(c, N, F, F);
+    const prim::KeySort<u64> E = edge_sort(c, N, F, F, 3ll * F);
     if (F > 0) {
         if (!sort_edges(c, s, E, 0)) return PICASSO_ERR_HIP;
     }

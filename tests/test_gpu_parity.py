@@ -579,6 +579,34 @@ def test_batch_of_more_meshes_than_the_tail_tallies_in_lds(pk, oracle):
         c.close()
 
 
+@pytest.mark.parametrize("what", ["two_sided", "soup", "loose_triangles"])
+@pytest.mark.parametrize("seed", [0, 77])
+def test_rounds_with_other_than_six_half_edges_per_vertex(ctx, pk, oracle, what, seed):
+    """The digit of a later round's edge sort goes by the half-edges to expect of it: twelve per vertex, a hundred and more, and
+    none at all (every facet of the first round collapses, and a patch beside them is left)."""
+    if what == "two_sided":
+        V, F = meshgen.noisy_grid(330, 300, seed=2)
+        F = np.stack([F, F[:, ::-1]], 1).reshape(-1, 3)
+    elif what == "soup":
+        rng = np.random.default_rng(3)
+        n, m = 9000, 400_000
+        V, a = rng.normal(size=(n, 3)), rng.integers(0, n, m)
+        F = np.stack([a, (a + rng.integers(1, 40, m)) % n, (a + rng.integers(41, 80, m)) % n], 1)
+    else:
+        P, Q = meshgen.noisy_grid(20, 20, seed=4)
+        V = np.concatenate([np.random.default_rng(5).normal(size=(360_000, 3)), P])
+        F = np.concatenate([np.arange(360_000).reshape(-1, 3), Q + 360_000])
+    V, F = V.astype(np.float32), np.ascontiguousarray(F.astype(np.int32))
+    target = V.shape[0] // 4
+    ctx.set_option(pk.PICASSO_OPT_SHUFFLE_SEED, seed)
+    try:
+        print(f"{what}: N={V.shape[0]} F={F.shape[0]} target={target} seed={seed}", flush=True)
+        st, vo, fo, cid = ctx.picasso_decimate(dev(V), dev(F), target)
+    finally:
+        ctx.set_option(pk.PICASSO_OPT_SHUFFLE_SEED, 0)
+    assert_same_result(st, vo, fo, cid, oracle.decimate(V, F, target, shuffle_seed=seed))
+
+
 def _unwelded_quads(n):
     """n flat squares of two triangles and four vertices of their own."""
     x, y = 2.0 * (np.arange(n) % 50), 2.0 * (np.arange(n) // 50)
