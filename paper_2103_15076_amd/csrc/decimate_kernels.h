@@ -257,8 +257,8 @@ struct FewMeshes {
 
 // Incidence keys for S0: (vertex << fbits) | facet, one per facet corner, so that sorting the keys
 // alone lists every vertex's facets in ascending facet order; edge keys for the first round (see edge_keys_kernel, which is
-// the first kernel of the others).  With COUNT_SMALL / COUNT_LARGE the
-// kernel also adds both keys' top 8- / 12-bit digits to the histograms that the sorts start from (zero on entry; left so
+// the first kernel of the others).  With COUNT_SMALL (digits of 8 to 10 bits) and COUNT_LARGE (11 and 12) the
+// kernel also adds both keys' top digits to the histograms that the sorts start from (zero on entry; left so
 // by the sorts); the sorts make the keys again from the validated facets, so they are
 // written nowhere.  COUNT_XL: digits as wide as the masks say, counted in memory.  COUNT_NONE: no round follows.  edges: the
 // edges' digits are wanted, and the round's set-up is made.
@@ -614,8 +614,8 @@ struct QuadricRows {
 // S1: candidate pairs = distinct mesh edges (Alg. 2 line 1)
 //
 // First kernel of every round but the first (whose part init_kernel takes): the round's set-up (block 0), the per-vertex selection state, and the digits of the
-// 64-bit keys (lower vertex, higher vertex), one per half-edge: the kernel adds the keys' top digits (8 bits with
-// COUNT_SMALL, 12 with COUNT_LARGE, as xl_digit_bits says with COUNT_XL) to the histogram that the sort of the keys starts from
+// 64-bit keys (lower vertex, higher vertex), one per half-edge: the kernel adds the keys' top digits (8 to 10 bits with
+// COUNT_SMALL, 11 or 12 with COUNT_LARGE, as xl_digit_bits says with COUNT_XL) to the histogram that the sort of the keys starts from
 // (zeroed beforehand); the sort makes the keys again from the facets, so they are not written.
 //
 // The round before has contracted pairs and the facets still name its vertices: they are taken to

@@ -786,12 +786,7 @@ struct KeySort {
 // up to 16 times the capacity) is sorted in parts, runs of whole groups that fit, each read out of the
 // bucket by the workgroup and written to k0; if it also has a group of more than 64 keys, or is larger still, it
 // takes the slow global-memory route of bucket_sort_oversize.  Out then gets the keys from there.  Workgroups are small (256
-// lanes for the 4096-bucket sorts) so that several of them share a compute unit and cover each other's barriers.
-// Bound by vector issue (three quarters of its time at 10.2 M vertices), so: lane counts and prefix sums by the instructions that
-// make them, no 64-bit arithmetic on 32-bit keys, groups that are the rows (not every other one empty), no workgroups for
-// digits that cannot occur.  First round of 10.2 M vertices / 61 M facet corners, incidence and edge keys: 611 us for the sorts, 472 for the
-// quadrics by a launch that read the sorted keys again, 437 for costs with the search for distinct edges; now 616 and 392.  1.2 M: 53 + 65 + 68
-// -> 63 + 52; 115 k: 12.5 + 10.4 + 14.4 -> 13.3 + 10.4; lists of 5.7 M corners 22.9 + 15.0 -> 19.7.
+// lanes) so that several of them share a compute unit and cover each other's barriers.
 // Bound by vector issue (three quarters of its time at 10.2 M vertices), so: lane counts and prefix sums by the instructions that
 // make them, no 64-bit arithmetic on 32-bit keys, groups that are the rows (not every other one empty), no workgroups for
 // digits that cannot occur.  First round of 10.2 M vertices, 61 M incidence and 61 M edge keys: 611 us for the sorts, 472 for the
@@ -1266,8 +1261,7 @@ struct TwoSources {
     __device__ __forceinline__ bool keep(bool second, K k) const { return second ? b.keep(k) : a.keep(k); }
 };
 
-// Partition of keys WITHOUT values by their top 8-bit digit in one pass.
-// Digits of 8 to 10 bits, 2^(BITS - 8) of them to a thread.  hist[d] = number of keys with digit d over the whole input (so digit d owns the output range
+// Partition of keys WITHOUT values by their top digit, of 8 to 10 bits (2^(BITS - 8) digits to a thread), in one pass.  hist[d] = number of keys with digit d over the whole input (so digit d owns the output range
 // that starts at the sum of the counts before it; the first tile also writes these first
 // positions to `starts`); taken[d] = how much of that range is in use, zero at the start.  Every tile counts its keys per digit in LDS, takes its share of each
 // digit's range with one returning atomic per digit it holds, and writes its keys there.  The
@@ -1467,20 +1461,22 @@ inline int bucket_sort_large(hipStream_t s, K* k0, K* k1, u32* v0, u32* v1, cons
 
 // ---------------------------------------------------------------------------
 // Keys without values beyond BUCKET_SORT_MAX_KEYS: the same two sweeps (partition on a top digit, then one workgroup
-// per bucket), with a digit of 12 bits, beyond BUCKET_SORT_LARGE_MAX_KEYS as wide as the input needs for buckets of
-// about a thousand keys.  Arrays with one word per digit then do not fit LDS, or fill it; a tile of mesh keys holds few
+// per bucket), with a digit of 11 or 12 bits, beyond BUCKET_SORT_LARGE_MAX_KEYS as wide as the input needs for buckets of
+// BUCKET_KEYS_AIM keys at most, half of that at least.  Arrays with one word per digit then do not fit LDS, or fill it; a tile of mesh keys holds few
 // distinct digits, though, so it counts them in a small hash table.  Bound by memory: 8 bytes read and 8 written per key and sweep
 // (less 4 read where keys are made on the fly), where plain radix passes read every key twice and wrote it once for
 // every 8 bits (61 M keys of 48 bits: 6 passes, 2.9 ms; this way 0.5 ms).
 // ---------------------------------------------------------------------------
 constexpr int XL_BITS_MIN = 13, XL_BITS_MAX = 22;
-// Keys per bucket aimed at, 1,000 to 2,000 then or, where ids do not fill their bit range, up to twice that: a workgroup's own part (counters, their
-// prefix sums, what is made of the keys) costs as much as 700 keys do (33 M keys of the second round of 10.2 M vertices: 711 to a bucket 230 us,
-// 1,422 to a bucket 140).
+// Keys per bucket, over all that there can be, at most: 1,000 to 2,000 from 2^22 keys on, 500 to 2,000 from 2^20.  Ids that fill
+// little more than half of their bit range leave almost half of the buckets empty, and the others hold up to twice that.  A workgroup's own
+// part (counters, their prefix sums, what is made of the keys) costs as much as 700 keys do (33 M keys of the second round of 10.2 M
+// vertices: 711 to a bucket 230 us, 1,422 to a bucket 140).
 constexpr long long BUCKET_KEYS_AIM = 2048;
-// Below 2^20 keys the chip also has to be filled: a bucket's keys by one workgroup of 256 lanes, edge and incidence keys of the first round with
-// 8 bits and workgroups of 512 / 9 / 10 bits: 682 k keys 13.3 / 12.7 / 15.3 us, 920 k 22.9 / - / 16.3, 368 k 11.5 / 12.1 / -, the second round's
-// 147 k 9.4 / 10.0 / -.
+// Below 2^20 keys the chip also has to be filled.  Partition and bucket sorts of the first round of lattices, us with 8 / 9 / 10 bits: 64 k
+// keys 12.0 / 13.4 / 14.4, 147 k 13.0 / 14.3 / 16.8, 220 k 15.6 / 14.9 / 14.7, 368 k 18.2 / 17.6 / 19.7, 500 k 20.7 / 19.7 / 18.4, 682 k
+// 21.8 / 20.0 / 22.0, 740 k 22.4 / 20.3 / 23.0, 790 k 75 / 24.1 / 21.0, 920 k 80 / 27.8 / 25.0, 1 M 85 / 29.1 / 24.6 (eight bits from 786 k on: buckets
+// beyond what LDS holds).  So 9 bits end where 10 are better; 8 bits could go to about 180 k, for a microsecond.
 constexpr long long NARROW_8_BITS_MAX_KEYS = 1 << 16, NARROW_9_BITS_MAX_KEYS = 3 << 18;
 inline int xl_bits_for(long long n) {
     int b = XL_BITS_MIN;

@@ -758,7 +758,7 @@ def test_on_a_stream_of_the_callers(pk, ctx, oracle):
     assert_same_result(st, vo, fo, cid, ref)
     side.synchronize()
     assert np.array_equal(doubled.cpu().numpy(), ref["verts"] * np.float32(2.0))
-    # larger input: the first round's edge sort runs on the context's own stream beside the caller's
+    # larger input
     c = meshgen.config("scene1p2m")
     V2, F2, t2 = c["verts"], c["facets"], int(c["target"][0])
     with torch.cuda.stream(side):
@@ -768,10 +768,14 @@ def test_on_a_stream_of_the_callers(pk, ctx, oracle):
 
 
 @pytest.mark.parametrize("w,h,what", [
-    (419, 419, "just below 2^20 half-edges: 256-bucket sort, one lane per edge in every sub-round"),
-    (420, 419, "just above 2^20 half-edges: 4096-bucket sort, sparse sub-rounds"),
-    (363, 362, "just below 2^18 facets"),
-    (364, 363, "just above 2^18 facets"),
+    (105, 106, "just below 2^16 half-edges: 8-bit digits"),
+    (106, 106, "just above 2^16 half-edges: 9-bit digits"),
+    (363, 362, "just below 3 x 2^18 half-edges: 9-bit digits"),
+    (364, 363, "just above 3 x 2^18 half-edges: 10-bit digits"),
+    (419, 419, "just below 2^20 half-edges: 10-bit digits, one lane per edge in every sub-round"),
+    (420, 419, "just above 2^20 half-edges: 11-bit digits, listed sub-rounds"),
+    (837, 837, "just below 2^22 half-edges: 11-bit digits"),
+    (838, 837, "just above 2^22 half-edges: 12-bit digits"),
 ])
 def test_sizes_on_either_side_of_the_path_switches(ctx, oracle, w, h, what):
     V, F = meshgen.noisy_grid(w, h, seed=w + h, noise=0.004)

@@ -162,8 +162,8 @@ def test_features_at_addresses_that_are_not_16_byte_aligned(pk, ctx, oracle):
 
 
 @pytest.mark.parametrize("n_in,n_out,every", [
-    (70_000, 1, 1), (70_000, 3, 1), (70_000, 129, 1), (70_000, 257, 3),                  # 256 digits: rows of one digit and of many,
-    (1_200_000, 1, 1), (1_200_000, 16, 1), (1_200_000, 4097, 5), (1_200_000, 1_000_000, 7),  # 4,096 digits, rows without members,
+    (70_000, 1, 1), (70_000, 3, 1), (70_000, 129, 1), (70_000, 257, 3),                  # 512 digits: rows of one digit and of many,
+    (1_200_000, 1, 1), (1_200_000, 16, 1), (1_200_000, 4097, 5), (1_200_000, 1_000_000, 7),  # 2,048 digits, rows without members,
     (7_400_000, 40, 3), (7_400_000, 600_000, 1),                                         # ... beyond what a list of one sort takes
 ])
 def test_lists_of_rows_of_any_length(ctx, n_in, n_out, every):
