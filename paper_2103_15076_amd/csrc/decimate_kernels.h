@@ -137,13 +137,24 @@ struct RoundTab {
     const int* voff;
     const int* target;
     int* active;
+    const int* was_active;  // in the round before
     int* stuck;
     int* nrem;
-    int* matched;
+    const int* matched;     // ... pairs formed then
     int* mslots;
     int* live_n;  // see SelArgs
     int first_round;
 };
+
+// A mesh takes part in a round if it has more vertices than it is to keep, unless it formed no pair in a round before.  (Said by the
+// workgroups of a round's first kernel, each for itself, while one of them writes it down: none of what they read changes but `stuck`,
+// which that one sets where this says so anyway.)
+__device__ __forceinline__ bool mesh_stuck(const RoundTab& R, int b) {
+    return R.stuck[b] != 0 || (!R.first_round && R.was_active[b] != 0 && R.matched[b] == 0);
+}
+__device__ __forceinline__ bool mesh_active(const RoundTab& R, int b) {
+    return R.voff[b + 1] - R.voff[b] > R.target[b] && !mesh_stuck(R, b);
+}
 
 // Per-mesh budgets and the round's counters, by one workgroup.
 __device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) {
@@ -151,11 +162,10 @@ __device__ __forceinline__ void round_begin_block(const RoundTab& R, State* st) 
     if (threadIdx.x < 32) R.live_n[threadIdx.x * MATCH_PAD] = 0;
     for (int b = threadIdx.x; b < R.B; b += blockDim.x) {
         const int nvb = R.voff[b + 1] - R.voff[b];
-        if (!R.first_round && R.active[b] && R.matched[b] == 0) R.stuck[b] = 1;
-        const int act = (nvb > R.target[b]) && !R.stuck[b];
+        const int act = mesh_active(R, b);
+        if (mesh_stuck(R, b)) R.stuck[b] = 1;
         R.active[b] = act;
         R.nrem[b] = act ? nvb - R.target[b] : 0;
-        R.matched[b] = 0;
     }
     if (threadIdx.x == 0) {
         st->nh = 0;
@@ -305,6 +315,7 @@ struct DigitTally<COUNT_NONE> {
     __device__ __forceinline__ void flush(const DigitCount&) {}
 };
 
+enum { EDGES_NONE = 0, EDGES_BY_FACETS = 1, EDGES_SORTED = 2 };
 template <int COUNT, class Tables>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
                                                      const int* __restrict__ facets, int F, int B,
@@ -339,13 +350,13 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
             init.hdr[i] = v;
         }
     }
-    if (edges && blockIdx.x == 0) {
+    if (edges != EDGES_NONE && blockIdx.x == 0) {
         __syncthreads();  // (the header, where this workgroup has written it)
         round_begin_block(R, st);
     }
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
     corners.clear(inc);
-    sides.clear(edge);
+    if (edges == EDGES_SORTED) sides.clear(edge);
     __syncthreads();
     int err = 0;
     for (int w = g; w < N; w += stride) {
@@ -357,10 +368,12 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
             r.a00 = r.a01 = r.a02 = r.a11 = r.a12 = r.a22 = r.b0 = r.b1 = r.b2 = r.c = r.w1 = r.w2 = 0.f;
             vrec[w] = r;
         }
-        cid[w] = w;
-        if (edges) {
+        if (cid) cid[w] = w;
+        if (edges != EDGES_NONE) {
             vmin0[w] = VMIN_NONE;
             vmin1[w] = VMIN_NONE;
+        }
+        if (edges == EDGES_SORTED) {
             mate[w] = -1;
             pcost[w] = ~0u;
         }
@@ -395,7 +408,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         if (planes && ok) planes[f] = facet_plane(verts, at[0], at[1], at[2]);
 #pragma unroll
         for (int c = 0; c < 3; ++c) corners.count(inc, ok, ((u64)(u32)at[c] << fbits) | (u64)(u32)f);
-        if (edges) {
+        if (edges == EDGES_SORTED) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const int a = at[c], b = at[c == 2 ? 0 : c + 1];
@@ -405,17 +418,17 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         if constexpr (COUNT == COUNT_XL) {
             __syncthreads();
             corners.flush(inc);
-            sides.flush(edge);
+            if (edges == EDGES_SORTED) sides.flush(edge);
             __syncthreads();
             corners.clear(inc);
-            sides.clear(edge);
+            if (edges == EDGES_SORTED) sides.clear(edge);
             __syncthreads();
         }
     }
     if constexpr (COUNT != COUNT_XL) {
         __syncthreads();
         corners.flush(inc);
-        sides.flush(edge);
+        if (edges == EDGES_SORTED) sides.flush(edge);
     }
     if (err) atomicOr(&st->err, err);
 }
@@ -760,12 +773,18 @@ __device__ __forceinline__ bool quadric_minimiser(float a00, float a01, float a0
 // pair would be contracted to: the pair's mean, or with PLACE_INVERSE the point
 // of least error where the quadric has one (Alg. 2 line 2; supplementary
 // Q(x) = x^T A x + 2 b^T x + c and the two placement equations).
+struct VertexWords {
+    float4 w[4];
+};
+__device__ __forceinline__ VertexWords load_vertex(const VRec* __restrict__ vrec, int v) {
+    const float4* r = reinterpret_cast<const float4*>(&vrec[v]);
+    return VertexWords{{r[0], r[1], r[2], r[3]}};
+}
+// (The same to the bit with its ends exchanged: every step in which they meet is a sum of two.)
 template <int PLACE>
-__device__ __forceinline__ float pair_cost(const VRec* __restrict__ vrec, int u, int v, float rcond_min) {
-    const float4* ru = reinterpret_cast<const float4*>(&vrec[u]);
-    const float4* rv = reinterpret_cast<const float4*>(&vrec[v]);
-    const float4 u0 = ru[0], u1 = ru[1], u2 = ru[2], u3 = ru[3];
-    const float4 v0 = rv[0], v1 = rv[1], v2 = rv[2], v3 = rv[3];
+__device__ __forceinline__ float pair_cost(const VertexWords& U, const VertexWords& V, float rcond_min) {
+    const float4 u0 = U.w[0], u1 = U.w[1], u2 = U.w[2], u3 = U.w[3];
+    const float4 v0 = V.w[0], v1 = V.w[1], v2 = V.w[2], v3 = V.w[3];
     const float a00 = u1.x + v1.x, a01 = u1.y + v1.y, a02 = u1.z + v1.z, a11 = u1.w + v1.w;
     const float a12 = u2.x + v2.x, a22 = u2.y + v2.y, b0 = u2.z + v2.z, b1 = u2.w + v2.w;
     const float b2 = u3.x + v3.x, c = u3.y + v3.y;
@@ -786,14 +805,14 @@ __device__ __forceinline__ float pair_cost(const VRec* __restrict__ vrec, int u,
 // words (24) as with one, but lanes of a wave that name the same word take a request each (1.7 lines with 8 lanes per word).  The edges of a workgroup touch few vertices, and those lie in few lines, so the table
 // holds lines: each goes out as one request.  A line that finds no place (a mesh numbered without locality) goes out
 // by itself.  1.2 M vertices, first round: costs and bids 106 -> 83 us, sub-round 0 59 -> 51.
-template <int LINES>
+template <int LINES, int THREADS = BLOCK>
 struct BidTable {
     static constexpr int PROBES = 4;
     int line[LINES];
     u64 bid[8 * LINES];
     __device__ __forceinline__ void clear() {
-        for (int i = threadIdx.x; i < LINES; i += BLOCK) line[i] = -1;
-        for (int i = threadIdx.x; i < 8 * LINES; i += BLOCK) bid[i] = VMIN_NONE;
+        for (int i = threadIdx.x; i < LINES; i += THREADS) line[i] = -1;
+        for (int i = threadIdx.x; i < 8 * LINES; i += THREADS) bid[i] = VMIN_NONE;
     }
     // A bid p on vertex v.  rst: an array whose word of every vertex that is bid on is cleared (or null).
     __device__ __forceinline__ void put(u64* __restrict__ vmin, u64* __restrict__ rst, int v, u64 p) {
@@ -812,7 +831,7 @@ struct BidTable {
         if (rst) rst[v] = VMIN_NONE;
     }
     __device__ __forceinline__ void flush(u64* __restrict__ vmin, u64* __restrict__ rst) {
-        for (int i = threadIdx.x; i < 8 * LINES; i += BLOCK) {
+        for (int i = threadIdx.x; i < 8 * LINES; i += THREADS) {
             const u64 b = bid[i];
             if (b == VMIN_NONE) continue;
             const size_t v = 8 * (size_t)line[i >> 3] + (size_t)(i & 7);
@@ -879,7 +898,7 @@ __global__ __launch_bounds__(BLOCK) void unique_cost_kernel(EdgeList E, u64* __r
             }
         const u64 k = b.whole(keys[E.starts[b.number] + (u32)at]);
         const int u = (int)(k >> vbits), v = (int)(k & vmask), e = before + q;
-        const u32 ck = cost_key(pair_cost<PLACE>(vrec, u, v, rcond_min));
+        const u32 ck = cost_key(pair_cost<PLACE>(load_vertex(vrec, u), load_vertex(vrec, v), rcond_min));
         const bool act = mt.active[mesh_of(mt.voff, mt.B, u)] != 0;
         ekey[e] = k;
         ecost[e] = ck;
@@ -948,10 +967,18 @@ struct SelArgs {
     unsigned char* estate;  // per edge: 0 = live, 1 = retired (paired, or an end was paired); in listed rounds only before sub-round 0,
                             // of one mesh, all of whose edges are live then, not at all (null: the kernels of a call of 10.2 M vertices 5,431 -> 5,384 us)
     int bound;              // edges of this round at most (no less than 1)
-    u64* lkey;              // listed rounds: the live edges (key, cost key, number), see select_listed_kernel
+    u64* lkey;              // listed rounds: the live edges (key, cost key, with shuffle their numbers), see select_listed_kernel
     u32* lcost;
     int* lidx;
     int* lcount;
+    int list_tile;          // ... places of the lists' tiles,
+    int list_tiles;         // ... how many (0: as the round's edges fill)
+    const int* fcur;        // rounds by facets (see facet_costs_kernel): the facets,
+    const u32* fcost;       // ... their sides' cost keys, n_facets of each side
+    const int* fcount;      // ... per tile how many of its places are taken (null: all),
+    int n_facets, parts;    // ... the places, the workgroups' parts of facets and vertices,
+    int nv;                 // ... vertices
+    const int* nf_slots;    // ... facets that have not collapsed (null: State says so), in MATCH_SLOTS parts
     State* st;
     MeshTab mt;
     int vbits;
@@ -1049,18 +1076,20 @@ __device__ __forceinline__ void count_pairs(const SelArgs& A, bool sel, int m) {
 // and added by one atomic in the end.  (The counters of a mesh lie in MATCH_SLOTS lines, and a line takes an atomic every
 // 11 to 14 ns: with one per wave they took longer than the rest of a sub-round, 150 of 420 us at 30 M edges.)
 struct PairTally {
-    int mesh, pairs;
-    // by one thread; e = the workgroup's first edge
-    __device__ __forceinline__ void begin(const SelArgs& A, long long e, int n) {
-        mesh = A.mt.B <= 1 || e >= n ? 0 : mesh_of(A.mt.voff, A.mt.B, (int)(A.ekey[e] >> A.vbits));
+    int mesh, first, end_v, pairs;  // the mesh and its vertices
+    // by one thread; v = a vertex of the mesh
+    __device__ __forceinline__ void begin(const SelArgs& A, int v) {
+        mesh = mesh_of(A.mt.voff, A.mt.B, v);
+        first = A.mt.B <= 1 ? 0 : A.mt.voff[mesh];
+        end_v = A.mt.B <= 1 ? 0x7FFFFFFF : A.mt.voff[mesh + 1];
         pairs = 0;
     }
     // by all lanes of a wave; u = an end of the pair
     __device__ __forceinline__ void count(const SelArgs& A, bool sel, int u) {
-        const int m = A.mt.B > 1 && sel ? mesh_of(A.mt.voff, A.mt.B, u) : 0;
-        const u64 mine = prim::ballot(sel && m == mesh);
+        const bool here = u >= first && u < end_v;
+        const u64 mine = prim::ballot(sel && here);
         if (mine && prim::lane_id() == 0) atomicAdd(&pairs, (int)__popcll(mine));
-        if (A.mt.B > 1) count_pairs(A, sel && m != mesh, m);
+        if (A.mt.B > 1 && __any(sel && !here)) count_pairs(A, sel && !here, sel && !here ? mesh_of(A.mt.voff, A.mt.B, u) : 0);
     }
     // by one thread, behind a barrier
     __device__ __forceinline__ void end(const SelArgs& A) const {
@@ -1163,18 +1192,18 @@ constexpr int LISTED_MIN_EDGES = 1 << 20;  // below this the sub-rounds are at t
 constexpr int LISTED_TILE_SHIFT = 10, LISTED_TILE = 1 << LISTED_TILE_SHIFT, LISTED_PER_LANE = LISTED_TILE / BLOCK;
 constexpr int LISTED_GROUP_MAX = 4;
 constexpr int LISTED_LINES = 256;
-// Parts that sub-round k >= 1 joins, and their size (bits): a workgroup has a few hundred live edges every time.
-constexpr int LISTED_SPAN_MAX = 16;
+// Parts that sub-round k >= 1 joins, and how many tiles a part is (bits): a workgroup has a few hundred live edges every time.
+constexpr int LISTED_PART_SHIFT_MAX = 6;
 inline int listed_group_shift(int k) { return k <= 3 ? 1 : 2; }
-inline int listed_span(int k) {
-    int span = LISTED_TILE_SHIFT;
-    for (int j = 1; j < k && span < LISTED_SPAN_MAX; ++j) span += listed_group_shift(j);
-    return span;
+inline int listed_part_shift(int k) {
+    int shift = 0;
+    for (int j = 1; j < k && shift < LISTED_PART_SHIFT_MAX; ++j) shift += listed_group_shift(j);
+    return shift;
 }
-inline int listed_group(int k) { return listed_span(k) >= LISTED_SPAN_MAX ? 1 : 1 << listed_group_shift(k); }
+inline int listed_group(int k) { return listed_part_shift(k) >= LISTED_PART_SHIFT_MAX ? 1 : 1 << listed_group_shift(k); }
 
 // Places of the lanes' live edges among the workgroup's (N per lane, wave by wave); total = their number.  Contains barriers.
-template <int N>
+template <int N, int NWAVES = prim::WAVES>
 __device__ __forceinline__ void live_places(const bool (&alive)[N], u32* smem, int (&place)[N], int& total) {
     const int w = prim::wave_id();
     u32 run = 0;
@@ -1189,7 +1218,7 @@ __device__ __forceinline__ void live_places(const bool (&alive)[N], u32* smem, i
     __syncthreads();
     u32 before = 0, all = 0;
 #pragma unroll
-    for (int j = 0; j < prim::WAVES; ++j) {
+    for (int j = 0; j < NWAVES; ++j) {
         const u32 c = smem[j];
         if (j < w) before += c;
         all += c;
@@ -1227,7 +1256,7 @@ __global__ __launch_bounds__(BLOCK) void select_first_kernel(SelArgs A) {
 #pragma unroll
         for (int j = 0; j < N; ++j) E[j].on = A.estate[min(i0 + j * 64, n - 1)] == 0 && E[j].on;
     bids.clear();
-    if (threadIdx.x == 0) tally.begin(A, base, n);
+    if (threadIdx.x == 0) tally.begin(A, (int)(E[0].key >> A.vbits));
     judge_edges<SHUFFLE, N>(A, cur, E);
     bool alive[N];
     int place[N], total;
@@ -1242,7 +1271,7 @@ __global__ __launch_bounds__(BLOCK) void select_first_kernel(SelArgs A) {
             const size_t p = (size_t)base + (size_t)place[j];
             A.lkey[p] = x.key;
             A.lcost[p] = x.cost;
-            A.lidx[p] = x.e;
+            if constexpr (SHUFFLE) A.lidx[p] = x.e;
             bids.put(nxt, rst, x.u, x.pu);
             bids.put(nxt, rst, x.v, x.pv);
         }
@@ -1256,28 +1285,332 @@ __global__ __launch_bounds__(BLOCK) void select_first_kernel(SelArgs A) {
     }
 }
 
-// TABLE: bids are put together in LDS (many live edges per line of vertices), else they go out as they are.
-template <bool SHUFFLE, bool APPEND, bool TABLE>
-__global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, int span_shift, int group) {
+// ---------------------------------------------------------------------------
+// Rounds by facets: S1, S2 and the first bids without a list of the distinct edges.
+//
+// Where nothing needs the edges' numbers (ties that go by the shuffle, line 11, the statistics) an edge may as well be met once per facet that has
+// it: its cost is the same to the bit each time, and bids are minima.  So one kernel takes the facets to the round's numbering, as
+// edge_keys_kernel does, fetches each facet's three vertex records, and leaves the cost keys of its three sides and the better of a vertex's
+// two bids; the sort of the half-edges (partition and per-bucket kernel) and unique_cost_kernel, which number the distinct
+// ones, do not run.  Facets that have collapsed leave their tile, so that each round reads what the one before has left.
+// Bound by memory: the first round's launch moves 1.55 GB of 10.2 M vertices / 20 M facets in 353 us (4.4 TB/s), later ones wait
+// for a chain of gathers (344 and 298 us, 3.1 and 2.4 TB/s; six waves a SIMD, hence the bound on registers: 409 and 321 without).
+// Rounds 2 and 3 of that mesh took 686 and 565 us up to the first bids with the sort, 227 k facets 32 us of round 2, now 9; whole calls with the
+// sort / by facets: 4 k vertices 178 / 155 us, 115 k 213 / 189, 1.2 M 848 / 702, 10.2 M 5,400 / 4,720.
+// ---------------------------------------------------------------------------
+// What a workgroup wants to know of the meshes: of up to TALLY_MESHES from LDS, as a search is a chain of loads.
+struct MeshFlags {
+    int voff[TALLY_MESHES + 1];
+    unsigned char active[TALLY_MESHES], done[TALLY_MESHES];
+    // by the workgroup, in front of a barrier
+    __device__ __forceinline__ void begin(const RoundTab& R, const int* __restrict__ done_) {
+        const int t = threadIdx.x;
+        if (R.B > TALLY_MESHES) return;
+        if (t <= R.B) voff[t] = R.voff[t];
+        if (t < R.B) {
+            active[t] = mesh_active(R, t) ? 1 : 0;
+            done[t] = done_ && done_[t] != 0 ? 1 : 0;
+        }
+    }
+    __device__ __forceinline__ bool is_active(const RoundTab& R, int v) const {
+        return R.B <= TALLY_MESHES ? active[mesh_of(voff, R.B, v)] != 0 : mesh_active(R, mesh_of(R.voff, R.B, v));
+    }
+    __device__ __forceinline__ bool is_done(const RoundTab& R, const int* __restrict__ done_, int v) const {
+        return R.B <= TALLY_MESHES ? done[mesh_of(voff, R.B, v)] != 0 : done_[mesh_of(R.voff, R.B, v)] != 0;
+    }
+};
+
+// The facets stand in tiles of THREADS * PER places, each with its own at the front, in order, `fcount` of them (null: all places
+// are taken): a collapsed facet leaves its tile.
+template <int PLACE, int THREADS, int PER, bool FIRST>
+__global__ __launch_bounds__(THREADS, FIRST ? 1 : 6) void facet_costs_kernel(int* __restrict__ fcur, int F, State* st, int cur,
+                                                              const VRec* __restrict__ vrec, u64* __restrict__ vmin0,
+                                                              u64* __restrict__ vmin1, u32* __restrict__ fcost, RoundTab R,
+                                                              const int* __restrict__ vmap, const int* __restrict__ done,
+                                                              int* __restrict__ cid, int n_orig, float rcond_min,
+                                                              const int* fcount, int* fcount_out, int* __restrict__ nf_slots,
+                                                              int* __restrict__ nf_next) {
+    constexpr int TILE = THREADS * PER, WAVES = THREADS / 64;
+    __shared__ BidTable<THREADS * PER <= 1024 ? 128 : 256, THREADS> bids;
+    __shared__ MeshFlags M;
+    __shared__ int at[FIRST ? 1 : 3][FIRST ? 1 : TILE];  // the corners of those left
+    __shared__ int left[PER][WAVES];
+    const int t = threadIdx.x, stride = gridDim.x * THREADS, g = blockIdx.x * THREADS + t;
+    const int tile = prim::xcd_tile(F, TILE);
+    const long long f0 = (long long)tile * TILE;
+    int n = (int)max(min((long long)F - f0, (long long)TILE), 0ll);
+    Corners q[PER];
+    int label = 0;
+    if constexpr (FIRST) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) q[j] = load_corners(fcur, (size_t)(j * THREADS + t < n ? f0 + j * THREADS + t : 0));
+    } else {
+        if (PER == 1) q[0] = load_corners(fcur, (size_t)(t < n ? f0 + t : 0));  // (not yet known to be one)
+        if (g < n_orig) label = cid[g];
+        const int nv = st->nv[cur];
+        if (fcount && n > 0) n = fcount[tile];
+        if (PER > 1)
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (j * THREADS + t < n) q[j] = load_corners(fcur, (size_t)(f0 + j * THREADS + t));
+        for (int w = g; w < nv; w += stride) vmin1[w] = VMIN_NONE;
+        if (blockIdx.x == 0) round_begin_block(R, st);
+    }
+    if (blockIdx.x == 0 && t < MATCH_SLOTS) nf_next[t * MATCH_PAD] = 0;
+    bids.clear();
+    M.begin(R, FIRST ? nullptr : done);
+    __syncthreads();
+    if constexpr (!FIRST) {
+        bool ok[PER];
+        Corners m[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            ok[j] = j * THREADS + t < n && q[j].a >= 0;
+            if (PER == 1 || ok[j]) m[j] = Corners{vmap[ok[j] ? q[j].a : 0], vmap[ok[j] ? q[j].b : 0], vmap[ok[j] ? q[j].c : 0]};
+        }
+        if (g < n_orig) cid[g] = vmap[label];
+        u64 bal[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (ok[j] && (m[j].a == m[j].b || m[j].b == m[j].c || m[j].a == m[j].c)) ok[j] = !M.is_done(R, done, m[j].a);
+            bal[j] = prim::ballot(ok[j]);
+            if (prim::lane_id() == 0) left[j][prim::wave_id()] = (int)__popcll(bal[j]);
+        }
+        __syncthreads();  // (behind it all of the tile has been read, too)
+        int before = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            int mine = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                if (w == prim::wave_id()) mine = before;
+                before += left[j][w];
+            }
+            if (ok[j]) {
+                const int p = mine + (int)prim::mask_below(bal[j]);
+                at[0][p] = m[j].a; at[1][p] = m[j].b; at[2][p] = m[j].c;
+                int* o = fcur + 3 * (size_t)(f0 + p);
+                o[0] = m[j].a; o[1] = m[j].b; o[2] = m[j].c;
+            }
+        }
+        if (t == 0 && n > 0) fcount_out[tile] = before;
+        n = before;
+        __syncthreads();
+    }
+    auto facet = [&](size_t f, const Corners& p) {
+        if (R.B > 1 && !M.is_active(R, p.a)) return;
+        const VertexWords A = load_vertex(vrec, p.a), B = load_vertex(vrec, p.b), C = load_vertex(vrec, p.c);
+        const u32 ab = cost_key(pair_cost<PLACE>(A, B, rcond_min)), bc = cost_key(pair_cost<PLACE>(B, C, rcond_min)),
+                  ca = cost_key(pair_cost<PLACE>(C, A, rcond_min));
+        fcost[f] = ab;
+        fcost[(size_t)F + f] = bc;
+        fcost[2 * (size_t)F + f] = ca;
+        auto bid = [&](int u, int v, u32 cost) -> u64 { return u == v ? VMIN_NONE : ((u64)cost << 32) | (u32)v; };
+        auto put = [&](int v, u64 x, u64 y) {
+            const u64 best = x < y ? x : y;
+            if (best != VMIN_NONE) bids.put(vmin0, nullptr, v, best);
+        };
+        put(p.a, bid(p.a, p.b, ab), bid(p.a, p.c, ca));
+        put(p.b, bid(p.b, p.c, bc), bid(p.b, p.a, ab));
+        put(p.c, bid(p.c, p.a, ca), bid(p.c, p.b, bc));
+    };
+    if constexpr (FIRST) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (j * THREADS + t < n) facet((size_t)(f0 + j * THREADS + t), q[j]);
+    } else {
+#pragma unroll 1
+        for (int i = t; i < n; i += THREADS) facet((size_t)(f0 + i), Corners{at[0][i], at[1][i], at[2][i]});
+    }
+    if constexpr (!FIRST)
+        for (int o = g + stride; o < n_orig; o += stride) cid[o] = vmap[cid[o]];
+    __syncthreads();
+    bids.flush(vmin0, nullptr);
+    if (!FIRST && t == 0 && n > 0) atomicAdd(&nf_slots[(blockIdx.x & (MATCH_SLOTS - 1)) * MATCH_PAD], n);
+}
+
+// The pairs formed so far, counted by their lower vertices, COUNT_VERTICES to a workgroup.  A vertex is paired if it has a partner already, or if
+// in the sub-round of this launch (whose bids are `cur`) the best bid on it names a vertex whose best bid names it; its partner is then being
+// written by other workgroups.  Old bids do no harm: an edge of which both ends hold the bid bid on both in one sub-round, in which it was accepted.
+constexpr int COUNT_VERTICES = 4 * BLOCK;
+__device__ __forceinline__ void count_paired(const SelArgs& A, const u64* __restrict__ cur, PairTally& tally, int part) {
+    const int nv = A.st->nv[A.cur], t = threadIdx.x;
+    const long long v0 = (long long)part * COUNT_VERTICES;
+    if (v0 >= nv) return;
+    int m[4];
+    u64 b[4], back[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int w = (int)min(v0 + j * BLOCK + t, (long long)nv - 1);
+        m[j] = A.mate[w];
+        b[j] = cur[w];
+    }
+    if (t == 0) tally.begin(A, (int)v0);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) back[j] = cur[m[j] < 0 && b[j] != VMIN_NONE ? (int)(u32)b[j] : 0];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const long long w = v0 + j * BLOCK + t;
+        const bool now = b[j] != VMIN_NONE && back[j] == ((b[j] & 0xFFFFFFFF00000000ull) | (u32)w);
+        const int p = m[j] >= 0 ? m[j] : now ? (int)(u32)b[j] : -1;
+        tally.count(A, w < nv && p > w, (int)w);
+    }
+    __syncthreads();
+    if (t == 0) tally.end(A);
+}
+
+// Sub-round 0 of such a round.  A vertex is paired if the best bid on it names a vertex whose best bid names it: said by the vertices
+// (which also start the pairs' arrays).  A facet's side stays live if neither of its ends is paired; the workgroup leaves its
+// live sides as a list, as select_listed_kernel takes them, without those that it also has the other way round (a table of
+// the sides from the lower to the higher end, in which one may take another's place: copies do no harm).
+template <int THREADS, int PER, bool APPEND>
+__global__ __launch_bounds__(THREADS) void select_facets_kernel(SelArgs A) {
+    constexpr int TILE = THREADS * PER, N = 3 * PER, SIDES = PER == 1 ? 1024 : 4 * THREADS;
+    const u64* __restrict__ cur = A.vmin[0];
+    u64* __restrict__ nxt = A.vmin[1];
+    __shared__ BidTable<PER == 1 ? 128 : THREADS / 2, THREADS> bids;
+    __shared__ u64 side[SIDES];
+    __shared__ PairTally tally;
+    __shared__ u32 smem[THREADS / 64];
+    const int t = threadIdx.x;
+    if (blockIdx.x == 0 && t == 0) A.st->sel_k = 1;
+    const int part = prim::xcd_item((int)blockIdx.x, A.parts);
+    if (part >= A.parts) return;
+    const long long f0 = (long long)part * TILE;
+    int n = (int)max(min(A.n_facets - f0, (long long)TILE), 0ll);
+    const int nv = A.st->nv[A.cur];
+    Corners q[PER];
+    u32 cost[PER][3];
+    auto load = [&](int j) {
+        const size_t f = (size_t)(j * THREADS + t < n ? f0 + j * THREADS + t : 0);
+        q[j] = load_corners(A.fcur, f);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) cost[j][c] = A.fcost[(size_t)c * A.n_facets + f];
+    };
+    if (PER == 1) load(0);  // (not yet known to be one)
+    if (A.fcount && n > 0) n = A.fcount[part];
+    if (PER > 1)
+#pragma unroll
+        for (int j = 0; j < PER; ++j) load(j);
+    const int per = ((nv - 1) / A.parts + 64) & ~63, v0 = (int)min((long long)part * per, (long long)nv), v1 = min(v0 + per, nv);
+    auto vertex_bid = [&](int w) -> u64 { return w < v1 ? cur[w] : VMIN_NONE; };
+    auto partner_bid = [&](u64 m) -> u64 { return cur[m != VMIN_NONE ? (int)(u32)m : 0]; };
+    auto vertex = [&](int w, u64 m, u64 back) {
+        const int p = (int)(u32)m;
+        const bool paired = m != VMIN_NONE && back == ((m & 0xFFFFFFFF00000000ull) | (u32)w);
+        if (w < v1) {
+            A.mate[w] = paired ? p : -1;
+            A.pcost[w] = paired && w < p ? (u32)(m >> 32) : PAIR_NONE;
+            A.vmin[2][w] = VMIN_NONE;
+        }
+        if (APPEND) tally.count(A, paired && w < p, w);
+    };
+    const u64 m0 = vertex_bid(v0 + t);
+    bids.clear();
+    for (int i = t; i < SIDES; i += THREADS) side[i] = 0;  // (no side's key)
+    if (APPEND && t == 0) tally.begin(A, min(v0, nv - 1));
+    u64 best[PER][3], back[PER][3];
+    bool ok[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        ok[j] = j * THREADS + t < n && q[j].a >= 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) best[j][c] = cur[ok[j] ? corner(q[j], c) : 0];
+    }
+    const u64 back0 = partner_bid(m0);
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) back[j][c] = partner_bid(best[j][c]);
+    __syncthreads();
+    vertex(v0 + t, m0, back0);
+    for (int w0 = v0 + THREADS; w0 < v1; w0 += THREADS) {  // (few facets)
+        const u64 m = vertex_bid(w0 + t);
+        vertex(w0 + t, m, partner_bid(m));
+    }
+    bool alive[N], up[N];
+    u64 key[N];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        bool open[3];
+        u64 bid_out[3], bid_in[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            open[c] = ok[j] && best[j][c] != VMIN_NONE && back[j][c] != ((best[j][c] & 0xFFFFFFFF00000000ull) | (u32)corner(q[j], c));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int d = c == 2 ? 0 : c + 1, a = corner(q[j], c), b = corner(q[j], d);
+            const bool on = open[c] && open[d] && a != b;
+            alive[3 * j + c] = on;
+            up[3 * j + c] = a < b;
+            key[3 * j + c] = ((u64)(u32)min(a, b) << A.vbits) | (u64)(u32)max(a, b);
+            bid_out[c] = on ? ((u64)cost[j][c] << 32) | (u32)b : VMIN_NONE;  // on its start, on its end
+            bid_in[d] = on ? ((u64)cost[j][c] << 32) | (u32)a : VMIN_NONE;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const u64 b = bid_out[c] < bid_in[c] ? bid_out[c] : bid_in[c];
+            if (b != VMIN_NONE) bids.put(nxt, nullptr, corner(q[j], c), b);
+        }
+    }
+    auto place_of = [&](u64 k) -> u32 { return (((u32)k ^ (u32)(k >> 32)) * 0x9E3779B1u >> 16) & (u32)(SIDES - 1); };
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (alive[i] && up[i]) side[place_of(key[i])] = key[i];
+    __syncthreads();
+    bool emit[N];
+    int place[N], total;
+#pragma unroll
+    for (int i = 0; i < N; ++i) emit[i] = alive[i] && (up[i] || side[place_of(key[i])] != key[i]);
+    live_places<N, THREADS / 64>(emit, smem, place, total);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (emit[i]) {
+            const size_t p = (size_t)part * (3 * TILE) + (size_t)place[i];
+            A.lkey[p] = key[i];
+            A.lcost[p] = cost[i / 3][i % 3];
+        }
+        if (APPEND) append_live(A, emit[i], key[i], cost[i / 3][i % 3], 0);
+    }
+    bids.flush(nxt, nullptr);
+    if (t == 0) {
+        if (part == 0 || f0 < A.n_facets) A.lcount[part] = total;
+        if (APPEND) tally.end(A);
+    }
+}
+
+// COPIES: an edge may be listed more than once (rounds by facets), so pairs are not counted edge by edge: the last sub-round, which lists for
+// the tail, has workgroups beside those with edges (list_groups of them) that count them vertex by vertex.
+template <bool SHUFFLE, bool COPIES, bool APPEND, bool TABLE>
+__global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, int part_shift, int group, int list_groups) {
     constexpr int N = 2;
+    constexpr bool COUNT = !COPIES;
     const u64* __restrict__ cur = A.vmin[k % 3];
     u64* __restrict__ nxt = A.vmin[(k + 1) % 3];
     u64* __restrict__ rst = A.vmin[(k + 2) % 3];
     __shared__ BidTable<TABLE ? LISTED_LINES : 1> bids;
     __shared__ PairTally tally;
     __shared__ u32 smem[prim::WAVES];
-    const int n = A.st->ne, t = threadIdx.x;
+    const int t = threadIdx.x;
+    if (COPIES && APPEND && (int)blockIdx.x >= list_groups) {
+        count_paired(A, cur, tally, (int)blockIdx.x - list_groups);
+        return;
+    }
+    const int tiles = COPIES ? A.list_tiles : (A.st->ne + LISTED_TILE - 1) / LISTED_TILE;
+    const int cap = COPIES ? A.list_tile : LISTED_TILE;
     if (blockIdx.x == 0 && t == 0) A.st->sel_k = k + 1;
-    const int parts = (int)(((long long)n + (1ll << span_shift) - 1) >> span_shift);
+    const int parts = (tiles + (1 << part_shift) - 1) >> part_shift;
     const int first = prim::xcd_tile(parts, group) * group;  // (the first of the workgroup's parts)
     if (first >= parts) return;
-    const size_t base = (size_t)first << span_shift;
+    const size_t part_size = (size_t)cap << part_shift, base = (size_t)first * part_size;
+    int* const count = A.lcount + ((size_t)first << part_shift);
     int upto[LISTED_GROUP_MAX], n_live = 0;
 #pragma unroll
     for (int g = 0; g < LISTED_GROUP_MAX; ++g)
-        upto[g] = n_live += g < group && first + g < parts ? A.lcount[(size_t)(first + g) << (span_shift - LISTED_TILE_SHIFT)] : 0;
+        upto[g] = n_live += g < group && first + g < parts ? count[(size_t)g << part_shift] : 0;
     if (n_live == 0) {
-        if (t == 0) A.lcount[base >> LISTED_TILE_SHIFT] = 0;
+        if (t == 0) *count = 0;
         return;
     }
     if (TABLE) bids.clear();
@@ -1290,16 +1623,13 @@ __global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, 
             size_t p = base + (size_t)at;
 #pragma unroll
             for (int g = 0; g + 1 < LISTED_GROUP_MAX; ++g)
-                if (at >= upto[g]) p = base + ((size_t)(g + 1) << span_shift) + (size_t)(at - upto[g]);
+                if (at >= upto[g]) p = base + (size_t)(g + 1) * part_size + (size_t)(at - upto[g]);
             E[j].key = A.lkey[p];
             E[j].cost = A.lcost[p];
-            E[j].e = A.lidx[p];
+            E[j].e = SHUFFLE ? A.lidx[p] : 0;
             E[j].on = q < n_live;
         }
-        if (q0 == 0 && t == 0) {
-            tally.mesh = A.mt.B <= 1 ? 0 : mesh_of(A.mt.voff, A.mt.B, (int)(E[0].key >> A.vbits));
-            tally.pairs = 0;
-        }
+        if (COUNT && q0 == 0 && t == 0) tally.begin(A, (int)(E[0].key >> A.vbits));
         judge_edges<SHUFFLE, N>(A, cur, E);
         bool alive[N];
         int place[N], total;
@@ -1309,12 +1639,12 @@ __global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, 
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             const JudgedEdge<SHUFFLE>& x = E[j];
-            tally.count(A, x.sel, x.u);
+            if (COUNT) tally.count(A, x.sel, x.u);
             if (x.alive) {
                 const size_t p = base + (size_t)(left + place[j]);
                 A.lkey[p] = x.key;
                 A.lcost[p] = x.cost;
-                A.lidx[p] = x.e;
+                if constexpr (SHUFFLE) A.lidx[p] = x.e;
                 if (TABLE) {
                     bids.put(nxt, rst, x.u, x.pu);
                     bids.put(nxt, rst, x.v, x.pv);
@@ -1332,8 +1662,8 @@ __global__ __launch_bounds__(BLOCK) void select_listed_kernel(SelArgs A, int k, 
     __syncthreads();
     if (TABLE) bids.flush(nxt, rst);
     if (t == 0) {
-        A.lcount[base >> LISTED_TILE_SHIFT] = left;
-        tally.end(A);
+        *count = left;
+        if (COUNT) tally.end(A);
     }
 }
 
@@ -1361,6 +1691,7 @@ struct TailLds {
     unsigned short lst[2][TAIL_MAX];
     int cnt[3];                  // live edges of the sub-round, of the next, of the one after that, in turn
     int seg_at[LIVE_SEGS + 1];   // first place of each segment's edges
+    int nh;
     int pairs[TAIL_LDS_MESHES];  // pairs this kernel formed, per mesh (batches of up to this many meshes)
 };
 static_assert(sizeof(TailLds) <= 160 * 1024, "one workgroup's LDS");
@@ -1410,8 +1741,15 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     // what earlier kernels have left: asked for now, used at the end
     constexpr int LIVE0 = (int)(offsetof(State, live) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int));
     static_assert(GO0 <= TAIL_THREADS, "one thread per word");
-    const int hdr_word = tid < GO0 ? reinterpret_cast<const int*>(A.st)[tid] : 0;
+    int hdr_word = tid < GO0 ? reinterpret_cast<const int*>(A.st)[tid] : 0;
+    constexpr int NH = (int)(offsetof(State, nh) / sizeof(int));
     const int slot_pairs = tid < A.mt.B * MATCH_SLOTS ? A.mt.mslots[(size_t)tid * MATCH_PAD] : 0;
+    if (A.nf_slots && w == 1) {  // (rounds by facets: half-edges there are)
+        int n = lane < MATCH_SLOTS ? A.nf_slots[lane * MATCH_PAD] : 0;
+#pragma unroll
+        for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) n += __shfl_xor(n, d, 64);
+        if (lane == 0) L.nh = 3 * n;
+    }
     if (w == 0) {  // the segments' places
         const int c = lane < LIVE_SEGS ? A.live_n[lane * MATCH_PAD] : 0;
         const bool full = __any(c > A.live_cap);
@@ -1435,9 +1773,12 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     if (lds_pairs)
         for (int b = tid; b < A.mt.B; b += TAIL_THREADS) L.pairs[b] = 0;
     __syncthreads();
+    if (A.nf_slots && tid == NH) hdr_word = L.nh;
     int n = L.cnt[0];
     if (n > TAIL_MAX) {  // too many: the host runs more grid-wide sub-rounds, the last of which lists again
         if (tid < LIVE_SEGS) A.live_n[tid * MATCH_PAD] = 0;
+        if (A.fcur)  // (rounds by facets: the last of them counts all pairs again)
+            for (int i = tid; i < A.mt.B * MATCH_SLOTS; i += TAIL_THREADS) A.mt.mslots[(size_t)i * MATCH_PAD] = 0;
         if (tid == 0) {
             A.st->live[0] = n;
             tail_set_guard(A, false);
@@ -1454,7 +1795,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         for (int j = lane; j < m; j += 64) {
             const LiveEdge E = A.live[(size_t)seg * A.live_cap + j];
             const int i = s0 + j, su = tail_slot(L.vkey, (int)(E.key >> A.vbits)), sv = tail_slot(L.vkey, (int)(E.key & vmask));
-            L.prio[i] = A.tb.priority(E.cost, E.e);
+            L.prio[i] = A.tb.on ? A.tb.priority(E.cost, E.e) : (u64)E.cost << 32;
             L.su[i] = (unsigned short)su;
             L.sv[i] = (unsigned short)sv;
             L.lst[0][i] = (unsigned short)i;
@@ -1464,20 +1805,20 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     }
     __syncthreads();
 
-    // an edge that holds the best bid at both ends is accepted
-    auto accept = [&](int i, u64 p, bool& sel, int& u) {
-        const int su = L.su[i], sv = L.sv[i];
-        sel = L.bid[su] == p && L.bid[sv] == p;
+    // the bids of an edge of priority p between the vertices u and v
+    auto bid_on_u = [&](u64 p, int v) -> u64 { return A.tb.on ? p : p | (u32)v; };
+    auto bid_on_v = [&](u64 p, int u) -> u64 { return A.tb.on ? p : p | (u32)u; };
+    // an edge that holds the best bid at both ends is accepted; of several copies of it one is told so
+    auto accept = [&](int i, int su, int sv, int u, int v, u64 p, bool& sel) {
+        sel = L.bid[su] == bid_on_u(p, v) && L.bid[sv] == bid_on_v(p, u);
         if (sel) {
-            u = L.vkey[su];
-            const int v = L.vkey[sv];
             A.mate[u] = v;
             A.mate[v] = u;
             A.pcost[min(u, v)] = (u32)(p >> 32);
             if (A.tb.on) A.ptie[min(u, v)] = (u32)p;
-            L.bid[su] = TAIL_PAIRED;  // (any other edge's bid differs from both values)
+            sel = atomicExch(&L.bid[su], TAIL_PAIRED) != TAIL_PAIRED;  // (any other edge's bid differs from both values)
             L.bid[sv] = TAIL_PAIRED;
-            if (A.mt.B > 1) L.prio[i] = TAIL_PAIRED;
+            if (A.mt.B > 1 && sel) L.prio[i] = TAIL_PAIRED;
         }
     };
     int wave_pairs = 0;  // (one mesh)
@@ -1492,18 +1833,19 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         const int padded = (n + 63) & ~63;  // whole waves run each step so that the ballots are uniform
         if (tid == 0) L.cnt[after] = 0;
         for (int j = tid; j < n; j += TAIL_THREADS) {
-            const int i = L.lst[side][j];
+            const int i = L.lst[side][j], su = L.su[i], sv = L.sv[i];
             const u64 p = L.prio[i];
-            atomicMin(&L.bid[L.su[i]], p);
-            atomicMin(&L.bid[L.sv[i]], p);
+            atomicMin(&L.bid[su], bid_on_u(p, L.vkey[sv]));
+            atomicMin(&L.bid[sv], bid_on_v(p, L.vkey[su]));
         }
         __syncthreads();
         for (int j = tid; j < padded; j += TAIL_THREADS) {
             bool sel = false;
             int u = 0;
             if (j < n) {
-                const int i = L.lst[side][j];
-                accept(i, L.prio[i], sel, u);
+                const int i = L.lst[side][j], su = L.su[i], sv = L.sv[i];
+                u = L.vkey[su];
+                accept(i, su, sv, u, L.vkey[sv], L.prio[i], sel);
             }
             tally(sel, u);
         }
@@ -1535,17 +1877,16 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
         bool alive = lane < n;
         const int i = alive ? L.lst[side][lane] : 0;
         const u64 p = alive ? L.prio[i] : 0;
-        const int su = alive ? L.su[i] : 0, sv = alive ? L.sv[i] : 0;
+        const int su = alive ? L.su[i] : 0, sv = alive ? L.sv[i] : 0, u = alive ? L.vkey[su] : 0, v = alive ? L.vkey[sv] : 0;
         while (__any(alive)) {
             if (alive) {
-                atomicMin(&L.bid[su], p);
-                atomicMin(&L.bid[sv], p);
+                atomicMin(&L.bid[su], bid_on_u(p, v));
+                atomicMin(&L.bid[sv], bid_on_v(p, u));
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             __builtin_amdgcn_wave_barrier();
             bool sel = false;
-            int u = 0;
-            if (alive) accept(i, p, sel, u);
+            if (alive) accept(i, su, sv, u, v, p, sel);
             tally(sel, u);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             __builtin_amdgcn_wave_barrier();
@@ -1588,6 +1929,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void select_tail_kernel(SelArgs A) {
     }
     if (tid == 0) {
         A.st->live[0] = 0;
+        if (A.nf_slots) A.st->nh = L.nh;
         tail_set_guard(A, true);
     }
     if (lds_pairs) {
@@ -2336,7 +2678,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                                                          int cur, int chunks, const int* __restrict__ tilesum, int prefixed,
                                                          int B, const int* __restrict__ voff_cur, int* __restrict__ voff_nxt,
                                                          const int* __restrict__ active, int* __restrict__ done,
-                                                         int* __restrict__ htab, int n_clear,
+                                                         int* __restrict__ htab, int n_clear, u64* __restrict__ vmin0,
                                                          float rcond_min, const int* __restrict__ arep,
                                                          const int* __restrict__ acnt, const u64* __restrict__ akey, int vbits,
                                                          const int* __restrict__ guard, HostSignal tell) {
@@ -2396,6 +2738,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
         if (!alive) continue;
         const int w = (int)i, nw = (int)incl - 1, m = mate[w];
         vmap[w] = nw;
+        if (vmin0) vmin0[nw] = VMIN_NONE;  // (the next round's first bids, see facet_costs_kernel)
         const float4* a = reinterpret_cast<const float4*>(&vin[w]);
         float4 r0 = a[0], r1 = a[1], r2 = a[2], r3 = a[3];
         if (m >= 0) {
@@ -2545,7 +2888,8 @@ struct FacetList {
 };
 
 template <int SEG>
-__global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restrict__ fcur, int F, FacetList L,
+__global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restrict__ fcur, int F, const int* __restrict__ fcount,
+                                                             int tile_shift, FacetList L, int* __restrict__ mslots,
                                                              const int* __restrict__ vmap, const State* st, int cur,
                                                              u32* __restrict__ htab, u32 hmask, int fbits, int B,
                                                              const int* __restrict__ voff, const int* __restrict__ done,
@@ -2587,13 +2931,17 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
         slot = (int)h;
         return true;
     };
+    if (B > 1)
+        for (int i = g; i < B * MATCH_SLOTS; i += stride) mslots[(size_t)i * MATCH_PAD] = 0;
     const int wave = __builtin_amdgcn_readfirstlane(g >> 6);
     for (long long s0 = (long long)wave * (64 * SEG); s0 < F; s0 += (long long)stride * SEG) {
         int n = 0;
-        for (int c = 0; c < SEG; ++c) {
+        const long long tile = s0 >> tile_shift;  // (facets stand at the front of their tiles, see facet_costs_kernel)
+        const long long end = fcount ? min((tile << tile_shift) + fcount[tile], (long long)F) : (long long)F;
+        for (int c = 0; c < SEG && s0 + c * 64 < end; ++c) {
             const long long f = s0 + c * 64 + lane;
             Corners q{-1, -1, -1};
-            if (f < F) q = renumbered(load_corners(fcur, (size_t)f));
+            if (f < end) q = renumbered(load_corners(fcur, (size_t)f));
             int slot = 0;
             const bool in = enter((int)f, q, slot);
             const u64 all = prim::ballot(in);
@@ -2610,7 +2958,7 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
         if (lane == 0) L.n[s0 / (64 * SEG)] = n;
     }
     for (int o = g; o < n_orig; o += stride) {
-        const int c = cid_in[o];
+        const int c = cid_in ? cid_in[o] : o;
         cid_out[o] = vmap ? vmap[c] : c;
     }
     if (verts_out)
@@ -2622,11 +2970,12 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
         }
 }
 
-// The survivors among the listed facets, counted per tile of BLOCK * CHUNKS facets (as a compaction's count pass does) and wave of it:
+// The survivors among the listed facets, counted per mesh (in its slots; the next kernel adds them up), per tile of BLOCK * CHUNKS facets (as a compaction's count pass does) and wave of it:
 // a facet survives if it is the first of its triple, the one that its slot holds.
 template <int CHUNKS>
 __global__ __launch_bounds__(BLOCK) void count_facets_kernel(FacetList L, int F, const u32* __restrict__ htab, int fbits,
-                                                             int* __restrict__ tilesum) {
+                                                             int* __restrict__ tilesum, int B, const int* __restrict__ voff,
+                                                             int* __restrict__ mslots) {
     constexpr int SEG = facet_segment(CHUNKS), SEGS = CHUNKS / SEG, SPAN = 64 * SEG;
     __shared__ u32 smem[prim::WAVES];
     const int w = prim::wave_id(), lane = prim::lane_id();
@@ -2635,6 +2984,10 @@ __global__ __launch_bounds__(BLOCK) void count_facets_kernel(FacetList L, int F,
 #pragma unroll
     for (int j = 0; j < SEGS; ++j) n[j] = at + j * SPAN < F ? L.n[at / SPAN + j] : 0;
     u32 kept = 0;
+    int mesh = -1, of_mesh = 0;  // of the wave's survivors, how many are of the mesh it is at
+    auto add_to_mesh = [&] {
+        if (of_mesh && lane == 0) atomicAdd(&mslots[((size_t)mesh * MATCH_SLOTS + (blockIdx.x & (MATCH_SLOTS - 1))) * MATCH_PAD], of_mesh);
+    };
 #pragma unroll
     for (int j = 0; j < SEGS; ++j)
         for (int i0 = 0; i0 < SPAN && (i0 == 0 || i0 < n[j]); i0 += 64) {  // (the first entries are asked for together with their number)
@@ -2645,8 +2998,24 @@ __global__ __launch_bounds__(BLOCK) void count_facets_kernel(FacetList L, int F,
                 k = h == FSLOT_KEEP || facet_slot_index(htab[max(h, 0)], fbits) == (u32)f;
                 L.keep[p] = k ? 1 : 0;
             }
-            kept += (u32)__popcll(prim::ballot(k));
+            u64 all = prim::ballot(k);
+            kept += (u32)__popcll(all);
+            if (B > 1) {
+                const int m = k ? mesh_of(voff, B, L.corners[3 * p]) : -1;
+                while (all) {  // a mesh after the other
+                    const int first = __shfl(m, __ffsll((long long)all) - 1, 64);
+                    const u64 same = prim::ballot(m == first);
+                    if (first != mesh) {
+                        add_to_mesh();
+                        mesh = first;
+                        of_mesh = 0;
+                    }
+                    of_mesh += (int)__popcll(same);
+                    all &= ~same;
+                }
+            }
         }
+    if (B > 1) add_to_mesh();
     if (lane == 0) {
         smem[w] = kept;
         L.wave_n[blockIdx.x * prim::WAVES + w] = (int)kept;
@@ -2655,11 +3024,11 @@ __global__ __launch_bounds__(BLOCK) void count_facets_kernel(FacetList L, int F,
     if (threadIdx.x == 0) tilesum[blockIdx.x] = (int)(smem[0] + smem[1] + smem[2] + smem[3]);
 }
 
-// ... and written out, in order.  foff_out[b] = those in front of mesh b, whose facets came at foff[b] ...
+// ... and written out, in order.
 template <int CHUNKS>
 __global__ __launch_bounds__(BLOCK) void facets_out_kernel(FacetList L, int F, const int* __restrict__ tilesum, int prefixed,
-                                                           const int* __restrict__ foff, int B, int* __restrict__ out,
-                                                           int* __restrict__ foff_out, int* __restrict__ nf_out) {
+                                                           int B, int* __restrict__ out, const int* __restrict__ mslots,
+                                                           int* __restrict__ mesh_facets, int* __restrict__ nf_out) {
     constexpr int SEG = facet_segment(CHUNKS), SEGS = CHUNKS / SEG, SPAN = 64 * SEG;
     __shared__ u32 smem[prim::WAVES];
     const int t = threadIdx.x, w = prim::wave_id(), lane = prim::lane_id(), tile = blockIdx.x;
@@ -2676,25 +3045,23 @@ __global__ __launch_bounds__(BLOCK) void facets_out_kernel(FacetList L, int F, c
         for (int j = t; j < tile; j += BLOCK) part += (u32)tilesum[j];
         run = prim::block_sum(part, smem);
     }
-    if (tile == (int)gridDim.x - 1 && t == 0) *nf_out = (int)run + ((waves.x + waves.y) + (waves.z + waves.w));
+    if (tile == (int)gridDim.x - 1 && t == 0) {
+        const int all = (int)run + ((waves.x + waves.y) + (waves.z + waves.w));
+        *nf_out = all;
+        if (B == 1) mesh_facets[0] = all;
+    }
+    if (B > 1)
+        for (int i = tile * BLOCK + t; i < B * MATCH_SLOTS; i += (int)gridDim.x * BLOCK) {  // (a mesh's slots in half a wave)
+            int n_b = mslots[(size_t)i * MATCH_PAD];
+#pragma unroll
+            for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) n_b += __shfl_xor(n_b, d, 64);
+            if ((i & (MATCH_SLOTS - 1)) == 0) mesh_facets[i / MATCH_SLOTS] = n_b;
+        }
     run += (u32)((w > 0 ? waves.x : 0) + (w > 1 ? waves.y : 0) + (w > 2 ? waves.z : 0));
 #pragma unroll
     for (int j = 0; j < SEGS; ++j) {
         const long long s0 = at + j * SPAN;
         if (s0 >= F) break;
-        for (int b0 = 0; b0 <= B; b0 += 64) {  // meshes that start in the segment
-            const int p = b0 + lane <= B ? foff[b0 + lane] : -1;
-            u64 here = prim::ballot((p > s0 && p <= s0 + SPAN) || (p == 0 && s0 == 0));
-            for (; here; here &= here - 1) {
-                const int b = __ffsll((long long)here) - 1, end = __shfl(p, b, 64);
-                u32 front = run;
-                for (int i0 = 0; i0 < n[j]; i0 += 64) {
-                    const bool in = i0 + lane < n[j];
-                    front += (u32)__popcll(prim::ballot(in && L.keep[s0 + i0 + lane] != 0 && L.facet[s0 + i0 + lane] < end));
-                }
-                if (lane == 0) foff_out[b0 + b] = (int)front;
-            }
-        }
         for (int i0 = 0; i0 < SPAN && (i0 == 0 || i0 < n[j]); i0 += 64) {
             const long long p = min(s0 + i0 + lane, (long long)F - 1);
             const unsigned char flag = L.keep[p];

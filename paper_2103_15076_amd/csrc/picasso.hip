@@ -71,6 +71,7 @@ struct picasso_ctx {
     u32* ptie() const { return reinterpret_cast<u32*>(vmap); }  // (vmap is free between a round's first kernel and its contraction)
     int* vmap = nullptr;
     int* list = nullptr;
+    int* fcount() const { return list; }  // per tile of facets, how many there are (rounds by facets, which list no edges there)
     unsigned char* estate = nullptr;
     int* htab = nullptr;
     unsigned char* keep = nullptr;
@@ -91,9 +92,10 @@ struct picasso_ctx {
     // per-mesh tables
     int* voff[2] = {nullptr, nullptr};
     int* foff = nullptr;
-    int* foff_out = nullptr;
+    int* mesh_facets = nullptr;
     int* target = nullptr;
-    int* active = nullptr;
+    int* active[2] = {nullptr, nullptr};  // by the round's parity
+    int* nf_slots[2] = {nullptr, nullptr};  // facets that have not collapsed, by the round's parity (see facet_costs_kernel)
     int* stuck = nullptr;
     int* done = nullptr;   // mesh has taken part in a round that contracted
     int* nrem = nullptr;
@@ -150,7 +152,7 @@ struct picasso_ctx {
 namespace {
 
 constexpr int HDR_STATE_INTS = (int)(sizeof(State) / sizeof(int));
-constexpr size_t hdr_ints(size_t b) { return HDR_STATE_INTS + 9 * b + 3; }  // for up to b meshes (see carve)
+constexpr size_t hdr_ints(size_t b) { return HDR_STATE_INTS + 10 * b + 3; }  // for up to b meshes (see carve)
 constexpr int SEQ_CHECK_WORD = 16;  // within the sequence word's 32-int area: the selection tail's copy of the number (a cache line further)
 
 struct Carver {
@@ -182,7 +184,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     picasso_ctx dummy;
     picasso_ctx* x = c ? c : &dummy;
     // header: everything the host uploads or reads back, contiguous so that one copy moves it.
-    //   [State][matched B][foff_out B+1] | [voff0 B+1][foff B+1][target B][stuck B][active B][done B]
+    //   [State][matched B][mesh_facets B+1] | [voff0 B+1][foff B+1][target B][stuck B][active0 B][active1 B][done B]
     //   <-------- read back ----------->
     int* hdr = cv.take<int>(hdr_ints(b));
     x->hdr = hdr;
@@ -190,12 +192,13 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     if (hdr) {
         int* q = hdr + HDR_STATE_INTS;
         x->matched = q; q += b;
-        x->foff_out = q; q += b + 1;
+        x->mesh_facets = q; q += b + 1;
         x->voff[0] = q; q += b + 1;
         x->foff = q; q += b + 1;
         x->target = q; q += b;
         x->stuck = q; q += b;
-        x->active = q; q += b;
+        x->active[0] = q; q += b;
+        x->active[1] = q; q += b;
         x->done = q; q += b;
     }
     x->vrec[0] = cv.take<VRec>(n);
@@ -243,6 +246,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->mslots = cv.take<int>(b * MATCH_SLOTS * MATCH_PAD);
     x->live = cv.take<LiveEdge>((size_t)LIVE_SEGS * TAIL_MAX);
     x->live_n = cv.take<int>(LIVE_SEGS * MATCH_PAD);
+    for (int i = 0; i < 2; ++i) x->nf_slots[i] = cv.take<int>(MATCH_SLOTS * MATCH_PAD);
     x->abid = cv.take<u64>(n);
     x->arep = cv.take<int>(n);
     x->acnt = cv.take<int>(n);
@@ -403,7 +407,8 @@ QuadricRows quadric_rows(picasso_ctx* c, const float* d_verts, int N, int F) {
 }
 
 RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
-    return RoundTab{B, c->voff[cur_], c->target, c->active, c->stuck, c->nrem, c->matched, c->mslots, c->live_n, round_ == 0};
+    return RoundTab{B, c->voff[cur_], c->target, c->active[round_ & 1], c->active[(round_ & 1) ^ 1], c->stuck, c->nrem, c->matched, c->mslots,
+                    c->live_n, round_ == 0};
 }
 
 // First kernel of a round after the first: facets and labels follow the last contraction, the edges' digits are counted.
@@ -482,28 +487,63 @@ void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>&
 #undef PICASSO_UNIQUE_LINES
 }
 
+// Facets to a tile in the rounds by facets: small ones while the workgroups are to fill the chip, large ones (fewer copies of an edge, lists and
+// tables per workgroup that serve more) beyond 2^20 facets.  Whole calls with small | large tiles, us: one mesh of 227 k facets 190 | 222, 800 k
+// 391 | 408, 1.4 M 503 | 502, 2.4 M 721 | 702, 20 M 5173 | 4720; 16 meshes of 750 k together 315 | 313, 1.13 M 408 | 394, 1.9 M 629 | 567.
+constexpr int FACET_TILE_SMALL = 256, FACET_TILE_LARGE = 1024;
+constexpr int FACET_TILE_SMALL_MAX = 1 << 20;
+inline int facet_tile(int F) { return F <= FACET_TILE_SMALL_MAX ? FACET_TILE_SMALL : FACET_TILE_LARGE; }
+inline int facet_tiles(int F) { return std::max((F + facet_tile(F) - 1) / facet_tile(F), 1); }
+// Workgroups of facets and vertices that a round of at most nv vertices has.
+inline int facet_parts(int F, int nv) { return std::max(facet_tiles(F), (nv + 1023) / 1024); }
+// Where a round's contraction leaves its map of the vertices.  The first round's is the labels of the input vertices at the same time; rounds by
+// facets leave it where the labels are.
+int* round_map(picasso_ctx* c, bool by_facets, int round_) { return by_facets && round_ == 0 ? c->cid : c->vmap; }
+void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, int N, int F) {
+    const int grid = prim::xcd_grid(round_ == 0 && facet_tile(F) > 512 ? std::max((F + 511) / 512, 1) : facet_parts(F, N)), par = round_ & 1;
+#define PICASSO_FACET_COSTS(PLACE, THREADS, PER, FIRST)                                                                              \
+    facet_costs_kernel<PLACE, THREADS, PER, FIRST><<<grid, THREADS, 0, s>>>(                                                            \
+        c->fcur, F, c->st, cur_, c->vrec[cur_], c->vmin[0], c->vmin[1], c->ecost, round_tab(c, B, round_, cur_), round_map(c, true, round_ - 1), c->done, \
+        c->cid, round_ > 1 ? N : 0, c->opt_rcond_min, round_ > 1 ? c->fcount() : nullptr, c->fcount(), c->nf_slots[par], c->nf_slots[par ^ 1])
+#define PICASSO_FACET_COSTS_PER(PLACE, THREADS, PER)                         \
+    do {                                                                \
+        if (round_ == 0) PICASSO_FACET_COSTS(PLACE, 256, PER == 1 ? 1 : 2, true);      \
+        else PICASSO_FACET_COSTS(PLACE, THREADS, PER, false);              \
+    } while (0)
+#define PICASSO_FACET_COSTS_PLACE(PLACE)                                        \
+    do {                                                                        \
+        if (facet_tile(F) == FACET_TILE_SMALL) PICASSO_FACET_COSTS_PER(PLACE, 256, 1);       \
+        else PICASSO_FACET_COSTS_PER(PLACE, 256, 4);                                \
+    } while (0)
+    if (c->opt_placement == PLACE_INVERSE) PICASSO_FACET_COSTS_PLACE(PLACE_INVERSE);
+    else PICASSO_FACET_COSTS_PLACE(PLACE_MEAN);
+#undef PICASSO_FACET_COSTS_PLACE
+#undef PICASSO_FACET_COSTS_PER
+#undef PICASSO_FACET_COSTS
+}
+
 // Up to this many facets the facet set is cleared by the call's first kernel (see launch_init).
 constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 
 // The validating kernel, instantiated for the sorts its keys go to.  work: rounds (or S0) follow; edges: the first round's
-// set-up and edges as well.
+// set-up as well (EDGES_BY_FACETS), and its edges' digits (EDGES_SORTED).
 int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, const int32_t* d_facets, int F, int B,
-                bool work, bool edges, const HeaderInit& init = HeaderInit{}, const FewMeshes& tables = FewMeshes{}) {
+                bool work, int edges, const HeaderInit& init = HeaderInit{}, const FewMeshes& tables = FewMeshes{}) {
     const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F, 3ll * F);
     if (work && c->hist_dirty)  // (a call ended between a count of its edges and their sort)
         prim::fill_u32_kernel<<<prim::MSD_ZERO_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, prim::MSD_ZERO_WORDS, 0u);
     if (work) {
-        c->hist_dirty = edges && F > 0;
+        c->hist_dirty = edges == EDGES_SORTED && F > 0;
         clear_wide_counts(s, I);
-        if (edges) clear_wide_counts(s, E);
+        if (edges == EDGES_SORTED) clear_wide_counts(s, E);
     }
     float4* planes = work ? facet_planes(c) : nullptr;
     // the facet set that the end of the call uses (larger ones are cleared by the last contraction, when fewer facets are left)
     const int n_clear = F <= CLEAR_AHEAD_MAX_FACETS ? (int)facet_slots((size_t)F) : 0;
 #define PICASSO_INIT_TABLES(COUNT, TABLES)                                                                                     \
     init_kernel<COUNT><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
-        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], c->cid, c->fcur, incidence_fbits(F), digit_count(I),      \
-        digit_count(E), edges ? 1 : 0, E.key_bits / 2, c->st, init, TABLES, planes, c->htab, n_clear, c->vmin[0], c->vmin[1],   \
+        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], edges == EDGES_BY_FACETS ? nullptr : c->cid, c->fcur, incidence_fbits(F), digit_count(I),      \
+        digit_count(E), edges, E.key_bits / 2, c->st, init, TABLES, planes, c->htab, n_clear, c->vmin[0], c->vmin[1],   \
         c->mate, c->pcost(), round_tab(c, B, 0, 0))
 #define PICASSO_INIT(COUNT)                                             \
     do {                                                                \
@@ -580,7 +620,7 @@ hipError_t wait_for_signal(picasso_ctx* c, hipStream_t s, const HostSignal& sig)
     return hipStreamSynchronize(s);
 }
 
-// [State][matched][foff_out] brought to the pinned read-back area by a one-workgroup kernel that then
+// [State][matched][mesh_facets] brought to the pinned read-back area by a one-workgroup kernel that then
 // tells the host; returns when the host has them (and everything queued before has been executed).
 int read_header(picasso_ctx* c, hipStream_t s, u32* zero = nullptr, int n_zero = 0) {
     const HostSignal done = next_signal(c);
@@ -651,6 +691,28 @@ int pair_budget(picasso_ctx* c, hipStream_t s, const TieBreak& tb, int B, const 
 void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bool last, int round) {
     const bool listed = sa.bound >= LISTED_MIN_EDGES;
     const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, k == 0); /* (the first only) */
+    const int shift = listed_part_shift(k), group = listed_group(k);
+    if (sa.fcur) {
+        if (k == 0) {
+            const int grid = prim::xcd_grid(sa.parts);
+            const bool small = facet_tile(sa.n_facets) == FACET_TILE_SMALL;
+            if (small && last) select_facets_kernel<256, 1, true><<<grid, 256, 0, s>>>(sa);
+            else if (small) select_facets_kernel<256, 1, false><<<grid, 256, 0, s>>>(sa);
+            else if (last) select_facets_kernel<512, 2, true><<<grid, 512, 0, s>>>(sa);
+            else select_facets_kernel<512, 2, false><<<grid, 512, 0, s>>>(sa);
+            return;
+        }
+        const int parts = ((sa.list_tiles - 1) >> shift) + 1, groups = prim::xcd_grid((parts + group - 1) / group);
+        const int grid = groups + (last ? (sa.nv + COUNT_VERTICES - 1) / COUNT_VERTICES : 0);
+        if (k <= 2) {
+            if (last) select_listed_kernel<false, true, true, true><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, groups);
+            else select_listed_kernel<false, true, false, true><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, groups);
+        } else {
+            if (last) select_listed_kernel<false, true, true, false><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, groups);
+            else select_listed_kernel<false, true, false, false><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, groups);
+        }
+        return;
+    }
 #define PICASSO_SUBROUND(SHUFFLE, APPEND)                                                                                   \
     do {                                                                                                                     \
         if (!listed) {                                                                                                       \
@@ -658,11 +720,10 @@ void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bo
         } else if (k == 0) {                                                                                                 \
             select_first_kernel<SHUFFLE, APPEND><<<prim::xcd_grid((sa.bound + LISTED_TILE - 1) / LISTED_TILE), BLOCK, 0, s>>>(sa); \
         } else {                                                                                                             \
-            const int span = listed_span(k), group = listed_group(k);                                                        \
-            const long long parts = (((long long)sa.bound - 1) >> span) + 1;                                                 \
-            const int grid = prim::xcd_grid((int)((parts + group - 1) / group));                                             \
-            if (k <= 2) select_listed_kernel<SHUFFLE, APPEND, true><<<grid, BLOCK, 0, s>>>(sa, k, span, group);              \
-            else select_listed_kernel<SHUFFLE, APPEND, false><<<grid, BLOCK, 0, s>>>(sa, k, span, group);                    \
+            const int parts = (((sa.bound - 1) / LISTED_TILE) >> shift) + 1;                                                 \
+            const int grid = prim::xcd_grid((parts + group - 1) / group);                                                    \
+            if (k <= 2) select_listed_kernel<SHUFFLE, false, APPEND, true><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, grid); \
+            else select_listed_kernel<SHUFFLE, false, APPEND, false><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, grid);       \
         }                                                                                                                    \
     } while (0)
     if (sa.tb.on) {
@@ -793,10 +854,12 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // input, not on each other: they share their launches.  (Not when stage times are being recorded, to keep them
     // attributable, and in a call whose kernels are bracketed by events: a bracketed kernel then has the chip to itself,
     // and its duration is its own.)
-    const bool together = work && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
+    // The rounds go by facets where nothing needs the edges' numbers (see facet_costs_kernel).
+    const bool by_facets = c->opt_shuffle_seed == 0 && !c->opt_absorb && !stats;
+    const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
                           edge_sort(c, N, F, F, 3ll * F).half == incidence_sort(c, N, F).half;
     tm.begin(0, PICASSO_ST_QUADRICS);
-    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, work, hinit, tables);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, !work ? EDGES_NONE : by_facets ? EDGES_BY_FACETS : EDGES_SORTED, hinit, tables);
     if (rc != PICASSO_OK) return rc;
     if (work) {
         const prim::KeySort<u64> I = incidence_sort(c, N, F);
@@ -818,23 +881,28 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     int round = 0;
     int ne_prev = 0, nv_prev = 0;  // edge and vertex counts of the round before
     bool validated = false;
+    bool compacted = false;   // collapsed facets have left their tiles
     bool renumbered = false;  // the facets and labels still have the numbers from before the last contraction
 
     while (work && (c->opt_max_rounds < 0 || round < c->opt_max_rounds)) {
         const int H = 3 * nf_bound;
         const int vbits = edge_vertex_bits(nv_total, H);
-        MeshTab mt{B, c->voff[cur], c->target, c->active, c->nrem, c->matched, c->mslots};
+        MeshTab mt{B, c->voff[cur], c->target, c->active[round & 1], c->nrem, c->matched, c->mslots};
 
         // ---- S1 (+S2): edges and costs
         tm.begin(round, PICASSO_ST_EDGES);
-        const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F, round > 0 ? expected_half_edges(H, ne_prev, nv_prev - nv_total) : H);
-        if (round > 0) launch_edge_keys(c, s, B, round, cur, E, N, F);
-        if (!(round == 0 && together) && H > 0 && !sort_edges(c, s, E, round)) return PICASSO_ERR_HIP;
-        renumbered = false;
-        {
+        if (by_facets) {
+            const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);
+            launch_facet_costs(c, s, B, round, cur, N, F);
+            compacted = round > 0;
+        } else {
+            const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F, round > 0 ? expected_half_edges(H, ne_prev, nv_prev - nv_total) : H);
+            if (round > 0) launch_edge_keys(c, s, B, round, cur, E, N, F);
+            if (!(round == 0 && together) && H > 0 && !sort_edges(c, s, E, round)) return PICASSO_ERR_HIP;
             const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);
             launch_unique_cost(c, s, E, H, mt, tb, c->vrec[cur]);
         }
+        renumbered = false;
         tm.end();
 
         // The contraction.  `guarded`: queued behind the selection tail before the host
@@ -863,10 +931,10 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const int prefixed = tiles > prim::COMPACT_MAX_SUMMED_TILES;
             static_assert(CONTRACT_COUNTS_MAX <= BLOCK * prim::COMPACT_MAX_SUMMED_TILES, "tiles of one chunk");
 #define PICASSO_CONTRACT(PLACE, ABSORB, COUNTS, RCOND)                                                               \
-    contract_kernel<PLACE, ABSORB, COUNTS><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, c->vmap, c->st, cur,  \
+    contract_kernel<PLACE, ABSORB, COUNTS><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, round_map(c, by_facets, round), c->st, cur,  \
                                                            chunks, c->tilesum, prefixed, B, c->voff[cur],             \
-                                                           c->voff[nxt], c->active, c->done, c->htab, (int)clear,     \
-                                                           RCOND, c->arep, c->acnt, akeys, vbits, guard, tell)
+                                                           c->voff[nxt], c->active[round & 1], c->done, c->htab, (int)clear, \
+                                                           by_facets ? c->vmin[0] : nullptr, RCOND, c->arep, c->acnt, akeys, vbits, guard, tell)
             if (c->opt_placement == PLACE_INVERSE) {
                 if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, false, c->opt_rcond_min);
                 else if (counts) PICASSO_CONTRACT(PLACE_INVERSE, false, true, c->opt_rcond_min);
@@ -922,6 +990,15 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         sa.lcost = c->val32;
         sa.lidx = c->list;
         sa.lcount = c->fslot;
+        sa.list_tile = by_facets ? 3 * facet_tile(F) : LISTED_TILE;
+        sa.list_tiles = by_facets ? facet_tiles(F) : 0;
+        sa.fcur = by_facets ? c->fcur : nullptr;
+        sa.fcost = c->ecost;
+        sa.fcount = round > 0 ? c->fcount() : nullptr;
+        sa.n_facets = F;
+        sa.parts = facet_parts(F, nv_total);
+        sa.nv = nv_total;
+        sa.nf_slots = by_facets && round > 0 ? c->nf_slots[round & 1] : nullptr;
         sa.st = c->st;
         sa.mt = mt;
         sa.vbits = vbits;
@@ -944,7 +1021,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             // live edges fall by about 2.8x, 2.7x, 3.2x, 4x, 5x, ... per sub-round on meshes with varied costs
             static const int decay_x10[] = {28, 27, 32, 40, 50, 60};
             int wide = 0;
-            for (long long l = live_est; l > TAIL_MAX; ++wide) l = l * 10 / decay_x10[std::min(wide, 5)];
+            for (long long l = by_facets ? live_est * 5 / 4 : live_est; l > TAIL_MAX; ++wide) l = l * 10 / decay_x10[std::min(wide, 5)];
             wide = std::min<int>(wide, (int)std::max<int64_t>(1, c->opt_subround_batch));
             wide = std::max(wide, 1);  // (the last of them lists what it leaves live for the tail)
             for (int j = 0; j < wide; ++j) launch_subround(c, s, sa, sel_k + j, j == wide - 1, round);
@@ -997,14 +1074,15 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         }
         for (int b = 0; b < B; ++b) h_matched[b] = c->h_pin[HDR_STATE_INTS + b];
         const int nf_now = round == 0 ? F : hst->nh / 3;
+        const int ne_now = by_facets ? (int)(3ll * nf_now / 2) : hst->ne;  // (about)
         nf_bound = std::min(nf_bound, nf_now);
         if (c->n_rounds_noted < NF_ROUND_CAP) {
             c->nf_round[c->n_rounds_noted] = nf_now;
             c->nv_round[c->n_rounds_noted] = nv_total;
-            c->ne_round[c->n_rounds_noted] = hst->ne;
+            c->ne_round[c->n_rounds_noted] = ne_now;
             ++c->n_rounds_noted;
         }
-        ne_prev = hst->ne;
+        ne_prev = ne_now;
         nv_prev = nv_total;
         if (stats && round < PICASSO_STATS_ROUNDS) {
             stats->nv[round] = nv_total;
@@ -1091,13 +1169,18 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     int* const spare = reinterpret_cast<int*>(c->key64[0]);
     const size_t wave_at = ((size_t)F + 3) / 4 * 4, n_at = wave_at + prim::WAVES * (size_t)prim::compact_tiles(std::max(F, 1), chunks);
     const FacetList fl{c->fmap, c->fslot, spare, c->keep, spare + n_at, spare + wave_at};
+    // (facets of rounds by facets stand at the front of their tiles once a second round has begun)
+    const int* const fcount = compacted ? c->fcount() : nullptr;
+    const int tile_shift = ceil_log2(facet_tile(F));
+    // (null: what a vertex's label is in front of the last contraction is its number; see round_map)
+    const int* const labels = by_facets && (round == 0 || (round == 1 && renumbered)) ? nullptr : c->cid;
     tm.begin(std::max(round - 1, 0), PICASSO_ST_FACETS);
     {
         const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round - 1, renumbered);
 #define PICASSO_FINAL_FACETS(SEG)                                                                                       \
     final_facets_kernel<SEG><<<grid_for(std::max(N, F), 8192), BLOCK, 0, s>>>(                                          \
-        c->fcur, F, fl, renumbered ? c->vmap : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur],     \
-        c->done, c->cid, drop ? c->cid : d_cluster_id, N, c->vrec[cur], drop ? nullptr : d_verts_out)
+        c->fcur, F, fcount, tile_shift, fl, c->mslots, renumbered ? round_map(c, by_facets, round - 1) : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur],     \
+        c->done, labels, drop ? c->cid : d_cluster_id, N, c->vrec[cur], drop ? nullptr : d_verts_out)
         switch (facet_segment(chunks)) {
             case 1: PICASSO_FINAL_FACETS(1); break;
             case 2: PICASSO_FINAL_FACETS(2); break;
@@ -1105,14 +1188,15 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         }
 #undef PICASSO_FINAL_FACETS
     }
+    if (F == 0) prim::fill_u32_kernel<<<grid_for(B), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->mesh_facets), B, 0u);
     if (F > 0) {
         const int tiles = prim::compact_tiles(F, chunks);
         int* const out = drop ? c->fcur : d_facets_out;
 #define PICASSO_FACETS_OUT(CHUNKS)                                                                                      \
-    count_facets_kernel<CHUNKS><<<tiles, BLOCK, 0, s>>>(fl, F, htab, fbits, c->tilesum);                                \
+    count_facets_kernel<CHUNKS><<<tiles, BLOCK, 0, s>>>(fl, F, htab, fbits, c->tilesum, B, c->voff[cur], c->mslots);         \
     prim::compact_scan_sums(s, nullptr, F, c->tilesum);                                                                 \
     facets_out_kernel<CHUNKS><<<tiles, BLOCK, 0, s>>>(fl, F, c->tilesum, tiles > prim::COMPACT_MAX_SUMMED_TILES,        \
-                                                      c->foff, B, out, c->foff_out, &c->st->nf)
+                                                      B, out, c->mslots, c->mesh_facets, &c->st->nf)
         switch (chunks) {
             case 1: PICASSO_FACETS_OUT(1); break;
             case 4: PICASSO_FACETS_OUT(4); break;
@@ -1142,7 +1226,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     if (stats) HIP_TRY(c, hipEventSynchronize(c->ev_total[1]));
     else if (c->kt.nrec > 0) HIP_TRY(c, hipEventSynchronize(c->kt_pool[c->kt.recs[c->kt.nrec - 1].e1]));
     HIP_TRY(c, hipGetLastError());
-    const int* h_foff = c->h_pin + HDR_STATE_INTS + c->cap_b;
+    const int* h_nf = c->h_pin + HDR_STATE_INTS + c->cap_b;
 
     // the bracketed kernels: event times and the algorithmic bytes of their rounds (see picasso_timed_kernel)
     for (int i = 0; i < c->kt.nrec; ++i) {
@@ -1155,8 +1239,12 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             double bytes = 0.0;
             switch (kernel) {
                 case PICASSO_KERNEL_SORT: bytes = 4.0 * H + 4.0 * ne; break;
-                case PICASSO_KERNEL_UNIQUE_COST: bytes = 17.0 * ne + 72.0 * nv; break;
-                case PICASSO_KERNEL_SUBROUND0: bytes = 14.0 * ne + 24.0 * nv; break;
+                case PICASSO_KERNEL_UNIQUE_COST:
+                    if (!by_facets) bytes = 17.0 * ne + 72.0 * nv;
+                    else if (rd == 0) bytes = 24.0 * nf + 72.0 * nv;
+                    else bytes = 12.0 * (double)c->nf_round[rd - 1] + 24.0 * nf + 4.0 * (double)c->nv_round[rd - 1] + 80.0 * nv + (rd > 1 ? 8.0 * (double)N : 0.0);
+                    break;
+                case PICASSO_KERNEL_SUBROUND0: bytes = by_facets ? 24.0 * nf + 32.0 * nv : 14.0 * ne + 24.0 * nv; break;
                 case PICASSO_KERNEL_FACET_INSERT:  // (the last round's is another kernel)
                     if (rd + 1 < c->n_rounds_noted) bytes = 24.0 * nf + 4.0 * nv + 8.0 * (double)N + 24.0 * (double)c->nv_round[rd + 1];
                     else bytes = 28.0 * nf + 4.0 * nv + 8.0 * (double)N + (drop ? 0.0 : 28.0 * (double)nv_total);
@@ -1174,7 +1262,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     for (int b = 0; b < B; ++b) {
         // (with degenerated vertices dropped, the last kernels have left the meshes' counts where the pair counts were)
         h_nv_out[b] = c->opt_drop_degenerated ? c->h_pin[HDR_STATE_INTS + b] : nvb[b];
-        h_nf_out[b] = h_foff[b + 1] - h_foff[b];
+        h_nf_out[b] = h_nf[b];
         if (nvb[b] > target_nv[b] && (c->opt_max_rounds < 0 || stuck[b])) warn = PICASSO_WARN_BUDGET_UNMET;
     }
     if (stats) {
@@ -1489,7 +1577,7 @@ int picasso_vertex_quadrics(picasso_ctx* c, void* stream, const float* d_verts, 
     int64_t n64, f64;
     int rc = upload_header(c, s, 1, &N, &F, &big, &n64, &f64);
     if (rc != PICASSO_OK) return rc;
-    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true, false);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true, EDGES_NONE);
     if (rc != PICASSO_OK) return rc;
     rc = checked_vertex_quadrics(c, s, d_verts, N, F);
     if (rc != PICASSO_OK) return rc;
@@ -1510,13 +1598,13 @@ int picasso_edge_costs(picasso_ctx* c, void* stream, const float* d_verts, int32
     int64_t n64, f64;
     int rc = upload_header(c, s, 1, &N, &F, &one, &n64, &f64);
     if (rc != PICASSO_OK) return rc;
-    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true, true);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, 1, true, EDGES_SORTED);
     if (rc != PICASSO_OK) return rc;
     State* hst = reinterpret_cast<State*>(c->h_pin);
     rc = checked_vertex_quadrics(c, s, d_verts, N, F);
     if (rc != PICASSO_OK) return rc;
     const int H = 3 * F, vbits = edge_vertex_bits(N, H);
-    MeshTab mt{1, c->voff[0], c->target, c->active, c->nrem, c->matched, c->mslots};
+    MeshTab mt{1, c->voff[0], c->target, c->active[0], c->nrem, c->matched, c->mslots};
     const prim::KeySort<u64> E = edge_sort(c, N, F, F, 3ll * F);
     if (F > 0) {
         if (!sort_edges(c, s, E, 0)) return PICASSO_ERR_HIP;

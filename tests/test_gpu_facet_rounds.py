@@ -1,0 +1,97 @@
+"""Rounds by facets (no list of the distinct edges) against the oracle: tiles' edges, copies of an edge in one tile and in several,
+meshes that end within a tile, more meshes than the workgroups keep in LDS, and selections that hand back to the host."""
+import numpy as np
+import pytest
+
+from paper_2103_15076_amd import meshgen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def pk():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2103_15076_amd
+    return paper_2103_15076_amd
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def same(got, ref):
+    st, vo, fo, cid = got[:4]
+    assert st == ref["status"]
+    np.testing.assert_array_equal(cid.cpu().numpy(), ref["cluster_id"])
+    np.testing.assert_array_equal(fo.cpu().numpy(), ref["facets"])
+    np.testing.assert_array_equal(vo.cpu().numpy().view(np.uint32), ref["verts"].view(np.uint32))
+
+
+def lattice(n_facets, seed, turned=0.0, repeated=0.0):
+    """A noisy lattice cut to n_facets facets; some wound the other way round (both copies of an edge run the same way then), some there
+    a second time (edges with more than two facets)."""
+    rng = np.random.default_rng(seed)
+    w = int(np.sqrt(n_facets / 2)) + 2
+    V, F = meshgen.noisy_grid(w, w, seed=seed)
+    F = F[:n_facets].copy()
+    flip = rng.random(len(F)) < turned
+    F[flip] = F[flip][:, ::-1]
+    again = rng.random(len(F)) < repeated
+    F[again] = F[rng.integers(0, len(F), again.sum())]
+    return V, F
+
+
+@pytest.mark.parametrize("n_facets", [1, 2, 255, 256, 257, 513, 1024, 5000])
+@pytest.mark.parametrize("turned,repeated", [(0.0, 0.0), (0.5, 0.1)])
+def test_tile_edges_and_copies(pk, oracle, n_facets, turned, repeated):
+    V, F = lattice(n_facets, 7 + n_facets, turned, repeated)
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    for keep in (0.6, 0.15):
+        target = max(1, int(len(V) * keep))
+        same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target))
+
+
+@pytest.mark.parametrize("n_facets,turned,repeated,batch", [((1 << 20) - 1, 0.0, 0.0, 16), ((1 << 20) + 1, 0.3, 0.05, 16), ((1 << 20) + 1025, 0.3, 0.05, 2)])
+def test_large_tiles(pk, oracle, n_facets, turned, repeated, batch):
+    """Either side of where tiles grow; with two sub-rounds per batch the tail hands back and the pairs are counted again."""
+    V, F = lattice(n_facets, 3, turned, repeated)
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    ctx.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, batch)
+    target = len(V) // 4
+    same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target))
+
+
+@pytest.mark.parametrize("sizes", [[300, 1, 700, 90, 2000] * 3, [40] * 70, [130, 20, 260] * 400])
+@pytest.mark.parametrize("batch", [16, 1])
+def test_meshes_end_within_tiles(pk, oracle, sizes, batch):
+    """Up to 64 meshes in LDS, more, and more than the tail tallies; meshes that need no round keep their repeated facets."""
+    parts = [lattice(n, k, 0.3, 0.1) for k, n in enumerate(sizes)]
+    nv, nf = [len(v) for v, _ in parts], [len(f) for _, f in parts]
+    base = np.concatenate([[0], np.cumsum(nv)])
+    V = np.concatenate([v for v, _ in parts])
+    F = np.concatenate([f + np.int32(base[k]) for k, (_, f) in enumerate(parts)])
+    target = [n if k % 4 == 3 else max(1, n * (k % 5 + 1) // 8) for k, n in enumerate(nv)]
+    ctx = pk.Context(len(V), len(F), len(sizes), device=0)
+    ctx.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, batch)
+    got = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
+    ref = oracle.decimate_batch(V, F, nv, nf, target)
+    same(got, ref)
+    assert list(got[4]) == list(ref["nv"]) and list(got[5]) == list(ref["nf"])
+
+
+def test_large_tiles_of_several_meshes(pk, oracle):
+    sizes = [400001, 1, 300077, 90000, 350123]
+    parts = [lattice(n, k, 0.1, 0.02) for k, n in enumerate(sizes)]
+    nv, nf = [len(v) for v, _ in parts], [len(f) for _, f in parts]
+    base = np.concatenate([[0], np.cumsum(nv)])
+    V = np.concatenate([v for v, _ in parts])
+    F = np.concatenate([f + np.int32(base[k]) for k, (_, f) in enumerate(parts)])
+    target = [max(1, n * (k + 1) // 8) for k, n in enumerate(nv)]
+    ctx = pk.Context(len(V), len(F), len(sizes), device=0)
+    got = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
+    ref = oracle.decimate_batch(V, F, nv, nf, target)
+    same(got, ref)
+    assert list(got[4]) == list(ref["nv"]) and list(got[5]) == list(ref["nf"])
