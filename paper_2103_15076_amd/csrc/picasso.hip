@@ -1692,7 +1692,7 @@ int picasso_v2f_forward(picasso_ctx* c, void* stream, const float* d_x, int32_t 
     if (!c || !d_x || N < 1 || C < 1 || !d_facets || F < 1 || !d_w || !d_y) return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const pool::RowMap m = pool::row_map(C);
+    const pool::RowMap m = pool::row_map(C, false, pool::beyond_cache(C, (long long)N + F));
     const int per_wave = conv::facets_per_wave(m, F), per_block = per_wave * (pool::BLOCK / 64);
     const dim3 grid(prim::xcd_grid((F + per_block - 1) / per_block), pool::row_parts(m));
 #define PICASSO_CALL(K) \
@@ -1781,7 +1781,7 @@ int picasso_f2v_forward(picasso_ctx* c, void* stream, const float* d_y, int32_t 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
+    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N, pool::beyond_cache(C, (long long)N + F));
     const int per_block = (T <= 16 ? m.per_wave : m.row.rw) * (pool::BLOCK / 64);
     const dim3 grid(prim::xcd_grid((N + per_block - 1) / per_block), pool::row_parts(m.row));
 #define PICASSO_F2V(NP, K) \

@@ -102,17 +102,28 @@ struct RowMap {
     int Q, qc, rw, inv;  // rw = rows per wave and step; inv = ceil(65536 / qc)
 };
 inline int row_parts(const RowMap& m) { return (m.Q + m.qc - 1) / m.qc; }
-// one_wave: all lanes of a row in one wave, Q <= 64 (for sums across a row's lanes)
-inline RowMap row_map(int C, bool one_wave = false) {
+// One wave per row where a wave's lanes hold at least two rows (Q <= 32): dealt to several waves, a row's parts end within lines, each
+// wave fetches the row's indices again, and what that costs grows with the rows, while lanes without a pack cost next to nothing
+// (fewer idle lanes by 2 or 3 parts against one: vertex2facet of 720 k facets, 24 channels 36 -> 19 us, 52: 68 -> 42, 100: 184 -> 136;
+// max pooling of 360 k vertices, 100 channels 88 -> 53; the passes over the vertices' facets 97 -> 54, 145 -> 93, 268 -> 178).  From 33 packs
+// on a wave holds one row, and up to half of its lanes may be idle: two parts where they use a fifth more of them (120 k facets, 132
+// channels: facet2vertex 42 -> 32 us, vertex2facet's backward pass 42 -> 45, pooling the same).  Beyond 64, as few idle lanes as can be.
+// one_wave: all lanes of a row in one wave, Q <= 64 (for sums across a row's lanes).  beyond_cache: the rows do not fit the Infinity
+// Cache; parts of whole 128-byte lines then pay up to 32 packs too (96 channels, 720 k facets: vertex2facet 116 us in one part, 100 in three; 120 k
+// facets 13 and 20).
+inline RowMap row_map(int C, bool one_wave = false, bool beyond_cache = false) {
     RowMap best{}, m;
     double best_use = -1.0;
     m.Q = (C + 3) / 4;
     const int least = (m.Q + 63) / 64;
-    for (int parts = least; parts <= (one_wave ? 1 : least + 3) && parts <= m.Q; ++parts) {
+    const double a_part = m.Q > 64 ? 0.04 : m.Q > 32 ? 0.2 : 0.1;  // share of the lanes that a further part has to bring to work
+    const int most = one_wave || (m.Q <= 32 && !beyond_cache) ? least : least + 3;
+    for (int parts = least; parts <= most && parts <= m.Q; ++parts) {
         m.qc = (m.Q + parts - 1) / parts;
+        if (m.Q <= 32 && parts > 1 && (m.Q % 8 != 0 || m.qc % 8 != 0)) continue;
         m.rw = 64 / m.qc;
         m.inv = (65536 + m.qc - 1) / m.qc;
-        const double use = (double)m.rw * m.Q / (64.0 * row_parts(m)) - 0.04 * (parts - least);  // lanes at work
+        const double use = (double)m.rw * m.Q / (64.0 * row_parts(m)) - a_part * (parts - least);  // lanes at work
         if (use > best_use) {
             best_use = use;
             best = m;
@@ -120,6 +131,7 @@ inline RowMap row_map(int C, bool one_wave = false) {
     }
     return best;
 }
+inline bool beyond_cache(int C, long long rows) { return 4ll * C * rows > (256ll << 20); }
 // workgroups so that every wave takes `steps` x rw rows
 inline dim3 row_grid(const RowMap& m, int rows, int steps = 1) {
     const long long per_block = (long long)m.rw * steps * (BLOCK / 64);

@@ -1,0 +1,53 @@
+"""Channel counts on both sides of the lines at which rows are dealt to lanes and waves in another way (24 to 128 channels: a wave holds
+several rows, whose lanes need not fill it; 132 to 256: one row, or a part of one; 260: several waves a row): pooling and the convolutions
+against the fp64 oracle, whose bounds are those of test_gpu_conv and test_gpu_pooling."""
+import numpy as np
+import pytest
+from scipy.special import softmax
+
+from paper_2103_15076_amd import meshgen
+from test_gpu_conv import _close, _gw_terms, ctx, dev, pk  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("C", [24, 52, 99, 128, 132, 160, 164, 256, 260])
+def test_rows_dealt_to_lanes_and_waves(pk, ctx, oracle, C):  # noqa: F811
+    V, F = meshgen.noisy_grid(37, 29, seed=C, noise=0.02)
+    N, nF, T = V.shape[0], F.shape[0], 5
+    print(f"row map C={C}", flush=True)
+    rng = np.random.default_rng(C)
+    x, gx = rng.normal(size=(2, N, C)).astype(np.float32)
+    y, gy = rng.normal(size=(2, nF, C)).astype(np.float32)
+    w3, w = rng.normal(size=(3, C)).astype(np.float32), rng.normal(size=(T, C)).astype(np.float32)
+    pi = softmax(rng.normal(size=(nF, T)), axis=1).astype(np.float32)
+    lv = rng.integers(1, 4, nF).astype(np.int32)
+    off, cor = ctx.picasso_vertex_corner_csr(dev(F), N)
+    deg = int(np.bincount(F.reshape(-1), minlength=N).max())
+    got = ctx.picasso_v2f_forward(dev(x), dev(F), dev(lv), dev(w3))
+    _close(got, oracle.v2f_forward(x, F, lv, w3), 9, oracle.v2f_forward(np.abs(x), F, lv, np.abs(w3)), "v2f")
+    ggx, ggw = ctx.picasso_v2f_backward(dev(gy), dev(x), dev(F), dev(lv), dev(w3), off, cor)
+    ref, bar = oracle.v2f_backward(gy, x, F, lv, w3), oracle.v2f_backward(np.abs(gy), np.abs(x), F, lv, np.abs(w3))
+    _close(ggx, ref[0], 4 * deg, bar[0], "v2f gx")
+    _close(ggw, ref[1], _gw_terms(nF, 4), bar[1], "v2f gw")
+    got = ctx.picasso_f2v_forward(dev(y), dev(pi), dev(w), off, cor, N)
+    _close(got, oracle.f2v_forward(y, pi, w, F, N), (T + 2) * deg, oracle.f2v_forward(np.abs(y), pi, np.abs(w), F, N), "f2v")
+    got = ctx.picasso_f2v_backward(dev(gx), dev(y), dev(pi), dev(w), dev(F), off)
+    ref, bar = oracle.f2v_backward(gx, y, pi, w, F), oracle.f2v_backward(np.abs(gx), np.abs(y), pi, np.abs(w), F)
+    for g, r, b, terms in zip(got, ref, bar, (T + 8, _gw_terms(nF, 6), 6 * C)):
+        _close(g, r, terms, b, "f2v backward")
+    n_out = N // 2 + 1
+    cid = (np.arange(N) // 2).astype(np.int32)
+    off, mem = ctx.picasso_cluster_csr(dev(cid), n_out)
+    y, arg = ctx.picasso_pool_forward(pk.PICASSO_POOL_MAX, dev(x), off, mem)
+    y = y.cpu().numpy()
+    two = np.stack([x[0:2 * (N // 2):2], x[1:2 * (N // 2):2]])
+    assert np.array_equal(y[:N // 2], two.max(0))
+    back = ctx.picasso_pool_backward(pk.PICASSO_POOL_MAX, dev(gx[:n_out]), dev(cid), off, mem, argmax=arg).cpu().numpy()
+    want = np.zeros_like(x)
+    a = arg.cpu().numpy()[:n_out]
+    for k in range(C):
+        has = a[:, k] >= 0
+        want[a[has, k], k] = gx[:n_out][has, k]
+    assert np.array_equal(back, want)
+    assert np.array_equal(ctx.picasso_unpool_forward(dev(gx[:n_out]), dev(cid)).cpu().numpy(), gx[:n_out][cid])
