@@ -60,7 +60,7 @@ struct picasso_ctx {
     int* fcur = nullptr;                // the facets, re-indexed in place round by round
     int* fmap = nullptr;                // ... after the last round, before compaction
     int* cid = nullptr;
-    u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys); the filter gradients' partial sums lie in the first
+    u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys); the filter gradients' partial sums lie from the first to ecost
     u32* val32 = nullptr;                // ... for the values of the exported sorts
     u64* ekey = nullptr;
     u32* ecost = nullptr;
@@ -1292,7 +1292,7 @@ int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts,
 
 // Filter gradients of the convolutions' backward passes: `rows` x C values summed over n_rows rows in two stages
 // (conv::rows_to_partial, conv::reduce_rows_stage2_kernel).  Stage 1's workgroups leave their partial sums in the
-// context's sort buffer.  As many workgroups as the chip holds at once (256 compute units; a workgroup takes several
+// context's sort buffers.  As many workgroups as the chip holds at once (256 compute units; a workgroup takes several
 // turns of rows_per_turn rows, keeping their sums in registers), fewer where there are not so many turns or the
 // buffer does not hold their partials.
 struct FilterSplit {
@@ -1311,9 +1311,12 @@ struct FilterSplit {
 
 int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_turn, int blocks_per_cu, bool wanted,
                       FilterSplit* out) {
-    const size_t cap = (size_t)3 * (size_t)c->max_facets * sizeof(u64) / sizeof(float);  // floats in key64[0]
+    // (The sorts' buffers from key64[0] to ecost lie behind one another.  With the first alone 22 k facets of 200 channels and 6
+    // components left 110 workgroups to facet2vertex's backward pass, 56 us; now 440, 23.)
+    const size_t h = (size_t)3 * (size_t)c->max_facets;
+    const size_t cap = (size_t)(reinterpret_cast<char*>(c->ecost + h) - reinterpret_cast<char*>(c->key64[0])) / sizeof(float);
     const size_t per_group = (size_t)rows * C;
-    if (wanted && per_group > cap) return PICASSO_ERR_WORKSPACE;
+    if (wanted && per_group > h * sizeof(u64) / sizeof(float)) return PICASSO_ERR_WORKSPACE;
     const long long turns = ((long long)n_rows + rows_per_turn - 1) / rows_per_turn;
     long long most = 256ll * blocks_per_cu;
     if (wanted) most = std::min<long long>(most, (long long)(cap / per_group));
@@ -1326,8 +1329,8 @@ int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_
     return PICASSO_OK;
 }
 void sum_filter_rows(hipStream_t s, const FilterSplit& sp, int width, float* d_out) {
-    conv::reduce_rows_stage2_kernel<<<pool::grid_for((long long)width * 64), pool::BLOCK, 0, s>>>(sp.partial, sp.groups, width,
-                                                                                                  d_out);
+    conv::reduce_rows_stage2_kernel<<<(width + conv::REDUCE_VALUES - 1) / conv::REDUCE_VALUES, conv::REDUCE_THREADS, 0, s>>>(sp.partial, sp.groups,
+                                                                                                                          width, d_out);
 }
 
 // Items 0 .. n - 1 listed per row (d_row_of[i] in [0, n_rows)), ascending: d_off [n_rows + 1], d_items [n].
@@ -1711,8 +1714,8 @@ int picasso_v2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
     FilterSplit sp;
+    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
     const int rc = split_filter_rows(c, N, 3, C, m.per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
     if (rc != PICASSO_OK) return rc;
     const dim3 grid(sp.groups, pool::row_parts(m.row));
