@@ -1089,4 +1089,297 @@ __global__ __launch_bounds__(BLOCK) void f2v_backward_pi_kernel(const float* __r
     }
 }
 
+// ---------------------------------------------------------------------------
+// Narrow rows, up to NARROW_C channels: a lane has a whole row (vertex, or facet in facet2vertex's backward pass), all channels in
+// registers.  The kernels above give such rows a lane for four channels of every second to eighth item and fetch 64 items at a time
+// through LDS, so that a wave walks 8 to 32 rows in steps of two trips to memory each; here 64 rows take three (offsets, corners, rows),
+// four items in flight.  Facet2vertex's components need no sum across lanes for the coefficients' gradients, and the
+// filter comes from scalar registers.  A row of more than NARROW_LONG items goes to all lanes of the wave.  By the kernels above / here,
+// 720 k facets, 6 components, us: 3 channels facet2vertex 30 / 11, its backward pass 23 / 13, vertex2facet's 39 / 12; 6 channels 35 / 15, 29 / 18,
+// 49 / 21; 8 channels 29 / 18, 26 / 21, 39 / 24 (120 k facets, 6 channels: 10 / 5, 17 / 9, 15 / 9).  The line at 8 channels is where registers run
+// out: a row of vertex2facet's backward pass takes 10 values per channel besides the four rows in flight.
+// ---------------------------------------------------------------------------
+constexpr int NARROW_C = 8, NARROW_LONG = 64, NARROW_VALUES = 64;  // NARROW_VALUES: of a filter's gradient, in registers
+template <int C>
+struct NarrowRow {
+    float v[C];
+};
+template <int C, typename T>
+__device__ __forceinline__ T* narrow_at(T* p, int i) {
+    return row_at<pool::ROW_TAIL>(p, i, C, 0);
+}
+template <int C>
+__device__ __forceinline__ NarrowRow<C> load_narrow(const float* p, int i) {
+    return *reinterpret_cast<const NarrowRow<C>*>(narrow_at<C>(p, i));
+}
+template <int C>
+__device__ __forceinline__ void store_narrow(float* p, int i, const float (&v)[C]) {
+    NarrowRow<C> r;
+#pragma unroll
+    for (int c = 0; c < C; ++c) r.v[c] = v[c];
+    *reinterpret_cast<NarrowRow<C>*>(narrow_at<C>(p, i)) = r;
+}
+
+template <int C>
+__device__ __forceinline__ void arrived(float (&v)[C]) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) pool::arrived(v[c]);
+}
+
+constexpr int pow2_at_least(int n) {
+    int p = 1;
+    while (p < n) p <<= 1;
+    return p;
+}
+// The sums over a wave's lanes of V values each: halves of what a lane still holds are exchanged until it holds one
+// (V - 1 shuffles, not 6 V), in a fixed tree.  Lane l gets the sum of value l * P / 64, P = V filled up to a power of two.
+template <int P, int D>
+__device__ __forceinline__ void exchange_halves(float (&v)[P]) {
+    if constexpr (P > 1) {
+        const bool up = ((int)threadIdx.x & D) != 0;
+        float half[P / 2];
+#pragma unroll
+        for (int i = 0; i < P / 2; ++i) half[i] = (up ? v[i + P / 2] : v[i]) + __shfl_xor(up ? v[i] : v[i + P / 2], D, 64);
+        exchange_halves<P / 2, D / 2>(half);
+        v[0] = half[0];
+    } else if constexpr (D > 0) {
+        v[0] = v[0] + __shfl_xor(v[0], D, 64);
+        exchange_halves<1, D / 2>(v);
+    }
+}
+template <int V>
+__device__ __forceinline__ float wave_sums(const float (&in)[V]) {
+    constexpr int P = pow2_at_least(V);
+    static_assert(P <= 64, "a value per lane");
+    float v[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) v[i] = i < V ? in[i] : 0.0f;
+    exchange_halves<P, 32>(v);
+    return v[0];
+}
+// A workgroup's sums of V values per lane: value i to at(i).
+template <int V, class At>
+__device__ __forceinline__ void narrow_partial(const float (&in)[V], float (*lds)[64] /* [BLOCK / 64] */, At at_value) {
+    constexpr int LANES = 64 / pow2_at_least(V);  // of a value
+    const float mine = wave_sums<V>(in);
+    const int lane = (int)threadIdx.x & 63;
+    if (lane % LANES == 0) lds[wave_id()][lane / LANES] = mine;
+    __syncthreads();
+    const int i = threadIdx.x;
+    if (i < V) {
+        float* out = at_value(i);
+        if (out) *out = (lds[0][i] + lds[1][i]) + (lds[2][i] + lds[3][i]);
+    }
+}
+
+// The items [s, e) of the lane's row, in order, U of them at a time: items(j, n) with n <= U of them from j on in use.  Longer rows, by all lanes of the wave:
+// every lane makes the sums of every 64th item (acc: V of them, zero at first), which are added up in a fixed tree and handed to the row's lane.
+template <int U, int V, class Items>
+__device__ __forceinline__ void narrow_walk(int s, int e, float (&acc)[V], Items items) {
+    const bool is_long = e - s > NARROW_LONG;
+    if (!is_long)
+        for (int j = s; j < e; j += U) items(j, min(U, e - j), 1, acc);
+    for (unsigned long long rest = __ballot(is_long); rest; rest &= rest - 1) {
+        const int owner = __ffsll((long long)rest) - 1, lane = (int)threadIdx.x & 63;
+        const int s0 = __shfl(s, owner, 64), e0 = __shfl(e, owner, 64);
+        float part[V] = {};
+        for (int j = s0 + lane; j < e0; j += 64 * U) items(j, min(U, (e0 - j + 63) / 64), 64, part);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) part[i] = part[i] + __shfl_xor(part[i], d, 64);
+            if (lane == owner) acc[i] = part[i];
+        }
+    }
+}
+
+// See V2fBackwardOp.  Workgroup b takes the vertices of its chunk, one per lane and turn.
+template <int C>
+__global__ __launch_bounds__(BLOCK) void v2f_backward_narrow_kernel(const float* __restrict__ gy, const float* __restrict__ x,
+                                                                    const int* __restrict__ level, const float* __restrict__ w,
+                                                                    const int* __restrict__ off, const int* __restrict__ corners,
+                                                                    int N, int H, int chunk, float* __restrict__ gx,
+                                                                    float* __restrict__ partial) {
+    constexpr int U = 4;
+    __shared__ float lds[BLOCK / 64][64];
+    float gw[3 * C] = {};
+    const int begin = min(xcd_block() * chunk, N), end = min(begin + chunk, N);
+    for (int v0 = begin; v0 < end; v0 += BLOCK) {  // (whole waves, for the long rows)
+        const int v = v0 + (int)threadIdx.x;
+        const bool on = v < end;
+        const Int2 o = load_pair(at<pool::ROW_TAIL>(off, on ? v : begin));
+        const int s = min(max(o.a, 0), H), e = on ? min(max(o.b, s), H) : s;
+        const NarrowRow<C> xv = partial ? load_narrow<C>(x, on ? v : begin) : NarrowRow<C>{};
+        float acc[4 * C] = {};  // A_0, A_1, A_2, B
+        narrow_walk<U>(s, e, acc, [&](int j, int n, int step, float (&sum)[4 * C]) {
+            int f[U], place[U], lv[U];
+            NarrowRow<C> g[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) place[u] = in_range_or_zero(*at<pool::ROW_TAIL>(corners, j + min(u, n - 1) * step), H);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                f[u] = place[u] / 3;
+                place[u] -= 3 * f[u];
+                lv[u] = level ? *at<pool::ROW_TAIL>(level, f[u]) : 1;
+                g[u] = load_narrow<C>(gy, f[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) arrived(g[u].v);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u < n) {
+                    float amb, b;
+                    lattice_moments(lv[u], amb, b);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) sum[3 * C + c] = fmaf(b, g[u].v[c], sum[3 * C + c]);
+                    if (amb != 0.0f) {  // (a facet of level 1, nearly every one, has a = b)
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) {
+                            const float a = place[u] == p ? amb : 0.0f;
+#pragma unroll
+                            for (int c = 0; c < C; ++c) sum[p * C + c] = fmaf(a, g[u].v[c], sum[p * C + c]);
+                        }
+                    }
+                }
+        });
+        if (gx && on) {
+            float out[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const float w0 = w[c], w1 = w[C + c], w2 = w[2 * C + c];
+                out[c] = fmaf((w0 + w1) + w2, acc[3 * C + c], fmaf(w2, acc[2 * C + c], fmaf(w1, acc[C + c], w0 * acc[c])));
+            }
+            store_narrow<C>(gx, v, out);
+        }
+        if (on)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int c = 0; c < C; ++c) gw[p * C + c] = fmaf(xv.v[c], acc[p * C + c] + acc[3 * C + c], gw[p * C + c]);
+    }
+    if (partial) narrow_partial<3 * C>(gw, lds, [&](int i) { return partial + (size_t)blockIdx.x * (3 * C) + i; });
+}
+
+// Facet2vertex forward (T <= 4 NP components): the filter is put together per corner.
+template <int C, int NP>
+__global__ __launch_bounds__(BLOCK) void f2v_forward_narrow_kernel(const float* __restrict__ y, const float* __restrict__ pi, int T,
+                                                                   const float* __restrict__ w, const int* __restrict__ off,
+                                                                   const int* __restrict__ corners, int N, int H,
+                                                                   float* __restrict__ x) {
+    constexpr int TT = 4 * NP, U = NP <= 2 ? 4 : 2;
+    const int v = xcd_block() * BLOCK + (int)threadIdx.x;
+    const bool on = v < N;
+    const Int2 o = load_pair(at<pool::ROW_TAIL>(off, on ? v : 0));
+    const int s = min(max(o.a, 0), H), e = on ? min(max(o.b, s), H) : s;
+    float acc[C] = {};
+    narrow_walk<U>(s, e, acc, [&](int j, int n, int step, float (&sum)[C]) {
+        int f[U];
+        NarrowRow<C> yf[U];
+        float p[U][TT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) f[u] = in_range_or_zero(*at<pool::ROW_TAIL>(corners, j + min(u, n - 1) * step), H) / 3;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            yf[u] = load_narrow<C>(y, f[u]);
+            load_coefficients<NP>(p[u], row_at<pool::ROW_TAIL>(pi, f[u], T, 0), T);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) arrived(yf[u].v);
+        float coef[U][C] = {};
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+            if (slot_used<NP>(t, T)) {
+                const float* wt = w + slot_component<NP>(t, T) * C;  // (the same in all lanes)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) coef[u][c] = fmaf(p[u][t], wt[c], coef[u][c]);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (u < n)
+#pragma unroll
+                for (int c = 0; c < C; ++c) sum[c] = fmaf(coef[u][c], yf[u].v[c], sum[c]);
+    });
+    if (!on) return;
+    const float n = (float)(e - s);
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = n > 0.0f ? acc[c] / n : 0.0f;
+    store_narrow<C>(x, v, acc);
+}
+
+// See f2v_backward_kernel; T <= 4 NP components, 4 NP C <= NARROW_VALUES.
+template <int C, int NP>
+__global__ __launch_bounds__(BLOCK) void f2v_backward_narrow_kernel(const float* __restrict__ gx, const float* __restrict__ y,
+                                                                    const float* __restrict__ pi, int T, const float* __restrict__ w,
+                                                                    const int* __restrict__ facets, int F, const int* __restrict__ off,
+                                                                    int N, int chunk, float* __restrict__ gy,
+                                                                    float* __restrict__ partial, float* __restrict__ gpi) {
+    constexpr int TT = 4 * NP;
+    __shared__ float lds[BLOCK / 64][64];
+    float gw[TT * C] = {};
+    const int begin = min(xcd_block() * chunk, F), end = min(begin + chunk, F);
+    for (int f = begin + (int)threadIdx.x; f < end; f += BLOCK) {
+        const Int3 v = load_triple(row_at<pool::ROW_TAIL>(facets, f, 3, 0));
+        float p[TT];
+        load_coefficients<NP>(p, row_at<pool::ROW_TAIL>(pi, f, T, 0), T);
+        const NarrowRow<C> yf = load_narrow<C>(y, f);
+        const int at_v[3] = {in_range_or_zero(v.a, N), in_range_or_zero(v.b, N), in_range_or_zero(v.c, N)};
+        Int2 o[3];
+        NarrowRow<C> gv[3];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            o[s] = load_pair(at<pool::ROW_TAIL>(off, at_v[s]));
+            gv[s] = load_narrow<C>(gx, at_v[s]);
+        }
+        float g[C], h[C], coef[C] = {};
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const float n = (float)(o[s].b - o[s].a), r = 1.0f / n;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const float q = quotient(gv[s].v[c], n, r);
+                g[c] = s == 0 ? q : g[c] + q;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) h[c] = yf.v[c] * g[c];
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+            if (slot_used<NP>(t, T)) {
+                const float* wt = w + slot_component<NP>(t, T) * C;  // (the same in all lanes)
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    coef[c] = fmaf(p[t], wt[c], coef[c]);
+                    gw[t * C + c] = fmaf(p[t], h[c], gw[t * C + c]);
+                }
+            }
+        if (gpi) {
+            float* out = row_at<pool::ROW_TAIL>(gpi, f, T, 0);
+#pragma unroll
+            for (int g0 = 0; g0 < TT; g0 += 4) {  // (four slots, four components in a row)
+                Pack d{};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float* wt = w + min(slot_component<NP>(g0 + k, T), T - 1) * C;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) d.v[k] = fmaf(wt[c], h[c], d.v[k]);
+                }
+                if constexpr (NP > 1) store_row<pool::ROW_EVEN>(out + slot_component<NP>(g0, T), d, 4);
+                else store_row<pool::ROW_TAIL>(out, d, T);
+            }
+        }
+        if (gy) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) coef[c] = coef[c] * g[c];
+            store_narrow<C>(gy, f, coef);
+        }
+    }
+    if (partial)
+        narrow_partial<TT * C>(gw, lds, [&](int i) -> float* {
+            const int t = i / C;
+            return slot_used<NP>(t, T) ? partial + ((size_t)blockIdx.x * T + slot_component<NP>(t, T)) * C + (i - t * C) : nullptr;
+        });
+}
+
 }  // namespace conv

@@ -1309,6 +1309,24 @@ struct FilterSplit {
         }                                                         \
     } while (0)
 
+// Rows narrow enough for a lane each (conv.h); arrays beyond 32-bit offsets go by the kernels for any.
+bool narrow_rows(int C, int width, long long max_rows) {
+    return C <= conv::NARROW_C && pool::row_kind(C, width, max_rows) != pool::ROW_ANY;
+}
+#define PICASSO_NARROW(C, CALL)                                       \
+    do {                                                              \
+        switch (C) {                                                  \
+            case 1: CALL(1); break;                                   \
+            case 2: CALL(2); break;                                   \
+            case 3: CALL(3); break;                                   \
+            case 4: CALL(4); break;                                   \
+            case 5: CALL(5); break;                                   \
+            case 6: CALL(6); break;                                   \
+            case 7: CALL(7); break;                                   \
+            default: CALL(8);                                         \
+        }                                                             \
+    } while (0)
+
 int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_turn, int blocks_per_cu, bool wanted,
                       FilterSplit* out) {
     // (The sorts' buffers from key64[0] to ecost lie behind one another.  With the first alone 22 k facets of 200 channels and 6
@@ -1715,6 +1733,17 @@ int picasso_v2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
     FilterSplit sp;
+    if (narrow_rows(C, C, std::max(N, F))) {
+        const int rc = split_filter_rows(c, N, 3, C, pool::BLOCK, 5, d_gw != nullptr, &sp);
+        if (rc != PICASSO_OK) return rc;
+#define PICASSO_CALL(CH) \
+    conv::v2f_backward_narrow_kernel<CH><<<sp.groups, pool::BLOCK, 0, s>>>(d_gy, d_x, d_level, d_w, d_offsets, d_corners, N, 3 * F, sp.chunk, d_gx, sp.partial)
+        PICASSO_NARROW(C, PICASSO_CALL);
+#undef PICASSO_CALL
+        if (d_gw) sum_filter_rows(s, sp, 3 * C, d_gw);
+        HIP_TRY(c, hipGetLastError());
+        return PICASSO_OK;
+    }
     const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
     const int rc = split_filter_rows(c, N, 3, C, m.per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
     if (rc != PICASSO_OK) return rc;
@@ -1784,6 +1813,21 @@ int picasso_f2v_forward(picasso_ctx* c, void* stream, const float* d_y, int32_t 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
+    if (T <= 16 && narrow_rows(C, std::max(C, T), std::max(N, F))) {
+        const int grid = prim::xcd_grid((N + pool::BLOCK - 1) / pool::BLOCK);
+#define PICASSO_F2V(CH, NP) \
+    conv::f2v_forward_narrow_kernel<CH, NP><<<grid, pool::BLOCK, 0, s>>>(d_y, d_pi, T, d_w, d_offsets, d_corners, N, 3 * F, d_x)
+#define PICASSO_CALL(CH)                      \
+    if (T <= 4) PICASSO_F2V(CH, 1);           \
+    else if (T <= 8) PICASSO_F2V(CH, 2);      \
+    else if (T <= 12) PICASSO_F2V(CH, 3);     \
+    else PICASSO_F2V(CH, 4)
+        PICASSO_NARROW(C, PICASSO_CALL);
+#undef PICASSO_CALL
+#undef PICASSO_F2V
+        HIP_TRY(c, hipGetLastError());
+        return PICASSO_OK;
+    }
     const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N, pool::beyond_cache(C, (long long)N + F));
     const int per_block = (T <= 16 ? m.per_wave : m.row.rw) * (pool::BLOCK / 64);
     const dim3 grid(prim::xcd_grid((N + per_block - 1) / per_block), pool::row_parts(m.row));
@@ -1810,6 +1854,29 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
         return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
+    const int np = (T + 3) / 4;
+    if (np <= 4 && 4 * np * C <= conv::NARROW_VALUES && narrow_rows(C, std::max(C, T), std::max(N, F))) {
+        FilterSplit sp;
+        const int rc = split_filter_rows(c, F, T, C, pool::BLOCK, 5, d_gw != nullptr, &sp);
+        if (rc != PICASSO_OK) return rc;
+#define PICASSO_F2V_BACK(CH, NP)                                                                                        \
+    do {                                                                                                                \
+        if constexpr (4 * (NP) * (CH) <= conv::NARROW_VALUES)                                                           \
+            conv::f2v_backward_narrow_kernel<CH, NP><<<sp.groups, pool::BLOCK, 0, s>>>(                                 \
+                d_gx, d_y, d_pi, T, d_w, d_facets, F, d_offsets, N, sp.chunk, d_gy, sp.partial, d_gpi);                 \
+    } while (0)
+#define PICASSO_CALL(CH)                        \
+    if (np == 1) PICASSO_F2V_BACK(CH, 1);       \
+    else if (np == 2) PICASSO_F2V_BACK(CH, 2);  \
+    else if (np == 3) PICASSO_F2V_BACK(CH, 3);  \
+    else PICASSO_F2V_BACK(CH, 4)
+        PICASSO_NARROW(C, PICASSO_CALL);
+#undef PICASSO_CALL
+#undef PICASSO_F2V_BACK
+        if (d_gw) sum_filter_rows(s, sp, T * C, d_gw);
+        HIP_TRY(c, hipGetLastError());
+        return PICASSO_OK;
+    }
     // one pass per 16 filter rows; gpi with it where a row's lanes fit a wave, else by a kernel of its own
     const bool gpi_fused = d_gpi && C <= 256;
     const pool::RowMap m = pool::row_map(C, gpi_fused);
