@@ -1294,7 +1294,8 @@ __global__ __launch_bounds__(BLOCK) void select_first_kernel(SelArgs A) {
 // two bids; the sort of the half-edges (partition and per-bucket kernel) and unique_cost_kernel, which number the distinct
 // ones, do not run.  Facets that have collapsed leave their tile, so that each round reads what the one before has left.
 // Bound by memory: the first round's launch moves 1.55 GB of 10.2 M vertices / 20 M facets in 353 us (4.4 TB/s), later ones wait
-// for a chain of gathers (344 and 298 us, 3.1 and 2.4 TB/s; six waves a SIMD, hence the bound on registers: 409 and 321 without).
+// for a chain of gathers (346 and 285 us; six waves a SIMD, hence the bound on registers (409 and 321 without), and workgroups as small as can be:
+// tiles of 1,024 facets by 256 lanes took 343 and 299, by 512 lanes 429 and 366, tiles of 512 by 128 lanes with twice the table 361 and 315).
 // Rounds 2 and 3 of that mesh took 686 and 565 us up to the first bids with the sort, 227 k facets 32 us of round 2, now 9; whole calls with the
 // sort / by facets: 4 k vertices 178 / 155 us, 115 k 213 / 189, 1.2 M 848 / 702, 10.2 M 5,400 / 4,720.
 // ---------------------------------------------------------------------------
@@ -1331,7 +1332,7 @@ __global__ __launch_bounds__(THREADS, FIRST ? 1 : 6) void facet_costs_kernel(int
                                                               const int* fcount, int* fcount_out, int* __restrict__ nf_slots,
                                                               int* __restrict__ nf_next) {
     constexpr int TILE = THREADS * PER, WAVES = THREADS / 64;
-    __shared__ BidTable<THREADS * PER <= 1024 ? 128 : 256, THREADS> bids;
+    __shared__ BidTable<!FIRST && THREADS == 128 ? 64 : 128, THREADS> bids;
     __shared__ MeshFlags M;
     __shared__ int at[FIRST ? 1 : 3][FIRST ? 1 : TILE];  // the corners of those left
     __shared__ int left[PER][WAVES];

@@ -488,9 +488,11 @@ void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>&
 }
 
 // Facets to a tile in the rounds by facets: small ones while the workgroups are to fill the chip, large ones (fewer copies of an edge, lists and
-// tables per workgroup that serve more) beyond 2^20 facets.  Whole calls with small | large tiles, us: one mesh of 227 k facets 190 | 222, 800 k
-// 391 | 408, 1.4 M 503 | 502, 2.4 M 721 | 702, 20 M 5173 | 4720; 16 meshes of 750 k together 315 | 313, 1.13 M 408 | 394, 1.9 M 629 | 567.
-constexpr int FACET_TILE_SMALL = 256, FACET_TILE_LARGE = 1024;
+// tables per workgroup that serve more) beyond 2^20 facets.  Whole calls with tiles of 256 | 1,024, us: one mesh of 227 k facets 190 | 222, 800 k
+// 391 | 408, 1.4 M 503 | 502, 2.4 M 721 | 702, 20 M 5173 | 4720; 16 meshes of 750 k together 315 | 313, 1.13 M 408 | 394, 1.9 M 629 | 567.  Large
+// ones of 512 against 1,024 (more and smaller workgroups, whose barriers hold up fewer waves): 2.4 M 698 -> 690, 20 M 4724 -> 4676, a ladder of four
+// levels from 1.9 M 1169 -> 1155; joining two such tiles from the third round on, when half of their places are empty, took longer (703 -> 737, 4742 -> 5077).
+constexpr int FACET_TILE_SMALL = 256, FACET_TILE_LARGE = 512;
 constexpr int FACET_TILE_SMALL_MAX = 1 << 20;
 inline int facet_tile(int F) { return F <= FACET_TILE_SMALL_MAX ? FACET_TILE_SMALL : FACET_TILE_LARGE; }
 inline int facet_tiles(int F) { return std::max((F + facet_tile(F) - 1) / facet_tile(F), 1); }
@@ -513,7 +515,7 @@ void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cu
 #define PICASSO_FACET_COSTS_PLACE(PLACE)                                        \
     do {                                                                        \
         if (facet_tile(F) == FACET_TILE_SMALL) PICASSO_FACET_COSTS_PER(PLACE, 256, 1);       \
-        else PICASSO_FACET_COSTS_PER(PLACE, 256, 4);                                \
+        else PICASSO_FACET_COSTS_PER(PLACE, 128, 4);                                \
     } while (0)
     if (c->opt_placement == PLACE_INVERSE) PICASSO_FACET_COSTS_PLACE(PLACE_INVERSE);
     else PICASSO_FACET_COSTS_PLACE(PLACE_MEAN);
@@ -698,8 +700,8 @@ void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bo
             const bool small = facet_tile(sa.n_facets) == FACET_TILE_SMALL;
             if (small && last) select_facets_kernel<256, 1, true><<<grid, 256, 0, s>>>(sa);
             else if (small) select_facets_kernel<256, 1, false><<<grid, 256, 0, s>>>(sa);
-            else if (last) select_facets_kernel<512, 2, true><<<grid, 512, 0, s>>>(sa);
-            else select_facets_kernel<512, 2, false><<<grid, 512, 0, s>>>(sa);
+            else if (last) select_facets_kernel<256, 2, true><<<grid, 256, 0, s>>>(sa);
+            else select_facets_kernel<256, 2, false><<<grid, 256, 0, s>>>(sa);
             return;
         }
         const int parts = ((sa.list_tiles - 1) >> shift) + 1, groups = prim::xcd_grid((parts + group - 1) / group);
