@@ -271,7 +271,7 @@ struct FewMeshes {
 // kernel also adds both keys' top digits to the histograms that the sorts start from (zero on entry; left so
 // by the sorts); the sorts make the keys again from the validated facets, so they are
 // written nowhere.  COUNT_XL: digits as wide as the masks say, counted in memory.  COUNT_NONE: no round follows.  edges: the
-// edges' digits are wanted, and the round's set-up is made.
+// round's set-up is made; SORTED (EDGES_SORTED): the edges' digits are wanted as well.
 struct DigitCount {
     u32* hist;
     int shift;
@@ -550,6 +550,62 @@ struct QuadricRows {
         int gap[2 * QR_GAPS];  // runs [first, end) of vertices without facets
         int n_gaps;
     };
+    // Mostly a group of the sort is a vertex: a lane then sorts its vertex's keys in registers and goes on with them (up to
+    // GROUP_LANE keys; a wave sorts more).  (With the groups sorted in LDS and the vertices found again among the keys 115 k vertices took 12.3 us, now 9.6, 1.2 M
+    // 49 and 42.5, 10.2 M 450 and 421.)
+    __device__ bool rows_are_groups(const prim::Bucket& b, int R) const { return (1 << (b.low_bits - fbits)) == R && b.low_bits > fbits; }
+    template <int G, typename LK>
+    __device__ __forceinline__ void add_group(float (&acc)[10], const prim::Bucket& b, const LK* key, int g) const {
+        LK k[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) k[j] = j < g ? key[j] : (LK) ~(LK)0;
+        prim::network_sort_regs<LK, G>(k);
+#pragma unroll
+        for (int j0 = 0; j0 < G; j0 += 8) {  // (eight planes in flight)
+            float4 p[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j0 + j < g) p[j] = planes[b.item(k[j0 + j], fbits)];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j0 + j < g) add_plane_quadric(acc, p[j]);
+        }
+    }
+    template <int THREADS, int ITEMS, class L>
+    __device__ __forceinline__ void emit_groups(L& lds, const prim::Bucket& b, int R) const {
+        const int t = threadIdx.x, lane = prim::lane_id(), lo = b.number * R, n = min(R, N - lo);
+        if (t == 0) lds.nlong = 0;
+        __syncthreads();
+        for (int gi = t; gi < n; gi += THREADS) {
+            const int gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
+            float acc[10] = {};
+            if (g > 16) {
+                lds.gcnt[atomicAdd(&lds.nlong, 1u)] = (u32)gi;
+                continue;
+            }
+            if (g > 8) add_group<16>(acc, b, lds.skey + gs, g);
+            else add_group<8>(acc, b, lds.skey + gs, g);
+            write_vertex_record(vrec, verts, lo + gi, acc);
+        }
+        __syncthreads();
+        for (int li = prim::wave_id(); li < (int)lds.nlong; li += THREADS / 64) {
+            const int gi = (int)lds.gcnt[li], gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
+            prim::rank_group_lds(lds.skey + gs, g);
+            if (lane == 0) {
+                float acc[10] = {};
+                for (int j0 = 0; j0 < g; j0 += 8) {
+                    float4 p[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (j0 + j < g) p[j] = planes[b.item(lds.skey[gs + j0 + j], fbits)];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (j0 + j < g) add_plane_quadric(acc, p[j]);
+                }
+                write_vertex_record(vrec, verts, lo + gi, acc);
+            }
+        }
+    }
     template <int THREADS, int ITEMS, class L, typename LK, class KeyAt>
     __device__ __forceinline__ void emit(bool, L& lds, const prim::Bucket& b, LK*, LK*, KeyAt key_at) const {
         const int t = threadIdx.x, lane = prim::lane_id(), w = prim::wave_id(), n = b.cnt;

@@ -401,6 +401,9 @@ constexpr int BUCKET_THREADS_4096 = 512;  // 4096 buckets: up to 4096 keys (8 pe
                                           // vertex ids need not fill their bit range, so those buckets run fuller)
 // keys without values (bucket_keys_kernel): lanes and keys per lane of a bucket's workgroup
 constexpr int BUCKET_KEYS_THREADS = 256, BUCKET_KEYS_ITEMS = 16;  // up to 4096 keys in LDS
+// Half as many lanes (and keys in LDS) where vertices or the like are made from the groups of buckets that hold this many keys or less on average: then
+// a lane has a group, and more buckets fit a compute unit (10.2 M vertices, 128 and 765 keys to a bucket: 421 -> 354 us).
+constexpr int BUCKET_FEW_KEYS = 1024;
 constexpr int BUCKET_MSD_BITS = 8, NARROW_BITS_MAX = 10;  // (bits of a narrow digit: 8 to 10)
 constexpr long long BUCKET_SORT_MAX_KEYS = 1ll << 20;  // average bucket <= half of what LDS holds
 
@@ -847,6 +850,23 @@ __device__ __forceinline__ void group_sort_lds(K* skey, int gs, int g) {
 }
 
 
+// ... and of g <= 64 keys by a wave, one lane per key: a key's place is the number of keys of the group that go before it (every lane reads the
+// same address, one read after the other with nothing waiting in between, where an insertion sort by one lane would wait for
+// LDS at every step).
+template <typename K>
+__device__ __forceinline__ void rank_group_lds(K* key, int g) {
+    const int lane = lane_id();
+    const K k = lane < g ? key[lane] : (K)0;
+    int r = 0;
+    for (int i = 0; i < g; ++i) {
+        const K o = key[i];
+        r += (o < k || (o == k && i < lane)) ? 1 : 0;
+    }
+    __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations complete in order)
+    if (lane < g) key[r] = k;
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <typename LK, int THREADS, int ITEMS>
 struct BucketLds {
     static constexpr int NW = THREADS / 64, CAP = THREADS * ITEMS, RMAX = 1 << BUCKET_GROUP_BITS;
@@ -858,10 +878,11 @@ struct BucketLds {
 };
 
 // The cnt keys at kin sorted on their low_bits low bits by one workgroup; then emit(key_at), key_at(i) = the i-th of them (from LDS, or,
-// where they did not fit, from kout).  For cnt = 0 only emit is called.
-template <typename LK, int THREADS, int ITEMS, class Emit>
+// where they did not fit, from kout).  For cnt = 0 only emit is called.  Where the keys are in LDS by groups, none of which is longer than
+// the lanes and waves sort, groups(R) is asked first whether it makes what is wanted from the R groups as they are, not sorted.
+template <typename LK, int THREADS, int ITEMS, class Groups, class Emit>
 __device__ __forceinline__ void sort_bucket(BucketLds<LK, THREADS, ITEMS>& L, LK* kin, LK* kout, const int cnt,
-                                            const int low_bits, const int group_bits, Emit emit) {
+                                            const int low_bits, const int group_bits, Groups groups, Emit emit) {
     constexpr int NW = THREADS / 64;
     constexpr int CAP = THREADS * ITEMS;
     constexpr int RMAX = 1 << BUCKET_GROUP_BITS;
@@ -902,24 +923,14 @@ __device__ __forceinline__ void sort_bucket(BucketLds<LK, THREADS, ITEMS>& L, LK
             }
         }
         __syncthreads();
-        // groups of 17 to 64 keys: a wave takes a group, one lane per key; a key's place is the number of
-        // keys of the group that go before it (every lane reads the same address, one read after the
-        // other with nothing waiting in between, where an insertion sort by one lane would wait for
-        // LDS at every step)
+        // groups of 17 to 64 keys: a wave takes a group
         const int n_long = (int)L.nlong;
         if (n_long > 0) {
             for (int li = w; li < n_long; li += NW) {
                 const int gi = (int)gcnt[li];
                 const int gs = (int)gstart[gi] - lds0;
                 const int g = (int)gstart[gi + 1] - (int)gstart[gi];
-                const LK k = lane < g ? skey[gs + lane] : (LK)0;
-                int r = 0;
-                for (int i = 0; i < g; ++i) {
-                    const LK o = skey[gs + i];
-                    r += (o < k || (o == k && i < lane)) ? 1 : 0;
-                }
-                __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations complete in order)
-                if (lane < g) skey[gs + r] = k;
+                rank_group_lds(skey + gs, g);
             }
             __syncthreads();
         }
@@ -1034,6 +1045,7 @@ __device__ __forceinline__ void sort_bucket(BucketLds<LK, THREADS, ITEMS>& L, LK
             if (i < items && i * THREADS + t < cnt) skey[gstart[digit_of<LK>(key[i], rest, dmask)] + pos[i]] = key[i];
         __syncthreads();
         if (rest > 0 && !any_long) {
+            if (groups((int)R)) return;
             sort_groups(0, (int)R);
         } else if (rest > 0) {
             // some group is longer still: the whole bucket through a bitonic network, padded to a power of two
@@ -1086,6 +1098,12 @@ struct Bucket {
     }
 };
 
+// ... or, if it has emit_groups(LDS, bucket, R) and rows_are_groups(bucket, R) agrees, from the R groups of a bucket in LDS (BucketLds), unsorted.
+template <class Out, class = void>
+struct TakesGroups : std::false_type {};
+template <class Out>
+struct TakesGroups<Out, std::void_t<decltype(&Out::rows_are_groups)>> : std::true_type {};
+
 template <typename K, typename LK, int THREADS, int ITEMS, class Out>
 __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int blocks_first, Out out) {
     __shared__ BucketLds<LK, THREADS, ITEMS> L;
@@ -1100,11 +1118,23 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
     b.low_bits = S.key_bits - S.digit_bits;
     LK* kin = reinterpret_cast<LK*>(S.k1) + b.start;
     LK* kout = reinterpret_cast<LK*>(S.k0) + b.start;
-    sort_bucket<LK, THREADS, ITEMS>(L, kin, kout, b.cnt, b.low_bits, S.group_bits, [&](auto key_at) {
-        if (threadIdx.x == 0 && b.cnt > 0) {  // (every thread has read its count: barriers lie between)
+    auto reset = [&] {  // (every thread has read its count: barriers lie between)
+        if (threadIdx.x == 0 && b.cnt > 0) {
             S.hist[b.number] = 0;
             if (S.taken) S.taken[b.number] = 0;
         }
+    };
+    auto groups = [&](int R) -> bool {
+        if constexpr (TakesGroups<Out>::value) {
+            if (!out.rows_are_groups(b, R)) return false;
+            reset();
+            out.template emit_groups<THREADS, ITEMS>(L, b, R);
+            return true;
+        }
+        return false;
+    };
+    sort_bucket<LK, THREADS, ITEMS>(L, kin, kout, b.cnt, b.low_bits, S.group_bits, groups, [&](auto key_at) {
+        reset();
         out.template emit<THREADS, ITEMS>(second, O, b, kin, kout, key_at);
     });
 }
@@ -1699,8 +1729,11 @@ inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_
         }
         if (timed) lt->end(s);
         timed = lt && lt->begin(s, tag);
-        bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS, BUCKET_KEYS_ITEMS, Out>
-            <<<blocks_sort_a + blocks_sort_b, BUCKET_KEYS_THREADS, 0, s>>>(a, b, blocks_sort_a, out);
+        const int blocks = blocks_sort_a + blocks_sort_b;
+        if (TakesGroups<Out>::value && !b_or_null && (long long)a.n * Src::PER <= (long long)BUCKET_FEW_KEYS * a.buckets)
+            bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS / 2, BUCKET_KEYS_ITEMS, Out><<<blocks, BUCKET_KEYS_THREADS / 2, 0, s>>>(a, b, blocks_sort_a, out);
+        else
+            bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS, BUCKET_KEYS_ITEMS, Out><<<blocks, BUCKET_KEYS_THREADS, 0, s>>>(a, b, blocks_sort_a, out);
         if (timed) lt->end(s);
     };
     if constexpr (std::is_same<Out, PlainKeys<K>>::value) launch(K{});
