@@ -316,7 +316,7 @@ struct DigitTally<COUNT_NONE> {
 };
 
 enum { EDGES_NONE = 0, EDGES_BY_FACETS = 1, EDGES_SORTED = 2 };
-template <int COUNT, class Tables>
+template <int COUNT, bool SORTED, class Tables>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
                                                      const int* __restrict__ facets, int F, int B,
                                                      const int* __restrict__ voff, const int* __restrict__ foff,
@@ -326,7 +326,8 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                                                      float4* __restrict__ planes, int* __restrict__ htab, int n_clear,
                                                      u64* __restrict__ vmin0, u64* __restrict__ vmin1,
                                                      int* __restrict__ mate, u32* __restrict__ pcost, RoundTab R) {
-    __shared__ DigitTally<COUNT> corners, sides;
+    __shared__ DigitTally<COUNT> corners;
+    __shared__ DigitTally<SORTED ? COUNT : COUNT_NONE> sides;
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     constexpr bool ONE = std::is_same<Tables, OneMesh>::value;
@@ -356,7 +357,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
     }
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
     corners.clear(inc);
-    if (edges == EDGES_SORTED) sides.clear(edge);
+    if (SORTED) sides.clear(edge);
     __syncthreads();
     int err = 0;
     for (int w = g; w < N; w += stride) {
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
             vmin0[w] = VMIN_NONE;
             vmin1[w] = VMIN_NONE;
         }
-        if (edges == EDGES_SORTED) {
+        if (SORTED) {
             mate[w] = -1;
             pcost[w] = ~0u;
         }
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         if (planes && ok) planes[f] = facet_plane(verts, at[0], at[1], at[2]);
 #pragma unroll
         for (int c = 0; c < 3; ++c) corners.count(inc, ok, ((u64)(u32)at[c] << fbits) | (u64)(u32)f);
-        if (edges == EDGES_SORTED) {
+        if (SORTED) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const int a = at[c], b = at[c == 2 ? 0 : c + 1];
@@ -418,17 +419,17 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         if constexpr (COUNT == COUNT_XL) {
             __syncthreads();
             corners.flush(inc);
-            if (edges == EDGES_SORTED) sides.flush(edge);
+            if (SORTED) sides.flush(edge);
             __syncthreads();
             corners.clear(inc);
-            if (edges == EDGES_SORTED) sides.clear(edge);
+            if (SORTED) sides.clear(edge);
             __syncthreads();
         }
     }
     if constexpr (COUNT != COUNT_XL) {
         __syncthreads();
         corners.flush(inc);
-        if (edges == EDGES_SORTED) sides.flush(edge);
+        if (SORTED) sides.flush(edge);
     }
     if (err) atomicOr(&st->err, err);
 }

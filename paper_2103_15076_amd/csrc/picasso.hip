@@ -542,21 +542,27 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     float4* planes = work ? facet_planes(c) : nullptr;
     // the facet set that the end of the call uses (larger ones are cleared by the last contraction, when fewer facets are left)
     const int n_clear = F <= CLEAR_AHEAD_MAX_FACETS ? (int)facet_slots((size_t)F) : 0;
-#define PICASSO_INIT_TABLES(COUNT, TABLES)                                                                                     \
-    init_kernel<COUNT><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
+#define PICASSO_INIT_TABLES(COUNT, SORTED, TABLES)                                                                             \
+    init_kernel<COUNT, SORTED><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
         d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], edges == EDGES_BY_FACETS ? nullptr : c->cid, c->fcur, incidence_fbits(F), digit_count(I),      \
         digit_count(E), edges, E.key_bits / 2, c->st, init, TABLES, planes, c->htab, n_clear, c->vmin[0], c->vmin[1],   \
         c->mate, c->pcost(), round_tab(c, B, 0, 0))
+#define PICASSO_INIT_EDGES(COUNT, SORTED)                                           \
+    do {                                                                            \
+        if (B == 1) PICASSO_INIT_TABLES(COUNT, SORTED, OneMesh{tables.target[0]});  \
+        else PICASSO_INIT_TABLES(COUNT, SORTED, tables);                            \
+    } while (0)
 #define PICASSO_INIT(COUNT)                                             \
     do {                                                                \
-        if (B == 1) PICASSO_INIT_TABLES(COUNT, OneMesh{tables.target[0]}); \
-        else PICASSO_INIT_TABLES(COUNT, tables);                        \
+        if (edges == EDGES_SORTED) PICASSO_INIT_EDGES(COUNT, true);     \
+        else PICASSO_INIT_EDGES(COUNT, false);                          \
     } while (0)
-    if (!work) PICASSO_INIT(COUNT_NONE);
+    if (!work) PICASSO_INIT_EDGES(COUNT_NONE, false);
     else if (count_kind(I) == COUNT_SMALL) PICASSO_INIT(COUNT_SMALL);
     else if (count_kind(I) == COUNT_LARGE) PICASSO_INIT(COUNT_LARGE);
     else PICASSO_INIT(COUNT_XL);
 #undef PICASSO_INIT
+#undef PICASSO_INIT_EDGES
 #undef PICASSO_INIT_TABLES
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }
