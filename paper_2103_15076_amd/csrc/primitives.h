@@ -434,7 +434,7 @@ __device__ __forceinline__ K coherent_load(const K* p) {
 template <typename K, bool HAS_VAL, int BUCKET_THREADS>
 __device__ void bucket_sort_oversize(K* a, K* b, u32* va, u32* vb, int cnt, int low_bits, u32* hist /*[256]*/,
                                      u32* smem) {
-    constexpr int BUCKET_WAVES = BUCKET_THREADS / 64;
+    constexpr int BUCKET_WAVES = BUCKET_THREADS / 64, PER = BUCKET_THREADS < 256 ? 256 / BUCKET_THREADS : 1;  // counters of a thread
     // data starts in b (the partition pass wrote it there) and must end in a
     K* src = b;
     K* dst = a;
@@ -447,15 +447,24 @@ __device__ void bucket_sort_oversize(K* a, K* b, u32* va, u32* vb, int cnt, int 
     for (int p = 0; p < passes; ++p) {
         const int bits = (low_bits - shift) < per ? (low_bits - shift) : per;
         const u32 R = 1u << bits, dmask = R - 1;
-        if (t < 256) hist[t] = 0;
+        for (int i = t; i < 256; i += BUCKET_THREADS) hist[i] = 0;
         __syncthreads();
         for (int i = t; i < cnt; i += BUCKET_THREADS) atomicAdd(&hist[digit_of<K>(coherent_load(&src[i]), shift, dmask)], 1u);
         __syncthreads();
-        u32 tot;
-        const u32 c = (t < 256 && (u32)t < R) ? hist[t] : 0u;
-        const u32 ex = wide_block_exclusive_scan<BUCKET_WAVES>(c, smem, tot);
+        u32 tot, c[PER], sum = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const u32 d = (u32)(t * PER + j);
+            c[j] = d < R ? hist[d] : 0u;
+            sum += c[j];
+        }
+        u32 ex = wide_block_exclusive_scan<BUCKET_WAVES>(sum, smem, tot);
         __syncthreads();
-        if (t < 256) hist[t] = ex;  // running output position of each digit
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {  // running output position of each digit
+            if (t * PER + j < 256) hist[t * PER + j] = ex;
+            ex += c[j];
+        }
         __syncthreads();
         if (t < 64) {
             for (int base = 0; base < cnt; base += 64) {

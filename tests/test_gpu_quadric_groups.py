@@ -1,5 +1,5 @@
 """Vertex quadrics from the groups of the incidence sort, a lane per vertex: vertices of 0 to 16 facets (one lane sorts them), 17 to 64 (a
-wave), one more (the whole bucket is sorted the other way), buckets that end behind the last vertex, few and many keys to a bucket;
+wave), one more (the whole bucket is sorted the other way) and more than a workgroup of 128 lanes keeps in LDS, buckets that end behind the last vertex, few and many keys to a bucket;
 bit for bit against the oracle."""
 import numpy as np
 import pytest
@@ -10,7 +10,8 @@ from test_gpu_facet_rounds import dev, pk  # noqa: F401  (fixture)
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("sizes", [[], [1, 4, 7, 8, 9, 12, 15, 16], [16, 17, 18, 40, 63, 64], [17, 64, 65, 300]], ids=["surface", "lane", "wave", "long"])
+@pytest.mark.parametrize("sizes", [[], [1, 4, 7, 8, 9, 12, 15, 16], [16, 17, 18, 40, 63, 64], [17, 64, 65, 300], [3000]],
+                         ids=["surface", "lane", "wave", "long", "beyond-lds"])
 @pytest.mark.parametrize("w,h", [(53, 57), (300, 241), (700, 501)])
 def test_vertices_of_any_number_of_facets(pk, oracle, sizes, w, h):  # noqa: F811
     V, F = meshgen.noisy_grid(w, h, seed=w)
