@@ -888,7 +888,8 @@ struct BucketLds {
 
 // The cnt keys at kin sorted on their low_bits low bits by one workgroup; then emit(key_at), key_at(i) = the i-th of them (from LDS, or,
 // where they did not fit, from kout).  For cnt = 0 only emit is called.  Where the keys are in LDS by groups, none of which is longer than
-// the lanes and waves sort, groups(R) is asked first whether it makes what is wanted from the R groups as they are, not sorted.
+// the lanes and waves sort, groups(R, false) is asked first whether it makes what is wanted from the R groups as they are, not sorted, and groups(R,
+// true) when each has been sorted.
 template <typename LK, int THREADS, int ITEMS, class Groups, class Emit>
 __device__ __forceinline__ void sort_bucket(BucketLds<LK, THREADS, ITEMS>& L, LK* kin, LK* kout, const int cnt,
                                             const int low_bits, const int group_bits, Groups groups, Emit emit) {
@@ -1054,8 +1055,9 @@ __device__ __forceinline__ void sort_bucket(BucketLds<LK, THREADS, ITEMS>& L, LK
             if (i < items && i * THREADS + t < cnt) skey[gstart[digit_of<LK>(key[i], rest, dmask)] + pos[i]] = key[i];
         __syncthreads();
         if (rest > 0 && !any_long) {
-            if (groups((int)R)) return;
+            if (groups((int)R, false)) return;
             sort_groups(0, (int)R);
+            if (groups((int)R, true)) return;
         } else if (rest > 0) {
             // some group is longer still: the whole bucket through a bitonic network, padded to a power of two
             int P = 64;
@@ -1107,7 +1109,8 @@ struct Bucket {
     }
 };
 
-// ... or, if it has emit_groups(LDS, bucket, R) and rows_are_groups(bucket, R) agrees, from the R groups of a bucket in LDS (BucketLds), unsorted.
+// ... or, if it has emit_groups(LDS, bucket, R) and rows_are_groups(bucket, R) agrees, from the R groups of a bucket in LDS (BucketLds), which are
+// sorted first or not (GROUPS_SORTED).
 template <class Out, class = void>
 struct TakesGroups : std::false_type {};
 template <class Out>
@@ -1133,9 +1136,9 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
             if (S.taken) S.taken[b.number] = 0;
         }
     };
-    auto groups = [&](int R) -> bool {
+    auto groups = [&](int R, bool sorted) -> bool {
         if constexpr (TakesGroups<Out>::value) {
-            if (!out.rows_are_groups(b, R)) return false;
+            if (sorted != Out::GROUPS_SORTED || !out.rows_are_groups(b, R)) return false;
             reset();
             out.template emit_groups<THREADS, ITEMS>(L, b, R);
             return true;
