@@ -210,6 +210,9 @@ __global__ __launch_bounds__(BLOCK) void facet_level_kernel(const float* __restr
                                                             const unsigned* __restrict__ ext, int alpha, int beta,
                                                             int* __restrict__ level) {
     const int first = blockIdx.x * (BLOCK * GEO_ITEMS), last = min(first + BLOCK * GEO_ITEMS, F) - 1;
+    float area[GEO_ITEMS];
+#pragma unroll
+    for (int j = 0; j < GEO_ITEMS; ++j) area[j] = areas[min(first + j * BLOCK + (int)threadIdx.x, last)];
     const int mesh0 = mesh_of_facet(foff, first);  // (the same in all lanes)
     const bool one_mesh = foff[mesh0 + 1] > last;
     float lo, hi;
@@ -219,7 +222,7 @@ __global__ __launch_bounds__(BLOCK) void facet_level_kernel(const float* __restr
         const int f = first + j * BLOCK + (int)threadIdx.x;
         if (f > last) break;
         if (!one_mesh) mesh_extremes(ext, mesh_of_facet(foff, f), lo, hi);
-        const float ratio = hi > lo ? (areas[f] - lo) / (hi - lo) : 0.0f;
+        const float ratio = hi > lo ? (area[j] - lo) / (hi - lo) : 0.0f;
         level[f] = (int)floorf(ratio) * alpha + beta;
     }
 }
