@@ -487,7 +487,7 @@ struct RowLists {
     // Where a group of the sort is a row, its first position is the row's.  (Found among the keys, a key and the one in front of it at a
     // time, before: lists of 5.7 M corners of 960 k vertices 19.9 us, now 17.0; of 115 k members of 41 k clusters 6.2 and 5.2.)
     static constexpr bool GROUPS_SORTED = true;
-    __device__ bool rows_are_groups(const prim::Bucket& b, int R) const { return b.low_bits > ibits && (1 << (b.low_bits - ibits)) == R; }
+    __device__ bool rows_are_groups(bool, const prim::Bucket& b, int R) const { return b.low_bits > ibits && (1 << (b.low_bits - ibits)) == R; }
     template <int THREADS, int ITEMS, class L>
     __device__ __forceinline__ void emit_groups(L& lds, const prim::Bucket& b, int R) const {
         const int t = threadIdx.x, start = (int)b.start, lo = b.number * R, rows = min(R, n_rows - lo);
@@ -566,7 +566,7 @@ struct QuadricRows {
     // GROUP_LANE keys; a wave sorts more).  (With the groups sorted in LDS and the vertices found again among the keys 115 k vertices took 12.3 us, now 9.6, 1.2 M
     // 49 and 42.5, 10.2 M 450 and 421.)
     static constexpr bool GROUPS_SORTED = false;
-    __device__ bool rows_are_groups(const prim::Bucket& b, int R) const { return (1 << (b.low_bits - fbits)) == R && b.low_bits > fbits; }
+    __device__ bool rows_are_groups(bool, const prim::Bucket& b, int R) const { return (1 << (b.low_bits - fbits)) == R && b.low_bits > fbits; }
     template <int G, typename LK>
     __device__ __forceinline__ void add_group(float (&acc)[10], const prim::Bucket& b, const LK* key, int g) const {
         LK k[G];
@@ -2564,7 +2564,7 @@ __global__ __launch_bounds__(BLOCK) void select_release_kernel(Keys K, const int
 // the two founders of a cluster attract: a vertex that joined pulls in nobody.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void absorb_begin_kernel(u64* __restrict__ abid, int* __restrict__ arep,
-                                                             int* __restrict__ acnt, const State* st, int cur, int B,
+                                                             const State* st, int cur, int B,
                                                              const int* __restrict__ nrem,
                                                              const int* __restrict__ matched, int* __restrict__ arem,
                                                              int* __restrict__ acand) {
@@ -2574,7 +2574,6 @@ __global__ __launch_bounds__(BLOCK) void absorb_begin_kernel(u64* __restrict__ a
     for (int w = g; w < nv; w += stride) {
         abid[w] = ABID_NONE;
         arep[w] = -1;
-        acnt[w] = 0;
     }
     for (int b = g; b < B; b += stride) {
         const int left = nrem[b] - matched[b];
@@ -2655,31 +2654,45 @@ __global__ __launch_bounds__(ABSORB_COUNT_THREADS) void absorb_count_kernel(cons
 }
 
 // For every listed edge that still stands: the joining vertex records its cluster's representative
-// (the founding pair's smaller index) and emits the key (representative, vertex); withdrawn ones
-// emit the all-ones key, which sorts behind every real one.
+// (the founding pair's smaller index) and leaves the key (representative, vertex), whose digit is counted; withdrawn ones
+// leave the all-ones key, which the sort does not keep.
 __global__ __launch_bounds__(BLOCK) void absorb_keys_kernel(const int* __restrict__ list, const State* st,
                                                             const u64* __restrict__ ekey,
                                                             const u32* __restrict__ ecost, int vbits,
                                                             const int* __restrict__ mate, const u64* __restrict__ abid,
-                                                            int* __restrict__ arep, int* __restrict__ acnt,
-                                                            u64* __restrict__ akey, TieBreak tb) {
+                                                            int* __restrict__ arep, u64* __restrict__ akey, DigitCount digits,
+                                                            TieBreak tb) {
     const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i >= st->absorb_n) return;
-    const int e = list[i];
-    const u64 k = ekey[e];
-    const int u = (int)(k >> vbits), v = (int)(k & ((1ull << vbits) - 1ull));
-    const int w = joining_end(mate, u, v);
-    u64 out = (vbits >= 32) ? ~0ull : ((1ull << (2 * vbits)) - 1ull);
-    if (w >= 0 && abid[w] == tb.priority(ecost[e], e)) {
-        const int o = (w == u) ? v : u;
-        const int mo = mate[o];
-        const int r = o < mo ? o : mo;
-        arep[w] = r;
-        atomicAdd(&acnt[r], 1);  // (so that representatives nobody joined need not look)
-        out = ((u64)(u32)r << vbits) | (u64)(u32)w;
+    u64 out = edge_sentinel(vbits);
+    if (i < st->absorb_n) {
+        const int e = list[i];
+        const u64 k = ekey[e];
+        const int u = (int)(k >> vbits), v = (int)(k & ((1ull << vbits) - 1ull));
+        const int w = joining_end(mate, u, v);
+        if (w >= 0 && abid[w] == tb.priority(ecost[e], e)) {
+            const int o = (w == u) ? v : u;
+            const int mo = mate[o];
+            const int r = o < mo ? o : mo;
+            arep[w] = r;
+            out = ((u64)(u32)r << vbits) | (u64)(u32)w;
+        }
+        akey[i] = out;
     }
-    akey[i] = out;
+    const bool joins = out != edge_sentinel(vbits);
+    const u32 d = (u32)(out >> digits.shift) & digits.mask;
+    const prim::SameDigit same = prim::wave_same_digit(joins, d);
+    if (joins && same.below == 0) atomicAdd(&digits.hist[d], same.count);
 }
+// ... and the source of their sort, whose lists (RowLists) are what joins every representative's cluster.
+struct JoinedKeys {
+    const u64* p;
+    u64 none;
+    static constexpr int PER = 1;
+    typedef u64 Raw;
+    __device__ __forceinline__ u64 load(int i) const { return p[i]; }
+    __device__ __forceinline__ u64 key(u64 raw, int, int) const { return raw; }
+    __device__ __forceinline__ bool keep(u64 k) const { return k != none; }
+};
 
 // ---------------------------------------------------------------------------
 // S4 + S6: contraction (Alg. 2 lines 12-16) and survivor renumbering
@@ -2732,8 +2745,8 @@ __device__ __forceinline__ void flagged_before(const int* __restrict__ at, int B
 // BLOCK * chunks vertices) and move to their new slot; a pair's representative takes the summed
 // quadric and the pair's target position (the mean; with PLACE_INVERSE the
 // point of least error where there is one).  With ABSORB a cluster may have
-// more members than its pair: `akey` lists (representative, member) in
-// ascending order for the vertices that joined, and quadric and position are
+// more members than its pair: alist[aoff[w]] .. lists, in ascending order, the vertices that joined
+// representative w, and quadric and position are
 // summed over all members in ascending index order, the position sum divided
 // by their number.  vmap[w] = output slot of w's cluster, written by its representative's lane for all its
 // members (numbering and contraction were two launches and an array between them; in one they cost what contracting did).
@@ -2750,7 +2763,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                                                          const int* __restrict__ active, int* __restrict__ done,
                                                          int* __restrict__ htab, int n_clear, u64* __restrict__ vmin0,
                                                          float rcond_min, const int* __restrict__ arep,
-                                                         const int* __restrict__ acnt, const u64* __restrict__ akey, int vbits,
+                                                         const int* __restrict__ aoff, const int* __restrict__ alist,
                                                          const int* __restrict__ guard, HostSignal tell) {
     if (COUNTS && blockIdx.x == 0 && threadIdx.x == 0) tell_host(tell);
     if (guard && *guard == 0) return;  // queued ahead of the host's look, and the selection was not finished
@@ -2813,19 +2826,8 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
         float4 r0 = a[0], r1 = a[1], r2 = a[2], r3 = a[3];
         if (m >= 0) {
             vmap[m] = nw;
-            int j = 0, jend = 0;  // this cluster's part of akey
-            if (ABSORB && acnt[w] > 0) {
-                const int n = st->absorb_n;
-                const u64 first = (u64)(u32)w << vbits;
-                int lo = 0, hi = n;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (akey[mid] >= first) hi = mid; else lo = mid + 1;
-                }
-                j = lo;
-                jend = min(lo + acnt[w], n);
-            }
-            if (!ABSORB || j == jend) {
+            const int j0 = ABSORB ? aoff[w] : 0, jend = ABSORB ? aoff[w + 1] : 0;  // this cluster's part of alist (a pair's lower vertex is not the last one)
+            if (!ABSORB || j0 == jend) {
                 const float4* b = reinterpret_cast<const float4*>(&vin[m]);
                 const float4 s0 = b[0], s1 = b[1], s2 = b[2], s3 = b[3];
                 r0.x = (r0.x + s0.x) * 0.5f; r0.y = (r0.y + s0.y) * 0.5f; r0.z = (r0.z + s0.z) * 0.5f;
@@ -2834,15 +2836,14 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                 r3.x = r3.x + s3.x; r3.y = r3.y + s3.y;
             } else {
                 // merge w < m with the ascending list of joined vertices
-                const u64 low = (1ull << vbits) - 1ull;
                 bool done_w = false, done_m = false;
-                int cnt_in = 0;
+                int cnt_in = 0, j = j0;
                 while (!done_w || !done_m || j < jend) {
                     int x = 0x7FFFFFFF, from = -1;
                     if (!done_w) { x = w; from = 0; }
                     else if (!done_m) { x = m; from = 1; }
                     if (j < jend) {
-                        const int y = (int)(akey[j] & low);
+                        const int y = alist[j];
                         if (y < x) { x = y; from = 2; }
                     }
                     if (from == 0) {

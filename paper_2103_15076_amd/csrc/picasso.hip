@@ -128,7 +128,8 @@ struct picasso_ctx {
     uint64_t opt_shuffle_seed = 0;  // != 0: pairs of equal cost in the order of the seeded tie-break
     u64* abid = nullptr;   // per vertex: cheapest edge through which it could join a pair's cluster
     int* arep = nullptr;   // per vertex: representative of the cluster it joined, or -1
-    int* acnt = nullptr;   // per vertex: how many vertices joined the cluster it represents
+    int* aoff = nullptr;   // per vertex: the first of those that joined the cluster it represents, in joiners()
+    int* joiners() const { return reinterpret_cast<int*>(val32); }  // (free between the edges' sort and the next round)
     int* acand = nullptr;  // per mesh: vertices that could join
     int* arem = nullptr;   // per mesh: budget left after the pairs
     u32* area_ext = nullptr;  // per mesh: largest facet area and largest complement of one (conv::EXT_SLOTS; zero between calls)
@@ -249,7 +250,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     for (int i = 0; i < 2; ++i) x->nf_slots[i] = cv.take<int>(MATCH_SLOTS * MATCH_PAD);
     x->abid = cv.take<u64>(n);
     x->arep = cv.take<int>(n);
-    x->acnt = cv.take<int>(n);
+    x->aoff = cv.take<int>(n + 1);
     x->acand = cv.take<int>(b);
     x->arem = cv.take<int>(b);
     x->area_ext = cv.take<u32>(b * conv::EXT_SLOTS * conv::EXT_PAD);
@@ -746,11 +747,11 @@ void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bo
 
 // Alg. 2 line 11 on the device for the round whose pairs are final (see the kernels).  nrem /
 // h_matched: per-mesh budget and pairs kept (host mirrors); h_joined receives the vertices that
-// join per mesh; *akeys the sorted (representative, vertex) keys, st->absorb_n of them.  Waits for
+// join per mesh; where any does, aoff and joiners() list them by representative.  Waits for
 // the stream once (the per-mesh candidate counts decide whether the budget step is needed).
 int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne, int nv_total, const MeshTab& mt,
-               const TieBreak& tb, const int* nrem, const int* h_matched, int* h_joined, const u64** akeys) {
-    absorb_begin_kernel<<<grid_for(std::max(nv_total, B), 4096), BLOCK, 0, s>>>(c->abid, c->arep, c->acnt, c->st, cur, B, c->nrem,
+               const TieBreak& tb, const int* nrem, const int* h_matched, int* h_joined) {
+    absorb_begin_kernel<<<grid_for(std::max(nv_total, B), 4096), BLOCK, 0, s>>>(c->abid, c->arep, c->st, cur, B, c->nrem,
                                                                               c->matched, c->arem, c->acand);
     absorb_bid_kernel<<<grid_for(std::max(ne, 1), 8192), BLOCK, 0, s>>>(c->ekey, c->ecost, c->st, vbits, c->mate, mt,
                                                                       c->arem, c->abid, tb);
@@ -780,12 +781,20 @@ int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne,
         const int rc = budget_step(c, s, JoinKeys{c->abid}, B, c->voff[cur], nv_total, most, least, c->acand, c->arem, false);
         if (rc != PICASSO_OK) return rc;
     }
-    absorb_keys_kernel<<<grid_for(n_list), BLOCK, 0, s>>>(c->list, c->st, c->ekey, c->ecost, vbits, c->mate, c->abid,
-                                                         c->arep, c->acnt, c->key64[0], tb);
     prim::KeySort<u64> S = key_sort_for(c, false, n_list, (int)n_list, 2 * vbits);
     S.n_ptr = &c->st->absorb_n;
-    if (!prim::key_sort_array(s, S)) return PICASSO_ERR_HIP;
-    *akeys = S.k0;
+    // (few keys over many representatives: a digit or two more, where a group of a bucket is then one of them)
+    const int within = S.low_bits() - vbits, more = within - prim::BUCKET_GROUP_BITS;
+    if (more > 0 && S.digit_bits + more <= prim::NARROW_BITS_MAX) {
+        S.digit_bits += more;
+        S.half = S.fits_half();
+    }
+    rows_of(S, nv_total, vbits, n_list);
+    clear_wide_counts(s, S);
+    absorb_keys_kernel<<<grid_for(n_list), BLOCK, 0, s>>>(c->list, c->st, c->ekey, c->ecost, vbits, c->mate, c->abid,
+                                                         c->arep, c->key64[0], digit_count(S), tb);
+    const RowLists lists{c->aoff, c->joiners(), (int)n_list, nv_total, vbits, S.digit_bits};
+    if (!prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<JoinedKeys>{{c->key64[0], edge_sentinel(vbits)}}, lists)) return PICASSO_ERR_HIP;
     HIP_TRY(c, hipGetLastError());
     return PICASSO_OK;
 }
@@ -917,7 +926,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // has looked; it then goes by what the tail leaves in State (go, guard_nv) and does
         // nothing unless it finished the matching.  clear: slots of the facet set to clear on the way.
         // releases: a budget step has left limits that the count applies.
-        auto issue_contract = [&](int n_joined, const u64* akeys, size_t clear, bool releases, bool guarded, HostSignal tell) {
+        auto issue_contract = [&](int n_joined, size_t clear, bool releases, bool guarded, HostSignal tell) {
             const int nxt = cur ^ 1;
             const int* guard = guarded ? &c->st->go : nullptr;
             const int* n_ptr = guarded ? &c->st->guard_nv : nullptr;
@@ -942,7 +951,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     contract_kernel<PLACE, ABSORB, COUNTS><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, round_map(c, by_facets, round), c->st, cur,  \
                                                            chunks, c->tilesum, prefixed, B, c->voff[cur],             \
                                                            c->voff[nxt], c->active[round & 1], c->done, c->htab, (int)clear, \
-                                                           by_facets ? c->vmin[0] : nullptr, RCOND, c->arep, c->acnt, akeys, vbits, guard, tell)
+                                                           by_facets ? c->vmin[0] : nullptr, RCOND, c->arep, c->aoff, c->joiners(), guard, tell)
             if (c->opt_placement == PLACE_INVERSE) {
                 if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, false, c->opt_rcond_min);
                 else if (counts) PICASSO_CONTRACT(PLACE_INVERSE, false, true, c->opt_rcond_min);
@@ -1045,7 +1054,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                     rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_bound, 0, true, true, tail_done);
                     if (rc != PICASSO_OK) return rc;
                 }
-                issue_contract(0, nullptr, 0, ahead_budget, true, ahead_budget ? nothing : tail_done);
+                issue_contract(0, 0, ahead_budget, true, ahead_budget ? nothing : tail_done);
             } else {
                 signal_kernel<<<1, 64, 0, s>>>(tail_done);
             }
@@ -1120,12 +1129,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 
         // ---- Alg. 2 line 11 (option): un-paired vertices join a neighbouring pair's cluster while budget is left
         int n_joined = 0;
-        const u64* akeys = nullptr;
         for (int b = 0; b < B; ++b) h_joined[b] = 0;
         bool budget_left = false;
         for (int b = 0; b < B; ++b) budget_left |= (h_matched[b] > 0 && nrem[b] > h_matched[b]);
         if (c->opt_absorb && budget_left) {
-            rc = run_absorb(c, s, B, cur, vbits, hst->ne, nv_total, mt, tb, nrem, h_matched, h_joined, &akeys);
+            rc = run_absorb(c, s, B, cur, vbits, hst->ne, nv_total, mt, tb, nrem, h_matched, h_joined);
             if (rc != PICASSO_OK) return rc;
             for (int b = 0; b < B; ++b) n_joined += h_joined[b];
         }
@@ -1149,7 +1157,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const bool last = !work || (c->opt_max_rounds >= 0 && round + 1 >= c->opt_max_rounds);
             const size_t clear = last && slots_clear == 0 ? facet_slots((size_t)nf_bound) : 0;
             tm.begin(round, PICASSO_ST_CONTRACT);
-            issue_contract(n_joined, akeys, clear, releases, false, HostSignal{nullptr, 0});
+            issue_contract(n_joined, clear, releases, false, HostSignal{nullptr, 0});
             tm.end();
             slots_clear = std::max(slots_clear, clear);
         }

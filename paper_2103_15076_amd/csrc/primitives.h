@@ -1109,7 +1109,7 @@ struct Bucket {
     }
 };
 
-// ... or, if it has emit_groups(LDS, bucket, R) and rows_are_groups(bucket, R) agrees, from the R groups of a bucket in LDS (BucketLds), which are
+// ... or, if it has emit_groups(LDS, bucket, R) and rows_are_groups(second, bucket, R) agrees, from the R groups of a bucket in LDS (BucketLds), which are
 // sorted first or not (GROUPS_SORTED).
 template <class Out, class = void>
 struct TakesGroups : std::false_type {};
@@ -1138,7 +1138,7 @@ __global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_s
     };
     auto groups = [&](int R, bool sorted) -> bool {
         if constexpr (TakesGroups<Out>::value) {
-            if (sorted != Out::GROUPS_SORTED || !out.rows_are_groups(b, R)) return false;
+            if (sorted != Out::GROUPS_SORTED || !out.rows_are_groups(second, b, R)) return false;
             reset();
             out.template emit_groups<THREADS, ITEMS>(L, b, R);
             return true;
@@ -1223,11 +1223,17 @@ __device__ __forceinline__ u32 distinct_in_front(const u32* __restrict__ per_buc
     return block_sum(part, smem);
 }
 
-// Two sorts in one launch.
+// Two sorts in one launch (the second one's groups are not taken).
 template <class A, class B>
 struct TwoOuts {
     A a;
     B b;
+    static constexpr bool GROUPS_SORTED = A::GROUPS_SORTED;
+    __device__ bool rows_are_groups(bool second, const Bucket& bk, int R) const { return !second && a.rows_are_groups(false, bk, R); }
+    template <int THREADS, int ITEMS, class L>
+    __device__ __forceinline__ void emit_groups(L& lds, const Bucket& bk, int R) const {
+        a.template emit_groups<THREADS, ITEMS>(lds, bk, R);
+    }
     template <int THREADS, int ITEMS>
     union Lds {
         typename A::template Lds<THREADS, ITEMS> a;
