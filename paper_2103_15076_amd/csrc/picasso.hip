@@ -745,12 +745,10 @@ void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bo
 #undef PICASSO_SUBROUND
 }
 
-// Alg. 2 line 11 on the device for the round whose pairs are final (see the kernels).  nrem /
-// h_matched: per-mesh budget and pairs kept (host mirrors); h_joined receives the vertices that
-// join per mesh; where any does, aoff and joiners() list them by representative.  Waits for
-// the stream once (the per-mesh candidate counts decide whether the budget step is needed).
-int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne, int nv_total, const MeshTab& mt,
-               const TieBreak& tb, const int* nrem, const int* h_matched, int* h_joined) {
+// Alg. 2 line 11 on the device for the round whose pairs are final (see the kernels).  First its candidates, counted per mesh; `counted` is
+// told when the counts are in the read-back area.  ne: the round's edges at most.
+void list_joiners(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne, int nv_total, const MeshTab& mt, const TieBreak& tb,
+                  const HostSignal& counted) {
     absorb_begin_kernel<<<grid_for(std::max(nv_total, B), 4096), BLOCK, 0, s>>>(c->abid, c->arep, c->st, cur, B, c->nrem,
                                                                               c->matched, c->arem, c->acand);
     absorb_bid_kernel<<<grid_for(std::max(ne, 1), 8192), BLOCK, 0, s>>>(c->ekey, c->ecost, c->st, vbits, c->mate, mt,
@@ -759,10 +757,13 @@ int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int ne,
     JoinListOut jl{c->list};
     prim::compact(s, jp, jp, jl, &c->st->ne, ne, c->tilesum, &c->st->absorb_n);
     int* host_counts = c->h_pin_dev + HDR_STATE_INTS + c->cap_b;  // (the offsets' slots of the read-back area: free until the end)
-    const HostSignal counted = next_signal(c);
-    absorb_count_kernel<<<1, ABSORB_COUNT_THREADS, 0, s>>>(c->list, c->st, c->ekey, vbits, B, c->voff[cur], c->acand, host_counts,
-                                            counted);
-    HIP_TRY(c, wait_for_signal(c, s, counted));
+    absorb_count_kernel<<<1, ABSORB_COUNT_THREADS, 0, s>>>(c->list, c->st, c->ekey, vbits, B, c->voff[cur], c->acand, host_counts, counted);
+}
+// Then, when the host has the counts, what the budgets leave of them.  nrem / h_matched: per-mesh budget and pairs kept (host mirrors);
+// h_joined receives the vertices that join per mesh; where any does, aoff and joiners() list them by representative.  (The counts decide
+// whether the budget step is needed.)
+int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int nv_total, const TieBreak& tb, const int* nrem,
+               const int* h_matched, int* h_joined) {
     const int* h_cand = c->h_pin + HDR_STATE_INTS + c->cap_b;
     long long n_list = 0;
     int most = 0, least = 0x7FFFFFFF;
@@ -986,6 +987,10 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             ahead_budget = seg_bound > 0;
             if (ahead_budget && !(likely && seg_bound <= c->opt_trunc_block_max)) ahead_ok = false;
         }
+        // Line 11's candidates likewise, where no budget step can come in front of them: one look of the host less (its counts come with the tail's;
+        // should the tail hand back, they are made again).  Not in listed rounds, whose lists lie where the candidates go.
+        bool joiners_ahead = c->opt_absorb && !stats && c->opt_ahead && std::max(H, 1) < LISTED_MIN_EDGES;
+        for (int b = 0; b < B; ++b) joiners_ahead &= !act[b] || 2ll * nrem[b] >= nvb[b];
         bool ahead = false;  // the kernels are queued and the tail has finished the matching
 
         // ---- S3: selection sub-rounds
@@ -1055,6 +1060,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                     if (rc != PICASSO_OK) return rc;
                 }
                 issue_contract(0, 0, ahead_budget, true, ahead_budget ? nothing : tail_done);
+            } else if (joiners_ahead) {
+                list_joiners(c, s, B, cur, vbits, ne_bound, nv_total, mt, tb, tail_done);
             } else {
                 signal_kernel<<<1, 64, 0, s>>>(tail_done);
             }
@@ -1133,7 +1140,12 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         bool budget_left = false;
         for (int b = 0; b < B; ++b) budget_left |= (h_matched[b] > 0 && nrem[b] > h_matched[b]);
         if (c->opt_absorb && budget_left) {
-            rc = run_absorb(c, s, B, cur, vbits, hst->ne, nv_total, mt, tb, nrem, h_matched, h_joined);
+            if (!joiners_ahead) {
+                const HostSignal counted = next_signal(c);
+                list_joiners(c, s, B, cur, vbits, hst->ne, nv_total, mt, tb, counted);
+                HIP_TRY(c, wait_for_signal(c, s, counted));
+            }
+            rc = run_absorb(c, s, B, cur, vbits, nv_total, tb, nrem, h_matched, h_joined);
             if (rc != PICASSO_OK) return rc;
             for (int b = 0; b < B; ++b) n_joined += h_joined[b];
         }
