@@ -107,14 +107,16 @@ enum picasso_option {
                                       synchronises the stream if it has not come by then.  1
                                       (default) = 20,000 us; 0 = synchronise the stream at once;
                                       at most 10,000,000.  The results are the same either way.  */
-    PICASSO_OPT_LAUNCH_AHEAD = 11, /* 1 (default): in a round of at most 2^20 facets in
+    PICASSO_OPT_LAUNCH_AHEAD = 11, /* 1 (default): in a round of at most 2^22 facets in
                                       which the outcome of the selection decides nothing but
                                       counts (no mesh can exceed its budget, or some mesh surely
                                       will and the per-mesh budget step can take it), the kernels
                                       that follow the selection are queued behind it before the
-                                      host has looked; they do nothing if the selection turns out
-                                      to need more passes.  0: queued after the look.  Same
-                                      results.                                                   */
+                                      host has looked, as are those that find line 11's
+                                      candidates in a round of less than 2^20 half-edges in which
+                                      no mesh can exceed its budget; they do nothing, or are
+                                      queued again, if the selection turns out to need more
+                                      passes.  0: queued after the look.  Same results.          */
     PICASSO_OPT_TRUNC_WIDTH = 12,  /* test hook for the per-mesh budget step: 0 (default) = its
                                       workgroups take up to 4,096 or 32,768 cost keys as the
                                       largest mesh needs; 4, 8, 16 or 32 = always 1,024 times
