@@ -3,6 +3,7 @@ four, rows with as many items as one lane walks, one more (the whole wave's) and
 waves and workgroups incomplete; against the fp64 oracle with the bounds of test_gpu_conv."""
 import numpy as np
 import pytest
+import torch
 from scipy.special import softmax
 
 from test_gpu_conv import _close, _gw_terms, ctx, dev, pk  # noqa: F401  (fixtures)
@@ -50,3 +51,30 @@ def test_narrow_rows(pk, ctx, oracle, C, T, sizes, n):  # noqa: F811
         _close(got[1], ref[1], _gw_terms(nF, 6), bar[1], "f2v gw")
         if want:
             _close(got[2], ref[2], 6 * C, bar[2], "f2v gpi")
+
+
+@pytest.mark.parametrize("C,T", [(3, 6), (6, 6), (8, 5)])
+def test_narrow_rows_at_any_4_byte_address(pk, ctx, oracle, C, T):  # noqa: F811
+    """Arrays that begin 4, 8 and 12 bytes behind a 16-byte line give what aligned ones give, bit for bit."""
+    F = _fans([64, 65, 3, 200], 500)
+    n, nF = 500, F.shape[0]
+    rng = np.random.default_rng(C)
+    host = [rng.normal(size=s).astype(np.float32) for s in ((n, C), (n, C), (nF, C), (nF, C), (3, C), (T, C))]
+    pi = softmax(rng.normal(size=(nF, T)), axis=1).astype(np.float32)
+    off, cor = ctx.picasso_vertex_corner_csr(dev(F), n)
+
+    def calls(shift):
+        def put(a):
+            b = torch.zeros(a.size + 4, device="cuda:0")
+            b[shift:shift + a.size] = torch.from_numpy(a.reshape(-1)).to("cuda:0")
+            return b[shift:shift + a.size].reshape(a.shape)
+        x, gx, y, gy, w3, w = map(put, host)
+        p = put(pi)
+        out = [*ctx.picasso_v2f_backward(gy, x, dev(F), None, w3, off, cor), ctx.picasso_f2v_forward(y, p, w, off, cor, n),
+               *ctx.picasso_f2v_backward(gx, y, p, w, dev(F), off)]
+        return [t.cpu().numpy().view(np.uint32) for t in out]
+
+    want = calls(0)
+    for shift in (1, 2, 3):
+        for a, b in zip(calls(shift), want):
+            np.testing.assert_array_equal(a, b)
