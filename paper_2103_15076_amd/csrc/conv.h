@@ -946,14 +946,40 @@ __device__ __forceinline__ float row_sum(float v, int q, int n) {
     return v;
 }
 
+// V such sums at once, for rows of Q = 2 d lanes, a power of two (such rows begin at multiples of Q).  A step halves the values: a lane keeps
+// the half that its bit d of q names and gives the other away; then, one value left, the further bits are summed as they are.  V - 1
+// shuffles or fewer and one for each further bit, where one by one they take V for every bit.  Lane q holds, in front of v, the sums
+// q V / Q up to (q + 1) V / Q (V >= Q), or the sum q V / Q rounded down (V < Q).
+template <int V>
+__device__ __forceinline__ void shared_row_sums(float (&v)[V], int q, int d) {
+    if (d == 0) return;
+    if constexpr (V == 1) {
+        for (; d > 0; d >>= 1) v[0] = v[0] + __shfl_xor(v[0], d, 64);
+    } else {
+        const bool up = (q & d) != 0;
+        float half[V / 2];
+#pragma unroll
+        for (int i = 0; i < V / 2; ++i) half[i] = (up ? v[i + V / 2] : v[i]) + __shfl_xor(up ? v[i] : v[i + V / 2], d, 64);
+        shared_row_sums<V / 2>(half, q, d >> 1);
+#pragma unroll
+        for (int i = 0; i < V / 2; ++i) v[i] = half[i];
+    }
+}
+
 // Backward pass of facet2vertex (supplementary, facet2vertex kernel).  With G = the incoming gradients of a
 // facet's three vertices, each divided by its |N(v)|, summed:
 //   gy_f = (sum_t pi_ft w_t) G,   gw_t = sum_f pi_ft (J_f G),   gpi_ft = sum over channels of w_t (J_f G),
 // so one pass over the facets, which gathers the vertices' gradients once, makes all three (one pass for each
 // before).  It takes the filter rows t0 .. t0 + rows - 1, rows <= 4 NP (slots as above); gy is made by the pass with t0 = 0, whose caller leaves
-// it null in the others.  GPI: a row's lanes lie in one wave (row_map's one_wave) and are summed there.  A wave
+// it null in the others.  GPI: a row's lanes lie in one wave (row_map's one_wave) and each component's product is summed across them.  Bound by
+// those shuffles, log2(Q) for a component, where they are taken one by one (GPI_ANY).  Rows of 2^k lanes sum 4 or 8 components together
+// (GPI_POW2): with Q = 16, eight components take 8 shuffles for 32.  The pass with all three results, 240 k vertices, 16 / 32 / 64 / 128 channels,
+// T = 6: 34.5 / 57.7 / 130.9 / 274.5 -> 30.8 / 43.9 / 88.6 / 170.3 us; T = 10: 62.7 / 120.3 / 177.7 / 388.6 -> 51.7 / 80.9 / 117.5 / 229.6; T = 1 by 1 to
+// 5 % less.  Not with 13 to 16 components (NP = 4): the products kept back take 203 registers for 166 and so one of three waves; 360 k
+// vertices, T = 13, 16 / 32 channels: 71 / 152 us one by one, 86 / 170 together.  A wave
 // takes per_wave facets at a time, whose indices, counts and coefficients it brings to LDS, one facet per lane.
-template <int NP, int KIND, bool GPI>
+enum { GPI_NONE, GPI_ANY, GPI_POW2 };
+template <int NP, int KIND, int GPI>
 __global__ __launch_bounds__(BLOCK) void f2v_backward_kernel(const float* __restrict__ gx, const float* __restrict__ y, int C,
                                                              const float* __restrict__ pi, int T, int t0, int rows,
                                                              const float* __restrict__ w,
@@ -961,7 +987,7 @@ __global__ __launch_bounds__(BLOCK) void f2v_backward_kernel(const float* __rest
                                                              const int* __restrict__ off, int N, int chunk, int per_wave,
                                                              float* __restrict__ gy, float* __restrict__ partial,
                                                              float* __restrict__ gpi, RowMap map) {
-    constexpr int TT = 4 * NP;
+    constexpr int TT = 4 * NP, SHARED = NP == 2 ? 8 : 4;  // SHARED: components summed together
     __shared__ float4 wl[TT * 64 > 2 * BLOCK ? TT * 64 : 2 * BLOCK];
     __shared__ int4 sv[BLOCK];         // per facet of the waves' batches: its vertices,
     __shared__ float4 sn[BLOCK], sr[BLOCK];  // ... their |N(v)| and the reciprocals,
@@ -994,9 +1020,9 @@ __global__ __launch_bounds__(BLOCK) void f2v_backward_kernel(const float* __rest
         for (int i0 = 0; i0 < n; i0 += map.rw) {
             const int i = i0 + l.r, f = base + i, at_i = w0 + min(i, n - 1);
             const bool on = l.on && i < n;
-            if (!GPI && !on) break;
+            if (GPI == GPI_NONE && !on) break;
             Pack gv[3] = {}, yf{};
-            if (!GPI || on) {
+            if (GPI == GPI_NONE || on) {
                 const int4 v = sv[at_i];
                 gv[0] = load_row<KIND>(row_at<KIND>(gx, v.x, C, c0), left);
                 gv[1] = load_row<KIND>(row_at<KIND>(gx, v.y, C, c0), left);
@@ -1005,6 +1031,7 @@ __global__ __launch_bounds__(BLOCK) void f2v_backward_kernel(const float* __rest
             }
             const float4 nn = sn[at_i], rr = sr[at_i];
             Pack g, h, coef{};
+            float dots[SHARED] = {};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 g.v[k] = (quotient(gv[0].v[k], nn.x, rr.x) + quotient(gv[1].v[k], nn.y, rr.y)) + quotient(gv[2].v[k], nn.z, rr.z);
@@ -1023,11 +1050,25 @@ __global__ __launch_bounds__(BLOCK) void f2v_backward_kernel(const float* __rest
                         coef.v[2] = fmaf(p[tq], wt.z, coef.v[2]); coef.v[3] = fmaf(p[tq], wt.w, coef.v[3]);
 #pragma unroll
                         for (int k = 0; k < 4; ++k) gw[t][k] = fmaf(p[tq], h.v[k], gw[t][k]);
-                        if constexpr (GPI) {
+                        if constexpr (GPI != GPI_NONE) {
                             float d = fmaf(wt.w, h.v[3], fmaf(wt.z, h.v[2], fmaf(wt.y, h.v[1], wt.x * h.v[0])));
-                            d = row_sum(d, lq, map.Q);
-                            if (on && lq == 0) gpi[(size_t)f * T + t0 + slot_component<NP>(t, rows)] = d;
+                            if constexpr (GPI == GPI_POW2) {
+                                dots[t % SHARED] = d;
+                            } else {
+                                d = row_sum(d, lq, map.Q);
+                                if (on && lq == 0) gpi[(size_t)f * T + t0 + slot_component<NP>(t, rows)] = d;
+                            }
                         }
+                    }
+                }
+                if constexpr (GPI == GPI_POW2) {
+                    if ((4 * gq + 4) % SHARED == 0) {
+                        shared_row_sums<SHARED>(dots, lq, map.Q >> 1);
+                        const int each = max(SHARED / map.Q, 1), way = max(map.Q / SHARED, 1);  // sums to a lane, lanes to a sum
+                        const int first = lq / way * each, t1 = 4 * gq + 4 - SHARED + first;
+#pragma unroll
+                        for (int i = 0; i < SHARED; ++i)
+                            if (on && lq % way == 0 && i < each && slot_used<NP>(t1 + i, rows)) gpi[(size_t)f * T + t0 + slot_component<NP>(t1 + i, rows)] = dots[i];
                     }
                 }
             }

@@ -1918,14 +1918,15 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
             const int rc = split_filter_rows(c, F, rows, C, per_wave * (pool::BLOCK / 64), rows <= 4 ? 6 : (rows <= 12 ? 4 : 3), d_gw != nullptr, &sp);
             if (rc != PICASSO_OK) return rc;
             const dim3 grid(sp.groups, pool::row_parts(m));
+#define PICASSO_F2V_BACK_GPI(NP, K, GPI)                                                                              \
+    conv::f2v_backward_kernel<NP, K, GPI><<<grid, pool::BLOCK, 0, s>>>(                                               \
+        d_gx, d_y, C, d_pi, T, t0, rows, d_w, d_facets, F, d_offsets, N, sp.chunk, per_wave, gy, sp.partial, d_gpi, m)
 #define PICASSO_F2V_BACK(NP, K)                                                                                       \
     do {                                                                                                              \
-        if (gpi_fused)                                                                                                \
-            conv::f2v_backward_kernel<NP, K, true><<<grid, pool::BLOCK, 0, s>>>(                                      \
-                d_gx, d_y, C, d_pi, T, t0, rows, d_w, d_facets, F, d_offsets, N, sp.chunk, per_wave, gy, sp.partial, d_gpi, m); \
-        else                                                                                                          \
-            conv::f2v_backward_kernel<NP, K, false><<<grid, pool::BLOCK, 0, s>>>(                                     \
-                d_gx, d_y, C, d_pi, T, t0, rows, d_w, d_facets, F, d_offsets, N, sp.chunk, per_wave, gy, sp.partial, d_gpi, m); \
+        /* (components together where GPI_POW2 is the faster: conv.h) */                                               \
+        if (gpi_fused && (m.Q & (m.Q - 1)) == 0) PICASSO_F2V_BACK_GPI(NP, K, NP <= 3 ? conv::GPI_POW2 : conv::GPI_ANY); \
+        else if (gpi_fused) PICASSO_F2V_BACK_GPI(NP, K, conv::GPI_ANY);                                               \
+        else PICASSO_F2V_BACK_GPI(NP, K, conv::GPI_NONE);                                                             \
     } while (0)
 #define PICASSO_CALL(K)                         \
     if (rows <= 4) PICASSO_F2V_BACK(1, K);      \
@@ -1935,6 +1936,7 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
             PICASSO_ROW_KINDS(C, std::max(C, T), std::max(N, F), PICASSO_CALL);
 #undef PICASSO_CALL
 #undef PICASSO_F2V_BACK
+#undef PICASSO_F2V_BACK_GPI
             if (d_gw) sum_filter_rows(s, sp, rows * C, d_gw + (size_t)t0 * C);
         }
     }
