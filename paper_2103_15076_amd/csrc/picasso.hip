@@ -60,7 +60,9 @@ struct picasso_ctx {
     int* fcur = nullptr;                // the facets, re-indexed in place round by round
     int* fmap = nullptr;                // ... after the last round, before compaction
     int* cid = nullptr;
-    u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys); the filter gradients' partial sums lie from the first to ecost
+    char* sort_buf = nullptr;            // the five arrays below in one piece, all of which the filter gradients' partial sums may take
+    size_t sort_bytes = 0;
+    u64* key64[2] = {nullptr, nullptr};  // sort buffers (3F keys)
     u32* val32 = nullptr;                // ... for the values of the exported sorts
     u64* ekey = nullptr;
     u32* ecost = nullptr;
@@ -207,11 +209,19 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->fcur = cv.take<int>(3 * f);
     x->fmap = cv.take<int>(3 * f);
     x->cid = cv.take<int>(n);
-    x->key64[0] = cv.take<u64>(h);
-    x->key64[1] = cv.take<u64>(h);
-    x->val32 = cv.take<u32>(h);
-    x->ekey = cv.take<u64>(h);
-    x->ecost = cv.take<u32>(h);
+    auto sort_buffers = [&](char* at) {
+        Carver in;
+        in.base = at;
+        x->key64[0] = in.take<u64>(h);
+        x->key64[1] = in.take<u64>(h);
+        x->val32 = in.take<u32>(h);
+        x->ekey = in.take<u64>(h);
+        x->ecost = in.take<u32>(h);
+        return in.off;
+    };
+    x->sort_bytes = sort_buffers(nullptr);
+    x->sort_buf = cv.take<char>(x->sort_bytes);
+    sort_buffers(x->sort_buf);
     for (int i = 0; i < 3; ++i) x->vmin[i] = cv.take<u64>(n);
     x->mate = cv.take<int>(n);
     x->newid = cv.take<int>(n);
@@ -1320,7 +1330,7 @@ int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts,
 
 // Filter gradients of the convolutions' backward passes: `rows` x C values summed over n_rows rows in two stages
 // (conv::rows_to_partial, conv::reduce_rows_stage2_kernel).  Stage 1's workgroups leave their partial sums in the
-// context's sort buffers.  As many workgroups as the chip holds at once (256 compute units; a workgroup takes several
+// context's sort buffers (sort_buf).  As many workgroups as the chip holds at once (256 compute units; a workgroup takes several
 // turns of rows_per_turn rows, keeping their sums in registers), fewer where there are not so many turns or the
 // buffer does not hold their partials.
 struct FilterSplit {
@@ -1357,10 +1367,10 @@ bool narrow_rows(int C, int width, long long max_rows) {
 
 int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_turn, int blocks_per_cu, bool wanted,
                       FilterSplit* out) {
-    // (The sorts' buffers from key64[0] to ecost lie behind one another.  With the first alone 22 k facets of 200 channels and 6
-    // components left 110 workgroups to facet2vertex's backward pass, 56 us; now 440, 23.)
+    // (With the first of the sorts' buffers alone 22 k facets of 200 channels and 6 components left 110
+    // workgroups to facet2vertex's backward pass, 56 us; now 440, 23.)
     const size_t h = (size_t)3 * (size_t)c->max_facets;
-    const size_t cap = (size_t)(reinterpret_cast<char*>(c->ecost + h) - reinterpret_cast<char*>(c->key64[0])) / sizeof(float);
+    const size_t cap = c->sort_bytes / sizeof(float);
     const size_t per_group = (size_t)rows * C;
     if (wanted && per_group > h * sizeof(u64) / sizeof(float)) return PICASSO_ERR_WORKSPACE;
     const long long turns = ((long long)n_rows + rows_per_turn - 1) / rows_per_turn;
@@ -1371,7 +1381,7 @@ int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_
     if (groups >= 8 && (groups + 7) / 8 * 8 <= most) groups = (groups + 7) / 8 * 8;  // (see conv::xcd_block)
     out->chunk = (int)std::min<long long>(per_block * rows_per_turn, 0x7FFFFFFFll / groups);
     out->groups = (int)groups;
-    out->partial = wanted ? reinterpret_cast<float*>(c->key64[0]) : nullptr;
+    out->partial = wanted ? reinterpret_cast<float*>(c->sort_buf) : nullptr;
     return PICASSO_OK;
 }
 void sum_filter_rows(hipStream_t s, const FilterSplit& sp, int width, float* d_out) {
