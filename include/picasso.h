@@ -140,7 +140,7 @@ enum picasso_option {
 #define PICASSO_STATS_ROUNDS 32
 enum picasso_stage { /* index into picasso_stats.ms_stage[round][...] */
     PICASSO_ST_QUADRICS = 0, /* S0, round 0 only */
-    PICASSO_ST_EDGES = 1,    /* S1 emit + sort + unique (+ fused S2 cost) */
+    PICASSO_ST_EDGES = 1,    /* S1 and S2: by facets their costs, else emit + sort + unique (+ fused cost) */
     PICASSO_ST_SELECT = 2,   /* S3 sub-rounds (+ budget truncation, S2b) */
     PICASSO_ST_CONTRACT = 3, /* S4 + S6 vertex side */
     PICASSO_ST_FACETS = 4,   /* S5 facet clean-up + compaction */
@@ -153,7 +153,8 @@ typedef struct picasso_stats {
     int32_t nv[PICASSO_STATS_ROUNDS];        /* vertices entering round r                           */
     int32_t nf[PICASSO_STATS_ROUNDS];        /* facets entering round r (after the first: those with three
                                                 distinct corners; repeated ones go at the end)      */
-    int32_t ne[PICASSO_STATS_ROUNDS];        /* distinct edges in round r                           */
+    int32_t ne[PICASSO_STATS_ROUNDS];        /* distinct edges in round r (counted for the statistics
+                                                alone where the round goes by facets: in no time below) */
     int32_t nsel[PICASSO_STATS_ROUNDS];      /* vertices removed in round r (pairs; + joiners of line 11) */
     int32_t subrounds[PICASSO_STATS_ROUNDS]; /* selection sub-rounds launched in round r            */
     float ms_stage[PICASSO_STATS_ROUNDS][PICASSO_ST_COUNT];
@@ -178,8 +179,8 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  * bytes a launch of each is charged with (what the step has to move at least, from the sizes of the
  * round it runs in: nv vertices, nf facets, H = 3 nf half-edges, E distinct edges; N, F = the call's
  * input sizes):
- * In a call that needs the edges' numbers (shuffle, line 11, statistics) the edges of a round are sorted, in any other one
- * its rounds go by facets (edges met once per facet that has them) and SORT does not run.
+ * In a call that needs the edges' numbers (shuffle, line 11), and in one that gives statistics and whose kernels are bracketed at the
+ * same time, the edges of a round are sorted, in any other one its rounds go by facets (edges met once per facet that has them) and SORT does not run.
  *   SORT          per-bucket kernel of the edge-key sort (Alg. 2 line 1): every key read once as a 4-byte
  *                 word, 4 H, the distinct ones written, 4 E.
  *   UNIQUE_COST   costs (Alg. 2 line 2) and first bids of the distinct edges: 4 E read + 13 E (edge key, cost

@@ -1499,6 +1499,32 @@ __global__ __launch_bounds__(THREADS, FIRST ? 1 : 6) void facet_costs_kernel(int
     if (!FIRST && t == 0 && n > 0) atomicAdd(&nf_slots[(blockIdx.x & (MATCH_SLOTS - 1)) * MATCH_PAD], n);
 }
 
+// The distinct edges of such a round, for the statistics: the sides of the facets entered into a set (open addressing over `slots` >= 6 F slots,
+// all EDGE_NONE beforehand, so that at least half stay free), those that were not there yet counted.
+constexpr u64 EDGE_NONE = ~0ull;
+__global__ __launch_bounds__(BLOCK) void count_edges_kernel(const int* __restrict__ fcur, int F, const int* __restrict__ fcount,
+                                                            int tile_shift, u64* __restrict__ set, u64 slots, int* __restrict__ ne) {
+    int fresh = 0;
+    for (long long f = (long long)blockIdx.x * BLOCK + threadIdx.x; f < F; f += (long long)gridDim.x * BLOCK) {
+        if (fcount && (int)(f & ((1 << tile_shift) - 1)) >= fcount[f >> tile_shift]) continue;
+        const Corners q = load_corners(fcur, (size_t)f);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int a = corner(q, c), b = corner(q, c == 2 ? 0 : c + 1);
+            if (a == b) continue;
+            const u64 key = ((u64)(u32)min(a, b) << 32) | (u64)(u32)max(a, b);
+            for (u64 h = __umul64hi(key * 0x9E3779B97F4A7C15ull, slots);; h = h + 1 == slots ? 0 : h + 1) {
+                const u64 there = atomicCAS(&set[h], EDGE_NONE, key);
+                fresh += there == EDGE_NONE ? 1 : 0;
+                if (there == EDGE_NONE || there == key) break;
+            }
+        }
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) fresh += __shfl_xor(fresh, d, 64);
+    if (prim::lane_id() == 0 && fresh) atomicAdd(ne, fresh);
+}
+
 // The pairs formed so far, counted by their lower vertices, COUNT_VERTICES to a workgroup.  A vertex is paired if it has a partner already, or if
 // in the sub-round of this launch (whose bids are `cur`) the best bid on it names a vertex whose best bid names it; its partner is then being
 // written by other workgroups.  Old bids do no harm: an edge of which both ends hold the bid bid on both in one sub-round, in which it was accepted.

@@ -283,9 +283,10 @@ struct StageTimer {
     bool on;
     int n_recs = 0;  // records in c->st_recs
     int open = -1;
+    // (stage PICASSO_ST_COUNT: work for the statistics alone, which is no part of the call's time)
     void begin(int round, int stage) {
         constexpr int cap = (int)(sizeof(c->st_recs) / sizeof(c->st_recs[0]));
-        if (!on || n_recs >= cap || c->n_ev + 2 > (int)(sizeof(c->ev) / sizeof(c->ev[0]))) return;
+        if ((!on && stage != PICASSO_ST_COUNT) || n_recs >= cap || c->n_ev + 2 > (int)(sizeof(c->ev) / sizeof(c->ev[0]))) return;
         const StageRec r{round, stage, c->n_ev, c->n_ev + 1};
         c->n_ev += 2;
         (void)hipEventRecord(c->ev[r.e0], s);
@@ -293,17 +294,18 @@ struct StageTimer {
         open = n_recs++;
     }
     void end() {
-        if (!on || open < 0) return;
+        if (open < 0) return;
         (void)hipEventRecord(c->ev[c->st_recs[open].e1], s);
         open = -1;
     }
     void collect(picasso_stats* stats) {
-        if (!on || !stats) return;
+        if (!stats) return;
         for (int i = 0; i < n_recs; ++i) {
             const StageRec& r = c->st_recs[i];
             float ms = 0.f;
-            if (hipEventElapsedTime(&ms, c->ev[r.e0], c->ev[r.e1]) == hipSuccess && r.round < PICASSO_STATS_ROUNDS)
-                stats->ms_stage[r.round][r.stage] += ms;
+            if (hipEventElapsedTime(&ms, c->ev[r.e0], c->ev[r.e1]) != hipSuccess || r.round >= PICASSO_STATS_ROUNDS) continue;
+            if (r.stage == PICASSO_ST_COUNT) stats->ms_total -= ms;
+            else stats->ms_stage[r.round][r.stage] += ms;
         }
     }
 };
@@ -533,6 +535,19 @@ void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cu
 #undef PICASSO_FACET_COSTS_PLACE
 #undef PICASSO_FACET_COSTS_PER
 #undef PICASSO_FACET_COSTS
+}
+
+// The distinct edges of a round by facets, for the statistics.  (In front of the selection the sorts' buffers are free but for the costs, which lie
+// behind the first two, of 48 bytes a facet.)
+void launch_count_edges(picasso_ctx* c, hipStream_t s, int round_, int F) {
+    const long long slots = 6ll * F, words = 2 * slots;
+    u32* const set = reinterpret_cast<u32*>(c->sort_buf);
+    for (long long at = 0; at < words; at += 1 << 30) {
+        const int n = (int)std::min(words - at, 1ll << 30);
+        prim::fill_u32_kernel<<<grid_for(n), BLOCK, 0, s>>>(set + at, n, ~0u);
+    }
+    count_edges_kernel<<<grid_for(F, 8192), BLOCK, 0, s>>>(c->fcur, F, round_ > 0 ? c->fcount() : nullptr, ceil_log2(facet_tile(F)),
+                                                          reinterpret_cast<u64*>(set), (u64)slots, &c->st->ne);
 }
 
 // Up to this many facets the facet set is cleared by the call's first kernel (see launch_init).
@@ -882,8 +897,9 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // input, not on each other: they share their launches.  (Not when stage times are being recorded, to keep them
     // attributable, and in a call whose kernels are bracketed by events: a bracketed kernel then has the chip to itself,
     // and its duration is its own.)
-    // The rounds go by facets where nothing needs the edges' numbers (see facet_costs_kernel).
-    const bool by_facets = c->opt_shuffle_seed == 0 && !c->opt_absorb && !stats;
+    // The rounds go by facets where nothing needs the edges' numbers (see facet_costs_kernel; a call that gives statistics and
+    // brackets its kernels brackets those of the sorts).
+    const bool by_facets = c->opt_shuffle_seed == 0 && !c->opt_absorb && !(stats && c->kt_this_call);
     const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
                           edge_sort(c, N, F, F, 3ll * F).half == incidence_sort(c, N, F).half;
     tm.begin(0, PICASSO_ST_QUADRICS);
@@ -932,6 +948,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         }
         renumbered = false;
         tm.end();
+        if (by_facets && stats && F > 0 && round < PICASSO_STATS_ROUNDS) {
+            tm.begin(round, PICASSO_ST_COUNT);
+            launch_count_edges(c, s, round, F);
+            tm.end();
+        }
 
         // The contraction.  `guarded`: queued behind the selection tail before the host
         // has looked; it then goes by what the tail leaves in State (go, guard_nv) and does
