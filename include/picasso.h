@@ -116,7 +116,8 @@ enum picasso_option {
                                       candidates in a round of less than 2^20 half-edges in which
                                       no mesh can exceed its budget; they do nothing, or are
                                       queued again, if the selection turns out to need more
-                                      passes.  0: queued after the look.  Same results.          */
+                                      passes (of a selection that then goes on slowly, nothing is
+                                      queued ahead).  0: queued after the look.  Same results.   */
     PICASSO_OPT_TRUNC_WIDTH = 12,  /* test hook for the per-mesh budget step: 0 (default) = its
                                       workgroups take up to 4,096 or 32,768 cost keys as the
                                       largest mesh needs; 4, 8, 16 or 32 = always 1,024 times

@@ -1252,7 +1252,7 @@ __global__ __launch_bounds__(BLOCK) void select_subround_kernel(SelArgs A, int k
 // 16 bytes per live edge in a row, where a walk over all edges' states fetched the keys and costs of a few per cent of them
 // line by line.  A workgroup has a part of the edges to itself, its part of the lists is the same places of lkey, lcost and lidx, and
 // it leaves their number in lcount: no counter is shared.  Sub-round 0 takes all edges, LISTED_TILE to a workgroup; a
-// later one takes the `group` parts of 2^span_shift edges in front of it together and joins what is left of them (in place: a live
+// later one takes `group` parts of 2^part_shift tiles together and joins what is left of them (in place: a live
 // edge's new place is never behind its old one).  Bound by memory and by the bids' atomics; sub-round 0 has four edges per lane in
 // flight, the others two.  10.2 M vertices, 31 M edges: the first round's seven sub-rounds 967 -> 740 us, all three rounds' 1,800 -> 1,380;
 // 1.2 M: 117 -> 95 and 253 -> 205.  Bids put together in LDS in the first three sub-rounds, while several live edges share a line of vertices
@@ -1261,15 +1261,25 @@ constexpr int LISTED_MIN_EDGES = 1 << 20;  // below this the sub-rounds are at t
 constexpr int LISTED_TILE_SHIFT = 10, LISTED_TILE = 1 << LISTED_TILE_SHIFT, LISTED_PER_LANE = LISTED_TILE / BLOCK;
 constexpr int LISTED_GROUP_MAX = 4;
 constexpr int LISTED_LINES = 256;
-// Parts that sub-round k >= 1 joins, and how many tiles a part is (bits): a workgroup has a few hundred live edges every time.
-constexpr int LISTED_PART_SHIFT_MAX = 6;
-inline int listed_group_shift(int k) { return k <= 3 ? 1 : 2; }
-inline int listed_part_shift(int k) {
-    int shift = 0;
-    for (int j = 1; j < k && shift < LISTED_PART_SHIFT_MAX; ++j) shift += listed_group_shift(j);
+// How many parts sub-round k >= 1 joins, and how many tiles a part is (bits), of `tiles` tiles: a workgroup has a few hundred live edges every time
+// where these get fewer as on surfaces of varied costs.  Where they hardly do (ties: on a flat lattice of 200 x 200 vertices a round takes 299
+// sub-rounds), joining on would leave the whole chip's work to a few workgroups (five there, 230 us a sub-round), so that at
+// least LISTED_GROUPS_MIN workgroups are left.
+constexpr int LISTED_GROUPS_MIN = 512;
+inline int listed_group_shift(int k, int part_shift, int tiles) {
+    int shift = k <= 3 ? 1 : 2;
+    while (shift > 0 && ((tiles - 1) >> (part_shift + shift)) + 1 < LISTED_GROUPS_MIN) --shift;
     return shift;
 }
-inline int listed_group(int k) { return listed_part_shift(k) >= LISTED_PART_SHIFT_MAX ? 1 : 1 << listed_group_shift(k); }
+inline int listed_part_shift(int k, int tiles) {
+    int shift = 0;
+    for (int j = 1; j < k; ++j) {
+        const int more = listed_group_shift(j, shift, tiles);
+        if (more == 0) break;  // (and none from here on)
+        shift += more;
+    }
+    return shift;
+}
 
 // Places of the lanes' live edges among the workgroup's (N per lane, wave by wave); total = their number.  Contains barriers.
 template <int N, int NWAVES = prim::WAVES>

@@ -722,10 +722,13 @@ int pair_budget(picasso_ctx* c, hipStream_t s, const TieBreak& tb, int B, const 
 }
 
 // Sub-round k of the selection.  last: it lists the edges it leaves live for the tail.
-void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bool last, int round) {
+// many: most edges are live still, also beyond the first sub-rounds, so bids are put together in LDS there, too (400 k vertices of one plane,
+// to a quarter: 56 -> 28 ms).
+void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bool last, bool many, int round) {
     const bool listed = sa.bound >= LISTED_MIN_EDGES;
     const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round, k == 0); /* (the first only) */
-    const int shift = listed_part_shift(k), group = listed_group(k);
+    const int tiles = sa.fcur ? sa.list_tiles : (sa.bound - 1) / LISTED_TILE + 1;
+    const int shift = listed_part_shift(k, tiles), group = 1 << listed_group_shift(k, shift, tiles);
     if (sa.fcur) {
         if (k == 0) {
             const int grid = prim::xcd_grid(sa.parts);
@@ -736,9 +739,9 @@ void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bo
             else select_facets_kernel<256, 2, false><<<grid, 256, 0, s>>>(sa);
             return;
         }
-        const int parts = ((sa.list_tiles - 1) >> shift) + 1, groups = prim::xcd_grid((parts + group - 1) / group);
+        const int parts = ((tiles - 1) >> shift) + 1, groups = prim::xcd_grid((parts + group - 1) / group);
         const int grid = groups + (last ? (sa.nv + COUNT_VERTICES - 1) / COUNT_VERTICES : 0);
-        if (k <= 2) {
+        if (k <= 2 || many) {
             if (last) select_listed_kernel<false, true, true, true><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, groups);
             else select_listed_kernel<false, true, false, true><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, groups);
         } else {
@@ -754,9 +757,9 @@ void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bo
         } else if (k == 0) {                                                                                                 \
             select_first_kernel<SHUFFLE, APPEND><<<prim::xcd_grid((sa.bound + LISTED_TILE - 1) / LISTED_TILE), BLOCK, 0, s>>>(sa); \
         } else {                                                                                                             \
-            const int parts = (((sa.bound - 1) / LISTED_TILE) >> shift) + 1;                                                 \
+            const int parts = ((tiles - 1) >> shift) + 1;                                                                     \
             const int grid = prim::xcd_grid((parts + group - 1) / group);                                                    \
-            if (k <= 2) select_listed_kernel<SHUFFLE, false, APPEND, true><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, grid); \
+            if (k <= 2 || many) select_listed_kernel<SHUFFLE, false, APPEND, true><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, grid); \
             else select_listed_kernel<SHUFFLE, false, APPEND, false><<<grid, BLOCK, 0, s>>>(sa, k, shift, group, grid);       \
         }                                                                                                                    \
     } while (0)
@@ -1070,14 +1073,25 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         long long live_est = std::max(H / 2, 1);
         if (round > 0 && ne_prev > 0 && nv_prev > 0)
             live_est = std::max<long long>(1, std::min<long long>(H, (long long)ne_prev * nv_total / nv_prev * 21 / 20));
+        if (by_facets) live_est = live_est * 5 / 4;  // (copies)
+        // Where many costs are equal the edges can be live for long (a flat lattice of 200 x 200 vertices: 299 sub-rounds, most of which end
+        // a few hundred of 119,000 edges): a batch that leaves more than half of its edges live is followed by one of twice
+        // its sub-rounds, and nothing is queued ahead behind that, which would do nothing.  That lattice to a quarter, with batches of four sub-rounds
+        // each: by sorted edges 4.4 ms, by facets 79 with five workgroups to a sub-round (see listed_group_shift); so 3.8.  With line 11's
+        // candidates queued behind each batch 7.6, so 3.0.
+        bool slow = false, queued = false;
+        int wide_before = 0;
         for (;;) {
             // live edges fall by about 2.8x, 2.7x, 3.2x, 4x, 5x, ... per sub-round on meshes with varied costs
             static const int decay_x10[] = {28, 27, 32, 40, 50, 60};
-            int wide = 0;
-            for (long long l = by_facets ? live_est * 5 / 4 : live_est; l > TAIL_MAX; ++wide) l = l * 10 / decay_x10[std::min(wide, 5)];
+            int wide = slow ? 2 * wide_before : 0;
+            if (!slow)
+                for (long long l = live_est; l > TAIL_MAX; ++wide) l = l * 10 / decay_x10[std::min(wide, 5)];
             wide = std::min<int>(wide, (int)std::max<int64_t>(1, c->opt_subround_batch));
             wide = std::max(wide, 1);  // (the last of them lists what it leaves live for the tail)
-            for (int j = 0; j < wide; ++j) launch_subround(c, s, sa, sel_k + j, j == wide - 1, round);
+            wide_before = wide;
+            queued = !slow;
+            for (int j = 0; j < wide; ++j) launch_subround(c, s, sa, sel_k + j, j == wide - 1, slow, round);
             sel_k += wide;
             // the kernel behind the tail tells the host that the tail's results are in the read-back area
             const HostSignal tail_done = next_signal(c);
@@ -1085,13 +1099,13 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             select_tail_kernel<<<1, TAIL_THREADS, 0, s>>>(sa);
             launched += wide + 1;
             const HostSignal nothing{nullptr, 0};
-            if (ahead_ok) {
+            if (ahead_ok && queued) {
                 if (ahead_budget) {
                     rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_bound, 0, true, true, tail_done);
                     if (rc != PICASSO_OK) return rc;
                 }
                 issue_contract(0, 0, ahead_budget, true, ahead_budget ? nothing : tail_done);
-            } else if (joiners_ahead) {
+            } else if (joiners_ahead && queued) {
                 list_joiners(c, s, B, cur, vbits, ne_bound, nv_total, mt, tb, tail_done);
             } else {
                 signal_kernel<<<1, 64, 0, s>>>(tail_done);
@@ -1122,9 +1136,10 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             sel_k = hst->sel_k;
             const int live = hst->live[0];
             if (live == 0) {
-                ahead = ahead_ok;
+                ahead = ahead_ok && queued;
                 break;
             }
+            slow = 2ll * live > live_est;
             live_est = live;
         }
         for (int b = 0; b < B; ++b) h_matched[b] = c->h_pin[HDR_STATE_INTS + b];
@@ -1171,7 +1186,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         bool budget_left = false;
         for (int b = 0; b < B; ++b) budget_left |= (h_matched[b] > 0 && nrem[b] > h_matched[b]);
         if (c->opt_absorb && budget_left) {
-            if (!joiners_ahead) {
+            if (!joiners_ahead || !queued) {
                 const HostSignal counted = next_signal(c);
                 list_joiners(c, s, B, cur, vbits, hst->ne, nv_total, mt, tb, counted);
                 HIP_TRY(c, wait_for_signal(c, s, counted));
