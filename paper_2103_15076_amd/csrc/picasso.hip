@@ -1073,7 +1073,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         long long live_est = std::max(H / 2, 1);
         if (round > 0 && ne_prev > 0 && nv_prev > 0)
             live_est = std::max<long long>(1, std::min<long long>(H, (long long)ne_prev * nv_total / nv_prev * 21 / 20));
-        if (by_facets) live_est = live_est * 5 / 4;  // (copies)
+        // (by facets copies of them as well: a third more on surfaces in order, of one side or two, twice as many where the facets are in none)
+        if (by_facets) live_est = live_est * 3 / 2;
         // Where many costs are equal the edges can be live for long (a flat lattice of 200 x 200 vertices: 299 sub-rounds, most of which end
         // a few hundred of 119,000 edges): a batch that leaves more than half of its edges live is followed by one of twice
         // its sub-rounds, and nothing is queued ahead behind that, which would do nothing.  That lattice to a quarter, with batches of four sub-rounds

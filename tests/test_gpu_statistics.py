@@ -40,3 +40,14 @@ def test_sub_rounds_are_those_by_facets(pk, oracle):  # noqa: F811
         assert st.ne[0] == len(oracle.edges(F))
         launched.append(st.subrounds[0])
     assert launched == [4, 2]
+
+
+def test_a_batch_of_sub_rounds_does_for_two_sided_surfaces(pk):  # noqa: F811
+    """Every edge of which has four facets: five sub-rounds and the tail, which need not hand back."""
+    V, F = lattice(79000, 9)
+    F = np.concatenate([F, F[:, ::-1]])
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    ctx.set_option(pk.PICASSO_OPT_MAX_ROUNDS, 1)
+    st = pk.picasso_stats()
+    ctx.picasso_decimate(dev(V), dev(F), 1, stats=st)
+    assert st.subrounds[0] == 6
