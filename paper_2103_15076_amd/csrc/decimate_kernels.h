@@ -1264,8 +1264,9 @@ constexpr int LISTED_LINES = 256;
 // How many parts sub-round k >= 1 joins, and how many tiles a part is (bits), of `tiles` tiles: a workgroup has a few hundred live edges every time
 // where these get fewer as on surfaces of varied costs.  Where they hardly do (ties: on a flat lattice of 200 x 200 vertices a round takes 299
 // sub-rounds), joining on would leave the whole chip's work to a few workgroups (five there, 230 us a sub-round), so that at
-// least LISTED_GROUPS_MIN workgroups are left.
-constexpr int LISTED_GROUPS_MIN = 512;
+// least LISTED_GROUPS_MIN workgroups are left, one for every compute unit.  (With 512 flat lattices of 115 k and 400 k vertices, to a quarter, take
+// 10.9 and 27.8 ms for 11.4 and 37.0, but those with varied costs 241 us for 235, 2 M 1,028 for 1,021, 16 meshes of 60 k 581 for 577.)
+constexpr int LISTED_GROUPS_MIN = 256;
 inline int listed_group_shift(int k, int part_shift, int tiles) {
     int shift = k <= 3 ? 1 : 2;
     while (shift > 0 && ((tiles - 1) >> (part_shift + shift)) + 1 < LISTED_GROUPS_MIN) --shift;
