@@ -109,18 +109,20 @@ inline int row_parts(const RowMap& m) { return (m.Q + m.qc - 1) / m.qc; }
 // on a wave holds one row, and up to half of its lanes may be idle: two parts where they use a fifth more of them (120 k facets, 132
 // channels: facet2vertex 42 -> 32 us, vertex2facet's backward pass 42 -> 45, pooling the same).  Beyond 64, as few idle lanes as can be.
 // one_wave: all lanes of a row in one wave, Q <= 64 (for sums across a row's lanes).  beyond_cache: the rows do not fit the Infinity
-// Cache; parts of whole 128-byte lines then pay up to 32 packs too (96 channels, 720 k facets: vertex2facet 116 us in one part, 100 in three; 120 k
-// facets 13 and 20).
+// Cache.  Rows of whole 128-byte lines may then go in parts of whole lines up to 32 packs, too; 32, 64 and 128 channels leave no lane idle as they
+// are, so that 96 are dealt to three waves (forward passes, in one part | in three, us: 720 k facets vertex2facet 119 | 106, facet2vertex 136 | 126;
+// 1.28 M 185 | 169, 212 | 205; from the cache, 120 k facets, 13 | 20).  Parts of rows that are not whole lines end within lines there as everywhere (95
+// channels, 1.28 M facets: 334 | 526, 310 | 465).
 inline RowMap row_map(int C, bool one_wave = false, bool beyond_cache = false) {
     RowMap best{}, m;
     double best_use = -1.0;
     m.Q = (C + 3) / 4;
     const int least = (m.Q + 63) / 64;
     const double a_part = m.Q > 64 ? 0.04 : m.Q > 32 ? 0.2 : 0.1;  // share of the lanes that a further part has to bring to work
-    const int most = one_wave || (m.Q <= 32 && !beyond_cache) ? least : least + 3;
+    const int most = one_wave || (m.Q <= 32 && !(beyond_cache && C % 32 == 0)) ? least : least + 3;
     for (int parts = least; parts <= most && parts <= m.Q; ++parts) {
         m.qc = (m.Q + parts - 1) / parts;
-        if (m.Q <= 32 && parts > 1 && (m.Q % 8 != 0 || m.qc % 8 != 0)) continue;
+        if (m.Q <= 32 && parts > 1 && m.qc % 8 != 0) continue;
         m.rw = 64 / m.qc;
         m.inv = (65536 + m.qc - 1) / m.qc;
         const double use = (double)m.rw * m.Q / (64.0 * row_parts(m)) - a_part * (parts - least);  // lanes at work
