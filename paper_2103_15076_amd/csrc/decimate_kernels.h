@@ -1426,7 +1426,8 @@ __global__ __launch_bounds__(THREADS, FIRST ? 1 : 6) void facet_costs_kernel(int
 #pragma unroll
         for (int j = 0; j < PER; ++j) q[j] = load_corners(fcur, (size_t)(j * THREADS + t < n ? f0 + j * THREADS + t : 0));
     } else {
-        if (PER == 1) q[0] = load_corners(fcur, (size_t)(t < n ? f0 + t : 0));  // (not yet known to be one)
+        // (not yet known to be one; within the tile, as the others' workgroups rewrite theirs)
+        if (PER == 1 && t < n) q[0] = load_corners(fcur, (size_t)(f0 + t));
         if (g < n_orig) label = cid[g];
         const int nv = st->nv[cur];
         if (fcount && n > 0) n = fcount[tile];
