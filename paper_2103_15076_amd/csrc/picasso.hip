@@ -507,6 +507,9 @@ void launch_unique_cost(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>&
 // levels from 1.9 M 1169 -> 1155; joining two such tiles from the third round on, when half of their places are empty, took longer (703 -> 737, 4742 -> 5077).
 constexpr int FACET_TILE_SMALL = 256, FACET_TILE_LARGE = 512;
 constexpr int FACET_TILE_SMALL_MAX = 1 << 20;
+// Lanes of their workgroups: of the rounds' first kernel behind the first round, where tiles are large, half as many.
+constexpr int FACET_LANES = 256, FACET_LANES_LARGE = 128;
+static_assert((FACET_TILE_SMALL & (FACET_TILE_SMALL - 1)) == 0 && (FACET_TILE_LARGE & (FACET_TILE_LARGE - 1)) == 0, "a facet's tile is found by a shift");
 inline int facet_tile(int F) { return F <= FACET_TILE_SMALL_MAX ? FACET_TILE_SMALL : FACET_TILE_LARGE; }
 inline int facet_tiles(int F) { return std::max((F + facet_tile(F) - 1) / facet_tile(F), 1); }
 // Workgroups of facets and vertices that a round of at most nv vertices has.
@@ -515,25 +518,28 @@ inline int facet_parts(int F, int nv) { return std::max(facet_tiles(F), (nv + 10
 // facets leave it where the labels are.
 int* round_map(picasso_ctx* c, bool by_facets, int round_) { return by_facets && round_ == 0 ? c->cid : c->vmap; }
 void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, int N, int F) {
-    const int grid = prim::xcd_grid(round_ == 0 && facet_tile(F) > 512 ? std::max((F + 511) / 512, 1) : facet_parts(F, N)), par = round_ & 1;
-#define PICASSO_FACET_COSTS(PLACE, THREADS, PER, FIRST)                                                                              \
-    facet_costs_kernel<PLACE, THREADS, PER, FIRST><<<grid, THREADS, 0, s>>>(                                                            \
-        c->fcur, F, c->st, cur_, c->vrec[cur_], c->vmin[0], c->vmin[1], c->ecost, round_tab(c, B, round_, cur_), round_map(c, true, round_ - 1), c->done, \
-        c->cid, round_ > 1 ? N : 0, c->opt_rcond_min, round_ > 1 ? c->fcount() : nullptr, c->fcount(), c->nf_slots[par], c->nf_slots[par ^ 1])
-#define PICASSO_FACET_COSTS_PER(PLACE, THREADS, PER)                         \
-    do {                                                                \
-        if (round_ == 0) PICASSO_FACET_COSTS(PLACE, 256, PER == 1 ? 1 : 2, true);      \
-        else PICASSO_FACET_COSTS(PLACE, THREADS, PER, false);              \
+    const int grid = prim::xcd_grid(facet_parts(F, N)), par = round_ & 1;
+#define PICASSO_FACET_COSTS(PLACE, TILE, THREADS, FIRST)                                                                              \
+    do {                                                                                                                                \
+        static_assert((TILE) % (THREADS) == 0, "whole tiles");                                                                          \
+        facet_costs_kernel<PLACE, THREADS, (TILE) / (THREADS), FIRST><<<grid, THREADS, 0, s>>>(                                         \
+            c->fcur, F, c->st, cur_, c->vrec[cur_], c->vmin[0], c->vmin[1], c->ecost, round_tab(c, B, round_, cur_), round_map(c, true, round_ - 1), c->done, \
+            c->cid, round_ > 1 ? N : 0, c->opt_rcond_min, round_ > 1 ? c->fcount() : nullptr, c->fcount(), c->nf_slots[par], c->nf_slots[par ^ 1]); \
     } while (0)
-#define PICASSO_FACET_COSTS_PLACE(PLACE)                                        \
-    do {                                                                        \
-        if (facet_tile(F) == FACET_TILE_SMALL) PICASSO_FACET_COSTS_PER(PLACE, 256, 1);       \
-        else PICASSO_FACET_COSTS_PER(PLACE, 128, 4);                                \
+#define PICASSO_FACET_COSTS_TILE(PLACE, TILE, THREADS)                                \
+    do {                                                                              \
+        if (round_ == 0) PICASSO_FACET_COSTS(PLACE, TILE, FACET_LANES, true);         \
+        else PICASSO_FACET_COSTS(PLACE, TILE, THREADS, false);                        \
+    } while (0)
+#define PICASSO_FACET_COSTS_PLACE(PLACE)                                                                                             \
+    do {                                                                                                                             \
+        if (facet_tile(F) == FACET_TILE_SMALL) PICASSO_FACET_COSTS_TILE(PLACE, FACET_TILE_SMALL, FACET_LANES);                       \
+        else PICASSO_FACET_COSTS_TILE(PLACE, FACET_TILE_LARGE, FACET_LANES_LARGE);                                                   \
     } while (0)
     if (c->opt_placement == PLACE_INVERSE) PICASSO_FACET_COSTS_PLACE(PLACE_INVERSE);
     else PICASSO_FACET_COSTS_PLACE(PLACE_MEAN);
 #undef PICASSO_FACET_COSTS_PLACE
-#undef PICASSO_FACET_COSTS_PER
+#undef PICASSO_FACET_COSTS_TILE
 #undef PICASSO_FACET_COSTS
 }
 
@@ -733,10 +739,11 @@ void launch_subround(picasso_ctx* c, hipStream_t s, const SelArgs& sa, int k, bo
         if (k == 0) {
             const int grid = prim::xcd_grid(sa.parts);
             const bool small = facet_tile(sa.n_facets) == FACET_TILE_SMALL;
-            if (small && last) select_facets_kernel<256, 1, true><<<grid, 256, 0, s>>>(sa);
-            else if (small) select_facets_kernel<256, 1, false><<<grid, 256, 0, s>>>(sa);
-            else if (last) select_facets_kernel<256, 2, true><<<grid, 256, 0, s>>>(sa);
-            else select_facets_kernel<256, 2, false><<<grid, 256, 0, s>>>(sa);
+            constexpr int PER_SMALL = FACET_TILE_SMALL / FACET_LANES, PER_LARGE = FACET_TILE_LARGE / FACET_LANES;
+            if (small && last) select_facets_kernel<FACET_LANES, PER_SMALL, true><<<grid, FACET_LANES, 0, s>>>(sa);
+            else if (small) select_facets_kernel<FACET_LANES, PER_SMALL, false><<<grid, FACET_LANES, 0, s>>>(sa);
+            else if (last) select_facets_kernel<FACET_LANES, PER_LARGE, true><<<grid, FACET_LANES, 0, s>>>(sa);
+            else select_facets_kernel<FACET_LANES, PER_LARGE, false><<<grid, FACET_LANES, 0, s>>>(sa);
             return;
         }
         const int parts = ((tiles - 1) >> shift) + 1, groups = prim::xcd_grid((parts + group - 1) / group);
