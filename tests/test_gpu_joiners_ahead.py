@@ -26,20 +26,24 @@ def test_candidates_of_one_mesh(pk, oracle, n_facets, keep, seed, batch):  # noq
 
 
 @pytest.mark.parametrize("keeps", [(0.3, 0.4, 0.5), (0.2, 0.9, 0.4), (0.1, 1.0, 0.6)])
-def test_candidates_of_several_meshes(pk, keeps):  # noqa: F811
+def test_candidates_of_several_meshes(pk, oracle, keeps):  # noqa: F811
     parts = [lattice(n, k) for k, n in enumerate((5000, 900, 20000))]
     nv, nf = [len(v) for v, _ in parts], [len(f) for _, f in parts]
     base = np.concatenate([[0], np.cumsum(nv)])
     V = np.concatenate([v for v, _ in parts])
     F = np.concatenate([f + np.int32(base[k]) for k, (_, f) in enumerate(parts)])
     target = [max(1, int(n * k)) for n, k in zip(nv, keeps)]
+    refs = [oracle.decimate(v, f, t, absorb=True) for (v, f), t in zip(parts, target)]
+    nv_ref, nf_ref = [len(r["verts"]) for r in refs], [len(r["facets"]) for r in refs]
+    first = np.concatenate([[0], np.cumsum(nv_ref)])  # (of a mesh's output vertices)
+    ref = dict(status=max(r["status"] for r in refs), verts=np.concatenate([r["verts"] for r in refs]),
+               facets=np.concatenate([r["facets"] + np.int32(first[k]) for k, r in enumerate(refs)]),
+               cluster_id=np.concatenate([r["cluster_id"] + np.int32(first[k]) for k, r in enumerate(refs)]))
     ctx = pk.Context(len(V), len(F), 3, device=0)
     ctx.set_option(pk.PICASSO_OPT_ABSORB, 1)
-    outs = []
     for ahead, batch in ((0, 16), (1, 16), (1, 1)):
         ctx.set_option(pk.PICASSO_OPT_LAUNCH_AHEAD, ahead)
         ctx.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, batch)
-        st, vo, fo, cid, nvo, nfo = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
-        outs.append((st, vo.cpu().numpy(), fo.cpu().numpy(), cid.cpu().numpy(), list(nvo), list(nfo)))
-        for a, b in zip(outs[0], outs[-1]):
-            np.testing.assert_array_equal(a, b)
+        got = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
+        same(got, ref)
+        assert list(got[4]) == nv_ref and list(got[5]) == nf_ref
