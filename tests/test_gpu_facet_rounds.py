@@ -1,5 +1,5 @@
 """Rounds by facets (no list of the distinct edges) against the oracle: tiles' edges, copies of an edge in one tile and in several,
-meshes that end within a tile, more meshes than the workgroups keep in LDS, and selections that hand back to the host."""
+meshes that end within a tile, more meshes than the workgroups keep in LDS, both placements, and selections that hand back to the host."""
 import numpy as np
 import pytest
 
@@ -62,6 +62,16 @@ def test_large_tiles(pk, oracle, n_facets, turned, repeated, batch):
     ctx.set_option(pk.PICASSO_OPT_SUBROUND_BATCH, batch)
     target = len(V) // 4
     same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target))
+
+
+@pytest.mark.parametrize("keep", [0.55, 0.2])
+def test_large_tiles_with_inverse_placement(pk, oracle, keep):
+    """One round and several; costs have to be the same to the bit from either end of an edge here, too."""
+    V, F = lattice((1 << 20) + 1025, 5, 0.3, 0.05)
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    ctx.set_placement(pk.PICASSO_PLACE_INVERSE, 1e-3)
+    target = int(len(V) * keep)
+    same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target, placement=pk.PICASSO_PLACE_INVERSE, rcond_min=1e-3))
 
 
 @pytest.mark.parametrize("sizes", [[300, 1, 700, 90, 2000] * 3, [40] * 70, [130, 20, 260] * 400])
