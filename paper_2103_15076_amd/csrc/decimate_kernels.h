@@ -566,6 +566,7 @@ struct QuadricRows {
     // GROUP_LANE keys; a wave sorts more).  (With the groups sorted in LDS and the vertices found again among the keys 115 k vertices took 12.3 us, now 9.6, 1.2 M
     // 49 and 42.5, 10.2 M 450 and 421.)
     static constexpr bool GROUPS_SORTED = false;
+    static constexpr int GROUP_SHORT = 8, GROUP_LANE = 16;  // (sizes of a lane's sort)
     __device__ bool rows_are_groups(bool, const prim::Bucket& b, int R) const { return (1 << (b.low_bits - fbits)) == R && b.low_bits > fbits; }
     template <int G, typename LK>
     __device__ __forceinline__ void add_group(float (&acc)[10], const prim::Bucket& b, const LK* key, int g) const {
@@ -592,12 +593,12 @@ struct QuadricRows {
         for (int gi = t; gi < n; gi += THREADS) {
             const int gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
             float acc[10] = {};
-            if (g > 16) {
+            if (g > GROUP_LANE) {
                 lds.gcnt[atomicAdd(&lds.nlong, 1u)] = (u32)gi;
                 continue;
             }
-            if (g > 8) add_group<16>(acc, b, lds.skey + gs, g);
-            else add_group<8>(acc, b, lds.skey + gs, g);
+            if (g > GROUP_SHORT) add_group<GROUP_LANE>(acc, b, lds.skey + gs, g);
+            else add_group<GROUP_SHORT>(acc, b, lds.skey + gs, g);
             write_vertex_record(vrec, verts, lo + gi, acc);
         }
         __syncthreads();
@@ -3191,7 +3192,7 @@ __global__ __launch_bounds__(BLOCK) void facets_out_kernel(FacetList L, int F, c
 // ---------------------------------------------------------------------------
 // Results
 // ---------------------------------------------------------------------------
-// The call's last kernel, one workgroup: the header's first n ints ([State][matched][foff_out])
+// The call's last kernel, one workgroup: the header's first n ints ([State][matched][mesh_facets])
 // copied to the host's read-back area, then the host is told.
 // zero[i * zero_stride] and the word behind it, i < n_zero: words that their users find zero, cleared on the way.
 __global__ __launch_bounds__(BLOCK) void publish_header_kernel(int* __restrict__ hdr, int n,
