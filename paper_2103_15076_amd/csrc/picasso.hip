@@ -1795,7 +1795,7 @@ int picasso_v2f_forward(picasso_ctx* c, void* stream, const float* d_x, int32_t 
     if (!c || !d_x || N < 1 || C < 1 || !d_facets || F < 1 || !d_w || !d_y) return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const pool::RowMap m = pool::row_map(C, false, pool::beyond_cache(C, (long long)N + F));
+    const pool::RowMap m = pool::row_map(C, false, C > 128 || pool::beyond_cache(C, (long long)N + F));  // (see there)
     const int per_wave = conv::facets_per_wave(m, F), per_block = per_wave * (pool::BLOCK / 64);
     const dim3 grid(prim::xcd_grid((F + per_block - 1) / per_block), pool::row_parts(m));
 #define PICASSO_CALL(K) \
@@ -1910,7 +1910,7 @@ int picasso_f2v_forward(picasso_ctx* c, void* stream, const float* d_y, int32_t 
         HIP_TRY(c, hipGetLastError());
         return PICASSO_OK;
     }
-    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N, pool::beyond_cache(C, (long long)N + F));
+    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N, true);
     const int per_block = (T <= 16 ? m.per_wave : m.row.rw) * (pool::BLOCK / 64);
     const dim3 grid(prim::xcd_grid((N + per_block - 1) / per_block), pool::row_parts(m.row));
 #define PICASSO_F2V(NP, K) \
@@ -2088,7 +2088,7 @@ int picasso_unpool_forward(picasso_ctx* c, void* stream, const float* d_y, int32
     if (!c || !d_y || !d_cluster_id || !d_x || n_in < 1 || C < 1) return PICASSO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    const pool::RowMap m = pool::row_map(C);
+    const pool::RowMap m = pool::row_map(C, false, true);
 #define PICASSO_CALL(K) \
     pool::unpool_forward_kernel<K><<<pool::row_grid(m, n_in), pool::BLOCK, 0, s>>>(d_y, n_in, C, d_cluster_id, d_x, m)
     PICASSO_ROW_KINDS(C, C, n_in, PICASSO_CALL);

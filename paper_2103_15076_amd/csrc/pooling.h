@@ -108,21 +108,26 @@ inline int row_parts(const RowMap& m) { return (m.Q + m.qc - 1) / m.qc; }
 // max pooling of 360 k vertices, 100 channels 88 -> 53; the passes over the vertices' facets 97 -> 54, 145 -> 93, 268 -> 178).  From 33 packs
 // on a wave holds one row, and up to half of its lanes may be idle: two parts where they use a fifth more of them (120 k facets, 132
 // channels: facet2vertex 42 -> 32 us, vertex2facet's backward pass 42 -> 45, pooling the same).  Beyond 64, as few idle lanes as can be.
-// one_wave: all lanes of a row in one wave, Q <= 64 (for sums across a row's lanes).  beyond_cache: the rows do not fit the Infinity
-// Cache.  Rows of whole 128-byte lines may then go in parts of whole lines up to 32 packs, too; 32, 64 and 128 channels leave no lane idle as they
-// are, so that 96 are dealt to three waves (forward passes, in one part | in three, us: 720 k facets vertex2facet 119 | 106, facet2vertex 136 | 126;
-// 1.28 M 185 | 169, 212 | 205; from the cache, 120 k facets, 13 | 20).  Parts of rows that are not whole lines end within lines there as everywhere (95
-// channels, 1.28 M facets: 334 | 526, 310 | 465).
-inline RowMap row_map(int C, bool one_wave = false, bool beyond_cache = false) {
+// one_wave: all lanes of a row in one wave, Q <= 64 (for sums across a row's lanes).
+// lines: rows of whole 128-byte lines may go in parts of whole lines, which leave nothing between two waves: three parts of 96 or of 192
+// channels (32, 64, 128, 160 and 256 go as they would anyhow).  In one part | in three, us: 192 channels, 115 k vertices, vertex2facet 64 | 54,
+// facet2vertex (6 components) 101 | 64, average pooling 21.1 | 20.0, max pooling's backward pass 27.9 | 24.7; 400 k vertices 268 | 218, 305 | 266, 91 | 88, 129 | 107;
+// 96 channels, 115 k vertices, facet2vertex 44 | 39, pooling 12.8 | 11.6.  Not in the passes that sum filter gradients, where a part more is a set of
+// partial sums more (192 channels, 60 k vertices: 46 | 55 and 49 | 59), nor in vertex2facet of 96 channels as long as the rows fit the Infinity Cache
+// (beyond_cache): 120 k facets 14 | 20, but 720 k 119 | 106, 1.28 M 185 | 169.  Parts that end within lines stay slow beyond it as well (95 channels,
+// 1.28 M facets: 334 | 526).
+inline RowMap row_map(int C, bool one_wave = false, bool lines = false) {
     RowMap best{}, m;
     double best_use = -1.0;
     m.Q = (C + 3) / 4;
     const int least = (m.Q + 63) / 64;
-    const double a_part = m.Q > 64 ? 0.04 : m.Q > 32 ? 0.2 : 0.1;  // share of the lanes that a further part has to bring to work
-    const int most = one_wave || (m.Q <= 32 && !(beyond_cache && C % 32 == 0)) ? least : least + 3;
+    lines = lines && C % 32 == 0;
+    const int most = one_wave || (m.Q <= 32 && !lines) ? least : least + 3;
     for (int parts = least; parts <= most && parts <= m.Q; ++parts) {
         m.qc = (m.Q + parts - 1) / parts;
-        if (m.Q <= 32 && parts > 1 && m.qc % 8 != 0) continue;
+        const bool whole = lines && m.qc % 8 == 0;
+        if (m.Q <= 32 && parts > 1 && !whole) continue;
+        const double a_part = m.Q > 64 ? 0.04 : m.Q > 32 && !whole ? 0.2 : 0.1;  // share of the lanes that a further part has to bring to work
         m.rw = 64 / m.qc;
         m.inv = (65536 + m.qc - 1) / m.qc;
         const double use = (double)m.rw * m.Q / (64.0 * row_parts(m)) - a_part * (parts - least);  // lanes at work
@@ -334,7 +339,7 @@ inline int grid_for(long long n) { return (int)((n + BLOCK - 1) / BLOCK > 0 ? (n
 template <int KIND>
 inline void launch_pool_forward(hipStream_t s, int mode, const float* x, int C, const int* off, const int* mem,
                                 int n_out, const float* w, float* y, int* argmax) {
-    const RowMap m = row_map(C);
+    const RowMap m = row_map(C, false, true);
     const dim3 g = row_grid(m, n_out);
     switch (mode) {
         case AVG: pool_forward_kernel<AVG, KIND><<<g, BLOCK, 0, s>>>(x, C, off, mem, n_out, w, y, argmax, m); break;
@@ -347,7 +352,7 @@ inline void launch_pool_forward(hipStream_t s, int mode, const float* x, int C, 
 template <int KIND>
 inline void launch_pool_backward(hipStream_t s, int mode, const float* gy, int n_in, int C, const int* cid,
                                  const int* off, const int* mem, const float* w, const int* argmax, float* gx) {
-    const RowMap m = row_map(C);
+    const RowMap m = row_map(C, false, true);
     const dim3 g = row_grid(m, n_in);
     switch (mode) {
         case AVG: pool_backward_kernel<AVG, KIND><<<g, BLOCK, 0, s>>>(gy, n_in, C, cid, off, mem, w, argmax, gx, m); break;

@@ -1,6 +1,6 @@
 """Channel counts on both sides of the lines at which rows are dealt to lanes and waves in another way (24 to 128 channels: a wave holds
-several rows, whose lanes need not fill it; 132 to 256: one row, or a part of one; 260: several waves a row; 96 where the rows do not fit the
-cache: three waves): pooling and the convolutions against the fp64 oracle, whose bounds are those of test_gpu_conv and test_gpu_pooling."""
+several rows, whose lanes need not fill it; 132 to 256: one row, or a part of one; 260: several waves a row; 96 and 192, rows of whole
+cache lines: three waves, 96 in vertex2facet only where the rows do not fit the cache): pooling and the convolutions against the fp64 oracle, whose bounds are those of test_gpu_conv and test_gpu_pooling."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +12,7 @@ from test_gpu_conv import _close, _gw_terms, ctx, dev, pk  # noqa: F401  (fixtur
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("C", [24, 52, 99, 128, 132, 160, 164, 256, 260])
+@pytest.mark.parametrize("C", [24, 52, 96, 99, 128, 132, 160, 164, 192, 256, 260])
 def test_rows_dealt_to_lanes_and_waves(pk, ctx, oracle, C):  # noqa: F811
     V, F = meshgen.noisy_grid(37, 29, seed=C, noise=0.02)
     N, nF, T = V.shape[0], F.shape[0], 5
