@@ -2952,6 +2952,14 @@ __device__ __forceinline__ u32 facet_home(int x, u32 hx, float slots_per_vertex)
     const float at = (float)x * slots_per_vertex;  // (below 2^32: x is below the vertex count)
     return (u32)at + (hx & ((1u << FACET_HOME_WINDOW_BITS) - 1u));
 }
+// ... and where it goes on when every FACET_HOME_PROBES steps along the line have found no place, j = 1, 2, ...: a vertex may have very many facets,
+// and where vertices are numbered in no order the smallest of a facet's three is a low one, so that much of the table's low end is full.  A search must
+// not walk through that: calls that keep 99 % of such vertices took 45 ms of 130 k and 270 ms of 500 k with one jump and steps along the line
+// from there on, now 0.40 and 1.06.  The strides are odd and the sizes powers of two: every slot is a start once, so that a search ends.
+__device__ __forceinline__ u32 facet_next_home(u32 hx, u32 j) {
+    const u32 stride = ((hx << 16 | hx >> 16) * 0x9E3779B1u) | 1u;
+    return hx + (j - 1u) * stride;
+}
 
 // A slot of the table: the facet's index in its low `fbits` bits (all ones are no facet's index), bits of its triple's hash above: facets
 // whose bits differ have different triples, so that a search passes the slots of others without a look at their corners (a facet and three
@@ -3034,9 +3042,8 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
                     break;
                 }
             }
-            // a few steps along the line, then (a crowded stretch: a vertex with very many facets) on from
-            // a place that the whole triple decides
-            h = (probe == FACET_HOME_PROBES ? hx : h + 1u) & hmask;
+            // a few steps along the line, then (a crowded stretch) on from places that the whole triple decides
+            h = (probe % FACET_HOME_PROBES != 0 ? h + 1u : facet_next_home(hx, (u32)probe / FACET_HOME_PROBES)) & hmask;
         }
         slot = (int)h;
         return true;
