@@ -1376,7 +1376,11 @@ int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts,
 // (conv::rows_to_partial, conv::reduce_rows_stage2_kernel).  Stage 1's workgroups leave their partial sums in the
 // context's sort buffers (sort_buf).  As many workgroups as the chip holds at once (256 compute units; a workgroup takes several
 // turns of rows_per_turn rows, keeping their sums in registers), fewer where there are not so many turns or the
-// buffer does not hold their partials.
+// buffer does not hold their partials.  Where rows are dealt to several workgroups in parts that leave a wave several rows (narrow ones, that end
+// within cache lines), all parts of a row are counted: those at work on the same rows then find the lines that they share in the caches, and so
+// they do not with as many workgroups for each part, of which the chip takes up one part after the other.  In all | for each, us: 60 k vertices, 260
+// channels, vertex2facet's backward pass 56 | 73, facet2vertex's (6 components) 98 | 123, 300: 83 | 96, 106 | 127, 132: 38 | 43, 37 | 50; 115 k, 260: 152 | 177,
+// 188 | 210, 132: 67 | 83, 97 | 111.  Parts of a row to a wave share a line in sixteen, and stay as they were (115 k, 500 channels: 333 | 293).
 struct FilterSplit {
     int groups, chunk;
     float* partial;
@@ -1409,7 +1413,8 @@ bool narrow_rows(int C, int width, long long max_rows) {
         }                                                             \
     } while (0)
 
-int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_turn, int blocks_per_cu, bool wanted,
+// m: how rows are dealt to workgroups (null: to one)
+int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, const pool::RowMap* m, int rows_per_turn, int blocks_per_cu, bool wanted,
                       FilterSplit* out) {
     // (With the first of the sorts' buffers alone 22 k facets of 200 channels and 6 components left 110
     // workgroups to facet2vertex's backward pass, 56 us; now 440, 23.)
@@ -1418,7 +1423,9 @@ int split_filter_rows(picasso_ctx* c, int n_rows, int rows, int C, int rows_per_
     const size_t per_group = (size_t)rows * C;
     if (wanted && per_group > h * sizeof(u64) / sizeof(float)) return PICASSO_ERR_WORKSPACE;
     const long long turns = ((long long)n_rows + rows_per_turn - 1) / rows_per_turn;
-    long long most = 256ll * blocks_per_cu;
+    const int parts = m && m->rw > 1 ? pool::row_parts(*m) : 1;
+    // (five to a compute unit are as many as gain there: 60 k vertices, 260 channels, one component 88 us, with six 112)
+    long long most = parts > 1 ? std::max(256 * std::min(blocks_per_cu, 5) / parts, 1) : 256 * blocks_per_cu;
     if (wanted) most = std::min<long long>(most, (long long)(cap / per_group));
     const long long per_block = (turns + most - 1) / most;  // turns of a workgroup
     long long groups = (turns + per_block - 1) / per_block;
@@ -1816,7 +1823,7 @@ int picasso_v2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
     HIP_TRY(c, hipSetDevice(c->device));
     FilterSplit sp;
     if (narrow_rows(C, C, std::max(N, F))) {
-        const int rc = split_filter_rows(c, N, 3, C, pool::BLOCK, 5, d_gw != nullptr, &sp);
+        const int rc = split_filter_rows(c, N, 3, C, nullptr, pool::BLOCK, 5, d_gw != nullptr, &sp);
         if (rc != PICASSO_OK) return rc;
 #define PICASSO_CALL(CH) \
     conv::v2f_backward_narrow_kernel<CH><<<sp.groups, pool::BLOCK, 0, s>>>(d_gy, d_x, d_level, d_w, d_offsets, d_corners, N, 3 * F, sp.chunk, d_gx, sp.partial)
@@ -1827,7 +1834,7 @@ int picasso_v2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
         return PICASSO_OK;
     }
     const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
-    const int rc = split_filter_rows(c, N, 3, C, m.per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
+    const int rc = split_filter_rows(c, N, 3, C, &m.row, m.per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
     if (rc != PICASSO_OK) return rc;
     const dim3 grid(sp.groups, pool::row_parts(m.row));
 #define PICASSO_CALL(K)                                                                                                     \
@@ -1866,7 +1873,7 @@ int picasso_f2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
     const pool::RowMap m = pool::row_map(C);
     FilterSplit sp;
     const int per_wave = (int)std::max<long long>(1, std::min<long long>(conv::WALK_WAVE_ROWS / 2, F / 4096));
-    const int rc = split_filter_rows(c, F, 3, C, per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
+    const int rc = split_filter_rows(c, F, 3, C, &m, per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
     if (rc != PICASSO_OK) return rc;
     const dim3 grid(sp.groups, pool::row_parts(m));
 #define PICASSO_CALL(K)                                                                                                     \
@@ -1939,7 +1946,7 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
     const int np = (T + 3) / 4;
     if (np <= 4 && 4 * np * C <= conv::NARROW_VALUES && narrow_rows(C, std::max(C, T), std::max(N, F))) {
         FilterSplit sp;
-        const int rc = split_filter_rows(c, F, T, C, pool::BLOCK, 5, d_gw != nullptr, &sp);
+        const int rc = split_filter_rows(c, F, T, C, nullptr, pool::BLOCK, 5, d_gw != nullptr, &sp);
         if (rc != PICASSO_OK) return rc;
 #define PICASSO_F2V_BACK(CH, NP)                                                                                        \
     do {                                                                                                                \
@@ -1969,7 +1976,7 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
             if (!gy && !d_gw && !gpi_fused) break;
             const int rows = std::min(16, T - t0);
             FilterSplit sp;
-            const int rc = split_filter_rows(c, F, rows, C, per_wave * (pool::BLOCK / 64), rows <= 4 ? 6 : (rows <= 12 ? 4 : 3), d_gw != nullptr, &sp);
+            const int rc = split_filter_rows(c, F, rows, C, &m, per_wave * (pool::BLOCK / 64), rows <= 4 ? 6 : (rows <= 12 ? 4 : 3), d_gw != nullptr, &sp);
             if (rc != PICASSO_OK) return rc;
             const dim3 grid(sp.groups, pool::row_parts(m));
 #define PICASSO_F2V_BACK_GPI(NP, K, GPI)                                                                              \
