@@ -908,7 +908,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // attributable, and in a call whose kernels are bracketed by events: a bracketed kernel then has the chip to itself,
     // and its duration is its own.)
     // The rounds go by facets where nothing needs the edges' numbers (see facet_costs_kernel; a call that gives statistics and
-    // brackets its kernels brackets those of the sorts).
+    // brackets its kernels brackets those of the sorts).  By sorted edges | by facets, us: rooms of 115 k vertices to 25 % 279 | 237, to 70 % (one round)
+    // 163 | 157, a lattice of 400 k 455 | 359, 260 | 231.  Facets in no order, whose bids find no place in the workgroups' tables, gain where rounds
+    // follow the first, and one round of them alone only beyond a million vertices: 115 k to 25 % 434 | 352, to 70 % 247 | 254, an icosphere of 164 k 453 | 420,
+    // 233 | 263, 1.2 M 2,550 | 2,091, 1,803 | 1,639.  (The first round could be sorted where the host knew the order; a look at the word in front
+    // of a bid's atomic takes longer: 263 -> 287.)
     const bool by_facets = c->opt_shuffle_seed == 0 && !c->opt_absorb && !(stats && c->kt_this_call);
     const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
                           edge_sort(c, N, F, F, 3ll * F).half == incidence_sort(c, N, F).half;
