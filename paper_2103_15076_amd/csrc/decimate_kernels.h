@@ -2799,7 +2799,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                                                          const int* __restrict__ mate, int* __restrict__ vmap, State* st,
                                                          int cur, int chunks, const int* __restrict__ tilesum, int prefixed,
                                                          int B, const int* __restrict__ voff_cur, int* __restrict__ voff_nxt,
-                                                         const int* __restrict__ active, int* __restrict__ done,
+                                                         const int* __restrict__ matched, int* __restrict__ done,
                                                          int* __restrict__ htab, int n_clear, u64* __restrict__ vmin0,
                                                          float rcond_min, const int* __restrict__ arep,
                                                          const int* __restrict__ aoff, const int* __restrict__ alist,
@@ -2812,7 +2812,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
     for (int b = g; b < B; b += stride)
-        if (active[b]) done[b] = 1;
+        if (matched[b] > 0) done[b] = 1;  // (a mesh without a pair is as it was, whatever the others do)
     const int t = threadIdx.x, w64 = prim::wave_id(), lane = prim::lane_id();
     const int tile = blockIdx.x;
     const long long base = (long long)tile * BLOCK * chunks;
@@ -3026,7 +3026,7 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
     auto enter = [&](int f, Corners q, int& slot) -> bool {
         if (q.a < 0) return false;
         slot = FSLOT_KEEP;
-        if (!done[mesh_of(voff, B, q.a)]) return true;  // the mesh took part in no round: facets kept as they are
+        if (!done[mesh_of(voff, B, q.a)]) return true;  // the mesh contracted in no round: facets kept as they are
         if (q.a == q.b || q.b == q.c || q.a == q.c) return false;
         sort3(q.a, q.b, q.c);
         const u32 hx = hash3(q.a, q.b, q.c), mine = facet_slot_word(hx, f, fbits);

@@ -99,7 +99,7 @@ struct picasso_ctx {
     int* active[2] = {nullptr, nullptr};  // by the round's parity
     int* nf_slots[2] = {nullptr, nullptr};  // facets that have not collapsed, by the round's parity (see facet_costs_kernel)
     int* stuck = nullptr;
-    int* done = nullptr;   // mesh has taken part in a round that contracted
+    int* done = nullptr;   // mesh has contracted pairs in some round
     int* nrem = nullptr;
     int* matched = nullptr;
     SelectSlot* select_slots = nullptr;  // the budget step's counts (long runs, see budget_step)
@@ -996,7 +996,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 #define PICASSO_CONTRACT(PLACE, ABSORB, COUNTS, RCOND)                                                               \
     contract_kernel<PLACE, ABSORB, COUNTS><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, round_map(c, by_facets, round), c->st, cur,  \
                                                            chunks, c->tilesum, prefixed, B, c->voff[cur],             \
-                                                           c->voff[nxt], c->active[round & 1], c->done, c->htab, (int)clear, \
+                                                           c->voff[nxt], c->matched, c->done, c->htab, (int)clear, \
                                                            by_facets ? c->vmin[0] : nullptr, RCOND, c->arep, c->aoff, c->joiners(), guard, tell)
             if (c->opt_placement == PLACE_INVERSE) {
                 if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, false, c->opt_rcond_min);
