@@ -1,5 +1,5 @@
 """The set in which a call finds repeated facets, at its fullest (just under a facet for every two slots) and with vertices numbered in no order, whose
-facets crowd its low end: against the oracle, and in a time that says that no search walks through what is full."""
+facets crowd its low end: against the oracle, and in a time that says that no search walks through what is full, or comes back to it."""
 import time
 
 import numpy as np
@@ -33,3 +33,22 @@ def test_crowded_low_end(pk, oracle, n_facets, repeated):  # noqa: F811
         ctx.picasso_decimate(v, f, target)
         times.append(time.perf_counter() - t0)
     assert min(times) < 4e-3, times  # (2^18 facets: 45 ms with one jump and steps along the line from there on, 0.4 now)
+
+
+def test_crowded_vertices(pk, oracle):  # noqa: F811
+    """20 k random facets on 1 k vertices, more to a vertex than there are places around it: keeping nearly all of them takes hardly longer than
+    keeping 60 % (1.5 times as long when searches went on by equal strides)."""
+    rng = np.random.default_rng(2)
+    V, F = rng.standard_normal((1000, 3)).astype(np.float32), rng.integers(0, 1000, (20000, 3)).astype(np.int32)
+    v, f = dev(V), dev(F)
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    took = []
+    for target in (950, 600):
+        same(ctx.picasso_decimate(v, f, target), oracle.decimate(V, F, target))
+        times = []
+        for _ in range(30):
+            t0 = time.perf_counter()
+            ctx.picasso_decimate(v, f, target)
+            times.append(time.perf_counter() - t0)
+        took.append(sorted(times)[len(times) // 2])
+    assert took[0] < 1.25 * took[1], took
