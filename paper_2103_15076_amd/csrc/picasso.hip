@@ -348,6 +348,7 @@ void rows_of(prim::KeySort<u64>& S, int n_rows, int item_bits, long long n) {
     if (within < 0) return;
     S.buckets = (int)(((long long)n_rows + (1ll << within) - 1) >> within);
     if (within >= 1 && within < S.group_bits && n <= 8ll * n_rows) S.group_bits = within;
+    S.crowded = n < n_rows;
 }
 
 // Kernels that count the keys' digits for it go by COUNT_ (see init_kernel) and its DigitCount.
@@ -826,6 +827,7 @@ int run_absorb(picasso_ctx* c, hipStream_t s, int B, int cur, int vbits, int nv_
         S.half = S.fits_half();
     }
     rows_of(S, nv_total, vbits, n_list);
+    S.crowded = false;  // (joined vertices lie where the pairs do, all over the mesh)
     clear_wide_counts(s, S);
     absorb_keys_kernel<<<grid_for(n_list), BLOCK, 0, s>>>(c->list, c->st, c->ekey, c->ecost, vbits, c->mate, c->abid,
                                                          c->arep, c->key64[0], digit_count(S), tb);

@@ -402,7 +402,9 @@ constexpr int BUCKET_THREADS_4096 = 512;  // 4096 buckets: up to 4096 keys (8 pe
 // keys without values (bucket_keys_kernel): lanes and keys per lane of a bucket's workgroup
 constexpr int BUCKET_KEYS_THREADS = 256, BUCKET_KEYS_ITEMS = 16;  // up to 4096 keys in LDS
 // Half as many lanes (and keys in LDS) where vertices or the like are made from the groups of buckets that hold this many keys or less on average: then
-// a lane has a group, and more buckets fit a compute unit (10.2 M vertices, 128 and 765 keys to a bucket: 421 -> 354 us).
+// a lane has a group, and more buckets fit a compute unit (10.2 M vertices, 128 and 765 keys to a bucket: 421 -> 354 us).  Not where most rows have no item
+// (KeySort::crowded): then a few buckets hold nearly all keys, many times the average, and one workgroup sorts each through memory (3.6 k vertices
+// with facets and 300 k without: 549 us by 128 lanes, 264 by 256; lists of their corners, whole calls, 450 and 234).
 constexpr int BUCKET_FEW_KEYS = 1024;
 constexpr int BUCKET_MSD_BITS = 8, NARROW_BITS_MAX = 10;  // (bits of a narrow digit: 8 to 10)
 constexpr long long BUCKET_SORT_MAX_KEYS = 1ll << 20;  // average bucket <= half of what LDS holds
@@ -758,6 +760,7 @@ struct KeySort {
     int key_bits = 0, digit_bits = 0;
     int buckets = 0;     // digits that occur are below this
     int group_bits = BUCKET_GROUP_BITS;  // bits below the digit that make a group (see sort_bucket)
+    bool crowded = false;  // fewer items than rows: some buckets may hold many times the average
     // Behind the partition the keys are 32-bit words (in k1, and in k0 where that is scratch): their low 32 bits, which hold
     // all that a bucket's keys differ in.  Half the bytes of three sweeps.
     bool half = false;
@@ -1748,7 +1751,7 @@ inline bool key_sort(hipStream_t s, const KeySort<K>& a, const KeySort<K>* b_or_
         if (timed) lt->end(s);
         timed = lt && lt->begin(s, tag);
         const int blocks = blocks_sort_a + blocks_sort_b;
-        if (TakesGroups<Out>::value && !b_or_null && (long long)a.n * Src::PER <= (long long)BUCKET_FEW_KEYS * a.buckets)
+        if (TakesGroups<Out>::value && !b_or_null && !a.crowded && (long long)a.n * Src::PER <= (long long)BUCKET_FEW_KEYS * a.buckets)
             bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS / 2, BUCKET_KEYS_ITEMS, Out><<<blocks, BUCKET_KEYS_THREADS / 2, 0, s>>>(a, b, blocks_sort_a, out);
         else
             bucket_keys_kernel<K, LK, BUCKET_KEYS_THREADS, BUCKET_KEYS_ITEMS, Out><<<blocks, BUCKET_KEYS_THREADS, 0, s>>>(a, b, blocks_sort_a, out);

@@ -30,3 +30,19 @@ def test_vertices_of_any_number_of_facets(pk, oracle, sizes, w, h):  # noqa: F81
     got = ctx.picasso_vertex_quadrics(dev(V), dev(F)).cpu().numpy()
     want = oracle.vertex_quadrics(V, F).astype(np.float32)
     np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+def test_vertices_most_of_which_have_no_facet(pk, oracle):  # noqa: F811
+    """Two buckets hold all keys, five times what fits LDS: 256 lanes sort them, not the 128 of buckets that hold as few as these do on average (549 us)."""
+    V, F = meshgen.noisy_grid(60, 60, seed=60)
+    V = np.concatenate([V, np.random.default_rng(1).normal(size=(300000, 3)).astype(np.float32)])
+    v, f = dev(V), dev(F)
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    got = ctx.picasso_vertex_quadrics(v, f).cpu().numpy()
+    np.testing.assert_array_equal(got.view(np.uint32), oracle.vertex_quadrics(V, F).astype(np.float32).view(np.uint32))
+    ctx.set_option(pk.PICASSO_OPT_KERNEL_TIMING, 1)
+    ctx.picasso_kernel_timing(pk.PICASSO_KERNEL_QUADRIC_ROWS, reset=True)
+    for _ in range(10):
+        ctx.picasso_decimate(v, f, len(V) - 500)
+    took = ctx.picasso_kernel_timing(pk.PICASSO_KERNEL_QUADRIC_ROWS, reset=True)
+    assert took["launches"] == 10 and took["ms_total"] / 10 < 0.4, took
