@@ -383,9 +383,9 @@ struct WalkMap {
 };
 // So that a step's items about fill the window (`average` items per row) and, where rows differ in length, no
 // group walks alone for long; and walks as long as keep all waves busy.
-inline WalkMap walk_map(int C, long long n_rows, double average, bool lines = false) {
+inline WalkMap walk_map(int C, long long n_rows, double average, bool lines = false, bool odd = false) {
     WalkMap m;
-    m.row = pool::row_map(C, false, lines);
+    m.row = pool::row_map(C, false, lines, odd);
     m.split = 0;
     while (m.split < 3 && (m.row.rw >> (m.split + 1)) >= 1 && (m.row.rw >> m.split) * average > 48.0) ++m.split;
     m.rows = m.row.rw >> m.split;

@@ -1839,7 +1839,7 @@ int picasso_v2f_backward(picasso_ctx* c, void* stream, const float* d_gy, const 
         HIP_TRY(c, hipGetLastError());
         return PICASSO_OK;
     }
-    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N);
+    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N, C > 128 || pool::beyond_cache(C, (long long)N + F), true);  // (see row_map)
     const int rc = split_filter_rows(c, N, 3, C, &m.row, m.per_wave * (pool::BLOCK / 64), 5, d_gw != nullptr, &sp);
     if (rc != PICASSO_OK) return rc;
     const dim3 grid(sp.groups, pool::row_parts(m.row));
@@ -1923,7 +1923,7 @@ int picasso_f2v_forward(picasso_ctx* c, void* stream, const float* d_y, int32_t 
         HIP_TRY(c, hipGetLastError());
         return PICASSO_OK;
     }
-    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N, true);
+    const conv::WalkMap m = conv::walk_map(C, N, (double)(3ll * F) / N, true, true);  // (see row_map)
     const int per_block = (T <= 16 ? m.per_wave : m.row.rw) * (pool::BLOCK / 64);
     const dim3 grid(prim::xcd_grid((N + per_block - 1) / per_block), pool::row_parts(m.row));
 #define PICASSO_F2V(NP, K) \
@@ -1974,7 +1974,7 @@ int picasso_f2v_backward(picasso_ctx* c, void* stream, const float* d_gx, const 
     }
     // one pass per 16 filter rows; gpi with it where a row's lanes fit a wave, else by a kernel of its own
     const bool gpi_fused = d_gpi && C <= 256;
-    const pool::RowMap m = pool::row_map(C, gpi_fused);
+    const pool::RowMap m = pool::row_map(C, gpi_fused, C > 128 && pool::beyond_cache(C, (long long)N + F));
     const int per_wave = conv::facets_per_wave(m, F);
     if (d_gy || d_gw || gpi_fused) {
         for (int t0 = 0; t0 < T; t0 += 16) {

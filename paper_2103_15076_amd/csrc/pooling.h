@@ -112,22 +112,29 @@ inline int row_parts(const RowMap& m) { return (m.Q + m.qc - 1) / m.qc; }
 // lines: rows of whole 128-byte lines may go in parts of whole lines, which leave nothing between two waves: three parts of 96 or of 192
 // channels (32, 64, 128, 160 and 256 go as they would anyhow).  In one part | in three, us: 192 channels, 115 k vertices, vertex2facet 64 | 54,
 // facet2vertex (6 components) 101 | 64, average pooling 21.1 | 20.0, max pooling's backward pass 27.9 | 24.7; 400 k vertices 268 | 218, 305 | 266, 91 | 88, 129 | 107;
-// 96 channels, 115 k vertices, facet2vertex 44 | 39, pooling 12.8 | 11.6.  Not in the passes that sum filter gradients, where a part more is a set of
-// partial sums more (192 channels, 60 k vertices: 46 | 55 and 49 | 59), nor in vertex2facet of 96 channels as long as the rows fit the Infinity Cache
-// (beyond_cache): 120 k facets 14 | 20, but 720 k 119 | 106, 1.28 M 185 | 169.  Parts that end within lines stay slow beyond it as well (95 channels,
-// 1.28 M facets: 334 | 526).
-inline RowMap row_map(int C, bool one_wave = false, bool lines = false) {
+// 96 channels, 115 k vertices, facet2vertex 44 | 39, pooling 12.8 | 11.6.  Not in vertex2facet of 96 channels, either way, as long as the rows fit the
+// Infinity Cache (beyond_cache): 120 k facets 14 | 20, but 720 k 119 | 106, 1.28 M 185 | 169; the backward pass 60 k vertices 29.2 | 32.0, 360 k 199 | 170 (192
+// channels 30 k 29.8 | 28.6, 60 k 48.9 | 50.3, 122 k 107 | 100, 360 k 384 | 353).  Parts that end within lines stay slow beyond it as well (95 channels,
+// 1.28 M facets: 334 | 526).  facet2vertex's backward pass, where a part more is a set of partial sums more: beyond the cache, 192 channels only (30 k vertices
+// 31.1 | 34.9, 122 k 119 | 109, 360 k 365 | 346; 96 channels 177 | 182).
+// odd: rows of no whole number of packs (their loads cross lines whichever way they are dealt) in the passes that walk the vertices' corners
+// (facet2vertex, vertex2facet's backward pass), where a wave holds two of them or one: parts by the lanes at work, a tenth of them to be brought by
+// each.  In one part | in two, 85 to 95 channels: facet2vertex 30 k vertices 21.2 | 18.9 us, 122 k 68 | 56, 360 k 204 | 208, vertex2facet's backward
+// pass 28.0 | 25.9, 75 | 66, 301 | 230; in one | in three, 169 to 191 channels: 33.6 | 31.8, 141 | 112, 392 | 389 and 39.4 | 37.0, 167 | 148, 569 | 441.
+inline RowMap row_map(int C, bool one_wave = false, bool lines = false, bool odd = false) {
     RowMap best{}, m;
     double best_use = -1.0;
     m.Q = (C + 3) / 4;
     const int least = (m.Q + 63) / 64;
     lines = lines && C % 32 == 0;
-    const int most = one_wave || (m.Q <= 32 && !lines) ? least : least + 3;
+    odd = odd && C % 4 != 0 && m.Q > 21;
+    const int most = one_wave || (m.Q <= 32 && !lines && !odd) ? least : least + 3;
     for (int parts = least; parts <= most && parts <= m.Q; ++parts) {
         m.qc = (m.Q + parts - 1) / parts;
         const bool whole = lines && m.qc % 8 == 0;
-        if (m.Q <= 32 && parts > 1 && !whole) continue;
-        const double a_part = m.Q > 64 ? 0.04 : m.Q > 32 && !whole ? 0.2 : 0.1;  // share of the lanes that a further part has to bring to work
+        if (m.Q <= 32 && parts > 1 && !whole && !odd) continue;
+        // share of the lanes that a further part has to bring to work
+        const double a_part = m.Q > 64 ? 0.04 : m.Q > 32 && !whole && !odd ? 0.2 : 0.1;
         m.rw = 64 / m.qc;
         m.inv = (65536 + m.qc - 1) / m.qc;
         const double use = (double)m.rw * m.Q / (64.0 * row_parts(m)) - a_part * (parts - least);  // lanes at work

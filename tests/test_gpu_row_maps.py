@@ -1,6 +1,7 @@
 """Channel counts on both sides of the lines at which rows are dealt to lanes and waves in another way (24 to 128 channels: a wave holds
 several rows, whose lanes need not fill it; 132 to 256: one row, or a part of one; 260: several waves a row; 96 and 192, rows of whole
-cache lines: three waves, 96 in vertex2facet only where the rows do not fit the cache): pooling and the convolutions against the fp64 oracle, whose bounds are those of test_gpu_conv and test_gpu_pooling."""
+cache lines: three waves, 96 in vertex2facet only where the rows do not fit the cache; 85 and 94, 170 and 189, no whole packs: two and three waves in the
+passes that walk the vertices' corners): pooling and the convolutions against the fp64 oracle, whose bounds are those of test_gpu_conv and test_gpu_pooling."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +13,7 @@ from test_gpu_conv import _close, _gw_terms, ctx, dev, pk  # noqa: F401  (fixtur
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("C", [24, 52, 96, 99, 128, 132, 160, 164, 192, 256, 260])
+@pytest.mark.parametrize("C", [24, 52, 85, 94, 96, 99, 128, 132, 160, 164, 170, 189, 192, 256, 260])
 def test_rows_dealt_to_lanes_and_waves(pk, ctx, oracle, C):  # noqa: F811
     V, F = meshgen.noisy_grid(37, 29, seed=C, noise=0.02)
     N, nF, T = V.shape[0], F.shape[0], 5
@@ -59,9 +60,9 @@ def _large(w):
     return V.shape[0], F
 
 
-@pytest.mark.parametrize("C", [93, 96])
+@pytest.mark.parametrize("C", [93, 96, 192])
 def test_rows_beyond_the_cache(pk, oracle, C):  # noqa: F811
-    """Forward passes whose rows exceed 256 MiB: of whole lines (in three parts) and not."""
+    """Passes whose rows exceed 256 MiB: of whole lines (in three parts) and not (two parts of 93 in those that walk the corners)."""
     N, F = _large(500)
     nF, T = F.shape[0], 5
     assert 4 * C * (N + nF) > 256 << 20
@@ -78,6 +79,35 @@ def test_rows_beyond_the_cache(pk, oracle, C):  # noqa: F811
     _close(got, oracle.v2f_forward(x, F, lv, w3), 9, oracle.v2f_forward(np.abs(x), F, lv, np.abs(w3)), "v2f")
     got = ctx.picasso_f2v_forward(dev(y), dev(pi), dev(w), off, cor, N)
     _close(got, oracle.f2v_forward(y, pi, w, F, N), (T + 2) * deg, oracle.f2v_forward(np.abs(y), pi, np.abs(w), F, N), "f2v")
+    got = ctx.picasso_v2f_backward(dev(y), dev(x), dev(F), dev(lv), dev(w3), off, cor)
+    ref, bar = oracle.v2f_backward(y, x, F, lv, w3), oracle.v2f_backward(np.abs(y), np.abs(x), F, lv, np.abs(w3))
+    for g, r, b, terms in zip(got, ref, bar, (4 * deg, _gw_terms(nF, 4))):
+        _close(g, r, terms, b, "v2f backward")
+    got = ctx.picasso_f2v_backward(dev(x), dev(y), dev(pi), dev(w), dev(F), off, want_gpi=False)
+    ref, bar = oracle.f2v_backward(x, y, pi, w, F), oracle.f2v_backward(np.abs(x), np.abs(y), pi, np.abs(w), F)
+    for g, r, b, terms in zip(got[:2], ref, bar, (T + 8, _gw_terms(nF, 6))):
+        _close(g, r, terms, b, "f2v backward")
+
+
+def test_rows_of_no_whole_packs_in_parts(pk):  # noqa: F811
+    """720 k facets of 172 and 174 channels, backwards: the unaligned rows take 1.2 times as long (1.5 times when one wave had a row)."""
+    N, F = _large(600)
+    f, lv = dev(F), torch.ones(F.shape[0], dtype=torch.int32, device="cuda:0")
+    ctx = pk.Context(N, F.shape[0], 1, device=0)  # noqa: F811
+    off, cor = ctx.picasso_vertex_corner_csr(f, N)
+    took = []
+    for C in (172, 174):
+        x, gy, w3 = (torch.randn(n, C, device="cuda:0") for n in (N, F.shape[0], 3))
+        ms = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ctx.picasso_v2f_backward(gy, x, f, lv, w3, off, cor)
+            b.record()
+            b.synchronize()
+            ms.append(a.elapsed_time(b))
+        took.append(sorted(ms)[len(ms) // 2])
+    assert took[1] < 1.35 * took[0], took
 
 
 def test_rows_that_are_not_whole_lines_stay_in_one_wave(pk):  # noqa: F811
