@@ -39,6 +39,7 @@ struct State {
     int sel_k;     // sub-round index the selection has reached (buffer rotation phase)
     int absorb_n;  // edges through which an un-paired vertex would join a pair's cluster (Alg. 2 line 11)
     int nv_kept;   // output vertices that some output facet refers to (option: degenerated vertices dropped)
+    int wide;      // rounds by rings: a vertex has more facets or neighbours than a row takes
     // Written by every selection tail for kernels that the host queued behind it before looking
     // (they run only if the tail finished the matching): 1 / nv of the round then, else zeros.
     int go, guard_nv;
@@ -315,6 +316,7 @@ struct DigitTally<COUNT_NONE> {
     __device__ __forceinline__ void flush(const DigitCount&) {}
 };
 
+constexpr int RINGS_TAKEN = 3 * 33 * MATCH_PAD;  // counters of the rings' rows (RingRows): two sets of rings, one of neighbours
 enum { EDGES_NONE = 0, EDGES_BY_FACETS = 1, EDGES_SORTED = 2 };
 template <int COUNT, bool SORTED, class Tables>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
@@ -325,7 +327,8 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                                                      int edges, int vbits, State* st, HeaderInit init, Tables tables,
                                                      float4* __restrict__ planes, int* __restrict__ htab, int n_clear,
                                                      u64* __restrict__ vmin0, u64* __restrict__ vmin1,
-                                                     int* __restrict__ mate, u32* __restrict__ pcost, RoundTab R) {
+                                                     int* __restrict__ mate, u32* __restrict__ pcost, RoundTab R,
+                                                     int* __restrict__ taken /* RINGS_TAKEN words, or null */) {
     __shared__ DigitTally<COUNT> corners;
     __shared__ DigitTally<SORTED ? COUNT : COUNT_NONE> sides;
     const int stride = gridDim.x * BLOCK;
@@ -356,6 +359,8 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         round_begin_block(R, st);
     }
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
+    if (taken && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < RINGS_TAKEN; i += BLOCK) taken[i] = 0;
     corners.clear(inc);
     if (SORTED) sides.clear(edge);
     __syncthreads();
@@ -551,11 +556,156 @@ __device__ __forceinline__ void add_plane_quadric(float (&acc)[10], const float4
     acc[8] = acc[8] + q8; acc[9] = acc[9] + q9;
 }
 
+// The rings of rounds by rings (see ring_costs_kernel): per vertex the facets that have it, each as its other two corners.  Of up to RING_MAX facets that name up to
+// RING_MAX vertices, as mostly, these vertices are a row of 32 bytes (`ids`): facet i's first corner is the i-th of them, its second one that of the number that
+// info gives.  (A ring is found from its vertex alone, most of them in one access.)  Other rings are noted facet by facet (first corner | second corner << 32), up to ROW_SMALL of
+// them in a row of one size, up to ROW_MAX in one of the other.
+// info: vertices | facets << 4 | numbers, three bits each, << 8; of other rings RING_ROWS | facets << 4 | row << 12.
+// Neighbours with their costs lie the same way: of short rings as a row of the costs in `ids`, of others as (cost << 32 | neighbour), info: RING_ROWS | how many << 4 | row << 12.
+constexpr int RING_MAX = 8;
+constexpr u32 RING_ROWS = 15;
+constexpr int ROW_LINE = 8, ROW_SMALL = 16, ROW_MAX = 64;
+__device__ __forceinline__ u32 rows_info(int n, u32 row) { return RING_ROWS | ((u32)n << 4) | (row << 12); }
+__device__ __forceinline__ int rows_length(u32 info) { return (int)(info >> 4 & 255u); }
+__device__ __forceinline__ u32 rows_number(u32 info) { return info >> 12; }
+__device__ __forceinline__ bool ring_in_rows(u32 info) { return (info & 15u) == RING_ROWS; }
+__device__ __forceinline__ int ring_ids(u32 info) { return (int)(info & 15u); }  // (of a short ring)
+__device__ __forceinline__ int ring_facets(u32 info) { return (int)(info >> 4 & (ring_in_rows(info) ? 255u : 15u)); }
+__device__ __forceinline__ int ring_second(u32 info, int i) { return (int)(info >> (8 + 3 * i) & 7u); }
+// Small rows are handed out in parts, each with a counter in a cache line of its own (a line takes an atomic every 11 ns).
+constexpr int ROW_ARENAS = 32, ROW_TRIES = 4;
+static_assert(RINGS_TAKEN == 3 * (ROW_ARENAS + 1) * MATCH_PAD, "a counter each");
+struct RingRows {
+    u32* ids;
+    u32* info;
+    u64* small;
+    u64* large;
+    int* taken;  // [ROW_ARENAS + 1][MATCH_PAD]: small rows in use of each part, then large ones
+    int arena_rows, large_rows;
+    int* wide;   // set where there is no row
+    __device__ __forceinline__ u64* row(int n, u32 number) const {
+        return n <= ROW_SMALL ? small + (size_t)number * ROW_SMALL : large + (size_t)number * ROW_MAX;
+    }
+    __device__ __forceinline__ u64* row_of(u32 info_) const { return row(rows_length(info_), rows_number(info_)); }
+    // A row for n entries; n comes back 0 where there is none.
+    __device__ __forceinline__ u32 take_row(int& n) const {
+        if (n <= ROW_SMALL) {
+            for (int k = 0; k < ROW_TRIES; ++k) {
+                const int arena = (int)(blockIdx.x + k) & (ROW_ARENAS - 1), at = atomicAdd(&taken[arena * MATCH_PAD], 1);
+                if (at < arena_rows) return (u32)(arena * arena_rows + at);
+            }
+        } else if (n <= ROW_MAX) {
+            const int at = atomicAdd(&taken[ROW_ARENAS * MATCH_PAD], 1);
+            if (at < large_rows) return (u32)at;
+        }
+        *wide = 1;
+        n = 0;
+        return 0;
+    }
+    __device__ __forceinline__ void load_ids(int v, u32 (&x)[RING_MAX]) const {
+        const uint4* r = reinterpret_cast<const uint4*>(ids + (size_t)v * RING_MAX);
+        const uint4 a = r[0], b = r[1];
+        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+        x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    }
+    __device__ __forceinline__ void store_ids(int v, const u32 (&x)[RING_MAX]) const {
+        uint4* r = reinterpret_cast<uint4*>(ids + (size_t)v * RING_MAX);
+        r[0] = make_uint4(x[0], x[1], x[2], x[3]);
+        r[1] = make_uint4(x[4], x[5], x[6], x[7]);
+    }
+};
+// A facet of a ring.
+__device__ __forceinline__ u64 ring_entry(int next, int prev) { return ((u64)(u32)prev << 32) | (u32)next; }
+__device__ __forceinline__ u64 ring_entry_of(const Corners& q, int v) {
+    return q.a == v ? ring_entry(q.b, q.c) : q.b == v ? ring_entry(q.c, q.a) : ring_entry(q.a, q.b);
+}
+// The short ring of the first n of these facets, or RING_ROWS where it takes more than RING_MAX vertices.  (On a surface the second corners are the first ones in
+// another order, but for open edges and facets wound the other way round.)
+__device__ __forceinline__ u32 make_ring(const u64 (&e)[RING_MAX], int n, u32 (&id)[RING_MAX]) {
+#pragma unroll
+    for (int k = 0; k < RING_MAX; ++k) id[k] = k < n ? (u32)e[k] : ~0u;
+    u32 seconds = 0, missing = 0;
+#pragma unroll
+    for (int i = 0; i < RING_MAX; ++i) {
+        const u32 q = (u32)(e[i] >> 32);
+        u32 at = RING_MAX;
+#pragma unroll
+        for (int k = RING_MAX - 1; k >= 0; --k) at = id[k] == q ? (u32)k : at;
+        missing |= i < n && at == RING_MAX ? 1u << i : 0u;
+        seconds |= (at & 7u) << (3 * i);
+    }
+    int m = n;
+    while (missing != 0 && m < RING_MAX) {
+        u32 q = 0;
+#pragma unroll
+        for (int i = RING_MAX - 1; i >= 0; --i) q = missing >> i & 1u ? (u32)(e[i] >> 32) : q;
+#pragma unroll
+        for (int k = 0; k < RING_MAX; ++k) id[k] = k == m ? q : id[k];
+#pragma unroll
+        for (int i = 0; i < RING_MAX; ++i)
+            if ((missing >> i & 1u) && (u32)(e[i] >> 32) == q) {
+                seconds = (seconds & ~(7u << (3 * i))) | ((u32)m << (3 * i));
+                missing &= ~(1u << i);
+            }
+        ++m;
+    }
+    return missing != 0 ? RING_ROWS : (u32)m | ((u32)n << 4) | (seconds << 8);
+}
+
+// The same where facets are wound both ways round, which puts vertices among the first corners twice and others not at all (or for any other reason there are too many):
+// the ring in the order in which they follow one another around the vertex, each from the vertex that it shares with the one in front of it, or RING_ROWS.  A
+// walk goes on from a vertex by the first or the last facet that has it, whichever it has not come by, and has met them all if they are n different ones; one that is
+// stuck before has come to an end of an open fan, if there is one: the second goes from there.  (Vertices and facets' numbers in one word: RING_VERTICES.)
+constexpr int RING_VERTICES = 1 << 29;  // rounds by rings take fewer vertices than this
+__device__ __forceinline__ u32 order_ring(const u64 (&e)[RING_MAX], int n, u32 (&id)[RING_MAX]) {
+    constexpr u32 NONE = ~0u;
+    u32 p[RING_MAX], q[RING_MAX];
+#pragma unroll
+    for (int j = 0; j < RING_MAX; ++j) {
+        p[j] = j < n ? (u32)e[j] << 3 | j : NONE;
+        q[j] = j < n ? (u32)(e[j] >> 32) << 3 | j : NONE;
+    }
+    const u32 all = (1u << n) - 1u;
+    u32 start = p[0] >> 3, at = start, met = 0;
+    for (int turn = 0; turn < 2 && met != all; ++turn) {
+        u32 came_by = RING_MAX;
+        start = at;
+        met = 0;
+#pragma unroll
+        for (int s = 0; s < RING_MAX; ++s) {
+            id[s] = at;
+            u32 lo = NONE, hi = NONE;
+#pragma unroll
+            for (int j = 0; j < RING_MAX; ++j) {
+                hi = p[j] == (at << 3 | j) ? q[j] : hi;
+                hi = q[j] == (at << 3 | j) ? p[j] : hi;
+            }
+#pragma unroll
+            for (int j = RING_MAX - 1; j >= 0; --j) {
+                lo = p[j] == (at << 3 | j) ? q[j] : lo;
+                lo = q[j] == (at << 3 | j) ? p[j] : lo;
+            }
+            const u32 on = (lo & 7u) == came_by ? hi : lo;
+            const bool stuck = on == NONE || (on & 7u) == came_by || (met >> (on & 7u) & 1u) != 0;
+            met |= stuck ? 0u : 1u << (on & 7u);
+            came_by = stuck ? came_by : on & 7u;
+            at = stuck ? at : on >> 3;
+        }
+    }
+    constexpr u32 NEXT = 1u | 2u << 3 | 3u << 6 | 4u << 9 | 5u << 12 | 6u << 15 | 7u << 18;
+    if (met != all) return RING_ROWS;
+    if (at == start) return (u32)n | ((u32)n << 4) | ((NEXT & ~(7u << (3 * (n - 1)))) << 8);  // (the last one leads to the first vertex)
+    return n < RING_MAX ? (u32)(n + 1) | ((u32)n << 4) | (NEXT << 8) : RING_ROWS;
+}
+// RINGS: the vertex's ring (see ring_costs_kernel) is left as well, from the corners of the facets.
+template <bool RINGS>
 struct QuadricRows {
     VRec* vrec;
     const float* verts;
     const float4* planes;
     int N, fbits;
+    const int* fcur;
+    RingRows ring;
     template <int THREADS, int ITEMS>
     struct Lds {
         unsigned short start[THREADS / 64][QR_WINDOW];  // (within the window)
@@ -585,6 +735,50 @@ struct QuadricRows {
                 if (j0 + j < g) add_plane_quadric(acc, p[j]);
         }
     }
+    // The ring of a group that a lane has sorted, in any order of its facets.  (By itself, behind the quadrics of all groups: together they take 140 registers.)
+    template <int G, typename LK>
+    __device__ __forceinline__ u32 ring_of_group(const prim::Bucket& b, const LK* key, int g, int v) const {
+        u32 info = 0;
+        u64* row = nullptr;
+        if (G > RING_MAX) {
+            const u32 number = ring.take_row(g);
+            info = rows_info(g, number);
+            row = ring.row(g, number);
+        }
+#pragma unroll
+        for (int j0 = 0; j0 < G; j0 += 8) {
+            u64 e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                e[j] = j0 + j < g ? ring_entry_of(load_corners(fcur, b.item(key[j0 + j], fbits)), v) : 0ull;
+            if (G <= RING_MAX) info = leave_ring(v, e, g);
+            else
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (j0 + j < g) row[j0 + j] = e[j];
+        }
+        return info;
+    }
+    // the ring of up to eight facets
+    __device__ __forceinline__ u32 leave_ring(int v, const u64 (&e)[8], int g) const {
+        u32 id[RING_MAX];
+        u32 info = make_ring(e, g, id);
+        if (info == RING_ROWS) info = order_ring(e, g, id);
+        if (info != RING_ROWS) {
+            ring.store_ids(v, id);
+            return info;
+        }
+        const u32 number = ring.take_row(g);
+        u64* const row = ring.row(g, number);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (j < g) row[j] = e[j];
+        return rows_info(g, number);
+    }
+    __device__ __forceinline__ void write(int v, const float (&acc)[10], u32 info) const {
+        write_vertex_record(vrec, verts, v, acc);
+        if constexpr (RINGS) ring.info[v] = info;
+    }
     template <int THREADS, int ITEMS, class L>
     __device__ __forceinline__ void emit_groups(L& lds, const prim::Bucket& b, int R) const {
         const int t = threadIdx.x, lane = prim::lane_id(), lo = b.number * R, n = min(R, N - lo);
@@ -601,10 +795,26 @@ struct QuadricRows {
             else add_group<GROUP_SHORT>(acc, b, lds.skey + gs, g);
             write_vertex_record(vrec, verts, lo + gi, acc);
         }
+        if constexpr (RINGS)
+            for (int gi = t; gi < n; gi += THREADS) {
+                const int gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
+                if (g > GROUP_LANE) continue;
+                if (g > GROUP_SHORT) ring.info[lo + gi] = ring_of_group<GROUP_LANE>(b, lds.skey + gs, g, lo + gi);
+                else ring.info[lo + gi] = ring_of_group<GROUP_SHORT>(b, lds.skey + gs, g, lo + gi);
+            }
         __syncthreads();
         for (int li = prim::wave_id(); li < (int)lds.nlong; li += THREADS / 64) {
             const int gi = (int)lds.gcnt[li], gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
             prim::rank_group_lds(lds.skey + gs, g);
+            int n = g;
+            u32 number = 0;
+            if constexpr (RINGS) {
+                if (lane == 0) number = ring.take_row(n);
+                n = __shfl(n, 0, 64);
+                number = (u32)__shfl((int)number, 0, 64);
+                u64* const row = ring.row(n, number);
+                for (int j = lane; j < n; j += 64) row[j] = ring_entry_of(load_corners(fcur, b.item(lds.skey[gs + j], fbits)), lo + gi);
+            }
             if (lane == 0) {
                 float acc[10] = {};
                 for (int j0 = 0; j0 < g; j0 += 8) {
@@ -616,7 +826,7 @@ struct QuadricRows {
                     for (int j = 0; j < 8; ++j)
                         if (j0 + j < g) add_plane_quadric(acc, p[j]);
                 }
-                write_vertex_record(vrec, verts, lo + gi, acc);
+                write(lo + gi, acc, rows_info(n, number));
             }
         }
     }
@@ -629,7 +839,7 @@ struct QuadricRows {
         const int lo = (int)lo64, hi = (int)min(lo64 + (1ll << per), (long long)N);  // the bucket's vertices
         const float zero[10] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (n == 0) {
-            for (int v = lo + t; v < hi; v += THREADS) write_vertex_record(vrec, verts, v, zero);
+            for (int v = lo + t; v < hi; v += THREADS) write(v, zero, 0);
             return;
         }
         if (t == 0) lds.n_gaps = 0;
@@ -642,7 +852,7 @@ struct QuadricRows {
                 lds.gap[2 * slot] = first;
                 lds.gap[2 * slot + 1] = end;
             } else {
-                for (int g = first; g < end; ++g) write_vertex_record(vrec, verts, g, zero);
+                for (int g = first; g < end; ++g) write(g, zero, 0);
             }
         };
         unsigned short* list = lds.start[w];
@@ -682,6 +892,28 @@ struct QuadricRows {
                         if (j0 + j < end) add_plane_quadric(acc, p[j]);
                 }
                 write_vertex_record(vrec, verts, v, acc);
+                if constexpr (RINGS) {
+                    int n_ring = end - hp;
+                    u32 info = 0;
+                    u64* row = nullptr;
+                    if (n_ring > RING_MAX) {
+                        const u32 number = ring.take_row(n_ring);
+                        info = rows_info(n_ring, number);
+                        row = ring.row(n_ring, number);
+                    }
+                    for (int j0 = hp; j0 < hp + n_ring; j0 += 8) {
+                        u64 e[8];
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            e[j] = j0 + j < end ? ring_entry_of(load_corners(fcur, b.item(key_at(j0 + j), fbits)), v) : 0ull;
+                        if (n_ring <= RING_MAX) info = leave_ring(v, e, n_ring);
+                        else
+#pragma unroll
+                            for (int j = 0; j < 8; ++j)
+                                if (j0 + j < end) row[j0 + j - hp] = e[j];
+                    }
+                    ring.info[v] = info;
+                }
                 if (end == n && v + 1 < hi) note_gap(v + 1, hi);
             }
             __builtin_amdgcn_wave_barrier();
@@ -689,7 +921,7 @@ struct QuadricRows {
         __syncthreads();
         const int ng = min(lds.n_gaps, QR_GAPS);
         for (int i = 0; i < ng; ++i)
-            for (int g = lds.gap[2 * i] + t; g < lds.gap[2 * i + 1]; g += THREADS) write_vertex_record(vrec, verts, g, zero);
+            for (int g = lds.gap[2 * i] + t; g < lds.gap[2 * i + 1]; g += THREADS) write(g, zero, 0);
     }
 };
 
@@ -2073,6 +2305,500 @@ __global__ void signal_kernel(HostSignal done) {
     if (threadIdx.x == 0) tell_host(done);
 }
 
+// ---------------------------------------------------------------------------
+// Rounds by rings: S1 to S3 without a list of the edges, and the whole matching in one launch.
+//
+// A vertex's ring is the facets that have it, each as its other two corners (RingRows).  The quadrics' kernel leaves the rings of the input; a contraction's
+// vertex takes over the rings of the two it was made of, in the new numbering, without the facets whose corners have met.  So no round after the first reads
+// a facet, and every vertex has its edges at hand: ring_costs_kernel evaluates them once from either end (the same to the bit) and leaves the neighbours with
+// their costs.
+//
+// The matching (Alg. 2 lines 3-10) is the one in which pairs are accepted in the order of (cost, edge); it is unique, and the edges at a vertex compare by
+// (cost, other end).  suitor_kernel makes it the way of Manne and Halappanavar ("New effective multithreaded matching algorithms", IPDPS 2014): every vertex
+// bids on its best neighbour; of two bids on a vertex the better one stays, the other's vertex goes on to its next best neighbour, whose bid it betters, and
+// so on.  Bids only improve, so a neighbour that has refused a vertex once need not be asked again, no vertex waits for another, and what is left when all
+// have ended does not depend on the order.  In the end two vertices are a pair if each holds the other's bid.
+// ---------------------------------------------------------------------------
+constexpr int RING_THREADS = 128, RING_GROUP = 16;
+constexpr u64 BID_COST = 0xFFFFFFFF00000000ull;  // the cost key of a bid or a neighbour's entry; below it a vertex
+
+__device__ __forceinline__ void load_line(u64 (&x)[ROW_LINE], const u64* p) {
+    const ulonglong2* q = reinterpret_cast<const ulonglong2*>(p);
+#pragma unroll
+    for (int j = 0; j < ROW_LINE; j += 2) {
+        const ulonglong2 two = q[j / 2];
+        x[j] = two.x;
+        x[j + 1] = two.y;
+    }
+}
+
+// what the other lane of a pair holds
+__device__ __forceinline__ u32 of_pair(u32 x) { return (u32)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true); }  // (quad_perm 1, 0, 3, 2)
+__device__ __forceinline__ u64 of_pair(u64 x) { return ((u64)of_pair((u32)(x >> 32)) << 32) | of_pair((u32)x); }
+
+constexpr int RING_TILE = RING_THREADS / 2;    // vertices of a workgroup
+constexpr int RING_LABELS = 4 * RING_THREADS;  // labels of one of the workgroups behind those of the vertices
+
+// Two lanes a vertex: each takes over the ring of one of the two that the vertex was made of, then evaluates every other neighbour.
+template <int PLACE, bool FIRST>
+__global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int nv, const VRec* __restrict__ vrec, RingRows in, RingRows out,
+                                                                  RingRows adj, u64* __restrict__ first, u64* __restrict__ bids, RoundTab R,
+                                                                  const int4* __restrict__ from, const int* __restrict__ vmap,
+                                                                  int* __restrict__ cid, int n_labels, float rcond_min,
+                                                                  int* __restrict__ facet_slots, int* __restrict__ facet_next) {
+    __shared__ MeshFlags M;
+    constexpr int HALF = RING_MAX / 2;
+    static_assert(64 / RING_GROUP * ROW_MAX <= 64 * RING_MAX, "the groups' rings fit the wave's part");
+    __shared__ u64 stages[RING_THREADS / 64][64 * RING_MAX];  // a wave's part: its lanes' vertices, then their facets, then the facets of the rings that its groups are at
+    __shared__ int facets;
+    const int t = threadIdx.x, lane = prim::lane_id(), half = lane & 1;
+    if constexpr (!FIRST) {  // (the labels follow the last contraction)
+        const int part = (int)blockIdx.x - (((nv + RING_TILE - 1) / RING_TILE + 7) & ~7);
+        if (part >= 0) {
+            int c[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const long long o = (long long)part * RING_LABELS + j * RING_THREADS + t;
+                c[j] = o < n_labels ? cid[o] : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c[j] = vmap[c[j]];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const long long o = (long long)part * RING_LABELS + j * RING_THREADS + t;
+                if (o < n_labels) cid[o] = c[j];
+            }
+            return;
+        }
+    }
+    const int tiles = (nv + RING_TILE - 1) / RING_TILE, w = prim::xcd_item((int)blockIdx.x, tiles) * RING_TILE + t / 2, v = min(w, nv - 1);
+    const bool here = w < nv, lead = here && half == 0;
+    u64* const stage = stages[prim::wave_id()];
+    auto in_order = [] {  // (a wave's LDS operations complete in order: what is to be kept in order is the compiler)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+    };
+    u32 info, id[RING_MAX];
+    int4 two = make_int4(0, -1, 0, 0);
+    VertexWords own;
+    if constexpr (!FIRST) {
+        two = from[v];
+        if (blockIdx.x == 0) round_begin_block(R, st);
+        if (t == 0) facets = 0;
+    }
+    if (blockIdx.x == 0 && t < MATCH_SLOTS) facet_next[t * MATCH_PAD] = 0;
+    if (R.B > 1) M.begin(R, nullptr);
+    own = load_vertex(vrec, v);
+    if constexpr (FIRST) {
+        info = in.info[v];
+        in.load_ids(v, id);  // (whatever its row holds)
+    } else {
+        // the facets of the two it was made of, in the new numbering, without those whose corners have met
+        const u32 mine = (u32)(half ? two.w : two.z), theirs = (u32)(half ? two.z : two.w);
+        const bool short_rings = !ring_in_rows(mine) && !ring_in_rows(theirs);
+        u32 x[RING_MAX], y[RING_MAX];
+        in.load_ids(half ? max(two.y, 0) : two.x, x);
+        // Rings go either way round; where the vertex that follows the other one is the same in both, the second is taken backwards (else first corners are met twice).
+        const u32 other = (u32)(half ? two.x : two.y);
+        u32 follows = x[0], at = 0;
+#pragma unroll
+        for (int j = 1; j < RING_MAX; ++j) at = x[j] == other && j < ring_facets(mine) ? (u32)j : at;
+        at = (u32)ring_second(mine, (int)at);
+#pragma unroll
+        for (int j = 1; j < RING_MAX; ++j) follows = at == (u32)j ? x[j] : follows;
+        const bool backwards = half != 0 && of_pair(follows) == follows;
+        const int n_ids = short_rings ? ring_ids(mine) : 0, n_mine = short_rings ? ring_facets(mine) : 0;
+#pragma unroll
+        for (int j = 0; j < RING_MAX; ++j) x[j] = (u32)vmap[j < n_ids ? x[j] : 0u];
+        u32* const ids = reinterpret_cast<u32*>(stage) + lane;
+#pragma unroll
+        for (int j = 0; j < RING_MAX; ++j) ids[j * 64] = x[j];
+        in_order();
+#pragma unroll
+        for (int j = 0; j < RING_MAX; ++j) y[j] = ids[ring_second(mine, j) * 64];
+        in_order();
+        u32 ok = 0;
+#pragma unroll
+        for (int j = 0; j < RING_MAX; ++j) ok |= x[j] != (u32)w && y[j] != (u32)w && x[j] != y[j] ? 1u << j : 0u;
+        ok &= (1u << n_mine) - 1u;
+        const int n_ok = __popc(ok), n_other = (int)of_pair((u32)n_ok), n = n_ok + n_other;
+        u64* const facet = stage + lane / 2;  // (the pair's: in rows of 32)
+#pragma unroll
+        for (int j = 0; j < RING_MAX; ++j) {
+            const int place = (half ? n_other : 0) + __popc(ok & ((1u << j) - 1u));
+            if ((ok >> j & 1u) && place < RING_MAX)
+                facet[place * 32] = ring_entry((int)(backwards ? y[j] : x[j]), (int)(backwards ? x[j] : y[j]));
+        }
+        in_order();
+        info = RING_ROWS;
+        if (short_rings && n <= RING_MAX) {
+            u64 e[RING_MAX];
+#pragma unroll
+            for (int j = 0; j < RING_MAX; ++j) e[j] = facet[j * 32];
+            info = make_ring(e, n, id);
+            if (info == RING_ROWS) info = order_ring(e, n, id);
+            if (lead && info != RING_ROWS) {
+                out.store_ids(w, id);
+                out.info[w] = info;
+            }
+        }
+    }
+    if (!FIRST || R.B > 1) __syncthreads();
+    const bool active = here && (R.B <= 1 || M.is_active(R, v)), in_rows = here && ring_in_rows(info);
+    auto neighbour = [&](int u, const VertexWords& U, int x, const VertexWords& X) -> u32 {
+        return u == x ? PAIR_NONE : cost_key(pair_cost<PLACE>(U, X, rcond_min));
+    };
+    auto bid = [&](int u, u64 best) {  // the first one, on the best neighbour
+        first[u] = best;
+        if (best != VMIN_NONE) atomicMin(&bids[(u32)best], (best & BID_COST) | (u32)u);
+    };
+    const int n = active && !in_rows ? ring_ids(info) : 0;
+    if (n > 0) {
+        u32 x[HALF], cost[HALF];  // every other neighbour
+        u64 best = VMIN_NONE;
+        VertexWords X[HALF];
+#pragma unroll
+        for (int j = 0; j < HALF; ++j) {
+            x[j] = 2 * j + half < n ? id[2 * j + half] : (u32)v;
+            cost[j] = PAIR_NONE;
+        }
+#pragma unroll
+        for (int j = 0; j < HALF; ++j)
+            if (j + 1 < HALF || n > 2 * j) X[j] = load_vertex(vrec, (int)x[j]);
+#pragma unroll
+        for (int j = 0; j < HALF; ++j)
+            if (j + 1 < HALF || n > 2 * j) {
+                cost[j] = neighbour(v, own, (int)x[j], X[j]);
+                const u64 key = x[j] == (u32)v ? VMIN_NONE : ((u64)cost[j] << 32) | x[j];
+                best = key < best ? key : best;
+            }
+        const u64 others = of_pair(best);
+        best = others < best ? others : best;
+        // the costs in the order of the neighbours: each lane writes half of them
+        static_assert(HALF == 4, "two costs of each lane to a half");
+        const u32 s0 = of_pair(half ? cost[0] : cost[2]), s1 = of_pair(half ? cost[1] : cost[3]);
+        uint4* const row = reinterpret_cast<uint4*>(adj.ids + (size_t)v * RING_MAX) + half;
+        *row = half ? make_uint4(s0, cost[2], s1, cost[3]) : make_uint4(cost[0], s0, cost[1], s1);
+        if (lead) bid(v, best);
+    } else if (lead && !in_rows) {
+        first[v] = VMIN_NONE;
+    }
+    // Rings in rows: RING_GROUP lanes a ring, the wave's lanes with such rings one group after the other.
+    int n_facets = lead && !in_rows ? ring_facets(info) : 0;
+    in_order();
+    for (u64 todo = prim::ballot(lead && in_rows); todo != 0;) {
+        const int sub = lane & (RING_GROUP - 1), group = lane / RING_GROUP;
+        int owner = -1;
+#pragma unroll
+        for (int k = 0; k < 64 / RING_GROUP; ++k) {
+            if (k == group && todo) owner = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+        }
+        const int from_lane = max(owner, 0), u = __shfl(v, from_lane, 64), its_active = __shfl(active ? 1 : 0, from_lane, 64);
+        const bool on = owner >= 0, counts = on && its_active != 0;
+        const int4 pair = make_int4(__shfl(two.x, from_lane, 64), __shfl(two.y, from_lane, 64), __shfl(two.z, from_lane, 64), __shfl(two.w, from_lane, 64));
+        u64* const facet = stage + group * ROW_MAX;
+        const u32 group_mask = (1u << RING_GROUP) - 1u;
+        const int group_lead = lane & ~(RING_GROUP - 1);
+        auto of_group = [&](bool x) -> u32 { return (u32)(prim::ballot(x) >> (group * RING_GROUP)) & group_mask; };
+        // a row of the group for n entries (n = 0: there is none)
+        auto group_row = [&](const RingRows& rows, int& n_, u32& number) {
+            number = 0;
+            if (sub == 0 && n_ > 0) number = rows.take_row(n_);
+            n_ = __shfl(n_, group_lead, 64);
+            number = (u32)__shfl((int)number, group_lead, 64);
+        };
+        int k = 0;  // facets there are
+        if constexpr (FIRST) {
+            const u32 row = (u32)__shfl((int)info, from_lane, 64);
+            k = on ? rows_length(row) : 0;
+            const u64* const of = in.row_of(row);
+            for (int i = sub; i < k; i += RING_GROUP) facet[i] = of[i];
+        } else {
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+                const int src = h ? pair.y : pair.x;
+                const u32 row = (u32)(h ? pair.w : pair.z);
+                const int count = on && src >= 0 ? ring_facets(row) : 0;
+                for (int i0 = 0; __any(i0 < count); i0 += RING_GROUP) {
+                    const int i = i0 + sub;
+                    bool ok = i < count;
+                    u64 e = 0;
+                    if (ok) {
+                        const u32* const of = in.ids + (size_t)src * RING_MAX;
+                        if (ring_in_rows(row)) e = in.row_of(row)[i];
+                        else e = ring_entry((int)of[i], (int)of[ring_second(row, i)]);
+                    }
+                    const int a = vmap[ok ? (u32)e : 0u], b = vmap[ok ? (u32)(e >> 32) : 0u];
+                    ok = ok && a != u && b != u && a != b;
+                    const u32 in_group = of_group(ok);
+                    const int place = k + __popc(in_group & ((1u << sub) - 1u));
+                    if (ok && place < ROW_MAX) facet[place] = ring_entry(a, b);
+                    k += __popc(in_group);
+                }
+            }
+        }
+        in_order();
+        if constexpr (!FIRST) {
+            u32 number;
+            group_row(out, k, number);  // (more than ROW_MAX do not fit)
+            u64* const row = out.row(k, number);
+            for (int i = sub; i < k; i += RING_GROUP) row[i] = facet[i];
+            if (on && sub == 0) out.info[u] = rows_info(k, number);
+        }
+        if (sub == 0) n_facets += k;
+        // its neighbours: the facets' first other corners, and the second ones that are no facet's first
+        const VertexWords U = load_vertex(vrec, u);
+        const int fits = counts ? k : 0;
+        u32 only = 0;  // of the lane's facets, one in every turn
+        int m = fits;
+        for (int i0 = 0, turn = 0; __any(i0 < fits); i0 += RING_GROUP, ++turn) {
+            const bool ok = i0 + sub < fits;
+            const int b = ok ? (int)(u32)(facet[i0 + sub] >> 32) : u;
+            bool is = b != u;
+            for (int j = 0; j < fits; ++j) is = is && (int)(u32)facet[j] != b;
+            only |= is ? 1u << turn : 0u;
+            m += __popc(of_group(is));
+        }
+        u32 number;
+        group_row(adj, m, number);
+        u64* const row = adj.row(m, number);
+        u64 best = VMIN_NONE;
+        int place0 = fits;
+        for (int i0 = 0, turn = 0; __any(m > 0 && i0 < fits); i0 += RING_GROUP, ++turn) {
+            const int i = i0 + sub;
+            const bool ok = m > 0 && i < fits, is = ok && (only >> turn & 1u);
+            const u64 e = ok ? facet[i] : 0;
+            const int a = ok ? (int)(u32)e : u, b = is ? (int)(u32)(e >> 32) : u;
+            const u64 key = ((u64)neighbour(u, U, a, load_vertex(vrec, a)) << 32) | (u32)a;
+            if (ok) row[i] = key;
+            if (a != u && key < best) best = key;
+            const u32 more = of_group(is);
+            if (is) {
+                const u64 key_b = ((u64)neighbour(u, U, b, load_vertex(vrec, b)) << 32) | (u32)b;
+                row[place0 + __popc(more & ((1u << sub) - 1u))] = key_b;
+                if (key_b < best) best = key_b;
+            }
+            place0 += __popc(more);
+        }
+#pragma unroll
+        for (int d = RING_GROUP / 2; d > 0; d >>= 1) {
+            const u64 other = __shfl_xor(best, d, 64);
+            best = other < best ? other : best;
+        }
+        if (on && sub == 0) {
+            adj.info[u] = rows_info(m, number);
+            bid(u, best);
+        }
+        in_order();
+    }
+    if constexpr (!FIRST) {
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) n_facets += __shfl_xor(n_facets, d, 64);
+        if (lane == 0 && n_facets) atomicAdd(&facets, n_facets);
+        __syncthreads();
+        if (t == 0 && facets) atomicAdd(&facet_slots[(blockIdx.x & (MATCH_SLOTS - 1)) * MATCH_PAD], facets);
+    }
+}
+
+// The matching from the first bids (on every vertex's best neighbour) on.  A wave has `per` vertices in a row to itself: it lists whose bids have been bettered, so many at a
+// time; its lanes take one after the other, and with it whoever their bids drive out in turn.  Several lanes may come to go on for a vertex (one that finds its bid
+// gone, and the one that drove it out): they ask the same neighbours in the same order, and the one that finds the vertex's own bid there ends.
+constexpr int SUITOR_LOOK = 4;  // vertices of a lane that are looked at together
+__global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, State* st, RingRows ring, RingRows adj, const u64* __restrict__ first, u64* bids,
+                                                       int* __restrict__ taken_next) {
+    __shared__ u64 tried[prim::WAVES][64 * SUITOR_LOOK];  // the neighbour (with its cost) that has refused the vertex
+    __shared__ int lost[prim::WAVES][64 * SUITOR_LOOK];
+    const int t = threadIdx.x, lane = prim::lane_id(), w = prim::wave_id();
+    if (blockIdx.x == 0 && t <= ROW_ARENAS) adj.taken[t * MATCH_PAD] = taken_next[t * MATCH_PAD] = 0;  // (of the next round)
+    if (st->wide) return;
+    const long long from = (long long)prim::xcd_item((int)blockIdx.x, (nv - 1) / (per * prim::WAVES) + 1) * prim::WAVES + w;
+    long long at = from * per;  // the next vertex to look at
+    const long long end = min(at + per, (long long)nv);
+    int listed = 0, taken = 0;
+    bool busy = false, fetch = false;
+    int u = 0, m = 0;
+    const u64* longer = nullptr;  // a long row
+    u64 last = 0, row[ROW_LINE];
+#pragma unroll
+    for (int j = 0; j < ROW_LINE; ++j) row[j] = VMIN_NONE;
+    for (;;) {
+        while (taken == listed && at < end && __any(!busy)) {
+            u64 k[SUITOR_LOOK], b[SUITOR_LOOK];
+#pragma unroll
+            for (int j = 0; j < SUITOR_LOOK; ++j) k[j] = at + j * 64 + lane < end ? first[at + j * 64 + lane] : VMIN_NONE;
+#pragma unroll
+            for (int j = 0; j < SUITOR_LOOK; ++j) b[j] = bids[k[j] != VMIN_NONE ? (u32)k[j] : 0u];
+            listed = taken = 0;
+#pragma unroll
+            for (int j = 0; j < SUITOR_LOOK; ++j) {
+                const int v = (int)at + j * 64 + lane;
+                const bool gone = k[j] != VMIN_NONE && b[j] != ((k[j] & BID_COST) | (u32)v);
+                const u64 all = prim::ballot(gone);
+                if (gone) {
+                    tried[w][listed + (int)prim::mask_below(all)] = k[j];
+                    lost[w][listed + (int)prim::mask_below(all)] = v;
+                }
+                listed += (int)__popcll(all);
+            }
+            at += 64 * SUITOR_LOOK;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+        }
+        const u64 idle = prim::ballot(!busy);
+        if (taken < listed) {
+            const int i = taken + (int)prim::mask_below(idle);
+            if (!busy && i < listed) {
+                u = lost[w][i];
+                last = tried[w][i];
+                busy = fetch = true;
+            }
+            taken = min(listed, taken + (int)__popcll(idle));
+        }
+        if (!__any(busy)) break;
+        if (fetch) {
+            const u32 info = ring.info[u];
+            u32 id[RING_MAX], cost[RING_MAX];
+            ring.load_ids(u, id);
+            adj.load_ids(u, cost);
+            m = ring_ids(info);
+#pragma unroll
+            for (int j = 0; j < ROW_LINE; ++j) row[j] = ((u64)cost[j] << 32) | id[j];
+            if (ring_in_rows(info)) {
+                const u32 with = adj.info[u];
+                longer = adj.row_of(with);
+                m = rows_length(with);
+                if (m > 0) load_line(row, longer);
+            }
+            fetch = false;
+        }
+        // the best neighbour behind `last` whose bid u's betters or is (what others have bid meanwhile only makes it fewer)
+        u64 want = VMIN_NONE;
+        auto consider = [&](const u64 (&x)[ROW_LINE], int i0) {
+            u64 there[ROW_LINE];
+            bool open[ROW_LINE];
+#pragma unroll
+            for (int j = 0; j < ROW_LINE; ++j) {
+                open[j] = busy && i0 + j < m && x[j] > last && (u32)(x[j] >> 32) != PAIR_NONE;
+                if (open[j]) there[j] = bids[(u32)x[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < ROW_LINE; ++j)
+                if (open[j] && there[j] >= ((x[j] & BID_COST) | (u32)u) && x[j] < want) want = x[j];
+        };
+        consider(row, 0);
+        for (int i0 = ROW_LINE; __any(busy && i0 < m); i0 += ROW_LINE) {
+            u64 x[ROW_LINE];
+            if (busy && i0 < m) {
+                load_line(x, longer + i0);
+            } else {
+#pragma unroll
+                for (int j = 0; j < ROW_LINE; ++j) x[j] = VMIN_NONE;
+            }
+            consider(x, i0);
+        }
+        if (busy) {
+            if (want == VMIN_NONE) {
+                busy = false;  // (nobody is left: u stays alone)
+            } else {
+                const u64 mine = (want & BID_COST) | (u32)u;
+                const u64 old = atomicMin(&bids[(u32)want], mine);
+                if (old > mine) {
+                    busy = fetch = old != VMIN_NONE;
+                    if (busy) {  // whose bid was there goes on behind this vertex
+                        last = (old & BID_COST) | (u32)want;
+                        u = (int)(u32)old;
+                    }
+                } else {
+                    busy = old != mine;
+                    last = want;
+                }
+            }
+        }
+    }
+}
+
+// The pairs that the bids come to: partners and costs by vertex, how many there are of each mesh, and per tile the vertices that survive them (as a
+// compaction's count pass does).
+template <int CHUNKS>
+__global__ __launch_bounds__(BLOCK) void pairs_kernel(SelArgs A, const u64* __restrict__ bids, int* __restrict__ tilesum) {
+    __shared__ PairTally tally;
+    __shared__ u32 smem[prim::WAVES];
+    const int nv = A.nv, wave = prim::wave_id(), lane = prim::lane_id(), t = threadIdx.x;
+    const bool wide = A.st->wide != 0;
+    if (blockIdx.x == 0 && t == 0) {  // (what the kernels queued behind this one go by)
+        A.st->go = wide ? 0 : 1;
+        A.st->guard_nv = wide ? 0 : nv;
+    }
+    if (wide) return;
+    const long long base = (long long)blockIdx.x * (BLOCK * CHUNKS), i0 = base + wave * (64 * CHUNKS) + lane;
+    u64 b[CHUNKS], back[CHUNKS];
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) b[c] = i0 + c * 64 < nv ? bids[i0 + c * 64] : VMIN_NONE;
+    if (t == 0) tally.begin(A, (int)base);
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) back[c] = bids[b[c] != VMIN_NONE ? (u32)b[c] : 0u];
+    __syncthreads();
+    u32 stay = 0;
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        const long long i = i0 + c * 64;
+        const int w = (int)i, p = (int)(u32)b[c];
+        const bool paired = b[c] != VMIN_NONE && back[c] == ((b[c] & BID_COST) | (u32)w), lower = paired && w < p;
+        if (i < nv) {
+            A.mate[w] = paired ? p : -1;
+            A.pcost[w] = lower ? (u32)(b[c] >> 32) : PAIR_NONE;
+        }
+        tally.count(A, lower, w);
+        stay += (u32)__popcll(prim::ballot(i < nv && (!paired || lower)));
+    }
+    if (lane == 0) smem[wave] = stay;
+    __syncthreads();
+    if (t == 0) {
+        tilesum[blockIdx.x] = (int)(smem[0] + smem[1] + smem[2] + smem[3]);
+        tally.end(A);
+    }
+}
+
+// The round's pair counts and State for the host, by one workgroup of a kernel behind pairs_kernel (the number `at`, which does nothing else).
+struct PairPublish {
+    int at;  // -1: published already
+    State* st;
+    const int* mslots;
+    int* matched;
+    int* done;  // (or null) meshes with pairs are marked
+    int B;
+    const int* facet_slots;  // (or null: all facets are left)
+    int* host_img;
+    int publish_ints;
+    int* host_check;
+    HostSignal tell;
+};
+__device__ __forceinline__ void publish_pairs(const PairPublish& P) {
+    constexpr int STATE_INTS = (int)(sizeof(State) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int)), NH = (int)(offsetof(State, nh) / sizeof(int));
+    static_assert(MATCH_SLOTS == 32, "a mesh's slots fill half a wave");
+    const int t = threadIdx.x, n = blockDim.x;
+    const bool wide = P.st->wide != 0;
+    auto slots_sum = [](int x) {
+#pragma unroll
+        for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+        return x;
+    };
+    const int corners = slots_sum(P.facet_slots ? P.facet_slots[(t & (MATCH_SLOTS - 1)) * MATCH_PAD] : 0);
+    for (int i = t; i < P.B * MATCH_SLOTS; i += n) {  // (whole half waves)
+        const int sum = slots_sum(P.mslots[(size_t)i * MATCH_PAD]), b = i / MATCH_SLOTS;
+        if ((i & (MATCH_SLOTS - 1)) == 0 && !wide) {
+            P.matched[b] = sum;
+            if (P.done && sum > 0) P.done[b] = 1;
+            if (STATE_INTS + b < P.publish_ints) host_store(&P.host_img[STATE_INTS + b], sum);
+        }
+    }
+    for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : reinterpret_cast<const int*>(P.st)[i]);
+    if (t == 0) host_store(P.host_check, P.tell.seq);
+    signal_host(P.tell, t, true);
+}
+__global__ __launch_bounds__(BLOCK) void publish_pairs_kernel(PairPublish P) { publish_pairs(P); }
+
 constexpr u64 ABID_NONE = ~0ull;
 
 // The end of an edge that line 11 of Alg. 2 could add to the other end's cluster: the un-paired
@@ -2169,7 +2895,7 @@ __global__ __launch_bounds__(TRUNC_THREADS) void trunc_mesh_kernel(Keys K, const
                                                                    const int* __restrict__ counts,
                                                                    const int* __restrict__ budgets, int cap, int longer_than,
                                                                    const int* __restrict__ guard, State* st, HostSignal tell,
-                                                                   KeyLimit* __restrict__ limits) {
+                                                                   KeyLimit* __restrict__ limits, PairPublish publish) {
     constexpr int Q = 16, STEP = Q * TRUNC_THREADS, WALK_BITS = 12;
     static_assert(1 << WALK_BITS == 4 * TRUNC_THREADS, "four digits per thread");
     __shared__ u64 list[TRUNC_LIST];
@@ -2180,9 +2906,17 @@ __global__ __launch_bounds__(TRUNC_THREADS) void trunc_mesh_kernel(Keys K, const
     __shared__ u32 n_list, n_below;
     u32* hist = reinterpret_cast<u32*>(hist4);
     const int b = blockIdx.x, tid = threadIdx.x, lane = prim::lane_id();
+    if (b == publish.at) {
+        publish_pairs(publish);
+        return;
+    }
     if (b == 0 && tid == 0) tell_host(tell);
     // (all of these loads are in flight together)
-    const int go = guard ? *guard : 1, n = counts[b], keep = budgets[b], v0 = voff[b], v1 = voff[b + 1];
+    const int go = guard ? *guard : 1, keep = budgets[b], v0 = voff[b], v1 = voff[b + 1];
+    int n = publish.at >= 0 ? publish.mslots[((size_t)b * MATCH_SLOTS + (tid & (MATCH_SLOTS - 1))) * MATCH_PAD] : counts[b];
+    if (publish.at >= 0)
+#pragma unroll
+        for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) n += __shfl_xor(n, d, 64);
     if (limits && tid == 0) limits[b] = KeyLimit{0u, 0u, 0};
     if (go == 0) return;  // queued ahead of the host's look, and the selection was not finished
     if (n <= keep) return;
@@ -2803,16 +3537,22 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                                                          int* __restrict__ htab, int n_clear, u64* __restrict__ vmin0,
                                                          float rcond_min, const int* __restrict__ arep,
                                                          const int* __restrict__ aoff, const int* __restrict__ alist,
-                                                         const int* __restrict__ guard, HostSignal tell) {
+                                                         const int* __restrict__ guard, HostSignal tell, PairPublish publish,
+                                                         int4* __restrict__ from, const u32* __restrict__ rows) {
     if (COUNTS && blockIdx.x == 0 && threadIdx.x == 0) tell_host(tell);
+    if ((int)blockIdx.x == publish.at) {
+        publish_pairs(publish);
+        return;
+    }
     if (guard && *guard == 0) return;  // queued ahead of the host's look, and the selection was not finished
     __shared__ u32 smem[prim::WAVES];
     const int nv = st->nv[cur];
     const int stride = gridDim.x * BLOCK;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     for (int i = g; i < n_clear; i += stride) htab[i] = -1;  // (see final_facets_kernel)
-    for (int b = g; b < B; b += stride)
-        if (matched[b] > 0) done[b] = 1;  // (a mesh without a pair is as it was, whatever the others do)
+    if (publish.at < 0)
+        for (int b = g; b < B; b += stride)
+            if (matched[b] > 0) done[b] = 1;  // (a mesh without a pair is as it was, whatever the others do)
     const int t = threadIdx.x, w64 = prim::wave_id(), lane = prim::lane_id();
     const int tile = blockIdx.x;
     const long long base = (long long)tile * BLOCK * chunks;
@@ -2863,6 +3603,7 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
         if (vmin0) vmin0[nw] = VMIN_NONE;  // (the next round's first bids, see facet_costs_kernel)
         const float4* a = reinterpret_cast<const float4*>(&vin[w]);
         float4 r0 = a[0], r1 = a[1], r2 = a[2], r3 = a[3];
+        if (from) from[nw] = make_int4(w, m, (int)rows[w], m >= 0 ? (int)rows[m] : 0);  // (rounds by rings, see ring_costs_kernel)
         if (m >= 0) {
             vmap[m] = nw;
             const int j0 = ABSORB ? aoff[w] : 0, jend = ABSORB ? aoff[w + 1] : 0;  // this cluster's part of alist (a pair's lower vertex is not the last one)
@@ -3007,7 +3748,7 @@ struct FacetList {
 template <int SEG>
 __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restrict__ fcur, int F, const int* __restrict__ fcount,
                                                              int tile_shift, FacetList L, int* __restrict__ mslots,
-                                                             const int* __restrict__ vmap, const State* st, int cur,
+                                                             const int* __restrict__ before, const int* __restrict__ vmap, const State* st, int cur,
                                                              u32* __restrict__ htab, u32 hmask, int fbits, int B,
                                                              const int* __restrict__ voff, const int* __restrict__ done,
                                                              const int* cid_in, int* cid_out,
@@ -3017,7 +3758,8 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
     const int g = blockIdx.x * BLOCK + threadIdx.x, lane = prim::lane_id();
     const int nv = st->nv[cur];
     const float slots_per_vertex = ((float)hmask + 1.0f) / (float)(nv > 0 ? nv : 1);
-    auto renumbered = [&](const Corners& q) -> Corners {  // (a collapsed facet's corners are -1)
+    auto renumbered = [&](Corners q) -> Corners {  // (a collapsed facet's corners are -1)
+        if (before) q = Corners{before[q.a], before[q.b], before[q.c]};
         if (!vmap) return q;
         const Corners m{vmap[max(q.a, 0)], vmap[max(q.b, 0)], vmap[max(q.c, 0)]};
         return q.a >= 0 ? m : q;

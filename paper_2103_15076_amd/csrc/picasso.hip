@@ -134,6 +134,9 @@ struct picasso_ctx {
     int* joiners() const { return reinterpret_cast<int*>(val32); }  // (free between the edges' sort and the next round)
     int* acand = nullptr;  // per mesh: vertices that could join
     int* arem = nullptr;   // per mesh: budget left after the pairs
+    RingRows ring[2], adj;  // rounds by rings: the rings, by the round's parity, and the neighbours with their costs (see ring_costs_kernel)
+    int* rows_taken = nullptr;  // ... (see RINGS_TAKEN)
+    int4* from = nullptr;   // ... per vertex: the two of the round before that it was made of, and their rows' info
     u32* area_ext = nullptr;  // per mesh: largest facet area and largest complement of one (conv::EXT_SLOTS; zero between calls)
     int64_t kt_calls = 0;           // decimate calls since the option was set
     bool kt_this_call = false;
@@ -264,6 +267,27 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->acand = cv.take<int>(b);
     x->arem = cv.take<int>(b);
     x->area_ext = cv.take<u32>(b * conv::EXT_SLOTS * conv::EXT_PAD);
+    // The rings lie in the sorts' buffers, which rounds by rings do not use (the neighbours' where the facets' planes have been), if these are large enough, as they are where
+    // vertices have five and a half facets or more.
+    const size_t ring_bytes = n * (sizeof(u32) * RING_MAX + sizeof(u32)), region = align_up(h * sizeof(u64)), wanted = ring_bytes + n * 8 + 4096;
+    x->rows_taken = cv.take<int>(RINGS_TAKEN);
+    for (int i = 0; i < 3; ++i) {
+        RingRows& r = i < 2 ? x->ring[i] : x->adj;
+        const size_t bytes = std::max(region, align_up(wanted));
+        char* const own = region < wanted ? cv.take<char>(bytes) : nullptr;
+        char* const at = region < wanted ? own : reinterpret_cast<char*>(i == 0 ? x->key64[0] : i == 1 ? x->key64[1] : x->ekey);
+        Carver in;
+        in.base = at;
+        r.ids = in.take<u32>(n * RING_MAX);
+        r.info = in.take<u32>(n);
+        r.arena_rows = (int)std::min<size_t>((bytes - in.off) / (ROW_ARENAS * ROW_SMALL * sizeof(u64)), (1u << 20) / ROW_ARENAS - 1);
+        r.small = in.take<u64>((size_t)r.arena_rows * ROW_ARENAS * ROW_SMALL);
+        r.large_rows = (int)std::min<size_t>(n / 512 + 64, (1u << 20) - 1);
+        r.large = cv.take<u64>((size_t)r.large_rows * ROW_MAX);
+        r.taken = x->rows_taken ? x->rows_taken + i * (ROW_ARENAS + 1) * MATCH_PAD : nullptr;
+        r.wide = x->st ? &x->st->wide : nullptr;
+    }
+    x->from = cv.take<int4>(n);
     return cv.off;
 }
 
@@ -416,8 +440,9 @@ prim::KeySort<u64> incidence_sort(picasso_ctx* c, int N, int F) {
 // Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
 // before the first round's costs are computed (24 bytes per facet there, 16 needed).
 inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c->ekey); }
-QuadricRows quadric_rows(picasso_ctx* c, const float* d_verts, int N, int F) {
-    return QuadricRows{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F)};
+template <bool RINGS>
+QuadricRows<RINGS> quadric_rows(picasso_ctx* c, const float* d_verts, int N, int F) {
+    return QuadricRows<RINGS>{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F), c->fcur, c->ring[0]};
 }
 
 RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
@@ -448,10 +473,11 @@ bool sort_edges(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, int 
     return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<EdgeKeys>{{c->fcur, S.key_bits / 2}}, distinct_keys(c),
                           c->kt_this_call ? &c->kt : nullptr, round_);
 }
-// Sorts the incidence keys and sums the vertices' quadrics.
+// Sorts the incidence keys and sums the vertices' quadrics (RINGS: leaves their rings, too).
+template <bool RINGS>
 bool sort_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, const float* d_verts, int N, int F) {
     return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<IncidenceKeys>{{c->fcur, incidence_fbits(F)}},
-                          quadric_rows(c, d_verts, N, F), c->kt_this_call ? &c->kt : nullptr, PICASSO_KERNEL_QUADRIC_ROWS << 8,
+                          quadric_rows<RINGS>(c, d_verts, N, F), c->kt_this_call ? &c->kt : nullptr, PICASSO_KERNEL_QUADRIC_ROWS << 8,
                           PICASSO_KERNEL_SORT_INCIDENCE << 8);
 }
 // Both in the same launches.
@@ -459,7 +485,7 @@ bool sort_edges_and_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySor
                                const float* d_verts, int N, int F) {
     c->hist_dirty = false;
     return prim::key_sort(s, I, &E, prim::TwoSources<IncidenceKeys, EdgeKeys>{{c->fcur, incidence_fbits(F)}, {c->fcur, E.key_bits / 2}},
-                          prim::TwoOuts<QuadricRows, prim::DistinctKeys>{quadric_rows(c, d_verts, N, F), distinct_keys(c)});
+                          prim::TwoOuts<QuadricRows<false>, prim::DistinctKeys>{quadric_rows<false>(c, d_verts, N, F), distinct_keys(c)});
 }
 
 // Whether a round of one or several meshes, of at most `edges` edges, keeps a state for each.
@@ -518,14 +544,15 @@ inline int facet_parts(int F, int nv) { return std::max(facet_tiles(F), (nv + 10
 // Where a round's contraction leaves its map of the vertices.  The first round's is the labels of the input vertices at the same time; rounds by
 // facets leave it where the labels are.
 int* round_map(picasso_ctx* c, bool by_facets, int round_) { return by_facets && round_ == 0 ? c->cid : c->vmap; }
-void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, int N, int F) {
+// fresh: the first such round of a call that has had rounds by rings; the facets are the input's, the labels up to date.
+void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, int N, int F, bool fresh) {
     const int grid = prim::xcd_grid(facet_parts(F, N)), par = round_ & 1;
 #define PICASSO_FACET_COSTS(PLACE, TILE, THREADS, FIRST)                                                                              \
     do {                                                                                                                                \
         static_assert((TILE) % (THREADS) == 0, "whole tiles");                                                                          \
         facet_costs_kernel<PLACE, THREADS, (TILE) / (THREADS), FIRST><<<grid, THREADS, 0, s>>>(                                         \
-            c->fcur, F, c->st, cur_, c->vrec[cur_], c->vmin[0], c->vmin[1], c->ecost, round_tab(c, B, round_, cur_), round_map(c, true, round_ - 1), c->done, \
-            c->cid, round_ > 1 ? N : 0, c->opt_rcond_min, round_ > 1 ? c->fcount() : nullptr, c->fcount(), c->nf_slots[par], c->nf_slots[par ^ 1]); \
+            c->fcur, F, c->st, cur_, c->vrec[cur_], c->vmin[0], c->vmin[1], c->ecost, round_tab(c, B, round_, cur_), fresh ? c->cid : round_map(c, true, round_ - 1), c->done, \
+            c->cid, round_ > 1 && !fresh ? N : 0, c->opt_rcond_min, round_ > 1 && !fresh ? c->fcount() : nullptr, c->fcount(), c->nf_slots[par], c->nf_slots[par ^ 1]); \
     } while (0)
 #define PICASSO_FACET_COSTS_TILE(PLACE, TILE, THREADS)                                \
     do {                                                                              \
@@ -542,6 +569,43 @@ void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cu
 #undef PICASSO_FACET_COSTS_PLACE
 #undef PICASSO_FACET_COSTS_TILE
 #undef PICASSO_FACET_COSTS
+}
+
+// A round by rings up to its pairs (see ring_costs_kernel).
+constexpr int SUITOR_WAVES = 8192;  // as many as the chip holds
+void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, int nv, int N, const SelArgs& sa) {
+    const int par = round_ & 1;
+    const RingRows in = c->ring[par ^ 1], out = c->ring[par];
+    {
+        const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round_);
+        const int tiles = (nv + RING_TILE - 1) / RING_TILE, n_labels = round_ > 1 ? N : 0;
+        const int grid = prim::xcd_grid(tiles) + (n_labels + RING_LABELS - 1) / RING_LABELS;
+#define PICASSO_RING_COSTS(PLACE, FIRST)                                                                                                            \
+    ring_costs_kernel<PLACE, FIRST><<<grid, RING_THREADS, 0, s>>>(c->st, nv, c->vrec[cur_], (FIRST) ? out : in, out, c->adj, c->vmin[1], c->vmin[0], \
+                                                                  round_tab(c, B, round_, cur_), c->from, round_map(c, true, round_ - 1), c->cid,  \
+                                                                  n_labels, c->opt_rcond_min, c->nf_slots[par], c->nf_slots[par ^ 1])
+        if (c->opt_placement == PLACE_INVERSE) {
+            if (round_ == 0) PICASSO_RING_COSTS(PLACE_INVERSE, true);
+            else PICASSO_RING_COSTS(PLACE_INVERSE, false);
+        } else {
+            if (round_ == 0) PICASSO_RING_COSTS(PLACE_MEAN, true);
+            else PICASSO_RING_COSTS(PLACE_MEAN, false);
+        }
+#undef PICASSO_RING_COSTS
+    }
+    {
+        const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round_);
+        const int waves = (int)std::min<long long>(((long long)nv + 63) / 64, SUITOR_WAVES), per = (int)(((long long)nv + waves - 1) / waves + 63) / 64 * 64;
+        const int grid = prim::xcd_grid((int)(((long long)nv + (long long)per * prim::WAVES - 1) / ((long long)per * prim::WAVES)));
+        suitor_kernel<<<grid, BLOCK, 0, s>>>(nv, per, c->st, out, c->adj, c->vmin[1], c->vmin[0], in.taken);
+    }
+    const int chunks = prim::compact_chunks_for(nv), tiles = prim::compact_tiles(nv, chunks);
+    switch (chunks) {
+        case 1: pairs_kernel<1><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum); break;
+        case 4: pairs_kernel<4><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum); break;
+        default: pairs_kernel<16><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum);
+    }
+    if (tiles > prim::COMPACT_MAX_SUMMED_TILES) prim::compact_scan_sums(s, nullptr, nv, c->tilesum);
 }
 
 // The distinct edges of a round by facets, for the statistics.  (In front of the selection the sorts' buffers are free but for the costs, which lie
@@ -579,7 +643,7 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     init_kernel<COUNT, SORTED><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
         d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], edges == EDGES_BY_FACETS ? nullptr : c->cid, c->fcur, incidence_fbits(F), digit_count(I),      \
         digit_count(E), edges, E.key_bits / 2, c->st, init, TABLES, planes, c->htab, n_clear, c->vmin[0], c->vmin[1],   \
-        c->mate, c->pcost(), round_tab(c, B, 0, 0))
+        c->mate, c->pcost(), round_tab(c, B, 0, 0), edges == EDGES_BY_FACETS ? c->rows_taken : nullptr)
 #define PICASSO_INIT_EDGES(COUNT, SORTED)                                           \
     do {                                                                            \
         if (B == 1) PICASSO_INIT_TABLES(COUNT, SORTED, OneMesh{tables.target[0]});  \
@@ -687,7 +751,8 @@ int status_from_err_bits(int bits) {
 // by_count: the kernel that counts the survivors releases what the search of one workgroup per mesh leaves beyond its limits.
 template <class Keys>
 int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* voff, int nv_max, int most, int least,
-                const int* counts, const int* budgets, bool by_count, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
+                const int* counts, const int* budgets, bool by_count, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0},
+                const PairPublish& publish = PairPublish{-1}) {
     const int limit = (int)c->opt_trunc_block_max;
     const bool longer = most > limit;
     if (guarded && longer) return PICASSO_ERR_INVALID_ARG;
@@ -699,7 +764,7 @@ int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* 
         if (c->opt_trunc_width) cap = c->opt_trunc_width * TRUNC_THREADS;  // (test hook)
         const bool here = cap <= TRUNC_SMALL_CAP && !by_count;  // (few keys: released by the search itself)
         KeyLimit* limits = here ? nullptr : c->limits;
-        trunc_mesh_kernel<Keys><<<B, TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer_than, guard, c->st, tell, limits);
+        trunc_mesh_kernel<Keys><<<B + (publish.at >= 0 ? 1 : 0), TRUNC_THREADS, 0, s>>>(K, voff, counts, budgets, cap, longer_than, guard, c->st, tell, limits, publish);
         if (!here && !by_count) trunc_release_kernel<Keys><<<grid_for(nv_max), BLOCK, 0, s>>>(K, nv_max, voff, B, c->limits);
     }
     if (longer) {
@@ -722,10 +787,10 @@ int budget_step(picasso_ctx* c, hipStream_t s, const Keys& K, int B, const int* 
     return hipGetLastError() == hipSuccess ? PICASSO_OK : PICASSO_ERR_HIP;
 }
 int pair_budget(picasso_ctx* c, hipStream_t s, const TieBreak& tb, int B, const int* voff, int nv_max, int most, int least,
-                bool by_count, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}) {
+                bool by_count, bool guarded = false, HostSignal tell = HostSignal{nullptr, 0}, const PairPublish& publish = PairPublish{-1}) {
     if (tb.on)
-        return budget_step(c, s, PairKeys<true>{c->pcost(), c->ptie(), c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, by_count, guarded, tell);
-    return budget_step(c, s, PairKeys<false>{c->pcost(), nullptr, c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, by_count, guarded, tell);
+        return budget_step(c, s, PairKeys<true>{c->pcost(), c->ptie(), c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, by_count, guarded, tell, publish);
+    return budget_step(c, s, PairKeys<false>{c->pcost(), nullptr, c->mate}, B, voff, nv_max, most, least, c->matched, c->nrem, by_count, guarded, tell, publish);
 }
 
 // Sub-round k of the selection.  last: it lists the edges it leaves live for the tail.
@@ -916,6 +981,12 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // 233 | 263, 1.2 M 2,550 | 2,091, 1,803 | 1,639.  (The first round could be sorted where the host knew the order; a look at the word in front
     // of a bid's atomic takes longer: 263 -> 287.)
     const bool by_facets = c->opt_shuffle_seed == 0 && !c->opt_absorb && !(stats && c->kt_this_call);
+    // ... and of these by rings (see ring_costs_kernel) where the vertices have about six facets, as on a surface; in calls for statistics, which count the edges of
+    // the facets, by facets.  By facets | by rings, us: lattices of 20 k vertices to a quarter 184 | 147, of 400 k 381 | 307, an icosphere of 164 k 385 | 249, facets permuted, 115 k
+    // 389 | 243, 2.25 M 4,179 | 2,663, vertices as well 407 | 265, 4,928 | 4,106, a flat lattice of 116 k 8,694 | 1,867.  But two-sided lattices (twelve facets a vertex,
+    // whose rings lie in rows) of 40 k 210 | 437, 20 k vertices with 60 k facets of any three of them 375 | 621.
+    bool rings = by_facets && !stats && work && F > 0 && 4ll * F <= 9ll * N && N < RING_VERTICES;
+    bool fresh = false;  // (see launch_facet_costs)
     const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
                           edge_sort(c, N, F, F, 3ll * F).half == incidence_sort(c, N, F).half;
     tm.begin(0, PICASSO_ST_QUADRICS);
@@ -926,7 +997,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         if (together) {
             if (!sort_edges_and_incidences(c, s, edge_sort(c, N, F, F, 3ll * F), I, d_verts, N, F)) return PICASSO_ERR_HIP;
         } else if (F > 0) {
-            if (!sort_incidences(c, s, I, d_verts, N, F)) return PICASSO_ERR_HIP;
+            if (!(rings ? sort_incidences<true>(c, s, I, d_verts, N, F) : sort_incidences<false>(c, s, I, d_verts, N, F))) return PICASSO_ERR_HIP;
         }
     }
     tm.end();
@@ -951,9 +1022,11 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 
         // ---- S1 (+S2): edges and costs
         tm.begin(round, PICASSO_ST_EDGES);
-        if (by_facets) {
+        if (rings) {  // (below: with the selection)
+        } else if (by_facets) {
             const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);
-            launch_facet_costs(c, s, B, round, cur, N, F);
+            launch_facet_costs(c, s, B, round, cur, N, F, fresh);
+            fresh = false;
             compacted = round > 0;
         } else {
             const prim::KeySort<u64> E = edge_sort(c, nv_total, nf_bound, F, round > 0 ? expected_half_edges(H, ne_prev, nv_prev - nv_total) : H);
@@ -962,6 +1035,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);
             launch_unique_cost(c, s, E, H, mt, tb, c->vrec[cur]);
         }
+        const bool was_renumbered = renumbered;
         renumbered = false;
         tm.end();
         if (by_facets && stats && F > 0 && round < PICASSO_STATS_ROUNDS) {
@@ -974,12 +1048,13 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // has looked; it then goes by what the tail leaves in State (go, guard_nv) and does
         // nothing unless it finished the matching.  clear: slots of the facet set to clear on the way.
         // releases: a budget step has left limits that the count applies.
-        auto issue_contract = [&](int n_joined, size_t clear, bool releases, bool guarded, HostSignal tell) {
+        // counted: the tiles' survivors are there already (see pairs_kernel).
+        auto issue_contract = [&](int n_joined, size_t clear, bool releases, bool guarded, HostSignal tell, bool counted = false, PairPublish publish = PairPublish{-1}) {
             const int nxt = cur ^ 1;
             const int* guard = guarded ? &c->st->go : nullptr;
             const int* n_ptr = guarded ? &c->st->guard_nv : nullptr;
-            const bool counts = n_joined == 0 && !releases && nv_total <= CONTRACT_COUNTS_MAX;
-            if (counts) {
+            const bool counts = n_joined == 0 && !releases && nv_total <= CONTRACT_COUNTS_MAX && !counted;
+            if (counts || counted) {
             } else if (n_joined > 0) {
                 prim::compact_count(s, AlivePredT<true>{c->mate, c->arep}, n_ptr, nv_total, c->tilesum);
             } else if (releases && tb.on) {
@@ -994,12 +1069,15 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             }
             const int chunks = prim::compact_chunks_for(nv_total), tiles = prim::compact_tiles(nv_total, chunks);
             const int prefixed = tiles > prim::COMPACT_MAX_SUMMED_TILES;
+            if (publish.at >= 0) publish.at = tiles;
+            const int grid = tiles + (publish.at >= 0 ? 1 : 0);
             static_assert(CONTRACT_COUNTS_MAX <= BLOCK * prim::COMPACT_MAX_SUMMED_TILES, "tiles of one chunk");
 #define PICASSO_CONTRACT(PLACE, ABSORB, COUNTS, RCOND)                                                               \
-    contract_kernel<PLACE, ABSORB, COUNTS><<<tiles, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, round_map(c, by_facets, round), c->st, cur,  \
+    contract_kernel<PLACE, ABSORB, COUNTS><<<grid, BLOCK, 0, s>>>(c->vrec[cur], c->vrec[nxt], c->mate, round_map(c, by_facets, round), c->st, cur,  \
                                                            chunks, c->tilesum, prefixed, B, c->voff[cur],             \
                                                            c->voff[nxt], c->matched, c->done, c->htab, (int)clear, \
-                                                           by_facets ? c->vmin[0] : nullptr, RCOND, c->arep, c->aoff, c->joiners(), guard, tell)
+                                                           by_facets ? c->vmin[0] : nullptr, RCOND, c->arep, c->aoff, c->joiners(), guard, tell, publish, \
+                                                           rings ? c->from : nullptr, c->ring[round & 1].info)
             if (c->opt_placement == PLACE_INVERSE) {
                 if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, false, c->opt_rcond_min);
                 else if (counts) PICASSO_CONTRACT(PLACE_INVERSE, false, true, c->opt_rcond_min);
@@ -1076,6 +1154,35 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         sa.host_check = c->h_pin_dev + c->h_seq_off + SEQ_CHECK_WORD;
         sa.tb = tb;
         int sel_k = 0;
+        bool recount = true;  // the tiles' survivors are still to be counted when the budget step, if any, is done
+        if (rings) {
+            launch_ring_round(c, s, B, round, cur, nv_total, N, sa);
+            const HostSignal done = next_signal(c);
+            PairPublish publish{0, c->st, c->mslots, c->matched, nullptr, B, round > 0 ? c->nf_slots[round & 1] : nullptr, c->h_pin_dev, HDR_STATE_INTS + B, sa.host_check, done};
+            const HostSignal nothing{nullptr, 0};
+            if (ahead_ok && ahead_budget) {
+                publish.at = B;
+                rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_bound, 0, true, true, nothing, publish);
+                if (rc != PICASSO_OK) return rc;
+                issue_contract(0, 0, true, true, nothing);
+            } else if (ahead_ok) {
+                publish.done = c->done;
+                issue_contract(0, 0, false, true, nothing, true, publish);
+            } else {
+                publish_pairs_kernel<<<1, BLOCK, 0, s>>>(publish);
+            }
+            HIP_TRY(c, wait_for_signal(c, s, done));
+            ahead = ahead_ok;
+            recount = false;
+            if (hst->wide) {  // a row did not fit: this round and those behind it by facets
+                rings = false;
+                fresh = round > 0;
+                for (int i = 0; i < 2; ++i) prim::fill_u32_kernel<<<grid_for(2ll * nv_total), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->vmin[i]), 2 * nv_total, ~0u);
+                prim::fill_u32_kernel<<<grid_for(MATCH_SLOTS * MATCH_PAD), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->nf_slots[round & 1]), MATCH_SLOTS * MATCH_PAD, 0u);
+                renumbered = was_renumbered;
+                continue;
+            }
+        }
         // Grid-wide sub-rounds while many edges are live (the live count falls about 3x per
         // sub-round), then the live edges are gathered and one workgroup finishes; the host
         // looks once per batch.
@@ -1095,7 +1202,23 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // candidates queued behind each batch 7.6, so 3.0.
         bool slow = false, queued = false;
         int wide_before = 0;
-        for (;;) {
+        auto check_errors = [&]() -> int {
+            if (!validated) {
+                const int st_err = status_from_err_bits(hst->err);
+                if (st_err != PICASSO_OK) {  // (the flags go back to zero for the next call, see HeaderInit)
+                    prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
+                    return st_err;
+                }
+                validated = true;
+            }
+            if (hst->err & ERR_BIT_INTERNAL) {  // a kernel of the round before has refused its sizes
+                prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
+                return PICASSO_ERR_INTERNAL;
+            }
+            return PICASSO_OK;
+        };
+        if (rings && (rc = check_errors()) != PICASSO_OK) return rc;
+        while (!rings) {
             // live edges fall by about 2.8x, 2.7x, 3.2x, 4x, 5x, ... per sub-round on meshes with varied costs
             static const int decay_x10[] = {28, 27, 32, 40, 50, 60};
             int wide = slow ? 2 * wide_before : 0;
@@ -1135,18 +1258,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                     return PICASSO_ERR_HIP;
                 }
             }
-            if (!validated) {
-                const int st_err = status_from_err_bits(hst->err);
-                if (st_err != PICASSO_OK) {  // (the flags go back to zero for the next call, see HeaderInit)
-                    prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
-                    return st_err;
-                }
-                validated = true;
-            }
-            if (hst->err & ERR_BIT_INTERNAL) {  // a kernel of the round before has refused its sizes
-                prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
-                return PICASSO_ERR_INTERNAL;
-            }
+            if ((rc = check_errors()) != PICASSO_OK) return rc;
             sel_k = hst->sel_k;
             const int live = hst->live[0];
             if (live == 0) {
@@ -1157,7 +1269,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             live_est = live;
         }
         for (int b = 0; b < B; ++b) h_matched[b] = c->h_pin[HDR_STATE_INTS + b];
-        const int nf_now = round == 0 ? F : hst->nh / 3;
+        const int nf_now = round == 0 ? F : hst->nh / 3;  // (rounds by rings: of the rings' entries)
         const int ne_now = by_facets ? (int)(3ll * nf_now / 2) : hst->ne;  // (about)
         nf_bound = std::min(nf_bound, nf_now);
         if (c->n_rounds_noted < NF_ROUND_CAP) {
@@ -1190,6 +1302,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         if (seg_max > 0 && !ahead) {
             // (line 11 reads the pairs before they are counted)
             releases = !c->opt_absorb && seg_min <= c->opt_trunc_block_max;
+            recount = true;
             rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_max, seg_min, releases);
             if (rc != PICASSO_OK) return rc;
         }
@@ -1229,7 +1342,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             const bool last = !work || (c->opt_max_rounds >= 0 && round + 1 >= c->opt_max_rounds);
             const size_t clear = last && slots_clear == 0 ? facet_slots((size_t)nf_bound) : 0;
             tm.begin(round, PICASSO_ST_CONTRACT);
-            issue_contract(n_joined, clear, releases, false, HostSignal{nullptr, 0});
+            issue_contract(n_joined, clear, releases, false, HostSignal{nullptr, 0}, !recount);
             tm.end();
             slots_clear = std::max(slots_clear, clear);
         }
@@ -1262,13 +1375,16 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     const int tile_shift = ceil_log2(facet_tile(F));
     // (null: what a vertex's label is in front of the last contraction is its number; see round_map)
     const int* const labels = by_facets && (round == 0 || (round == 1 && renumbered)) ? nullptr : c->cid;
+    // rounds by rings have left the facets as they came: the labels in front of the last contraction take them there
+    const int* const before = rings && round > 0 ? labels : nullptr;
+    int* const labels_out = !drop ? d_cluster_id : before ? c->arep : c->cid;  // (where the labels are still read: beside them)
     tm.begin(std::max(round - 1, 0), PICASSO_ST_FACETS);
     {
         const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round - 1, renumbered);
 #define PICASSO_FINAL_FACETS(SEG)                                                                                       \
     final_facets_kernel<SEG><<<grid_for(std::max(N, F), 8192), BLOCK, 0, s>>>(                                          \
-        c->fcur, F, fcount, tile_shift, fl, c->mslots, renumbered ? round_map(c, by_facets, round - 1) : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur],     \
-        c->done, labels, drop ? c->cid : d_cluster_id, N, c->vrec[cur], drop ? nullptr : d_verts_out)
+        c->fcur, F, fcount, tile_shift, fl, c->mslots, before, renumbered ? round_map(c, by_facets, round - 1) : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur],     \
+        c->done, labels, labels_out, N, c->vrec[cur], drop ? nullptr : d_verts_out)
         switch (facet_segment(chunks)) {
             case 1: PICASSO_FINAL_FACETS(1); break;
             case 2: PICASSO_FINAL_FACETS(2); break;
@@ -1302,7 +1418,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         const RefPred rp{ref};
         const RefOut ro{c->newid};
         prim::compact(s, rp, rp, ro, &c->st->nv[cur], nv_total, c->tilesum, &c->st->nv_kept);
-        drop_out_kernel<<<out_grid, BLOCK, 0, s>>>(c->vrec[cur], c->fcur, c->cid, c->st, cur, N, d_verts_out, d_facets_out,
+        drop_out_kernel<<<out_grid, BLOCK, 0, s>>>(c->vrec[cur], c->fcur, labels_out, c->st, cur, N, d_verts_out, d_facets_out,
                                                    d_cluster_id, B, c->voff[cur], ref, c->newid, c->matched);
     }
     if (stats) HIP_TRY(c, hipEventRecord(c->ev_total[1], s));
@@ -1374,7 +1490,7 @@ int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts,
         return rc;
     }
     const prim::KeySort<u64> I = incidence_sort(c, N, F);
-    if (F > 0 && !sort_incidences(c, s, I, d_verts, N, F)) return PICASSO_ERR_HIP;
+    if (F > 0 && !sort_incidences<false>(c, s, I, d_verts, N, F)) return PICASSO_ERR_HIP;
     return PICASSO_OK;
 }
 
