@@ -196,13 +196,20 @@ __device__ __forceinline__ Corners load_corners(const int* __restrict__ facets, 
 }
 __device__ __forceinline__ int corner(const Corners& q, int c) { return c == 0 ? q.a : (c == 1 ? q.b : q.c); }
 
+// The same of facets as the caller gives them, where no copy of them is made (rounds by rings): an index that is out of range, of which the host has yet to hear, counts as 0.
+__device__ __forceinline__ int given_vertex(int v, int n_verts) { return (u32)v < (u32)n_verts ? v : 0; }
+__device__ __forceinline__ Corners load_given(const int* __restrict__ facets, size_t f, int n_verts) {
+    const Corners q = load_corners(facets, f);
+    return Corners{given_vertex(q.a, n_verts), given_vertex(q.b, n_verts), given_vertex(q.c, n_verts)};
+}
+
 // Incidence keys of a facet, one per corner: (vertex << fbits) | facet.
 struct IncidenceKeys {
-    const int* fcur;
-    int fbits;
+    const int* facets;
+    int fbits, n_verts;
     static constexpr int PER = 3;
     typedef Corners Raw;
-    __device__ __forceinline__ Corners load(int f) const { return load_corners(fcur, (size_t)f); }
+    __device__ __forceinline__ Corners load(int f) const { return load_given(facets, (size_t)f, n_verts); }
     __device__ __forceinline__ u64 key(const Corners& q, int f, int c) const { return ((u64)(u32)corner(q, c) << fbits) | (u64)(u32)f; }
     __device__ __forceinline__ bool keep(u64) const { return true; }
 };
@@ -323,7 +330,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
                                                      const int* __restrict__ facets, int F, int B,
                                                      const int* __restrict__ voff, const int* __restrict__ foff,
                                                      VRec* __restrict__ vrec, int* __restrict__ cid,
-                                                     int* __restrict__ fcur, int fbits, DigitCount inc, DigitCount edge,
+                                                     int* __restrict__ fcur /* or null */, int fbits, DigitCount inc, DigitCount edge,
                                                      int edges, int vbits, State* st, HeaderInit init, Tables tables,
                                                      float4* __restrict__ planes, int* __restrict__ htab, int n_clear,
                                                      u64* __restrict__ vmin0, u64* __restrict__ vmin1,
@@ -377,7 +384,7 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         if (cid) cid[w] = w;
         if (edges != EDGES_NONE) {
             vmin0[w] = VMIN_NONE;
-            vmin1[w] = VMIN_NONE;
+            if (vmin1) vmin1[w] = VMIN_NONE;
         }
         if (SORTED) {
             mate[w] = -1;
@@ -407,8 +414,8 @@ __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ v
         for (int c = 0; c < 3; ++c) {
             const bool bad = ok && (at[c] < lo || at[c] >= hi);
             if (bad) err |= 1;
-            if (bad || !ok) at[c] = lo;
-            if (ok) fcur[3 * (size_t)f + c] = at[c];
+            if (bad || !ok) at[c] = fcur ? lo : given_vertex(at[c], N);
+            if (ok && fcur) fcur[3 * (size_t)f + c] = at[c];
         }
         // the facet's plane, once per facet, for the vertex quadrics that S0 sums from it
         if (planes && ok) planes[f] = facet_plane(verts, at[0], at[1], at[2]);
@@ -557,27 +564,31 @@ __device__ __forceinline__ void add_plane_quadric(float (&acc)[10], const float4
 }
 
 // The rings of rounds by rings (see ring_costs_kernel): per vertex the facets that have it, each as its other two corners.  Of up to RING_MAX facets that name up to
-// RING_MAX vertices, as mostly, these vertices are a row of 32 bytes (`ids`): facet i's first corner is the i-th of them, its second one that of the number that
-// info gives.  (A ring is found from its vertex alone, most of them in one access.)  Other rings are noted facet by facet (first corner | second corner << 32), up to ROW_SMALL of
-// them in a row of one size, up to ROW_MAX in one of the other.
-// info: vertices | facets << 4 | numbers, three bits each, << 8; of other rings RING_ROWS | facets << 4 | row << 12.
-// Neighbours with their costs lie the same way: of short rings as a row of the costs in `ids`, of others as (cost << 32 | neighbour), info: RING_ROWS | how many << 4 | row << 12.
-constexpr int RING_MAX = 8;
+// RING_MAX vertices, as nearly always, these vertices are noted, RING_ROW of them in a row of 32 bytes (`ids`), the others beside (`more`): facet i's first corner is the i-th of
+// them, its second one that of the number that info gives.  (A ring is found from its vertex alone, most of them in one access.)  Other rings are noted facet by facet (first
+// corner | second corner << 32), up to ROW_SMALL of them in a row of one size, up to ROW_MAX in one of the other.  Scanned surfaces have 0 % of vertices with more than 8
+// facets at first and 3 % once they have been decimated, 0.1 % with more than 10: with eight at most a ladder of four levels of 16 meshes took 1,099 us.
+// info: vertices | facets << 4 | numbers, four bits each, << 8; of other rings RING_ROWS | facets << 4 | row << 12.
+// Neighbours with their costs lie the same way: of short rings as rows of the costs in `ids` and `more`, of others as (cost << 32 | neighbour), info: RING_ROWS | how many << 4 | row << 12.
+constexpr int RING_VERTICES = 1 << 28;  // (rounds by rings take fewer vertices)
+constexpr int RING_MAX = 10, RING_ROW = 8, RING_MORE = RING_MAX - RING_ROW;
 constexpr u32 RING_ROWS = 15;
 constexpr int ROW_LINE = 8, ROW_SMALL = 16, ROW_MAX = 64;
-__device__ __forceinline__ u32 rows_info(int n, u32 row) { return RING_ROWS | ((u32)n << 4) | (row << 12); }
-__device__ __forceinline__ int rows_length(u32 info) { return (int)(info >> 4 & 255u); }
-__device__ __forceinline__ u32 rows_number(u32 info) { return info >> 12; }
-__device__ __forceinline__ bool ring_in_rows(u32 info) { return (info & 15u) == RING_ROWS; }
-__device__ __forceinline__ int ring_ids(u32 info) { return (int)(info & 15u); }  // (of a short ring)
-__device__ __forceinline__ int ring_facets(u32 info) { return (int)(info >> 4 & (ring_in_rows(info) ? 255u : 15u)); }
-__device__ __forceinline__ int ring_second(u32 info, int i) { return (int)(info >> (8 + 3 * i) & 7u); }
+__device__ __forceinline__ u64 rows_info(int n, u32 row) { return RING_ROWS | ((u32)n << 4) | (row << 12); }
+__device__ __forceinline__ int rows_length(u64 info) { return (int)((u32)info >> 4 & 255u); }
+__device__ __forceinline__ u32 rows_number(u64 info) { return (u32)info >> 12; }
+__device__ __forceinline__ u64 ring_info(int vertices, int facets, u64 numbers) { return (u64)((u32)vertices | ((u32)facets << 4)) | (numbers << 8); }
+__device__ __forceinline__ bool ring_in_rows(u64 info) { return ((u32)info & 15u) == RING_ROWS; }
+__device__ __forceinline__ int ring_ids(u64 info) { return (int)((u32)info & 15u); }  // (of a short ring)
+__device__ __forceinline__ int ring_facets(u64 info) { return (int)((u32)info >> 4 & (ring_in_rows(info) ? 255u : 15u)); }
+__device__ __forceinline__ int ring_second(u64 info, int i) { return (int)((u32)(info >> (8 + 4 * i)) & 15u); }
 // Small rows are handed out in parts, each with a counter in a cache line of its own (a line takes an atomic every 11 ns).
 constexpr int ROW_ARENAS = 32, ROW_TRIES = 4;
 static_assert(RINGS_TAKEN == 3 * (ROW_ARENAS + 1) * MATCH_PAD, "a counter each");
 struct RingRows {
     u32* ids;
-    u32* info;
+    u32* more;
+    u64* info;
     u64* small;
     u64* large;
     int* taken;  // [ROW_ARENAS + 1][MATCH_PAD]: small rows in use of each part, then large ones
@@ -586,7 +597,7 @@ struct RingRows {
     __device__ __forceinline__ u64* row(int n, u32 number) const {
         return n <= ROW_SMALL ? small + (size_t)number * ROW_SMALL : large + (size_t)number * ROW_MAX;
     }
-    __device__ __forceinline__ u64* row_of(u32 info_) const { return row(rows_length(info_), rows_number(info_)); }
+    __device__ __forceinline__ u64* row_of(u64 info_) const { return row(rows_length(info_), rows_number(info_)); }
     // A row for n entries; n comes back 0 where there is none.
     __device__ __forceinline__ u32 take_row(int& n) const {
         if (n <= ROW_SMALL) {
@@ -602,101 +613,69 @@ struct RingRows {
         n = 0;
         return 0;
     }
-    __device__ __forceinline__ void load_ids(int v, u32 (&x)[RING_MAX]) const {
-        const uint4* r = reinterpret_cast<const uint4*>(ids + (size_t)v * RING_MAX);
+    // n: how many there are (of a row the first RING_ROW are fetched whatever n is)
+    __device__ __forceinline__ void load_ids(int v, u32 (&x)[RING_MAX], int n) const {
+        const uint4* r = reinterpret_cast<const uint4*>(ids + (size_t)v * RING_ROW);
         const uint4 a = r[0], b = r[1];
         x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
         x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+        x[8] = x[9] = 0;
+        if (n > RING_ROW) {
+            const uint2 c = *reinterpret_cast<const uint2*>(more + (size_t)v * RING_MORE);
+            x[8] = c.x; x[9] = c.y;
+        }
     }
-    __device__ __forceinline__ void store_ids(int v, const u32 (&x)[RING_MAX]) const {
-        uint4* r = reinterpret_cast<uint4*>(ids + (size_t)v * RING_MAX);
+    __device__ __forceinline__ void store_ids(int v, const u32 (&x)[RING_MAX], int n) const {
+        uint4* r = reinterpret_cast<uint4*>(ids + (size_t)v * RING_ROW);
         r[0] = make_uint4(x[0], x[1], x[2], x[3]);
         r[1] = make_uint4(x[4], x[5], x[6], x[7]);
+        if (n > RING_ROW) *reinterpret_cast<uint2*>(more + (size_t)v * RING_MORE) = make_uint2(x[8], x[9]);
+    }
+    __device__ __forceinline__ u32 id(int v, int i) const {
+        return i < RING_ROW ? ids[(size_t)v * RING_ROW + i] : more[(size_t)v * RING_MORE + (i - RING_ROW)];
     }
 };
+static_assert(RING_MORE == 2, "two beside the row");
 // A facet of a ring.
 __device__ __forceinline__ u64 ring_entry(int next, int prev) { return ((u64)(u32)prev << 32) | (u32)next; }
 __device__ __forceinline__ u64 ring_entry_of(const Corners& q, int v) {
     return q.a == v ? ring_entry(q.b, q.c) : q.b == v ? ring_entry(q.c, q.a) : ring_entry(q.a, q.b);
 }
-// The short ring of the first n of these facets, or RING_ROWS where it takes more than RING_MAX vertices.  (On a surface the second corners are the first ones in
+// The short ring of the first n of these facets, or rows_info(0, 0) where it takes more than RING_MAX vertices.  (On a surface the second corners are the first ones in
 // another order, but for open edges and facets wound the other way round.)
-__device__ __forceinline__ u32 make_ring(const u64 (&e)[RING_MAX], int n, u32 (&id)[RING_MAX]) {
+template <int N>
+__device__ __forceinline__ u64 make_ring(const u64 (&e)[N], int n, u32 (&id)[RING_MAX]) {
 #pragma unroll
-    for (int k = 0; k < RING_MAX; ++k) id[k] = k < n ? (u32)e[k] : ~0u;
-    u32 seconds = 0, missing = 0;
+    for (int k = 0; k < RING_MAX; ++k) id[k] = k < N && k < n ? (u32)e[k < N ? k : 0] : ~0u;
+    u64 seconds = 0;
+    u32 missing = 0;
 #pragma unroll
-    for (int i = 0; i < RING_MAX; ++i) {
+    for (int i = 0; i < N; ++i) {
         const u32 q = (u32)(e[i] >> 32);
         u32 at = RING_MAX;
 #pragma unroll
-        for (int k = RING_MAX - 1; k >= 0; --k) at = id[k] == q ? (u32)k : at;
+        for (int k = N - 1; k >= 0; --k) at = id[k] == q ? (u32)k : at;
         missing |= i < n && at == RING_MAX ? 1u << i : 0u;
-        seconds |= (at & 7u) << (3 * i);
+        seconds |= (u64)at << (4 * i);
     }
     int m = n;
     while (missing != 0 && m < RING_MAX) {
         u32 q = 0;
 #pragma unroll
-        for (int i = RING_MAX - 1; i >= 0; --i) q = missing >> i & 1u ? (u32)(e[i] >> 32) : q;
+        for (int i = N - 1; i >= 0; --i) q = missing >> i & 1u ? (u32)(e[i] >> 32) : q;
 #pragma unroll
         for (int k = 0; k < RING_MAX; ++k) id[k] = k == m ? q : id[k];
 #pragma unroll
-        for (int i = 0; i < RING_MAX; ++i)
+        for (int i = 0; i < N; ++i)
             if ((missing >> i & 1u) && (u32)(e[i] >> 32) == q) {
-                seconds = (seconds & ~(7u << (3 * i))) | ((u32)m << (3 * i));
+                seconds = (seconds & ~(15ull << (4 * i))) | ((u64)(u32)m << (4 * i));
                 missing &= ~(1u << i);
             }
         ++m;
     }
-    return missing != 0 ? RING_ROWS : (u32)m | ((u32)n << 4) | (seconds << 8);
+    return missing != 0 ? rows_info(0, 0) : ring_info(m, n, seconds);
 }
 
-// The same where facets are wound both ways round, which puts vertices among the first corners twice and others not at all (or for any other reason there are too many):
-// the ring in the order in which they follow one another around the vertex, each from the vertex that it shares with the one in front of it, or RING_ROWS.  A
-// walk goes on from a vertex by the first or the last facet that has it, whichever it has not come by, and has met them all if they are n different ones; one that is
-// stuck before has come to an end of an open fan, if there is one: the second goes from there.  (Vertices and facets' numbers in one word: RING_VERTICES.)
-constexpr int RING_VERTICES = 1 << 29;  // rounds by rings take fewer vertices than this
-__device__ __forceinline__ u32 order_ring(const u64 (&e)[RING_MAX], int n, u32 (&id)[RING_MAX]) {
-    constexpr u32 NONE = ~0u;
-    u32 p[RING_MAX], q[RING_MAX];
-#pragma unroll
-    for (int j = 0; j < RING_MAX; ++j) {
-        p[j] = j < n ? (u32)e[j] << 3 | j : NONE;
-        q[j] = j < n ? (u32)(e[j] >> 32) << 3 | j : NONE;
-    }
-    const u32 all = (1u << n) - 1u;
-    u32 start = p[0] >> 3, at = start, met = 0;
-    for (int turn = 0; turn < 2 && met != all; ++turn) {
-        u32 came_by = RING_MAX;
-        start = at;
-        met = 0;
-#pragma unroll
-        for (int s = 0; s < RING_MAX; ++s) {
-            id[s] = at;
-            u32 lo = NONE, hi = NONE;
-#pragma unroll
-            for (int j = 0; j < RING_MAX; ++j) {
-                hi = p[j] == (at << 3 | j) ? q[j] : hi;
-                hi = q[j] == (at << 3 | j) ? p[j] : hi;
-            }
-#pragma unroll
-            for (int j = RING_MAX - 1; j >= 0; --j) {
-                lo = p[j] == (at << 3 | j) ? q[j] : lo;
-                lo = q[j] == (at << 3 | j) ? p[j] : lo;
-            }
-            const u32 on = (lo & 7u) == came_by ? hi : lo;
-            const bool stuck = on == NONE || (on & 7u) == came_by || (met >> (on & 7u) & 1u) != 0;
-            met |= stuck ? 0u : 1u << (on & 7u);
-            came_by = stuck ? came_by : on & 7u;
-            at = stuck ? at : on >> 3;
-        }
-    }
-    constexpr u32 NEXT = 1u | 2u << 3 | 3u << 6 | 4u << 9 | 5u << 12 | 6u << 15 | 7u << 18;
-    if (met != all) return RING_ROWS;
-    if (at == start) return (u32)n | ((u32)n << 4) | ((NEXT & ~(7u << (3 * (n - 1)))) << 8);  // (the last one leads to the first vertex)
-    return n < RING_MAX ? (u32)(n + 1) | ((u32)n << 4) | (NEXT << 8) : RING_ROWS;
-}
 // RINGS: the vertex's ring (see ring_costs_kernel) is left as well, from the corners of the facets.
 template <bool RINGS>
 struct QuadricRows {
@@ -704,7 +683,7 @@ struct QuadricRows {
     const float* verts;
     const float4* planes;
     int N, fbits;
-    const int* fcur;
+    const int* facets;
     RingRows ring;
     template <int THREADS, int ITEMS>
     struct Lds {
@@ -737,45 +716,37 @@ struct QuadricRows {
     }
     // The ring of a group that a lane has sorted, in any order of its facets.  (By itself, behind the quadrics of all groups: together they take 140 registers.)
     template <int G, typename LK>
-    __device__ __forceinline__ u32 ring_of_group(const prim::Bucket& b, const LK* key, int g, int v) const {
-        u32 info = 0;
-        u64* row = nullptr;
-        if (G > RING_MAX) {
+    __device__ __forceinline__ u64 ring_of_group(const prim::Bucket& b, const LK* key, int g, int v) const {
+        if constexpr (G <= RING_MAX) {
+            u64 e[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j) e[j] = j < g ? ring_entry_of(load_given(facets, b.item(key[j], fbits), N), v) : 0ull;
+            return leave_ring(v, e, g);
+        } else {
             const u32 number = ring.take_row(g);
-            info = rows_info(g, number);
-            row = ring.row(g, number);
+            u64* const row = ring.row(g, number);
+#pragma unroll 8
+            for (int j = 0; j < g; ++j) row[j] = ring_entry_of(load_given(facets, b.item(key[j], fbits), N), v);
+            return rows_info(g, number);
         }
-#pragma unroll
-        for (int j0 = 0; j0 < G; j0 += 8) {
-            u64 e[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                e[j] = j0 + j < g ? ring_entry_of(load_corners(fcur, b.item(key[j0 + j], fbits)), v) : 0ull;
-            if (G <= RING_MAX) info = leave_ring(v, e, g);
-            else
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (j0 + j < g) row[j0 + j] = e[j];
-        }
-        return info;
     }
-    // the ring of up to eight facets
-    __device__ __forceinline__ u32 leave_ring(int v, const u64 (&e)[8], int g) const {
+    // the ring of up to N facets
+    template <int N>
+    __device__ __forceinline__ u64 leave_ring(int v, const u64 (&e)[N], int g) const {
         u32 id[RING_MAX];
-        u32 info = make_ring(e, g, id);
-        if (info == RING_ROWS) info = order_ring(e, g, id);
-        if (info != RING_ROWS) {
-            ring.store_ids(v, id);
+        const u64 info = make_ring(e, g, id);
+        if (!ring_in_rows(info)) {
+            ring.store_ids(v, id, ring_ids(info));
             return info;
         }
         const u32 number = ring.take_row(g);
         u64* const row = ring.row(g, number);
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+        for (int j = 0; j < N; ++j)
             if (j < g) row[j] = e[j];
         return rows_info(g, number);
     }
-    __device__ __forceinline__ void write(int v, const float (&acc)[10], u32 info) const {
+    __device__ __forceinline__ void write(int v, const float (&acc)[10], u64 info) const {
         write_vertex_record(vrec, verts, v, acc);
         if constexpr (RINGS) ring.info[v] = info;
     }
@@ -791,7 +762,7 @@ struct QuadricRows {
                 lds.gcnt[atomicAdd(&lds.nlong, 1u)] = (u32)gi;
                 continue;
             }
-            if (g > GROUP_SHORT) add_group<GROUP_LANE>(acc, b, lds.skey + gs, g);
+            if (__any(g > GROUP_SHORT)) add_group<GROUP_LANE>(acc, b, lds.skey + gs, g);  // (one of the two for the wave, not one after the other)
             else add_group<GROUP_SHORT>(acc, b, lds.skey + gs, g);
             write_vertex_record(vrec, verts, lo + gi, acc);
         }
@@ -799,7 +770,8 @@ struct QuadricRows {
             for (int gi = t; gi < n; gi += THREADS) {
                 const int gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
                 if (g > GROUP_LANE) continue;
-                if (g > GROUP_SHORT) ring.info[lo + gi] = ring_of_group<GROUP_LANE>(b, lds.skey + gs, g, lo + gi);
+                if (g > RING_MAX) ring.info[lo + gi] = ring_of_group<GROUP_LANE>(b, lds.skey + gs, g, lo + gi);
+                else if (__any(g > GROUP_SHORT)) ring.info[lo + gi] = ring_of_group<RING_MAX>(b, lds.skey + gs, g, lo + gi);
                 else ring.info[lo + gi] = ring_of_group<GROUP_SHORT>(b, lds.skey + gs, g, lo + gi);
             }
         __syncthreads();
@@ -813,7 +785,7 @@ struct QuadricRows {
                 n = __shfl(n, 0, 64);
                 number = (u32)__shfl((int)number, 0, 64);
                 u64* const row = ring.row(n, number);
-                for (int j = lane; j < n; j += 64) row[j] = ring_entry_of(load_corners(fcur, b.item(lds.skey[gs + j], fbits)), lo + gi);
+                for (int j = lane; j < n; j += 64) row[j] = ring_entry_of(load_given(facets, b.item(lds.skey[gs + j], fbits), N), lo + gi);
             }
             if (lane == 0) {
                 float acc[10] = {};
@@ -894,23 +866,18 @@ struct QuadricRows {
                 write_vertex_record(vrec, verts, v, acc);
                 if constexpr (RINGS) {
                     int n_ring = end - hp;
-                    u32 info = 0;
-                    u64* row = nullptr;
-                    if (n_ring > RING_MAX) {
+                    u64 info;
+                    if (n_ring <= RING_MAX) {
+                        u64 e[RING_MAX];
+#pragma unroll
+                        for (int j = 0; j < RING_MAX; ++j)
+                            e[j] = j < n_ring ? ring_entry_of(load_given(facets, b.item(key_at(hp + j), fbits), N), v) : 0ull;
+                        info = leave_ring(v, e, n_ring);
+                    } else {
                         const u32 number = ring.take_row(n_ring);
+                        u64* const row = ring.row(n_ring, number);
                         info = rows_info(n_ring, number);
-                        row = ring.row(n_ring, number);
-                    }
-                    for (int j0 = hp; j0 < hp + n_ring; j0 += 8) {
-                        u64 e[8];
-#pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            e[j] = j0 + j < end ? ring_entry_of(load_corners(fcur, b.item(key_at(j0 + j), fbits)), v) : 0ull;
-                        if (n_ring <= RING_MAX) info = leave_ring(v, e, n_ring);
-                        else
-#pragma unroll
-                            for (int j = 0; j < 8; ++j)
-                                if (j0 + j < end) row[j0 + j - hp] = e[j];
+                        for (int j = 0; j < n_ring; ++j) row[j] = ring_entry_of(load_given(facets, b.item(key_at(hp + j), fbits), N), v);
                     }
                     ring.info[v] = info;
                 }
@@ -2343,8 +2310,8 @@ constexpr int RING_LABELS = 4 * RING_THREADS;  // labels of one of the workgroup
 template <int PLACE, bool FIRST>
 __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int nv, const VRec* __restrict__ vrec, RingRows in, RingRows out,
                                                                   RingRows adj, u64* __restrict__ first, u64* __restrict__ bids, RoundTab R,
-                                                                  const int4* __restrict__ from, const int* __restrict__ vmap,
-                                                                  int* __restrict__ cid, int n_labels, float rcond_min,
+                                                                  const int2* __restrict__ from, const ulonglong2* __restrict__ from_info,
+                                                                  const int* __restrict__ vmap, int* __restrict__ cid, int n_labels, float rcond_min,
                                                                   int* __restrict__ facet_slots, int* __restrict__ facet_next) {
     __shared__ MeshFlags M;
     constexpr int HALF = RING_MAX / 2;
@@ -2378,11 +2345,14 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         __builtin_amdgcn_wave_barrier();
     };
-    u32 info, id[RING_MAX];
-    int4 two = make_int4(0, -1, 0, 0);
+    u64 info;
+    u32 id[RING_MAX];
+    int2 two = make_int2(0, -1);
+    ulonglong2 two_info = make_ulonglong2(0, 0);
     VertexWords own;
     if constexpr (!FIRST) {
         two = from[v];
+        two_info = from_info[v];
         if (blockIdx.x == 0) round_begin_block(R, st);
         if (t == 0) facets = 0;
     }
@@ -2391,13 +2361,13 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
     own = load_vertex(vrec, v);
     if constexpr (FIRST) {
         info = in.info[v];
-        in.load_ids(v, id);  // (whatever its row holds)
+        in.load_ids(v, id, ring_in_rows(info) ? 0 : ring_ids(info));
     } else {
         // the facets of the two it was made of, in the new numbering, without those whose corners have met
-        const u32 mine = (u32)(half ? two.w : two.z), theirs = (u32)(half ? two.z : two.w);
+        const u64 mine = half ? two_info.y : two_info.x, theirs = half ? two_info.x : two_info.y;
         const bool short_rings = !ring_in_rows(mine) && !ring_in_rows(theirs);
         u32 x[RING_MAX], y[RING_MAX];
-        in.load_ids(half ? max(two.y, 0) : two.x, x);
+        in.load_ids(half ? max(two.y, 0) : two.x, x, ring_in_rows(mine) ? 0 : ring_ids(mine));
         // Rings go either way round; where the vertex that follows the other one is the same in both, the second is taken backwards (else first corners are met twice).
         const u32 other = (u32)(half ? two.x : two.y);
         u32 follows = x[0], at = 0;
@@ -2409,13 +2379,14 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         const bool backwards = half != 0 && of_pair(follows) == follows;
         const int n_ids = short_rings ? ring_ids(mine) : 0, n_mine = short_rings ? ring_facets(mine) : 0;
 #pragma unroll
-        for (int j = 0; j < RING_MAX; ++j) x[j] = (u32)vmap[j < n_ids ? x[j] : 0u];
+        for (int j = 0; j < RING_MAX; ++j)
+            if (j < RING_ROW || j < n_ids) x[j] = (u32)vmap[j < n_ids ? x[j] : 0u];
         u32* const ids = reinterpret_cast<u32*>(stage) + lane;
 #pragma unroll
         for (int j = 0; j < RING_MAX; ++j) ids[j * 64] = x[j];
         in_order();
 #pragma unroll
-        for (int j = 0; j < RING_MAX; ++j) y[j] = ids[ring_second(mine, j) * 64];
+        for (int j = 0; j < RING_MAX; ++j) y[j] = ids[min(ring_second(mine, j), RING_MAX - 1) * 64];  // (of facets it has not: any number)
         in_order();
         u32 ok = 0;
 #pragma unroll
@@ -2430,15 +2401,19 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
                 facet[place * 32] = ring_entry((int)(backwards ? y[j] : x[j]), (int)(backwards ? x[j] : y[j]));
         }
         in_order();
-        info = RING_ROWS;
+        info = rows_info(0, 0);
         if (short_rings && n <= RING_MAX) {
-            u64 e[RING_MAX];
+            auto make = [&](auto size) {
+                constexpr int N = decltype(size)::value;
+                u64 e[N];
 #pragma unroll
-            for (int j = 0; j < RING_MAX; ++j) e[j] = facet[j * 32];
-            info = make_ring(e, n, id);
-            if (info == RING_ROWS) info = order_ring(e, n, id);
-            if (lead && info != RING_ROWS) {
-                out.store_ids(w, id);
+                for (int j = 0; j < N; ++j) e[j] = facet[j * 32];
+                info = make_ring(e, n, id);
+            };
+            if (__any(n > RING_ROW)) make(std::integral_constant<int, RING_MAX>());  // (one of the two for the wave, not one after the other)
+            else make(std::integral_constant<int, RING_ROW>());
+            if (lead && !ring_in_rows(info)) {
+                out.store_ids(w, id, ring_ids(info));
                 out.info[w] = info;
             }
         }
@@ -2456,29 +2431,33 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
     if (n > 0) {
         u32 x[HALF], cost[HALF];  // every other neighbour
         u64 best = VMIN_NONE;
-        VertexWords X[HALF];
 #pragma unroll
         for (int j = 0; j < HALF; ++j) {
             x[j] = 2 * j + half < n ? id[2 * j + half] : (u32)v;
             cost[j] = PAIR_NONE;
         }
+        auto evaluate = [&](auto from_j, auto to_j) {  // (their records in flight together)
+            constexpr int J0 = decltype(from_j)::value, J1 = decltype(to_j)::value;
+            VertexWords X[J1 - J0];
 #pragma unroll
-        for (int j = 0; j < HALF; ++j)
-            if (j + 1 < HALF || n > 2 * j) X[j] = load_vertex(vrec, (int)x[j]);
+            for (int j = J0; j < J1; ++j) X[j - J0] = load_vertex(vrec, (int)x[j]);
 #pragma unroll
-        for (int j = 0; j < HALF; ++j)
-            if (j + 1 < HALF || n > 2 * j) {
-                cost[j] = neighbour(v, own, (int)x[j], X[j]);
+            for (int j = J0; j < J1; ++j) {
+                cost[j] = neighbour(v, own, (int)x[j], X[j - J0]);
                 const u64 key = x[j] == (u32)v ? VMIN_NONE : ((u64)cost[j] << 32) | x[j];
                 best = key < best ? key : best;
             }
+        };
+        evaluate(std::integral_constant<int, 0>(), std::integral_constant<int, 3>());  // (a surface's vertices have six)
+        if (n > 6) evaluate(std::integral_constant<int, 3>(), std::integral_constant<int, HALF>());
         const u64 others = of_pair(best);
         best = others < best ? others : best;
         // the costs in the order of the neighbours: each lane writes half of them
-        static_assert(HALF == 4, "two costs of each lane to a half");
+        static_assert(RING_ROW == 8 && HALF == 5, "two costs of each lane to a half of the row, one beside it");
         const u32 s0 = of_pair(half ? cost[0] : cost[2]), s1 = of_pair(half ? cost[1] : cost[3]);
-        uint4* const row = reinterpret_cast<uint4*>(adj.ids + (size_t)v * RING_MAX) + half;
+        uint4* const row = reinterpret_cast<uint4*>(adj.ids + (size_t)v * RING_ROW) + half;
         *row = half ? make_uint4(s0, cost[2], s1, cost[3]) : make_uint4(cost[0], s0, cost[1], s1);
+        if (n > RING_ROW) adj.more[(size_t)v * RING_MORE + half] = cost[HALF - 1];
         if (lead) bid(v, best);
     } else if (lead && !in_rows) {
         first[v] = VMIN_NONE;
@@ -2496,7 +2475,8 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         }
         const int from_lane = max(owner, 0), u = __shfl(v, from_lane, 64), its_active = __shfl(active ? 1 : 0, from_lane, 64);
         const bool on = owner >= 0, counts = on && its_active != 0;
-        const int4 pair = make_int4(__shfl(two.x, from_lane, 64), __shfl(two.y, from_lane, 64), __shfl(two.z, from_lane, 64), __shfl(two.w, from_lane, 64));
+        const int2 pair = make_int2(__shfl(two.x, from_lane, 64), __shfl(two.y, from_lane, 64));
+        const ulonglong2 pair_info = make_ulonglong2(__shfl(two_info.x, from_lane, 64), __shfl(two_info.y, from_lane, 64));
         u64* const facet = stage + group * ROW_MAX;
         const u32 group_mask = (1u << RING_GROUP) - 1u;
         const int group_lead = lane & ~(RING_GROUP - 1);
@@ -2510,7 +2490,7 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         };
         int k = 0;  // facets there are
         if constexpr (FIRST) {
-            const u32 row = (u32)__shfl((int)info, from_lane, 64);
+            const u64 row = __shfl(info, from_lane, 64);
             k = on ? rows_length(row) : 0;
             const u64* const of = in.row_of(row);
             for (int i = sub; i < k; i += RING_GROUP) facet[i] = of[i];
@@ -2518,16 +2498,15 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
 #pragma unroll 1
             for (int h = 0; h < 2; ++h) {
                 const int src = h ? pair.y : pair.x;
-                const u32 row = (u32)(h ? pair.w : pair.z);
+                const u64 row = h ? pair_info.y : pair_info.x;
                 const int count = on && src >= 0 ? ring_facets(row) : 0;
                 for (int i0 = 0; __any(i0 < count); i0 += RING_GROUP) {
                     const int i = i0 + sub;
                     bool ok = i < count;
                     u64 e = 0;
                     if (ok) {
-                        const u32* const of = in.ids + (size_t)src * RING_MAX;
                         if (ring_in_rows(row)) e = in.row_of(row)[i];
-                        else e = ring_entry((int)of[i], (int)of[ring_second(row, i)]);
+                        else e = ring_entry((int)in.id(src, i), (int)in.id(src, ring_second(row, i)));
                     }
                     const int a = vmap[ok ? (u32)e : 0u], b = vmap[ok ? (u32)(e >> 32) : 0u];
                     ok = ok && a != u && b != u && a != b;
@@ -2539,47 +2518,94 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
             }
         }
         in_order();
-        if constexpr (!FIRST) {
-            u32 number;
-            group_row(out, k, number);  // (more than ROW_MAX do not fit)
-            u64* const row = out.row(k, number);
-            for (int i = sub; i < k; i += RING_GROUP) row[i] = facet[i];
-            if (on && sub == 0) out.info[u] = rows_info(k, number);
-        }
-        if (sub == 0) n_facets += k;
-        // its neighbours: the facets' first other corners, and the second ones that are no facet's first
+        if (sub == 0) n_facets += min(k, ROW_MAX);
         const VertexWords U = load_vertex(vrec, u);
-        const int fits = counts ? k : 0;
-        u32 only = 0;  // of the lane's facets, one in every turn
-        int m = fits;
-        for (int i0 = 0, turn = 0; __any(i0 < fits); i0 += RING_GROUP, ++turn) {
-            const bool ok = i0 + sub < fits;
-            const int b = ok ? (int)(u32)(facet[i0 + sub] >> 32) : u;
-            bool is = b != u;
-            for (int j = 0; j < fits; ++j) is = is && (int)(u32)facet[j] != b;
-            only |= is ? 1u << turn : 0u;
-            m += __popc(of_group(is));
-        }
-        u32 number;
-        group_row(adj, m, number);
-        u64* const row = adj.row(m, number);
         u64 best = VMIN_NONE;
-        int place0 = fits;
-        for (int i0 = 0, turn = 0; __any(m > 0 && i0 < fits); i0 += RING_GROUP, ++turn) {
-            const int i = i0 + sub;
-            const bool ok = m > 0 && i < fits, is = ok && (only >> turn & 1u);
-            const u64 e = ok ? facet[i] : 0;
-            const int a = ok ? (int)(u32)e : u, b = is ? (int)(u32)(e >> 32) : u;
-            const u64 key = ((u64)neighbour(u, U, a, load_vertex(vrec, a)) << 32) | (u32)a;
-            if (ok) row[i] = key;
-            if (a != u && key < best) best = key;
-            const u32 more = of_group(is);
-            if (is) {
-                const u64 key_b = ((u64)neighbour(u, U, b, load_vertex(vrec, b)) << 32) | (u32)b;
-                row[place0 + __popc(more & ((1u << sub) - 1u))] = key_b;
-                if (key_b < best) best = key_b;
+        // A short ring after all, if the facets follow one another around the vertex (where some are wound the other way round, first corners are met twice and others not at
+        // all): a lane a facet, a walk goes on from a vertex by one not yet taken that has it.  One that is stuck has come to an end of an open fan, if there is one: the
+        // second walk goes from there.
+        const u64 mine = sub < k && k <= RING_MAX ? facet[sub] : 0;
+        const u32 mine_p = (u32)mine, mine_q = (u32)(mine >> 32);
+        u32 begin = (u32)facet[0], at = begin, my_first = 0;
+        int my_step = -1, steps = 0;
+        for (int turn = 0; turn < 2 && __any(k <= RING_MAX && steps != k); ++turn) {
+            if (k <= RING_MAX && steps == k) continue;  // (this group is done)
+            begin = at;
+            my_step = -1;
+            steps = 0;
+            for (int step = 0; step < RING_MAX; ++step) {
+                const u32 has = of_group(my_step < 0 && sub < k && k <= RING_MAX && (mine_p == at || mine_q == at));
+                if (has == 0) break;
+                const int j = __ffs((int)has) - 1;
+                if (sub == j) {
+                    my_step = step;
+                    my_first = at;
+                }
+                at ^= (u32)__shfl((int)(mine_p ^ mine_q), group_lead + j, 64);
+                ++steps;
             }
-            place0 += __popc(more);
+        }
+        const int n_ids = at == begin ? k : k + 1;
+        const bool is_short = on && k > 0 && k <= RING_MAX && steps == k && n_ids <= RING_MAX;
+        in_order();
+        u32* const ids = reinterpret_cast<u32*>(facet);  // (of a short ring: in the facets' place)
+        if (is_short) {
+            if (my_step >= 0) ids[my_step] = my_first;
+            if (sub == 0 && n_ids > k) ids[k] = at;
+        }
+        in_order();
+        if (is_short && sub < n_ids) {
+            constexpr u64 NEXT = 0xA987654321ull;
+            const u32 x = ids[sub];
+            (sub < RING_ROW ? out.ids[(size_t)u * RING_ROW + sub] : out.more[(size_t)u * RING_MORE + sub - RING_ROW]) = x;
+            if (sub == 0) out.info[u] = ring_info(n_ids, k, n_ids > k ? NEXT : NEXT & ~(15ull << (4 * (k - 1))));  // (the last one of a closed fan leads to the first vertex)
+            if (counts) {
+                const u32 cost = neighbour(u, U, (int)x, load_vertex(vrec, (int)x));
+                (sub < RING_ROW ? adj.ids[(size_t)u * RING_ROW + sub] : adj.more[(size_t)u * RING_MORE + sub - RING_ROW]) = cost;
+                if (x != (u32)u) best = ((u64)cost << 32) | x;
+            }
+        }
+        u32 number = 0;
+        int fits = 0, m = 0;
+        if (__any(on && !is_short)) {
+            // ... or in a row
+            if constexpr (!FIRST) {
+                if (is_short) k = 0;
+                group_row(out, k, number);  // (more than ROW_MAX do not fit)
+                u64* const row = out.row(k, number);
+                for (int i = sub; i < k; i += RING_GROUP) row[i] = facet[i];
+                if (on && !is_short && sub == 0) out.info[u] = rows_info(k, number);
+            }
+            // its neighbours: the facets' first corners, and the second ones that are no facet's first
+            m = fits = counts && !is_short ? k : 0;
+            u32 only = 0;  // of the lane's facets, one in every turn
+            for (int i0 = 0, turn = 0; __any(i0 < fits); i0 += RING_GROUP, ++turn) {
+                const bool ok = i0 + sub < fits;
+                const int b = ok ? (int)(u32)(facet[i0 + sub] >> 32) : u;
+                bool is = b != u;
+                for (int j = 0; j < fits; ++j) is = is && (int)(u32)facet[j] != b;
+                only |= is ? 1u << turn : 0u;
+                m += __popc(of_group(is));
+            }
+            group_row(adj, m, number);
+            u64* const row = adj.row(m, number);
+            int place0 = fits;
+            for (int i0 = 0, turn = 0; __any(m > 0 && i0 < fits); i0 += RING_GROUP, ++turn) {
+                const int i = i0 + sub;
+                const bool ok = m > 0 && i < fits, is = ok && (only >> turn & 1u);
+                const u64 e = ok ? facet[i] : 0;
+                const int a = ok ? (int)(u32)e : u, b = is ? (int)(u32)(e >> 32) : u;
+                const u64 key = ((u64)neighbour(u, U, a, load_vertex(vrec, a)) << 32) | (u32)a;
+                if (ok) row[i] = key;
+                if (a != u && key < best) best = key;
+                const u32 more = of_group(is);
+                if (is) {
+                    const u64 key_b = ((u64)neighbour(u, U, b, load_vertex(vrec, b)) << 32) | (u32)b;
+                    row[place0 + __popc(more & ((1u << sub) - 1u))] = key_b;
+                    if (key_b < best) best = key_b;
+                }
+                place0 += __popc(more);
+            }
         }
 #pragma unroll
         for (int d = RING_GROUP / 2; d > 0; d >>= 1) {
@@ -2587,7 +2613,7 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
             best = other < best ? other : best;
         }
         if (on && sub == 0) {
-            adj.info[u] = rows_info(m, number);
+            if (!is_short) adj.info[u] = rows_info(m, number);
             bid(u, best);
         }
         in_order();
@@ -2657,15 +2683,16 @@ __global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, State* s
         }
         if (!__any(busy)) break;
         if (fetch) {
-            const u32 info = ring.info[u];
+            const u64 info = ring.info[u];
             u32 id[RING_MAX], cost[RING_MAX];
-            ring.load_ids(u, id);
-            adj.load_ids(u, cost);
+            ring.load_ids(u, id, 0);
+            adj.load_ids(u, cost, 0);
             m = ring_ids(info);
 #pragma unroll
             for (int j = 0; j < ROW_LINE; ++j) row[j] = ((u64)cost[j] << 32) | id[j];
+            longer = nullptr;
             if (ring_in_rows(info)) {
-                const u32 with = adj.info[u];
+                const u64 with = adj.info[u];
                 longer = adj.row_of(with);
                 m = rows_length(with);
                 if (m > 0) load_line(row, longer);
@@ -2689,11 +2716,17 @@ __global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, State* s
         consider(row, 0);
         for (int i0 = ROW_LINE; __any(busy && i0 < m); i0 += ROW_LINE) {
             u64 x[ROW_LINE];
-            if (busy && i0 < m) {
-                load_line(x, longer + i0);
-            } else {
 #pragma unroll
-                for (int j = 0; j < ROW_LINE; ++j) x[j] = VMIN_NONE;
+            for (int j = 0; j < ROW_LINE; ++j) x[j] = VMIN_NONE;
+            if (busy && i0 < m) {
+                if (longer) {
+                    load_line(x, longer + i0);
+                } else {
+                    const uint2 id = *reinterpret_cast<const uint2*>(ring.more + (size_t)u * RING_MORE);
+                    const uint2 cost = *reinterpret_cast<const uint2*>(adj.more + (size_t)u * RING_MORE);
+                    x[0] = ((u64)cost.x << 32) | id.x;
+                    x[1] = ((u64)cost.y << 32) | id.y;
+                }
             }
             consider(x, i0);
         }
@@ -3538,7 +3571,8 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
                                                          float rcond_min, const int* __restrict__ arep,
                                                          const int* __restrict__ aoff, const int* __restrict__ alist,
                                                          const int* __restrict__ guard, HostSignal tell, PairPublish publish,
-                                                         int4* __restrict__ from, const u32* __restrict__ rows) {
+                                                         int2* __restrict__ from, ulonglong2* __restrict__ from_info,
+                                                         const u64* __restrict__ rings) {
     if (COUNTS && blockIdx.x == 0 && threadIdx.x == 0) tell_host(tell);
     if ((int)blockIdx.x == publish.at) {
         publish_pairs(publish);
@@ -3603,7 +3637,10 @@ __global__ __launch_bounds__(BLOCK) void contract_kernel(const VRec* __restrict_
         if (vmin0) vmin0[nw] = VMIN_NONE;  // (the next round's first bids, see facet_costs_kernel)
         const float4* a = reinterpret_cast<const float4*>(&vin[w]);
         float4 r0 = a[0], r1 = a[1], r2 = a[2], r3 = a[3];
-        if (from) from[nw] = make_int4(w, m, (int)rows[w], m >= 0 ? (int)rows[m] : 0);  // (rounds by rings, see ring_costs_kernel)
+        if (from) {  // (rounds by rings, see ring_costs_kernel)
+            from[nw] = make_int2(w, m);
+            from_info[nw] = make_ulonglong2(rings[w], m >= 0 ? rings[m] : 0ull);
+        }
         if (m >= 0) {
             vmap[m] = nw;
             const int j0 = ABSORB ? aoff[w] : 0, jend = ABSORB ? aoff[w + 1] : 0;  // this cluster's part of alist (a pair's lower vertex is not the last one)
@@ -3820,10 +3857,11 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
         }
         if (lane == 0) L.n[s0 / (64 * SEG)] = n;
     }
-    for (int o = g; o < n_orig; o += stride) {
-        const int c = cid_in ? cid_in[o] : o;
-        cid_out[o] = vmap ? vmap[c] : c;
-    }
+    if (cid_out)
+        for (int o = g; o < n_orig; o += stride) {
+            const int c = cid_in ? cid_in[o] : o;
+            cid_out[o] = vmap ? vmap[c] : c;
+        }
     if (verts_out)
         for (int w = g; w < nv; w += stride) {
             const float4 p = *reinterpret_cast<const float4*>(&vrec[w]);
@@ -3831,6 +3869,21 @@ __global__ __launch_bounds__(BLOCK) void final_facets_kernel(const int* __restri
             verts_out[3 * (size_t)w + 1] = p.y;
             verts_out[3 * (size_t)w + 2] = p.z;
         }
+}
+
+// The final labels by themselves, in front of that kernel, where there are so many facets that it is better for them to go by these than by both maps, one after the other.
+constexpr int LABELS_APART_MIN = 1 << 20;  // vertices of the input
+constexpr int LABELS_ITEMS = 4;
+__global__ __launch_bounds__(BLOCK) void final_labels_kernel(const int* __restrict__ cid_in, const int* __restrict__ vmap, int* __restrict__ cid_out, int n) {
+    const long long o0 = (long long)blockIdx.x * (BLOCK * LABELS_ITEMS) + threadIdx.x;
+    int c[LABELS_ITEMS];
+#pragma unroll
+    for (int j = 0; j < LABELS_ITEMS; ++j) c[j] = o0 + j * BLOCK < n ? cid_in[o0 + j * BLOCK] : 0;
+#pragma unroll
+    for (int j = 0; j < LABELS_ITEMS; ++j) c[j] = vmap[c[j]];
+#pragma unroll
+    for (int j = 0; j < LABELS_ITEMS; ++j)
+        if (o0 + j * BLOCK < n) cid_out[o0 + j * BLOCK] = c[j];
 }
 
 // The survivors among the listed facets, counted per mesh (in its slots; the next kernel adds them up), per tile of BLOCK * CHUNKS facets (as a compaction's count pass does) and wave of it:

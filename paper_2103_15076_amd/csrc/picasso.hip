@@ -136,7 +136,8 @@ struct picasso_ctx {
     int* arem = nullptr;   // per mesh: budget left after the pairs
     RingRows ring[2], adj;  // rounds by rings: the rings, by the round's parity, and the neighbours with their costs (see ring_costs_kernel)
     int* rows_taken = nullptr;  // ... (see RINGS_TAKEN)
-    int4* from = nullptr;   // ... per vertex: the two of the round before that it was made of, and their rows' info
+    int2* from = nullptr;   // ... per vertex: the two of the round before that it was made of, and their rings' info
+    ulonglong2* from_info = nullptr;
     u32* area_ext = nullptr;  // per mesh: largest facet area and largest complement of one (conv::EXT_SLOTS; zero between calls)
     int64_t kt_calls = 0;           // decimate calls since the option was set
     bool kt_this_call = false;
@@ -269,25 +270,39 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->area_ext = cv.take<u32>(b * conv::EXT_SLOTS * conv::EXT_PAD);
     // The rings lie in the sorts' buffers, which rounds by rings do not use (the neighbours' where the facets' planes have been), if these are large enough, as they are where
     // vertices have five and a half facets or more.
-    const size_t ring_bytes = n * (sizeof(u32) * RING_MAX + sizeof(u32)), region = align_up(h * sizeof(u64)), wanted = ring_bytes + n * 8 + 4096;
+    const size_t ring_bytes = n * (sizeof(u32) * RING_ROW + sizeof(u64)), region = align_up(h * sizeof(u64)), wanted = ring_bytes + n * 4 + 4096;
+    const bool fits = region >= wanted;
     x->rows_taken = cv.take<int>(RINGS_TAKEN);
     for (int i = 0; i < 3; ++i) {
         RingRows& r = i < 2 ? x->ring[i] : x->adj;
         const size_t bytes = std::max(region, align_up(wanted));
-        char* const own = region < wanted ? cv.take<char>(bytes) : nullptr;
-        char* const at = region < wanted ? own : reinterpret_cast<char*>(i == 0 ? x->key64[0] : i == 1 ? x->key64[1] : x->ekey);
+        char* const own = fits ? nullptr : cv.take<char>(bytes);
+        char* const at = fits ? reinterpret_cast<char*>(i == 0 ? x->key64[0] : i == 1 ? x->key64[1] : x->ekey) : own;
         Carver in;
         in.base = at;
-        r.ids = in.take<u32>(n * RING_MAX);
-        r.info = in.take<u32>(n);
+        r.ids = in.take<u32>(n * RING_ROW);
+        r.info = in.take<u64>(n);
+        r.more = !fits ? cv.take<u32>(n * RING_MORE) : nullptr;
         r.arena_rows = (int)std::min<size_t>((bytes - in.off) / (ROW_ARENAS * ROW_SMALL * sizeof(u64)), (1u << 20) / ROW_ARENAS - 1);
         r.small = in.take<u64>((size_t)r.arena_rows * ROW_ARENAS * ROW_SMALL);
-        r.large_rows = (int)std::min<size_t>(n / 512 + 64, (1u << 20) - 1);
+        r.large_rows = (int)std::min<size_t>(n / 2048 + 16, (1u << 20) - 1);
         r.large = cv.take<u64>((size_t)r.large_rows * ROW_MAX);
         r.taken = x->rows_taken ? x->rows_taken + i * (ROW_ARENAS + 1) * MATCH_PAD : nullptr;
         r.wide = x->st ? &x->st->wide : nullptr;
     }
-    x->from = cv.take<int4>(n);
+    if (fits) {
+        Carver costs, values;  // (the incidence keys, which are in use while the first rings are made, have room for the others' only)
+        values.base = reinterpret_cast<char*>(x->val32);
+        x->from = values.take<int2>(n);
+        x->ring[0].more = values.take<u32>(n * RING_MORE);
+        x->ring[1].more = reinterpret_cast<u32*>(x->s0_key[0]);
+        x->adj.more = reinterpret_cast<u32*>(x->s0_key[1]);
+        costs.base = reinterpret_cast<char*>(x->ecost);
+        x->from_info = costs.take<ulonglong2>(n);
+    } else {
+        x->from = cv.take<int2>(n);
+        x->from_info = cv.take<ulonglong2>(n);
+    }
     return cv.off;
 }
 
@@ -441,8 +456,8 @@ prim::KeySort<u64> incidence_sort(picasso_ctx* c, int N, int F) {
 // before the first round's costs are computed (24 bytes per facet there, 16 needed).
 inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c->ekey); }
 template <bool RINGS>
-QuadricRows<RINGS> quadric_rows(picasso_ctx* c, const float* d_verts, int N, int F) {
-    return QuadricRows<RINGS>{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F), c->fcur, c->ring[0]};
+QuadricRows<RINGS> quadric_rows(picasso_ctx* c, const float* d_verts, const int* facets, int N, int F) {
+    return QuadricRows<RINGS>{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F), facets, c->ring[0]};
 }
 
 RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
@@ -473,19 +488,19 @@ bool sort_edges(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, int 
     return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<EdgeKeys>{{c->fcur, S.key_bits / 2}}, distinct_keys(c),
                           c->kt_this_call ? &c->kt : nullptr, round_);
 }
-// Sorts the incidence keys and sums the vertices' quadrics (RINGS: leaves their rings, too).
+// Sorts the incidence keys of these facets and sums the vertices' quadrics (RINGS: leaves their rings, too).
 template <bool RINGS>
-bool sort_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, const float* d_verts, int N, int F) {
-    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<IncidenceKeys>{{c->fcur, incidence_fbits(F)}},
-                          quadric_rows<RINGS>(c, d_verts, N, F), c->kt_this_call ? &c->kt : nullptr, PICASSO_KERNEL_QUADRIC_ROWS << 8,
+bool sort_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& S, const float* d_verts, const int* facets, int N, int F) {
+    return prim::key_sort(s, S, (const prim::KeySort<u64>*)nullptr, prim::OneSource<IncidenceKeys>{{facets, incidence_fbits(F), N}},
+                          quadric_rows<RINGS>(c, d_verts, facets, N, F), c->kt_this_call ? &c->kt : nullptr, PICASSO_KERNEL_QUADRIC_ROWS << 8,
                           PICASSO_KERNEL_SORT_INCIDENCE << 8);
 }
 // Both in the same launches.
 bool sort_edges_and_incidences(picasso_ctx* c, hipStream_t s, const prim::KeySort<u64>& E, const prim::KeySort<u64>& I,
                                const float* d_verts, int N, int F) {
     c->hist_dirty = false;
-    return prim::key_sort(s, I, &E, prim::TwoSources<IncidenceKeys, EdgeKeys>{{c->fcur, incidence_fbits(F)}, {c->fcur, E.key_bits / 2}},
-                          prim::TwoOuts<QuadricRows<false>, prim::DistinctKeys>{quadric_rows<false>(c, d_verts, N, F), distinct_keys(c)});
+    return prim::key_sort(s, I, &E, prim::TwoSources<IncidenceKeys, EdgeKeys>{{c->fcur, incidence_fbits(F), N}, {c->fcur, E.key_bits / 2}},
+                          prim::TwoOuts<QuadricRows<false>, prim::DistinctKeys>{quadric_rows<false>(c, d_verts, c->fcur, N, F), distinct_keys(c)});
 }
 
 // Whether a round of one or several meshes, of at most `edges` edges, keeps a state for each.
@@ -582,7 +597,7 @@ void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur
         const int grid = prim::xcd_grid(tiles) + (n_labels + RING_LABELS - 1) / RING_LABELS;
 #define PICASSO_RING_COSTS(PLACE, FIRST)                                                                                                            \
     ring_costs_kernel<PLACE, FIRST><<<grid, RING_THREADS, 0, s>>>(c->st, nv, c->vrec[cur_], (FIRST) ? out : in, out, c->adj, c->vmin[1], c->vmin[0], \
-                                                                  round_tab(c, B, round_, cur_), c->from, round_map(c, true, round_ - 1), c->cid,  \
+                                                                  round_tab(c, B, round_, cur_), c->from, c->from_info, round_map(c, true, round_ - 1), c->cid,  \
                                                                   n_labels, c->opt_rcond_min, c->nf_slots[par], c->nf_slots[par ^ 1])
         if (c->opt_placement == PLACE_INVERSE) {
             if (round_ == 0) PICASSO_RING_COSTS(PLACE_INVERSE, true);
@@ -627,7 +642,7 @@ constexpr int64_t CLEAR_AHEAD_MAX_FACETS = 1 << 20;
 // The validating kernel, instantiated for the sorts its keys go to.  work: rounds (or S0) follow; edges: the first round's
 // set-up as well (EDGES_BY_FACETS), and its edges' digits (EDGES_SORTED).
 int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, const int32_t* d_facets, int F, int B,
-                bool work, int edges, const HeaderInit& init = HeaderInit{}, const FewMeshes& tables = FewMeshes{}) {
+                bool work, int edges, const HeaderInit& init = HeaderInit{}, const FewMeshes& tables = FewMeshes{}, bool rings = false) {
     const prim::KeySort<u64> I = incidence_sort(c, N, F), E = edge_sort(c, N, F, F, 3ll * F);
     if (work && c->hist_dirty)  // (a call ended between a count of its edges and their sort)
         prim::fill_u32_kernel<<<prim::MSD_ZERO_WORDS / BLOCK, BLOCK, 0, s>>>(c->hist12, prim::MSD_ZERO_WORDS, 0u);
@@ -641,9 +656,9 @@ int launch_init(picasso_ctx* c, hipStream_t s, const float* d_verts, int N, cons
     const int n_clear = F <= CLEAR_AHEAD_MAX_FACETS ? (int)facet_slots((size_t)F) : 0;
 #define PICASSO_INIT_TABLES(COUNT, SORTED, TABLES)                                                                             \
     init_kernel<COUNT, SORTED><<<grid_for(std::max(N, F), 4096), BLOCK, 0, s>>>(                                                      \
-        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], edges == EDGES_BY_FACETS ? nullptr : c->cid, c->fcur, incidence_fbits(F), digit_count(I),      \
-        digit_count(E), edges, E.key_bits / 2, c->st, init, TABLES, planes, c->htab, n_clear, c->vmin[0], c->vmin[1],   \
-        c->mate, c->pcost(), round_tab(c, B, 0, 0), edges == EDGES_BY_FACETS ? c->rows_taken : nullptr)
+        d_verts, N, d_facets, F, B, c->voff[0], c->foff, c->vrec[0], edges == EDGES_BY_FACETS ? nullptr : c->cid, rings ? nullptr : c->fcur, incidence_fbits(F), digit_count(I),      \
+        digit_count(E), edges, E.key_bits / 2, c->st, init, TABLES, planes, c->htab, n_clear, c->vmin[0], rings ? nullptr : c->vmin[1],   \
+        c->mate, c->pcost(), round_tab(c, B, 0, 0), rings ? c->rows_taken : nullptr)
 #define PICASSO_INIT_EDGES(COUNT, SORTED)                                           \
     do {                                                                            \
         if (B == 1) PICASSO_INIT_TABLES(COUNT, SORTED, OneMesh{tables.target[0]});  \
@@ -990,14 +1005,14 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
                           edge_sort(c, N, F, F, 3ll * F).half == incidence_sort(c, N, F).half;
     tm.begin(0, PICASSO_ST_QUADRICS);
-    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, !work ? EDGES_NONE : by_facets ? EDGES_BY_FACETS : EDGES_SORTED, hinit, tables);
+    rc = launch_init(c, s, d_verts, N, d_facets, F, B, work, !work ? EDGES_NONE : by_facets ? EDGES_BY_FACETS : EDGES_SORTED, hinit, tables, rings);
     if (rc != PICASSO_OK) return rc;
     if (work) {
         const prim::KeySort<u64> I = incidence_sort(c, N, F);
         if (together) {
             if (!sort_edges_and_incidences(c, s, edge_sort(c, N, F, F, 3ll * F), I, d_verts, N, F)) return PICASSO_ERR_HIP;
         } else if (F > 0) {
-            if (!(rings ? sort_incidences<true>(c, s, I, d_verts, N, F) : sort_incidences<false>(c, s, I, d_verts, N, F))) return PICASSO_ERR_HIP;
+            if (!(rings ? sort_incidences<true>(c, s, I, d_verts, d_facets, N, F) : sort_incidences<false>(c, s, I, d_verts, c->fcur, N, F))) return PICASSO_ERR_HIP;
         }
     }
     tm.end();
@@ -1077,7 +1092,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                                                            chunks, c->tilesum, prefixed, B, c->voff[cur],             \
                                                            c->voff[nxt], c->matched, c->done, c->htab, (int)clear, \
                                                            by_facets ? c->vmin[0] : nullptr, RCOND, c->arep, c->aoff, c->joiners(), guard, tell, publish, \
-                                                           rings ? c->from : nullptr, c->ring[round & 1].info)
+                                                           rings ? c->from : nullptr, c->from_info, c->ring[round & 1].info)
             if (c->opt_placement == PLACE_INVERSE) {
                 if (n_joined > 0) PICASSO_CONTRACT(PLACE_INVERSE, true, false, c->opt_rcond_min);
                 else if (counts) PICASSO_CONTRACT(PLACE_INVERSE, false, true, c->opt_rcond_min);
@@ -1154,6 +1169,21 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         sa.host_check = c->h_pin_dev + c->h_seq_off + SEQ_CHECK_WORD;
         sa.tb = tb;
         int sel_k = 0;
+        auto check_errors = [&]() -> int {
+            if (!validated) {
+                const int st_err = status_from_err_bits(hst->err);
+                if (st_err != PICASSO_OK) {  // (the flags go back to zero for the next call, see HeaderInit)
+                    prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
+                    return st_err;
+                }
+                validated = true;
+            }
+            if (hst->err & ERR_BIT_INTERNAL) {  // a kernel of the round before has refused its sizes
+                prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
+                return PICASSO_ERR_INTERNAL;
+            }
+            return PICASSO_OK;
+        };
         bool recount = true;  // the tiles' survivors are still to be counted when the budget step, if any, is done
         if (rings) {
             launch_ring_round(c, s, B, round, cur, nv_total, N, sa);
@@ -1172,11 +1202,13 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                 publish_pairs_kernel<<<1, BLOCK, 0, s>>>(publish);
             }
             HIP_TRY(c, wait_for_signal(c, s, done));
+            if ((rc = check_errors()) != PICASSO_OK) return rc;
             ahead = ahead_ok;
             recount = false;
             if (hst->wide) {  // a row did not fit: this round and those behind it by facets
                 rings = false;
                 fresh = round > 0;
+                HIP_TRY(c, hipMemcpyAsync(c->fcur, d_facets, sizeof(int) * 3 * (size_t)F, hipMemcpyDeviceToDevice, s));
                 for (int i = 0; i < 2; ++i) prim::fill_u32_kernel<<<grid_for(2ll * nv_total), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->vmin[i]), 2 * nv_total, ~0u);
                 prim::fill_u32_kernel<<<grid_for(MATCH_SLOTS * MATCH_PAD), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->nf_slots[round & 1]), MATCH_SLOTS * MATCH_PAD, 0u);
                 renumbered = was_renumbered;
@@ -1202,22 +1234,6 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // candidates queued behind each batch 7.6, so 3.0.
         bool slow = false, queued = false;
         int wide_before = 0;
-        auto check_errors = [&]() -> int {
-            if (!validated) {
-                const int st_err = status_from_err_bits(hst->err);
-                if (st_err != PICASSO_OK) {  // (the flags go back to zero for the next call, see HeaderInit)
-                    prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
-                    return st_err;
-                }
-                validated = true;
-            }
-            if (hst->err & ERR_BIT_INTERNAL) {  // a kernel of the round before has refused its sizes
-                prim::fill_u32_kernel<<<1, BLOCK, 0, s>>>(reinterpret_cast<u32*>(&c->st->err), 1, 0u);
-                return PICASSO_ERR_INTERNAL;
-            }
-            return PICASSO_OK;
-        };
-        if (rings && (rc = check_errors()) != PICASSO_OK) return rc;
         while (!rings) {
             // live edges fall by about 2.8x, 2.7x, 3.2x, 4x, 5x, ... per sub-round on meshes with varied costs
             static const int decay_x10[] = {28, 27, 32, 40, 50, 60};
@@ -1376,15 +1392,22 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // (null: what a vertex's label is in front of the last contraction is its number; see round_map)
     const int* const labels = by_facets && (round == 0 || (round == 1 && renumbered)) ? nullptr : c->cid;
     // rounds by rings have left the facets as they came: the labels in front of the last contraction take them there
-    const int* const before = rings && round > 0 ? labels : nullptr;
+    const int* before = rings && round > 0 ? labels : nullptr;
     int* const labels_out = !drop ? d_cluster_id : before ? c->arep : c->cid;  // (where the labels are still read: beside them)
+    const int* last_map = renumbered ? round_map(c, by_facets, round - 1) : nullptr;
+    const bool labels_apart = before && last_map && N >= LABELS_APART_MIN;
+    if (labels_apart) {
+        final_labels_kernel<<<grid_for((N + LABELS_ITEMS - 1) / LABELS_ITEMS), BLOCK, 0, s>>>(labels, last_map, labels_out, N);
+        before = nullptr;
+        last_map = labels_out;
+    }
     tm.begin(std::max(round - 1, 0), PICASSO_ST_FACETS);
     {
         const KernelBracket timed(c, s, PICASSO_KERNEL_FACET_INSERT, round - 1, renumbered);
 #define PICASSO_FINAL_FACETS(SEG)                                                                                       \
     final_facets_kernel<SEG><<<grid_for(std::max(N, F), 8192), BLOCK, 0, s>>>(                                          \
-        c->fcur, F, fcount, tile_shift, fl, c->mslots, before, renumbered ? round_map(c, by_facets, round - 1) : nullptr, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur],     \
-        c->done, labels, labels_out, N, c->vrec[cur], drop ? nullptr : d_verts_out)
+        rings ? d_facets : c->fcur, F, fcount, tile_shift, fl, c->mslots, before, last_map, c->st, cur, htab, (u32)(slots - 1), fbits, B, c->voff[cur],     \
+        c->done, labels, labels_apart ? nullptr : labels_out, N, c->vrec[cur], drop ? nullptr : d_verts_out)
         switch (facet_segment(chunks)) {
             case 1: PICASSO_FINAL_FACETS(1); break;
             case 2: PICASSO_FINAL_FACETS(2); break;
@@ -1490,7 +1513,7 @@ int checked_vertex_quadrics(picasso_ctx* c, hipStream_t s, const float* d_verts,
         return rc;
     }
     const prim::KeySort<u64> I = incidence_sort(c, N, F);
-    if (F > 0 && !sort_incidences<false>(c, s, I, d_verts, N, F)) return PICASSO_ERR_HIP;
+    if (F > 0 && !sort_incidences<false>(c, s, I, d_verts, c->fcur, N, F)) return PICASSO_ERR_HIP;
     return PICASSO_OK;
 }
 
