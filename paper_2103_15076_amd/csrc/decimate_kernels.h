@@ -694,6 +694,8 @@ struct QuadricRows {
     // Mostly a group of the sort is a vertex: a lane then sorts its vertex's keys in registers and goes on with them (up to
     // GROUP_LANE keys; a wave sorts more).  (With the groups sorted in LDS and the vertices found again among the keys 115 k vertices took 12.3 us, now 9.6, 1.2 M
     // 49 and 42.5, 10.2 M 450 and 421.)
+    // (With the rings the compiler takes 118 registers, for four waves: 1.2 M vertices 69 us, with 80 for six 63; of a decimated mesh of 384 k 34 and 27.)
+    static constexpr int MIN_WAVES = RINGS ? 6 : 1;
     static constexpr bool GROUPS_SORTED = false;
     static constexpr int GROUP_SHORT = 8, GROUP_LANE = 16;  // (sizes of a lane's sort)
     __device__ bool rows_are_groups(bool, const prim::Bucket& b, int R) const { return (1 << (b.low_bits - fbits)) == R && b.low_bits > fbits; }

@@ -1119,8 +1119,14 @@ struct TakesGroups : std::false_type {};
 template <class Out>
 struct TakesGroups<Out, std::void_t<decltype(&Out::rows_are_groups)>> : std::true_type {};
 
+// ... and says for how many waves of a SIMD there are to be registers (MIN_WAVES; of keys whose workgroups LDS holds enough of).
+template <class Out, class = void>
+struct MinWaves : std::integral_constant<int, 1> {};
+template <class Out>
+struct MinWaves<Out, std::void_t<decltype(Out::MIN_WAVES)>> : std::integral_constant<int, Out::MIN_WAVES> {};
+
 template <typename K, typename LK, int THREADS, int ITEMS, class Out>
-__global__ __launch_bounds__(THREADS) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int blocks_first, Out out) {
+__global__ __launch_bounds__(THREADS, sizeof(LK) == 4 ? MinWaves<Out>::value : 1) void bucket_keys_kernel(KeySort<K> first_sort, KeySort<K> second_sort, int blocks_first, Out out) {
     __shared__ BucketLds<LK, THREADS, ITEMS> L;
     __shared__ typename Out::template Lds<THREADS, ITEMS> O;
     const bool second = (int)blockIdx.x >= blocks_first;
