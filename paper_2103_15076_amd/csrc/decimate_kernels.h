@@ -631,8 +631,21 @@ struct RingRows {
         r[1] = make_uint4(x[4], x[5], x[6], x[7]);
         if (n > RING_ROW) *reinterpret_cast<uint2*>(more + (size_t)v * RING_MORE) = make_uint2(x[8], x[9]);
     }
-    __device__ __forceinline__ u32 id(int v, int i) const {
-        return i < RING_ROW ? ids[(size_t)v * RING_ROW + i] : more[(size_t)v * RING_MORE + (i - RING_ROW)];
+    __device__ __forceinline__ u32* place(int v, int i) const {
+        return i < RING_ROW ? ids + (size_t)v * RING_ROW + i : more + (size_t)v * RING_MORE + (i - RING_ROW);
+    }
+    // facet i of v's ring
+    __device__ __forceinline__ void load_facet(int v, u64 info_, int i, u32& a, u32& b) const {
+        const u32 *p, *q;
+        if (ring_in_rows(info_)) {
+            p = reinterpret_cast<const u32*>(row_of(info_) + i);
+            q = p + 1;
+        } else {
+            p = place(v, i);
+            q = place(v, ring_second(info_, i));
+        }
+        a = *p;
+        b = *q;
     }
 };
 static_assert(RING_MORE == 2, "two beside the row");
@@ -2483,13 +2496,7 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         const u32 group_mask = (1u << RING_GROUP) - 1u;
         const int group_lead = lane & ~(RING_GROUP - 1);
         auto of_group = [&](bool x) -> u32 { return (u32)(prim::ballot(x) >> (group * RING_GROUP)) & group_mask; };
-        // a row of the group for n entries (n = 0: there is none)
-        auto group_row = [&](const RingRows& rows, int& n_, u32& number) {
-            number = 0;
-            if (sub == 0 && n_ > 0) number = rows.take_row(n_);
-            n_ = __shfl(n_, group_lead, 64);
-            number = (u32)__shfl((int)number, group_lead, 64);
-        };
+        const VertexWords U = load_vertex(vrec, u);
         int k = 0;  // facets there are
         if constexpr (FIRST) {
             const u64 row = __shfl(info, from_lane, 64);
@@ -2497,37 +2504,39 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
             const u64* const of = in.row_of(row);
             for (int i = sub; i < k; i += RING_GROUP) facet[i] = of[i];
         } else {
-#pragma unroll 1
-            for (int h = 0; h < 2; ++h) {
-                const int src = h ? pair.y : pair.x;
-                const u64 row = h ? pair_info.y : pair_info.x;
-                const int count = on && src >= 0 ? ring_facets(row) : 0;
-                for (int i0 = 0; __any(i0 < count); i0 += RING_GROUP) {
-                    const int i = i0 + sub;
-                    bool ok = i < count;
-                    u64 e = 0;
-                    if (ok) {
-                        if (ring_in_rows(row)) e = in.row_of(row)[i];
-                        else e = ring_entry((int)in.id(src, i), (int)in.id(src, ring_second(row, i)));
-                    }
-                    const int a = vmap[ok ? (u32)e : 0u], b = vmap[ok ? (u32)(e >> 32) : 0u];
-                    ok = ok && a != u && b != u && a != b;
+            const int count[2] = {on ? ring_facets(pair_info.x) : 0, on && pair.y >= 0 ? ring_facets(pair_info.y) : 0};
+            for (int i0 = 0; __any(i0 < max(count[0], count[1])); i0 += RING_GROUP) {
+                u32 a[2], b[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    a[h] = b[h] = 0;
+                    if (i0 + sub < count[h]) in.load_facet(h ? pair.y : pair.x, h ? pair_info.y : pair_info.x, i0 + sub, a[h], b[h]);
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    a[h] = (u32)vmap[a[h]];
+                    b[h] = (u32)vmap[b[h]];
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bool ok = i0 + sub < count[h] && a[h] != (u32)u && b[h] != (u32)u && a[h] != b[h];
                     const u32 in_group = of_group(ok);
                     const int place = k + __popc(in_group & ((1u << sub) - 1u));
-                    if (ok && place < ROW_MAX) facet[place] = ring_entry(a, b);
+                    if (ok && place < ROW_MAX) facet[place] = ring_entry((int)a[h], (int)b[h]);
                     k += __popc(in_group);
                 }
             }
         }
         in_order();
         if (sub == 0) n_facets += min(k, ROW_MAX);
-        const VertexWords U = load_vertex(vrec, u);
+        // a lane a facet, whose two corners' records are fetched while the facets are put in order
+        const u64 mine = sub < k ? facet[sub] : ring_entry(u, u);
+        const u32 mine_p = (u32)mine, mine_q = (u32)(mine >> 32);
+        const VertexWords P = load_vertex(vrec, (int)mine_p), Q = load_vertex(vrec, (int)mine_q);
         u64 best = VMIN_NONE;
         // A short ring after all, if the facets follow one another around the vertex (where some are wound the other way round, first corners are met twice and others not at
-        // all): a lane a facet, a walk goes on from a vertex by one not yet taken that has it.  One that is stuck has come to an end of an open fan, if there is one: the
+        // all): a walk goes on from a vertex by a facet not yet taken that has it.  One that is stuck has come to an end of an open fan, if there is one: the
         // second walk goes from there.
-        const u64 mine = sub < k && k <= RING_MAX ? facet[sub] : 0;
-        const u32 mine_p = (u32)mine, mine_q = (u32)(mine >> 32);
         u32 begin = (u32)facet[0], at = begin, my_first = 0;
         int my_step = -1, steps = 0;
         for (int turn = 0; turn < 2 && __any(k <= RING_MAX && steps != k); ++turn) {
@@ -2549,62 +2558,71 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         }
         const int n_ids = at == begin ? k : k + 1;
         const bool is_short = on && k > 0 && k <= RING_MAX && steps == k && n_ids <= RING_MAX;
-        in_order();
-        u32* const ids = reinterpret_cast<u32*>(facet);  // (of a short ring: in the facets' place)
-        if (is_short) {
-            if (my_step >= 0) ids[my_step] = my_first;
-            if (sub == 0 && n_ids > k) ids[k] = at;
+        // its neighbours, if in a row: the facets' first corners, and the second ones that are no facet's first
+        const int fits = counts && !is_short ? min(k, ROW_MAX) : 0;
+        int m = fits;
+        u32 only = 0;  // of the lane's facets, one in every turn
+        for (int i0 = 0, turn = 0; __any(i0 < fits); i0 += RING_GROUP, ++turn) {
+            const bool ok = i0 + sub < fits;
+            const int b = ok ? (int)(u32)(facet[i0 + sub] >> 32) : u;
+            bool is = b != u;
+            for (int j = 0; j < fits; ++j) is = is && (int)(u32)facet[j] != b;
+            only |= is ? 1u << turn : 0u;
+            m += __popc(of_group(is));
         }
-        in_order();
-        if (is_short && sub < n_ids) {
+        // rows for the facets and for the neighbours, taken together (none where there are none, or too many)
+        int n_row = !on || is_short ? 0 : sub == 0 ? (FIRST ? 0 : k) : sub == 1 ? m : 0;
+        u32 row_at = 0;
+        if (n_row > 0) row_at = (sub == 0 ? out : adj).take_row(n_row);
+        const int k_row = __shfl(n_row, group_lead, 64), m_row = __shfl(n_row, group_lead + 1, 64);
+        const u32 k_at = (u32)__shfl((int)row_at, group_lead, 64), m_at = (u32)__shfl((int)row_at, group_lead + 1, 64);
+        const u32 cost_p = neighbour(u, U, (int)mine_p, P), cost_q = neighbour(u, U, (int)mine_q, Q);
+        auto offer = [&](u32 cost, u32 x) {
+            const u64 key = ((u64)cost << 32) | x;
+            if (x != (u32)u && key < best) best = key;
+        };
+        if (is_short && my_step >= 0) {
             constexpr u64 NEXT = 0xA987654321ull;
-            const u32 x = ids[sub];
-            (sub < RING_ROW ? out.ids[(size_t)u * RING_ROW + sub] : out.more[(size_t)u * RING_MORE + sub - RING_ROW]) = x;
-            if (sub == 0) out.info[u] = ring_info(n_ids, k, n_ids > k ? NEXT : NEXT & ~(15ull << (4 * (k - 1))));  // (the last one of a closed fan leads to the first vertex)
-            if (counts) {
-                const u32 cost = neighbour(u, U, (int)x, load_vertex(vrec, (int)x));
-                (sub < RING_ROW ? adj.ids[(size_t)u * RING_ROW + sub] : adj.more[(size_t)u * RING_MORE + sub - RING_ROW]) = cost;
-                if (x != (u32)u) best = ((u64)cost << 32) | x;
-            }
+            const bool p_first = my_first == mine_p;
+            auto put = [&](int place, u32 x, u32 cost) {
+                *out.place(u, place) = x;
+                if (counts) {
+                    *adj.place(u, place) = cost;
+                    offer(cost, x);
+                }
+            };
+            put(my_step, my_first, p_first ? cost_p : cost_q);
+            if (my_step == k - 1 && n_ids > k) put(k, p_first ? mine_q : mine_p, p_first ? cost_q : cost_p);
+            if (my_step == 0) out.info[u] = ring_info(n_ids, k, n_ids > k ? NEXT : NEXT & ~(15ull << (4 * (k - 1))));  // (the last one of a closed fan leads to the first vertex)
         }
-        u32 number = 0;
-        int fits = 0, m = 0;
         if (__any(on && !is_short)) {
-            // ... or in a row
             if constexpr (!FIRST) {
-                if (is_short) k = 0;
-                group_row(out, k, number);  // (more than ROW_MAX do not fit)
-                u64* const row = out.row(k, number);
-                for (int i = sub; i < k; i += RING_GROUP) row[i] = facet[i];
-                if (on && !is_short && sub == 0) out.info[u] = rows_info(k, number);
+                u64* const row = out.row(k_row, k_at);
+                for (int i = sub; i < k_row; i += RING_GROUP) row[i] = facet[i];
+                if (on && !is_short && sub == 0) out.info[u] = rows_info(k_row, k_at);
             }
-            // its neighbours: the facets' first corners, and the second ones that are no facet's first
-            m = fits = counts && !is_short ? k : 0;
-            u32 only = 0;  // of the lane's facets, one in every turn
-            for (int i0 = 0, turn = 0; __any(i0 < fits); i0 += RING_GROUP, ++turn) {
-                const bool ok = i0 + sub < fits;
-                const int b = ok ? (int)(u32)(facet[i0 + sub] >> 32) : u;
-                bool is = b != u;
-                for (int j = 0; j < fits; ++j) is = is && (int)(u32)facet[j] != b;
-                only |= is ? 1u << turn : 0u;
-                m += __popc(of_group(is));
-            }
-            group_row(adj, m, number);
-            u64* const row = adj.row(m, number);
+            u64* const row = adj.row(m_row, m_at);
             int place0 = fits;
-            for (int i0 = 0, turn = 0; __any(m > 0 && i0 < fits); i0 += RING_GROUP, ++turn) {
+            for (int i0 = 0, turn = 0; __any(m_row > 0 && i0 < fits); i0 += RING_GROUP, ++turn) {
                 const int i = i0 + sub;
-                const bool ok = m > 0 && i < fits, is = ok && (only >> turn & 1u);
-                const u64 e = ok ? facet[i] : 0;
-                const int a = ok ? (int)(u32)e : u, b = is ? (int)(u32)(e >> 32) : u;
-                const u64 key = ((u64)neighbour(u, U, a, load_vertex(vrec, a)) << 32) | (u32)a;
-                if (ok) row[i] = key;
-                if (a != u && key < best) best = key;
+                const bool ok = m_row > 0 && i < fits, is = ok && (only >> turn & 1u);
+                u32 a = mine_p, b = mine_q, cost_a = cost_p, cost_b = cost_q;
+                if (i0 > 0) {
+                    const u64 e = ok ? facet[i] : ring_entry(u, u);
+                    a = (u32)e;
+                    b = (u32)(e >> 32);
+                    const VertexWords A = load_vertex(vrec, (int)a), B = load_vertex(vrec, (int)b);
+                    cost_a = neighbour(u, U, (int)a, A);
+                    cost_b = neighbour(u, U, (int)b, B);
+                }
+                if (ok) {
+                    row[i] = ((u64)cost_a << 32) | a;
+                    offer(cost_a, a);
+                }
                 const u32 more = of_group(is);
                 if (is) {
-                    const u64 key_b = ((u64)neighbour(u, U, b, load_vertex(vrec, b)) << 32) | (u32)b;
-                    row[place0 + __popc(more & ((1u << sub) - 1u))] = key_b;
-                    if (key_b < best) best = key_b;
+                    row[place0 + __popc(more & ((1u << sub) - 1u))] = ((u64)cost_b << 32) | b;
+                    offer(cost_b, b);
                 }
                 place0 += __popc(more);
             }
@@ -2615,7 +2633,7 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
             best = other < best ? other : best;
         }
         if (on && sub == 0) {
-            if (!is_short) adj.info[u] = rows_info(m, number);
+            if (!is_short) adj.info[u] = rows_info(m_row, m_at);
             bid(u, best);
         }
         in_order();
