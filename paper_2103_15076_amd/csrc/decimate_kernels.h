@@ -40,6 +40,7 @@ struct State {
     int absorb_n;  // edges through which an un-paired vertex would join a pair's cluster (Alg. 2 line 11)
     int nv_kept;   // output vertices that some output facet refers to (option: degenerated vertices dropped)
     int wide;      // rounds by rings: a vertex has more facets or neighbours than a row takes
+    int missed;    // ... the budget's last pair is not among those that budget_range_kernel has listed
     // Written by every selection tail for kernels that the host queued behind it before looking
     // (they run only if the tail finished the matching): 1 / nv of the round then, else zeros.
     int go, guard_nv;
@@ -2771,10 +2772,18 @@ __global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, State* s
     }
 }
 
+// Pairs that may be the budget's last one, as (cost - lo << 32) | lower vertex, for the two kernels of the budget step of a single mesh (see budget_range_kernel).
+constexpr int BUDGET_THREADS = 1024, BUDGET_LIST = 16 * BUDGET_THREADS;
+struct BudgetList {
+    u64 counts;  // pairs in front of the listed range (<< 32), listed ones (the list may hold less)
+    u32 lo, hi;  // the range
+    u64 entry[BUDGET_LIST];
+};
+
 // The pairs that the bids come to: partners and costs by vertex, how many there are of each mesh, and per tile the vertices that survive them (as a
 // compaction's count pass does).
 template <int CHUNKS>
-__global__ __launch_bounds__(BLOCK) void pairs_kernel(SelArgs A, const u64* __restrict__ bids, int* __restrict__ tilesum) {
+__global__ __launch_bounds__(BLOCK) void pairs_kernel(SelArgs A, const u64* __restrict__ bids, int* __restrict__ tilesum, BudgetList* __restrict__ budget) {
     __shared__ PairTally tally;
     __shared__ u32 smem[prim::WAVES];
     const int nv = A.nv, wave = prim::wave_id(), lane = prim::lane_id(), t = threadIdx.x;
@@ -2782,6 +2791,7 @@ __global__ __launch_bounds__(BLOCK) void pairs_kernel(SelArgs A, const u64* __re
     if (blockIdx.x == 0 && t == 0) {  // (what the kernels queued behind this one go by)
         A.st->go = wide ? 0 : 1;
         A.st->guard_nv = wide ? 0 : nv;
+        if (budget) budget->counts = 0;
     }
     if (wide) return;
     const long long base = (long long)blockIdx.x * (BLOCK * CHUNKS), i0 = base + wave * (64 * CHUNKS) + lane;
@@ -2827,8 +2837,9 @@ struct PairPublish {
     int* host_check;
     HostSignal tell;
 };
-__device__ __forceinline__ void publish_pairs(const PairPublish& P) {
-    constexpr int STATE_INTS = (int)(sizeof(State) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int)), NH = (int)(offsetof(State, nh) / sizeof(int));
+__device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed = false) {
+    constexpr int STATE_INTS = (int)(sizeof(State) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int)), NH = (int)(offsetof(State, nh) / sizeof(int)),
+                  MISSED = (int)(offsetof(State, missed) / sizeof(int));
     static_assert(MATCH_SLOTS == 32, "a mesh's slots fill half a wave");
     const int t = threadIdx.x, n = blockDim.x;
     const bool wide = P.st->wide != 0;
@@ -2846,11 +2857,220 @@ __device__ __forceinline__ void publish_pairs(const PairPublish& P) {
             if (STATE_INTS + b < P.publish_ints) host_store(&P.host_img[STATE_INTS + b], sum);
         }
     }
-    for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : reinterpret_cast<const int*>(P.st)[i]);
+    for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : i == MISSED ? (missed ? 1 : 0) : reinterpret_cast<const int*>(P.st)[i]);
     if (t == 0) host_store(P.host_check, P.tell.seq);
     signal_host(P.tell, t, true);
 }
 __global__ __launch_bounds__(BLOCK) void publish_pairs_kernel(PairPublish P) { publish_pairs(P); }
+
+// ---------------------------------------------------------------------------
+// The budget step of a single mesh in a round by rings, of more pairs than one compute unit walks in little time, by two launches that know nothing of the host and
+// leave the partners and the tiles' counts of survivors as the contraction takes them.
+// In the first every workgroup finds in a sample of the costs, the same for all, the range in which the budget's last pair lies (counts of 14 bits, 32 digits an
+// octave; six standard deviations of a rank in the middle); the pairs in it are listed, those in front of it counted.
+// In the second every workgroup finds the last pair among the listed ones, dissolves what lies beyond it among its own vertices and counts who survives.  Where the
+// sample has misled, or too many costs are equal, nothing is contracted, and the host, which is told, takes the general way.
+// Bound by chains: a sample's trip, its counts in LDS and their scan in the first; two trips and up to three counts of 12 bits in the second (many of a scanned wall's costs
+// are equal, so that the vertices decide).  115 k vertices (a second round of 62 k, 28 k pairs): the search by one workgroup took 22 us and the count of the survivors with the
+// release 5, these two 7 and 12; 1.2 M (350 k, 160 k pairs), where the whole chip's histogram passes behind a look of the host took 46 in eight launches, 15 and 19.
+// (The second by one workgroup, which then dissolves the listed ones itself: 24 and 42, most of it scattered stores.)
+// ---------------------------------------------------------------------------
+constexpr int BUDGET_BITS = 14, BUDGET_DIGITS = 1 << BUDGET_BITS, BUDGET_TILES = BUDGET_THREADS / BLOCK;
+constexpr int BUDGET_SAMPLES = 4;  // vertices of a place
+constexpr int BUDGET_FEW = 1 << 16;  // vertices up to which a lane samples one place, beyond four
+
+// Pairs of the mesh, by the lanes of a whole half wave.
+__device__ __forceinline__ int pairs_of_mesh(const int* __restrict__ mslots) {
+    int n = mslots[(threadIdx.x & (MATCH_SLOTS - 1)) * MATCH_PAD];
+#pragma unroll
+    for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) n += __shfl_xor(n, d, 64);
+    return n;
+}
+
+// Counts a digit of each lane with `on`.  Costs are equal in many pairs of scanned walls, and lanes that name one word take turns: those with the first one's digit go together.
+// (Of the sample, whose costs are of many digits, it takes longer: 15 us of the launch above, 19.)
+__device__ __forceinline__ void count_digit(u32* hist, bool on, u32 d) {
+    const u64 all = prim::ballot(on);
+    if (all == 0) return;
+    const int lead = __ffsll((long long)all) - 1;
+    const u32 first = (u32)__builtin_amdgcn_readlane((int)d, lead);
+    const u64 same = prim::ballot(on && d == first);
+    if (prim::lane_id() == lead) atomicAdd(&hist[first], (u32)__popcll(same));
+    else if (on && d != first) atomicAdd(&hist[d], 1u);
+}
+
+__global__ __launch_bounds__(BUDGET_THREADS) void budget_range_kernel(const u32* __restrict__ pcost, int nv, const State* __restrict__ st,
+                                                                      const int* __restrict__ mslots, const int* __restrict__ budget,
+                                                                      BudgetList* __restrict__ L) {
+    constexpr int N_WAVES = BUDGET_THREADS / 64, DIGITS_EACH = BUDGET_DIGITS / BUDGET_THREADS;
+    constexpr u32 HIGHEST = 0xFFFFFFFEu, IN_DIGIT = (1u << (32 - BUDGET_BITS)) - 1u;
+    __shared__ u32 hist[BUDGET_DIGITS + BUDGET_THREADS];  // (a word between the lanes' digits: they read them at a stride that meets all banks)
+    __shared__ u32 smem[N_WAVES], found[2], n_listed, n_below;
+    __shared__ u64 list_at;
+    const int t = threadIdx.x, lane = prim::lane_id(), w = (int)blockIdx.x * BUDGET_THREADS + t;
+    const bool here = w < nv;
+    const int go = st->go, keep = budget[0], n = pairs_of_mesh(mslots);
+    const u32 own = here ? pcost[w] : PAIR_NONE;  // (of a pair's lower vertex)
+    uint4 sample[BUDGET_SAMPLES];
+    int place[BUDGET_SAMPLES];
+#pragma unroll
+    for (int q = 0; q < BUDGET_SAMPLES; ++q) {
+        const bool on = q == 0 || nv > BUDGET_FEW;
+        place[q] = (int)(((long long)nv * (nv > BUDGET_FEW ? q * BUDGET_THREADS + t : t)) >> (nv > BUDGET_FEW ? 12 : 10)) & ~3;
+        sample[q] = on ? *reinterpret_cast<const uint4*>(pcost + place[q]) : make_uint4(PAIR_NONE, PAIR_NONE, PAIR_NONE, PAIR_NONE);
+    }
+    if (go == 0 || n <= keep) return;
+    for (int i = t; i < BUDGET_DIGITS + BUDGET_THREADS; i += BUDGET_THREADS) hist[i] = 0;
+    if (t < 2) found[t] = 0;
+    if (t == 0) n_listed = n_below = 0;
+    __syncthreads();
+    auto note = [&](u32 c, int v) {
+        const u32 d = c >> (32 - BUDGET_BITS);
+        if (c != PAIR_NONE && v < nv) atomicAdd(&hist[d + d / DIGITS_EACH], 1u);
+    };
+#pragma unroll
+    for (int q = 0; q < BUDGET_SAMPLES; ++q) {
+        note(sample[q].x, place[q]);
+        note(sample[q].y, place[q] + 1);
+        note(sample[q].z, place[q] + 2);
+        note(sample[q].w, place[q] + 3);
+    }
+    __syncthreads();
+    u32 c[DIGITS_EACH], sum = 0;
+#pragma unroll
+    for (int j = 0; j < DIGITS_EACH; ++j) {
+        c[j] = hist[t * (DIGITS_EACH + 1) + j];
+        sum += c[j];
+    }
+    u32 all, run = prim::wide_block_exclusive_scan<N_WAVES>(sum, smem, all);
+    const float rank = (float)all * (float)keep / (float)n, margin = 3.0f * sqrtf((float)all) + 4.0f;
+    const u32 from = rank > margin ? (u32)(rank - margin) : 0u, to = min((u32)(rank + margin), all + 1u);
+#pragma unroll
+    for (int j = 0; j < DIGITS_EACH; ++j) {
+        if (run < from && from <= run + c[j]) found[0] = (u32)(t * DIGITS_EACH + j);
+        if (run < to && to <= run + c[j]) found[1] = (u32)(t * DIGITS_EACH + j);
+        run += c[j];
+    }
+    __syncthreads();
+    const u32 lo = from > 0 ? found[0] << (32 - BUDGET_BITS) : 0u;
+    const u32 hi = to > 0 && to <= all ? min(HIGHEST, (found[1] << (32 - BUDGET_BITS)) | IN_DIGIT) : HIGHEST;
+    if (blockIdx.x == 0 && t == 0) {
+        L->lo = lo;
+        L->hi = hi;
+    }
+    const bool lists = own != PAIR_NONE && own >= lo && own <= hi, below = own < lo;
+    const u64 listed = prim::ballot(lists), in_front = prim::ballot(below);
+    u32 at = 0;
+    if (lane == 0) {
+        if (in_front) atomicAdd(&n_below, (u32)__popcll(in_front));
+        if (listed) at = atomicAdd(&n_listed, (u32)__popcll(listed));
+    }
+    __syncthreads();
+    if (t == 0) list_at = n_listed || n_below ? atomicAdd(&L->counts, ((u64)n_below << 32) | n_listed) : 0ull;
+    __syncthreads();
+    at = (u32)list_at + (u32)__shfl((int)at, 0, 64) + prim::mask_below(listed);
+    if (lists && at < (u32)BUDGET_LIST) L->entry[at] = ((u64)(own - lo) << 32) | (u32)w;
+}
+
+__global__ __launch_bounds__(BUDGET_THREADS) void budget_release_kernel(const u32* __restrict__ pcost, int* __restrict__ mate, int nv, State* st,
+                                                                        const int* __restrict__ mslots, const int* __restrict__ budget, int* __restrict__ tilesum,
+                                                                        const BudgetList* __restrict__ L, PairPublish publish) {
+    constexpr int N_WAVES = BUDGET_THREADS / 64, EACH = BUDGET_LIST / BUDGET_THREADS, BITS = 12;
+    static_assert(BLOCK == 4 * 64, "four waves a tile");
+    static_assert(1 << BITS == 4 * BUDGET_THREADS, "four digits a lane");
+    __shared__ uint4 hist4[BUDGET_THREADS];
+    __shared__ u32 smem[N_WAVES], found[3], n_few;
+    __shared__ u64 few[64], last;
+    u32* const hist = reinterpret_cast<u32*>(hist4);
+    const int t = threadIdx.x, lane = prim::lane_id();
+    int w = (int)blockIdx.x * BUDGET_THREADS + t;
+    const u64 counts = L->counts;
+    const u32 lo = L->lo, hi = L->hi;
+    const int go = st->go, keep = budget[0], n = pairs_of_mesh(mslots);
+    int m = w < nv ? mate[w] : -1;
+    const u32 n_below = (u32)(counts >> 32), listed = (u32)counts;
+    const bool binds = go != 0 && n > keep, found_it = (int)n_below < keep && keep <= (int)(n_below + listed) && listed <= (u32)BUDGET_LIST;
+    if ((int)blockIdx.x == publish.at) {
+        __syncthreads();  // (all have read it)
+        if (t == 0 && binds && !found_it) st->go = 0;
+        publish_pairs(publish, binds && !found_it);
+        return;
+    }
+    if (!binds || !found_it) return;
+    auto pair_key = [&]() { return m >= 0 ? ((u64)pcost[min(w, m)] << 32) | (u32)min(w, m) : 0ull; };
+    u64 own = pair_key();
+    u64 key[EACH];
+    const int each = (int)((listed + BUDGET_THREADS - 1) / BUDGET_THREADS);
+#pragma unroll
+    for (int j = 0; j < EACH; ++j) {
+        const u32 i = (u32)(j * BUDGET_THREADS + t);
+        key[j] = i < listed ? L->entry[i] : ~0ull;
+    }
+    // by counts of 12 bits a time, of the costs from the highest bit that there is, then of the vertices, until 64 or less are left, which one wave ranks
+    u32 want = (u32)keep - n_below, equal = listed;
+    int undecided = hi == lo ? 32 - __clz(nv) : 64 - __clz((int)(hi - lo));
+    u64 decided = undecided >= 64 ? 0ull : ~0ull << undecided, prefix = 0;
+    if (t == 0) n_few = 0;
+    hist4[t] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    while (equal > 64u && undecided > 0) {
+        const int nb = min(BITS, undecided > 32 ? undecided - 32 : undecided), shift = undecided - nb;
+#pragma unroll
+        for (int j = 0; j < EACH; ++j)
+            if (j < each) count_digit(hist, key[j] != ~0ull && (key[j] & decided) == prefix, (u32)(key[j] >> shift) & ((1u << nb) - 1u));
+        __syncthreads();
+        const uint4 c4 = hist4[t];
+        hist4[t] = make_uint4(0, 0, 0, 0);  // (for the next turn, behind the barriers that follow)
+        const u32 c[4] = {c4.x, c4.y, c4.z, c4.w};
+        u32 all, run = prim::wide_block_exclusive_scan<N_WAVES>((c[0] + c[1]) + (c[2] + c[3]), smem, all);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (run < want && want <= run + c[j]) {  // (in one thread)
+                found[0] = (u32)(4 * t + j);
+                found[1] = run;
+                found[2] = c[j];
+            }
+            run += c[j];
+        }
+        __syncthreads();
+        prefix |= (u64)found[0] << shift;
+        want -= found[1];
+        equal = found[2];
+        undecided = shift == 32 ? 32 - __clz(nv) : shift;
+        decided = ~0ull << undecided;
+    }
+#pragma unroll
+    for (int j = 0; j < EACH; ++j)
+        if (key[j] != ~0ull && (key[j] & decided) == prefix) {
+            const u32 p = atomicAdd(&n_few, 1u);
+            if (p < 64u) few[p] = key[j];
+        }
+    __syncthreads();
+    if (t < 64) {
+        const int c = (int)min(n_few, 64u);
+        const u64 k = few[min(t, c - 1)];
+        u32 below = 0;
+        for (int i = 0; i < c; ++i) below += few[i] < k ? 1u : 0u;
+        if (t < c && below + 1u == want) last = k;
+    }
+    __syncthreads();
+    const u64 limit = last + ((u64)lo << 32);
+    for (;;) {
+        const bool released = m >= 0 && own > limit;  // (each end by its own lane)
+        if (released) mate[w] = -1;
+        const u64 stays = prim::ballot(w < nv && (m < 0 || released || m > w));
+        if (lane == 0) smem[t / 64] = (u32)__popcll(stays);
+        __syncthreads();
+        const int tile = w / BUDGET_THREADS * BUDGET_TILES + t;
+        if (t < BUDGET_TILES && tile < (nv + BLOCK - 1) / BLOCK)
+            tilesum[tile] = (int)((smem[4 * t] + smem[4 * t + 1]) + (smem[4 * t + 2] + smem[4 * t + 3]));
+        w += ((int)gridDim.x - 1) * BUDGET_THREADS;
+        if (w - t >= nv) break;
+        m = w < nv ? mate[w] : -1;
+        own = pair_key();
+        __syncthreads();
+    }
+}
 
 constexpr u64 ABID_NONE = ~0ull;
 

@@ -131,6 +131,7 @@ struct picasso_ctx {
     u64* abid = nullptr;   // per vertex: cheapest edge through which it could join a pair's cluster
     int* arep = nullptr;   // per vertex: representative of the cluster it joined, or -1
     int* aoff = nullptr;   // per vertex: the first of those that joined the cluster it represents, in joiners()
+    BudgetList* budget_list() const { return reinterpret_cast<BudgetList*>(abid); }  // (of line 11, which rounds by rings do not have)
     int* joiners() const { return reinterpret_cast<int*>(val32); }  // (free between the edges' sort and the next round)
     int* acand = nullptr;  // per mesh: vertices that could join
     int* arem = nullptr;   // per mesh: budget left after the pairs
@@ -586,9 +587,9 @@ void launch_facet_costs(picasso_ctx* c, hipStream_t s, int B, int round_, int cu
 #undef PICASSO_FACET_COSTS
 }
 
-// A round by rings up to its pairs (see ring_costs_kernel).
+// A round by rings up to its pairs (see ring_costs_kernel); budget: a budget step by budget_range_kernel follows.
 constexpr int SUITOR_WAVES = 8192;  // as many as the chip holds
-void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, int nv, int N, const SelArgs& sa) {
+void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur_, int nv, int N, const SelArgs& sa, BudgetList* budget) {
     const int par = round_ & 1;
     const RingRows in = c->ring[par ^ 1], out = c->ring[par];
     {
@@ -616,9 +617,9 @@ void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur
     }
     const int chunks = prim::compact_chunks_for(nv), tiles = prim::compact_tiles(nv, chunks);
     switch (chunks) {
-        case 1: pairs_kernel<1><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum); break;
-        case 4: pairs_kernel<4><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum); break;
-        default: pairs_kernel<16><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum);
+        case 1: pairs_kernel<1><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum, budget); break;
+        case 4: pairs_kernel<4><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum, budget); break;
+        default: pairs_kernel<16><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum, budget);
     }
     if (tiles > prim::COMPACT_MAX_SUMMED_TILES) prim::compact_scan_sums(s, nullptr, nv, c->tilesum);
 }
@@ -756,6 +757,14 @@ int status_from_err_bits(int bits) {
     if (bits & ERR_BIT_NONFINITE) return PICASSO_ERR_NONFINITE;
     return PICASSO_OK;
 }
+
+// The budget step of a single mesh in rounds by rings goes by budget_range_kernel between these (pairs there may be at most).  Below the first the search of one workgroup takes
+// no longer and the list has no room (it lies in a word a vertex); from 160 k pairs, of which 12 to 13 k are listed, the list is full with some 200 k.  In a batch the meshes'
+// searches share the chip already (16 meshes of 32 k vertices 18 us).
+constexpr int BUDGET_GROUPS = 255;  // workgroups that release, one a compute unit with the one that tells the host
+constexpr int BUDGET_CHIP_MIN = 1 << 13, BUDGET_CHIP_MAX = 1 << 18;
+static_assert((2 * BUDGET_CHIP_MIN + 2) * sizeof(u64) >= sizeof(BudgetList), "a word for each of its vertices (budget_list)");
+static_assert(2ll * BUDGET_CHIP_MAX <= (long long)BLOCK * prim::COMPACT_MAX_SUMMED_TILES, "tiles of one chunk");
 
 // Budget step: among a mesh's keys (its formed pairs, or the vertices that could join clusters by line 11) where there are more
 // of them than it may use (counts[b] > budgets[b]) the budgets[b] first ones in ascending (cost key, tie-break) order stay;
@@ -1115,7 +1124,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         // the facet set on its way.)
         constexpr int AHEAD_MAX_FACETS = 1 << 22;
         bool ahead_ok = !c->opt_absorb && !stats && c->opt_ahead && nf_bound <= AHEAD_MAX_FACETS;
-        bool ahead_budget = false;
+        bool ahead_budget = false, chip_budget = false;
         int seg_bound = 0;  // pairs of the largest mesh that may exceed its budget, at most
         if (ahead_ok) {
             bool likely = false;
@@ -1125,7 +1134,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                     likely |= 5ll * nrem[b] < 2ll * nvb[b];
                 }
             ahead_budget = seg_bound > 0;
-            if (ahead_budget && !(likely && seg_bound <= c->opt_trunc_block_max)) ahead_ok = false;
+            chip_budget = rings && B == 1 && seg_bound > BUDGET_CHIP_MIN && seg_bound <= BUDGET_CHIP_MAX && c->opt_trunc_block_max == TRUNC_BLOCK_CAP && !c->opt_trunc_width;
+            if (ahead_budget && !(likely && (chip_budget || seg_bound <= c->opt_trunc_block_max))) ahead_ok = false;
         }
         // Line 11's candidates likewise, where no budget step can come in front of them: one look of the host less (its counts come with the tail's;
         // should the tail hand back, they are made again).  Not in listed rounds, whose lists lie where the candidates go.
@@ -1186,15 +1196,25 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
         };
         bool recount = true;  // the tiles' survivors are still to be counted when the budget step, if any, is done
         if (rings) {
-            launch_ring_round(c, s, B, round, cur, nv_total, N, sa);
+            BudgetList* const listed = ahead_ok && ahead_budget && chip_budget ? c->budget_list() : nullptr;
+            launch_ring_round(c, s, B, round, cur, nv_total, N, sa, listed);
             const HostSignal done = next_signal(c);
             PairPublish publish{0, c->st, c->mslots, c->matched, nullptr, B, round > 0 ? c->nf_slots[round & 1] : nullptr, c->h_pin_dev, HDR_STATE_INTS + B, sa.host_check, done};
             const HostSignal nothing{nullptr, 0};
-            if (ahead_ok && ahead_budget) {
+            size_t clear_ahead = 0;
+            if (listed) {
+                const int parts = (nv_total + BUDGET_THREADS - 1) / BUDGET_THREADS;
+                publish.at = std::min(parts, BUDGET_GROUPS);
+                budget_range_kernel<<<parts, BUDGET_THREADS, 0, s>>>(c->pcost(), nv_total, c->st, c->mslots, c->nrem, listed);
+                budget_release_kernel<<<publish.at + 1, BUDGET_THREADS, 0, s>>>(c->pcost(), c->mate, nv_total, c->st, c->mslots, c->nrem, c->tilesum, listed, publish);
+                clear_ahead = slots_clear == 0 ? facet_slots((size_t)nf_bound) : 0;  // (likely the last contraction)
+                issue_contract(0, clear_ahead, false, true, nothing, true);
+            } else if (ahead_ok && ahead_budget) {
                 publish.at = B;
                 rc = pair_budget(c, s, tb, B, c->voff[cur], nv_total, seg_bound, 0, true, true, nothing, publish);
                 if (rc != PICASSO_OK) return rc;
-                issue_contract(0, 0, true, true, nothing);
+                clear_ahead = slots_clear == 0 ? facet_slots((size_t)nf_bound) : 0;
+                issue_contract(0, clear_ahead, true, true, nothing);
             } else if (ahead_ok) {
                 publish.done = c->done;
                 issue_contract(0, 0, false, true, nothing, true, publish);
@@ -1205,6 +1225,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             if ((rc = check_errors()) != PICASSO_OK) return rc;
             ahead = ahead_ok;
             recount = false;
+            if (listed && hst->missed) ahead = false;  // (nothing has been contracted, nor dissolved)
+            else if (!hst->wide) slots_clear = std::max(slots_clear, clear_ahead);
             if (hst->wide) {  // a row did not fit: this round and those behind it by facets
                 rings = false;
                 fresh = round > 0;

@@ -1,0 +1,69 @@
+"""The budget step of a single mesh by the whole chip (rounds by rings) against the oracle, to the bit: either side of the sizes from which and up to which it is taken, budgets of
+one pair to all but one, costs that are all equal (fewer and more than the list holds), and costs that the sample does not show."""
+import numpy as np
+import pytest
+
+from paper_2103_15076_amd import meshgen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def pk():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2103_15076_amd
+    return paper_2103_15076_amd
+
+
+def check(pk, oracle, V, F, targets):
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    v, f = torch.from_numpy(V).to("cuda:0"), torch.from_numpy(F).to("cuda:0")
+    for target in targets:
+        ref = oracle.decimate(V, F, target)
+        st, vo, fo, cid = ctx.picasso_decimate(v, f, target)
+        assert st == ref["status"]
+        np.testing.assert_array_equal(cid.cpu().numpy(), ref["cluster_id"])
+        np.testing.assert_array_equal(fo.cpu().numpy(), ref["facets"])
+        np.testing.assert_array_equal(vo.cpu().numpy().view(np.uint32), ref["verts"].view(np.uint32))
+
+
+# 16,384 vertices: 8,192 pairs at most, by one workgroup; 16,512 just beyond; 65,536 and 65,792 the most and the fewest that are sampled at one and at four places a lane
+@pytest.mark.parametrize("w,h", [(128, 128), (129, 128), (256, 256), (257, 256), (431, 300)])
+def test_sizes_and_budgets(pk, oracle, w, h):
+    V, F = meshgen.noisy_grid(w, h, seed=w)
+    n = len(V)
+    check(pk, oracle, V, F, [n - 1, n - 17, int(0.97 * n), int(0.75 * n), int(0.61 * n), int(0.58 * n), int(0.35 * n), int(0.2 * n)])
+
+
+def test_most_pairs(pk, oracle):
+    """524,288 vertices, the most that are taken, and 1,024 more."""
+    for w in (1024, 1026):
+        V, F = meshgen.noisy_grid(w, 512, seed=w)
+        check(pk, oracle, V, F, [int(0.8 * len(V))])
+
+
+@pytest.mark.parametrize("w,h", [(140, 140), (220, 200)])
+def test_equal_costs(pk, oracle, w, h):
+    """8,000 to 10,000 pairs of one cost are listed and go by their vertices; 20,000 do not fit the list."""
+    V, F = meshgen.noisy_grid(w, h, seed=1)
+    V[:, 2] = 0
+    check(pk, oracle, V, F, [int(0.9 * len(V)), int(0.7 * len(V))])
+
+
+def test_half_of_equal_costs(pk, oracle):
+    V, F = meshgen.noisy_grid(300, 300, seed=4)
+    V[: 300 * 90, 2] = 0
+    check(pk, oracle, V, F, [int(f * len(V)) for f in (0.95, 0.88, 0.86, 0.7)])
+
+
+@pytest.mark.parametrize("rough_at_sample", [True, False])
+def test_sample_misleads(pk, oracle, rough_at_sample):
+    """The vertices at the places of the sample, 4 of every 64, lie where the surface is much rougher or smoother than elsewhere."""
+    V, F = meshgen.noisy_grid(256, 256, seed=9)
+    rng = np.random.default_rng(5)
+    near = (np.arange(len(V)) + 2) % 64 < 8
+    V[:, 2] = rng.normal(size=len(V)) * np.where(near == rough_at_sample, 1e-1, 1e-4)
+    check(pk, oracle, V.astype(np.float32), F, [int(f * len(V)) for f in (0.97, 0.8, 0.7, 0.62)])
