@@ -181,7 +181,8 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  * round it runs in: nv vertices, nf facets, H = 3 nf half-edges, E distinct edges; N, F = the call's
  * input sizes):
  * In a call that needs the edges' numbers (shuffle, line 11), and in one that gives statistics and whose kernels are bracketed at the
- * same time, the edges of a round are sorted, in any other one its rounds go by facets (edges met once per facet that has them) and SORT does not run.
+ * same time, the edges of a round are sorted; in any other one SORT does not run, and rounds go by rings (every vertex keeps its facets) on meshes of up to
+ * 2.25 facets a vertex, else, and in calls for statistics, by facets (edges met once per facet that has them).
  *   SORT          per-bucket kernel of the edge-key sort (Alg. 2 line 1): every key read once as a 4-byte
  *                 word, 4 H, the distinct ones written, 4 E.
  *   UNIQUE_COST   costs (Alg. 2 line 2) and first bids of the distinct edges: 4 E read + 13 E (edge key, cost
@@ -189,15 +190,19 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  *                 By facets (facet_costs_kernel): 24 nf (corners read, sides' cost keys written) + 72 nv; behind the first round
  *                 the same kernel takes the facets to the new numbering: 12 nf of the round before + 24 nf + 4 nv (vertex map) of the
  *                 round before + 80 nv (another bid word), from the third on + 8 N (labels).
+ *                 By rings (ring_costs_kernel): 152 nv (record, ring, neighbours' costs, two bid words); behind the first round, which takes the rings to the new
+ *                 numbering, 36 nv of the round before (its rings, the vertex map) + 176 nv, from the third on + 8 N (labels).
  *   SUBROUND0     first grid-wide sub-round of the selection (Alg. 2 lines 3-10): 13 E read, E
  *                 written (edge states), 3 x 8 nv (bids read, next bids written, third array cleared).
  *                 By facets (select_facets_kernel): 24 nf + 32 nv (the same, and the pairs' two arrays started).
+ *                 By rings (suitor_kernel, the whole matching): 16 nv (every vertex's first bid and the one on its neighbour); what the bettered ones ask
+ *                 beyond that goes by the mesh.
  *   FACET_INSERT  the kernel that takes the facets to the numbering a round leaves.  Behind every round but the
  *                 last (rounds of sorted edges only) edge_keys_kernel (facets re-indexed in place, labels composed, the next round set up,
  *                 edge keys' digits counted): 24 nf + 4 nv (vertex map) + 8 N (labels) + 24 nv' (two bid words,
  *                 mate and pair cost for each of the nv' vertices left).  Behind the last final_facets_kernel
  *                 (the same, facets entered into the hash set, positions written): 28 nf (a slot number
- *                 each) + 4 nv + 8 N + 28 nv'.
+ *                 each) + 4 nv + 8 N + 28 nv'; by rings, where it reads the call's own facets, 12 F + 16 nf in place of 28 nf.
  *   QUADRIC_ROWS  per-bucket kernel of the sort of the (vertex, facet) incidence keys, which sums the vertices' quadrics
  *                 from the facets' planes (supplementary, vertex quadric equation): 4 x 3F keys + 16 F planes
  *                 + 12 N positions + 64 N records.

@@ -43,8 +43,8 @@ PICASSO_PLACE_MEAN, PICASSO_PLACE_INVERSE = 0, 1
  PICASSO_KERNEL_QUADRIC_ROWS, PICASSO_KERNEL_SORT_INCIDENCE, PICASSO_KERNEL_COUNT) = range(7)
 TIMED_KERNEL_NAMES = (
     "bucket_keys_kernel (edge-key sort, per-bucket LDS sort, distinct edges)",
-    "facet_costs_kernel; of sorted edges unique_cost_kernel (costs, first bids)",
-    "select_facets_kernel; of sorted edges select_subround_kernel, select_first_kernel (first sub-round of the selection)",
+    "ring_costs_kernel, facet_costs_kernel; of sorted edges unique_cost_kernel (costs, first bids)",
+    "suitor_kernel (the whole matching), select_facets_kernel; of sorted edges select_subround_kernel, select_first_kernel (first sub-round of the selection)",
     "final_facets_kernel; behind rounds of sorted edges edge_keys_kernel (facets and labels re-indexed; behind the last: facet hash set)",
     "bucket_keys_kernel (incidence-key sort, per-bucket LDS sort, vertex quadrics from facet planes)",
     "msd_scatter_kernel, xl_scatter_kernel (incidence-key sort, partition)",

@@ -1490,13 +1490,15 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                 case PICASSO_KERNEL_SORT: bytes = 4.0 * H + 4.0 * ne; break;
                 case PICASSO_KERNEL_UNIQUE_COST:
                     if (!by_facets) bytes = 17.0 * ne + 72.0 * nv;
+                    else if (rings && rd == 0) bytes = 152.0 * nv;
+                    else if (rings) bytes = 36.0 * (double)c->nv_round[rd - 1] + 176.0 * nv + (rd > 1 ? 8.0 * (double)N : 0.0);
                     else if (rd == 0) bytes = 24.0 * nf + 72.0 * nv;
                     else bytes = 12.0 * (double)c->nf_round[rd - 1] + 24.0 * nf + 4.0 * (double)c->nv_round[rd - 1] + 80.0 * nv + (rd > 1 ? 8.0 * (double)N : 0.0);
                     break;
-                case PICASSO_KERNEL_SUBROUND0: bytes = by_facets ? 24.0 * nf + 32.0 * nv : 14.0 * ne + 24.0 * nv; break;
+                case PICASSO_KERNEL_SUBROUND0: bytes = rings ? 16.0 * nv : by_facets ? 24.0 * nf + 32.0 * nv : 14.0 * ne + 24.0 * nv; break;
                 case PICASSO_KERNEL_FACET_INSERT:  // (the last round's is another kernel)
                     if (rd + 1 < c->n_rounds_noted) bytes = 24.0 * nf + 4.0 * nv + 8.0 * (double)N + 24.0 * (double)c->nv_round[rd + 1];
-                    else bytes = 28.0 * nf + 4.0 * nv + 8.0 * (double)N + (drop ? 0.0 : 28.0 * (double)nv_total);
+                    else bytes = (rings ? 12.0 * (double)F + 16.0 * nf : 28.0 * nf) + 4.0 * nv + 8.0 * (double)N + (drop ? 0.0 : 28.0 * (double)nv_total);
                     break;
                 case PICASSO_KERNEL_SORT_INCIDENCE: bytes = 24.0 * (double)F; break;
                 default: bytes = 12.0 * (double)F + 16.0 * (double)F + 76.0 * (double)N; break;  // QUADRIC_ROWS
