@@ -2374,6 +2374,7 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
     }
     if (blockIdx.x == 0 && t < MATCH_SLOTS) facet_next[t * MATCH_PAD] = 0;
     if (R.B > 1) M.begin(R, nullptr);
+    const int hopeless = FIRST ? st->wide : 0;  // (a vertex of the input has more facets than a row takes: the round goes by facets, and this launch has nothing to do)
     own = load_vertex(vrec, v);
     if constexpr (FIRST) {
         info = in.info[v];
@@ -2435,6 +2436,7 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         }
     }
     if (!FIRST || R.B > 1) __syncthreads();
+    if (FIRST && __any(hopeless)) return;
     const bool active = here && (R.B <= 1 || M.is_active(R, v)), in_rows = here && ring_in_rows(info);
     auto neighbour = [&](int u, const VertexWords& U, int x, const VertexWords& X) -> u32 {
         return u == x ? PAIR_NONE : cost_key(pair_cost<PLACE>(U, X, rcond_min));
@@ -3070,6 +3072,21 @@ __global__ __launch_bounds__(BUDGET_THREADS) void budget_release_kernel(const u3
         own = pair_key();
         __syncthreads();
     }
+}
+
+// Where a round by rings has found a vertex that fits no row: what the round by facets in its place takes (the facets, no bids, no count of facets).  A copy and three fills
+// instead took 10 us longer at 1.2 M vertices, 1 to 7 at 115 k and as long at 4 k.
+__global__ __launch_bounds__(BLOCK) void facets_again_kernel(const int* __restrict__ facets, int F, int* __restrict__ fcur, int nv, u64* __restrict__ vmin0,
+                                                             u64* __restrict__ vmin1, int* __restrict__ facet_slots) {
+    const int g = blockIdx.x * BLOCK + threadIdx.x, stride = gridDim.x * BLOCK;
+    if (g < MATCH_SLOTS) facet_slots[g * MATCH_PAD] = 0;
+    for (long long f = g; f < F; f += stride) {
+        const Corners q = load_corners(facets, (size_t)f);
+        fcur[3 * f] = q.a;
+        fcur[3 * f + 1] = q.b;
+        fcur[3 * f + 2] = q.c;
+    }
+    for (long long v = g; v < nv; v += stride) vmin0[v] = vmin1[v] = VMIN_NONE;
 }
 
 constexpr u64 ABID_NONE = ~0ull;

@@ -1009,6 +1009,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // the facets, by facets.  By facets | by rings, us: lattices of 20 k vertices to a quarter 184 | 147, of 400 k 381 | 307, an icosphere of 164 k 385 | 249, facets permuted, 115 k
     // 389 | 243, 2.25 M 4,179 | 2,663, vertices as well 407 | 265, 4,928 | 4,106, a flat lattice of 116 k 8,694 | 1,867.  But two-sided lattices (twelve facets a vertex,
     // whose rings lie in rows) of 40 k 210 | 437, 20 k vertices with 60 k facets of any three of them 375 | 621.
+    // A vertex of more than 64 facets, which the host cannot see beforehand, sends its call back to rounds by facets: spheres of segments and rings, whose two poles are such,
+    // of 4 k vertices to a quarter 171 | 190, of 115 k 280 | 306, of 1.2 M 1,149 | 1,205; poles of 60, whose rings lie in long rows first, 164 | 222.
     bool rings = by_facets && !stats && work && F > 0 && 4ll * F <= 9ll * N && N < RING_VERTICES;
     bool fresh = false;  // (see launch_facet_costs)
     const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
@@ -1230,9 +1232,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             if (hst->wide) {  // a row did not fit: this round and those behind it by facets
                 rings = false;
                 fresh = round > 0;
-                HIP_TRY(c, hipMemcpyAsync(c->fcur, d_facets, sizeof(int) * 3 * (size_t)F, hipMemcpyDeviceToDevice, s));
-                for (int i = 0; i < 2; ++i) prim::fill_u32_kernel<<<grid_for(2ll * nv_total), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->vmin[i]), 2 * nv_total, ~0u);
-                prim::fill_u32_kernel<<<grid_for(MATCH_SLOTS * MATCH_PAD), BLOCK, 0, s>>>(reinterpret_cast<u32*>(c->nf_slots[round & 1]), MATCH_SLOTS * MATCH_PAD, 0u);
+                facets_again_kernel<<<grid_for(std::max(nv_total, F), 4096), BLOCK, 0, s>>>(d_facets, F, c->fcur, nv_total, c->vmin[0], c->vmin[1], c->nf_slots[round & 1]);
                 renumbered = was_renumbered;
                 continue;
             }
