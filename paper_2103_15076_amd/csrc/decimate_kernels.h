@@ -39,7 +39,9 @@ struct State {
     int sel_k;     // sub-round index the selection has reached (buffer rotation phase)
     int absorb_n;  // edges through which an un-paired vertex would join a pair's cluster (Alg. 2 line 11)
     int nv_kept;   // output vertices that some output facet refers to (option: degenerated vertices dropped)
-    int wide;      // rounds by rings: a vertex has more facets or neighbours than a row takes
+    int wide;      // rounds by rings: this round goes by facets (most vertices of the input are no surface's, or there was no place left for a vertex's facets)
+    int row_words;   // ... facets of rings in rows (given to the host only)
+    int longest[2];  // ... of the longest one of more than 64, by the round's parity
     int missed;    // ... the budget's last pair is not among those that budget_range_kernel has listed
     // Written by every selection tail for kernels that the host queued behind it before looking
     // (they run only if the tail finished the matching): 1 / nv of the round then, else zeros.
@@ -324,7 +326,7 @@ struct DigitTally<COUNT_NONE> {
     __device__ __forceinline__ void flush(const DigitCount&) {}
 };
 
-constexpr int RINGS_TAKEN = 3 * 33 * MATCH_PAD;  // counters of the rings' rows (RingRows): two sets of rings, one of neighbours
+constexpr int RINGS_TAKEN = 2 * 33 * MATCH_PAD;  // counters of the rings' rows (RingRows): two sets of rings
 enum { EDGES_NONE = 0, EDGES_BY_FACETS = 1, EDGES_SORTED = 2 };
 template <int COUNT, bool SORTED, class Tables>
 __global__ __launch_bounds__(BLOCK) void init_kernel(const float* __restrict__ verts, int N,
@@ -567,52 +569,55 @@ __device__ __forceinline__ void add_plane_quadric(float (&acc)[10], const float4
 // The rings of rounds by rings (see ring_costs_kernel): per vertex the facets that have it, each as its other two corners.  Of up to RING_MAX facets that name up to
 // RING_MAX vertices, as nearly always, these vertices are noted, RING_ROW of them in a row of 32 bytes (`ids`), the others beside (`more`): facet i's first corner is the i-th of
 // them, its second one that of the number that info gives.  (A ring is found from its vertex alone, most of them in one access.)  Other rings are noted facet by facet (first
-// corner | second corner << 32), up to ROW_SMALL of them in a row of one size, up to ROW_MAX in one of the other.  Scanned surfaces have 0 % of vertices with more than 8
-// facets at first and 3 % once they have been decimated, 0.1 % with more than 10: with eight at most a ladder of four levels of 16 meshes took 1,099 us.
-// info: vertices | facets << 4 | numbers, four bits each, << 8; of other rings RING_ROWS | facets << 4 | row << 12.
-// Neighbours with their costs lie the same way: of short rings as rows of the costs in `ids` and `more`, of others as (cost << 32 | neighbour), info: RING_ROWS | how many << 4 | row << 12.
+// corner | second corner << 32), one behind the other, in `rows`: those of the input where their incidences lie among all, so that there is a place for each, later ones where
+// counters say.  Scanned surfaces have 0 % of vertices with more than 8 facets at first and 3 % once they have been decimated, 0.1 % with more than 10: with eight at most a
+// ladder of four levels of 16 meshes took 1,099 us.
+// info: vertices | facets << 4 | numbers, four bits each, << 8; of other rings RING_ROWS | facets << 4 | where in `rows` << 32.
+// The neighbours' costs lie the same way: of short rings in `ids` and `more`, of others beside the facets (first corner's | second corner's << 32, PAIR_NONE where the second one is
+// a facet's first).  info of the neighbours, for up to ROW_SMALL facets: how many of them may have a second corner's cost (none or all) | facets << 8.
 constexpr int RING_VERTICES = 1 << 28;  // (rounds by rings take fewer vertices)
 constexpr int RING_MAX = 10, RING_ROW = 8, RING_MORE = RING_MAX - RING_ROW;
 constexpr u32 RING_ROWS = 15;
-constexpr int ROW_LINE = 8, ROW_SMALL = 16, ROW_MAX = 64;
-__device__ __forceinline__ u64 rows_info(int n, u32 row) { return RING_ROWS | ((u32)n << 4) | (row << 12); }
-__device__ __forceinline__ int rows_length(u64 info) { return (int)((u32)info >> 4 & 255u); }
-__device__ __forceinline__ u32 rows_number(u64 info) { return (u32)info >> 12; }
+constexpr int ROW_LINE = 8, ROW_SMALL = 16;  // (up to ROW_SMALL facets are a pair of lanes' and a quarter of a wave's work, more a wave's)
+__device__ __forceinline__ u64 rows_info(int n, u32 at) { return (u64)(RING_ROWS | ((u32)n << 4)) | ((u64)at << 32); }
+__device__ __forceinline__ int rows_length(u64 info) { return (int)((u32)info >> 4); }
+__device__ __forceinline__ u32 rows_at(u64 info) { return (u32)(info >> 32); }
 __device__ __forceinline__ u64 ring_info(int vertices, int facets, u64 numbers) { return (u64)((u32)vertices | ((u32)facets << 4)) | (numbers << 8); }
 __device__ __forceinline__ bool ring_in_rows(u64 info) { return ((u32)info & 15u) == RING_ROWS; }
 __device__ __forceinline__ int ring_ids(u64 info) { return (int)((u32)info & 15u); }  // (of a short ring)
-__device__ __forceinline__ int ring_facets(u64 info) { return (int)((u32)info >> 4 & (ring_in_rows(info) ? 255u : 15u)); }
+__device__ __forceinline__ int ring_facets(u64 info) { return ring_in_rows(info) ? rows_length(info) : (int)((u32)info >> 4 & 15u); }
 __device__ __forceinline__ int ring_second(u64 info, int i) { return (int)((u32)(info >> (8 + 4 * i)) & 15u); }
-// Small rows are handed out in parts, each with a counter in a cache line of its own (a line takes an atomic every 11 ns).
+// Places in rows are handed out in parts, each with a counter in a cache line of its own (a line takes an atomic every 11 ns); those that are too long for a part come from the
+// rest, as do those that find no room in a few parts.
 constexpr int ROW_ARENAS = 32, ROW_TRIES = 4;
-static_assert(RINGS_TAKEN == 3 * (ROW_ARENAS + 1) * MATCH_PAD, "a counter each");
+static_assert(RINGS_TAKEN == 2 * (ROW_ARENAS + 1) * MATCH_PAD, "a counter each");
 struct RingRows {
     u32* ids;
     u32* more;
     u64* info;
-    u64* small;
-    u64* large;
-    int* taken;  // [ROW_ARENAS + 1][MATCH_PAD]: small rows in use of each part, then large ones
-    int arena_rows, large_rows;
-    int* wide;   // set where there is no row
-    __device__ __forceinline__ u64* row(int n, u32 number) const {
-        return n <= ROW_SMALL ? small + (size_t)number * ROW_SMALL : large + (size_t)number * ROW_MAX;
+    u64* rows;   // as many as the input has corners
+    int* taken;  // [ROW_ARENAS + 1][MATCH_PAD]: words in use of each part, then of the rest
+    u32 arena_words, rest_words;
+    int* wide;   // set where there is no place
+    // By one lane: a place of that many words, ~0u where there is none; asked for first, then looked at, so that the atomic's trip need not be waited for in between.
+    __device__ __forceinline__ u32 ask(u32 words) const {
+        const u32 part = words <= arena_words ? blockIdx.x & (ROW_ARENAS - 1) : (u32)ROW_ARENAS;
+        return (u32)atomicAdd(&taken[part * MATCH_PAD], (int)words);
     }
-    __device__ __forceinline__ u64* row_of(u64 info_) const { return row(rows_length(info_), rows_number(info_)); }
-    // A row for n entries; n comes back 0 where there is none.
-    __device__ __forceinline__ u32 take_row(int& n) const {
-        if (n <= ROW_SMALL) {
-            for (int k = 0; k < ROW_TRIES; ++k) {
-                const int arena = (int)(blockIdx.x + k) & (ROW_ARENAS - 1), at = atomicAdd(&taken[arena * MATCH_PAD], 1);
-                if (at < arena_rows) return (u32)(arena * arena_rows + at);
+    __device__ __forceinline__ u32 take(u32 words, u32 asked) const {
+        u32 at = asked;
+        if (words <= arena_words) {
+            for (int k = 0;; ++k) {
+                const u32 arena = (blockIdx.x + k) & (ROW_ARENAS - 1);
+                if (k > 0) at = (u32)atomicAdd(&taken[arena * MATCH_PAD], (int)words);
+                if ((u64)at + words <= arena_words) return arena * arena_words + at;
+                if (k + 1 == ROW_TRIES) break;
             }
-        } else if (n <= ROW_MAX) {
-            const int at = atomicAdd(&taken[ROW_ARENAS * MATCH_PAD], 1);
-            if (at < large_rows) return (u32)at;
+            at = (u32)atomicAdd(&taken[ROW_ARENAS * MATCH_PAD], (int)words);
         }
+        if ((u64)at + words <= rest_words) return ROW_ARENAS * arena_words + at;
         *wide = 1;
-        n = 0;
-        return 0;
+        return ~0u;
     }
     // n: how many there are (of a row the first RING_ROW are fetched whatever n is)
     __device__ __forceinline__ void load_ids(int v, u32 (&x)[RING_MAX], int n) const {
@@ -639,7 +644,7 @@ struct RingRows {
     __device__ __forceinline__ void load_facet(int v, u64 info_, int i, u32& a, u32& b) const {
         const u32 *p, *q;
         if (ring_in_rows(info_)) {
-            p = reinterpret_cast<const u32*>(row_of(info_) + i);
+            p = reinterpret_cast<const u32*>(rows + rows_at(info_) + i);
             q = p + 1;
         } else {
             p = place(v, i);
@@ -699,6 +704,8 @@ struct QuadricRows {
     int N, fbits;
     const int* facets;
     RingRows ring;
+    int* unfit;       // [ROW_ARENAS][MATCH_PAD]: vertices of few facets with more neighbours than a short ring has, as where facets are any three vertices; zero at the start
+    int unfit_limit;  // ... of a part, from which on the call goes by facets
     template <int THREADS, int ITEMS>
     struct Lds {
         unsigned short start[THREADS / 64][QR_WINDOW];  // (within the window)
@@ -708,8 +715,9 @@ struct QuadricRows {
     // Mostly a group of the sort is a vertex: a lane then sorts its vertex's keys in registers and goes on with them (up to
     // GROUP_LANE keys; a wave sorts more).  (With the groups sorted in LDS and the vertices found again among the keys 115 k vertices took 12.3 us, now 9.6, 1.2 M
     // 49 and 42.5, 10.2 M 450 and 421.)
-    // (With the rings the compiler takes 118 registers, for four waves: 1.2 M vertices 69 us, with 80 for six 63; of a decimated mesh of 384 k 34 and 27.)
-    static constexpr int MIN_WAVES = RINGS ? 6 : 1;
+    // (With the rings the compiler takes 118 registers, for four waves: 1.2 M vertices 69 us, with 96 for five 63; of a decimated mesh of 384 k 34 and 28.  With 80 for six it spills:
+    // as long there, but 16 spheres with poles of 128 facets, whose buckets are sorted whole, 73 us for 63.)
+    static constexpr int MIN_WAVES = RINGS ? 5 : 1;
     static constexpr bool GROUPS_SORTED = false;
     static constexpr int GROUP_SHORT = 8, GROUP_LANE = 16;  // (sizes of a lane's sort)
     __device__ bool rows_are_groups(bool, const prim::Bucket& b, int R) const { return (1 << (b.low_bits - fbits)) == R && b.low_bits > fbits; }
@@ -730,37 +738,38 @@ struct QuadricRows {
                 if (j0 + j < g) add_plane_quadric(acc, p[j]);
         }
     }
-    // The ring of a group that a lane has sorted, in any order of its facets.  (By itself, behind the quadrics of all groups: together they take 140 registers.)
+    // The ring of a group that a lane has sorted, in any order of its facets, the first of which is the bucket's incidence `start`.  (By itself, behind the quadrics of all groups:
+    // together they take 140 registers.)
     template <int G, typename LK>
-    __device__ __forceinline__ u64 ring_of_group(const prim::Bucket& b, const LK* key, int g, int v) const {
+    __device__ __forceinline__ u64 ring_of_group(const prim::Bucket& b, const LK* key, int g, int v, const u32* start) const {
         if constexpr (G <= RING_MAX) {
             u64 e[G];
 #pragma unroll
             for (int j = 0; j < G; ++j) e[j] = j < g ? ring_entry_of(load_given(facets, b.item(key[j], fbits), N), v) : 0ull;
-            return leave_ring(v, e, g);
+            return leave_ring(v, e, g, [&] { return b.start + *start; });
         } else {
-            const u32 number = ring.take_row(g);
-            u64* const row = ring.row(g, number);
+            const u32 at = b.start + *start;
+            u64* const row = ring.rows + at;
 #pragma unroll 8
             for (int j = 0; j < g; ++j) row[j] = ring_entry_of(load_given(facets, b.item(key[j], fbits), N), v);
-            return rows_info(g, number);
+            return rows_info(g, at);
         }
     }
     // the ring of up to N facets
-    template <int N>
-    __device__ __forceinline__ u64 leave_ring(int v, const u64 (&e)[N], int g) const {
+    template <int N, class At>
+    __device__ __forceinline__ u64 leave_ring(int v, const u64 (&e)[N], int g, At where) const {
         u32 id[RING_MAX];
         const u64 info = make_ring(e, g, id);
         if (!ring_in_rows(info)) {
             ring.store_ids(v, id, ring_ids(info));
             return info;
         }
-        const u32 number = ring.take_row(g);
-        u64* const row = ring.row(g, number);
+        const u32 at = where();
+        u64* const row = ring.rows + at;
 #pragma unroll
         for (int j = 0; j < N; ++j)
             if (j < g) row[j] = e[j];
-        return rows_info(g, number);
+        return rows_info(g, at);
     }
     __device__ __forceinline__ void write(int v, const float (&acc)[10], u64 info) const {
         write_vertex_record(vrec, verts, v, acc);
@@ -782,27 +791,31 @@ struct QuadricRows {
             else add_group<GROUP_SHORT>(acc, b, lds.skey + gs, g);
             write_vertex_record(vrec, verts, lo + gi, acc);
         }
-        if constexpr (RINGS)
+        if constexpr (RINGS) {
+            int n_unfit = 0;
             for (int gi = t; gi < n; gi += THREADS) {
                 const int gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
                 if (g > GROUP_LANE) continue;
-                if (g > RING_MAX) ring.info[lo + gi] = ring_of_group<GROUP_LANE>(b, lds.skey + gs, g, lo + gi);
-                else if (__any(g > GROUP_SHORT)) ring.info[lo + gi] = ring_of_group<RING_MAX>(b, lds.skey + gs, g, lo + gi);
-                else ring.info[lo + gi] = ring_of_group<GROUP_SHORT>(b, lds.skey + gs, g, lo + gi);
+                u64 info;
+                if (g > RING_MAX) info = ring_of_group<GROUP_LANE>(b, lds.skey + gs, g, lo + gi, &lds.gstart[gi]);
+                else if (__any(g > GROUP_SHORT)) info = ring_of_group<RING_MAX>(b, lds.skey + gs, g, lo + gi, &lds.gstart[gi]);
+                else info = ring_of_group<GROUP_SHORT>(b, lds.skey + gs, g, lo + gi, &lds.gstart[gi]);
+                ring.info[lo + gi] = info;
+                n_unfit += g <= RING_MAX && ring_in_rows(info) ? 1 : 0;
             }
+            if (__any(n_unfit)) {
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1) n_unfit += __shfl_xor(n_unfit, d, 64);
+                if (lane == 0 && atomicAdd(&unfit[(b.number & (ROW_ARENAS - 1)) * MATCH_PAD], n_unfit) > unfit_limit) *ring.wide = 1;
+            }
+        }
         __syncthreads();
         for (int li = prim::wave_id(); li < (int)lds.nlong; li += THREADS / 64) {
             const int gi = (int)lds.gcnt[li], gs = (int)lds.gstart[gi], g = (int)lds.gstart[gi + 1] - gs;
             prim::rank_group_lds(lds.skey + gs, g);
-            int n = g;
-            u32 number = 0;
-            if constexpr (RINGS) {
-                if (lane == 0) number = ring.take_row(n);
-                n = __shfl(n, 0, 64);
-                number = (u32)__shfl((int)number, 0, 64);
-                u64* const row = ring.row(n, number);
-                for (int j = lane; j < n; j += 64) row[j] = ring_entry_of(load_given(facets, b.item(lds.skey[gs + j], fbits), N), lo + gi);
-            }
+            if constexpr (RINGS)
+                for (int j = lane; j < g; j += 64)
+                    ring.rows[b.start + (u32)(gs + j)] = ring_entry_of(load_given(facets, b.item(lds.skey[gs + j], fbits), N), lo + gi);
             if (lane == 0) {
                 float acc[10] = {};
                 for (int j0 = 0; j0 < g; j0 += 8) {
@@ -814,7 +827,7 @@ struct QuadricRows {
                     for (int j = 0; j < 8; ++j)
                         if (j0 + j < g) add_plane_quadric(acc, p[j]);
                 }
-                write(lo + gi, acc, rows_info(n, number));
+                write(lo + gi, acc, rows_info(g, b.start + (u32)gs));
             }
         }
     }
@@ -856,48 +869,52 @@ struct QuadricRows {
                 m += (int)__popcll(bal);
             }
             __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations complete in order)
-            for (int r = lane; r < m; r += 64) {
-                const int hp = base + (int)list[r], v = vertex_at(hp);
-                int end;
-                if (r + 1 < m) {
-                    end = base + (int)list[r + 1];
-                } else {
-                    end = min(base + QR_WINDOW, n);
-                    while (end < n && vertex_at(end) == v) ++end;
-                }
-                const int pv = hp > 0 ? vertex_at(hp - 1) : lo - 1;
-                if (pv + 1 < v) note_gap(pv + 1, v);
-                float acc[10];
-#pragma unroll
-                for (int k = 0; k < 10; ++k) acc[k] = 0.0f;
-                for (int j0 = hp; j0 < end; j0 += 8) {
-                    float4 p[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (j0 + j < end) p[j] = planes[b.item(key_at(j0 + j), fbits)];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (j0 + j < end) add_plane_quadric(acc, p[j]);
-                }
-                write_vertex_record(vrec, verts, v, acc);
-                if constexpr (RINGS) {
-                    int n_ring = end - hp;
-                    u64 info;
-                    if (n_ring <= RING_MAX) {
-                        u64 e[RING_MAX];
-#pragma unroll
-                        for (int j = 0; j < RING_MAX; ++j)
-                            e[j] = j < n_ring ? ring_entry_of(load_given(facets, b.item(key_at(hp + j), fbits), N), v) : 0ull;
-                        info = leave_ring(v, e, n_ring);
+            for (int r0 = 0; r0 < m; r0 += 64) {
+                const int r = r0 + lane;
+                int hp = 0, end = 0, v = 0;
+                if (r < m) {
+                    hp = base + (int)list[r];
+                    v = vertex_at(hp);
+                    if (r + 1 < m) {
+                        end = base + (int)list[r + 1];
                     } else {
-                        const u32 number = ring.take_row(n_ring);
-                        u64* const row = ring.row(n_ring, number);
-                        info = rows_info(n_ring, number);
-                        for (int j = 0; j < n_ring; ++j) row[j] = ring_entry_of(load_given(facets, b.item(key_at(hp + j), fbits), N), v);
+                        end = min(base + QR_WINDOW, n);
+                        while (end < n && vertex_at(end) == v) ++end;
                     }
-                    ring.info[v] = info;
+                    const int pv = hp > 0 ? vertex_at(hp - 1) : lo - 1;
+                    if (pv + 1 < v) note_gap(pv + 1, v);
+                    float acc[10];
+#pragma unroll
+                    for (int k = 0; k < 10; ++k) acc[k] = 0.0f;
+                    for (int j0 = hp; j0 < end; j0 += 8) {
+                        float4 p[8];
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if (j0 + j < end) p[j] = planes[b.item(key_at(j0 + j), fbits)];
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if (j0 + j < end) add_plane_quadric(acc, p[j]);
+                    }
+                    write_vertex_record(vrec, verts, v, acc);
+                    if (end == n && v + 1 < hi) note_gap(v + 1, hi);
+                    if constexpr (RINGS)
+                        if (end - hp <= RING_MAX) {
+                            u64 e[RING_MAX];
+#pragma unroll
+                            for (int j = 0; j < RING_MAX; ++j)
+                                e[j] = j < end - hp ? ring_entry_of(load_given(facets, b.item(key_at(hp + j), fbits), N), v) : 0ull;
+                            ring.info[v] = leave_ring(v, e, end - hp, [&] { return b.start + (u32)hp; });
+                        } else {
+                            ring.info[v] = rows_info(end - hp, b.start + (u32)hp);
+                        }
                 }
-                if (end == n && v + 1 < hi) note_gap(v + 1, hi);
+                if constexpr (RINGS)  // (the facets of the others, one after the other by all lanes)
+                    for (u64 todo = prim::ballot(end - hp > RING_MAX); todo != 0; todo &= todo - 1) {
+                        const int from = __ffsll((long long)todo) - 1, first = __shfl(hp, from, 64), last = __shfl(end, from, 64), its = __shfl(v, from, 64);
+#pragma unroll 4
+                        for (int j = first + lane; j < last; j += 64)
+                            ring.rows[b.start + (u32)j] = ring_entry_of(load_given(facets, b.item(key_at(j), fbits), N), its);
+                    }
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -2302,37 +2319,37 @@ __global__ void signal_kernel(HostSignal done) {
 // so on.  Bids only improve, so a neighbour that has refused a vertex once need not be asked again, no vertex waits for another, and what is left when all
 // have ended does not depend on the order.  In the end two vertices are a pair if each holds the other's bid.
 // ---------------------------------------------------------------------------
-constexpr int RING_THREADS = 128, RING_GROUP = 16;
+constexpr int RING_THREADS = 128;
 constexpr u64 BID_COST = 0xFFFFFFFF00000000ull;  // the cost key of a bid or a neighbour's entry; below it a vertex
-
-__device__ __forceinline__ void load_line(u64 (&x)[ROW_LINE], const u64* p) {
-    const ulonglong2* q = reinterpret_cast<const ulonglong2*>(p);
-#pragma unroll
-    for (int j = 0; j < ROW_LINE; j += 2) {
-        const ulonglong2 two = q[j / 2];
-        x[j] = two.x;
-        x[j + 1] = two.y;
-    }
-}
 
 // what the other lane of a pair holds
 __device__ __forceinline__ u32 of_pair(u32 x) { return (u32)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true); }  // (quad_perm 1, 0, 3, 2)
 __device__ __forceinline__ u64 of_pair(u64 x) { return ((u64)of_pair((u32)(x >> 32)) << 32) | of_pair((u32)x); }
 
+// ... and the next one of a row of 16, or the first one
+__device__ __forceinline__ u32 next_in_row(u32 x) { return (u32)__builtin_amdgcn_mov_dpp((int)x, 0x12F, 0xF, 0xF, true); }  // (row_ror 15)
+
 constexpr int RING_TILE = RING_THREADS / 2;    // vertices of a workgroup
 constexpr int RING_LABELS = 4 * RING_THREADS;  // labels of one of the workgroups behind those of the vertices
 
-// Two lanes a vertex: each takes over the ring of one of the two that the vertex was made of, then evaluates every other neighbour.
+// Two lanes a vertex: each takes over the ring of one of the two that the vertex was made of, then evaluates every other neighbour.  Rings that stay in rows of up to ROW_SMALL facets
+// are made the same way and evaluated four at a time, a facet a lane; longer ones by the whole wave, 128 facets a turn, one ring after the other.  (Hubs of the input by workgroups of
+// their own: a cone of 4,000 facets 1,604 us for 1,650, but every first round 1 us longer.)  With the rows of 11 to 64 facets made and evaluated in one turn of four after the other and a longer one given up for rounds by facets, spheres of segments and
+// rings (us a call to a quarter, by facets | then | now): 4 k vertices with poles of 48 facets 159 | 199 | 153, of 128 166 | 188 | 173, 115 k 279 | 304 | 232, 1.2 M 1,153 | 1,211 | 1,015;
+// 20 k vertices of a lattice of two sides among 159 k 257 | 298 | 229; a cone of 4,000 facets to 70 % 1,569 | 1,587 | 1,604.
+// Bound by the trips from vertex to ring to records, and where rows are rare by the fetching of their code: every step of them that was unrolled, or done twice for few and for
+// many, took the 30 % of a decimated mesh's waves that have a row 2 to 4 us longer.  Four waves a SIMD: with five 10 M vertices take 503 us in the first round, 469 with four (the parts' lines push each
+// other out of the L2).
 template <int PLACE, bool FIRST>
-__global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int nv, const VRec* __restrict__ vrec, RingRows in, RingRows out,
+__global__ __launch_bounds__(RING_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void ring_costs_kernel(State* st, int round, int nv, const VRec* __restrict__ vrec, RingRows in, RingRows out,
                                                                   RingRows adj, u64* __restrict__ first, u64* __restrict__ bids, RoundTab R,
                                                                   const int2* __restrict__ from, const ulonglong2* __restrict__ from_info,
                                                                   const int* __restrict__ vmap, int* __restrict__ cid, int n_labels, float rcond_min,
                                                                   int* __restrict__ facet_slots, int* __restrict__ facet_next) {
     __shared__ MeshFlags M;
     constexpr int HALF = RING_MAX / 2;
-    static_assert(64 / RING_GROUP * ROW_MAX <= 64 * RING_MAX, "the groups' rings fit the wave's part");
-    __shared__ u64 stages[RING_THREADS / 64][64 * RING_MAX];  // a wave's part: its lanes' vertices, then their facets, then the facets of the rings that its groups are at
+    static_assert(32 * ROW_SMALL <= 64 * RING_MAX, "rows of pairs fit the wave's part");
+    __shared__ u64 stages[RING_THREADS / 64][64 * RING_MAX];  // a wave's part: its lanes' vertices, then their pairs' facets
     __shared__ int facets;
     const int t = threadIdx.x, lane = prim::lane_id(), half = lane & 1;
     if constexpr (!FIRST) {  // (the labels follow the last contraction)
@@ -2354,15 +2371,21 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
             return;
         }
     }
+    auto neighbour = [&](int u, const VertexWords& U, int x, const VertexWords& X) -> u32 {
+        return u == x ? PAIR_NONE : cost_key(pair_cost<PLACE>(U, X, rcond_min));
+    };
     const int tiles = (nv + RING_TILE - 1) / RING_TILE, w = prim::xcd_item((int)blockIdx.x, tiles) * RING_TILE + t / 2, v = min(w, nv - 1);
     const bool here = w < nv, lead = here && half == 0;
     u64* const stage = stages[prim::wave_id()];
+    u64* const facet_of_pair = stage + lane / 2;  // (in rows of 32)
     auto in_order = [] {  // (a wave's LDS operations complete in order: what is to be kept in order is the compiler)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         __builtin_amdgcn_wave_barrier();
     };
     u64 info;
     u32 id[RING_MAX];
+    int k = 0;             // the facets of its ring, where they are in the pair's place or in a row
+    bool is_long = false;  // ... more than ROW_SMALL
     int2 two = make_int2(0, -1);
     ulonglong2 two_info = make_ulonglong2(0, 0);
     VertexWords own;
@@ -2374,16 +2397,22 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
     }
     if (blockIdx.x == 0 && t < MATCH_SLOTS) facet_next[t * MATCH_PAD] = 0;
     if (R.B > 1) M.begin(R, nullptr);
-    const int hopeless = FIRST ? st->wide : 0;  // (a vertex of the input has more facets than a row takes: the round goes by facets, and this launch has nothing to do)
+    const int hopeless = FIRST ? st->wide : 0;  // (the round goes by facets, and this launch has nothing to do)
     own = load_vertex(vrec, v);
+    u64 first_info = 0;
     if constexpr (FIRST) {
-        info = in.info[v];
+        info = first_info = in.info[v];
         in.load_ids(v, id, ring_in_rows(info) ? 0 : ring_ids(info));
-    } else {
+        k = ring_in_rows(info) ? rows_length(info) : 0;
+        is_long = here && k > ROW_SMALL;
+    }
+    if (FIRST && hopeless) return;  // (all workgroups)
+    u32 x[RING_MAX], y[RING_MAX], kept = 0;  // a short ring's first and second corners; of its facets or a row's, those that stay
+    bool backwards = false;
+    if constexpr (!FIRST) {
         // the facets of the two it was made of, in the new numbering, without those whose corners have met
-        const u64 mine = half ? two_info.y : two_info.x, theirs = half ? two_info.x : two_info.y;
-        const bool short_rings = !ring_in_rows(mine) && !ring_in_rows(theirs);
-        u32 x[RING_MAX], y[RING_MAX];
+        const u64 mine = half ? two_info.y : two_info.x;
+        const bool is_short = !ring_in_rows(mine);
         in.load_ids(half ? max(two.y, 0) : two.x, x, ring_in_rows(mine) ? 0 : ring_ids(mine));
         // Rings go either way round; where the vertex that follows the other one is the same in both, the second is taken backwards (else first corners are met twice).
         const u32 other = (u32)(half ? two.x : two.y);
@@ -2393,8 +2422,9 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         at = (u32)ring_second(mine, (int)at);
 #pragma unroll
         for (int j = 1; j < RING_MAX; ++j) follows = at == (u32)j ? x[j] : follows;
-        const bool backwards = half != 0 && of_pair(follows) == follows;
-        const int n_ids = short_rings ? ring_ids(mine) : 0, n_mine = short_rings ? ring_facets(mine) : 0;
+        const u32 they_follow = of_pair(follows);
+        backwards = half != 0 && they_follow == follows;
+        const int n_ids = is_short ? ring_ids(mine) : 0, n_mine = is_short ? ring_facets(mine) : 0;
 #pragma unroll
         for (int j = 0; j < RING_MAX; ++j)
             if (j < RING_ROW || j < n_ids) x[j] = (u32)vmap[j < n_ids ? x[j] : 0u];
@@ -2409,25 +2439,108 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
 #pragma unroll
         for (int j = 0; j < RING_MAX; ++j) ok |= x[j] != (u32)w && y[j] != (u32)w && x[j] != y[j] ? 1u << j : 0u;
         ok &= (1u << n_mine) - 1u;
-        const int n_ok = __popc(ok), n_other = (int)of_pair((u32)n_ok), n = n_ok + n_other;
-        u64* const facet = stage + lane / 2;  // (the pair's: in rows of 32)
+        kept = ok;
+        info = rows_info(0, 0);
+    }
+    // The facets that come from rows, up to ROW_SMALL of them.
+    const u64 row = FIRST ? info : half ? two_info.y : two_info.x;
+    const bool open = here && (ring_in_rows(row) || (!FIRST && (ring_in_rows(two_info.x) || ring_in_rows(two_info.y))));
+    const bool any_open = __any(open);
+    u64 e[FIRST ? 1 : ROW_SMALL];
+    if (any_open) {
+        const int length = open && ring_in_rows(row) ? rows_length(row) : 0;
+        is_long = max(length, (int)of_pair((u32)length)) > ROW_SMALL;
+        constexpr int EACH = ROW_SMALL / 2;
+        if constexpr (FIRST) {
+#pragma unroll
+            for (int j = 0; j < EACH; ++j)
+                if (!is_long && 2 * j + half < length) facet_of_pair[(2 * j + half) * 32] = in.rows[rows_at(row) + (u32)(2 * j + half)];
+            in_order();
+        } else {
+#pragma unroll
+            for (int j = 0; j < ROW_SMALL; ++j) e[j] = !is_long && j < length ? in.rows[rows_at(row) + (u32)j] : 0ull;
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {  // (all at once take 250 registers; in the end each is in its place again)
+                u32 a[EACH], b[EACH];
+#pragma unroll
+                for (int j = 0; j < EACH; ++j) {
+                    a[j] = (u32)vmap[(u32)e[j]];
+                    b[j] = (u32)vmap[(u32)(e[j] >> 32)];
+                }
+#pragma unroll
+                for (int j = 0; j < EACH; ++j) {
+                    e[j] = e[j + EACH];
+                    e[j + EACH] = ring_entry((int)a[j], (int)b[j]);
+                    if (!is_long && h * EACH + j < length && a[j] != (u32)w && b[j] != (u32)w && a[j] != b[j]) kept |= 1u << (h * EACH + j);
+                }
+            }
+        }
+    }
+    // The facets in the pair's place, the one lane's in front of the other's.
+    if constexpr (!FIRST) {
+        const int n_kept = __popc(kept), n_theirs = (int)of_pair((u32)n_kept), front = half ? n_theirs : 0;
+        k = n_kept + n_theirs;
+        is_long = is_long || (here && k > ROW_SMALL);
 #pragma unroll
         for (int j = 0; j < RING_MAX; ++j) {
-            const int place = (half ? n_other : 0) + __popc(ok & ((1u << j) - 1u));
-            if ((ok >> j & 1u) && place < RING_MAX)
-                facet[place * 32] = ring_entry((int)(backwards ? y[j] : x[j]), (int)(backwards ? x[j] : y[j]));
+            const int place = front + __popc(kept & ((1u << j) - 1u));
+            if (!ring_in_rows(row) && (kept >> j & 1u) && place < ROW_SMALL)
+                facet_of_pair[place * 32] = ring_entry((int)(backwards ? y[j] : x[j]), (int)(backwards ? x[j] : y[j]));
+        }
+        if (any_open) {
+#pragma unroll
+            for (int j = 0; j < ROW_SMALL; ++j) {
+                const int place = front + __popc(kept & ((1u << j) - 1u));
+                if (ring_in_rows(row) && (kept >> j & 1u) && place < ROW_SMALL) facet_of_pair[place * 32] = e[j];
+            }
         }
         in_order();
-        info = rows_info(0, 0);
-        if (short_rings && n <= RING_MAX) {
-            auto make = [&](auto size) {
-                constexpr int N = decltype(size)::value;
-                u64 e[N];
+    }
+    const bool made = here && !is_long && (!FIRST || open);  // the ring of the facets in the place
+    if constexpr (FIRST)
+        if (__any(made && k > RING_MAX)) {
+            // Where they are more than a short ring has, those that are there already (of the same two corners: a surface of two sides, say) are left out.  (Later rounds' rings
+            // are made of such.)
+            constexpr int EACH = ROW_SMALL / 2;
+            u64 e[EACH], corners[EACH];
+            u32 left = 0;
 #pragma unroll
-                for (int j = 0; j < N; ++j) e[j] = facet[j * 32];
-                info = make_ring(e, n, id);
-            };
-            if (__any(n > RING_ROW)) make(std::integral_constant<int, RING_MAX>());  // (one of the two for the wave, not one after the other)
+            for (int j = 0; j < EACH; ++j) {
+                const int i = 2 * j + half;
+                const bool there = made && i < k;
+                e[j] = facet_of_pair[i * 32];
+                const u32 p = (u32)e[j], q = (u32)(e[j] >> 32);
+                corners[j] = there ? ring_entry((int)min(p, q), (int)max(p, q)) : ~0ull;
+                left |= there ? 1u << j : 0u;
+            }
+            in_order();
+#pragma unroll
+            for (int i = 0; i < EACH; ++i) {
+                const u64 theirs = of_pair(corners[i]);
+                if (half && corners[i] == theirs) left &= ~(1u << i);
+#pragma unroll
+                for (int j = i + 1; j < EACH; ++j)
+                    if (corners[j] == theirs || corners[j] == corners[i]) left &= ~(1u << j);
+            }
+            const int n_left = __popc(left), n_theirs = (int)of_pair((u32)n_left);
+            if (made) {
+                k = n_left + n_theirs;
+#pragma unroll
+                for (int j = 0; j < EACH; ++j)
+                    if (left >> j & 1u) facet_of_pair[((half ? n_theirs : 0) + __popc(left & ((1u << j) - 1u))) * 32] = e[j];
+            }
+            in_order();
+        }
+    if (FIRST ? __any(made && k <= RING_MAX) : true) {
+        auto make = [&](auto size) {
+            constexpr int N = decltype(size)::value;
+            u64 e[N];
+#pragma unroll
+            for (int j = 0; j < N; ++j) e[j] = facet_of_pair[j * 32];
+            info = make_ring(e, k, id);
+        };
+        if (made && k <= RING_MAX) {
+            if (FIRST || __any(k > RING_ROW)) make(std::integral_constant<int, RING_MAX>());  // (one of the two for the wave, not one after the other)
             else make(std::integral_constant<int, RING_ROW>());
             if (lead && !ring_in_rows(info)) {
                 out.store_ids(w, id, ring_ids(info));
@@ -2436,11 +2549,7 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
         }
     }
     if (!FIRST || R.B > 1) __syncthreads();
-    if (FIRST && __any(hopeless)) return;
     const bool active = here && (R.B <= 1 || M.is_active(R, v)), in_rows = here && ring_in_rows(info);
-    auto neighbour = [&](int u, const VertexWords& U, int x, const VertexWords& X) -> u32 {
-        return u == x ? PAIR_NONE : cost_key(pair_cost<PLACE>(U, X, rcond_min));
-    };
     auto bid = [&](int u, u64 best) {  // the first one, on the best neighbour
         first[u] = best;
         if (best != VMIN_NONE) atomicMin(&bids[(u32)best], (best & BID_COST) | (u32)u);
@@ -2480,166 +2589,208 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
     } else if (lead && !in_rows) {
         first[v] = VMIN_NONE;
     }
-    // Rings in rows: RING_GROUP lanes a ring, the wave's lanes with such rings one group after the other.
     int n_facets = lead && !in_rows ? ring_facets(info) : 0;
-    in_order();
-    for (u64 todo = prim::ballot(lead && in_rows); todo != 0;) {
-        const int sub = lane & (RING_GROUP - 1), group = lane / RING_GROUP;
-        int owner = -1;
+    // Rings in rows of up to ROW_SMALL facets, a facet a lane, several rings at a time.
+    const u32 was_at = FIRST ? rows_at(first_info) : 0u;
+    const bool in_place = in_rows && !is_long;
+    u64 todo = prim::ballot(lead && in_place);
+    if (todo != 0) {
+        u32 at = was_at, place = 0;  // (all rings' places together)
+        int words = 0;
+        if constexpr (!FIRST) {
+            const int mine = lead && in_place ? k : 0;
+            words = mine;  // with those of the lanes in front
 #pragma unroll
-        for (int k = 0; k < 64 / RING_GROUP; ++k) {
-            if (k == group && todo) owner = __ffsll((long long)todo) - 1;
-            todo &= todo - 1;
+            for (int d = 1; d < 64; d <<= 1) {
+                const int x = __shfl_up(words, d, 64);
+                words += lane >= d ? x : 0;
+            }
+            at = (u32)(words - mine);
+            if (lane == 63) place = out.ask((u32)words);
         }
-        const int from_lane = max(owner, 0), u = __shfl(v, from_lane, 64), its_active = __shfl(active ? 1 : 0, from_lane, 64);
-        const bool on = owner >= 0, counts = on && its_active != 0;
-        const int2 pair = make_int2(__shfl(two.x, from_lane, 64), __shfl(two.y, from_lane, 64));
-        const ulonglong2 pair_info = make_ulonglong2(__shfl(two_info.x, from_lane, 64), __shfl(two_info.y, from_lane, 64));
-        u64* const facet = stage + group * ROW_MAX;
-        const u32 group_mask = (1u << RING_GROUP) - 1u;
-        const int group_lead = lane & ~(RING_GROUP - 1);
-        auto of_group = [&](bool x) -> u32 { return (u32)(prim::ballot(x) >> (group * RING_GROUP)) & group_mask; };
-        const VertexWords U = load_vertex(vrec, u);
-        int k = 0;  // facets there are
-        if constexpr (FIRST) {
-            const u64 row = __shfl(info, from_lane, 64);
-            k = on ? rows_length(row) : 0;
-            const u64* const of = in.row_of(row);
-            for (int i = sub; i < k; i += RING_GROUP) facet[i] = of[i];
-        } else {
-            const int count[2] = {on ? ring_facets(pair_info.x) : 0, on && pair.y >= 0 ? ring_facets(pair_info.y) : 0};
-            for (int i0 = 0; __any(i0 < max(count[0], count[1])); i0 += RING_GROUP) {
-                u32 a[2], b[2];
+        if (lead && in_place) n_facets = k;
+        const int sub = lane & (ROW_SMALL - 1), group = lane / ROW_SMALL;
+        for (bool first_turn = true; todo != 0; first_turn = false) {
+            int owner = -1;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    a[h] = b[h] = 0;
-                    if (i0 + sub < count[h]) in.load_facet(h ? pair.y : pair.x, h ? pair_info.y : pair_info.x, i0 + sub, a[h], b[h]);
-                }
+            for (int j = 0; j < 64 / ROW_SMALL; ++j) {
+                if (j == group && todo) owner = __ffsll((long long)todo) - 1;
+                todo &= todo - 1;
+            }
+            const int from_lane = max(owner, 0), u = __shfl(v, from_lane, 64), n_its = __shfl(k, from_lane, 64);
+            const bool ok = owner >= 0 && sub < n_its, counts = __shfl(active ? 1 : 0, from_lane, 64) != 0;
+            const u64 e = ok ? stage[sub * 32 + from_lane / 2] : ring_entry(u, u);
+            const u32 a = (u32)e, b = (u32)(e >> 32);
+            const VertexWords U = load_vertex(vrec, u), P = load_vertex(vrec, (int)a);
+            bool alone = ok && b != (u32)u;  // the second corner is no facet's first one
+            u32 other = a;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    a[h] = (u32)vmap[a[h]];
-                    b[h] = (u32)vmap[b[h]];
+            for (int j = 0; j < ROW_SMALL; ++j) {
+                alone = alone && b != other;
+                other = next_in_row(other);
+            }
+            const u64 alone_in_group = prim::ballot(alone) >> (group * ROW_SMALL) & ((1ull << ROW_SMALL) - 1ull);
+            if constexpr (!FIRST)
+                if (first_turn) {
+                    if (lane == 63) place = out.take((u32)words, place);
+                    place = (u32)__builtin_amdgcn_readlane((int)place, 63);
                 }
+            const u32 its_at = place + (u32)__shfl((int)at, from_lane, 64);
+            u32 cost_a = neighbour(u, U, (int)a, P), cost_b = PAIR_NONE;
+            if (__any(alone)) {
+                const VertexWords Q = load_vertex(vrec, alone ? (int)b : u);
+                cost_b = neighbour(u, U, alone ? (int)b : u, Q);
+            }
+            if (ok && place != ~0u) {  // (where there is no place the round will be done again by facets)
+                out.rows[its_at + (u32)sub] = e;
+                adj.rows[its_at + (u32)sub] = ((u64)cost_b << 32) | cost_a;
+            }
+            u64 best = a != (u32)u ? ((u64)cost_a << 32) | a : VMIN_NONE;
+            const u64 key_b = alone ? ((u64)cost_b << 32) | b : VMIN_NONE;
+            best = key_b < best ? key_b : best;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const bool ok = i0 + sub < count[h] && a[h] != (u32)u && b[h] != (u32)u && a[h] != b[h];
-                    const u32 in_group = of_group(ok);
-                    const int place = k + __popc(in_group & ((1u << sub) - 1u));
-                    if (ok && place < ROW_MAX) facet[place] = ring_entry((int)a[h], (int)b[h]);
-                    k += __popc(in_group);
-                }
+            for (int d = ROW_SMALL / 2; d > 0; d >>= 1) {
+                const u64 x = __shfl_xor(best, d, 64);
+                best = x < best ? x : best;
+            }
+            if (owner >= 0 && sub == 0) {
+                out.info[u] = rows_info(n_its, its_at);
+                adj.info[u] = (u64)(u32)((alone_in_group ? n_its : 0) | n_its << 8);
+                bid(u, counts ? best : VMIN_NONE);
             }
         }
-        in_order();
-        if (sub == 0) n_facets += min(k, ROW_MAX);
-        // a lane a facet, whose two corners' records are fetched while the facets are put in order
-        const u64 mine = sub < k ? facet[sub] : ring_entry(u, u);
-        const u32 mine_p = (u32)mine, mine_q = (u32)(mine >> 32);
-        const VertexWords P = load_vertex(vrec, (int)mine_p), Q = load_vertex(vrec, (int)mine_q);
-        u64 best = VMIN_NONE;
-        // A short ring after all, if the facets follow one another around the vertex (where some are wound the other way round, first corners are met twice and others not at
-        // all): a walk goes on from a vertex by a facet not yet taken that has it.  One that is stuck has come to an end of an open fan, if there is one: the
-        // second walk goes from there.
-        u32 begin = (u32)facet[0], at = begin, my_first = 0;
-        int my_step = -1, steps = 0;
-        for (int turn = 0; turn < 2 && __any(k <= RING_MAX && steps != k); ++turn) {
-            if (k <= RING_MAX && steps == k) continue;  // (this group is done)
-            begin = at;
-            my_step = -1;
-            steps = 0;
-            for (int step = 0; step < RING_MAX; ++step) {
-                const u32 has = of_group(my_step < 0 && sub < k && k <= RING_MAX && (mine_p == at || mine_q == at));
-                if (has == 0) break;
-                const int j = __ffs((int)has) - 1;
-                if (sub == j) {
-                    my_step = step;
-                    my_first = at;
-                }
-                at ^= (u32)__shfl((int)(mine_p ^ mine_q), group_lead + j, 64);
-                ++steps;
-            }
-        }
-        const int n_ids = at == begin ? k : k + 1;
-        const bool is_short = on && k > 0 && k <= RING_MAX && steps == k && n_ids <= RING_MAX;
-        // its neighbours, if in a row: the facets' first corners, and the second ones that are no facet's first
-        const int fits = counts && !is_short ? min(k, ROW_MAX) : 0;
-        int m = fits;
-        u32 only = 0;  // of the lane's facets, one in every turn
-        for (int i0 = 0, turn = 0; __any(i0 < fits); i0 += RING_GROUP, ++turn) {
-            const bool ok = i0 + sub < fits;
-            const int b = ok ? (int)(u32)(facet[i0 + sub] >> 32) : u;
-            bool is = b != u;
-            for (int j = 0; j < fits; ++j) is = is && (int)(u32)facet[j] != b;
-            only |= is ? 1u << turn : 0u;
-            m += __popc(of_group(is));
-        }
-        // rows for the facets and for the neighbours, taken together (none where there are none, or too many)
-        int n_row = !on || is_short ? 0 : sub == 0 ? (FIRST ? 0 : k) : sub == 1 ? m : 0;
-        u32 row_at = 0;
-        if (n_row > 0) row_at = (sub == 0 ? out : adj).take_row(n_row);
-        const int k_row = __shfl(n_row, group_lead, 64), m_row = __shfl(n_row, group_lead + 1, 64);
-        const u32 k_at = (u32)__shfl((int)row_at, group_lead, 64), m_at = (u32)__shfl((int)row_at, group_lead + 1, 64);
-        const u32 cost_p = neighbour(u, U, (int)mine_p, P), cost_q = neighbour(u, U, (int)mine_q, Q);
-        auto offer = [&](u32 cost, u32 x) {
-            const u64 key = ((u64)cost << 32) | x;
-            if (x != (u32)u && key < best) best = key;
+    }
+    // ... and of more, a facet a lane, one ring after the other.
+    for (todo = prim::ballot(lead && in_rows && is_long); todo != 0; todo &= todo - 1) {
+        const int from_lane = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
+        const int u = __builtin_amdgcn_readlane(v, from_lane), counts = __builtin_amdgcn_readlane(active ? 1 : 0, from_lane);
+        auto word = [&](u64 x) -> u64 {
+            return ((u64)(u32)__builtin_amdgcn_readlane((int)(x >> 32), from_lane) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)x, from_lane);
         };
-        if (is_short && my_step >= 0) {
-            constexpr u64 NEXT = 0xA987654321ull;
-            const bool p_first = my_first == mine_p;
-            auto put = [&](int place, u32 x, u32 cost) {
-                *out.place(u, place) = x;
-                if (counts) {
-                    *adj.place(u, place) = cost;
-                    offer(cost, x);
-                }
-            };
-            put(my_step, my_first, p_first ? cost_p : cost_q);
-            if (my_step == k - 1 && n_ids > k) put(k, p_first ? mine_q : mine_p, p_first ? cost_q : cost_p);
-            if (my_step == 0) out.info[u] = ring_info(n_ids, k, n_ids > k ? NEXT : NEXT & ~(15ull << (4 * (k - 1))));  // (the last one of a closed fan leads to the first vertex)
+        int source[2] = {0, 0}, count[2] = {0, 0};
+        u64 source_info[2] = {0, 0};
+        u32 at = 0;
+        if constexpr (FIRST) {
+            at = (u32)__builtin_amdgcn_readlane((int)was_at, from_lane);
+            count[0] = __builtin_amdgcn_readlane(k, from_lane);
+        } else {
+            source[0] = __builtin_amdgcn_readlane(two.x, from_lane);
+            source[1] = __builtin_amdgcn_readlane(two.y, from_lane);
+            source_info[0] = word(two_info.x);
+            source_info[1] = word(two_info.y);
+            count[0] = ring_facets(source_info[0]);
+            count[1] = source[1] >= 0 ? ring_facets(source_info[1]) : 0;
+            if (lane == 0) at = out.ask((u32)(count[0] + count[1]));
         }
-        if (__any(on && !is_short)) {
-            if constexpr (!FIRST) {
-                u64* const row = out.row(k_row, k_at);
-                for (int i = sub; i < k_row; i += RING_GROUP) row[i] = facet[i];
-                if (on && !is_short && sub == 0) out.info[u] = rows_info(k_row, k_at);
+        const VertexWords U = load_vertex(vrec, u);
+        const int n_from = count[0] + count[1];
+        int n_kept = 0;
+        u64 best = VMIN_NONE;
+        constexpr int AHEAD = 4;  // facets of a lane that are fetched together
+        u32 begin = (u32)u;       // the first corner of the first
+        bool any_alone = false;
+#pragma unroll 1
+        for (int i0 = 0; i0 < n_from; i0 += AHEAD * 64) {
+            u32 as[AHEAD], bs[AHEAD];
+#pragma unroll
+            for (int c = 0; c < AHEAD; ++c) {
+                const int i = i0 + c * 64 + lane;
+                as[c] = bs[c] = FIRST ? (u32)u : 0u;
+                if (i < n_from) {
+                    if constexpr (FIRST) {
+                        const u64 e = in.rows[at + (u32)i];
+                        as[c] = (u32)e;
+                        bs[c] = (u32)(e >> 32);
+                    } else {
+                        const bool second = i >= count[0];
+                        in.load_facet(second ? source[1] : source[0], second ? source_info[1] : source_info[0], second ? i - count[0] : i, as[c], bs[c]);
+                    }
+                }
             }
-            u64* const row = adj.row(m_row, m_at);
-            int place0 = fits;
-            for (int i0 = 0, turn = 0; __any(m_row > 0 && i0 < fits); i0 += RING_GROUP, ++turn) {
-                const int i = i0 + sub;
-                const bool ok = m_row > 0 && i < fits, is = ok && (only >> turn & 1u);
-                u32 a = mine_p, b = mine_q, cost_a = cost_p, cost_b = cost_q;
-                if (i0 > 0) {
-                    const u64 e = ok ? facet[i] : ring_entry(u, u);
-                    a = (u32)e;
-                    b = (u32)(e >> 32);
-                    const VertexWords A = load_vertex(vrec, (int)a), B = load_vertex(vrec, (int)b);
-                    cost_a = neighbour(u, U, (int)a, A);
-                    cost_b = neighbour(u, U, (int)b, B);
+            if constexpr (!FIRST)
+#pragma unroll
+                for (int c = 0; c < AHEAD; ++c) {
+                    as[c] = (u32)vmap[as[c]];
+                    bs[c] = (u32)vmap[bs[c]];
                 }
-                if (ok) {
-                    row[i] = ((u64)cost_a << 32) | a;
-                    offer(cost_a, a);
+#pragma unroll 1
+            for (int c0 = 0; c0 < AHEAD && i0 + c0 * 64 < n_from; c0 += 2) {  // (two records in flight together)
+                u32 a[2], b[2], cost_a[2], cost_b[2] = {PAIR_NONE, PAIR_NONE};
+                u64 all[2];
+                VertexWords X[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    a[h] = as[h];
+                    b[h] = bs[h];
+#pragma unroll
+                    for (int j = h + 2; j < AHEAD; j += 2) {
+                        as[j - 2] = as[j];
+                        bs[j - 2] = bs[j];
+                    }
+                    const bool ok = i0 + (c0 + h) * 64 + lane < n_from && (FIRST || (a[h] != (u32)u && b[h] != (u32)u && a[h] != b[h]));
+                    if (!ok) a[h] = b[h] = (u32)u;
+                    all[h] = prim::ballot(ok);
+                    X[h] = load_vertex(vrec, (int)a[h]);
                 }
-                const u32 more = of_group(is);
-                if (is) {
-                    row[place0 + __popc(more & ((1u << sub) - 1u))] = ((u64)cost_b << 32) | b;
-                    offer(cost_b, b);
+                if (i0 == 0 && c0 == 0) begin = (u32)__builtin_amdgcn_readlane((int)a[0], all[0] ? __ffsll((long long)all[0]) - 1 : 0);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) cost_a[h] = neighbour(u, U, (int)a[h], X[h]);
+                // second corners that the next facet does not begin with (behind the last one the first may follow)
+                bool alone[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const u64 behind = all[h] & ~((2ull << lane) - 1ull);
+                    u32 next = (u32)__shfl((int)a[h], behind ? __ffsll((long long)behind) - 1 : lane, 64);
+                    const u32 next_chunk = h == 0 && all[1] != 0 ? (u32)__builtin_amdgcn_readlane((int)a[1], __ffsll((long long)all[1]) - 1) : begin;
+                    next = behind ? next : next_chunk;
+                    alone[h] = (all[h] >> lane & 1u) != 0 && next != b[h] && b[h] != (u32)u;
                 }
-                place0 += __popc(more);
+                if (__any(alone[0] || alone[1])) {
+                    any_alone = true;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) X[h] = load_vertex(vrec, alone[h] ? (int)b[h] : u);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) cost_b[h] = neighbour(u, U, alone[h] ? (int)b[h] : u, X[h]);
+                }
+                if constexpr (!FIRST)
+                    if (i0 == 0 && c0 == 0) {
+                        if (lane == 0) at = out.take((u32)n_from, at);
+                        at = (u32)__builtin_amdgcn_readfirstlane((int)at);
+                    }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const u64 key_a = a[h] != (u32)u ? ((u64)cost_a[h] << 32) | a[h] : VMIN_NONE, key_b = alone[h] ? ((u64)cost_b[h] << 32) | b[h] : VMIN_NONE;
+                    best = key_a < best ? key_a : best;
+                    best = key_b < best ? key_b : best;
+                    if ((all[h] >> lane & 1u) != 0 && at != ~0u) {  // (where there is no place the round will be done again by facets)
+                        const u32 place = at + (u32)n_kept + prim::mask_below(all[h]);
+                        adj.rows[place] = ((u64)cost_b[h] << 32) | cost_a[h];
+                        if constexpr (!FIRST) out.rows[place] = ring_entry((int)a[h], (int)b[h]);
+                    }
+                    n_kept += (int)__popcll(all[h]);
+                }
             }
         }
 #pragma unroll
-        for (int d = RING_GROUP / 2; d > 0; d >>= 1) {
+        for (int d = 32; d > 0; d >>= 1) {
             const u64 other = __shfl_xor(best, d, 64);
             best = other < best ? other : best;
         }
-        if (on && sub == 0) {
-            if (!is_short) adj.info[u] = rows_info(m_row, m_at);
-            bid(u, best);
+        if (lane == 0) {
+            if constexpr (!FIRST) out.info[u] = rows_info(n_kept, at);
+            if (n_kept <= ROW_SMALL) adj.info[u] = (u64)(u32)((any_alone ? n_kept : 0) | n_kept << 8);
+            if (n_kept > 64) atomicMax(&st->longest[round & 1], n_kept);
+            n_facets += n_kept;
+            bid(u, counts ? best : VMIN_NONE);
         }
-        in_order();
+    }
+    if constexpr (FIRST) {  // (the places of the others have been counted when they were given out)
+        if (__any(in_rows)) {
+            int words = lead && in_rows ? k : 0;
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) words += __shfl_xor(words, d, 64);
+            if (lane == 0) atomicAdd(&out.taken[(blockIdx.x & (ROW_ARENAS - 1)) * MATCH_PAD], words);
+        }
     }
     if constexpr (!FIRST) {
 #pragma unroll
@@ -2654,20 +2805,22 @@ __global__ __launch_bounds__(RING_THREADS) void ring_costs_kernel(State* st, int
 // time; its lanes take one after the other, and with it whoever their bids drive out in turn.  Several lanes may come to go on for a vertex (one that finds its bid
 // gone, and the one that drove it out): they ask the same neighbours in the same order, and the one that finds the vertex's own bid there ends.
 constexpr int SUITOR_LOOK = 4;  // vertices of a lane that are looked at together
-__global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, State* st, RingRows ring, RingRows adj, const u64* __restrict__ first, u64* bids,
+constexpr int SUITOR_FEW = 4;   // rings in rows of a wave that all its lanes read together
+__global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, int round, State* st, RingRows ring, RingRows adj, const u64* __restrict__ first, u64* bids,
                                                        int* __restrict__ taken_next) {
     __shared__ u64 tried[prim::WAVES][64 * SUITOR_LOOK];  // the neighbour (with its cost) that has refused the vertex
     __shared__ int lost[prim::WAVES][64 * SUITOR_LOOK];
     const int t = threadIdx.x, lane = prim::lane_id(), w = prim::wave_id();
-    if (blockIdx.x == 0 && t <= ROW_ARENAS) adj.taken[t * MATCH_PAD] = taken_next[t * MATCH_PAD] = 0;  // (of the next round)
+    if (blockIdx.x == 0 && t <= ROW_ARENAS) taken_next[t * MATCH_PAD] = 0;  // (of the next round)
+    if (blockIdx.x == 0 && t == 0) st->longest[(round & 1) ^ 1] = 0;
     if (st->wide) return;
     const long long from = (long long)prim::xcd_item((int)blockIdx.x, (nv - 1) / (per * prim::WAVES) + 1) * prim::WAVES + w;
     long long at = from * per;  // the next vertex to look at
     const long long end = min(at + per, (long long)nv);
     int listed = 0, taken = 0;
     bool busy = false, fetch = false;
-    int u = 0, m = 0;
-    const u64* longer = nullptr;  // a long row
+    int u = 0, m = 0, k = 0, k_both = 0;  // a short ring's vertices; the facets of one in rows that have costs, and how many of them have two; they lie
+    u32 there_at = 0;                     // ... here
     u64 last = 0, row[ROW_LINE];
 #pragma unroll
     for (int j = 0; j < ROW_LINE; ++j) row[j] = VMIN_NONE;
@@ -2710,48 +2863,89 @@ __global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, State* s
             u32 id[RING_MAX], cost[RING_MAX];
             ring.load_ids(u, id, 0);
             adj.load_ids(u, cost, 0);
-            m = ring_ids(info);
+            const bool in_rows = ring_in_rows(info);
+            m = in_rows ? 0 : ring_ids(info);
+            k = in_rows ? rows_length(info) : 0;
+            there_at = rows_at(info);
+            k_both = k;
+            if (k > 0 && k <= ROW_SMALL) {
+                const u32 with = (u32)adj.info[u];
+                k_both = (int)(with & 255u);
+                k = (int)(with >> 8);
+            }
 #pragma unroll
             for (int j = 0; j < ROW_LINE; ++j) row[j] = ((u64)cost[j] << 32) | id[j];
-            longer = nullptr;
-            if (ring_in_rows(info)) {
-                const u64 with = adj.info[u];
-                longer = adj.row_of(with);
-                m = rows_length(with);
-                if (m > 0) load_line(row, longer);
-            }
             fetch = false;
         }
         // the best neighbour behind `last` whose bid u's betters or is (what others have bid meanwhile only makes it fewer)
         u64 want = VMIN_NONE;
-        auto consider = [&](const u64 (&x)[ROW_LINE], int i0) {
-            u64 there[ROW_LINE];
-            bool open[ROW_LINE];
+        auto consider = [&](const auto& x, int n) {
+            constexpr int N = (int)(sizeof(x) / sizeof(x[0]));
+            u64 there[N];
+            bool open[N];
 #pragma unroll
-            for (int j = 0; j < ROW_LINE; ++j) {
-                open[j] = busy && i0 + j < m && x[j] > last && (u32)(x[j] >> 32) != PAIR_NONE;
+            for (int j = 0; j < N; ++j) {
+                open[j] = busy && j < n && x[j] > last && (u32)(x[j] >> 32) != PAIR_NONE;
                 if (open[j]) there[j] = bids[(u32)x[j]];
             }
 #pragma unroll
-            for (int j = 0; j < ROW_LINE; ++j)
+            for (int j = 0; j < N; ++j)
                 if (open[j] && there[j] >= ((x[j] & BID_COST) | (u32)u) && x[j] < want) want = x[j];
         };
-        consider(row, 0);
-        for (int i0 = ROW_LINE; __any(busy && i0 < m); i0 += ROW_LINE) {
-            u64 x[ROW_LINE];
-#pragma unroll
-            for (int j = 0; j < ROW_LINE; ++j) x[j] = VMIN_NONE;
-            if (busy && i0 < m) {
-                if (longer) {
-                    load_line(x, longer + i0);
-                } else {
-                    const uint2 id = *reinterpret_cast<const uint2*>(ring.more + (size_t)u * RING_MORE);
-                    const uint2 cost = *reinterpret_cast<const uint2*>(adj.more + (size_t)u * RING_MORE);
-                    x[0] = ((u64)cost.x << 32) | id.x;
-                    x[1] = ((u64)cost.y << 32) | id.y;
-                }
+        consider(row, m);
+        if (__any(busy && m > ROW_LINE)) {
+            u64 x[2] = {VMIN_NONE, VMIN_NONE};
+            if (busy && m > ROW_LINE) {
+                const uint2 id = *reinterpret_cast<const uint2*>(ring.more + (size_t)u * RING_MORE);
+                const uint2 cost = *reinterpret_cast<const uint2*>(adj.more + (size_t)u * RING_MORE);
+                x[0] = ((u64)cost.x << 32) | id.x;
+                x[1] = ((u64)cost.y << 32) | id.y;
             }
-            consider(x, i0);
+            consider(x, m - ROW_LINE);
+        }
+        if (__any(busy && k > 0)) {
+            // Rings in rows: each lane its own, four facets at a time; the long ones, and all where only a few lanes have more than eight neighbours so, all lanes together, one ring
+            // after the other.
+            constexpr int LINE = ROW_LINE / 2;
+            const bool small = busy && k > 0 && k <= ROW_SMALL, wide = small && (k > ROW_LINE || k_both > 0);
+            const bool alone = small && !(wide && __popcll(prim::ballot(wide)) <= SUITOR_FEW);
+            const int lines = (k + LINE - 1) / LINE, n_lines = alone ? lines + (k_both + LINE - 1) / LINE : 0;
+#pragma unroll 1
+            for (int l = 0; __any(l < n_lines); ++l) {
+                u64 x[LINE];
+                const bool second = l >= lines;
+                const int i0 = (second ? l - lines : l) * LINE, n = l >= n_lines ? 0 : second ? k_both : k;
+#pragma unroll
+                for (int j = 0; j < LINE; ++j) {
+                    x[j] = VMIN_NONE;
+                    if (i0 + j < n) {
+                        const u64 facet = ring.rows[there_at + (u32)(i0 + j)], cost = adj.rows[there_at + (u32)(i0 + j)];
+                        x[j] = second ? (cost & BID_COST) | (facet >> 32) : (cost << 32) | (u32)facet;
+                    }
+                }
+                consider(x, LINE);
+            }
+            for (u64 todo = prim::ballot(busy && k > 0 && !alone); todo != 0; todo &= todo - 1) {
+                const int from_lane = __builtin_amdgcn_readfirstlane(__ffsll((long long)todo) - 1);
+                const int its = __builtin_amdgcn_readlane(u, from_lane), n = __builtin_amdgcn_readlane(k, from_lane);
+                const u32 its_at = (u32)__builtin_amdgcn_readlane((int)there_at, from_lane);
+                const u64 behind = ((u64)(u32)__builtin_amdgcn_readlane((int)(last >> 32), from_lane) << 32) | (u32)__builtin_amdgcn_readlane((int)(u32)last, from_lane);
+                u64 its_want = VMIN_NONE;
+#pragma unroll 1
+                for (int i = lane; i < n; i += 64) {
+                    const u64 e = ring.rows[its_at + (u32)i], cost = adj.rows[its_at + (u32)i];
+                    const u64 x[2] = {(cost << 32) | (u32)e, (cost & BID_COST) | (e >> 32)};
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        if (x[j] > behind && (u32)(x[j] >> 32) != PAIR_NONE && bids[(u32)x[j]] >= ((x[j] & BID_COST) | (u32)its) && x[j] < its_want) its_want = x[j];
+                }
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1) {
+                    const u64 other = __shfl_xor(its_want, d, 64);
+                    its_want = other < its_want ? other : its_want;
+                }
+                if (lane == from_lane) want = its_want;
+            }
         }
         if (busy) {
             if (want == VMIN_NONE) {
@@ -2834,6 +3028,7 @@ struct PairPublish {
     int* done;  // (or null) meshes with pairs are marked
     int B;
     const int* facet_slots;  // (or null: all facets are left)
+    const int* rows_taken;   // (see RingRows::taken)
     int* host_img;
     int publish_ints;
     int* host_check;
@@ -2841,7 +3036,7 @@ struct PairPublish {
 };
 __device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed = false) {
     constexpr int STATE_INTS = (int)(sizeof(State) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int)), NH = (int)(offsetof(State, nh) / sizeof(int)),
-                  MISSED = (int)(offsetof(State, missed) / sizeof(int));
+                  MISSED = (int)(offsetof(State, missed) / sizeof(int)), ROW_WORDS = (int)(offsetof(State, row_words) / sizeof(int));
     static_assert(MATCH_SLOTS == 32, "a mesh's slots fill half a wave");
     const int t = threadIdx.x, n = blockDim.x;
     const bool wide = P.st->wide != 0;
@@ -2850,16 +3045,27 @@ __device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed 
         for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
         return x;
     };
+    int words = prim::lane_id() <= ROW_ARENAS ? P.rows_taken[prim::lane_id() * MATCH_PAD] : 0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) words += __shfl_xor(words, d, 64);
     const int corners = slots_sum(P.facet_slots ? P.facet_slots[(t & (MATCH_SLOTS - 1)) * MATCH_PAD] : 0);
-    for (int i = t; i < P.B * MATCH_SLOTS; i += n) {  // (whole half waves)
-        const int sum = slots_sum(P.mslots[(size_t)i * MATCH_PAD]), b = i / MATCH_SLOTS;
-        if ((i & (MATCH_SLOTS - 1)) == 0 && !wide) {
-            P.matched[b] = sum;
-            if (P.done && sum > 0) P.done[b] = 1;
-            if (STATE_INTS + b < P.publish_ints) host_store(&P.host_img[STATE_INTS + b], sum);
+    constexpr int TOGETHER = 8;
+    const int n_slots = P.B * MATCH_SLOTS;
+    for (int i0 = t; i0 < n_slots; i0 += TOGETHER * n) {  // (whole half waves)
+        int x[TOGETHER];
+#pragma unroll
+        for (int j = 0; j < TOGETHER; ++j) x[j] = i0 + j * n < n_slots ? P.mslots[(size_t)(i0 + j * n) * MATCH_PAD] : 0;
+#pragma unroll
+        for (int j = 0; j < TOGETHER; ++j) {
+            const int i = i0 + j * n, sum = slots_sum(x[j]), b = i / MATCH_SLOTS;
+            if (i < n_slots && (i & (MATCH_SLOTS - 1)) == 0 && !wide) {
+                P.matched[b] = sum;
+                if (P.done && sum > 0) P.done[b] = 1;
+                if (STATE_INTS + b < P.publish_ints) host_store(&P.host_img[STATE_INTS + b], sum);
+            }
         }
     }
-    for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : i == MISSED ? (missed ? 1 : 0) : reinterpret_cast<const int*>(P.st)[i]);
+    for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : i == MISSED ? (missed ? 1 : 0) : i == ROW_WORDS ? words : reinterpret_cast<const int*>(P.st)[i]);
     if (t == 0) host_store(P.host_check, P.tell.seq);
     signal_host(P.tell, t, true);
 }
@@ -3074,10 +3280,11 @@ __global__ __launch_bounds__(BUDGET_THREADS) void budget_release_kernel(const u3
     }
 }
 
-// Where a round by rings has found a vertex that fits no row: what the round by facets in its place takes (the facets, no bids, no count of facets).  A copy and three fills
-// instead took 10 us longer at 1.2 M vertices, 1 to 7 at 115 k and as long at 4 k.
+// Where rounds by rings end before the call does: what the round by facets that follows takes (the facets, no bids, no count of facets), and the labels in the present numbering,
+// where a contraction's map is still to be applied to them (vmap, or null).  A copy and three fills instead took 10 us longer at 1.2 M vertices, 1 to 7 at 115 k and as long at 4 k.
 __global__ __launch_bounds__(BLOCK) void facets_again_kernel(const int* __restrict__ facets, int F, int* __restrict__ fcur, int nv, u64* __restrict__ vmin0,
-                                                             u64* __restrict__ vmin1, int* __restrict__ facet_slots) {
+                                                             u64* __restrict__ vmin1, int* __restrict__ facet_slots, int* __restrict__ cid,
+                                                             const int* __restrict__ vmap, int n_labels) {
     const int g = blockIdx.x * BLOCK + threadIdx.x, stride = gridDim.x * BLOCK;
     if (g < MATCH_SLOTS) facet_slots[g * MATCH_PAD] = 0;
     for (long long f = g; f < F; f += stride) {
@@ -3087,6 +3294,8 @@ __global__ __launch_bounds__(BLOCK) void facets_again_kernel(const int* __restri
         fcur[3 * f + 2] = q.c;
     }
     for (long long v = g; v < nv; v += stride) vmin0[v] = vmin1[v] = VMIN_NONE;
+    if (vmap)
+        for (long long o = g; o < n_labels; o += stride) cid[o] = vmap[cid[o]];
 }
 
 constexpr u64 ABID_NONE = ~0ull;

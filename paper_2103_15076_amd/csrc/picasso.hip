@@ -212,7 +212,7 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->vrec[0] = cv.take<VRec>(n);
     x->vrec[1] = cv.take<VRec>(n);
     x->fcur = cv.take<int>(3 * f);
-    x->fmap = cv.take<int>(3 * f);
+    x->fmap = cv.take<int>(3 * f);  // (right behind: the two are the rows of a set of rings, too)
     x->cid = cv.take<int>(n);
     auto sort_buffers = [&](char* at) {
         Carver in;
@@ -270,34 +270,35 @@ size_t carve(picasso_ctx* c, char* base, int64_t N, int64_t F, int32_t B) {
     x->arem = cv.take<int>(b);
     x->area_ext = cv.take<u32>(b * conv::EXT_SLOTS * conv::EXT_PAD);
     // The rings lie in the sorts' buffers, which rounds by rings do not use (the neighbours' where the facets' planes have been), if these are large enough, as they are where
-    // vertices have five and a half facets or more.
-    const size_t ring_bytes = n * (sizeof(u32) * RING_ROW + sizeof(u64)), region = align_up(h * sizeof(u64)), wanted = ring_bytes + n * 4 + 4096;
+    // vertices have five and a half facets or more.  Rows lie where rounds by facets have the facets and where the incidence keys have been, with a word for every corner of
+    // the input: the input's own in the order of the incidences, later ones as RingRows hands places out.
+    const size_t ring_bytes = n * (sizeof(u32) * RING_ROW + sizeof(u64)), region = align_up(h * sizeof(u64)), wanted = ring_bytes + 512;
     const bool fits = region >= wanted;
     x->rows_taken = cv.take<int>(RINGS_TAKEN);
+    u64* const rows[3] = {reinterpret_cast<u64*>(x->fcur), x->s0_key[0], x->s0_key[1]};
     for (int i = 0; i < 3; ++i) {
         RingRows& r = i < 2 ? x->ring[i] : x->adj;
-        const size_t bytes = std::max(region, align_up(wanted));
-        char* const own = fits ? nullptr : cv.take<char>(bytes);
-        char* const at = fits ? reinterpret_cast<char*>(i == 0 ? x->key64[0] : i == 1 ? x->key64[1] : x->ekey) : own;
+        char* const own = fits ? nullptr : cv.take<char>(align_up(wanted));
         Carver in;
-        in.base = at;
+        in.base = fits ? reinterpret_cast<char*>(i == 0 ? x->key64[0] : i == 1 ? x->key64[1] : x->ekey) : own;
         r.ids = in.take<u32>(n * RING_ROW);
         r.info = in.take<u64>(n);
         r.more = !fits ? cv.take<u32>(n * RING_MORE) : nullptr;
-        r.arena_rows = (int)std::min<size_t>((bytes - in.off) / (ROW_ARENAS * ROW_SMALL * sizeof(u64)), (1u << 20) / ROW_ARENAS - 1);
-        r.small = in.take<u64>((size_t)r.arena_rows * ROW_ARENAS * ROW_SMALL);
-        r.large_rows = (int)std::min<size_t>(n / 2048 + 16, (1u << 20) - 1);
-        r.large = cv.take<u64>((size_t)r.large_rows * ROW_MAX);
-        r.taken = x->rows_taken ? x->rows_taken + i * (ROW_ARENAS + 1) * MATCH_PAD : nullptr;
+        r.rows = rows[i];
+        // (a ring of all facets fits the rest; where there are few words all are the rest, whose one counter is enough then)
+        r.arena_words = (u32)(h / 8 * 5 / ROW_ARENAS);
+        if (r.arena_words < 512) r.arena_words = 0;
+        r.rest_words = (u32)h - ROW_ARENAS * r.arena_words;
+        r.taken = x->rows_taken && i < 2 ? x->rows_taken + i * (ROW_ARENAS + 1) * MATCH_PAD : nullptr;
         r.wide = x->st ? &x->st->wide : nullptr;
     }
     if (fits) {
-        Carver costs, values;  // (the incidence keys, which are in use while the first rings are made, have room for the others' only)
+        Carver costs, values;
         values.base = reinterpret_cast<char*>(x->val32);
         x->from = values.take<int2>(n);
         x->ring[0].more = values.take<u32>(n * RING_MORE);
-        x->ring[1].more = reinterpret_cast<u32*>(x->s0_key[0]);
-        x->adj.more = reinterpret_cast<u32*>(x->s0_key[1]);
+        x->ring[1].more = reinterpret_cast<u32*>(x->vmin[2]);  // (of the selection by sub-rounds, as is the list of its edges)
+        x->adj.more = reinterpret_cast<u32*>(x->list);
         costs.base = reinterpret_cast<char*>(x->ecost);
         x->from_info = costs.take<ulonglong2>(n);
     } else {
@@ -458,7 +459,8 @@ prim::KeySort<u64> incidence_sort(picasso_ctx* c, int N, int F) {
 inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c->ekey); }
 template <bool RINGS>
 QuadricRows<RINGS> quadric_rows(picasso_ctx* c, const float* d_verts, const int* facets, int N, int F) {
-    return QuadricRows<RINGS>{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F), facets, c->ring[0]};
+    return QuadricRows<RINGS>{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F), facets, c->ring[0],
+                              c->ring[1].taken, N / (4 * ROW_ARENAS)};
 }
 
 RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
@@ -597,7 +599,7 @@ void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur
         const int tiles = (nv + RING_TILE - 1) / RING_TILE, n_labels = round_ > 1 ? N : 0;
         const int grid = prim::xcd_grid(tiles) + (n_labels + RING_LABELS - 1) / RING_LABELS;
 #define PICASSO_RING_COSTS(PLACE, FIRST)                                                                                                            \
-    ring_costs_kernel<PLACE, FIRST><<<grid, RING_THREADS, 0, s>>>(c->st, nv, c->vrec[cur_], (FIRST) ? out : in, out, c->adj, c->vmin[1], c->vmin[0], \
+    ring_costs_kernel<PLACE, FIRST><<<grid, RING_THREADS, 0, s>>>(c->st, round_, nv, c->vrec[cur_], (FIRST) ? out : in, out, c->adj, c->vmin[1], c->vmin[0], \
                                                                   round_tab(c, B, round_, cur_), c->from, c->from_info, round_map(c, true, round_ - 1), c->cid,  \
                                                                   n_labels, c->opt_rcond_min, c->nf_slots[par], c->nf_slots[par ^ 1])
         if (c->opt_placement == PLACE_INVERSE) {
@@ -613,7 +615,7 @@ void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur
         const KernelBracket timed(c, s, PICASSO_KERNEL_SUBROUND0, round_);
         const int waves = (int)std::min<long long>(((long long)nv + 63) / 64, SUITOR_WAVES), per = (int)(((long long)nv + waves - 1) / waves + 63) / 64 * 64;
         const int grid = prim::xcd_grid((int)(((long long)nv + (long long)per * prim::WAVES - 1) / ((long long)per * prim::WAVES)));
-        suitor_kernel<<<grid, BLOCK, 0, s>>>(nv, per, c->st, out, c->adj, c->vmin[1], c->vmin[0], in.taken);
+        suitor_kernel<<<grid, BLOCK, 0, s>>>(nv, per, round_, c->st, out, c->adj, c->vmin[1], c->vmin[0], in.taken);
     }
     const int chunks = prim::compact_chunks_for(nv), tiles = prim::compact_tiles(nv, chunks);
     switch (chunks) {
@@ -622,6 +624,15 @@ void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur
         default: pairs_kernel<16><<<tiles, BLOCK, 0, s>>>(sa, c->vmin[0], c->tilesum, budget);
     }
     if (tiles > prim::COMPACT_MAX_SUMMED_TILES) prim::compact_scan_sums(s, nullptr, nv, c->tilesum);
+}
+
+// Whether a call that has gone by rings goes on by facets, by the rings of the round before: where more than half a facet a vertex lies in rows (surfaces: 0.01 to 0.1; lattices of
+// two sides none, whose second side a ring leaves out), or one is so long that its wave outlasts the others.  By rings | by facets from the second round on, us a call to
+// a quarter: 500 wheels of 18 spokes 351 | 328, 20 k vertices of triangles of any three 508 | 366, a cone of 1,000 381 | 344; but 16 spheres of 4 k vertices with poles of 128 facets
+// 245 | 266, of 1.2 M with poles of 1,024 1,015 | 1,153 (by facets throughout).
+constexpr int RINGS_FEW = 2, RINGS_ALWAYS = 512, RINGS_LONG = 256, RINGS_LONG_EACH = 512;
+bool by_facets_from_here(const State* st, int nv) {
+    return (long long)RINGS_FEW * (st->row_words - RINGS_ALWAYS) > nv || std::max(st->longest[0], st->longest[1]) > RINGS_LONG + nv / RINGS_LONG_EACH;
 }
 
 // The distinct edges of a round by facets, for the statistics.  (In front of the selection the sorts' buffers are free but for the costs, which lie
@@ -1007,10 +1018,10 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     const bool by_facets = c->opt_shuffle_seed == 0 && !c->opt_absorb && !(stats && c->kt_this_call);
     // ... and of these by rings (see ring_costs_kernel) where the vertices have about six facets, as on a surface; in calls for statistics, which count the edges of
     // the facets, by facets.  By facets | by rings, us: lattices of 20 k vertices to a quarter 184 | 147, of 400 k 381 | 307, an icosphere of 164 k 385 | 249, facets permuted, 115 k
-    // 389 | 243, 2.25 M 4,179 | 2,663, vertices as well 407 | 265, 4,928 | 4,106, a flat lattice of 116 k 8,694 | 1,867.  But two-sided lattices (twelve facets a vertex,
-    // whose rings lie in rows) of 40 k 210 | 437, 20 k vertices with 60 k facets of any three of them 375 | 621.
-    // A vertex of more than 64 facets, which the host cannot see beforehand, sends its call back to rounds by facets: spheres of segments and rings, whose two poles are such,
-    // of 4 k vertices to a quarter 171 | 190, of 115 k 280 | 306, of 1.2 M 1,149 | 1,205; poles of 60, whose rings lie in long rows first, 164 | 222.
+    // 389 | 243, 2.25 M 4,179 | 2,663, vertices as well 407 | 265, 4,928 | 4,106, a flat lattice of 116 k 8,694 | 1,867.  Lattices of two sides (twelve facets a vertex, six
+    // neighbours) beside vertices of no facet, or beside a lattice, which pass the rule: 40 k to 70 % 181 | 168, 8 k among 64 k 204 | 182 to a quarter.  20 k vertices with 60 k facets of any three
+    // of them 375 | 621, and with 40 k, which pass it, 310 | 365 (to 70 %, one round, 123 | 175): nearly every vertex has more neighbours than a short ring then.
+    // Vertices of many facets, which the host cannot see beforehand: see ring_costs_kernel and by_facets_from_here.
     bool rings = by_facets && !stats && work && F > 0 && 4ll * F <= 9ll * N && N < RING_VERTICES;
     bool fresh = false;  // (see launch_facet_costs)
     const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
@@ -1041,7 +1052,18 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     bool compacted = false;   // collapsed facets have left their tiles
     bool renumbered = false;  // the facets and labels still have the numbers from before the last contraction
 
+    auto facets_again = [&](const int* map) {
+        nf_bound = F;  // (rings may hold repeated facets once)
+        facets_again_kernel<<<grid_for(std::max(std::max(nv_total, F), map ? N : 0), 4096), BLOCK, 0, s>>>(d_facets, F, c->fcur, nv_total, c->vmin[0], c->vmin[1],
+                                                                                                       c->nf_slots[round & 1], c->cid, map, N);
+    };
+
     while (work && (c->opt_max_rounds < 0 || round < c->opt_max_rounds)) {
+        if (rings && round > 0 && by_facets_from_here(hst, nv_total)) {
+            rings = false;
+            fresh = true;
+            facets_again(round > 1 ? c->vmap : nullptr);
+        }
         const int H = 3 * nf_bound;
         const int vbits = edge_vertex_bits(nv_total, H);
         MeshTab mt{B, c->voff[cur], c->target, c->active[round & 1], c->nrem, c->matched, c->mslots};
@@ -1201,7 +1223,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             BudgetList* const listed = ahead_ok && ahead_budget && chip_budget ? c->budget_list() : nullptr;
             launch_ring_round(c, s, B, round, cur, nv_total, N, sa, listed);
             const HostSignal done = next_signal(c);
-            PairPublish publish{0, c->st, c->mslots, c->matched, nullptr, B, round > 0 ? c->nf_slots[round & 1] : nullptr, c->h_pin_dev, HDR_STATE_INTS + B, sa.host_check, done};
+            PairPublish publish{0, c->st, c->mslots, c->matched, nullptr, B, round > 0 ? c->nf_slots[round & 1] : nullptr, c->ring[round & 1].taken, c->h_pin_dev, HDR_STATE_INTS + B, sa.host_check, done};
             const HostSignal nothing{nullptr, 0};
             size_t clear_ahead = 0;
             if (listed) {
@@ -1232,7 +1254,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             if (hst->wide) {  // a row did not fit: this round and those behind it by facets
                 rings = false;
                 fresh = round > 0;
-                facets_again_kernel<<<grid_for(std::max(nv_total, F), 4096), BLOCK, 0, s>>>(d_facets, F, c->fcur, nv_total, c->vmin[0], c->vmin[1], c->nf_slots[round & 1]);
+                facets_again(nullptr);
                 renumbered = was_renumbered;
                 continue;
             }

@@ -1,6 +1,6 @@
-"""Rounds by rings against the oracle, to the bit: vertices with as many facets as a short ring, its two lines and a block of rows take and one more, rings
-that outgrow their rows in a later round, facets wound both ways round, repeated and degenerate ones, batches whose meshes end at different times, equal costs, and the
-meshes on either side of the rule that takes a call to them."""
+"""Rounds by rings against the oracle, to the bit: vertices with as many facets as a short ring, a pair of lanes and a wave's turn have and one more, rings that
+grow from round to round, calls that go on by facets in a later round, facets wound both ways round, repeated (two-sided surfaces) and degenerate ones, batches whose meshes
+end at different times, equal costs, and the meshes on either side of the rule that takes a call to them."""
 import numpy as np
 import pytest
 
@@ -52,7 +52,7 @@ def wheels(spokes, closed, seed):
 @pytest.mark.parametrize("closed", [True, False])
 @pytest.mark.parametrize("spokes", [(3, 4, 5, 6, 7, 8, 9), (8, 9, 15, 16, 17), (16, 17, 31, 33, 63, 64), (65,), (64, 200)])
 def test_lengths_of_rings(pk, oracle, spokes, closed):
-    """Up to 8 facets a short ring, up to 16 in lines, up to 64 in a block; beyond, the round goes by facets."""
+    """Up to 10 facets of up to 10 vertices a short ring, up to 16 a pair of lanes' row, more a wave's."""
     V, F = wheels(spokes, closed, 11)
     ctx = pk.Context(len(V), len(F), 1, device=0)
     for keep in (0.8, 0.5, 0.1):
@@ -62,8 +62,7 @@ def test_lengths_of_rings(pk, oracle, spokes, closed):
 
 @pytest.mark.parametrize("n_rim", [24, 40, 104])
 def test_ring_of_two_hubs(pk, oracle, n_rim):
-    """A disc around two neighbouring vertices that become one: its ring grows beyond a line, a row and (104) what a row takes at most, so that the second
-    round goes by facets, on facets that are still the input's."""
+    """A disc around two neighbouring vertices that become one: its ring grows in the second round (24: from short ones to a row; 104: beyond a wave's lanes)."""
     rng = np.random.default_rng(n_rim)
     a = np.arange(n_rim) * 2 * np.pi / n_rim
     h = n_rim // 2
@@ -124,7 +123,7 @@ def test_equal_costs(pk, oracle, side):
 
 @pytest.mark.parametrize("meshes,one_is_wide", [(5, False), (5, True), (70, False)])
 def test_batches(pk, oracle, meshes, one_is_wide):
-    """Meshes that end in different rounds, one that takes no part, more than the workgroups keep in LDS; one vertex too many facets takes all of them to the other way."""
+    """Meshes that end in different rounds, one that takes no part, more than the workgroups keep in LDS; one with a vertex of a hundred facets."""
     parts = [meshgen.noisy_grid(6 + k % 9, 5 + k % 7, seed=k) for k in range(meshes)]
     if one_is_wide:
         parts[3] = wheels((100, 12), True, 3)
@@ -142,3 +141,94 @@ def test_batches(pk, oracle, meshes, one_is_wide):
         np.testing.assert_array_equal(vo[at_v:at_v + nvo[k]].view(np.uint32), ref["verts"].view(np.uint32))
         np.testing.assert_array_equal(fo[at_f:at_f + nfo[k]] - at_v, ref["facets"])
         at_v, at_f = at_v + nvo[k], at_f + nfo[k]
+
+
+def joined(parts):
+    base = np.concatenate([[0], np.cumsum([len(v) for v, _ in parts])])
+    return np.concatenate([v for v, _ in parts]).astype(np.float32), np.concatenate([f + np.int32(base[k]) for k, (_, f) in enumerate(parts)]).astype(np.int32)
+
+
+@pytest.mark.parametrize("closed", [True, False])
+@pytest.mark.parametrize("turned", [0.0, 0.4])
+@pytest.mark.parametrize("spokes", [(9, 10), (10, 11, 12), (8, 9, 10, 11)])
+def test_edge_of_short_rings(pk, oracle, spokes, closed, turned):
+    """Ten facets closed are the last short ring, ten open ones name eleven vertices, eleven are a row by their number; words nine and ten of a short ring lie beside its row.
+    With facets wound the other way round first corners are met twice, and fewer fit."""
+    V, F = wheels(spokes * 5, closed, 17)
+    flip = np.random.default_rng(5).random(len(F)) < turned
+    F[flip] = F[flip][:, ::-1]
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    for place in (pk.PICASSO_PLACE_MEAN, pk.PICASSO_PLACE_INVERSE):
+        ctx.set_placement(place, 1e-3)
+        for keep in (0.9, 0.5, 0.1):
+            target = max(1, int(len(V) * keep))
+            same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target, placement=place, rcond_min=1e-3))
+
+
+@pytest.mark.parametrize("closed", [True, False])
+@pytest.mark.parametrize("spokes", [(16, 17, 18), (63, 64, 65, 66), (127, 128, 129, 130), (255, 256, 257), (40,) * 30])
+@pytest.mark.parametrize("side", [5, 150])
+def test_long_rings(pk, oracle, spokes, closed, side):
+    """Either side of a pair's row and of a wave's turns (64 facets, 128 and 256); few vertices beside them, so that the rounds go on by facets, and many, so that they do not."""
+    V, F = joined([meshgen.noisy_grid(side, side, seed=3), wheels(spokes, closed, 23)])
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    for keep in (0.8, 0.4, 0.1):
+        target = max(1, int(len(V) * keep))
+        same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target))
+
+
+@pytest.mark.parametrize("drop", [0, 1])
+@pytest.mark.parametrize("spokes,side", [((60,) * 40, 140), ((280,), 140)])
+@pytest.mark.parametrize("two_sided", [False, True])
+def test_by_facets_in_a_later_round(pk, oracle, spokes, side, two_sided, drop):
+    """A mesh of wheels that takes no part beside a lattice that shrinks: from some round on the wheels' rings are many, or the one is long, for the vertices there are, and the
+    rounds go on by facets, with the labels that the rounds before have left.  Two-sided, the rings have every other facet left out, the facets have not."""
+    lat = meshgen.noisy_grid(side, side, seed=4)
+    if two_sided:
+        lat = (lat[0], np.concatenate([lat[1][:2000], lat[1], lat[1][:2000, ::-1]]))
+    wheel = wheels(spokes, True, 5)
+    parts = [lat, wheel, meshgen.noisy_grid(20, 20, seed=9)]
+    V, F = joined(parts)
+    nv, nf = [len(v) for v, _ in parts], [len(f) for _, f in parts]
+    target = [nv[0] // 50, nv[1], nv[2] // 3]
+    ctx = pk.Context(len(V), len(F), 3, device=0)
+    ctx.set_option(pk.PICASSO_OPT_DROP_DEGENERATED, drop)
+    got = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, target)
+    ref = oracle.decimate_batch(V, F, nv, nf, target)
+    if drop:
+        ref = oracle.drop_unreferenced(ref, ref["nv"])
+    same(got, ref)
+    assert list(got[4]) == list(ref["nv"]) and list(got[5]) == list(ref["nf"])
+
+
+@pytest.mark.parametrize("drop", [0, 1])
+@pytest.mark.parametrize("w,h,beside", [(3, 3, 20), (40, 30, 1300), (90, 90, 9000)])
+def test_two_sided_surfaces(pk, oracle, w, h, beside, drop):
+    """Lattices whose facets are there from both sides, beside vertices of no facet, which take the call to rounds by rings: twelve facets and six neighbours a vertex."""
+    rng = np.random.default_rng(w)
+    V, F = meshgen.noisy_grid(w, h, seed=w)
+    order = rng.permutation(2 * len(F))
+    for facets in (np.concatenate([F, F[:, ::-1]]), np.concatenate([F, F[:, [1, 0, 2]]])[order], np.concatenate([F, F])):
+        f = np.ascontiguousarray(facets, dtype=np.int32)
+        v = np.concatenate([V, rng.normal(size=(beside, 3))]).astype(np.float32)
+        ctx = pk.Context(len(v), len(f), 1, device=0)
+        ctx.set_option(pk.PICASSO_OPT_DROP_DEGENERATED, drop)
+        for target in (len(v) - len(V) // 4, len(v) - len(V) // 2, beside + 2):
+            ref = oracle.decimate(v, f, target)
+            same(ctx.picasso_decimate(dev(v), dev(f), target), oracle.drop_unreferenced(ref) if drop else ref)
+
+
+@pytest.mark.parametrize("n,m", [(40, 85), (3000, 6600), (20000, 40000)])
+@pytest.mark.parametrize("beside", [0, 1])
+def test_facets_of_any_vertices(pk, oracle, n, m, beside):
+    """Most vertices name more neighbours than a short ring has: the first round goes by facets when its rings have been made; beside twice as many vertices of a lattice it does not."""
+    rng = np.random.default_rng(n)
+    parts = [(rng.normal(size=(n, 3)), rng.integers(0, n, (m, 3)).astype(np.int32))]
+    if beside:
+        side = int((2 * n) ** 0.5) + 2
+        parts.append(meshgen.noisy_grid(side, side, seed=n))
+    V, F = joined(parts)
+    ctx = pk.Context(len(V), len(F), 1, device=0)
+    for keep in (0.8, 0.4, 0.1):
+        target = max(1, int(len(V) * keep))
+        same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target))
