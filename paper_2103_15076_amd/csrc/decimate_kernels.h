@@ -705,7 +705,8 @@ struct QuadricRows {
     const int* facets;
     RingRows ring;
     int* unfit;       // [ROW_ARENAS][MATCH_PAD]: vertices of few facets with more neighbours than a short ring has, as where facets are any three vertices; zero at the start
-    int unfit_limit;  // ... of a part, from which on the call goes by facets
+    int unfit_limit;  // ... of a part, beyond which the call goes by facets
+    int most_facets;  // ... as it does with a vertex of more
     template <int THREADS, int ITEMS>
     struct Lds {
         unsigned short start[THREADS / 64][QR_WINDOW];  // (within the window)
@@ -906,6 +907,7 @@ struct QuadricRows {
                             ring.info[v] = leave_ring(v, e, end - hp, [&] { return b.start + (u32)hp; });
                         } else {
                             ring.info[v] = rows_info(end - hp, b.start + (u32)hp);
+                            if (end - hp > most_facets) *ring.wide = 1;
                         }
                 }
                 if constexpr (RINGS)  // (the facets of the others, one after the other by all lanes)
@@ -2334,9 +2336,9 @@ constexpr int RING_LABELS = 4 * RING_THREADS;  // labels of one of the workgroup
 
 // Two lanes a vertex: each takes over the ring of one of the two that the vertex was made of, then evaluates every other neighbour.  Rings that stay in rows of up to ROW_SMALL facets
 // are made the same way and evaluated four at a time, a facet a lane; longer ones by the whole wave, 128 facets a turn, one ring after the other.  (Hubs of the input by workgroups of
-// their own: a cone of 4,000 facets 1,604 us for 1,650, but every first round 1 us longer.)  With the rows of 11 to 64 facets made and evaluated in one turn of four after the other and a longer one given up for rounds by facets, spheres of segments and
-// rings (us a call to a quarter, by facets | then | now): 4 k vertices with poles of 48 facets 159 | 199 | 153, of 128 166 | 188 | 173, 115 k 279 | 304 | 232, 1.2 M 1,153 | 1,211 | 1,015;
-// 20 k vertices of a lattice of two sides among 159 k 257 | 298 | 229; a cone of 4,000 facets to 70 % 1,569 | 1,587 | 1,604.
+// their own: a cone of 4,000 facets 1,604 us for 1,650, but every first round 1 us longer.  A vertex of more than a thousand sends the call to rounds by facets.)  With the rows of 11 to 64 facets made and evaluated in one turn of four after the other and a longer one given up for rounds by facets, spheres of segments and
+// rings (us a call to a quarter, by facets | then | now): 4 k vertices with poles of 48 facets 159 | 199 | 153, of 128 166 | 188 | 173, 115 k 279 | 304 | 232, 1.2 M 1,153 | 1,211 | 1,052;
+// 20 k vertices of a lattice of two sides among 159 k 257 | 298 | 229.
 // Bound by the trips from vertex to ring to records, and where rows are rare by the fetching of their code: every step of them that was unrolled, or done twice for few and for
 // many, took the 30 % of a decimated mesh's waves that have a row 2 to 4 us longer.  Four waves a SIMD: with five 10 M vertices take 503 us in the first round, 469 with four (the parts' lines push each
 // other out of the L2).

@@ -457,10 +457,13 @@ prim::KeySort<u64> incidence_sort(picasso_ctx* c, int N, int F) {
 // Where init_kernel leaves the facets' planes for S0: the edge-key array, which nothing else uses
 // before the first round's costs are computed (24 bytes per facet there, 16 needed).
 inline float4* facet_planes(picasso_ctx* c) { return reinterpret_cast<float4*>(c->ekey); }
+// A vertex of the input with more facets than this, and one for so many vertices, is evaluated by one wave for longer than rounds by facets take: cones of 1,000 facets by rings | by facets
+// when their quadrics have shown it, us to 70 %, 318 | 318, of 4,000 1,654 | 1,592, of 20,000 8,205 | 7,862.
+constexpr int RINGS_MOST = 1024, RINGS_MOST_EACH = 64;
 template <bool RINGS>
 QuadricRows<RINGS> quadric_rows(picasso_ctx* c, const float* d_verts, const int* facets, int N, int F) {
     return QuadricRows<RINGS>{c->vrec[0], d_verts, facet_planes(c), N, incidence_fbits(F), facets, c->ring[0],
-                              c->ring[1].taken, N / (4 * ROW_ARENAS)};
+                              c->ring[1].taken, N / (4 * ROW_ARENAS), RINGS_MOST + N / RINGS_MOST_EACH};
 }
 
 RoundTab round_tab(picasso_ctx* c, int B, int round_, int cur_) {
@@ -628,7 +631,7 @@ void launch_ring_round(picasso_ctx* c, hipStream_t s, int B, int round_, int cur
 
 // Whether a call that has gone by rings goes on by facets, by the rings of the round before: where more than half a facet a vertex lies in rows (surfaces: 0.01 to 0.1; lattices of
 // two sides none, whose second side a ring leaves out), or one is so long that its wave outlasts the others.  By rings | by facets from the second round on, us a call to
-// a quarter: 500 wheels of 18 spokes 351 | 328, 20 k vertices of triangles of any three 508 | 366, a cone of 1,000 381 | 344; but 16 spheres of 4 k vertices with poles of 128 facets
+// a quarter: 500 wheels of 18 spokes 351 | 328, 20 k vertices of triangles of any three 508 | 366, a cone of 1,000 381 | 354; but 16 spheres of 4 k vertices with poles of 128 facets
 // 245 | 266, of 1.2 M with poles of 1,024 1,015 | 1,153 (by facets throughout).
 constexpr int RINGS_FEW = 2, RINGS_ALWAYS = 512, RINGS_LONG = 256, RINGS_LONG_EACH = 512;
 bool by_facets_from_here(const State* st, int nv) {

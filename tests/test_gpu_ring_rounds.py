@@ -166,10 +166,10 @@ def test_edge_of_short_rings(pk, oracle, spokes, closed, turned):
 
 
 @pytest.mark.parametrize("closed", [True, False])
-@pytest.mark.parametrize("spokes", [(16, 17, 18), (63, 64, 65, 66), (127, 128, 129, 130), (255, 256, 257), (40,) * 30])
+@pytest.mark.parametrize("spokes", [(16, 17, 18), (63, 64, 65, 66), (127, 128, 129, 130), (255, 256, 257), (40,) * 30, (1023, 1100, 1400)])
 @pytest.mark.parametrize("side", [5, 150])
 def test_long_rings(pk, oracle, spokes, closed, side):
-    """Either side of a pair's row and of a wave's turns (64 facets, 128 and 256); few vertices beside them, so that the rounds go on by facets, and many, so that they do not."""
+    """Either side of a pair's row, of a wave's turns (64 facets, 128 and 256) and of what one wave takes (1,024 and one for 64 vertices); few vertices beside them, so that the rounds go on by facets, and many, so that they do not."""
     V, F = joined([meshgen.noisy_grid(side, side, seed=3), wheels(spokes, closed, 23)])
     ctx = pk.Context(len(V), len(F), 1, device=0)
     for keep in (0.8, 0.4, 0.1):
