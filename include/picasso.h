@@ -22,7 +22,9 @@
  *     it is bound to one device, which the calls make current; calls on one
  *     context must not overlap in time.  Contexts share no state: different
  *     contexts may be used from different host threads at the same time.
- *     Inputs are never modified.
+ *     Inputs are never modified, except where a decimate call's outputs are laid
+ *     over them: d_facets_out, d_verts_out and d_cluster_id may each lie over the
+ *     call's own d_verts or d_facets (not over one another).
  *   - Nothing is allocated inside the decimate calls.
  */
 #ifndef PICASSO_H

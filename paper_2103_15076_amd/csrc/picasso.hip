@@ -1025,7 +1025,14 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // neighbours) beside vertices of no facet, or beside a lattice, which pass the rule: 40 k to 70 % 181 | 168, 8 k among 64 k 204 | 182 to a quarter.  20 k vertices with 60 k facets of any three
     // of them 375 | 621, and with 40 k, which pass it, 310 | 365 (to 70 %, one round, 123 | 175): nearly every vertex has more neighbours than a short ring then.
     // Vertices of many facets, which the host cannot see beforehand: see ring_costs_kernel and by_facets_from_here.
-    bool rings = by_facets && !stats && work && F > 0 && 4ll * F <= 9ll * N && N < RING_VERTICES;
+    // Rounds by rings read the call's facets to its end, where its last kernels write: outputs laid over them (d_facets_out but for, which is written behind the last read) go by
+    // facets, which are copied first.
+    auto over_facets = [&](const void* out, size_t bytes) {
+        const uintptr_t a = (uintptr_t)out, b = (uintptr_t)d_facets;
+        return a < b + sizeof(int32_t) * 3 * (size_t)F && b < a + bytes;
+    };
+    const bool laid_over = over_facets(d_verts_out, sizeof(float) * 3 * (size_t)N) || over_facets(d_cluster_id, sizeof(int32_t) * (size_t)N);
+    bool rings = by_facets && !stats && work && F > 0 && 4ll * F <= 9ll * N && N < RING_VERTICES && !laid_over;
     bool fresh = false;  // (see launch_facet_costs)
     const bool together = work && !by_facets && F > 0 && c->opt_overlap && !tm.on && !c->kt_this_call &&
                           edge_sort(c, N, F, F, 3ll * F).half == incidence_sort(c, N, F).half;
