@@ -2971,11 +2971,11 @@ __global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, int roun
 }
 
 // Pairs that may be the budget's last one, as (cost - lo << 32) | lower vertex, for the two kernels of the budget step of a single mesh (see budget_range_kernel).
-constexpr int BUDGET_THREADS = 1024, BUDGET_LIST = 16 * BUDGET_THREADS;
+constexpr int BUDGET_THREADS = 1024, BUDGET_LIST = 32 * BUDGET_THREADS;
 struct BudgetList {
     u64 counts;  // pairs in front of the listed range (<< 32), listed ones (the list may hold less)
     u32 lo, hi;  // the range
-    u64 entry[BUDGET_LIST];
+    u64 entry[BUDGET_LIST];  // (of which there is room for all pairs of the mesh where these are fewer)
 };
 
 // The pairs that the bids come to: partners and costs by vertex, how many there are of each mesh, and per tile the vertices that survive them (as a
@@ -3079,7 +3079,8 @@ __global__ __launch_bounds__(BLOCK) void publish_pairs_kernel(PairPublish P) { p
 // In the first every workgroup finds in a sample of the costs, the same for all, the range in which the budget's last pair lies (counts of 14 bits, 32 digits an
 // octave; six standard deviations of a rank in the middle); the pairs in it are listed, those in front of it counted.
 // In the second every workgroup finds the last pair among the listed ones, dissolves what lies beyond it among its own vertices and counts who survives.  Where the
-// sample has misled, or too many costs are equal, nothing is contracted, and the host, which is told, takes the general way.
+// sample has misled, or too many costs are equal, nothing is contracted, and the host, which is told, takes the general way.  (Costs are few values: 165 k pairs of a lattice have 3,000, one of
+// them 13 k of the pairs, so the list has two of them in it now and then: 10 to 23 thousand of 165 thousand pairs, with 16 thousand places too many at every third budget.)
 // Bound by chains: a sample's trip, its counts in LDS and their scan in the first; two trips and up to three counts of 12 bits in the second (many of a scanned wall's costs
 // are equal, so that the vertices decide).  115 k vertices (a second round of 62 k, 28 k pairs): the search by one workgroup took 22 us and the count of the survivors with the
 // release 5, these two 7 and 12; 1.2 M (350 k, 160 k pairs), where the whole chip's histogram passes behind a look of the host took 46 in eight launches, 15 and 19.
@@ -3185,7 +3186,7 @@ __global__ __launch_bounds__(BUDGET_THREADS) void budget_range_kernel(const u32*
 __global__ __launch_bounds__(BUDGET_THREADS) void budget_release_kernel(const u32* __restrict__ pcost, int* __restrict__ mate, int nv, State* st,
                                                                         const int* __restrict__ mslots, const int* __restrict__ budget, int* __restrict__ tilesum,
                                                                         const BudgetList* __restrict__ L, PairPublish publish) {
-    constexpr int N_WAVES = BUDGET_THREADS / 64, EACH = BUDGET_LIST / BUDGET_THREADS, BITS = 12;
+    constexpr int N_WAVES = BUDGET_THREADS / 64, EACH = 16, AGAIN = 8, BITS = 12;  // keys that a lane keeps, and of what the list has beyond that, how many it fetches together in every turn
     static_assert(BLOCK == 4 * 64, "four waves a tile");
     static_assert(1 << BITS == 4 * BUDGET_THREADS, "four digits a lane");
     __shared__ uint4 hist4[BUDGET_THREADS];
@@ -3216,6 +3217,22 @@ __global__ __launch_bounds__(BUDGET_THREADS) void budget_release_kernel(const u3
         const u32 i = (u32)(j * BUDGET_THREADS + t);
         key[j] = i < listed ? L->entry[i] : ~0ull;
     }
+    auto each_key = [&](auto fn) {
+#pragma unroll
+        for (int j = 0; j < EACH; ++j)
+            if (j < each) fn(key[j]);
+#pragma unroll 1
+        for (int j0 = EACH; j0 < each; j0 += AGAIN) {
+            u64 more[AGAIN];
+#pragma unroll
+            for (int j = 0; j < AGAIN; ++j) {
+                const u32 i = (u32)((j0 + j) * BUDGET_THREADS + t);
+                more[j] = i < listed ? L->entry[i] : ~0ull;
+            }
+#pragma unroll
+            for (int j = 0; j < AGAIN; ++j) fn(more[j]);
+        }
+    };
     // by counts of 12 bits a time, of the costs from the highest bit that there is, then of the vertices, until 64 or less are left, which one wave ranks
     u32 want = (u32)keep - n_below, equal = listed;
     int undecided = hi == lo ? 32 - __clz(nv) : 64 - __clz((int)(hi - lo));
@@ -3225,9 +3242,7 @@ __global__ __launch_bounds__(BUDGET_THREADS) void budget_release_kernel(const u3
     __syncthreads();
     while (equal > 64u && undecided > 0) {
         const int nb = min(BITS, undecided > 32 ? undecided - 32 : undecided), shift = undecided - nb;
-#pragma unroll
-        for (int j = 0; j < EACH; ++j)
-            if (j < each) count_digit(hist, key[j] != ~0ull && (key[j] & decided) == prefix, (u32)(key[j] >> shift) & ((1u << nb) - 1u));
+        each_key([&](u64 k) { count_digit(hist, k != ~0ull && (k & decided) == prefix, (u32)(k >> shift) & ((1u << nb) - 1u)); });
         __syncthreads();
         const uint4 c4 = hist4[t];
         hist4[t] = make_uint4(0, 0, 0, 0);  // (for the next turn, behind the barriers that follow)
@@ -3249,12 +3264,12 @@ __global__ __launch_bounds__(BUDGET_THREADS) void budget_release_kernel(const u3
         undecided = shift == 32 ? 32 - __clz(nv) : shift;
         decided = ~0ull << undecided;
     }
-#pragma unroll
-    for (int j = 0; j < EACH; ++j)
-        if (key[j] != ~0ull && (key[j] & decided) == prefix) {
+    each_key([&](u64 k) {
+        if (k != ~0ull && (k & decided) == prefix) {
             const u32 p = atomicAdd(&n_few, 1u);
-            if (p < 64u) few[p] = key[j];
+            if (p < 64u) few[p] = k;
         }
+    });
     __syncthreads();
     if (t < 64) {
         const int c = (int)min(n_few, 64u);

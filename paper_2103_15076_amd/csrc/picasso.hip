@@ -773,11 +773,12 @@ int status_from_err_bits(int bits) {
 }
 
 // The budget step of a single mesh in rounds by rings goes by budget_range_kernel between these (pairs there may be at most).  Below the first the search of one workgroup takes
-// no longer and the list has no room (it lies in a word a vertex); from 160 k pairs, of which 12 to 13 k are listed, the list is full with some 200 k.  In a batch the meshes'
-// searches share the chip already (16 meshes of 32 k vertices 18 us).
+// no longer; up to the second the list holds what the sample points at, at most 18 % of the pairs of lattices and rooms.  In a batch the meshes' searches share the chip already
+// (16 meshes of 32 k vertices 18 us).
 constexpr int BUDGET_GROUPS = 255;  // workgroups that release, one a compute unit with the one that tells the host
-constexpr int BUDGET_CHIP_MIN = 1 << 13, BUDGET_CHIP_MAX = 1 << 18;
-static_assert((2 * BUDGET_CHIP_MIN + 2) * sizeof(u64) >= sizeof(BudgetList), "a word for each of its vertices (budget_list)");
+constexpr int BUDGET_CHIP_MIN = 1 << 13, BUDGET_CHIP_MAX = 180000;
+static_assert(offsetof(BudgetList, entry) + BUDGET_CHIP_MIN * sizeof(u64) <= 2 * BUDGET_CHIP_MIN * sizeof(u64), "a word for each of its vertices (budget_list): as many entries as it has pairs");
+static_assert(offsetof(BudgetList, entry) + BUDGET_LIST * sizeof(u64) <= (2 * BUDGET_LIST + 2) * sizeof(u64), "... or all");
 static_assert(2ll * BUDGET_CHIP_MAX <= (long long)BLOCK * prim::COMPACT_MAX_SUMMED_TILES, "tiles of one chunk");
 
 // Budget step: among a mesh's keys (its formed pairs, or the vertices that could join clusters by line 11) where there are more

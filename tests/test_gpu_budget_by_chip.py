@@ -39,15 +39,22 @@ def test_sizes_and_budgets(pk, oracle, w, h):
 
 
 def test_most_pairs(pk, oracle):
-    """524,288 vertices, the most that are taken, and 1,024 more."""
+    """More vertices than are taken."""
     for w in (1024, 1026):
         V, F = meshgen.noisy_grid(w, 512, seed=w)
         check(pk, oracle, V, F, [int(0.8 * len(V))])
 
 
-@pytest.mark.parametrize("w,h", [(140, 140), (220, 200)])
+@pytest.mark.parametrize("w,h", [(600, 600), (1000, 360), (600, 601)])
+def test_most_vertices(pk, oracle, w, h):
+    """360,000 vertices, the most that are taken, and 600 more; budgets in sparse and in dense stretches of the costs."""
+    V, F = meshgen.noisy_grid(w, h, seed=h)
+    check(pk, oracle, V, F, [int(f * len(V)) for f in (0.97, 0.8, 0.7, 0.62)])
+
+
+@pytest.mark.parametrize("w,h", [(140, 140), (220, 200), (300, 300)])
 def test_equal_costs(pk, oracle, w, h):
-    """8,000 to 10,000 pairs of one cost are listed and go by their vertices; 20,000 do not fit the list."""
+    """Some 10,000 and 20,000 pairs of one cost are listed and go by their vertices; 40,000 do not fit the list."""
     V, F = meshgen.noisy_grid(w, h, seed=1)
     V[:, 2] = 0
     check(pk, oracle, V, F, [int(0.9 * len(V)), int(0.7 * len(V))])
