@@ -194,6 +194,8 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  *                 round before + 80 nv (another bid word), from the third on + 8 N (labels).
  *                 By rings (ring_costs_kernel): 152 nv (record, ring, neighbours' costs, two bid words); behind the first round, which takes the rings to the new
  *                 numbering, 36 nv of the round before (its rings, the vertex map) + 176 nv, from the third on + 8 N (labels).
+ *                 By facets behind rounds by rings: 12 F + 24 nf + 4 N + 80 nv (the call's facets, the labels).  A round by rings that is done again by facets
+ *                 counts as the latter only.
  *   SUBROUND0     first grid-wide sub-round of the selection (Alg. 2 lines 3-10): 13 E read, E
  *                 written (edge states), 3 x 8 nv (bids read, next bids written, third array cleared).
  *                 By facets (select_facets_kernel): 24 nf + 32 nv (the same, and the pairs' two arrays started).

@@ -42,6 +42,9 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 constexpr int NF_ROUND_CAP = 64;  // rounds whose facet counts a call notes for the kernel-timing totals
 struct StageRec { int round, stage, e0, e1; };
 
+// How a round went: by sorted edges, by rings, by facets, by the call's facets behind rounds by rings.
+enum RoundWay : unsigned char { WAY_SORTED, WAY_RINGS, WAY_FACETS, WAY_FACETS_AGAIN };
+
 struct picasso_ctx {
     int device = 0;
     int64_t max_verts = 0, max_facets = 0;
@@ -153,6 +156,7 @@ struct picasso_ctx {
     int nf_round[NF_ROUND_CAP];  // facets, vertices, distinct edges of each round of the current call
     int nv_round[NF_ROUND_CAP];
     int ne_round[NF_ROUND_CAP];
+    unsigned char way_round[NF_ROUND_CAP];  // (see RoundWay)
     int n_rounds_noted = 0;
     StageRec st_recs[PICASSO_STATS_ROUNDS * PICASSO_ST_COUNT + 2];
 };
@@ -1070,6 +1074,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     };
 
     while (work && (c->opt_max_rounds < 0 || round < c->opt_max_rounds)) {
+        const int nrec_before = c->kt.nrec;  // (bracketed launches before this round)
         if (rings && round > 0 && by_facets_from_here(hst, nv_total)) {
             rings = false;
             fresh = true;
@@ -1081,6 +1086,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
 
         // ---- S1 (+S2): edges and costs
         tm.begin(round, PICASSO_ST_EDGES);
+        const unsigned char way = rings ? WAY_RINGS : by_facets ? (fresh ? WAY_FACETS_AGAIN : WAY_FACETS) : WAY_SORTED;
         if (rings) {  // (below: with the selection)
         } else if (by_facets) {
             const KernelBracket timed(c, s, PICASSO_KERNEL_UNIQUE_COST, round);
@@ -1266,6 +1272,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
                 rings = false;
                 fresh = round > 0;
                 facets_again(nullptr);
+                c->kt.nrec = nrec_before;  // (its launches have done nothing that counts)
                 renumbered = was_renumbered;
                 continue;
             }
@@ -1347,6 +1354,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             c->nf_round[c->n_rounds_noted] = nf_now;
             c->nv_round[c->n_rounds_noted] = nv_total;
             c->ne_round[c->n_rounds_noted] = ne_now;
+            c->way_round[c->n_rounds_noted] = way;
             ++c->n_rounds_noted;
         }
         ne_prev = ne_now;
@@ -1521,14 +1529,19 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             double bytes = 0.0;
             switch (kernel) {
                 case PICASSO_KERNEL_SORT: bytes = 4.0 * H + 4.0 * ne; break;
-                case PICASSO_KERNEL_UNIQUE_COST:
-                    if (!by_facets) bytes = 17.0 * ne + 72.0 * nv;
-                    else if (rings && rd == 0) bytes = 152.0 * nv;
-                    else if (rings) bytes = 36.0 * (double)c->nv_round[rd - 1] + 176.0 * nv + (rd > 1 ? 8.0 * (double)N : 0.0);
-                    else if (rd == 0) bytes = 24.0 * nf + 72.0 * nv;
-                    else bytes = 12.0 * (double)c->nf_round[rd - 1] + 24.0 * nf + 4.0 * (double)c->nv_round[rd - 1] + 80.0 * nv + (rd > 1 ? 8.0 * (double)N : 0.0);
+                case PICASSO_KERNEL_UNIQUE_COST: {
+                    const double nv_before = rd > 0 ? c->nv_round[rd - 1] : 0, nf_before = rd > 0 ? c->nf_round[rd - 1] : 0, labels = rd > 1 ? 8.0 * (double)N : 0.0;
+                    switch (c->way_round[rd]) {
+                        case WAY_SORTED: bytes = 17.0 * ne + 72.0 * nv; break;
+                        case WAY_RINGS: bytes = rd == 0 ? 152.0 * nv : 36.0 * nv_before + 176.0 * nv + labels; break;
+                        case WAY_FACETS_AGAIN: bytes = 12.0 * (double)F + 24.0 * nf + 4.0 * (double)N + 80.0 * nv; break;
+                        default: bytes = rd == 0 ? 24.0 * nf + 72.0 * nv : 12.0 * nf_before + 24.0 * nf + 4.0 * nv_before + 80.0 * nv + labels;
+                    }
                     break;
-                case PICASSO_KERNEL_SUBROUND0: bytes = rings ? 16.0 * nv : by_facets ? 24.0 * nf + 32.0 * nv : 14.0 * ne + 24.0 * nv; break;
+                }
+                case PICASSO_KERNEL_SUBROUND0:
+                    bytes = c->way_round[rd] == WAY_RINGS ? 16.0 * nv : c->way_round[rd] == WAY_SORTED ? 14.0 * ne + 24.0 * nv : 24.0 * nf + 32.0 * nv;
+                    break;
                 case PICASSO_KERNEL_FACET_INSERT:  // (the last round's is another kernel)
                     if (rd + 1 < c->n_rounds_noted) bytes = 24.0 * nf + 4.0 * nv + 8.0 * (double)N + 24.0 * (double)c->nv_round[rd + 1];
                     else bytes = (rings ? 12.0 * (double)F + 16.0 * nf : 28.0 * nf) + 4.0 * nv + 8.0 * (double)N + (drop ? 0.0 : 28.0 * (double)nv_total);

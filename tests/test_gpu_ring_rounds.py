@@ -178,7 +178,7 @@ def test_long_rings(pk, oracle, spokes, closed, side):
 
 
 @pytest.mark.parametrize("drop", [0, 1])
-@pytest.mark.parametrize("spokes,side", [((60,) * 40, 140), ((280,), 140)])
+@pytest.mark.parametrize("spokes,side", [((60,) * 100, 140), ((280,), 140)])
 @pytest.mark.parametrize("two_sided", [False, True])
 def test_by_facets_in_a_later_round(pk, oracle, spokes, side, two_sided, drop):
     """A mesh of wheels that takes no part beside a lattice that shrinks: from some round on the wheels' rings are many, or the one is long, for the vertices there are, and the
@@ -232,3 +232,33 @@ def test_facets_of_any_vertices(pk, oracle, n, m, beside):
     for keep in (0.8, 0.4, 0.1):
         target = max(1, int(len(V) * keep))
         same(ctx.picasso_decimate(dev(V), dev(F), target), oracle.decimate(V, F, target))
+
+
+def test_bracketed_kernels_of_every_way(pk):
+    """A launch and its bytes for every round, by the way that the round went: by rings, by facets where the first round by rings was given up, by facets from some round on."""
+    rng = np.random.default_rng(1)
+    lat, wheel = meshgen.noisy_grid(140, 140, seed=4), wheels((60,) * 100, True, 5)
+    any_three = (rng.normal(size=(3000, 3)).astype(np.float32), rng.integers(0, 3000, (6600, 3)).astype(np.int32))
+
+    def measured(parts, rounds):
+        V, F = joined(parts)
+        nv, nf = [len(v) for v, _ in parts], [len(f) for _, f in parts]
+        ctx = pk.Context(len(V), len(F), len(parts), device=0)
+        ctx.set_option(pk.PICASSO_OPT_KERNEL_TIMING, 1)
+        ctx.set_option(pk.PICASSO_OPT_MAX_ROUNDS, rounds)
+        left = ctx.picasso_decimate_batch(dev(V), dev(F), nv, nf, [max(1, nv[0] // 60)] + nv[1:])[1].shape[0]
+        got = [ctx.picasso_kernel_timing(k) for k in (pk.PICASSO_KERNEL_UNIQUE_COST, pk.PICASSO_KERNEL_SUBROUND0)]
+        return len(V), len(F), left, [g["launches"] for g in got], [g["bytes_total"] for g in got]
+
+    n, m, _, launches, nbytes = measured([lat], 1)
+    assert launches == [1, 1] and nbytes == [152 * n, 16 * n]
+    n, m, _, launches, nbytes = measured([any_three], 1)
+    assert launches == [1, 1] and nbytes == [24 * m + 72 * n, 24 * m + 32 * n]
+    n, before, by_rings = len(lat[0]) + len(wheel[0]), 0, []
+    for rounds in range(1, 8):
+        _, _, left, launches, nbytes = measured([lat, wheel], rounds)
+        assert launches == [rounds, rounds]
+        by_rings.append(nbytes[1] - before == 16 * n)
+        assert by_rings[-1] or nbytes[1] - before > 32 * n
+        n, before = left, nbytes[1]
+    assert by_rings[0] and not by_rings[-1] and by_rings == sorted(by_rings, reverse=True)
