@@ -3033,7 +3033,6 @@ struct PairPublish {
     const int* rows_taken;   // (see RingRows::taken)
     int* host_img;
     int publish_ints;
-    int* host_check;
     HostSignal tell;
 };
 __device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed = false) {
@@ -3068,7 +3067,6 @@ __device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed 
         }
     }
     for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : i == MISSED ? (missed ? 1 : 0) : i == ROW_WORDS ? words : reinterpret_cast<const int*>(P.st)[i]);
-    if (t == 0) host_store(P.host_check, P.tell.seq);
     signal_host(P.tell, t, true);
 }
 __global__ __launch_bounds__(BLOCK) void publish_pairs_kernel(PairPublish P) { publish_pairs(P); }
