@@ -384,6 +384,7 @@ def main():
         "paper_context": {"ms": 65.0, "gpu": "RTX 2080 Ti (paper's machine, its own 115,114-vertex mesh)"},
         "event_ms_per_step": round(ev_ms / args.steps, 4),
         "stage_ms": {k: round(sum(r[k] for r in sd["ms_stage"]), 4) for k in pk.binding.STAGE_NAMES},
+        "stage_ms_and_subrounds_are_of": "a call for statistics, whose rounds go by facets or sorted edges; the timed steps' rounds may go by rings",
         "roofline": roofline,
         "roofline_by_kernel": by_kernel,
         "cpu_baseline": cpu_baseline,

@@ -160,7 +160,9 @@ typedef struct picasso_stats {
                                                 alone where the round goes by facets: in no time below) */
     int32_t nsel[PICASSO_STATS_ROUNDS];      /* vertices removed in round r (pairs; + joiners of line 11) */
     int32_t subrounds[PICASSO_STATS_ROUNDS]; /* selection sub-rounds launched in round r            */
-    float ms_stage[PICASSO_STATS_ROUNDS][PICASSO_ST_COUNT];
+    float ms_stage[PICASSO_STATS_ROUNDS][PICASSO_ST_COUNT]; /* (subrounds and these are of the call
+                                                that asked for them, whose rounds go by facets or
+                                                sorted edges; without statistics it may go by rings) */
     float ms_total;                          /* whole call, hipEvents on `stream`                   */
 } picasso_stats;
 
@@ -184,7 +186,7 @@ const char* picasso_last_hip_error(picasso_ctx* ctx);
  * input sizes):
  * In a call that needs the edges' numbers (shuffle, line 11), and in one that gives statistics and whose kernels are bracketed at the
  * same time, the edges of a round are sorted; in any other one SORT does not run, and rounds go by rings (every vertex keeps its facets) on meshes of up to
- * 2.25 facets a vertex, else, and in calls for statistics, by facets (edges met once per facet that has them).
+ * 2.25 facets a vertex, else, in calls for statistics, and from a round on whose rings are many or long, by facets (edges met once per facet that has them).
  *   SORT          per-bucket kernel of the edge-key sort (Alg. 2 line 1): every key read once as a 4-byte
  *                 word, 4 H, the distinct ones written, 4 E.
  *   UNIQUE_COST   costs (Alg. 2 line 2) and first bids of the distinct edges: 4 E read + 13 E (edge key, cost

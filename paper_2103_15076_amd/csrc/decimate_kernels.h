@@ -2337,10 +2337,10 @@ constexpr int RING_LABELS = 4 * RING_THREADS;  // labels of one of the workgroup
 // Two lanes a vertex: each takes over the ring of one of the two that the vertex was made of, then evaluates every other neighbour.  Rings that stay in rows of up to ROW_SMALL facets
 // are made the same way and evaluated four at a time, a facet a lane; longer ones by the whole wave, 128 facets a turn, one ring after the other.  (Hubs of the input by workgroups of
 // their own: a cone of 4,000 facets 1,604 us for 1,650, but every first round 1 us longer.  A vertex of more than a thousand sends the call to rounds by facets.)  With the rows of 11 to 64 facets made and evaluated in one turn of four after the other and a longer one given up for rounds by facets, spheres of segments and
-// rings (us a call to a quarter, by facets | then | now): 4 k vertices with poles of 48 facets 159 | 199 | 153, of 128 166 | 188 | 173, 115 k 279 | 304 | 232, 1.2 M 1,153 | 1,211 | 1,052;
+// rings (us a call to a quarter, by facets | then | now): 4 k vertices with poles of 48 facets 159 | 199 | 153, of 128 166 | 188 | 174, 115 k 279 | 304 | 236, 1.2 M 1,153 | 1,211 | 1,052;
 // 20 k vertices of a lattice of two sides among 159 k 257 | 298 | 229.
 // Bound by the trips from vertex to ring to records, and where rows are rare by the fetching of their code: every step of them that was unrolled, or done twice for few and for
-// many, took the 30 % of a decimated mesh's waves that have a row 2 to 4 us longer.  Four waves a SIMD: with five 10 M vertices take 503 us in the first round, 469 with four (the parts' lines push each
+// many, took the 30 % of a decimated mesh's waves that have a row 2 to 4 us longer.  Four waves a SIMD: with five 10 M vertices take 482 us in the first round, 469 with four (the parts' lines push each
 // other out of the L2).
 template <int PLACE, bool FIRST>
 __global__ __launch_bounds__(RING_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4))) void ring_costs_kernel(State* st, int round, int nv, const VRec* __restrict__ vrec, RingRows in, RingRows out,

@@ -1028,7 +1028,8 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
     // the facets, by facets.  By facets | by rings, us: lattices of 20 k vertices to a quarter 184 | 147, of 400 k 381 | 307, an icosphere of 164 k 385 | 249, facets permuted, 115 k
     // 389 | 243, 2.25 M 4,179 | 2,663, vertices as well 407 | 265, 4,928 | 4,106, a flat lattice of 116 k 8,694 | 1,867.  Lattices of two sides (twelve facets a vertex, six
     // neighbours) beside vertices of no facet, or beside a lattice, which pass the rule: 40 k to 70 % 181 | 168, 8 k among 64 k 204 | 182 to a quarter.  20 k vertices with 60 k facets of any three
-    // of them 375 | 621, and with 40 k, which pass it, 310 | 365 (to 70 %, one round, 123 | 175): nearly every vertex has more neighbours than a short ring then.
+    // of them 375 | 621.  With 40 k, which pass it, nearly every vertex has more neighbours than a short ring, which the quadrics' kernel finds out, and the call goes by facets after all:
+    // 310 | 327 (to 70 %, one round, 123 | 157).
     // Vertices of many facets, which the host cannot see beforehand: see ring_costs_kernel and by_facets_from_here.
     // Rounds by rings read the call's facets to its end, where its last kernels write: outputs laid over them (d_facets_out but for, which is written behind the last read) go by
     // facets, which are copied first.
