@@ -40,7 +40,7 @@ struct State {
     int absorb_n;  // edges through which an un-paired vertex would join a pair's cluster (Alg. 2 line 11)
     int nv_kept;   // output vertices that some output facet refers to (option: degenerated vertices dropped)
     int wide;      // rounds by rings: this round goes by facets (most vertices of the input are no surface's, or there was no place left for a vertex's facets)
-    int row_words;   // ... facets of rings in rows (given to the host only)
+    int row_words;   // ... facets of the round's rings in rows: the sum of RingRows::taken
     int longest[2];  // ... of the longest one of more than 64, by the round's parity
     int missed;    // ... the budget's last pair is not among those that budget_range_kernel has listed
     // Written by every selection tail for kernels that the host queued behind it before looking
@@ -2815,6 +2815,13 @@ __global__ __launch_bounds__(BLOCK) void suitor_kernel(int nv, int per, int roun
     const int t = threadIdx.x, lane = prim::lane_id(), w = prim::wave_id();
     if (blockIdx.x == 0 && t <= ROW_ARENAS) taken_next[t * MATCH_PAD] = 0;  // (of the next round)
     if (blockIdx.x == 0 && t == 0) st->longest[(round & 1) ^ 1] = 0;
+    // The sum is made here, beside the matching: publish_pairs, which the host waits for, would take 1 us longer for it (16 meshes of 60 k vertices over four levels 1,070 us for 1,063).
+    if (blockIdx.x == 0 && w == prim::WAVES - 1) {
+        int words = lane <= ROW_ARENAS ? ring.taken[lane * MATCH_PAD] : 0;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) words += __shfl_xor(words, d, 64);
+        if (lane == 0) st->row_words = words;
+    }
     if (st->wide) return;
     const long long from = (long long)prim::xcd_item((int)blockIdx.x, (nv - 1) / (per * prim::WAVES) + 1) * prim::WAVES + w;
     long long at = from * per;  // the next vertex to look at
@@ -3030,14 +3037,13 @@ struct PairPublish {
     int* done;  // (or null) meshes with pairs are marked
     int B;
     const int* facet_slots;  // (or null: all facets are left)
-    const int* rows_taken;   // (see RingRows::taken)
     int* host_img;
     int publish_ints;
     HostSignal tell;
 };
 __device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed = false) {
     constexpr int STATE_INTS = (int)(sizeof(State) / sizeof(int)), GO0 = (int)(offsetof(State, go) / sizeof(int)), NH = (int)(offsetof(State, nh) / sizeof(int)),
-                  MISSED = (int)(offsetof(State, missed) / sizeof(int)), ROW_WORDS = (int)(offsetof(State, row_words) / sizeof(int));
+                  MISSED = (int)(offsetof(State, missed) / sizeof(int));
     static_assert(MATCH_SLOTS == 32, "a mesh's slots fill half a wave");
     const int t = threadIdx.x, n = blockDim.x;
     const bool wide = P.st->wide != 0;
@@ -3046,9 +3052,6 @@ __device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed 
         for (int d = MATCH_SLOTS / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
         return x;
     };
-    int words = prim::lane_id() <= ROW_ARENAS ? P.rows_taken[prim::lane_id() * MATCH_PAD] : 0;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) words += __shfl_xor(words, d, 64);
     const int corners = slots_sum(P.facet_slots ? P.facet_slots[(t & (MATCH_SLOTS - 1)) * MATCH_PAD] : 0);
     constexpr int TOGETHER = 8;
     const int n_slots = P.B * MATCH_SLOTS;
@@ -3058,15 +3061,17 @@ __device__ __forceinline__ void publish_pairs(const PairPublish& P, bool missed 
         for (int j = 0; j < TOGETHER; ++j) x[j] = i0 + j * n < n_slots ? P.mslots[(size_t)(i0 + j * n) * MATCH_PAD] : 0;
 #pragma unroll
         for (int j = 0; j < TOGETHER; ++j) {
-            const int i = i0 + j * n, sum = slots_sum(x[j]), b = i / MATCH_SLOTS;
-            if (i < n_slots && (i & (MATCH_SLOTS - 1)) == 0 && !wide) {
+            const int i = i0 + j * n, b = i / MATCH_SLOTS;
+            if (i >= n_slots) break;
+            const int sum = slots_sum(x[j]);
+            if ((i & (MATCH_SLOTS - 1)) == 0 && !wide) {
                 P.matched[b] = sum;
                 if (P.done && sum > 0) P.done[b] = 1;
                 if (STATE_INTS + b < P.publish_ints) host_store(&P.host_img[STATE_INTS + b], sum);
             }
         }
     }
-    for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : i == MISSED ? (missed ? 1 : 0) : i == ROW_WORDS ? words : reinterpret_cast<const int*>(P.st)[i]);
+    for (int i = t; i < GO0 && i < P.publish_ints; i += n) host_store(&P.host_img[i], i == NH ? corners : i == MISSED ? (missed ? 1 : 0) : reinterpret_cast<const int*>(P.st)[i]);
     signal_host(P.tell, t, true);
 }
 __global__ __launch_bounds__(BLOCK) void publish_pairs_kernel(PairPublish P) { publish_pairs(P); }

@@ -1241,7 +1241,7 @@ int decimate_impl(picasso_ctx* c, hipStream_t s, int B, const float* d_verts, co
             BudgetList* const listed = ahead_ok && ahead_budget && chip_budget ? c->budget_list() : nullptr;
             launch_ring_round(c, s, B, round, cur, nv_total, N, sa, listed);
             const HostSignal done = next_signal(c);
-            PairPublish publish{0, c->st, c->mslots, c->matched, nullptr, B, round > 0 ? c->nf_slots[round & 1] : nullptr, c->ring[round & 1].taken, c->h_pin_dev, HDR_STATE_INTS + B, done};
+            PairPublish publish{0, c->st, c->mslots, c->matched, nullptr, B, round > 0 ? c->nf_slots[round & 1] : nullptr, c->h_pin_dev, HDR_STATE_INTS + B, done};
             const HostSignal nothing{nullptr, 0};
             size_t clear_ahead = 0;
             if (listed) {
